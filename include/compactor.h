@@ -166,7 +166,8 @@ int compactor_srht_phi(int32_t sketch_dim, const uint8_t *signs, const int32_t *
 
 /* Bytes of device workspace that score / select / compress need for this batch. host.
  * The workspace must be 256-byte aligned; its contents are scratch (no state is kept
- * between calls).  The size depends on the number of compute units of the current HIP device
+ * between calls).  Part of it only speeds the factorisation of few heads up: a workspace that
+ * lacks no more than that part is accepted too and gives the same results.  The size depends on the number of compute units of the current HIP device
  * (it sets the number of partial Gram matrices): ask with the device current that will run the
  * call.  Where no device can be queried the size for 256 compute units (MI355X) is returned. */
 int compactor_workspace_size(const compactor_params_t *p, const compactor_request_t *reqs,

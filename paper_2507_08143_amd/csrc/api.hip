@@ -117,12 +117,16 @@ int score_tokens_for(const compactor_params_t *p, const SegTable &T, int cus) {
 
 struct GroupBytes {
   size_t partials, wt, hist1, sel, bstat, scores;   // in this order in the workspace
+  size_t shares;         // and, where the workspace has room for it, scratch that speeds up the
+                         // factorisation (the results do not depend on it)
   size_t total() const { return partials + wt + hist1 + sel + bstat + scores; }
   size_t off_wt() const { return partials; }
   size_t off_hist1() const { return off_wt() + wt; }
   size_t off_sel() const { return off_hist1() + hist1; }
   size_t off_bstat() const { return off_sel() + sel; }
   size_t off_scores() const { return off_bstat() + bstat; }
+  size_t off_shares() const { return total(); }
+  size_t wanted() const { return total() + shares; }
 };
 
 GroupBytes group_bytes_needed(const compactor_params_t *p, const SegTable &T, bool need_scores) {
@@ -130,9 +134,16 @@ GroupBytes group_bytes_needed(const compactor_params_t *p, const SegTable &T, bo
   long long rows = 0;
   for (int i = 0; i < T.nseg; ++i) rows += (long long)T.s[i].n * T.s[i].head_count;
   const int m = ks > 0 ? ks : D;
+  const int cus = compute_units();
+  const GramPlan gp = gram_plan(p, T, cus);
   GroupBytes g;
-  g.partials = align_up(((size_t)gram_plan(p, T, compute_units()).nwg + T.nheads) *
-                        GRAM_PARTIAL_FLOATS * sizeof(float));
+  g.partials = align_up(((size_t)gp.nwg + T.nheads) * GRAM_PARTIAL_FLOATS * sizeof(float));
+  // Many workgroups per head form S = Phi^T G Phi only where the heads alone do not fill the chip.
+  // Factorisation stage with / without shares on MI355X, k_s = 48, n = 2048: 8 heads 25 / 40 us,
+  // 128 heads 34 / 42, 256 heads 41 / 42 (40 against 52 us with two and more partials a head),
+  // 512 heads 61 / 55, 4096 heads 376 / 393 (k_s = 64: 662 / 583); one head of n = 131072 brings
+  // 64 partials, 27 us against 210.
+  g.shares = ks > 0 && T.nheads <= cus ? align_up(sketch_plan(T, ks, gp.tiles_per_wg).share_bytes) : 0;
   g.wt = align_up((size_t)T.nheads * W_TERMS * m * D * sizeof(uint16_t));
   g.hist1 = align_up((size_t)T.nheads * HIST1_BINS * sizeof(int));
   g.sel = select_needs_pools(T) ? align_up((size_t)select_scratch(T).ints() * sizeof(int)) : 0;
@@ -207,13 +218,14 @@ long long group_rows_of(const compactor_params_t *p) {
 }
 
 // Bytes of workspace a call needs: what its largest head group needs (groups run one after the
-// other on the stream and reuse the workspace).
+// other on the stream and reuse the workspace).  wanted: with the optional parts.
 int workspace_need(const compactor_params_t *p, const compactor_request_t *reqs, int32_t nreq,
-                   bool local_scores, size_t *bytes) {
+                   bool local_scores, bool wanted, size_t *bytes) {
   size_t need = 0;
   const int rc = for_each_group(p, reqs, nreq, group_rows_of(p), local_scores,
                                 [&](const SegTable &T, long long) {
-                                  const size_t t = group_bytes_needed(p, T, local_scores).total();
+                                  const GroupBytes gb = group_bytes_needed(p, T, local_scores);
+                                  const size_t t = wanted ? gb.wanted() : gb.total();
                                   if (t > need) need = t;
                                   return COMPACTOR_OK;
                                 });
@@ -247,11 +259,10 @@ struct Marks {
     if (rc_ != COMPACTOR_OK) return rc_; \
   } while (0)
 
-// score (+ blend) of one group.  With want_hist1 the per-pool histogram of the top 12 key bits
+// score (+ blend) of one group; gb describes the workspace.  With want_hist1 the per-pool histogram of the top 12 key bits
 // of the final scores is left at gb.off_hist1() of the workspace (for the selection).
-int enqueue_score(const compactor_params_t *p, const SegTable &T, long long rows, float *scores,
-                  int32_t *status, unsigned char *ws, hipStream_t st, bool want_hist1) {
-  const GroupBytes gb = group_bytes_needed(p, T, false);
+int enqueue_score(const compactor_params_t *p, const SegTable &T, const GroupBytes &gb, float *scores,
+                  int32_t *status, unsigned char *ws, size_t ws_bytes, hipStream_t st, bool want_hist1) {
   float *partials = reinterpret_cast<float *>(ws);
   uint16_t *wt = reinterpret_cast<uint16_t *>(ws + gb.off_wt());
   int *hist1 = want_hist1 ? reinterpret_cast<int *>(ws + gb.off_hist1()) : nullptr;
@@ -268,8 +279,9 @@ int enqueue_score(const compactor_params_t *p, const SegTable &T, long long rows
   MARK(m, COMPACTOR_STAGE_GRAM + 1);
   MARK(m, COMPACTOR_STAGE_REDUCE + 1);       // the fp64 sum of the partials is part of the next kernel
   if (p->sketch_dim > 0) {
-    HIP_TRY(launch_sketch_solve(T, p->sketch_dim, rpw, partials, p->phi, p->ridge_rel, wt, status,
-                                zero, zero_ints, st));
+    double *shares = gb.shares > 0 && ws_bytes >= gb.wanted() ? reinterpret_cast<double *>(ws + gb.off_shares()) : nullptr;
+    HIP_TRY(launch_sketch_solve(T, p->sketch_dim, rpw, sketch_plan(T, p->sketch_dim, rpw), partials, shares,
+                                p->phi, p->ridge_rel, wt, status, zero, zero_ints, st));
   } else {
     HIP_TRY(launch_exact_solve(T, rpw, partials, p->ridge_rel, wt, status, zero, zero_ints, st));
   }
@@ -331,18 +343,18 @@ int enqueue_compress(const compactor_params_t *p, const compactor_request_t *req
                      hipStream_t st) {
   const bool local_scores = scores == nullptr;
   size_t need;
-  const int rc = workspace_need(p, reqs, nreq, local_scores, &need);
+  const int rc = workspace_need(p, reqs, nreq, local_scores, false, &need);
   if (rc) return rc;
   if (!workspace || workspace_bytes < need) return COMPACTOR_EWORKSPACE;
   if (reinterpret_cast<uintptr_t>(workspace) & (WS_ALIGN - 1)) return COMPACTOR_EALIGN;
   drop_pending_error();
   unsigned char *ws = static_cast<unsigned char *>(workspace);
   return for_each_group(p, reqs, nreq, group_rows_of(p), local_scores,
-                        [&](const SegTable &T, long long rows) {
+                        [&](const SegTable &T, long long) {
     float *sc = scores;
-    const GroupBytes gb = group_bytes_needed(p, T, true);
+    const GroupBytes gb = group_bytes_needed(p, T, local_scores);
     if (local_scores) sc = reinterpret_cast<float *>(ws + gb.off_scores());
-    const int rc2 = enqueue_score(p, T, rows, sc, status, ws, st, true);
+    const int rc2 = enqueue_score(p, T, gb, sc, status, ws, workspace_bytes, st, true);
     if (rc2) return rc2;
     const Marks m{p->stage_events, st};
     int *hist1 = reinterpret_cast<int *>(ws + gb.off_hist1());
@@ -436,7 +448,7 @@ int compactor_workspace_size(const compactor_params_t *p, const compactor_reques
   rc = check_requests(reqs, nreq, 0);
   if (rc) return rc;
   // sized for the fused call that keeps its scores in the workspace, the largest user
-  return workspace_need(p, reqs, nreq, true, bytes);
+  return workspace_need(p, reqs, nreq, true, true, bytes);
 }
 
 int compactor_score(const compactor_params_t *p, const compactor_request_t *reqs, int32_t nreq,
@@ -448,7 +460,7 @@ int compactor_score(const compactor_params_t *p, const compactor_request_t *reqs
   if (rc) return rc;
   if (!scores || !status) return COMPACTOR_EINVAL;
   size_t need;
-  rc = workspace_need(p, reqs, nreq, false, &need);
+  rc = workspace_need(p, reqs, nreq, false, false, &need);
   if (rc) return rc;
   if (!workspace || workspace_bytes < need) return COMPACTOR_EWORKSPACE;
   if (reinterpret_cast<uintptr_t>(workspace) & (WS_ALIGN - 1)) return COMPACTOR_EALIGN;
@@ -456,8 +468,9 @@ int compactor_score(const compactor_params_t *p, const compactor_request_t *reqs
   unsigned char *ws = static_cast<unsigned char *>(workspace);
   hipStream_t st = static_cast<hipStream_t>(stream);
   return for_each_group(p, reqs, nreq, group_rows_of(p), false,
-                        [&](const SegTable &T, long long rows) {
-                          return enqueue_score(p, T, rows, scores, status, ws, st, false);
+                        [&](const SegTable &T, long long) {
+                          return enqueue_score(p, T, group_bytes_needed(p, T, false), scores, status, ws,
+                                               workspace_bytes, st, false);
                         });
 }
 
@@ -584,7 +597,7 @@ int compactor_compress_static(const compactor_params_t *p, const compactor_reque
   int rc = check_compress(p, reqs, nreq, kept_idx, kept_cnt, k_packed, v_packed, status);
   if (rc) return rc;
   size_t need;
-  rc = workspace_need(p, reqs, nreq, scores == nullptr, &need);
+  rc = workspace_need(p, reqs, nreq, scores == nullptr, false, &need);
   if (rc) return rc;
   if (need > STATIC_SCRATCH_BYTES) return COMPACTOR_EWORKSPACE;
   drop_pending_error();

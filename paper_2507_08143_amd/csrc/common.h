@@ -285,10 +285,17 @@ hipError_t launch_exact_solve(const SegTable &T, int tiles_per_wg, const float *
                               long long zero_ints, hipStream_t st);
 
 // Sketched mode: partial Gram blocks -> S = Phi^T G Phi + rho I -> W^T ([term][k_s][128] per
-// head) and status, in one kernel.
-hipError_t launch_sketch_solve(const SegTable &T, int ks, int tiles_per_wg, const float *partials,
-                               const float *phi, float ridge_rel, uint16_t *wt,
-                               int32_t *status, int *zero, long long zero_ints, hipStream_t st);
+// head) and status.  shares: plan.share_bytes of scratch, which lets many workgroups per head form
+// S (one launch more), or null: one workgroup per head forms it (the same bits).
+struct SketchPlan {
+  int parts;             // the partials of a head are added in this many runs
+  size_t share_bytes;
+};
+SketchPlan sketch_plan(const SegTable &T, int ks, int tiles_per_wg);
+hipError_t launch_sketch_solve(const SegTable &T, int ks, int tiles_per_wg, const SketchPlan &plan,
+                               const float *partials, double *shares, const float *phi,
+                               float ridge_rel, uint16_t *wt, int32_t *status, int *zero,
+                               long long zero_ints, hipStream_t st);
 
 // phi[128][ks] = sqrt(128/ks) * D H[cols]^T (signs, cols: host arrays, copied into the launch)
 hipError_t launch_srht_phi(int ks, const uint8_t *signs, const int32_t *cols, float *phi,

@@ -7,6 +7,8 @@
 // so that the score of a token is o_i = || W^T k_i ||^2 = k^_i^T S^{-1} k^_i, which equals
 // diag(U~ U~^T) of Algorithm 1 lines 5-6 when rho = 0.  All arithmetic here is fp64; W^T leaves
 // as a sum of bf16 planes for the MFMA score pass.
+#include <type_traits>
+
 #include "common.h"
 
 namespace cmp {
@@ -38,248 +40,345 @@ __device__ __forceinline__ float bf16_to_f32(uint16_t b) { return __uint_as_floa
 // accumulated Gram matrix resolves: the direction is dropped and the head flagged.
 constexpr double PIVOT_REL = 1.4901161193847656e-08;   // 2^-26
 
-// ---- sketched mode, one kernel: partial Gram blocks -> S -> L -> L^{-1} -> W^T ------------------
-// One workgroup (4 waves) per head; every O(n^3)-ish piece runs on the fp64 matrix cores
-// (16x16x4 MFMA: A[i][k] in lane (i = l & 15, k = l >> 4), B[k][j] in lane (j = l & 15,
-// k = l >> 4), register v of lane l of the result is D[4v + (l >> 4)][l & 15]):
-//   1. S = Phi^T G Phi, G summed in fp64 from the head's partial blocks; a wave takes 32 rows of G
-//      through T = G Phi to its share of S in registers, then the four shares are added
-//   2. blocked right-looking Cholesky of S + rho I with 16-wide panels: wave 0 factors the
-//      diagonal block in registers (the only serial part, 16 pivots) and inverts it, the panel
-//      below is L_qp = A_qp X_pp^T and the trailing blocks get A_qr -= L_qp L_rp^T
-//   3. X = L^{-1} block by block (X_qp = -X_qq sum_r L_qr X_rp), one wave per block column
-//   4. W^T = X Phi^T, split into bf16 planes
-// A pivot below PIVOT_REL of its own ridged diagonal entry is dropped: 1/L_kk := 0, which zeroes
-// column k of L, row and column k of X and row k of W^T, and flags the head.
+// All lanes of a wave's 16-lane row get the value of lane K of that row.
+template <int K>
+__device__ __forceinline__ double bcast16(double x) {
+  constexpr int ROW_NEWBCAST = 0x150;
+  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(x), ROW_NEWBCAST + K, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(x), ROW_NEWBCAST + K, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+
+// Compile-time loop: f(integral_constant<int, B>) ... f(integral_constant<int, E - 1>).
+template <int B, int E, class F>
+__device__ __forceinline__ void static_for(F &&f) {
+  if constexpr (B < E) {
+    f(std::integral_constant<int, B>{});
+    static_for<B + 1, E>(f);
+  }
+}
+
+// Stops the compiler from moving the computation of x past this point.
+__device__ __forceinline__ void computed_here(double &x) { asm volatile("" : "+v"(x)); }
+
 __device__ __forceinline__ void wave_fence() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-__device__ __forceinline__ double readlane_f64(double x, int lane) {
-  const int lo = __builtin_amdgcn_readlane(__double2loint(x), lane);
-  const int hi = __builtin_amdgcn_readlane(__double2hiint(x), lane);
-  return __hiloint2double(hi, lo);
-}
-
-// Rows 32 WV + 16t .. + 15 of G = sum of a head's partial Gram matrices, in the arrangement of
-// an fp64 MFMA A operand: g[q] of lane (l16, lq) is G[32 WV + 16t + l16][4q + lq].  G is
-// symmetric and only its upper blocks are stored, so an element left of the diagonal block is
-// read as its mirror image; in the diagonal block and right of it the 16 lanes of a row tile
-// read consecutive 16-byte pieces.  Sums are fp64, in split order, two splits in flight.
-struct PartialRows {
-  const float *src;     // the head's first partial
-  int nsplit, l16, lq;
-  int wv;               // the wave (uniform): rows 32 wv .. 32 wv + 31
-};
-__device__ __forceinline__ void fetch_partial_rows(const PartialRows &P, int sp, int t, float (&v)[32]) {
-  // float offsets inside a partial: the lane's part (one address register per arrangement) and
-  // a part that is the same for all lanes
-  const unsigned lane_up = 4 * P.l16 + P.lq;   // stored block (kb, wv): row 4(q&7) + lq, column 16t + l16
-  const unsigned lane_lo = (64 * (P.l16 >> 3) + 32 * ((P.l16 >> 2) & 1)) * 4 + (P.l16 & 3) + 4 * P.lq;
-                                               // stored block (wv, kb): row 16t + l16, column 4(q&7) + lq
-  const float *ps = P.src + (long long)sp * GRAM_PARTIAL_FLOATS;
-#pragma unroll
-  for (int kb = 0; kb < 4; ++kb) {
-    if (kb <= P.wv) {                          // uniform
-      const float *pb = ps + (upper_block(kb, P.wv) * 1024 + 64 * t);
-#pragma unroll
-      for (int u = 0; u < 8; ++u) v[8 * kb + u] = (pb + (64 * (u >> 1) + 32 * (u & 1)) * 4)[lane_up];
-    } else {
-      const float *pb = ps + (upper_block(P.wv, kb) * 1024 + 512 * t);
-#pragma unroll
-      for (int u = 0; u < 8; ++u) v[8 * kb + u] = (pb + 16 * u)[lane_lo];
-    }
-  }
-}
-// v0, v1 hold splits 0 and 1 on entry (fetched by the caller, so that they can be in flight behind
-// other work)
-__device__ __forceinline__ void sum_partial_rows(const PartialRows &P, int t, float (&v0)[32],
-                                                 float (&v1)[32], double (&g)[32]) {
-  for (int sp = 0; sp < P.nsplit; sp += 2) {
-#pragma unroll
-    for (int q = 0; q < 32; ++q) g[q] += (double)v0[q];
-    if (sp + 2 < P.nsplit) fetch_partial_rows(P, sp + 2, t, v0);
-    if (sp + 1 < P.nsplit) {
-#pragma unroll
-      for (int q = 0; q < 32; ++q) g[q] += (double)v1[q];
-      if (sp + 3 < P.nsplit) fetch_partial_rows(P, sp + 3, t, v1);
-    }
-  }
-}
-__device__ __forceinline__ void fetch_first_splits(const PartialRows &P, int t, float (&v0)[32],
-                                                   float (&v1)[32]) {
-  if (P.nsplit > 0) fetch_partial_rows(P, 0, t, v0);
-  if (P.nsplit > 1) fetch_partial_rows(P, 1, t, v1);
-}
-
-// Cholesky factor of a 16 x 16 diagonal block held one row per lane (lanes 0..15 of one wave):
-// lrow[k] = L[lane][k]; 1 / L[k][k] goes to rs[k] (LDS); returns false if a pivot was dropped.
-// The 16 pivots are one dependent chain.  What the next pivot needs of this one (column k + 1)
-// comes by a lane read; the rest of the column goes through LDS (col, 64 doubles) and is applied
-// one pivot later, behind that pivot's reciprocal square root, so no LDS round trip sits on the
-// chain.  Every element still receives its updates in pivot order.
-__device__ __forceinline__ bool chol16(double (&row)[16], double d0_mine, bool rowlane, int lane,
-                                       double *rs, double *col, double (&lrow)[16]) {
+// Inverse of the Cholesky factor of a 16 x 16 diagonal block, by one wave.  Lane i of every
+// 16-lane row holds row i of the block (row[], the lanes above 15 repeat what lanes 0..15 do) and
+// the ridged diagonal entry d0 of its row; on return x[i] of lane j is X[i][j], X = L^{-1}.  A
+// pivot that is not above PIVOT_REL d0 is dropped (row and column of X zero); returns whether
+// none was.
+// Bound: the dependent chain of 16 pivots and the 120 broadcasts; three panels take about 6 us
+// where an elimination through LDS and scalar registers, with its square root on the chain, took
+// 15.6 us (k_s = 48).  The elimination is the square-root free one (u_i the
+// column before scaling, t_i = u_i / d): what the next pivot waits for is a lane broadcast, a
+// reciprocal with two Newton steps, a product and an fma; the broadcast of u_{k+1} runs beside the
+// reciprocal and the square roots of all 16 pivots are taken at once at the end.  Broadcasts are
+// row_newbcast moves, so nothing passes through LDS or scalar registers.  The inverse takes the
+// same broadcasts in the same pass (lane j solves column j).
+__device__ __forceinline__ bool chol16_inverse(double (&row)[16], double d0, double (&x)[16]) {
+  const int l16 = threadIdx.x & 15;
   bool all_ok = true;
-  double cv[16], lk_prev = 0.0;
+  double d_mine = 0.0;
+  bool ok_mine = false;
 #pragma unroll
-  for (int k = 0; k < 16; ++k) {
-    const double piv = readlane_f64(row[k], k);
-    const double d0k = readlane_f64(d0_mine, k);
-    const bool ok = piv > PIVOT_REL * d0k && piv < 1.0e300;      // false for NaN too
-    const double r = ok ? rsqrt(piv) : 0.0;
-    all_ok &= ok;
-    if (lane == k) rs[k] = r;
-    const double lk = (rowlane && lane >= k) ? row[k] * r : 0.0;   // L[lane][k]
-    lrow[k] = lk;
-    if (k > 0) {
-#pragma unroll
-      for (int j = k + 1; j < 16; ++j) row[j] -= lk_prev * cv[j];  // pivot k - 1, cv[j] = L[j][k-1]
+  for (int i = 0; i < 16; ++i) x[i] = (i == l16) ? 1.0 : 0.0;
+  double u_prev = 0.0, t_prev = 0.0;               // column k - 1
+  static_for<0, 16>([&](auto kc) {
+    constexpr int k = decltype(kc)::value;
+    const double d = bcast16<k>(row[k]);
+    const bool ok = d > PIVOT_REL * bcast16<k>(d0) && d < 1.0e300;      // false for NaN too
+    double r = __builtin_amdgcn_rcp(d);
+    __builtin_amdgcn_sched_barrier(0);
+    // what pivot k - 1 still owes the columns behind this one, in the shadow of the reciprocal
+    if constexpr (k > 0) {
+      static_for<k, 16>([&](auto jc) {
+        constexpr int j = decltype(jc)::value;
+        const double tj = bcast16<j>(t_prev);
+        if constexpr (j > k) row[j] = fma(-tj, u_prev, row[j]);
+        x[j] = fma(-tj, x[k - 1], x[j]);
+      });
     }
-    if (k < 15) row[k + 1] -= lk * readlane_f64(lk, k + 1);        // pivot k, the column needed next
-    wave_fence();
-    col[lane] = lk;
-    wave_fence();
-#pragma unroll
-    for (int j = k + 2; j < 16; ++j) cv[j] = col[j];               // L[j][k], for the next round
-    lk_prev = lk;
-  }
+    r = fma(r, fma(-d, r, 1.0), r);
+    r = fma(r, fma(-d, r, 1.0), r);
+    if (!ok) r = 0.0;
+    all_ok &= ok;
+    if (l16 == k) {
+      d_mine = d;
+      ok_mine = ok;
+    }
+    u_prev = row[k];
+    t_prev = u_prev * r;                           // lane i: L[i][k] / L[k][k] for i > k
+    if constexpr (k < 15) row[k + 1] = fma(-bcast16<k + 1>(u_prev), t_prev, row[k + 1]);
+    // Keeps a pivot's updates with the pivot.  The compiler would otherwise collect the updates of
+    // x behind the last pivot (where x is stored) and hold all 120 broadcasts for them.
+    static_for<k, 16>([&](auto jc) { computed_here(x[decltype(jc)::value]); });
+    __builtin_amdgcn_sched_barrier(0);
+  });
+  const double rs = ok_mine ? rsqrt(d_mine) : 0.0;
+  static_for<0, 16>([&](auto ic) {
+    constexpr int i = decltype(ic)::value;
+    const double ri = bcast16<i>(rs);
+    x[i] = ri == 0.0 ? 0.0 : x[i] * ri;
+  });
   return all_ok;
 }
 
+// ---- sketched mode: partial Gram blocks -> S -> L -> L^{-1} -> W^T ------------------------------
+// Every O(n^3)-ish piece runs on the fp64 matrix cores (16x16x4 MFMA: A[i][k] in lane (i = l & 15,
+// k = l >> 4), B[k][j] in lane (j = l & 15, k = l >> 4), register v of lane l of the result is
+// D[4v + (l >> 4)][l & 15]):
+//   1. S = Phi^T G Phi, G summed in fp64 from the head's partial blocks
+//   2. blocked right-looking Cholesky of S + rho I with 16-wide panels: wave 0 inverts the factor
+//      of the diagonal block in registers (the only serial part, 16 pivots), the panel below is
+//      L_qp = A_qp X_pp^T and the trailing blocks get A_qr -= L_qp L_rp^T
+//   3. X = L^{-1} block by block (X_qp = -X_qq sum_r L_qr X_rp), one wave per block column
+//   4. W^T = X Phi^T, split into bf16 planes
+//
+// Step 1 is linear in the blocks and in the partials of a head, so it is cut into shares: share
+// (r, w) is the contribution of stored blocks 2w and 2w + 1 of the r-th part of the head's
+// partials, w < SHARE_BLOCKS.  B = sum over blocks (I, J) of Phi_J^T G_IJ^T Phi_I, the diagonal
+// blocks halved, gives S = B + B^T.  The shares of a head are added in their order, whoever
+// computes them: with room in the workspace they are computed by workgroups of their own
+// (sketch_share_kernel) and added by the factorisation, otherwise one workgroup per head computes
+// them one after the other.  Both give the same bits.
+constexpr int SHARE_BLOCKS = 5;
 template <int M>
-__global__ __launch_bounds__(256, M > 48 ? 1 : 2) void sketch_solve_kernel(
-    const SegTable T, int tiles_per_wg, const float *__restrict__ partials,
-    const float *__restrict__ phi, float ridge_rel, uint16_t *__restrict__ wt,
-    int32_t *__restrict__ status, int *__restrict__ zero, long long zero_ints) {
-  constexpr int P = M / 16, CT = M / 16;
-  // LDS pitch in doubles.  Two workgroups fit a CU, so that the serial parts of one overlap the
-  // matrix work of the other.
+struct Share {
+  static constexpr int P = M / 16, TILES = P * (P + 1) / 2;     // lower 16 x 16 tiles of S
+  static constexpr int DOUBLES = TILES * 256;                   // thread e of tile t: t * 256 + e
+};
+
+// The stored upper block number b is block (I, J) of G.
+__device__ __forceinline__ void upper_block_pos(int b, int &I, int &J) {
+  I = (b >= 4) + (b >= 7) + (b >= 9);
+  J = b - upper_block(I, I) + I;
+}
+
+// Share w of the partials src[0 .. count): B of it, in two halves, is left in ba and bb (M rows of
+// pitch M + 1; the share is ba + bb), complete after a barrier.  A wave takes 16 columns of a
+// block: lane (l16, lq) reads rows 4lq .. 4lq + 3 and 16 + 4lq .. of column l16 with two 16-byte
+// loads per partial and holds them as A operands of T = G^T Phi_I as they are (step (h, s) of the
+// contraction takes row 16h + 4lq + s of lane group lq); T's accumulators are the B operands of
+// Phi_J^T T.  Nothing of G or T passes through LDS.
+template <int M>
+__device__ __forceinline__ void sketch_share(const float *__restrict__ src, int count, int w,
+                                             const float *__restrict__ phi, double *ba, double *bb) {
+  constexpr int CT = M / 16, SP = M + 1, FLIGHT = 8;
+  const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lq = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int b = 2 * w + (wave >> 1), half = wave & 1;
+  int I, J;
+  upper_block_pos(b, I, J);
+  const float *p = src + (b * 1024 + (32 * lq + 16 * half + l16) * 4);
+  // operands of both products from Phi, requested before the partials
+  float pi[8][CT], pj[4][CT];
+#pragma unroll
+  for (int q = 0; q < 8; ++q)
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct)
+      pi[q][ct] = phi[(32 * I + 16 * (q >> 2) + 4 * lq + (q & 3)) * M + 16 * ct + l16];
+#pragma unroll
+  for (int v = 0; v < 4; ++v)
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct)
+      pj[v][ct] = phi[(32 * J + 16 * half + 4 * v + lq) * M + 16 * ct + l16];
+  double g[8];
+#pragma unroll
+  for (int q = 0; q < 8; ++q) g[q] = 0.0;
+  int sp = 0;
+  for (; sp + FLIGHT <= count; sp += FLIGHT) {
+    float4 a[FLIGHT], c[FLIGHT];
+#pragma unroll
+    for (int u = 0; u < FLIGHT; ++u) {
+      const float *pu = p + (long long)(sp + u) * GRAM_PARTIAL_FLOATS;
+      a[u] = *reinterpret_cast<const float4 *>(pu);
+      c[u] = *reinterpret_cast<const float4 *>(pu + 512);
+    }
+#pragma unroll
+    for (int u = 0; u < FLIGHT; ++u) {
+      g[0] += a[u].x; g[1] += a[u].y; g[2] += a[u].z; g[3] += a[u].w;
+      g[4] += c[u].x; g[5] += c[u].y; g[6] += c[u].z; g[7] += c[u].w;
+    }
+  }
+  if (sp < count) {
+    float4 a[FLIGHT - 1], c[FLIGHT - 1];
+#pragma unroll
+    for (int u = 0; u < FLIGHT - 1; ++u) {
+      const bool have = sp + u < count;              // uniform
+      const float *pu = p + (long long)(sp + (have ? u : 0)) * GRAM_PARTIAL_FLOATS;
+      a[u] = c[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (have) {
+        a[u] = *reinterpret_cast<const float4 *>(pu);
+        c[u] = *reinterpret_cast<const float4 *>(pu + 512);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < FLIGHT - 1; ++u) {
+      g[0] += a[u].x; g[1] += a[u].y; g[2] += a[u].z; g[3] += a[u].w;
+      g[4] += c[u].x; g[5] += c[u].y; g[6] += c[u].z; g[7] += c[u].w;
+    }
+  }
+  f64x4 tacc[CT];
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct) tacc[ct] = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int q = 0; q < 8; ++q)
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct)
+      tacc[ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(g[q], (double)pi[q][ct], tacc[ct], 0, 0, 0);
+  const double sc = I == J ? 0.5 : 1.0;
+  f64x4 sacc[CT][CT];
+#pragma unroll
+  for (int at = 0; at < CT; ++at)
+#pragma unroll
+    for (int bt = 0; bt < CT; ++bt) sacc[at][bt] = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int v = 0; v < 4; ++v)
+#pragma unroll
+    for (int at = 0; at < CT; ++at)
+#pragma unroll
+      for (int bt = 0; bt < CT; ++bt)
+        sacc[at][bt] = __builtin_amdgcn_mfma_f64_16x16x4f64(sc * (double)pj[v][at], tacc[bt][v],
+                                                            sacc[at][bt], 0, 0, 0);
+  // (wave 0 + wave 2) into ba, (wave 1 + wave 3) into bb
+  double *dst = (wave & 1) ? bb : ba;
+  if (wave >= 2) {
+#pragma unroll
+    for (int at = 0; at < CT; ++at)
+#pragma unroll
+      for (int bt = 0; bt < CT; ++bt)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) dst[(16 * at + 4 * v + lq) * SP + 16 * bt + l16] = sacc[at][bt][v];
+  }
+  __syncthreads();
+  if (wave < 2) {
+#pragma unroll
+    for (int at = 0; at < CT; ++at)
+#pragma unroll
+      for (int bt = 0; bt < CT; ++bt)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) dst[(16 * at + 4 * v + lq) * SP + 16 * bt + l16] += sacc[at][bt][v];
+  }
+}
+
+// f(t, row, column) for the lower tiles t of S, with the element of each that this thread has.
+template <int M, class F>
+__device__ __forceinline__ void for_lower_tiles(F &&f) {
+  const int r = threadIdx.x >> 4, c = threadIdx.x & 15;
+  int t = 0;
+#pragma unroll
+  for (int a = 0; a < M / 16; ++a)
+#pragma unroll
+    for (int b = 0; b <= a; ++b, ++t) f(t, 16 * a + r, 16 * b + c);
+}
+
+// Part r of `parts` of a head's nsplit partials.
+__device__ __forceinline__ void split_part(int nsplit, int parts, int r, int &first, int &count) {
+  const int per = (nsplit + parts - 1) / parts;
+  first = min(nsplit, r * per);
+  count = min(nsplit, first + per) - first;
+}
+
+// One workgroup per (head, part, share).  Bound by latency: one batch of partials after the
+// other, 60 MFMAs (k_s = 48) a wave, two barriers: 7 to 10 us for 8 heads with 8 to 64 partials
+// each, where one workgroup per head took 34 (8 partials, 4-byte loads) to 185 us (64) for this
+// step.  From 256 heads on (20 us) the fp64 matrix cores count: 1200 MFMAs of 64 clocks a head.
+template <int M>
+__global__ __launch_bounds__(256, 2) void sketch_share_kernel(
+    const SegTable T, int tiles_per_wg, int parts, const float *__restrict__ partials,
+    const float *__restrict__ phi, double *__restrict__ shares, int *__restrict__ zero,
+    long long zero_ints) {
   constexpr int SP = M + 1;
-  __shared__ double region[2 * M * SP];
-  __shared__ __attribute__((aligned(16))) float PH[D * M];
-  double *Ss = region;                 // S, then L in its lower blocks
-  double *Xs = region + M * SP;        // L^{-1} (lower blocks)
-  __shared__ double d0_s[M], rs_s[M], col_s[64];
+  __shared__ double ba[M * SP], bb[M * SP];
+  const int unit = blockIdx.x / SHARE_BLOCKS, w = blockIdx.x - unit * SHARE_BLOCKS;
+  const int lhead = unit / parts, r = unit - lhead * parts;
+  int nsplit, first, count;
+  const long long pb = partial_base(T, lhead, tiles_per_wg, nsplit);
+  split_part(nsplit, parts, r, first, count);
+  sketch_share<M>(partials + (pb + first) * GRAM_PARTIAL_FLOATS, count, w, phi, ba, bb);
+  zero_slice(zero, zero_ints);   // histograms that the score and selection kernels add into
+  __syncthreads();
+  double *out = shares + (long long)blockIdx.x * Share<M>::DOUBLES;
+  for_lower_tiles<M>([&](int t, int a, int b) {
+    out[t * 256 + threadIdx.x] = (ba[a * SP + b] + bb[a * SP + b]) + (ba[b * SP + a] + bb[b * SP + a]);
+  });
+}
+
+// One workgroup (4 waves) per head, steps 2 to 4; step 1 from the shares, or from
+// the partials.
+template <int M, bool SHARES>
+__global__ __launch_bounds__(256, 2) void sketch_solve_kernel(
+    const SegTable T, int tiles_per_wg, int parts, const float *__restrict__ partials,
+    const double *__restrict__ shares, const float *__restrict__ phi, float ridge_rel,
+    uint16_t *__restrict__ wt, int32_t *__restrict__ status, int *__restrict__ zero,
+    long long zero_ints) {
+  constexpr int P = M / 16, SP = M + 1, TILES = Share<M>::TILES;
+  __shared__ double Ss[M * SP];        // S, then L in its lower blocks
+  __shared__ double Xs[M * SP];        // L^{-1} (lower blocks)
+  __shared__ double d0_s[M];
   __shared__ int flag_s;
 
   const int lhead = blockIdx.x;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l16 = lane & 15, lq = lane >> 4;
-  // Phi on its way to LDS: the loads leave first and are stored once the loads of the partial
-  // sums and the clearing stores have been issued behind them
-  constexpr int PHN = (D * M / 4 + 255) / 256;
-  float4 ph_reg[PHN];
-#pragma unroll
-  for (int i = 0; i < PHN; ++i) {
-    const int idx = tid + 256 * i;
-    ph_reg[i] = idx < D * M / 4 ? reinterpret_cast<const float4 *>(phi)[idx] : make_float4(0.f, 0.f, 0.f, 0.f);
-  }
   if (tid == 0) flag_s = 0;
 
   // ---- 1. S = Phi^T G Phi ----
-  // Wave w owns rows 32w .. 32w+31 of G.  As the A operand of T = G Phi lane (l16, lq) holds
-  // G[32w + 16t + l16][4q + lq] for t < 2, q < 32; it fetches these 64 numbers of every partial
-  // straight from the stored blocks (G is symmetric, so whichever of (row, col) and (col, row)
-  // lies in an upper block is read) and sums them in fp64 in split order.  T's accumulators
-  // are in turn B operands of S_w = Phi_w^T T_w (the rows of this wave), so G and T never pass
-  // through LDS and nothing waits on a barrier until the four S_w are added.
-  int nsplit;
-  const long long pb = partial_base(T, lhead, tiles_per_wg, nsplit);
-  constexpr int CT2 = CT * CT;
-  const int wv = __builtin_amdgcn_readfirstlane(wave);
-  const PartialRows PR{partials + pb * GRAM_PARTIAL_FLOATS, nsplit, l16, lq, wv};
-  float v0[32], v1[32];
-  fetch_first_splits(PR, 0, v0, v1);
-  zero_slice(zero, zero_ints);   // histograms that the score and selection kernels add into
+  double sum[TILES];
 #pragma unroll
-  for (int i = 0; i < PHN; ++i) {
-    const int idx = tid + 256 * i;
-    if (idx < D * M / 4) reinterpret_cast<float4 *>(PH)[idx] = ph_reg[i];
-  }
-  __syncthreads();                                // Phi is in LDS
-  // T_w = G_w Phi, one 16-row tile of G at a time: CT tiles, 32 steps each, independent chains;
-  // the first splits of the second tile are in flight during the products of the first
-  f64x4 tacc[2][CT];
+  for (int t = 0; t < TILES; ++t) sum[t] = 0.0;
+  const int nshares = parts * SHARE_BLOCKS;
+  if constexpr (SHARES) {
+    const double *in = shares + (long long)lhead * nshares * Share<M>::DOUBLES + tid;
+    for (int s0 = 0; s0 < nshares; s0 += SHARE_BLOCKS) {
+      double v[SHARE_BLOCKS][TILES];
 #pragma unroll
-  for (int t = 0; t < 2; ++t) {
-    double ga[32];
+      for (int u = 0; u < SHARE_BLOCKS; ++u)
 #pragma unroll
-    for (int q = 0; q < 32; ++q) ga[q] = 0.0;
-    sum_partial_rows(PR, t, v0, v1, ga);
-    if (t == 0) fetch_first_splits(PR, 1, v0, v1);
+        for (int t = 0; t < TILES; ++t) v[u][t] = in[(long long)(s0 + u) * Share<M>::DOUBLES + t * 256];
 #pragma unroll
-    for (int ct = 0; ct < CT; ++ct) tacc[t][ct] = f64x4{0.0, 0.0, 0.0, 0.0};
+      for (int u = 0; u < SHARE_BLOCKS; ++u)
 #pragma unroll
-    for (int q0 = 0; q0 < 32; q0 += 8) {
-      float pbv[8][CT];
-#pragma unroll
-      for (int u = 0; u < 8; ++u)
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct) pbv[u][ct] = PH[(4 * (q0 + u) + lq) * M + 16 * ct + l16];
-#pragma unroll
-      for (int u = 0; u < 8; ++u)
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct)
-          tacc[t][ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(ga[q0 + u], (double)pbv[u][ct], tacc[t][ct], 0, 0, 0);
+        for (int t = 0; t < TILES; ++t) sum[t] += v[u][t];
     }
+  } else {
+    int nsplit;
+    const long long pb = partial_base(T, lhead, tiles_per_wg, nsplit);
+#pragma unroll 1
+    for (int s = 0; s < nshares; ++s) {
+      const int r = s / SHARE_BLOCKS, w = s - r * SHARE_BLOCKS;
+      int first, count;
+      split_part(nsplit, parts, r, first, count);
+      sketch_share<M>(partials + (pb + first) * GRAM_PARTIAL_FLOATS, count, w, phi, Ss, Xs);
+      __syncthreads();
+      for_lower_tiles<M>([&](int t, int a, int b) {
+        sum[t] += (Ss[a * SP + b] + Xs[a * SP + b]) + (Ss[b * SP + a] + Xs[b * SP + a]);
+      });
+      __syncthreads();
+    }
+    zero_slice(zero, zero_ints);
   }
-  // S_w = Phi_w^T T_w: register v of T's accumulators is row 4v + lq of the tile, which is the
-  // B operand of step v
-  f64x4 sacc[CT2];
+  for_lower_tiles<M>([&](int t, int a, int b) { Ss[a * SP + b] = sum[t]; });
+  // Phi as the A operand of W = Phi X^T (step 4), on its way during the factorisation.  Row i of a
+  // 16-channel tile holds channel 4 (i & 3) + (i >> 2), so that the four result registers of a
+  // lane are four consecutive channels.
+  constexpr int KS4 = M / 4;
+  float pw[2][KS4];
 #pragma unroll
-  for (int i = 0; i < CT2; ++i) sacc[i] = f64x4{0.0, 0.0, 0.0, 0.0};
+  for (int u = 0; u < 2; ++u)
 #pragma unroll
-  for (int t = 0; t < 2; ++t) {
-    float pav[4][CT];
-#pragma unroll
-    for (int v = 0; v < 4; ++v)
-#pragma unroll
-      for (int at = 0; at < CT; ++at) pav[v][at] = PH[(32 * wv + 16 * t + 4 * v + lq) * M + 16 * at + l16];
-#pragma unroll
-    for (int v = 0; v < 4; ++v)
-#pragma unroll
-      for (int at = 0; at < CT; ++at)
-#pragma unroll
-        for (int bt = 0; bt < CT; ++bt)
-          sacc[at * CT + bt] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)pav[v][at], tacc[t][bt][v],
-                                                                    sacc[at * CT + bt], 0, 0, 0);
-  }
-  // S = (S_0 + S_2) + (S_1 + S_3), in this order whatever the waves' timing
-  auto put = [&](double *dst) {
-#pragma unroll
-    for (int at = 0; at < CT; ++at)
-#pragma unroll
-      for (int bt = 0; bt < CT; ++bt)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) dst[(16 * at + 4 * v + lq) * SP + 16 * bt + l16] = sacc[at * CT + bt][v];
-  };
-  auto add = [&](const double *src) {
-#pragma unroll
-    for (int at = 0; at < CT; ++at)
-#pragma unroll
-      for (int bt = 0; bt < CT; ++bt)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) sacc[at * CT + bt][v] += src[(16 * at + 4 * v + lq) * SP + 16 * bt + l16];
-  };
-  if (wave == 2) put(Ss);
-  if (wave == 3) put(Xs);
-  __syncthreads();
-  if (wave == 0) add(Ss);
-  if (wave == 1) add(Xs);
-  __syncthreads();
-  if (wave == 1) put(Xs);
-  __syncthreads();
-  if (wave == 0) {
-    add(Xs);
-    put(Ss);
-  }
+    for (int ks = 0; ks < KS4; ++ks)
+      pw[u][ks] = phi[(16 * (wave + 4 * u) + 4 * (l16 & 3) + (l16 >> 2)) * M + 4 * ks + lq];
   __syncthreads();
 
-  // ridge: rho = ridge_rel * trace(S) / M (every thread sums in the same order)
-  double tr = 0.0;
-  for (int a = 0; a < M; ++a) tr += Ss[a * SP + a];
+  // ridge: rho = ridge_rel * trace(S) / M (every wave sums in the same order)
+  double tr = lane < M ? Ss[lane * SP + lane] : 0.0;
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) tr += __shfl_xor(tr, d);
   const double rho = (double)ridge_rel * tr / (double)M;
   __syncthreads();
   if (tid < M) {
@@ -294,31 +393,11 @@ __global__ __launch_bounds__(256, M > 48 ? 1 : 2) void sketch_solve_kernel(
   for (int p = 0; p < P; ++p) {
     if (wave == 0) {
       const int base = 16 * p;
-      const bool rowlane = lane < 16;
-      double row[16], lrow[16];
+      double row[16], x[16];
 #pragma unroll
-      for (int j = 0; j < 16; ++j) row[j] = rowlane ? Ss[(base + lane) * SP + base + j] : 0.0;
-      const double d0_mine = rowlane ? d0_s[base + lane] : 0.0;
-      if (!chol16(row, d0_mine, rowlane, lane, rs_s + base, col_s, lrow) && lane == 0)
-        flag_s = COMPACTOR_STATUS_PIVOT;
-      if (rowlane) {
-#pragma unroll
-        for (int k = 0; k < 16; ++k) Ss[(base + lane) * SP + base + k] = lrow[k];
-      }
-      wave_fence();
-      // X_pp = L_pp^{-1}: lane j solves column j by forward substitution.  Column by column of
-      // L: as soon as x[k] is known every later row takes its term, so the dependent chain is 16
-      // steps long and not 120 (each row still adds its terms in the order k = 0, 1, ...)
-      double x[16], acc[16];
-#pragma unroll
-      for (int i = 0; i < 16; ++i) acc[i] = (i == lane) ? 1.0 : 0.0;
-#pragma unroll
-      for (int k = 0; k < 16; ++k) {
-        x[k] = acc[k] * rs_s[base + k];
-#pragma unroll
-        for (int i = k + 1; i < 16; ++i) acc[i] -= Ss[(base + i) * SP + base + k] * x[k];
-      }
-      if (rowlane) {
+      for (int j = 0; j < 16; ++j) row[j] = Ss[(base + l16) * SP + base + j];
+      if (!chol16_inverse(row, d0_s[base + l16], x) && lane == 0) flag_s = COMPACTOR_STATUS_PIVOT;
+      if (lane < 16) {
 #pragma unroll
         for (int i = 0; i < 16; ++i) Xs[(base + i) * SP + base + lane] = x[i];
       }
@@ -384,36 +463,37 @@ __global__ __launch_bounds__(256, M > 48 ? 1 : 2) void sketch_solve_kernel(
   }
   __syncthreads();
 
-  // ---- 4. W^T = X Phi^T (M x 128), lower block triangle of X only ----
+  // ---- 4. W = Phi X^T (128 x M), lower block triangle of X only; stored as W^T ----
+  // a wave takes the channel tiles wave and wave + 4 of every row block: two chains
   uint16_t *wh = wt + (size_t)lhead * (W_TERMS * M * D);
-  auto emit = [&](int mt, int ct, const f64x4 &acc) {
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int m = 16 * mt + 4 * v + lq, c = 16 * ct + l16;
-      float x = (float)acc[v];
-#pragma unroll
-      for (int tt = 0; tt < W_TERMS; ++tt) {
-        const uint16_t b = bf16_rne(x);
-        wh[(tt * M + m) * D + c] = b;
-        x -= bf16_to_f32(b);
-      }
-    }
-  };
-  // a wave takes the column tiles ct = wave and wave + 4 of every row block: two chains
 #pragma unroll
   for (int mt = 0; mt < P; ++mt) {
-    f64x4 acc0 = {0.0, 0.0, 0.0, 0.0}, acc1 = {0.0, 0.0, 0.0, 0.0};
-    const int ct0 = wave, ct1 = wave + 4;
+    f64x4 acc[2];
+    acc[0] = acc[1] = f64x4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
     for (int ks = 0; ks < 4 * (mt + 1); ++ks) {
-      const double a = Xs[(16 * mt + l16) * SP + 4 * ks + lq];
-      const double b0 = (double)PH[(16 * ct0 + l16) * M + 4 * ks + lq];
-      const double b1 = (double)PH[(16 * ct1 + l16) * M + 4 * ks + lq];
-      acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b0, acc0, 0, 0, 0);
-      acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b1, acc1, 0, 0, 0);
+      const double b = Xs[(16 * mt + l16) * SP + 4 * ks + lq];
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+        acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)pw[u][ks], b, acc[u], 0, 0, 0);
     }
-    emit(mt, ct0, acc0);
-    emit(mt, ct1, acc1);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      float x[4];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) x[v] = (float)acc[u][v];
+#pragma unroll
+      for (int tt = 0; tt < W_TERMS; ++tt) {
+        uint16_t b[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          b[v] = bf16_rne(x[v]);
+          x[v] -= bf16_to_f32(b[v]);
+        }
+        *reinterpret_cast<uint2 *>(&wh[(tt * M + 16 * mt + l16) * D + 16 * (wave + 4 * u) + 4 * lq]) =
+            make_uint2((unsigned)b[0] | (unsigned)b[1] << 16, (unsigned)b[2] | (unsigned)b[3] << 16);
+      }
+    }
   }
   if (tid == 0) {
     const Where w = locate_head(T, lhead);
@@ -434,7 +514,7 @@ __global__ __launch_bounds__(256) void exact_solve_kernel(
   constexpr int M = D, P = M / 16, SP = M + 1;
   __shared__ double Ss[M * SP];
   __shared__ double Xd[P][16][17];
-  __shared__ double d0_s[M], rs_s[M], col_s[64];
+  __shared__ double d0_s[M];
   __shared__ int flag_s;
 
   const int lhead = blockIdx.x;
@@ -504,31 +584,11 @@ __global__ __launch_bounds__(256) void exact_solve_kernel(
   for (int p = 0; p < P; ++p) {
     if (wave == 0) {
       const int base = 16 * p;
-      const bool rowlane = lane < 16;
-      double row[16], lrow[16];
+      double row[16], x[16];
 #pragma unroll
-      for (int j = 0; j < 16; ++j) row[j] = rowlane ? Ss[(base + lane) * SP + base + j] : 0.0;
-      const double d0_mine = rowlane ? d0_s[base + lane] : 0.0;
-      if (!chol16(row, d0_mine, rowlane, lane, rs_s + base, col_s, lrow) && lane == 0)
-        flag_s = COMPACTOR_STATUS_PIVOT;
-      if (rowlane) {
-#pragma unroll
-        for (int k = 0; k < 16; ++k) Ss[(base + lane) * SP + base + k] = lrow[k];
-      }
-      wave_fence();
-      // X_pp = L_pp^{-1}: lane j solves column j by forward substitution.  Column by column of
-      // L: as soon as x[k] is known every later row takes its term, so the dependent chain is 16
-      // steps long and not 120 (each row still adds its terms in the order k = 0, 1, ...)
-      double x[16], acc[16];
-#pragma unroll
-      for (int i = 0; i < 16; ++i) acc[i] = (i == lane) ? 1.0 : 0.0;
-#pragma unroll
-      for (int k = 0; k < 16; ++k) {
-        x[k] = acc[k] * rs_s[base + k];
-#pragma unroll
-        for (int i = k + 1; i < 16; ++i) acc[i] -= Ss[(base + i) * SP + base + k] * x[k];
-      }
-      if (rowlane) {
+      for (int j = 0; j < 16; ++j) row[j] = Ss[(base + l16) * SP + base + j];
+      if (!chol16_inverse(row, d0_s[base + l16], x) && lane == 0) flag_s = COMPACTOR_STATUS_PIVOT;
+      if (lane < 16) {
 #pragma unroll
         for (int i = 0; i < 16; ++i) Xd[p][i][lane] = x[i];
       }
@@ -618,26 +678,53 @@ __global__ __launch_bounds__(256) void exact_solve_kernel(
   }
 }
 
+// Longest run of partials a share of its own takes before the head's partials are cut into parts:
+// a batch of eight is in flight at a time, about 1 us each.
+constexpr int SHARE_SPLITS = 64, SHARE_PARTS_MAX = 8;
+
+SketchPlan sketch_plan(const SegTable &T, int ks, int tiles_per_wg) {
+  int most = 1;
+  for (int i = 0; i < T.nseg; ++i) {
+    const int splits = (tiles_of(T.s[i].n) + tiles_per_wg - 1) / tiles_per_wg + 1;
+    if (splits > most) most = splits;
+  }
+  SketchPlan p;
+  p.parts = (most + SHARE_SPLITS - 1) / SHARE_SPLITS;
+  if (p.parts > SHARE_PARTS_MAX) p.parts = SHARE_PARTS_MAX;
+  const int P = ks / 16;
+  p.share_bytes = (size_t)T.nheads * p.parts * SHARE_BLOCKS * (P * (P + 1) / 2 * 256) * sizeof(double);
+  return p;
+}
+
 template <int M>
-static hipError_t launch_sketched(const SegTable &T, int tiles_per_wg, const float *partials,
-                                  const float *phi, float ridge_rel, uint16_t *wt,
-                                  int32_t *status, int *zero, long long zero_ints,
-                                  hipStream_t st) {
-  hipLaunchKernelGGL((sketch_solve_kernel<M>), dim3((unsigned)T.nheads), dim3(256), 0, st, T,
-                     tiles_per_wg, partials, phi, ridge_rel, wt, status, zero, zero_ints);
+static hipError_t launch_sketched(const SegTable &T, int tiles_per_wg, const SketchPlan &plan,
+                                  const float *partials, double *shares, const float *phi,
+                                  float ridge_rel, uint16_t *wt, int32_t *status, int *zero,
+                                  long long zero_ints, hipStream_t st) {
+  if (shares != nullptr) {
+    hipLaunchKernelGGL((sketch_share_kernel<M>), dim3((unsigned)(T.nheads * plan.parts * SHARE_BLOCKS)),
+                       dim3(256), 0, st, T, tiles_per_wg, plan.parts, partials, phi, shares, zero, zero_ints);
+    if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
+    hipLaunchKernelGGL((sketch_solve_kernel<M, true>), dim3((unsigned)T.nheads), dim3(256), 0, st, T,
+                       tiles_per_wg, plan.parts, partials, shares, phi, ridge_rel, wt, status, zero, zero_ints);
+  } else {
+    hipLaunchKernelGGL((sketch_solve_kernel<M, false>), dim3((unsigned)T.nheads), dim3(256), 0, st, T,
+                       tiles_per_wg, plan.parts, partials, shares, phi, ridge_rel, wt, status, zero, zero_ints);
+  }
   return hipGetLastError();
 }
 
-// Sketched mode: partial Gram blocks -> W^T in one kernel (see above).
-hipError_t launch_sketch_solve(const SegTable &T, int ks, int tiles_per_wg, const float *partials,
-                               const float *phi, float ridge_rel, uint16_t *wt,
-                               int32_t *status, int *zero, long long zero_ints, hipStream_t st) {
+// Sketched mode: partial Gram blocks -> W^T (see above).
+hipError_t launch_sketch_solve(const SegTable &T, int ks, int tiles_per_wg, const SketchPlan &plan,
+                               const float *partials, double *shares, const float *phi,
+                               float ridge_rel, uint16_t *wt, int32_t *status, int *zero,
+                               long long zero_ints, hipStream_t st) {
   if (T.nheads <= 0) return hipSuccess;
   switch (ks) {
-    case 16: return launch_sketched<16>(T, tiles_per_wg, partials, phi, ridge_rel, wt, status, zero, zero_ints, st);
-    case 32: return launch_sketched<32>(T, tiles_per_wg, partials, phi, ridge_rel, wt, status, zero, zero_ints, st);
-    case 48: return launch_sketched<48>(T, tiles_per_wg, partials, phi, ridge_rel, wt, status, zero, zero_ints, st);
-    case 64: return launch_sketched<64>(T, tiles_per_wg, partials, phi, ridge_rel, wt, status, zero, zero_ints, st);
+    case 16: return launch_sketched<16>(T, tiles_per_wg, plan, partials, shares, phi, ridge_rel, wt, status, zero, zero_ints, st);
+    case 32: return launch_sketched<32>(T, tiles_per_wg, plan, partials, shares, phi, ridge_rel, wt, status, zero, zero_ints, st);
+    case 48: return launch_sketched<48>(T, tiles_per_wg, plan, partials, shares, phi, ridge_rel, wt, status, zero, zero_ints, st);
+    case 64: return launch_sketched<64>(T, tiles_per_wg, plan, partials, shares, phi, ridge_rel, wt, status, zero, zero_ints, st);
     default: return hipErrorInvalidValue;
   }
 }

@@ -230,6 +230,35 @@ def test_gram_partitions_that_cross_heads(C, gram_wgs):
     _say("  max rel err %.3g, swaps %d" % (st["max_rel"], st["swaps"]))
 
 
+@pytest.mark.parametrize("ks,n,gram_wgs", [(16, 700, 0), (32, 1000, 5), (48, 8192, 128), (64, 5000, 70),
+                                           (48, 60, 0)])
+def test_factorisation_with_and_without_shares(C, ks, n, gram_wgs):
+    """With room in the workspace S = Phi^T G Phi is formed by several workgroups per head, without
+    it by one.  One to 129 partials a head (one run of up to eight, several, three parts of up to
+    64): same bits both ways, and the scores match the oracle."""
+    _say("factorisation: k_s = %d, n = %d, %d Gram workgroups" % (ks, n, gram_wgs))
+    w = W.config1(DEV, L=1, H=1 if gram_wgs > 100 else 3, n=n)
+    w.sketch_dim = ks
+    params, reqs = U.make_call(C, w, DEV)
+    params.gram_wgs = gram_wgs
+    full = C.compactor_workspace_size(params, reqs)
+    ws = torch.zeros(full, dtype=torch.uint8, device=DEV)
+    want, st = C.compactor_score(params, reqs, workspace=ws)
+    lo, hi = 0, full                      # the smallest workspace that is accepted
+    while hi - lo > 256:
+        mid = (lo + hi) // 512 * 256
+        try:
+            C.compactor_score(params, reqs, workspace=ws[:mid])
+            hi = mid
+        except C.CompactorError:
+            lo = mid
+    assert hi < full
+    got, st2 = C.compactor_score(params, reqs, workspace=ws[:hi])
+    assert torch.equal(want.view(torch.int32), got.view(torch.int32)) and torch.equal(st, st2)
+    stats, _ = U.run_and_check(C, w, DEV, tune={"gram_wgs": gram_wgs})
+    _say("  workspace %d of %d bytes; max rel err %.3g" % (hi, full, stats["max_rel"]))
+
+
 @pytest.mark.parametrize("score_tokens", [128, 1024, 8192, 32768])
 def test_score_runs_of_several_bursts(C, score_tokens):
     """A score workgroup takes `score_tokens` tokens and writes its scores in bursts of 4096 (2048
