@@ -143,7 +143,7 @@ GroupBytes group_bytes_needed(const compactor_params_t *p, const SegTable &T, bo
   // 128 heads 34 / 42, 256 heads 41 / 42 (40 against 52 us with two and more partials a head),
   // 512 heads 61 / 55, 4096 heads 376 / 393 (k_s = 64: 662 / 583); one head of n = 131072 brings
   // 64 partials, 27 us against 210.
-  g.shares = ks > 0 && T.nheads <= cus ? align_up(sketch_plan(T, ks, gp.tiles_per_wg).share_bytes) : 0;
+  g.shares = T.nheads <= cus ? align_up(solve_plan(T, ks, gp.tiles_per_wg).share_bytes) : 0;
   g.wt = align_up((size_t)T.nheads * W_TERMS * m * D * sizeof(uint16_t));
   g.hist1 = align_up((size_t)T.nheads * HIST1_BINS * sizeof(int));
   g.sel = select_needs_pools(T) ? align_up((size_t)select_scratch(T).ints() * sizeof(int)) : 0;
@@ -278,12 +278,13 @@ int enqueue_score(const compactor_params_t *p, const SegTable &T, const GroupByt
   HIP_TRY(launch_gram(T, gp.nwg, gp.tiles_per_wg, partials, st));
   MARK(m, COMPACTOR_STAGE_GRAM + 1);
   MARK(m, COMPACTOR_STAGE_REDUCE + 1);       // the fp64 sum of the partials is part of the next kernel
+  double *shares =
+      gb.shares > 0 && ws_bytes >= gb.wanted() ? reinterpret_cast<double *>(ws + gb.off_shares()) : nullptr;
   if (p->sketch_dim > 0) {
-    double *shares = gb.shares > 0 && ws_bytes >= gb.wanted() ? reinterpret_cast<double *>(ws + gb.off_shares()) : nullptr;
-    HIP_TRY(launch_sketch_solve(T, p->sketch_dim, rpw, sketch_plan(T, p->sketch_dim, rpw), partials, shares,
+    HIP_TRY(launch_sketch_solve(T, p->sketch_dim, rpw, solve_plan(T, p->sketch_dim, rpw), partials, shares,
                                 p->phi, p->ridge_rel, wt, status, zero, zero_ints, st));
   } else {
-    HIP_TRY(launch_exact_solve(T, rpw, partials, p->ridge_rel, wt, status, zero, zero_ints, st));
+    HIP_TRY(launch_exact_solve(T, rpw, partials, shares, p->ridge_rel, wt, status, zero, zero_ints, st));
   }
   MARK(m, COMPACTOR_STAGE_SOLVE + 1);
   const int score_tokens = score_tokens_for(p, T, cus);

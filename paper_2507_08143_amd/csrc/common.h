@@ -277,22 +277,24 @@ __device__ __forceinline__ long long partial_base(const SegTable &T, int lhead, 
 hipError_t launch_gram(const SegTable &T, int nwg, int tiles_per_wg, float *partials,
                        hipStream_t st);
 
-// Exact mode: partial Gram blocks -> G + rho I -> Cholesky -> W^T = L^{-1} (as W_TERMS bf16
-// planes, [term][128][128] per head) and the status word, in one kernel.
+// Factorisation: partial Gram blocks -> W^T ([term][k_s][128] per head as W_TERMS bf16 planes; exact
+// mode: [term][128][128], rows up to the end of their group of 32 channels) and the status word.
 // zero[0, zero_ints) is cleared on the way (selection histograms), if not null.
-hipError_t launch_exact_solve(const SegTable &T, int tiles_per_wg, const float *partials,
-                              float ridge_rel, uint16_t *wt, int32_t *status, int *zero,
-                              long long zero_ints, hipStream_t st);
-
-// Sketched mode: partial Gram blocks -> S = Phi^T G Phi + rho I -> W^T ([term][k_s][128] per
-// head) and status.  shares: plan.share_bytes of scratch, which lets many workgroups per head form
-// S (one launch more), or null: one workgroup per head forms it (the same bits).
-struct SketchPlan {
-  int parts;             // the partials of a head are added in this many runs
+// shares: plan.share_bytes of scratch, which lets many workgroups per head add the partials up (one
+// launch more), or null: one workgroup per head does it (the same bits).
+struct SolvePlan {
+  int parts;             // the partials of a head are added in this many runs (sketched mode)
   size_t share_bytes;
 };
-SketchPlan sketch_plan(const SegTable &T, int ks, int tiles_per_wg);
-hipError_t launch_sketch_solve(const SegTable &T, int ks, int tiles_per_wg, const SketchPlan &plan,
+SolvePlan solve_plan(const SegTable &T, int ks, int tiles_per_wg);
+
+// Exact mode: G + rho I -> Cholesky -> W^T = L^{-1}.
+hipError_t launch_exact_solve(const SegTable &T, int tiles_per_wg, const float *partials,
+                              double *shares, float ridge_rel, uint16_t *wt, int32_t *status,
+                              int *zero, long long zero_ints, hipStream_t st);
+
+// Sketched mode: S = Phi^T G Phi + rho I -> Cholesky -> W^T = L^{-1} Phi^T.
+hipError_t launch_sketch_solve(const SegTable &T, int ks, int tiles_per_wg, const SolvePlan &plan,
                                const float *partials, double *shares, const float *phi,
                                float ridge_rel, uint16_t *wt, int32_t *status, int *zero,
                                long long zero_ints, hipStream_t st);

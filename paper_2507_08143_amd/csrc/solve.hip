@@ -44,9 +44,7 @@ constexpr double PIVOT_REL = 1.4901161193847656e-08;   // 2^-26
 template <int K>
 __device__ __forceinline__ double bcast16(double x) {
   constexpr int ROW_NEWBCAST = 0x150;
-  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(x), ROW_NEWBCAST + K, 0xf, 0xf, true);
-  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(x), ROW_NEWBCAST + K, 0xf, 0xf, true);
-  return __hiloint2double(hi, lo);
+  return __builtin_amdgcn_mov_dpp(x, ROW_NEWBCAST + K, 0xf, 0xf, true);
 }
 
 // Compile-time loop: f(integral_constant<int, B>) ... f(integral_constant<int, E - 1>).
@@ -88,12 +86,14 @@ __device__ __forceinline__ bool chol16_inverse(double (&row)[16], double d0, dou
 #pragma unroll
   for (int i = 0; i < 16; ++i) x[i] = (i == l16) ? 1.0 : 0.0;
   double u_prev = 0.0, t_prev = 0.0;               // column k - 1
+  const double least = PIVOT_REL * d0;
   static_for<0, 16>([&](auto kc) {
     constexpr int k = decltype(kc)::value;
     const double d = bcast16<k>(row[k]);
-    const bool ok = d > PIVOT_REL * bcast16<k>(d0) && d < 1.0e300;      // false for NaN too
     double r = __builtin_amdgcn_rcp(d);
+    computed_here(r);
     __builtin_amdgcn_sched_barrier(0);
+    const bool ok = d > bcast16<k>(least) && d < 1.0e300;      // false for NaN too
     // what pivot k - 1 still owes the columns behind this one, in the shadow of the reciprocal
     if constexpr (k > 0) {
       static_for<k, 16>([&](auto jc) {
@@ -146,6 +146,109 @@ __device__ __forceinline__ bool chol16_inverse(double (&row)[16], double d0, dou
 // computes them: with room in the workspace they are computed by workgroups of their own
 // (sketch_share_kernel) and added by the factorisation, otherwise one workgroup per head computes
 // them one after the other.  Both give the same bits.
+// Steps 2 and 3 for a matrix of P panels, by NW waves.  Ss (16P rows of pitch 16P + 1 doubles) holds
+// S + rho I in its lower 16 x 16 blocks; on return L is below the diagonal blocks, the diagonal
+// blocks of X = L^{-1} are in Xd and the blocks of X below the diagonal, transposed, in the upper
+// blocks of Ss (element X[j][c], block of j below block of c, is at Ss[c][j]).
+// The serial chain is wave 0's: the diagonal block takes its last update and is eliminated.  In
+// its shadow the other waves apply what the previous panel owes the trailing matrix and X (Y_qc =
+// sum over r of L_qr X_rc grows in the place of X_qc) and hand on finished rows of X: row_done(p,
+// i, n) is called by n waves, i = 0 .. n - 1, when block row p of X is complete.  With three panels
+// that takes 1.2 us off the 13.8 us of one head, with eight (exact mode) 22 us off 52.
+template <int P, int NW, class F>
+__device__ __forceinline__ void factor_panels(double *Ss, double (*Xd)[16][17], const double *d0_s,
+                                              int *flag, F &&row_done) {
+  constexpr int SP = 16 * P + 1;
+  const int lane = threadIdx.x & 63, l16 = lane & 15, lq = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  // A_qr -= L_qp L_rp^T
+  auto trail = [&](int q, int r, int p) {
+    f64x4 acc;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) acc[v] = Ss[(16 * q + 4 * v + lq) * SP + 16 * r + l16];
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      const double a = -Ss[(16 * q + l16) * SP + 16 * p + 4 * ks + lq];
+      const double b = Ss[(16 * r + l16) * SP + 16 * p + 4 * ks + lq];
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) Ss[(16 * q + 4 * v + lq) * SP + 16 * r + l16] = acc[v];
+  };
+  // Y_qc += L_qp X_pc, c <= p
+  auto grow = [&](int q, int c, int p) {
+    double *y = &Ss[(16 * c + l16) * SP + 16 * q + lq];        // transposed: row 4v + lq, column l16
+    f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+    if (c < p) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) acc[v] = y[4 * v];
+    }
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      const double a = Ss[(16 * q + l16) * SP + 16 * p + 4 * ks + lq];
+      const double b = c == p ? Xd[p][4 * ks + lq][l16] : Ss[(16 * c + l16) * SP + 16 * p + 4 * ks + lq];
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) y[4 * v] = acc[v];
+  };
+#pragma unroll 1
+  for (int p = 0; p < P; ++p) {
+    if (wave == 0) {
+      if (p > 0) {
+        trail(p, p, p - 1);
+        wave_fence();
+      }
+      double row[16], x[16];
+#pragma unroll
+      for (int j = 0; j < 16; ++j) row[j] = Ss[(16 * p + l16) * SP + 16 * p + j];
+      if (!chol16_inverse(row, d0_s[16 * p + l16], x) && lane == 0) *flag = COMPACTOR_STATUS_PIVOT;
+      if (lane < 16) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) Xd[p][i][lane] = x[i];
+      }
+    } else if (p > 0) {
+      int t = 1;
+      for (int q = p; q < P; ++q) {
+        for (int r = p; r <= q; ++r) {
+          if (r == p && q == p) continue;                       // wave 0's
+          if (t == wave) trail(q, r, p - 1);
+          t = t == NW - 1 ? 1 : t + 1;
+        }
+        for (int c = 0; c < p; ++c) {
+          if (t == wave) grow(q, c, p - 1);
+          t = t == NW - 1 ? 1 : t + 1;
+        }
+      }
+      row_done(p - 1, wave - 1, NW - 1);
+    }
+    __syncthreads();
+    // the panel below the diagonal block, L_qp = A_qp X_pp^T, and row p of X, X_pc = -X_pp Y_pc
+    for (int i = wave; i < P; i += NW) {
+      if (i == p) continue;
+      f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+      if (i > p) {
+        double *l = &Ss[(16 * i) * SP + 16 * p];
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(l[l16 * SP + 4 * ks + lq], Xd[p][l16][4 * ks + lq],
+                                                     acc, 0, 0, 0);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) l[(4 * v + lq) * SP + l16] = acc[v];
+      } else {
+        double *y = &Ss[(16 * i + l16) * SP + 16 * p + lq];
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-Xd[p][l16][4 * ks + lq], y[4 * ks], acc, 0, 0, 0);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) y[4 * v] = acc[v];
+      }
+    }
+    __syncthreads();
+  }
+  row_done(P - 1, wave, NW);
+}
+
 constexpr int SHARE_BLOCKS = 5;
 template <int M>
 struct Share {
@@ -309,6 +412,12 @@ __global__ __launch_bounds__(256, 2) void sketch_share_kernel(
   });
 }
 
+template <int N>
+__device__ __forceinline__ void fetch_phi(const float *__restrict__ phi, float4 (&r)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) r[i] = reinterpret_cast<const float4 *>(phi)[threadIdx.x + 256 * i];
+}
+
 // One workgroup (4 waves) per head, steps 2 to 4; step 1 from the shares, or from
 // the partials.
 template <int M, bool SHARES>
@@ -318,14 +427,22 @@ __global__ __launch_bounds__(256, 2) void sketch_solve_kernel(
     uint16_t *__restrict__ wt, int32_t *__restrict__ status, int *__restrict__ zero,
     long long zero_ints) {
   constexpr int P = M / 16, SP = M + 1, TILES = Share<M>::TILES;
-  __shared__ double Ss[M * SP];        // S, then L in its lower blocks
-  __shared__ double Xs[M * SP];        // L^{-1} (lower blocks)
+  __shared__ double Ss[M * SP];        // S, then L and X = L^{-1} (factor_panels)
+  __shared__ double Xd[P][16][17];
+  // Phi, rows of pitch M + 4 (conflict-free operand reads); before that the second half of a share
+  constexpr int PP = M + 4, BB = D * PP / 2 > M * SP ? D * PP / 2 : M * SP;
+  __shared__ __attribute__((aligned(16))) double bb[SHARES ? D * PP / 2 : BB];
+  float *PH = reinterpret_cast<float *>(bb);
   __shared__ double d0_s[M];
   __shared__ int flag_s;
 
   const int lhead = blockIdx.x;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l16 = lane & 15, lq = lane >> 4;
   if (tid == 0) flag_s = 0;
+
+  constexpr int PHN = D * M / 4 / 256;
+  float4 ph_reg[PHN];                              // Phi on its way to LDS
+  if constexpr (SHARES) fetch_phi<PHN>(phi, ph_reg);
 
   // ---- 1. S = Phi^T G Phi ----
   double sum[TILES];
@@ -353,26 +470,22 @@ __global__ __launch_bounds__(256, 2) void sketch_solve_kernel(
       const int r = s / SHARE_BLOCKS, w = s - r * SHARE_BLOCKS;
       int first, count;
       split_part(nsplit, parts, r, first, count);
-      sketch_share<M>(partials + (pb + first) * GRAM_PARTIAL_FLOATS, count, w, phi, Ss, Xs);
+      sketch_share<M>(partials + (pb + first) * GRAM_PARTIAL_FLOATS, count, w, phi, Ss, bb);
       __syncthreads();
       for_lower_tiles<M>([&](int t, int a, int b) {
-        sum[t] += (Ss[a * SP + b] + Xs[a * SP + b]) + (Ss[b * SP + a] + Xs[b * SP + a]);
+        sum[t] += (Ss[a * SP + b] + bb[a * SP + b]) + (Ss[b * SP + a] + bb[b * SP + a]);
       });
       __syncthreads();
     }
+    fetch_phi<PHN>(phi, ph_reg);
     zero_slice(zero, zero_ints);
   }
   for_lower_tiles<M>([&](int t, int a, int b) { Ss[a * SP + b] = sum[t]; });
-  // Phi as the A operand of W = Phi X^T (step 4), on its way during the factorisation.  Row i of a
-  // 16-channel tile holds channel 4 (i & 3) + (i >> 2), so that the four result registers of a
-  // lane are four consecutive channels.
-  constexpr int KS4 = M / 4;
-  float pw[2][KS4];
 #pragma unroll
-  for (int u = 0; u < 2; ++u)
-#pragma unroll
-    for (int ks = 0; ks < KS4; ++ks)
-      pw[u][ks] = phi[(16 * (wave + 4 * u) + 4 * (l16 & 3) + (l16 >> 2)) * M + 4 * ks + lq];
+  for (int i = 0; i < PHN; ++i) {
+    const int c4 = tid + 256 * i;
+    *reinterpret_cast<float4 *>(&PH[c4 / (M / 4) * PP + c4 % (M / 4) * 4]) = ph_reg[i];
+  }
   __syncthreads();
 
   // ridge: rho = ridge_rel * trace(S) / M (every wave sums in the same order)
@@ -388,188 +501,144 @@ __global__ __launch_bounds__(256, 2) void sketch_solve_kernel(
   }
   __syncthreads();
 
-  // ---- 2. blocked Cholesky ----
-#pragma unroll 1
-  for (int p = 0; p < P; ++p) {
-    if (wave == 0) {
-      const int base = 16 * p;
-      double row[16], x[16];
-#pragma unroll
-      for (int j = 0; j < 16; ++j) row[j] = Ss[(base + l16) * SP + base + j];
-      if (!chol16_inverse(row, d0_s[base + l16], x) && lane == 0) flag_s = COMPACTOR_STATUS_PIVOT;
-      if (lane < 16) {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) Xs[(base + i) * SP + base + lane] = x[i];
-      }
-    }
-    __syncthreads();
-    // panel below the diagonal block: L_qp = A_qp X_pp^T
-    for (int q = p + 1 + wave; q < P; q += 4) {
-      f64x4 acc = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks) {
-        const double a = Ss[(16 * q + l16) * SP + 16 * p + 4 * ks + lq];
-        const double b = Xs[(16 * p + l16) * SP + 16 * p + 4 * ks + lq];
-        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
-      }
-#pragma unroll
-      for (int v = 0; v < 4; ++v) Ss[(16 * q + 4 * v + lq) * SP + 16 * p + l16] = acc[v];
-    }
-    __syncthreads();
-    // trailing blocks: A_qr -= L_qp L_rp^T for p < r <= q
-    int t = 0;
-    for (int q = p + 1; q < P; ++q)
-      for (int r = p + 1; r <= q; ++r, ++t) {
-        if ((t & 3) != wave) continue;
-        f64x4 acc;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) acc[v] = Ss[(16 * q + 4 * v + lq) * SP + 16 * r + l16];
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-          const double a = -Ss[(16 * q + l16) * SP + 16 * p + 4 * ks + lq];
-          const double b = Ss[(16 * r + l16) * SP + 16 * p + 4 * ks + lq];
-          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
-        }
-#pragma unroll
-        for (int v = 0; v < 4; ++v) Ss[(16 * q + 4 * v + lq) * SP + 16 * r + l16] = acc[v];
-      }
-    __syncthreads();
-  }
-
-  // ---- 3. the blocks of X = L^{-1} below the diagonal, block column `wave` ----
-  if (wave < P - 1) {
-    const int p = wave;
-    for (int q = p + 1; q < P; ++q) {
-      f64x4 acc = {0.0, 0.0, 0.0, 0.0};
-      for (int r = p; r < q; ++r) {
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-          const double a = Ss[(16 * q + l16) * SP + 16 * r + 4 * ks + lq];      // L_qr[i][k]
-          const double b = Xs[(16 * r + 4 * ks + lq) * SP + 16 * p + l16];      // X_rp[k][j]
-          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
-        }
-      }
-      // X_qp = -X_qq acc: the result layout of acc is the B-operand layout of the next product
-      f64x4 out = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks) {
-        const double a = -Xs[(16 * q + l16) * SP + 16 * q + 4 * ks + lq];
-        out = __builtin_amdgcn_mfma_f64_16x16x4f64(a, acc[ks], out, 0, 0, 0);
-      }
-#pragma unroll
-      for (int v = 0; v < 4; ++v) Xs[(16 * q + 4 * v + lq) * SP + 16 * p + l16] = out[v];
-      wave_fence();            // the next block row of this column reads what was just written
-    }
-  }
-  __syncthreads();
-
-  // ---- 4. W = Phi X^T (128 x M), lower block triangle of X only; stored as W^T ----
-  // a wave takes the channel tiles wave and wave + 4 of every row block: two chains
+  // ---- 2, 3, and 4 row by row: W = Phi X^T (128 x M), lower block triangle of X only; stored as W^T
   uint16_t *wh = wt + (size_t)lhead * (W_TERMS * M * D);
+  auto emit = [&](int mt, int ct, const f64x4 &acc) {
+    float x[4];
 #pragma unroll
-  for (int mt = 0; mt < P; ++mt) {
-    f64x4 acc[2];
-    acc[0] = acc[1] = f64x4{0.0, 0.0, 0.0, 0.0};
+    for (int v = 0; v < 4; ++v) x[v] = (float)acc[v];
 #pragma unroll
-    for (int ks = 0; ks < 4 * (mt + 1); ++ks) {
-      const double b = Xs[(16 * mt + l16) * SP + 4 * ks + lq];
+    for (int tt = 0; tt < W_TERMS; ++tt) {
+      uint16_t b[4];
 #pragma unroll
-      for (int u = 0; u < 2; ++u)
-        acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)pw[u][ks], b, acc[u], 0, 0, 0);
+      for (int v = 0; v < 4; ++v) {
+        b[v] = bf16_rne(x[v]);
+        x[v] -= bf16_to_f32(b[v]);
+      }
+      *reinterpret_cast<uint2 *>(&wh[(tt * M + 16 * mt + l16) * D + 16 * ct + 4 * lq]) =
+          make_uint2((unsigned)b[0] | (unsigned)b[1] << 16, (unsigned)b[2] | (unsigned)b[3] << 16);
     }
+  };
+  // Phi is the A operand: row i of a 16-channel tile holds channel 4 (i & 3) + (i >> 2), so that the
+  // four result registers of a lane are four consecutive channels
+  const float *phi_w = PH + (4 * (l16 & 3) + (l16 >> 2)) * PP + lq;
+  factor_panels<P, 4>(Ss, Xd, d0_s, &flag_s, [&](int mt, int i, int nw) {
+    constexpr int OWN = (D / 16 + 2) / 3;          // channel tiles of a wave, of three or four waves
+    f64x4 acc[OWN];
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      float x[4];
+    for (int u = 0; u < OWN; ++u) acc[u] = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+    for (int kb = 0; kb <= mt; ++kb) {
 #pragma unroll
-      for (int v = 0; v < 4; ++v) x[v] = (float)acc[u][v];
+      for (int k4 = 0; k4 < 4; ++k4) {
+        const int k = 16 * kb + 4 * k4;
+        const double x = kb == mt ? Xd[mt][l16][4 * k4 + lq] : Ss[(k + lq) * SP + 16 * mt + l16];
 #pragma unroll
-      for (int tt = 0; tt < W_TERMS; ++tt) {
-        uint16_t b[4];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          b[v] = bf16_rne(x[v]);
-          x[v] -= bf16_to_f32(b[v]);
-        }
-        *reinterpret_cast<uint2 *>(&wh[(tt * M + 16 * mt + l16) * D + 16 * (wave + 4 * u) + 4 * lq]) =
-            make_uint2((unsigned)b[0] | (unsigned)b[1] << 16, (unsigned)b[2] | (unsigned)b[3] << 16);
+        for (int u = 0; u < OWN; ++u)
+          if (i + nw * u < D / 16)                 // uniform
+            acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)phi_w[16 * (i + nw * u) * PP + k], x,
+                                                          acc[u], 0, 0, 0);
       }
     }
-  }
+#pragma unroll
+    for (int u = 0; u < OWN; ++u)
+      if (i + nw * u < D / 16) emit(mt, i + nw * u, acc[u]);
+  });
   if (tid == 0) {
     const Where w = locate_head(T, lhead);
     status[T.s[w.seg].ghead0 + w.head] = flag_s;
   }
 }
 
-// ---- exact mode, one kernel: partial Gram blocks -> G + rho I -> L -> L^{-1} = W^T -------------
-// The same blocked factorisation as above on the full 128 x 128 Gram matrix (8 panels of 16).
-// One matrix of 128 x 129 doubles is all LDS has room for, so L lives in its lower block
-// triangle and the blocks of X = L^{-1} below the diagonal are written, transposed, into the
-// upper block triangle, which the factorisation never reads (element X[j][c], block of j below
-// block of c, is at S[c][j]); the eight diagonal blocks of X have an array of their own.
-__global__ __launch_bounds__(256) void exact_solve_kernel(
-    const SegTable T, int tiles_per_wg, const float *__restrict__ partials, float ridge_rel,
-    uint16_t *__restrict__ wt, int32_t *__restrict__ status, int *__restrict__ zero,
-    long long zero_ints) {
-  constexpr int M = D, P = M / 16, SP = M + 1;
-  __shared__ double Ss[M * SP];
+// ---- exact mode: partial Gram blocks -> G + rho I -> L -> L^{-1} = W^T --------------------------
+// The same blocked factorisation on the full 128 x 128 Gram matrix (8 panels of 16).  Like S in
+// sketched mode, G is summed by workgroups of their own (gram_sum_kernel, one per stored block)
+// where the workspace has room, with the same bits.
+constexpr int EXACT_THREADS = 512;
+
+// The fp64 sum, in their order, of a thread's float4 of a block over `count` partials.
+__device__ __forceinline__ void sum_quads(const float *__restrict__ src, int count, double (&g)[4]) {
+  constexpr int FLIGHT = 8;
+  g[0] = g[1] = g[2] = g[3] = 0.0;
+  for (int s0 = 0; s0 < count; s0 += FLIGHT) {
+    float4 v[FLIGHT];
+#pragma unroll
+    for (int u = 0; u < FLIGHT; ++u) {
+      v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (s0 + u < count)                                       // uniform
+        v[u] = *reinterpret_cast<const float4 *>(src + (long long)(s0 + u) * GRAM_PARTIAL_FLOATS);
+    }
+#pragma unroll
+    for (int u = 0; u < FLIGHT; ++u) { g[0] += v[u].x; g[1] += v[u].y; g[2] += v[u].z; g[3] += v[u].w; }
+  }
+}
+
+__global__ __launch_bounds__(256) void gram_sum_kernel(const SegTable T, int tiles_per_wg,
+                                                       const float *__restrict__ partials,
+                                                       double *__restrict__ sums, int *__restrict__ zero,
+                                                       long long zero_ints) {
+  const int lhead = blockIdx.x / 10, b = blockIdx.x - 10 * lhead;
+  int nsplit;
+  const long long pb = partial_base(T, lhead, tiles_per_wg, nsplit);
+  double g[4];
+  sum_quads(partials + pb * GRAM_PARTIAL_FLOATS + b * 1024 + threadIdx.x * 4, nsplit, g);
+  zero_slice(zero, zero_ints);   // histograms that the score and selection kernels add into
+  double *out = sums + (long long)blockIdx.x * 1024 + threadIdx.x * 4;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) out[c] = g[c];
+}
+
+template <bool SUMS>
+__global__ __launch_bounds__(EXACT_THREADS) void exact_solve_kernel(
+    const SegTable T, int tiles_per_wg, const float *__restrict__ partials,
+    const double *__restrict__ sums, float ridge_rel, uint16_t *__restrict__ wt,
+    int32_t *__restrict__ status, int *__restrict__ zero, long long zero_ints) {
+  constexpr int M = D, P = M / 16, SP = M + 1, NW = EXACT_THREADS / 64;
+  __shared__ double Ss[M * SP];        // G, then L and X = L^{-1} (factor_panels)
   __shared__ double Xd[P][16][17];
   __shared__ double d0_s[M];
   __shared__ int flag_s;
 
   const int lhead = blockIdx.x;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l16 = lane & 15, lq = lane >> 4;
+  const int tid = threadIdx.x, lane = tid & 63;
   if (tid == 0) flag_s = 0;
-  zero_slice(zero, zero_ints);   // histograms that the score and selection kernels add into
 
-  // ---- 1. G: the head's 10 upper blocks summed over the splits in fp64 (split order) ----
-  int nsplit;
-  const long long pb = partial_base(T, lhead, tiles_per_wg, nsplit);
+  // ---- 1. G: the head's 10 upper blocks, five for each half of the workgroup ----
+  const int f = tid & 255, half = __builtin_amdgcn_readfirstlane(tid >> 8);
   int row0, col;
-  partial_quad(tid, row0, col);   // this thread's float4 of a block: rows row0..+3 of column col
-  double gsum[10][4];
+  partial_quad(f, row0, col);     // this thread's float4 of a block: rows row0..+3 of column col
+  double g[5][4];
+  if constexpr (SUMS) {
+    const double *in = sums + ((long long)lhead * 10 + half) * 1024 + f * 4;
 #pragma unroll
-  for (int b = 0; b < 10; ++b)
+    for (int i = 0; i < 5; ++i)
 #pragma unroll
-    for (int c = 0; c < 4; ++c) gsum[b][c] = 0.0;
-  {
-    const float *src = partials + pb * GRAM_PARTIAL_FLOATS + tid * 4;
-    for (int s0 = 0; s0 < nsplit; s0 += 2) {
-      float4 v[2][10];
+      for (int c = 0; c < 4; ++c) g[i][c] = in[i * 2048 + c];
+  } else {
+    int nsplit;
+    const long long pb = partial_base(T, lhead, tiles_per_wg, nsplit);
+    const float *src = partials + pb * GRAM_PARTIAL_FLOATS + half * 1024 + f * 4;
 #pragma unroll
-      for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int b = 0; b < 10; ++b) {
-          v[u][b] = make_float4(0.f, 0.f, 0.f, 0.f);
-          if (s0 + u < nsplit)
-            v[u][b] = *reinterpret_cast<const float4 *>(src + (long long)(s0 + u) * GRAM_PARTIAL_FLOATS + b * 1024);
-        }
-#pragma unroll
-      for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int b = 0; b < 10; ++b) {
-          gsum[b][0] += v[u][b].x; gsum[b][1] += v[u][b].y;
-          gsum[b][2] += v[u][b].z; gsum[b][3] += v[u][b].w;
-        }
-    }
+    for (int i = 0; i < 5; ++i) sum_quads(src + i * 2048, nsplit, g[i]);
+    zero_slice(zero, zero_ints);   // histograms that the score and selection kernels add into
   }
   // into the lower triangle: block (I, J), I < J, holds G[32I + r][32J + c] = G[32J + c][32I + r]
 #pragma unroll
-  for (int I = 0; I < 4; ++I)
+  for (int i = 0; i < 5; ++i) {
+    int I, J;
+    upper_block_pos(2 * i + half, I, J);
 #pragma unroll
-    for (int J = I; J < 4; ++J) {
-      const int blk = upper_block(I, J);
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        if (I == J) Ss[(32 * I + row0 + c) * SP + 32 * J + col] = gsum[blk][c];
-        else        Ss[(32 * J + col) * SP + 32 * I + row0 + c] = gsum[blk][c];
-      }
+    for (int c = 0; c < 4; ++c) {
+      if (I == J) Ss[(32 * I + row0 + c) * SP + 32 * J + col] = g[i][c];
+      else        Ss[(32 * J + col) * SP + 32 * I + row0 + c] = g[i][c];
     }
+  }
   __syncthreads();
 
-  // ridge: rho = ridge_rel * trace(G) / M (every thread sums in the same order)
-  double tr = 0.0;
-  for (int a = 0; a < M; ++a) tr += Ss[a * SP + a];
+  // ridge: rho = ridge_rel * trace(G) / M (every wave sums in the same order)
+  double tr = Ss[lane * SP + lane] + Ss[(lane + 64) * SP + lane + 64];
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) tr += __shfl_xor(tr, d);
   const double rho = (double)ridge_rel * tr / (double)M;
   __syncthreads();
   if (tid < M) {
@@ -579,99 +648,35 @@ __global__ __launch_bounds__(256) void exact_solve_kernel(
   }
   __syncthreads();
 
-  // ---- 2. blocked Cholesky ----
-#pragma unroll 1
-  for (int p = 0; p < P; ++p) {
-    if (wave == 0) {
-      const int base = 16 * p;
-      double row[16], x[16];
-#pragma unroll
-      for (int j = 0; j < 16; ++j) row[j] = Ss[(base + l16) * SP + base + j];
-      if (!chol16_inverse(row, d0_s[base + l16], x) && lane == 0) flag_s = COMPACTOR_STATUS_PIVOT;
-      if (lane < 16) {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) Xd[p][i][lane] = x[i];
-      }
-    }
-    __syncthreads();
-    // panel below the diagonal block: L_qp = A_qp X_pp^T
-    for (int q = p + 1 + wave; q < P; q += 4) {
-      f64x4 acc = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks) {
-        const double a = Ss[(16 * q + l16) * SP + 16 * p + 4 * ks + lq];
-        const double b = Xd[p][l16][4 * ks + lq];
-        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
-      }
-#pragma unroll
-      for (int v = 0; v < 4; ++v) Ss[(16 * q + 4 * v + lq) * SP + 16 * p + l16] = acc[v];
-    }
-    __syncthreads();
-    // trailing blocks: A_qr -= L_qp L_rp^T for p < r <= q
-    int t = 0;
-    for (int q = p + 1; q < P; ++q)
-      for (int r = p + 1; r <= q; ++r, ++t) {
-        if ((t & 3) != wave) continue;
-        f64x4 acc;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) acc[v] = Ss[(16 * q + 4 * v + lq) * SP + 16 * r + l16];
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-          const double a = -Ss[(16 * q + l16) * SP + 16 * p + 4 * ks + lq];
-          const double b = Ss[(16 * r + l16) * SP + 16 * p + 4 * ks + lq];
-          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
-        }
-#pragma unroll
-        for (int v = 0; v < 4; ++v) Ss[(16 * q + 4 * v + lq) * SP + 16 * r + l16] = acc[v];
-      }
-    __syncthreads();
-  }
-
-  // ---- 3. the blocks of X = L^{-1} below the diagonal: X_qp = -X_qq sum_r L_qr X_rp.  A wave
-  // takes the block columns p = wave and wave + 4; a column only reads what the same wave wrote.
-  for (int p = wave; p < P - 1; p += 4) {
-    for (int q = p + 1; q < P; ++q) {
-      f64x4 acc = {0.0, 0.0, 0.0, 0.0};
-      for (int r = p; r < q; ++r) {
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-          const double a = Ss[(16 * q + l16) * SP + 16 * r + 4 * ks + lq];        // L_qr[i][k]
-          const double b = r == p ? Xd[p][4 * ks + lq][l16]                        // X_pp[k][j]
-                                  : Ss[(16 * p + l16) * SP + 16 * r + 4 * ks + lq];  // X_rp[k][j], transposed
-          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
-        }
-      }
-      // the result layout of acc is the B-operand layout of the next product
-      f64x4 out = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks) {
-        const double a = -Xd[q][l16][4 * ks + lq];
-        out = __builtin_amdgcn_mfma_f64_16x16x4f64(a, acc[ks], out, 0, 0, 0);
-      }
-      // X_qp[i = 4v + lq][j = l16], stored transposed in block (p, q) of the upper triangle
-#pragma unroll
-      for (int v = 0; v < 4; ++v) Ss[(16 * p + l16) * SP + 16 * q + 4 * v + lq] = out[v];
-      wave_fence();            // the next block row of this column reads what was just written
-    }
-  }
-  __syncthreads();
-
-  // ---- 4. W^T = X (lower triangular), split into bf16 planes ----
+  // ---- 2 and 3, W^T = X split into bf16 planes row by row.  The score kernel reads of row j the
+  // channels of its group of 32 and of the groups before it. ----
   uint16_t *wh = wt + (size_t)lhead * (W_TERMS * M * D);
-  const int ch = tid & 127;
-  for (int j = tid >> 7; j < M; j += 2) {
-    const int qb = j >> 4, pb2 = ch >> 4;
-    double wv = 0.0;
-    if (pb2 == qb) wv = Xd[qb][j & 15][ch & 15];
-    else if (pb2 < qb) wv = Ss[ch * SP + j];
-    float x = (float)wv;
+  factor_panels<P, NW>(Ss, Xd, d0_s, &flag_s, [&](int p, int i, int nw) {
+    // a wave: 16 rows x 32 channels, a lane 8 consecutive channels of one row
+    const int r = lane & 15, c8 = 8 * (lane >> 4);
+    for (int g32 = i; g32 <= p >> 1; g32 += nw) {
+      const int ch0 = 32 * g32 + c8, cb = ch0 >> 4;
+      float x[8];
 #pragma unroll
-    for (int t = 0; t < W_TERMS; ++t) {
-      const uint16_t b = bf16_rne(x);
-      wh[(t * M + j) * D + ch] = b;
-      x -= bf16_to_f32(b);
+      for (int e = 0; e < 8; ++e) {
+        double v = 0.0;
+        if (cb == p) v = Xd[p][r][(ch0 & 15) + e];
+        else if (cb < p) v = Ss[(ch0 + e) * SP + 16 * p + r];
+        x[e] = (float)v;
+      }
+#pragma unroll
+      for (int t = 0; t < W_TERMS; ++t) {
+        unsigned w[4];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const uint16_t b = bf16_rne(x[e]);
+          w[e >> 1] = (e & 1) ? w[e >> 1] | (unsigned)b << 16 : (unsigned)b;
+          x[e] -= bf16_to_f32(b);
+        }
+        *reinterpret_cast<uint4 *>(&wh[(t * M + 16 * p + r) * D + ch0]) = make_uint4(w[0], w[1], w[2], w[3]);
+      }
     }
-  }
+  });
   if (tid == 0) {
     const Where w = locate_head(T, lhead);
     status[T.s[w.seg].ghead0 + w.head] = flag_s;
@@ -682,13 +687,18 @@ __global__ __launch_bounds__(256) void exact_solve_kernel(
 // a batch of eight is in flight at a time, about 1 us each.
 constexpr int SHARE_SPLITS = 64, SHARE_PARTS_MAX = 8;
 
-SketchPlan sketch_plan(const SegTable &T, int ks, int tiles_per_wg) {
+SolvePlan solve_plan(const SegTable &T, int ks, int tiles_per_wg) {
+  SolvePlan p;
+  p.parts = 1;
+  if (ks == 0) {
+    p.share_bytes = (size_t)T.nheads * 10 * 1024 * sizeof(double);
+    return p;
+  }
   int most = 1;
   for (int i = 0; i < T.nseg; ++i) {
     const int splits = (tiles_of(T.s[i].n) + tiles_per_wg - 1) / tiles_per_wg + 1;
     if (splits > most) most = splits;
   }
-  SketchPlan p;
   p.parts = (most + SHARE_SPLITS - 1) / SHARE_SPLITS;
   if (p.parts > SHARE_PARTS_MAX) p.parts = SHARE_PARTS_MAX;
   const int P = ks / 16;
@@ -697,7 +707,7 @@ SketchPlan sketch_plan(const SegTable &T, int ks, int tiles_per_wg) {
 }
 
 template <int M>
-static hipError_t launch_sketched(const SegTable &T, int tiles_per_wg, const SketchPlan &plan,
+static hipError_t launch_sketched(const SegTable &T, int tiles_per_wg, const SolvePlan &plan,
                                   const float *partials, double *shares, const float *phi,
                                   float ridge_rel, uint16_t *wt, int32_t *status, int *zero,
                                   long long zero_ints, hipStream_t st) {
@@ -715,7 +725,7 @@ static hipError_t launch_sketched(const SegTable &T, int tiles_per_wg, const Ske
 }
 
 // Sketched mode: partial Gram blocks -> W^T (see above).
-hipError_t launch_sketch_solve(const SegTable &T, int ks, int tiles_per_wg, const SketchPlan &plan,
+hipError_t launch_sketch_solve(const SegTable &T, int ks, int tiles_per_wg, const SolvePlan &plan,
                                const float *partials, double *shares, const float *phi,
                                float ridge_rel, uint16_t *wt, int32_t *status, int *zero,
                                long long zero_ints, hipStream_t st) {
@@ -757,13 +767,21 @@ hipError_t launch_srht_phi(int ks, const uint8_t *signs, const int32_t *cols, fl
   return hipGetLastError();
 }
 
-// Exact mode: partial Gram blocks -> Cholesky of G + rho I -> W^T = L^{-1}, in one kernel.
+// Exact mode: partial Gram blocks -> Cholesky of G + rho I -> W^T = L^{-1}.
 hipError_t launch_exact_solve(const SegTable &T, int tiles_per_wg, const float *partials,
-                              float ridge_rel, uint16_t *wt, int32_t *status, int *zero,
-                              long long zero_ints, hipStream_t st) {
+                              double *shares, float ridge_rel, uint16_t *wt, int32_t *status,
+                              int *zero, long long zero_ints, hipStream_t st) {
   if (T.nheads <= 0) return hipSuccess;
-  hipLaunchKernelGGL(exact_solve_kernel, dim3((unsigned)T.nheads), dim3(256), 0, st, T, tiles_per_wg,
-                     partials, ridge_rel, wt, status, zero, zero_ints);
+  if (shares != nullptr) {
+    hipLaunchKernelGGL(gram_sum_kernel, dim3((unsigned)T.nheads * 10), dim3(256), 0, st, T, tiles_per_wg,
+                       partials, shares, zero, zero_ints);
+    if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
+    hipLaunchKernelGGL((exact_solve_kernel<true>), dim3((unsigned)T.nheads), dim3(EXACT_THREADS), 0, st, T,
+                       tiles_per_wg, partials, shares, ridge_rel, wt, status, zero, zero_ints);
+  } else {
+    hipLaunchKernelGGL((exact_solve_kernel<false>), dim3((unsigned)T.nheads), dim3(EXACT_THREADS), 0, st, T,
+                       tiles_per_wg, partials, shares, ridge_rel, wt, status, zero, zero_ints);
+  }
   return hipGetLastError();
 }
 

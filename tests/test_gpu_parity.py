@@ -231,14 +231,14 @@ def test_gram_partitions_that_cross_heads(C, gram_wgs):
 
 
 @pytest.mark.parametrize("ks,n,gram_wgs", [(16, 700, 0), (32, 1000, 5), (48, 8192, 128), (64, 5000, 70),
-                                           (48, 60, 0)])
+                                           (48, 60, 0), (0, 1000, 5), (0, 8192, 128)])
 def test_factorisation_with_and_without_shares(C, ks, n, gram_wgs):
-    """With room in the workspace S = Phi^T G Phi is formed by several workgroups per head, without
-    it by one.  One to 129 partials a head (one run of up to eight, several, three parts of up to
+    """With room in the workspace S = Phi^T G Phi (exact mode, k_s = 0: G) is formed by several
+    workgroups per head, without it by one.  One to 129 partials a head (one run of up to eight, several, three parts of up to
     64): same bits both ways, and the scores match the oracle."""
     _say("factorisation: k_s = %d, n = %d, %d Gram workgroups" % (ks, n, gram_wgs))
     w = W.config1(DEV, L=1, H=1 if gram_wgs > 100 else 3, n=n)
-    w.sketch_dim = ks
+    w.sketch_dim, w.ridge_rel = ks, 0.0 if ks else 1e-4
     params, reqs = U.make_call(C, w, DEV)
     params.gram_wgs = gram_wgs
     full = C.compactor_workspace_size(params, reqs)
