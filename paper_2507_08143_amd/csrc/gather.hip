@@ -219,21 +219,49 @@ __global__ __launch_bounds__(GATHER_THREADS) void gather_paged_kernel(const SegT
 }
 
 // In place: a head's tokens already live in the pages (token t at logical slot t) and its
-// retained rows move to the front.  One workgroup per head walks the retained list in ascending
-// runs of 256 rows: all rows of a run are read, the workgroup meets, the run is written.  A run's
-// sources lie at or behind its own destinations and strictly behind those of earlier runs
-// (kept[j] >= j, ascending), so nothing is overwritten before it has been read; for the same
-// reason the next run's rows can be fetched while this run is being written (its sources lie
-// behind every slot written so far), which keeps loads in flight across the barrier.
-constexpr int INPLACE_THREADS = 1024, INPLACE_RUN = 256;
-struct InplaceRun {
-  uint4 kv[INPLACE_RUN / 64], vv[INPLACE_RUN / 64];
-  long long dst[INPLACE_RUN / 64];
+// retained rows move to the front.  A workgroup walks the retained list of one head in ascending
+// runs: all rows of a run are read, the workgroup meets, the run is written.  A run's sources lie
+// at or behind its own destinations and strictly behind those of earlier runs (kept[j] >= j,
+// ascending), so nothing is overwritten before it has been read; for the same reason the next
+// run's rows can be fetched while this run is being written (its sources lie behind every slot
+// written so far), which keeps loads in flight across the barrier.
+//
+// The order binds a head's rows but not its columns: K and V, and column slices of LANES * 16 bytes
+// within a row, move independently, each by a workgroup of its own.  What bounds a workgroup is the
+// latency of scattered row reads, about 7 ns a row and compute unit whether 64, 128 or 256 bytes of
+// it are taken and with 256 to 1024 threads alike (without the reads a pass takes a quarter of the
+// time), so few heads gain from narrow slices, and many heads, which fill the chip as they are, from
+// whole rows.  us on MI355X with slices of 64 / 128 / 256 bytes, n = 16384 and 30 % retained unless
+// said otherwise, against one workgroup per head for both tensors: 8 heads of 131072 (20 %)
+// 175 / 197 / 254 (799), 16 heads of 40007 101 / 108 / 137 (376), 32 heads 55 / 55 / 68 (158; with
+// part of the pool in the last-level cache 40 / 43 / 46), 64 heads 102 / 77 / 82, 96 heads of 30000
+// (50 %) 448 / 377 / 319, 128 heads 194 / 153 / 137 (211), 256 heads of 32768 708 / 588 / 527 (536).
+constexpr int INPLACE_THREADS = 512;
+template <int LANES>
+struct Inplace {
+  static constexpr int PASSES = 8;                      // rows in flight per lane
+  static constexpr int ROWS = INPLACE_THREADS / LANES;  // rows per pass
+  static constexpr int RUN = ROWS * PASSES;             // rows per run
+  // rows whose addresses a thread works out
+  static constexpr int OWN = (RUN + INPLACE_THREADS - 1) / INPLACE_THREADS;
+  static constexpr int SLICES = 16 / LANES;             // column slices of a row
 };
+
+// Pages of the rows j (destination) and tok (source), -1 where the row does not move.
+struct RowPages { int src, dst, src_slot, dst_slot; };
+
+template <int LANES>
 __global__ __launch_bounds__(INPLACE_THREADS) void compact_inplace_kernel(
-    const SegTable T, const PagePool P, const int32_t *__restrict__ kept_idx,
+    const SegTable T, const PagePool P, int page_shift, const int32_t *__restrict__ kept_idx,
     const int32_t *__restrict__ kept_cnt) {
-  const Where w = locate_block(T, blockIdx.x, 0, 1, false);      // one block per head
+  typedef Inplace<LANES> I;
+  __shared__ long long src_l[3][I::RUN], dst_l[3][I::RUN];   // element offsets; -1: does not move
+  // blocks b, b + 8, b + 16, .. (one XCD, hence one L2) hold the slices of one head
+  const int parts = 2 * I::SLICES;
+  const int part = (blockIdx.x >> 3) % parts, oct = (blockIdx.x >> 3) / parts;
+  const int hb = 8 * oct + (blockIdx.x & 7);
+  if (hb >= T.nheads) return;
+  const Where w = locate_block(T, hb, 0, 1, false);      // heads in launch order
   const Seg &s = T.s[w.seg];
   const int layer = w.head / s.H, h = w.head - layer * s.H;
   int rows = s.k_keep;
@@ -245,54 +273,124 @@ __global__ __launch_bounds__(INPLACE_THREADS) void compact_inplace_kernel(
     rows = cnt[h];
   }
   const int32_t *idx = kept_idx + first;
-  const int chunk = threadIdx.x & 15, sub = threadIdx.x >> 4;    // 64 rows per pass
-  auto fetch = [&](int base, InplaceRun &r) {
+  const int32_t *table = P.t[w.seg].pages;
+  const int tlen = P.t[w.seg].len;
+  const int tid = threadIdx.x;
+  const int lane = tid & (LANES - 1), sub = tid / LANES;
+  uint16_t *base = (part & 1 ? P.v : P.k) + ((long long)layer * P.layer_stride + (long long)h * P.head_stride) +
+                   (part >> 1) * (LANES * 8) + lane * 8;
+
+  // The address of a row takes three dependent loads (its index, two table entries); they are
+  // spread over the runs before: indices three runs ahead, table entries two.  Each thread does
+  // this for rows of its own and leaves the offsets in LDS for the lanes that move them.
+  auto fetch_idx = [&](int run, int (&tok)[I::OWN]) {
 #pragma unroll
-    for (int p = 0; p < INPLACE_RUN / 64; ++p) {
-      const int j = base + p * 64 + sub;
-      r.dst[p] = -1;
-      r.kv[p] = make_uint4(0, 0, 0, 0);
-      r.vv[p] = make_uint4(0, 0, 0, 0);
-      if (j < rows) {
-        const int tok = idx[j];
-        const long long src = (tok >= j && tok < s.n) ? page_slot(P, w.seg, layer, h, tok) : -1;
-        if (src >= 0) {
-          r.kv[p] = load_stream16(P.k + src + chunk * 8);
-          r.vv[p] = load_stream16(P.v + src + chunk * 8);
-          r.dst[p] = tok == j ? -1 : page_slot(P, w.seg, layer, h, j);   // already in place
-        }
+    for (int o = 0; o < I::OWN; ++o) {
+      const int jr = o * INPLACE_THREADS + tid;
+      const unsigned j = (unsigned)run * I::RUN + jr;       // runs past the end may pass 2^31
+      tok[o] = -1;
+      if (jr < I::RUN && j < (unsigned)rows) tok[o] = idx[j];
+    }
+  };
+  auto split = [&](int j, int &lp, int &slot) {
+    if (page_shift >= 0) { lp = j >> page_shift; slot = j & (P.page_size - 1); }
+    else { lp = (int)((unsigned)j / (unsigned)P.page_size); slot = j - lp * P.page_size; }
+  };
+  auto fetch_pages = [&](int run, const int (&tok)[I::OWN], RowPages (&pg)[I::OWN]) {
+#pragma unroll
+    for (int o = 0; o < I::OWN; ++o) {
+      const int j = run * I::RUN + o * INPLACE_THREADS + tid;
+      pg[o] = RowPages{-1, -1, 0, 0};
+      if (tok[o] > j && tok[o] < s.n) {           // tok == j: already in place; below: skipped
+        int lp;
+        split(tok[o], lp, pg[o].src_slot);
+        if (lp < tlen) pg[o].src = table[lp];
+        split(j, lp, pg[o].dst_slot);
+        if (lp < tlen) pg[o].dst = table[lp];
       }
     }
   };
-  auto write = [&](const InplaceRun &r) {
+  auto put_moves = [&](int slot, const RowPages (&pg)[I::OWN]) {
 #pragma unroll
-    for (int p = 0; p < INPLACE_RUN / 64; ++p) {
-      if (r.dst[p] >= 0) {
-        store_stream16(P.k + r.dst[p] + chunk * 8, r.kv[p]);
-        store_stream16(P.v + r.dst[p] + chunk * 8, r.vv[p]);
+    for (int o = 0; o < I::OWN; ++o) {
+      const int jr = o * INPLACE_THREADS + tid;
+      if (jr < I::RUN) {
+        const bool ok = pg[o].src >= 0 && pg[o].src < P.num_pages && pg[o].dst >= 0 && pg[o].dst < P.num_pages;
+        src_l[slot][jr] = ok ? (long long)pg[o].src * P.page_stride + (long long)pg[o].src_slot * P.slot_stride : -1;
+        dst_l[slot][jr] = ok ? (long long)pg[o].dst * P.page_stride + (long long)pg[o].dst_slot * P.slot_stride : -1;
       }
     }
   };
-  InplaceRun a, b;
-  fetch(0, a);
-  for (int base = 0; base < rows; base += 2 * INPLACE_RUN) {
-    __syncthreads();      // every row of run `a` has been read (the barrier waits for the loads)
-    fetch(base + INPLACE_RUN, b);
-    write(a);
-    if (base + INPLACE_RUN >= rows) break;         // uniform
+  auto load_rows = [&](int slot, uint4 (&r)[I::PASSES]) {
+    long long src[I::PASSES];
+#pragma unroll
+    for (int p = 0; p < I::PASSES; ++p) src[p] = src_l[slot][p * I::ROWS + sub];
+#pragma unroll
+    for (int p = 0; p < I::PASSES; ++p) {
+      r[p] = make_uint4(0, 0, 0, 0);
+      if (src[p] >= 0)     // whole rows are read once; a 128-byte line shared by slices may be cached
+        r[p] = LANES == 16 ? load_stream16(base + src[p]) : *reinterpret_cast<const uint4 *>(base + src[p]);
+    }
+  };
+  auto store_rows = [&](int slot, const uint4 (&r)[I::PASSES]) {
+    long long dst[I::PASSES];
+#pragma unroll
+    for (int p = 0; p < I::PASSES; ++p) dst[p] = dst_l[slot][p * I::ROWS + sub];
+#pragma unroll
+    for (int p = 0; p < I::PASSES; ++p)
+      if (dst[p] >= 0) store_stream16(base + dst[p], r[p]);
+  };
+
+  int tok[I::OWN];
+  RowPages pg[I::OWN];
+  uint4 a[I::PASSES], b[I::PASSES];
+  const int runs = (rows + I::RUN - 1) / I::RUN;
+  fetch_idx(0, tok);
+  fetch_pages(0, tok, pg);
+  fetch_idx(1, tok);
+  put_moves(0, pg);
+  fetch_pages(1, tok, pg);
+  fetch_idx(2, tok);
+  __syncthreads();
+  load_rows(0, a);
+  // on entry of step r: the rows of run r are being read, pg holds run r + 1, tok run r + 2
+  auto step = [&](int r, uint4 (&cur)[I::PASSES], uint4 (&next)[I::PASSES]) {
+    put_moves((r + 1) % 3, pg);
+    // every wave waits for its own rows of run r before it meets the others (a barrier by itself
+    // does not wait for loads): behind the barrier all of them have been read
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    fetch(base + 2 * INPLACE_RUN, a);
-    write(b);
+    fetch_pages(r + 2, tok, pg);
+    fetch_idx(r + 3, tok);
+    load_rows((r + 1) % 3, next);
+    store_rows(r % 3, cur);
+  };
+  for (int r = 0; r < runs; r += 2) {
+    step(r, a, b);
+    if (r + 1 >= runs) break;                      // uniform
+    step(r + 1, b, a);
   }
+}
+
+template <int LANES>
+static hipError_t launch_inplace(const SegTable &T, const PagePool &P, const int32_t *kept_idx,
+                                 const int32_t *kept_cnt, hipStream_t st) {
+  const long long nb = ((long long)T.nheads + 7) / 8 * 8 * 2 * Inplace<LANES>::SLICES;
+  if (nb > 0x7fffffffll) return hipErrorInvalidValue;
+  const int shift = (P.page_size & (P.page_size - 1)) == 0 ? __builtin_ctz((unsigned)P.page_size) : -1;
+  hipLaunchKernelGGL((compact_inplace_kernel<LANES>), dim3((unsigned)nb), dim3(INPLACE_THREADS), 0, st, T, P, shift,
+                     kept_idx, kept_cnt);
+  return hipGetLastError();
 }
 
 hipError_t launch_gather_paged(const SegTable &T, const PagePool &P, const int32_t *kept_idx,
                                const int32_t *kept_cnt, bool in_place, hipStream_t st) {
   if (T.nheads <= 0) return hipSuccess;
   if (in_place) {
-    hipLaunchKernelGGL(compact_inplace_kernel, dim3((unsigned)T.nheads), dim3(INPLACE_THREADS), 0,
-                       st, T, P, kept_idx, kept_cnt);
-    return hipGetLastError();
+    // slices by the number of heads (see compact_inplace_kernel for the times on both sides)
+    if (T.nheads <= 16) return launch_inplace<4>(T, P, kept_idx, kept_cnt, st);
+    if (T.nheads <= 64) return launch_inplace<8>(T, P, kept_idx, kept_cnt, st);
+    return launch_inplace<16>(T, P, kept_idx, kept_cnt, st);
   }
   long long nb = 0;
   if (T.layer_scope) {

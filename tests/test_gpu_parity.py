@@ -772,6 +772,16 @@ def test_compact_into_pages(C, in_place):
     _paged_case(C, W.config1(DEV, L=1, H=1, n=5000, ratio=1.0), C.SCOPE_HEAD, 256, in_place, 34)
 
 
+
+# in place: 1 to 16, 17 to 64 and more heads take rows in slices of 64, 128 and 256 bytes, in runs of
+# 1024, 512 and 256 rows: heads at both edges, several runs and a remainder, pages of 2^k and other sizes
+@pytest.mark.parametrize("L,H,n,ratio,scope,page", [
+    (2, 8, 5003, 0.5, 0, 16), (1, 3, 2049, 1.0, 0, 7), (1, 17, 2601, 0.43, 0, 32), (8, 8, 1030, 0.5, 1, 16),
+    (13, 5, 1537, 0.34, 0, 100), (9, 8, 520, 0.99, 1, 1)])
+def test_compact_in_place_slices(C, L, H, n, ratio, scope, page):
+    _paged_case(C, W.config1(DEV, L=L, H=H, n=n, ratio=ratio), scope, page, True, 35)
+
+
 def test_compact_into_pages_error_codes(C):
     w = W.config2(DEV, L=1, H=2, n=300)
     params, reqs = U.make_call(C, w, DEV)
