@@ -135,7 +135,47 @@ __device__ __forceinline__ uint32_t score_key(float s) {
   const uint32_t u = __float_as_uint(s);
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
-constexpr int HIST1_BINS = 4096;      // first radix digit of the selection: the top 12 key bits
+
+// First digit of the selection, two ways.  Scores that leave the scoring kernels are tallied there by
+// their top 12 key bits (8 bins an octave).  Scores of a separate selection call are tallied by
+// score_bin, a monotone map of the keys to 3536 bins: magnitudes from 2^-20 up to 2^4, where leverage
+// scores and z-scores lie, have 64 bins an octave, the octaves outside one bin each; negative numbers
+// mirror the positive ones, and NaN shares the lowest bin with -inf (whose keys are larger).  Eight bins
+// an octave put a fifth to a quarter of a head's scores into the threshold's bin, and so many lanes of a
+// wave onto one LDS counter that a tally is bound by it (112 heads of 131072 tokens: tally 22 us against
+// 18, threshold 25 against 16).  A scoring workgroup has more to do than tally, and it adds its histogram
+// to the pool's: 64 bins an octave are eight times the adds, and the fused calls take 0.2 to 0.5 %
+// longer with them.
+constexpr int HIST1_BINS = 4096;      // either way (score_bin never counts 3536 ..)
+constexpr uint32_t BIN_LO = 107u << 6, BIN_HI = 131u << 6;   // the fine range, in float bits >> 17
+constexpr int BIN_SIDE = 1768;        // bins of either sign: 107 + 24 * 64 + 125
+__host__ __device__ __forceinline__ int score_bin(uint32_t key) {
+  const bool pos = (key & 0x80000000u) != 0;
+  const uint32_t x = ((pos ? key : ~key) & 0x7fffffffu) >> 17;
+  const uint32_t lo = x < BIN_LO ? x : BIN_LO, hi = x > BIN_HI ? x : BIN_HI;
+  const uint32_t in = x < BIN_LO ? BIN_LO : (x > BIN_HI ? BIN_HI : x);
+  const int m = (int)((lo >> 6) + (in - BIN_LO) + (hi >> 6) - (BIN_HI >> 6));
+  return pos ? BIN_SIDE + m : BIN_SIDE - 1 - m;
+}
+// Place of a bin in a pool's histogram in memory: groups of 4 bins stand 256 bytes apart, in different
+// memory channels, because many workgroups add to the same few dozen bins at the same time.
+__host__ __device__ __forceinline__ int hist_at(int bin) {
+  return (bin >> 2 & 63) << 6 | bin >> 8 << 2 | (bin & 3);
+}
+
+// Smallest key of a bin and the number of low bits in which the bin's keys differ.
+struct BinKeys { uint32_t lo; int bits; };
+__host__ __device__ __forceinline__ BinKeys bin_keys(int bin, bool fine) {
+  if (!fine) return BinKeys{(uint32_t)bin << 20, 20};
+  const bool pos = bin >= BIN_SIDE;
+  const int m = pos ? bin - BIN_SIDE : BIN_SIDE - 1 - bin;
+  const int fine_lo = (int)(BIN_LO >> 6), fine_hi = fine_lo + (int)(BIN_HI - BIN_LO);
+  const bool in = m >= fine_lo && m < fine_hi;
+  const int bits = in ? 17 : 23;
+  const uint32_t u = in ? (BIN_LO + (uint32_t)(m - fine_lo)) << 17
+                        : (uint32_t)(m < fine_lo ? m : m - fine_hi + (int)(BIN_HI >> 6)) << 23;
+  return BinKeys{pos ? 0x80000000u | u : (0x7fffffffu - u) & ~((1u << bits) - 1u), bits};
+}
 
 // Streaming (non-temporal) 16-byte accesses for data that is touched once per pass: they do
 // not allocate in the caches and sustain a higher HBM rate than ordinary loads (measured:
@@ -326,7 +366,7 @@ hipError_t launch_select(const SegTable &T, const float *scores, const int *hist
 
 // Selection by several workgroups per pool (long heads, or layer scope).  hist1: pools x 4096
 // ints; hist1_ready: it holds the histogram of the scores' top 12 key bits already (otherwise it
-// is cleared and tallied here).  sel: scratch of select_scratch(T).ints() ints (candidate lists,
+// is cleared and tallied here, by score_bin).  sel: scratch of select_scratch(T).ints() ints (candidate lists,
 // one slot per token of the launch; per-chunk records and offsets; per-pool state), none of which
 // needs clearing.
 struct SelectScratch {

@@ -358,8 +358,8 @@ __global__ __launch_bounds__(256, 2) void score_kernel(
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const int lo = (int)(wd[j] & 0xffffu), hi = (int)(wd[j] >> 16);
-      if (lo) atomicAdd(&h1[16 * tid + 2 * j], lo);
-      if (hi) atomicAdd(&h1[16 * tid + 2 * j + 1], hi);
+      if (lo) atomicAdd(&h1[hist_at(16 * tid + 2 * j)], lo);
+      if (hi) atomicAdd(&h1[hist_at(16 * tid + 2 * j + 1)], hi);
     }
   }
 }

@@ -1,8 +1,8 @@
 // Per-head top-k selection (paper Sec. 3.3: retain the top ceil(r N) tokens by score, within a
 // single head) and the score blend of Eq. "scoring".
 //
-// Selection is an exact radix select on an order-preserving 32-bit key of the fp32 score
-// (12 + 12 + 8 bits, LDS histograms), followed by an ordered emit: tokens above the threshold
+// Selection is an exact radix select on an order-preserving 32-bit key of the fp32 score (a bin of
+// 17 to 23 key bits, then 12 bits and the 5 to 11 left; LDS histograms), followed by an ordered emit: tokens above the threshold
 // key, plus the lowest-indexed tokens equal to it until k_keep is reached, written in
 // ascending token order.  Ties therefore go to the lower index, deterministically.
 // Heads of up to 32768 tokens get one workgroup of 1024 threads each, which reads the scores
@@ -70,19 +70,18 @@ __device__ __forceinline__ int find_digit(const int *hist, int nb, int *need, in
   return found[0];
 }
 
-// One radix pass: histogram `bits` bits at `shift` of the keys whose higher bits equal `prefix`
-// (hi_shift = 32 means no prefix), then find_digit.  Keys come from LDS (FROM_LDS) or are
-// recomputed from the scores in global memory; with STORE the keys are also parked in LDS.
-template <bool FROM_LDS, bool STORE>
-__device__ int radix_pass(const float *__restrict__ sp, uint32_t *keys, int n, int shift, int bits,
-                          int hi_shift, uint32_t prefix, int *need, int *hist, int *wsum,
-                          int *found) {
-  const int nb = 1 << bits;
+// One pass of the radix select: histogram of a digit (`nb` values) of the keys, then find_digit.
+// digit(key) gives the digit, or -1 for a key that is out already.  Keys come from LDS (FROM_LDS) or
+// are recomputed from the scores in global memory; with STORE the keys are also parked in LDS.
+template <bool FROM_LDS, bool STORE, class F>
+__device__ int radix_pass(const float *__restrict__ sp, uint32_t *keys, int n, F &&digit, int nb,
+                          int *need, int *hist, int *wsum, int *found) {
   const int tid = threadIdx.x;
   for (int i = tid; i < 4096; i += SELECT_THREADS) hist[i] = 0;
   __syncthreads();
   auto tally = [&](uint32_t k) {
-    if (hi_shift >= 32 || (k >> hi_shift) == prefix) atomicAdd(&hist[(k >> shift) & (nb - 1)], 1);
+    const int d = digit(k);
+    if (d >= 0) atomicAdd(&hist[d], 1);
   };
   // 16-byte accesses: the LDS keys are aligned by token; scores in global memory are read from
   // the first 16-byte boundary on, the `lead` tokens in front of it (and the tail) one by one
@@ -233,7 +232,7 @@ __global__ __launch_bounds__(SELECT_THREADS) void select_kernel(const SegTable T
                                                                 int32_t *__restrict__ kept_idx,
                                                                 int32_t *__restrict__ kept_cnt) {
   __shared__ __attribute__((aligned(16))) uint32_t keys[LDS_KEYS];
-  __shared__ int hist[4096];
+  __shared__ __attribute__((aligned(16))) int hist[4096];
   __shared__ int wsum[SELECT_THREADS / 64];
   __shared__ int found[2];
 
@@ -244,48 +243,60 @@ __global__ __launch_bounds__(SELECT_THREADS) void select_kernel(const SegTable T
   int32_t *out = kept_idx + (s.kept_off + (long long)w.head * k);
   const int tid = threadIdx.x;
   if (tid == 0) kept_cnt[s.ghead0 + w.head] = k;
-  // threshold key = the k-th largest, by three radix passes (12 + 12 + 8 bits); the scores are
+  // threshold key = the k-th largest, by three radix passes (bin, 12 bits, the rest); the scores are
   // read once and their keys stay in LDS for the later passes (n <= LDS_KEYS, checked on the host)
   int need = k;
-  uint32_t d1, d2, d3;
-  if (hist1 != nullptr) {                // first digit already tallied by the score kernel
+  if (hist1 != nullptr) {                // bins already tallied by the score kernel
     const int *h1 = hist1 + (size_t)w.lhead * HIST1_BINS;
-    for (int i = tid; i < HIST1_BINS; i += SELECT_THREADS) hist[i] = h1[i];
+    static_assert(HIST1_BINS == 4 * SELECT_THREADS, "four bins per thread");
+    *reinterpret_cast<int4 *>(&hist[4 * tid]) = *reinterpret_cast<const int4 *>(h1 + hist_at(4 * tid));
     __syncthreads();
-    d1 = find_digit(hist, HIST1_BINS, &need, wsum, found);
-    d2 = radix_pass<false, true>(sp, keys, n, 8, 12, 20, d1, &need, hist, wsum, found);
-  } else {
-    d1 = radix_pass<false, true>(sp, keys, n, 20, 12, 32, 0u, &need, hist, wsum, found);
-    d2 = radix_pass<true, false>(sp, keys, n, 8, 12, 20, d1, &need, hist, wsum, found);
   }
-  d3 = radix_pass<true, false>(sp, keys, n, 0, 8, 8, (d1 << 12) | d2, &need, hist, wsum, found);
-  emit_kept_lds(keys, n, k, (d1 << 20) | (d2 << 8) | d3, need, out, reinterpret_cast<unsigned *>(hist));
+  const int bin = hist1 != nullptr
+                      ? find_digit(hist, HIST1_BINS, &need, wsum, found)
+                      : radix_pass<false, true>(sp, keys, n, [](uint32_t q) { return score_bin(q); },
+                                                HIST1_BINS, &need, hist, wsum, found);
+  const BinKeys bk = bin_keys(bin, hist1 == nullptr);
+  const int bits = bk.bits, rest = bits - 12;
+  const uint32_t key1 = bk.lo;
+  auto digit2 = [&](uint32_t q) { return (q >> bits) == (key1 >> bits) ? (int)((q >> rest) & 0xfffu) : -1; };
+  const int d2 = hist1 != nullptr
+                     ? radix_pass<false, true>(sp, keys, n, digit2, 4096, &need, hist, wsum, found)
+                     : radix_pass<true, false>(sp, keys, n, digit2, 4096, &need, hist, wsum, found);
+  const uint32_t key2 = key1 | (uint32_t)d2 << rest;
+  const int d3 = radix_pass<true, false>(
+      sp, keys, n,
+      [&](uint32_t q) { return (q >> rest) == (key2 >> rest) ? (int)(q & ((1u << rest) - 1u)) : -1; },
+      1 << rest, &need, hist, wsum, found);
+  emit_kept_lds(keys, n, k, key2 | (uint32_t)d3, need, out, reinterpret_cast<unsigned *>(hist));
 }
 
 // ---- selection by several workgroups per pool ------------------------------------------------
 // Used when a head is too long for one workgroup's LDS, and for head-adaptive selection, where
 // the pool is the H kv heads of a layer that share one budget of H * k_keep tokens (paper Sec. 3.3:
 // the top scores "across all heads"; scoring stays per head).  The same radix select and ordered
-// emit as above, with the scores read twice in all.  A pool (head or layer) is cut into chunks of
+// emit as above, with the scores read once or twice in all.  A pool (head or layer) is cut into chunks of
 // up to 8192 tokens of one head, one workgroup each; three launches:
-//   cand   the first digit d1 of the threshold key comes from the pool's histogram of the top 12
-//          key bits (made by the score kernel, the blend, or msel_hist1_kernel).  Keys above d1
-//          are retained for sure and only counted; the keys inside d1 (the candidates: a few
-//          percent of the pool unless the scores are heavily tied) leave their low 20 bits in a
-//          per-chunk list
-//   thr    one workgroup per pool finds the remaining 12 + 8 bits of the threshold among the
+//   cand   the threshold's bin comes from the pool's histogram (made by the score kernel, the blend,
+//          or msel_hist1_kernel).  Keys above the bin are retained for sure and only marked and
+//          counted; the keys inside it (the candidates: 2 to 25 % of the pool unless the
+//          scores are heavily tied) are marked and leave their low 23 bits in a per-chunk list
+//   thr    one workgroup per pool finds the remaining bits of the threshold among the
 //          candidates and derives, chunk by chunk in (head, token) order, every chunk's output
 //          position and its allowance of threshold ties
-//   emit   ordered emit of every chunk
+//   emit   ordered emit of every chunk, from the marks and the candidates' scores
 // Everything is integer work on exact counts, so the result does not depend on the order in which
 // candidates are listed.  A chunk workgroup's chain (locate, load, classify, write) is latency
-// bound, so the chunk kernels are small workgroups of 256 threads held to 64 registers: eight of
-// them share a CU and overlap each other's waits (1024-thread workgroups on 32768-token chunks
-// moved 2.4 TB/s).
+// bound, so the chunk kernels are small workgroups of 256 threads held to 64 or 72 registers: seven or
+// eight of them share a CU and overlap each other's waits (1024-thread workgroups on 32768-token chunks
+// moved 2.4 TB/s).  What is left is vector issue, hence float comparisons and marks instead of keys: emit
+// 28.7 us before and 11.8 now for 112 heads of 131072 tokens,
+// 11.3 and 5.4 for 8 heads; cand 22.9 and 17.9, 9.8 and 7.4 (5, 6, 7 and 8 workgroups a CU: 19.1, 19.3,
+// 17.9, 21.1; at 8 it spills).
 constexpr int CHUNK_THREADS = 256;
 constexpr int SEL_ROUNDS = SEL_CHUNK / (4 * CHUNK_THREADS);    // 4-token groups per thread
 constexpr int SEL_STATE = 8;             // ints of state per pool:
-enum { ST_D1 = 0, ST_NEED1, ST_THR, ST_TIES };
+enum { ST_BIN = 0, ST_NEED1, ST_THR, ST_TIES };
 static_assert(SEL_ROUNDS >= 1 && SEL_ROUNDS <= 8, "one validity bit per token in 32 bits");
 
 struct SelWhere {
@@ -358,13 +369,54 @@ __device__ __forceinline__ unsigned load_chunk_scores(const float *__restrict__ 
                                                       float (&f)[SEL_ROUNDS][4]) {
   return load_scores_part<SEL_ROUNDS>(sp, q, 0, f);
 }
-__device__ __forceinline__ void scores_to_keys(const float (&f)[SEL_ROUNDS][4],
-                                               uint32_t (&key)[SEL_ROUNDS][4]) {
-#pragma unroll
-  for (int r = 0; r < SEL_ROUNDS; ++r)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) key[r][e] = score_key(f[r][e]);
+
+// The float of a key (score_key's inverse; -0.0 has no key of its own).
+__device__ __forceinline__ float key_score(uint32_t key) {
+  return __uint_as_float((key & 0x80000000u) ? key ^ 0x80000000u : ~key);
 }
+
+// Classification of scores against a key interval [lo, hi] (the threshold's bin): float comparisons where
+// they give the order of the keys, which is everywhere but at NaN (key 0, below every number) and just
+// below zero (-0.0 is compared as +0.0 but a float equal to it).
+struct KeyRange {
+  uint32_t lo, hi;
+  float flo, fhi;
+  bool plain;
+  __device__ __forceinline__ KeyRange(uint32_t l, uint32_t h) : lo(l), hi(h), flo(key_score(l)), fhi(key_score(h)) {
+    plain = l >= 0x007fffffu && h <= 0xff800000u && h != 0x7fffffffu;      // -inf .. +inf
+  }
+};
+
+// bits of the tokens of f (see load_scores_part) above the range and inside it
+__device__ __forceinline__ void classify(const float (&f)[SEL_ROUNDS][4], unsigned valid, const KeyRange &k,
+                                         unsigned &above, unsigned &in) {
+  above = in = 0;
+  if (k.plain) {
+#pragma unroll
+    for (int r = 0; r < SEL_ROUNDS; ++r)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        above |= f[r][e] > k.fhi ? 1u << (4 * r + e) : 0u;
+        in |= f[r][e] >= k.flo ? 1u << (4 * r + e) : 0u;
+      }
+  } else {
+#pragma unroll
+    for (int r = 0; r < SEL_ROUNDS; ++r)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const uint32_t q = score_key(f[r][e]);
+        above |= q > k.hi ? 1u << (4 * r + e) : 0u;
+        in |= q >= k.lo ? 1u << (4 * r + e) : 0u;
+      }
+  }
+  above &= valid;
+  in &= valid & ~above;
+}
+
+// Room for the marks of a chunk of `tokens` tokens: a pair of words (above the bin, inside it) per thread
+// that has tokens.  They stand at the end of the chunk's part of the candidate list, where the candidates
+// leave that much room (otherwise the emit reads the scores again).
+__device__ __forceinline__ int mark_ints(int tokens) { return 2 * min(CHUNK_THREADS, (tokens + 3) >> 2); }
 
 // find_digit on the 4096-digit histogram of a pool in global memory (16-byte aligned), by a
 // workgroup of CHUNK_THREADS.
@@ -375,7 +427,7 @@ __device__ __forceinline__ int find_digit_global(const int *__restrict__ g, int 
   int c[PER], sum = 0;
 #pragma unroll
   for (int u = 0; u < PER / 4; ++u) {
-    const int4 v = *reinterpret_cast<const int4 *>(g + NB - 4 - t0 - 4 * u);
+    const int4 v = *reinterpret_cast<const int4 *>(g + hist_at(NB - 4 - t0 - 4 * u));
     c[4 * u] = v.w; c[4 * u + 1] = v.z; c[4 * u + 2] = v.y; c[4 * u + 3] = v.x;
     sum += v.x + v.y + v.z + v.w;
   }
@@ -399,7 +451,7 @@ template <int NT>
 __device__ __forceinline__ void flush_hist(const int *hist, int nb, int *__restrict__ g) {
   for (int i = threadIdx.x; i < nb; i += NT) {
     const int c = hist[i];
-    if (c) atomicAdd(&g[i], c);
+    if (c) atomicAdd(&g[hist_at(i)], c);
   }
 }
 
@@ -415,21 +467,19 @@ __global__ __launch_bounds__(CHUNK_THREADS, 8) void msel_hist1_kernel(const SegT
   const unsigned valid = load_chunk_scores(sp, q, f);
   for (int i = threadIdx.x; i < 4096; i += CHUNK_THREADS) hist[i] = 0;
   __syncthreads();
-  uint32_t key[SEL_ROUNDS][4];
-  scores_to_keys(f, key);
 #pragma unroll
   for (int r = 0; r < SEL_ROUNDS; ++r)
 #pragma unroll
     for (int e = 0; e < 4; ++e)
-      if (valid >> (4 * r + e) & 1) atomicAdd(&hist[key[r][e] >> 20], 1);
+      if (valid >> (4 * r + e) & 1) atomicAdd(&hist[score_bin(score_key(f[r][e]))], 1);
   __syncthreads();
   flush_hist<CHUNK_THREADS>(hist, 4096, hist1 + (size_t)q.pool * 4096);
 }
 
-// Candidates of a chunk: counts the keys above the threshold's first digit and lists the low 20
-// bits of the keys inside it (cand, at the chunk's position in the launch's token sequence, so a
-// list can never outgrow its room).  rec[chunk] = (keys above, candidates listed).
-__global__ __launch_bounds__(CHUNK_THREADS, 6) void msel_cand_kernel(const SegTable T,
+// Candidates of a chunk: counts the keys above the threshold's bin and lists the low 23 bits of the
+// keys inside it (cand, at the chunk's position in the launch's token sequence, so a list can never
+// outgrow its room), and marks both kinds for the emit.  rec[chunk] = (keys above, candidates listed).
+__global__ __launch_bounds__(CHUNK_THREADS, 7) void msel_cand_kernel(const SegTable T, int fine,
                                                                   const float *__restrict__ scores,
                                                                   const int *__restrict__ hist1,
                                                                   uint32_t *__restrict__ cand,
@@ -446,45 +496,50 @@ __global__ __launch_bounds__(CHUNK_THREADS, 6) void msel_cand_kernel(const SegTa
   if (threadIdx.x == 0) { above_s = 0; ncand_s = 0; }
   const int ph = pool_heads(T, s);
   int need = ph * s.k_keep;
-  const uint32_t d1 = find_digit_global(hist1 + (size_t)q.pool * 4096, &need, wsum, found);
+  const int bin = find_digit_global(hist1 + (size_t)q.pool * HIST1_BINS, &need, wsum, found);
   if (q.tile == 0 && q.lhead % ph == 0 && threadIdx.x == 0) {   // the pool's first chunk
-    state[q.pool * SEL_STATE + ST_D1] = (int)d1;
+    state[q.pool * SEL_STATE + ST_BIN] = bin;
     state[q.pool * SEL_STATE + ST_NEED1] = need;
   }
+  const BinKeys bk = bin_keys(bin, fine != 0);
+  const KeyRange range(bk.lo, bk.lo | ((1u << bk.bits) - 1u));
+  unsigned above, in;
+  classify(f, valid, range, above, in);
   uint32_t *list = cand + chunk_token_base(T, q);
-  uint32_t key[SEL_ROUNDS][4];
-  scores_to_keys(f, key);
   const int lane = threadIdx.x & 63;
-  // A thread's candidates go to consecutive slots: count, scan inside the wave, one LDS add per
-  // wave for the wave's share of the list (the order in which waves claim theirs does not matter).
-  int above = 0, mine = 0;
-#pragma unroll
-  for (int r = 0; r < SEL_ROUNDS; ++r)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const bool v = valid >> (4 * r + e) & 1;
-      const uint32_t top = key[r][e] >> 20;
-      above += (v && top > d1) ? 1 : 0;
-      mine += (v && top == d1) ? 1 : 0;
-    }
-  int inc = mine;
+  // A thread's candidates go to consecutive slots: count, scan inside the wave (packed with the count
+  // above, at most 2048 each), one LDS add per wave for the wave's share of the list (the order in which
+  // waves claim theirs does not matter).
+  const int mine = __popc(in);
+  int inc = mine | (__popc(above) << 16);
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) {
     const int o = __shfl_up(inc, d);
     if (lane >= d) inc += o;
   }
   int base = 0;
-  if (lane == 63 && inc) base = atomicAdd(&ncand_s, inc);
-  int off = __shfl(base, 63) + inc - mine;
+  if (lane == 63) {
+    if (inc & 0xffff) base = atomicAdd(&ncand_s, inc & 0xffff);
+    if (inc >> 16) atomicAdd(&above_s, inc >> 16);
+  }
+  int off = __shfl(base, 63) + (inc & 0xffff) - mine;
+  // the keys of a bin share their sign: below it, a key's low bits are the complement of the float's
+  const uint32_t flip = (bk.lo & 0x80000000u) ? 0u : 0x7fffffu;
 #pragma unroll
   for (int r = 0; r < SEL_ROUNDS; ++r)
 #pragma unroll
     for (int e = 0; e < 4; ++e)
-      if ((valid >> (4 * r + e) & 1) && (key[r][e] >> 20) == d1) list[off++] = key[r][e] & 0xfffffu;
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) above += __shfl_xor(above, d);
-  if (lane == 0 && above) atomicAdd(&above_s, above);
+      if (in >> (4 * r + e) & 1) {
+        uint32_t v = (__float_as_uint(f[r][e]) & 0x7fffffu) ^ flip;
+        if (!range.plain) v = score_key(f[r][e]) & 0x7fffffu;
+        list[off++] = v;
+      }
   __syncthreads();
+  const int tokens = q.tok_end - q.tok_begin, marks = mark_ints(tokens);
+  if (ncand_s <= tokens - marks && 2 * (int)threadIdx.x < marks) {
+    list[tokens - marks + 2 * threadIdx.x] = above;
+    list[tokens - marks + 2 * threadIdx.x + 1] = in;
+  }
   if (threadIdx.x == 0) {
     rec[2 * blockIdx.x] = above_s;
     rec[2 * blockIdx.x + 1] = ncand_s;
@@ -492,15 +547,16 @@ __global__ __launch_bounds__(CHUNK_THREADS, 6) void msel_cand_kernel(const SegTa
 }
 
 // Visits the `cnt` values of a candidate list, f(value) for each: a wave's lanes take 4
-// consecutive values each with one 16-byte load (at any 4-byte address), two loads in flight.
+// consecutive values each with one 16-byte load (at any 4-byte address), four loads in flight.
 template <class F>
 __device__ __forceinline__ void for_each_cand(const uint32_t *__restrict__ l, int cnt, int lane, F &&f) {
   typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(4)));
-  for (int i = 4 * lane; i < cnt; i += 512) {
-    uint32_t v[2][4];
-    int have[2];
+  constexpr int DEPTH = 4;
+  for (int i = 4 * lane; i < cnt; i += 256 * DEPTH) {
+    uint32_t v[DEPTH][4];
+    int have[DEPTH];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
+    for (int h = 0; h < DEPTH; ++h) {
       const int j = i + 256 * h;
       have[h] = min(4, cnt - j);
       if (have[h] == 4) {
@@ -512,7 +568,7 @@ __device__ __forceinline__ void for_each_cand(const uint32_t *__restrict__ l, in
       }
     }
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
+    for (int h = 0; h < DEPTH; ++h)
 #pragma unroll
       for (int e = 0; e < 4; ++e)
         if (e < have[h]) f(v[h][e]);
@@ -522,15 +578,17 @@ __device__ __forceinline__ void for_each_cand(const uint32_t *__restrict__ l, in
 // One workgroup per pool: the threshold key from the pool's candidates, then for every chunk of
 // the pool (in head, token order) the position of its first retained token in the pool's
 // output and how many threshold ties it may keep; the per-head counts.
-// Two passes over the candidates: (1) histogram of their bits 19..8 -> second digit d2;
-// (2) per chunk the count above d2, a histogram of the low 8 bits of those inside d2, and those
-// few themselves as (chunk, low byte) in a short LDS list, from which, once the last digit is
+// Two passes over the candidates: (1) histogram of the upper 12 bits in which they differ -> second
+// digit d2; (2) per chunk the count above d2, a histogram of the low bits (5 or 11) of those inside d2,
+// and those few themselves as (chunk, low bits) in a short LDS list, from which, once the last digit is
 // known, every chunk's counts above and at the threshold follow.  If the list overflows (heavily
 // tied scores) or the pool has more than THR_BLOCK chunks, a third pass counts instead.
 // The chunks' records are fetched into LDS in blocks of THR_BLOCK (a load per chunk in turn
-// would string their latencies together); inside a block a wave takes every fourth chunk.
-constexpr int THR_THREADS = 256, THR_BLOCK = 512, THR_SHORT = 2048;
-__global__ __launch_bounds__(THR_THREADS) void msel_thr_kernel(const SegTable T,
+// would string their latencies together); inside a block a wave takes every 16th chunk.  The passes
+// wait for loads, not for arithmetic: with 4 waves a wave went through four chunks of a head of 131072
+// tokens one after the other (13.3 us for the kernel, now 11.3; 112 such heads 15.8 and 11.3).
+constexpr int THR_THREADS = 1024, THR_BLOCK = 512, THR_SHORT = 2048;
+__global__ __launch_bounds__(THR_THREADS) void msel_thr_kernel(const SegTable T, int fine,
                                                                const uint32_t *__restrict__ cand,
                                                                const int *__restrict__ rec,
                                                                int *__restrict__ coff,
@@ -569,34 +627,37 @@ __global__ __launch_bounds__(THR_THREADS) void msel_thr_kernel(const SegTable T,
     __syncthreads();
   };
 
-  const uint32_t d1 = (uint32_t)state[pool * SEL_STATE + ST_D1];
+  const BinKeys bk = bin_keys(state[pool * SEL_STATE + ST_BIN], fine != 0);
+  const uint32_t key1 = bk.lo;
+  const int rest = bk.bits - 12;
+  const uint32_t low = (1u << rest) - 1u;
   int need = state[pool * SEL_STATE + ST_NEED1];
 
-  // pass 1: bits 19..8 of every candidate
+  // pass 1: the upper 12 bits of every candidate
   for (int i = tid; i < 4096; i += THR_THREADS) hist[i] = 0;
   if (tid == 0) nshort = 0;
   for (int cb = 0; cb < nchunks; cb += THR_BLOCK) {
     fetch(cb);
     for (int u = wave; u < THR_BLOCK && cb + u < nchunks; u += NW)
       for_each_cand(list_of(cb + u), cnt_c[u], lane,
-                    [&](uint32_t v) { atomicAdd(&hist[(v >> 8) & 0xfffu], 1); });
+                    [&](uint32_t v) { atomicAdd(&hist[(v >> rest) & 0xfffu], 1); });
   }
   __syncthreads();
   const uint32_t d2 = (uint32_t)find_digit<THR_THREADS>(hist, 4096, &need, wsum, found);
-  // pass 2: bits 7..0 of the candidates that share the second digit; per chunk those above it
-  for (int i = tid; i < 256; i += THR_THREADS) hist[i] = 0;
+  // pass 2: the low bits of the candidates that share the second digit; per chunk those above it
+  for (int i = tid; i <= (int)low; i += THR_THREADS) hist[i] = 0;
   for (int cb = 0; cb < nchunks; cb += THR_BLOCK) {
     if (!single) fetch(cb); else __syncthreads();
     for (int u = wave; u < THR_BLOCK && cb + u < nchunks; u += NW) {
       int gt = 0;
       for_each_cand(list_of(cb + u), cnt_c[u], lane, [&](uint32_t v) {
-        const uint32_t top = v >> 8;
+        const uint32_t top = (v >> rest) & 0xfffu;
         gt += top > d2;
         if (top == d2) {
-          atomicAdd(&hist[v & 0xffu], 1);
+          atomicAdd(&hist[v & low], 1);
           if (single) {
             const int at = atomicAdd(&nshort, 1);
-            if (at < THR_SHORT) short_l[at] = ((uint32_t)u << 8) | (v & 0xffu);
+            if (at < THR_SHORT) short_l[at] = ((uint32_t)u << 11) | (v & low);
           }
         }
       });
@@ -606,34 +667,34 @@ __global__ __launch_bounds__(THR_THREADS) void msel_thr_kernel(const SegTable T,
     }
   }
   __syncthreads();
-  const uint32_t d3 = (uint32_t)find_digit<THR_THREADS>(hist, 256, &need, wsum, found);
+  const uint32_t d3 = (uint32_t)find_digit<THR_THREADS>(hist, 1 << rest, &need, wsum, found);
   const int tie_keep = need;             // keys equal to the threshold that are retained
-  const uint32_t thr20 = (d2 << 8) | d3;
+  const uint32_t thr = key1 | (d2 << rest) | d3, thr23 = thr & 0x7fffffu;
   if (tid == 0) {
-    state[pool * SEL_STATE + ST_THR] = (int)((d1 << 20) | thr20);
+    state[pool * SEL_STATE + ST_THR] = (int)thr;
     state[pool * SEL_STATE + ST_TIES] = tie_keep;
   }
   const bool from_short = single && nshort <= THR_SHORT;
   if (from_short) {                      // the chunks' counts at the last digit, from the short list
     for (int i = tid; i < nshort; i += THR_THREADS) {
       const uint32_t e = short_l[i];
-      const uint32_t low = e & 0xffu;
-      if (low > d3) atomicAdd(&gt_c[e >> 8], 1);
-      else if (low == d3) atomicAdd(&eq_c[e >> 8], 1);
+      const uint32_t l = e & 0x7ffu;
+      if (l > d3) atomicAdd(&gt_c[e >> 11], 1);
+      else if (l == d3) atomicAdd(&eq_c[e >> 11], 1);
     }
   }
 
-  // every chunk's output position and tie allowance: thread 0 runs the prefix over the chunks in
-  // order, a block at a time
-  int pos = 0, eq_before = 0, head_kept = 0;
+  // every chunk's output position and tie allowance: prefix sums over the chunks in order, a block at a
+  // time; a head's count is the distance between the positions at its ends
+  int pos = 0, eq_before = 0, head_pos = 0;      // head_pos: where the head that a block begins in starts
   for (int cb = 0; cb < nchunks; cb += THR_BLOCK) {
     if (!from_short) {                   // pass 3: count against the full threshold
       if (!single) fetch(cb); else __syncthreads();
       for (int u = wave; u < THR_BLOCK && cb + u < nchunks; u += NW) {
         int gt = 0, eq = 0;
         for_each_cand(list_of(cb + u), cnt_c[u], lane, [&](uint32_t v) {
-          gt += v > thr20;
-          eq += v == thr20;
+          gt += v > thr23;
+          eq += v == thr23;
         });
 #pragma unroll
         for (int d = 32; d >= 1; d >>= 1) {
@@ -644,125 +705,152 @@ __global__ __launch_bounds__(THR_THREADS) void msel_thr_kernel(const SegTable T,
       }
     }
     __syncthreads();
-    if (tid == 0) {
-      for (int u = 0; u < THR_BLOCK && cb + u < nchunks; ++u) {
-        const int cc = cb + u;
-        const int allow = max(0, min(eq_c[u], tie_keep - eq_before));
-        const int kept = above_c[u] + gt_c[u] + allow;
-        *reinterpret_cast<int2 *>(coff + 2 * (chunk0 + cc)) = make_int2(pos, allow);
-        pos += kept;
-        eq_before += eq_c[u];
-        head_kept += kept;
-        if ((cc + 1) % bph == 0) {       // last chunk of a head
-          kept_cnt[s.ghead0 + head0 + cc / bph] = T.layer_scope ? head_kept : s.k_keep;
-          head_kept = 0;
-        }
-      }
+    const int cc = cb + tid;
+    const bool mine = tid < THR_BLOCK && cc < nchunks;
+    const int eq = mine ? eq_c[tid] : 0;
+    int eq_all, kept_all;
+    const int eq0 = eq_before + block_exclusive_scan<THR_THREADS>(eq, wsum, &eq_all);
+    const int allow = max(0, min(eq, tie_keep - eq0));
+    const int kept = mine ? above_c[tid] + gt_c[tid] + allow : 0;
+    const int at = pos + block_exclusive_scan<THR_THREADS>(kept, wsum, &kept_all);
+    if (mine) {
+      *reinterpret_cast<int2 *>(coff + 2 * (chunk0 + cc)) = make_int2(at, allow);
+      eq_c[tid] = at;                    // this chunk's count has been read
     }
+    __syncthreads();
+    const int hc = cc - cc % bph;        // first chunk of the head
+    if (mine && cc - hc == bph - 1) {    // its last
+      const int start = hc >= cb ? eq_c[hc - cb] : head_pos;
+      kept_cnt[s.ghead0 + head0 + cc / bph] = T.layer_scope ? at + kept - start : s.k_keep;
+    }
+    const int open = (cb + THR_BLOCK) / bph * bph;      // the head that the next block begins in
+    if (open >= cb + THR_BLOCK) head_pos = pos + kept_all;
+    else if (open >= cb && open < nchunks) head_pos = eq_c[open - cb];
+    pos += kept_all;
+    eq_before += eq_all;
   }
 }
 
-// Ordered emit of one chunk.  Token order inside a chunk is (round, wave, lane, element), so a
-// token's output position is the sum of four prefixes: rounds before it, waves before it in its
-// round, lanes before it in its wave, elements before it in its lane.  The lane prefix is a
-// wave scan, the other two come from one table of (round, wave) counts scanned once: two
-// workgroup barriers in all.  Counts are packed as (above | equal << 16), at most 8192 each.
-__global__ __launch_bounds__(CHUNK_THREADS, 6) void msel_emit_kernel(const SegTable T,
+// Ordered emit of one chunk.  The marks of the candidate pass say which tokens lie above the threshold's
+// bin and which inside it; only the scores of the latter are read again and compared with the threshold
+// (few with 64 bins an octave; with 8, or with heavy ties, most threads have some and whole rows are read,
+// as they are where the candidates left no room for marks).  Four tokens per thread and round come in:
+// a byte per such group passes through LDS, so that a thread then holds 32 consecutive tokens and one scan
+// over the workgroup gives every position.  Counts are packed as (above | equal << 16), at most 8192 each.
+__global__ __launch_bounds__(CHUNK_THREADS, 8) void msel_emit_kernel(const SegTable T,
                                                                    const float *__restrict__ scores,
+                                                                   const uint32_t *__restrict__ cand,
+                                                                   const int *__restrict__ rec,
                                                                    const int *__restrict__ coff,
                                                                    const int *__restrict__ state,
                                                                    int32_t *__restrict__ kept_idx) {
   constexpr int NW = CHUNK_THREADS / 64;
   constexpr int EMIT_STAGE = 4096;
-  __shared__ unsigned table[SEL_ROUNDS * NW];
-  __shared__ unsigned total_s;
+  __shared__ unsigned wtot[NW];
+  __shared__ __attribute__((aligned(8))) unsigned char quad[SEL_ROUNDS * CHUNK_THREADS];
   __shared__ int stage[EMIT_STAGE];
   const SelWhere q = sel_locate(T, blockIdx.x);
   const Seg &s = T.s[q.seg];
   const float *sp = scores + s.score_off + (long long)q.head * s.n;
-  float f[SEL_ROUNDS][4];
-  const unsigned valid = load_chunk_scores(sp, q, f);    // in flight with the three loads below
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tokens = q.tok_end - q.tok_begin, marks = mark_ints(tokens);
+  const uint32_t *mark = cand + chunk_token_base(T, q) + (tokens - marks);
+  unsigned gt = 0, in = 0, eq = 0;
+  if (2 * tid < marks && marks <= tokens) { gt = mark[2 * tid]; in = mark[2 * tid + 1]; }
+  const int ncand = rec[2 * blockIdx.x + 1];
   const int ph = pool_heads(T, s);
   const int limit = ph * s.k_keep;                       // rows of the pool's output
   int32_t *out = kept_idx + (s.kept_off + (long long)(q.head / ph) * limit);
   const uint32_t thr = (uint32_t)state[q.pool * SEL_STATE + ST_THR];
   const int2 pa = *reinterpret_cast<const int2 *>(coff + 2 * blockIdx.x);
   const int pos0 = pa.x, allow = pa.y;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  uint32_t key[SEL_ROUNDS][4];
-  scores_to_keys(f, key);
-
-  unsigned before[SEL_ROUNDS];      // packed counts of the lanes before this one, per round
+  // key > thr and key == thr as float comparisons; a threshold that is NaN (key 0) equals NaN only and
+  // every number lies above it
+  const float fthr = key_score(thr);
+  auto is_gt = [&](float x) { return thr ? x > fthr : x == x; };
+  auto is_eq = [&](float x) { return thr ? x == fthr : x != x; };
+  auto token_of = [&](int bit) { return q.tok_begin + 4 * ((bit >> 2) * CHUNK_THREADS + tid) + (bit & 3); };
+  constexpr int FEW = 4;
+  if (ncand > tokens - marks || __any(__popc(in) > FEW)) {
+    if (ncand > tokens - marks) gt = 0;
+    float f[SEL_ROUNDS][4];
+    const unsigned valid = load_chunk_scores(sp, q, f);
+    const unsigned look = ncand > tokens - marks ? valid : in;
 #pragma unroll
-  for (int r = 0; r < SEL_ROUNDS; ++r) {
-    unsigned mine = 0;
+    for (int r = 0; r < SEL_ROUNDS; ++r)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const bool v = valid >> (4 * r + e) & 1;
-      mine += (v && key[r][e] > thr) ? 1u : 0u;
-      mine += (v && key[r][e] == thr) ? 0x10000u : 0u;
+      for (int e = 0; e < 4; ++e) {
+        const unsigned bit = look & (1u << (4 * r + e));
+        gt |= is_gt(f[r][e]) ? bit : 0u;
+        eq |= is_eq(f[r][e]) ? bit : 0u;
+      }
+  } else {
+    float f[FEW];
+    unsigned bit[FEW];
+#pragma unroll
+    for (int j = 0; j < FEW; ++j) {
+      bit[j] = in & (0u - in);
+      f[j] = 0.f;
+      if (in) f[j] = sp[token_of(__ffs(in) - 1)];
+      in &= in - 1;
     }
-    unsigned inc = mine;
 #pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const unsigned o = __shfl_up(inc, d);
-      if (lane >= d) inc += o;
+    for (int j = 0; j < FEW; ++j) {
+      gt |= is_gt(f[j]) ? bit[j] : 0u;
+      eq |= is_eq(f[j]) ? bit[j] : 0u;
     }
-    before[r] = inc - mine;
-    if (lane == 63) table[r * NW + wave] = inc;
   }
+#pragma unroll
+  for (int r = 0; r < SEL_ROUNDS; ++r)
+    quad[r * CHUNK_THREADS + tid] = (unsigned char)((gt >> (4 * r) & 0xfu) | (eq >> (4 * r) & 0xfu) << 4);
   __syncthreads();
-  if (wave == 0) {                   // exclusive scan of the SEL_ROUNDS * NW entries
-    constexpr int PER = (SEL_ROUNDS * NW + 63) / 64;
-    unsigned v[PER], sum = 0;
+  // this thread's tokens are now tok_begin + 32 * tid ..: low and high nibbles of 8 bytes
+  const uint2 by = *reinterpret_cast<const uint2 *>(&quad[8 * tid]);
+  auto nibbles = [](unsigned lo, unsigned hi) {          // the low nibbles of 8 bytes, 4 bits each
+    auto four = [](unsigned x) {
+      x &= 0x0f0f0f0fu;
+      x = (x | x >> 4) & 0x00ff00ffu;
+      return (x | x >> 8) & 0xffffu;
+    };
+    return four(lo) | four(hi) << 16;
+  };
+  unsigned keep = nibbles(by.x, by.y);
+  unsigned ties = nibbles(by.x >> 4, by.y >> 4);
+  const unsigned mine = (unsigned)__popc(keep) | (unsigned)__popc(ties) << 16;
+  unsigned inc = mine;
 #pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int idx = lane * PER + i;
-      v[i] = idx < SEL_ROUNDS * NW ? table[idx] : 0u;
-      sum += v[i];
-    }
-    unsigned inc = sum;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const unsigned o = __shfl_up(inc, d);
-      if (lane >= d) inc += o;
-    }
-    unsigned run = inc - sum;
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int idx = lane * PER + i;
-      if (idx < SEL_ROUNDS * NW) table[idx] = run;
-      run += v[i];
-    }
-    if (lane == 63) total_s = run;
+  for (int d = 1; d < 64; d <<= 1) {
+    const unsigned o = __shfl_up(inc, d);
+    if (lane >= d) inc += o;
   }
+  if (lane == 63) wtot[wave] = inc;
   __syncthreads();
+  unsigned before = inc - mine, all = 0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    before += w < wave ? wtot[w] : 0u;
+    all += wtot[w];
+  }
+  const int ties_before = (int)(before >> 16);
+  for (int left = allow - ties_before; ties && left > 0; --left) {
+    keep |= ties & (0u - ties);
+    ties &= ties - 1;
+  }
   // the chunk's retained tokens are consecutive in the output: they are gathered in LDS and
   // written out as one run (what does not fit the stage goes straight to memory)
-#pragma unroll
-  for (int r = 0; r < SEL_ROUNDS; ++r) {
-    if (q.tok_begin + 4 * r * CHUNK_THREADS >= q.tok_end) break;       // uniform
-    const unsigned p = table[r * NW + wave] + before[r];
-    int pg = (int)(p & 0xffffu), pe = (int)(p >> 16);
-    const int i0 = q.tok_begin + 4 * (r * CHUNK_THREADS + (int)threadIdx.x);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      if (valid >> (4 * r + e) & 1) {
-        const bool is_gt = key[r][e] > thr, is_eq = key[r][e] == thr;
-        if (is_gt || (is_eq && pe < allow)) {
-          const int lp = pg + min(pe, allow);
-          if (lp < EMIT_STAGE) stage[lp] = i0 + e;
-          else if (pos0 + lp < limit) out[pos0 + lp] = i0 + e;
-        }
-        pg += is_gt;
-        pe += is_eq;
-      }
-    }
+  int at = (int)(before & 0xffffu) + min(ties_before, allow);
+  const int tok0 = q.tok_begin + 32 * tid;
+  while (keep) {
+    const int tok = tok0 + __ffs(keep) - 1;
+    if (at < EMIT_STAGE) stage[at] = tok;
+    else if (pos0 + at < limit) out[pos0 + at] = tok;
+    ++at;
+    keep &= keep - 1;
   }
   __syncthreads();
-  const int total = (int)(total_s & 0xffffu) + min((int)(total_s >> 16), allow);
+  const int total = (int)(all & 0xffffu) + min((int)(all >> 16), allow);
   const int staged = min(min(total, EMIT_STAGE), limit - pos0);
-  for (int j = threadIdx.x; j < staged; j += CHUNK_THREADS) out[pos0 + j] = stage[j];
+  for (int j = tid; j < staged; j += CHUNK_THREADS) out[pos0 + j] = stage[j];
 }
 
 // ---- blend: s = z(a) + lambda z(o) (paper Eq. "scoring"), population standard deviation ------
@@ -908,6 +996,7 @@ hipError_t launch_select_pools(const SegTable &T, const float *scores, int *hist
   uint32_t *cand = reinterpret_cast<uint32_t *>(sel);
   int *rec = sel + z.cand_ints, *coff = rec + z.rec_ints, *state = coff + z.coff_ints;
   const unsigned nb = (unsigned)z.chunks;
+  const int fine = hist1_ready ? 0 : 1;      // see score_bin
   if (!hist1_ready) {
     hipLaunchKernelGGL(fill_zero_kernel, dim3(256), dim3(256), 0, st, hist1,
                        (long long)z.pools * HIST1_BINS);
@@ -915,14 +1004,14 @@ hipError_t launch_select_pools(const SegTable &T, const float *scores, int *hist
     hipLaunchKernelGGL(msel_hist1_kernel, dim3(nb), dim3(CHUNK_THREADS), 0, st, T, scores, hist1);
     if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
   }
-  hipLaunchKernelGGL(msel_cand_kernel, dim3(nb), dim3(CHUNK_THREADS), 0, st, T, scores, hist1, cand,
-                     rec, state);
+  hipLaunchKernelGGL(msel_cand_kernel, dim3(nb), dim3(CHUNK_THREADS), 0, st, T, fine, scores, hist1,
+                     cand, rec, state);
   if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
-  hipLaunchKernelGGL(msel_thr_kernel, dim3((unsigned)z.pools), dim3(THR_THREADS), 0, st, T, cand,
+  hipLaunchKernelGGL(msel_thr_kernel, dim3((unsigned)z.pools), dim3(THR_THREADS), 0, st, T, fine, cand,
                      rec, coff, state, kept_cnt);
   if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
-  hipLaunchKernelGGL(msel_emit_kernel, dim3(nb), dim3(CHUNK_THREADS), 0, st, T, scores, coff,
-                     state, kept_idx);
+  hipLaunchKernelGGL(msel_emit_kernel, dim3(nb), dim3(CHUNK_THREADS), 0, st, T, scores, cand, rec,
+                     coff, state, kept_idx);
   return hipGetLastError();
 }
 

@@ -111,6 +111,38 @@ def test_select_across_the_heads_of_a_layer(C):
                  scope=C.SCOPE_LAYER)
 
 
+
+def _bin_edges(r, m):
+    """Both sides of bin edges of either sign, from denormals to the largest floats, and both zeros."""
+    e = np.ldexp(1.0 + r.integers(0, 64, m) / 64.0, r.integers(-149, 128, m)).astype(np.float32)
+    near = np.ldexp(1.0 + r.integers(0, 64, m) / 64.0, r.integers(-22, 6, m)).astype(np.float32)
+    s = np.where(r.random(m) < 0.3, e, near)
+    s = np.where(r.random(m) < 0.5, np.nextafter(s, np.float32(0)), s) * r.choice([-1.0, 1.0], m)
+    s[r.integers(0, m, m // 40 + 1)] = 0.0
+    s[r.integers(0, m, m // 40 + 1)] = -0.0
+    return s.astype(np.float32)
+
+
+def _half_in_one_bin(r, m):      # chunks with and without room for marks, few and many candidates a thread
+    run = (np.arange(m) // 3000 % 4) / 4.0
+    return np.where(r.random(m) < run, 1.0 + r.random(m) / 70.0, 3.0 * r.random(m))
+
+
+# thresholds in every kind of bin, the remainders of a chunk, and layers of more chunks than one block of
+# records holds, with heads that straddle two blocks
+@pytest.mark.parametrize("maker", [_bin_edges, _half_in_one_bin], ids=["edges", "half"])
+@pytest.mark.parametrize("L,H,ns,ratios,scope", [
+    (2, 2, [3001, 40003, 8193], [0.02, 0.5, 0.97], 0), (1, 2, [131075], [0.31], 0),
+    (2, 3, [3, 9, 1027, 8195, 33000], [0.4, 0.5, 0.03, 0.9, 0.6], 1), (1, 600, [10], [0.3], 1),
+    (1, 180, [17001], [0.2], 1)])
+def test_select_bins_and_marks(C, maker, L, H, ns, ratios, scope):
+    _select_case(C, ns, ratios, L, H, maker, 8, scope=scope)
+
+
+def test_select_many_chunks_all_equal(C):
+    _select_case(C, [17001], [0.4], 1, 180, lambda r, m: np.full(m, -0.5), 9, scope=C.SCOPE_LAYER)
+
+
 def test_layer_scope_compress_end_to_end(C):
     _say("compress, layer scope: config 2 shape (L=2, H=4, n=3000) and a ragged batch")
     for w in (W.config2(DEV, L=2, H=4, n=3000), W.config4(DEV, L=1, H=3, n_req=3, n_lo=500, n_hi=2500)):
