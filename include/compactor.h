@@ -292,7 +292,11 @@ typedef struct compactor_attn_params {
   float   scale;          /* logit scale; 0 = 1/sqrt(head_dim) */
 } compactor_attn_params_t;
 
-/* Bytes of device workspace compactor_attention_scores needs (the unpooled sums). host. */
+/* Bytes of device workspace for compactor_attention_scores (the unpooled sums). host.  A call of few
+ * blocks is shared by up to 4 workgroups per block, each with sums of its own, and asks for room for
+ * them; a workspace that holds the sums only once (4 * sum_b L*H*n_b bytes, rounded up to 256) is
+ * accepted too: the same sums are then added in another order.  Like compactor_workspace_size the
+ * answer depends on the current HIP device's compute units. */
 int compactor_attention_workspace_size(const compactor_attn_params_t *p,
                                        const compactor_attn_request_t *reqs, int32_t nreq,
                                        size_t *bytes);

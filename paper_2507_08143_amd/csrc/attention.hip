@@ -12,6 +12,9 @@
 // see a quarter of a query's keys; they exchange (max, sum) once per step through LDS and
 // merge them as in an online softmax.  The column sums accumulate in 32 registers per lane and
 // are reduced across lanes once per block.
+//
+// Where the blocks leave compute units idle, the queries of a block are shared by several workgroups,
+// each with column sums of its own, which the pooling adds in order (see query_parts).
 #include <math.h>
 #include <string.h>
 
@@ -41,6 +44,8 @@ struct AttnTable {
   int nseg;
   float scale;
   int pool;
+  int parts;              // workgroups that share the queries of a block
+  long long part_floats;  // floats from the sums of one part to those of the next
 };
 
 // Exchange between the two halves of a wave with the row-swap instruction of gfx950: after
@@ -73,15 +78,16 @@ struct AttnLds {
   float st_l[2][4][ATT_QB];          //           and the sum of its exponentials
 };
 
-// One (kv-head, block) of the column sums.  RAGGED is the last block of a head whose length is
+// Steps step0 .. step0 + nsteps - 1 (64 queries of one query head each) of one (kv-head, block) of the
+// column sums.  RAGGED is the last block of a head whose length is
 // not a multiple of the block: only there keys and queries past the end have to be masked.
 //
 // The products are 32x32x16 MFMAs: D[key][query] leaves lane l with 16 keys of query l & 31
 // (keys 8*(v>>2) + 4*(l>>5) + (v&3), v = 0..15), so a query's 64 keys of this wave are the 32
 // registers of two key tiles in lanes l and l ^ 32.
 template <bool RAGGED>
-__device__ __forceinline__ void attn_block(const AttnSeg &s, float scale, int head, int c0,
-                                           AttnLds &L, float *__restrict__ raw) {
+__device__ __forceinline__ void attn_block(const AttnSeg &s, float scale, int head, int c0, int step0,
+                                           int nsteps, AttnLds &L, float *__restrict__ raw) {
   const int n = s.n;
   const int layer = head / s.H, kvh = head - layer * s.H;
   const uint16_t *kp = s.k + (long long)layer * s.k_stride_l + (long long)kvh * s.k_stride_h;
@@ -116,7 +122,6 @@ __device__ __forceinline__ void attn_block(const AttnSeg &s, float scale, int he
   // shorter than the latency of a load while the memory system is busy).  One such load of a
   // wave moves four rows: lane l brings a 16-byte piece of row l >> 4 to LDS position
   // base + 16 l, which is position l & 15 of that row; it fetches the piece that belongs there.
-  const int nsteps = s.G * (ATT_C / ATT_QB);          // (query head of the group, 64-query block)
   const int wv = __builtin_amdgcn_readfirstlane(wave);
   const int ld_row = 4 * wv + (lane >> 4);            // row within a group of 16
   const int ld_piece = (lane & 15) ^ (ld_row & 15);
@@ -124,8 +129,8 @@ __device__ __forceinline__ void attn_block(const AttnSeg &s, float scale, int he
   // this lane's piece of row c0 + ld_row of the group's first query head; a step adds an offset
   // that is the same for all lanes
   const uint16_t *q_lane = q_head0 + (long long)(c0 + ld_row) * s.q_stride_t + ld_piece * 8;
-  auto issue_q = [&](int step) {
-    const int qh = step / (ATT_C / ATT_QB), r0 = (step % (ATT_C / ATT_QB)) * ATT_QB;
+  auto issue_q = [&](int step) {                      // step counts from step0, as below
+    const int qh = (step0 + step) / (ATT_C / ATT_QB), r0 = ((step0 + step) % (ATT_C / ATT_QB)) * ATT_QB;
     uint16_t *dst = &L.ql[step % ATT_QBUF][4 * wv * D];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -169,8 +174,8 @@ __device__ __forceinline__ void attn_block(const AttnSeg &s, float scale, int he
   // are therefore written out.  Loads complete in order and every step issues four per wave, so
   // "at most 8 outstanding" means: everything up to the next step's tile has arrived.
   issue_q(0);
-  issue_q(1);
-  issue_q(2);
+  if (nsteps > 1) issue_q(1);
+  if (nsteps > 2) issue_q(2);
   asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
   product(0, 0);
 
@@ -185,6 +190,9 @@ __device__ __forceinline__ void attn_block(const AttnSeg &s, float scale, int he
     // e = 2^(c*s - m) with c = scale * log2(e), so an element costs half a max3, one fma, one
     // exp and one add.  The product of the second query tile is issued ahead of the arithmetic
     // of the first.
+    // A wave in this stretch goes first, so that the other one of its SIMD is left to wait at its barrier
+    // or for its products (4 layers of 32768 tokens 412 us without and 409 with it).
+    __builtin_amdgcn_s_setprio(1);
     float m_mine = 0.f, l_mine = 0.f;    // statistics of query `lane` of the step (tile lh)
 #pragma unroll
     for (int qt = 0; qt < 2; ++qt) {
@@ -224,6 +232,7 @@ __device__ __forceinline__ void attn_block(const AttnSeg &s, float scale, int he
         l_mine = l;
       }
     }
+    __builtin_amdgcn_s_setprio(0);
     L.st_m[sb][wave][lane] = m_mine;
     L.st_l[sb][wave][lane] = l_mine;
 
@@ -245,7 +254,7 @@ __device__ __forceinline__ void attn_block(const AttnSeg &s, float scale, int he
     for (int w2 = 0; w2 < 4; ++w2) l = fmaf(L.st_l[sb][w2][lane], __builtin_amdgcn_exp2f(mw[w2] - m), l);
     float f = __builtin_amdgcn_exp2f(m_mine - m) * __builtin_amdgcn_rcpf(l);
     if (RAGGED) {
-      const int q0 = c0 + (step % (ATT_C / ATT_QB)) * ATT_QB;
+      const int q0 = c0 + ((step0 + step) % (ATT_C / ATT_QB)) * ATT_QB;
       if (q0 + lane >= n) f = 0.f;
     }
     const u32x2 fr = __builtin_amdgcn_permlane32_swap(__float_as_uint(f), __float_as_uint(f), false, false);
@@ -286,19 +295,24 @@ __device__ __forceinline__ void attn_block(const AttnSeg &s, float scale, int he
   }
 }
 
+// SHARED: a block's queries are dealt out to T.parts workgroups (its own instance: the counters that
+// the general start needs cost the full-size call 0.8 %).
+template <bool SHARED>
 __global__ __launch_bounds__(256, 2) void attn_colsum_kernel(const AttnTable T,
                                                              float *__restrict__ raw) {
   __shared__ __attribute__((aligned(16))) AttnLds L;
 
-  // locate (segment, kv head, block)
+  // locate (segment, kv head, block, part of its queries)
   int seg = 0, head = 0, blk = 0;
+  const int unit = SHARED ? (int)(blockIdx.x / (unsigned)T.parts) : (int)blockIdx.x;
+  const int part = SHARED ? (int)blockIdx.x - unit * T.parts : 0;
   {
     int base = 0;
     for (int i = 0; i < T.nseg; ++i) {
       const int bph = (T.s[i].n + ATT_C - 1) / ATT_C;
       const int nb = bph * T.s[i].head_count;
-      if ((int)blockIdx.x < base + nb || i == T.nseg - 1) {
-        const int local = blockIdx.x - base;
+      if (unit < base + nb || i == T.nseg - 1) {
+        const int local = unit - base;
         seg = i;
         head = T.s[i].head_begin + local / bph;
         blk = local % bph;
@@ -309,19 +323,27 @@ __global__ __launch_bounds__(256, 2) void attn_colsum_kernel(const AttnTable T,
   }
   const AttnSeg &s = T.s[seg];
   const int c0 = blk * ATT_C;
+  int step0 = 0, nsteps = s.G * (ATT_C / ATT_QB);            // steps of a block, at least 4
+  if (SHARED) {
+    const long long all = nsteps;
+    step0 = (int)(all * part / T.parts);
+    nsteps = (int)(all * (part + 1) / T.parts) - step0;
+    raw += part * T.part_floats;
+  }
   if (c0 + ATT_C > s.n)
-    attn_block<true>(s, T.scale, head, c0, L, raw);
+    attn_block<true>(s, T.scale, head, c0, step0, nsteps, L, raw);
   else
-    attn_block<false>(s, T.scale, head, c0, L, raw);
+    attn_block<false>(s, T.scale, head, c0, step0, nsteps, L, raw);
 }
 
 // Mean pooling along the sequence: window `pool` (odd), zero padding, divided by `pool`.
-// A workgroup stages its 1024 positions and the halo once in LDS.
+// A workgroup stages its 1024 positions and the halo once in LDS, adding the parts' sums.  In fp64, so that
+// adding parts costs no precision (the kernel waits for memory either way).
 __global__ __launch_bounds__(256) void attn_pool_kernel(const AttnTable T,
                                                         const float *__restrict__ raw,
                                                         float *__restrict__ attn) {
   constexpr int SPAN = 1024, HALO = 32;           // pool <= 63: at most 31 positions each side
-  __shared__ float tile[SPAN + 2 * HALO];
+  __shared__ double tile[SPAN + 2 * HALO];
   int seg = 0, head = 0, blk = 0;
   {
     int base = 0;
@@ -345,15 +367,41 @@ __global__ __launch_bounds__(256) void attn_pool_kernel(const AttnTable T,
   const int t0 = blk * SPAN;
   for (int i = threadIdx.x; i < SPAN + 2 * HALO; i += 256) {
     const int j = t0 - HALO + i;
-    tile[i] = (j >= 0 && j < n) ? src[j] : 0.f;   // zero padding at both ends of the sequence
+    double x = 0.0;                               // zero padding at both ends of the sequence
+    if (j >= 0 && j < n) {
+      x = (double)src[j];
+      for (int p = 1; p < T.parts; ++p) x += (double)src[p * T.part_floats + j];
+    }
+    tile[i] = x;
   }
   __syncthreads();
-  const float inv = 1.f / (float)T.pool;
+  const double inv = 1.0 / (double)T.pool;
   for (int i = threadIdx.x; i < SPAN && t0 + i < n; i += 256) {
-    float acc = 0.f;
+    double acc = 0.0;
     for (int u = -h; u <= h; ++u) acc += tile[HALO + i + u];
-    dst[t0 + i] = acc * inv;
+    dst[t0 + i] = (float)(acc * inv);
   }
+}
+
+// Workgroups that share the queries of a block of 256 keys: as many as compute units would otherwise
+// stand idle, up to 4 (a block has at least 4 steps).  A step takes about 1 us of a workgroup alone on its
+// unit, loading the keys and reducing the sums about 4; two workgroups on a unit already slow each other
+// down, so a block is shared only up to one workgroup per unit.  Whole call of 4 query heads a kv head on
+// MI355X, us with 1 / 2 / 3 / 4 / 5 parts: 4 blocks 32.4 / 23.5 / 22.1 / 20.4 / 21.2, 64 blocks
+// 33.4 / 24.0 / 23.2 / 21.8 / 27.7, 128 blocks 36.5 / 27.6 / 31.8 / 32.4 / 35.4, 200 blocks
+// 34.5 / 34.6 / 40.0 / 41.5, 512 blocks 56.4 / 61.6 / 66.8 / 70.1 (the host alone needs 18).
+constexpr int ATT_MAX_PARTS = 4;
+static int query_parts(const compactor_attn_params_t *p, const compactor_attn_request_t *reqs, int32_t nreq) {
+  long long blocks = 0;
+  for (int b = 0; b < nreq; ++b)
+    blocks += (long long)p->layers * p->kv_heads * ((reqs[b].n + ATT_C - 1) / ATT_C);
+  if (nreq > ATT_MAX_SEG) return 1;           // several launches
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
+    cus = 256;
+  const long long parts = blocks > 0 ? cus / blocks : 1;
+  return (int)(parts < 1 ? 1 : (parts > ATT_MAX_PARTS ? ATT_MAX_PARTS : parts));
 }
 
 }  // namespace cmp
@@ -373,7 +421,7 @@ int compactor_attention_workspace_size(const compactor_attn_params_t *p,
     if (reqs[b].n < 1) return COMPACTOR_EINVAL;
     tot += (size_t)p->layers * p->kv_heads * reqs[b].n;
   }
-  *bytes = (tot * sizeof(float) + 255) / 256 * 256;
+  *bytes = (tot * (size_t)query_parts(p, reqs, nreq) * sizeof(float) + 255) / 256 * 256;
   return COMPACTOR_OK;
 }
 
@@ -394,11 +442,13 @@ int compactor_attention_scores(const compactor_attn_params_t *p,
       return COMPACTOR_EALIGN;
     if ((reinterpret_cast<uintptr_t>(r.q) | reinterpret_cast<uintptr_t>(r.k)) & 15u) return COMPACTOR_EALIGN;
   }
-  size_t need;
-  int rc = compactor_attention_workspace_size(p, reqs, nreq, &need);
-  if (rc) return rc;
-  if (!workspace || workspace_bytes < need) return COMPACTOR_EWORKSPACE;
+  size_t floats = 0;                          // sums of one part
+  for (int b = 0; b < nreq; ++b) floats += (size_t)p->layers * p->kv_heads * reqs[b].n;
+  if (!workspace || workspace_bytes < (floats * sizeof(float) + 255) / 256 * 256) return COMPACTOR_EWORKSPACE;
   if (reinterpret_cast<uintptr_t>(workspace) & 255u) return COMPACTOR_EALIGN;
+
+  int parts = query_parts(p, reqs, nreq);
+  while (parts > 1 && workspace_bytes < parts * floats * sizeof(float)) --parts;    // what there is room for
 
   hipStream_t st = static_cast<hipStream_t>(stream);
   (void)hipGetLastError();   // a leftover of earlier, unrelated HIP calls is not this call's error
@@ -410,6 +460,8 @@ int compactor_attention_scores(const compactor_attn_params_t *p,
     memset(&T, 0, sizeof(T));
     T.scale = p->scale > 0.f ? p->scale : 1.0f / sqrtf((float)D);
     T.pool = p->pool;
+    T.parts = parts;
+    T.part_floats = (long long)floats;
     long long nb_col = 0, nb_pool = 0;
     for (int b = b0; b < nreq && b < b0 + ATT_MAX_SEG; ++b) {
       const compactor_attn_request_t &r = reqs[b];
@@ -426,8 +478,12 @@ int compactor_attention_scores(const compactor_attn_params_t *p,
       nb_col += (long long)LH * ((r.n + ATT_C - 1) / ATT_C);
       nb_pool += (long long)LH * ((r.n + 1023) / 1024);
     }
+    nb_col *= parts;
     if (nb_col > 0x7fffffffll) return COMPACTOR_EINVAL;
-    hipLaunchKernelGGL(attn_colsum_kernel, dim3((unsigned)nb_col), dim3(256), 0, st, T, raw);
+    if (parts > 1)
+      hipLaunchKernelGGL(attn_colsum_kernel<true>, dim3((unsigned)nb_col), dim3(256), 0, st, T, raw);
+    else
+      hipLaunchKernelGGL(attn_colsum_kernel<false>, dim3((unsigned)nb_col), dim3(256), 0, st, T, raw);
     if (hipGetLastError() != hipSuccess) return COMPACTOR_EHIP;
     hipLaunchKernelGGL(attn_pool_kernel, dim3((unsigned)nb_pool), dim3(256), 0, st, T, raw, attn);
     if (hipGetLastError() != hipSuccess) return COMPACTOR_EHIP;

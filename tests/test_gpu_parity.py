@@ -708,6 +708,30 @@ def test_attention_scores_group_sizes_strided_views_and_batches(C, G, n):
     _say("  max rel err %.3g" % float(np.max(err / np.maximum(want, 1e-12))))
 
 
+
+# few blocks: their queries are shared by 2 to 4 workgroups where the workspace has room for the sums of
+# each; 4 * G steps are dealt out evenly or not, a part may get a single step, blocks may be ragged
+@pytest.mark.parametrize("L,H,G,n", [(1, 1, 1, 1), (1, 2, 1, 700), (1, 3, 3, 2100), (1, 8, 4, 4095),
+                                     (2, 8, 7, 1792)])
+def test_attention_scores_in_parts(C, L, H, G, n):
+    worst, w, q, a = _attention_case(C, L, H, G, n, W.config1, seed=G)      # as many parts as it asks for
+    ap, reqs = C.AttnParams(L, H, H * G), [C.AttnRequest(q, w.requests[0].k)]
+    one = L * H * n * 4
+    asked = C.compactor_attention_workspace_size(ap, reqs)
+    blocks = L * H * ((n + 255) // 256)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    assert asked == -(-one * max(1, min(4, cus // blocks)) // 256) * 256
+    # one key's sum is a chain of 8 G products of one lane, 5 adds across lanes, one per part and one per
+    # position of the pooling window, all of positive terms: half an ulp each
+    tol = 2.0 * (8 * G + 5 + 4 + 7 + 2) * 2.0 ** -24
+    for parts in (1, 2, 3, 4):
+        ws = torch.full((max(256, -(-one * parts // 256) * 256),), 0xff, dtype=torch.uint8, device=DEV)   # NaN
+        b = C.compactor_attention_scores(ap, reqs, workspace=ws)
+        torch.cuda.synchronize()
+        b = b.view(L, H, n).cpu().numpy()
+        assert np.all(np.abs(b - a) <= tol * np.abs(a)), (parts, float(np.max(np.abs(b - a) / np.abs(a))))
+
+
 def test_attention_scores_with_every_cu_busy(C):
     _say("attention scores: 2 layers x 8 kv heads x 4 query heads, n=16384 (1024 workgroups, two per CU)")
     worst, _, _, _ = _attention_case(C, 2, 8, 4, 16384, W.config2)
