@@ -75,11 +75,16 @@ int compute_units() {
 }
 
 // Gram: a persistent launch of 2 workgroups per compute unit (or as many as there are tiles),
-// each taking an equal run of 64-row tiles.
+// each taking an equal run of 64-row tiles; of 1 where few heads' partials weigh more in the
+// factorisation than the second workgroup saves.  Whole call on MI355X, us with 1 / 2 workgroups a unit:
+// 8 heads of 20000 tokens 85.6 / 90.2, 32768 101.3 / 104.2, 40007 113.2 / 116.9, 49152 120.6 / 120.7,
+// 65536 135.7 / 134.9, 98304 170.8 / 167.6; 64 heads of 4000 91.8 / 90.1; exact mode, 8 heads of
+// 32768 127.1 / 137.2, 65536 161.2 / 167.4, 98304 196.9 / 200.6, 32 heads of 50001 322 / 313.
 struct GramPlan { int nwg, tiles_per_wg; };
 GramPlan gram_plan(const compactor_params_t *p, const SegTable &T, int cus) {
   const long long total = total_tiles(T);
-  long long want = p->gram_wgs > 0 ? p->gram_wgs : 2ll * cus;
+  const bool few = T.nheads <= 32 && total < (p->sketch_dim > 0 ? 24ll : 64ll) * cus;
+  long long want = p->gram_wgs > 0 ? p->gram_wgs : (few ? 1ll : 2ll) * cus;
   if (want > total) want = total;
   if (want < 1) want = 1;
   GramPlan g;
@@ -104,6 +109,18 @@ int score_tokens_for(const compactor_params_t *p, const SegTable &T, int cus) {
   // workgroup and gains 4 % from runs of 16384 tokens.
   const int cap = p->sketch_dim == 0 ? 16384 : SCORE_BURST;
   const int slots = 2 * cus;
+  // A call of few heads that gives a compute unit less than 1024 tokens is all latency: one workgroup per unit, but not
+  // below 256 tokens, where staging W^T and adding the histograms outweigh the steps saved.  Whole
+  // call on MI355X, us with runs of 128 / 256 / 512 / 768 / 1024 tokens: 8 heads of 4096 tokens 53.8 / 54.6 /
+  // 56.6 / 59.2 / 60.9, 8192 63.1 / 62.7 / 62.9 / 64.8 / 67.8, 16384 86.6 / 78.4 / 76.3 / 78.8 / 79.6, 24000
+  // 113.8 / 101.5 / 93.6 / 92.8 / 94.2, 32768 141 / 118 / 107.4 / 108.2 / 106.8, one head of 2048 51.2 / 51.3 /
+  // 51.8 / 54.2 / 55.7; exact mode, 8 heads of 8192 80.0 / 79.8 / 82.1 / 86.5 / 90.3.
+  long long rows = 0;
+  for (int i = 0; i < T.nseg; ++i) rows += (long long)T.s[i].n * T.s[i].head_count;
+  if (T.nheads <= cus && rows < 1024ll * cus) {
+    const int even = (int)((rows + cus - 1) / cus + SCORE_STEP - 1) / SCORE_STEP * SCORE_STEP;
+    return even < 256 ? 256 : even;
+  }
   int best = cap;
   double best_score = -1.0;
   for (int c = cap; c >= 1024; c -= SCORE_STEP) {

@@ -190,8 +190,8 @@ __global__ __launch_bounds__(256, 2) void score_kernel(
     for (int p = 0; p < NS; ++p)
 #pragma unroll
       for (int st = 0; st < NSUB; ++st) sums[p][st] = 0.f;
-#pragma unroll 1
-    for (int jb = 0; jb < M / 16; ++jb) {   // kept rolled: unrolling hoists every W^T operand
+#pragma unroll (M <= 48 ? M / 16 : 1)
+    for (int jb = 0; jb < M / 16; ++jb) {   // rolled for many rows: unrolling hoists their operands
       f32x4 acc[NS][NSUB];
 #pragma unroll
       for (int p = 0; p < NS; ++p)

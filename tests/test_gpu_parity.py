@@ -291,6 +291,19 @@ def test_factorisation_with_and_without_shares(C, ks, n, gram_wgs):
     _say("  workspace %d of %d bytes; max rel err %.3g" % (hi, full, stats["max_rel"]))
 
 
+# few heads: score runs of 256 to 1024 tokens up to 1024 tokens a compute unit, and one Gram workgroup a
+# unit up to 24 (exact mode: 64) tiles each; a step to either side of both limits, a short head, blended scores
+@pytest.mark.parametrize("H,n,exact,blend", [(1, 130, False, False), (3, 257, False, True), (8, 8191, False, True),
+                                             (2, 131071, False, False), (2, 131073, False, False),
+                                             (8, 49089, False, False), (8, 49153, False, False),
+                                             (3, 43691, True, False)])
+def test_launch_shapes_of_few_heads(C, H, n, exact, blend):
+    w = W.config5(DEV, L=1, H=H, n=n, exact=True) if exact else W.config1(DEV, L=1, H=H, n=n)
+    if blend:
+        w.requests[0].attn = W.synthetic_attention_scores(1, H, n, device=DEV, seed=n)
+    U.run_and_check(C, w, DEV, heads=[(0, 0, 0), (0, 0, H - 1)])
+
+
 @pytest.mark.parametrize("score_tokens", [128, 1024, 8192, 32768])
 def test_score_runs_of_several_bursts(C, score_tokens):
     """A score workgroup takes `score_tokens` tokens and writes its scores in bursts of 4096 (2048
