@@ -157,21 +157,30 @@ def _check(rc: int):
         raise CompactorError(rc)
 
 
+def _refuse(what: str):
+    raise ValueError("compactor: " + what)
+
+
 def _require(cond: bool, what: str):
     """The C boundary takes plain pointers and cannot see a tensor's size, type or device: what it
-    cannot check is checked here, before anything reaches the GPU."""
+    cannot check is checked here, before anything reaches the GPU.  (Checks whose message has to be
+    put together test first and call _refuse: a call makes dozens of them.)"""
     if not cond:
-        raise ValueError("compactor: " + what)
+        _refuse(what)
 
 
 def _out(t: Optional[torch.Tensor], numel: int, dtype, name: str):
     """A caller-supplied output (or flat input) buffer: right type, dense, large enough, on the GPU."""
     if t is None:
         return
-    _require(t.dtype == dtype, "%s must be %s, got %s" % (name, dtype, t.dtype))
-    _require(t.is_contiguous(), "%s must be contiguous" % name)
-    _require(t.numel() >= numel, "%s holds %d elements, %d needed" % (name, t.numel(), numel))
-    _require(t.is_cuda, "%s must live on the GPU" % name)
+    if t.dtype != dtype:
+        _refuse("%s must be %s, got %s" % (name, dtype, t.dtype))
+    if not t.is_contiguous():
+        _refuse("%s must be contiguous" % name)
+    if t.numel() < numel:
+        _refuse("%s holds %d elements, %d needed" % (name, t.numel(), numel))
+    if not t.is_cuda:
+        _refuse("%s must live on the GPU" % name)
 
 
 SCOPE_HEAD, SCOPE_LAYER = 0, 1
@@ -192,15 +201,20 @@ class Params:
     score_tokens: int = 0
     select_scope: int = 0                           # SCOPE_HEAD, or SCOPE_LAYER (head-adaptive)
 
+    def check_gpu(self):
+        if self.phi is not None and self.sketch_dim > 0:
+            _require(self.phi.is_cuda, "phi must live on the GPU")
+
     def c(self, on_gpu: bool = True) -> _Params:
         phi = 0
         if self.phi is not None and self.sketch_dim > 0:
             _require(self.phi.dtype == torch.float32 and self.phi.is_contiguous(),
                      "phi must be a contiguous float32 tensor")
-            _require(tuple(self.phi.shape) == (self.head_dim, self.sketch_dim),
-                     "phi must have shape [head_dim, sketch_dim] = [%d, %d], got %s"
-                     % (self.head_dim, self.sketch_dim, tuple(self.phi.shape)))
-            _require(self.phi.is_cuda or not on_gpu, "phi must live on the GPU")
+            if tuple(self.phi.shape) != (self.head_dim, self.sketch_dim):
+                _refuse("phi must have shape [head_dim, sketch_dim] = [%d, %d], got %s"
+                        % (self.head_dim, self.sketch_dim, tuple(self.phi.shape)))
+            if on_gpu:
+                self.check_gpu()
             phi = self.phi.data_ptr()
         ev = C.cast(self.stage_events.array, C.c_void_p) if self.stage_events is not None else None
         return _Params(self.layers, self.kv_heads, self.head_dim, self.sketch_dim, phi,
@@ -216,31 +230,36 @@ class Request:
     k_cache: Optional[torch.Tensor] = None     # bf16, same shape and strides; None = k_score
     attn: Optional[torch.Tensor] = None        # fp32 [L, H, n] contiguous
 
+    def check_gpu(self):
+        for name, t in (("v_cache", self.v_cache), ("k_cache", self.k_cache), ("attn", self.attn),
+                        ("k_score", self.k_score)):
+            if t is not None and not t.is_cuda:
+                _refuse("%s must live on the GPU" % name)
+
     def c(self, params: Optional["Params"] = None, on_gpu: bool = True) -> _Request:
         k = self.k_score
         _require(k.dtype == torch.bfloat16 and k.dim() == 4 and k.stride(3) == 1,
                  "k_score must be a bfloat16 tensor [L, H, n, d] with d contiguous")
-        if params is not None:
-            _require(k.shape[0] == params.layers and k.shape[1] == params.kv_heads and
-                     k.shape[3] == params.head_dim,
-                     "k_score has shape %s, the parameters say [%d, %d, n, %d]"
-                     % (tuple(k.shape), params.layers, params.kv_heads, params.head_dim))
+        shape, stride = k.shape, k.stride()
+        if params is not None and not (shape[0] == params.layers and shape[1] == params.kv_heads and
+                                       shape[3] == params.head_dim):
+            _refuse("k_score has shape %s, the parameters say [%d, %d, n, %d]"
+                    % (tuple(shape), params.layers, params.kv_heads, params.head_dim))
         for name, t in (("v_cache", self.v_cache), ("k_cache", self.k_cache)):
-            if t is not None:
-                _require(t.dtype == torch.bfloat16 and t.shape == k.shape and t.stride() == k.stride(),
-                         "%s must be bfloat16 with the shape and strides of k_score" % name)
-                _require(t.is_cuda or not on_gpu, "%s must live on the GPU" % name)
+            if t is not None and t is not k:
+                if t.dtype != torch.bfloat16 or t.shape != shape or t.stride() != stride:
+                    _refuse("%s must be bfloat16 with the shape and strides of k_score" % name)
         if self.attn is not None:
             _require(self.attn.dtype == torch.float32 and self.attn.is_contiguous() and
-                     self.attn.numel() >= k.shape[0] * k.shape[1] * k.shape[2],
+                     self.attn.numel() >= shape[0] * shape[1] * shape[2],
                      "attn must be a contiguous float32 tensor of L*H*n elements")
-            _require(self.attn.is_cuda or not on_gpu, "attn must live on the GPU")
-        _require(k.is_cuda or not on_gpu, "k_score must live on the GPU")
+        if on_gpu:
+            self.check_gpu()
         return _Request(k.data_ptr(),
                         self.k_cache.data_ptr() if self.k_cache is not None else 0,
                         self.v_cache.data_ptr() if self.v_cache is not None else 0,
                         self.attn.data_ptr() if self.attn is not None else 0,
-                        k.stride(0), k.stride(1), k.stride(2), k.shape[2], self.ratio)
+                        stride[0], stride[1], stride[2], shape[2], self.ratio)
 
 
 def _marshal(params: Params, reqs: Sequence[Request], on_gpu: bool = True):
@@ -249,12 +268,26 @@ def _marshal(params: Params, reqs: Sequence[Request], on_gpu: bool = True):
     return C.byref(params.c(on_gpu)), arr, len(reqs)
 
 
+def _check_gpu(params: Params, reqs: Sequence[Request]):
+    """The part of the marshalling that asks where the tensors live.  The entry points marshal once,
+    without it, to learn the sizes, and come back to this before the call."""
+    for r in reqs:
+        r.check_gpu()
+    params.check_gpu()
+
+
 def _ptr(t: Optional[torch.Tensor]):
     return 0 if t is None else t.data_ptr()
 
 
+# the current stream's handle without the Stream object that torch.cuda.current_stream() builds (3 us)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream):
     if stream is None:
+        if _raw_stream is not None:
+            return C.c_void_p(_raw_stream(torch.cuda.current_device()))
         stream = torch.cuda.current_stream()
     return C.c_void_p(stream.cuda_stream)
 
@@ -299,24 +332,30 @@ def compactor_srht_phi(sketch_dim: int, signs, cols, device, stream=None) -> tor
     return phi
 
 
-def compactor_layout(params: Params, reqs: Sequence[Request]):
-    """-> (score_off[nreq+1], kept_off[nreq+1], k_keep[nreq]) as Python lists."""
-    pp, arr, n = _marshal(params, reqs, on_gpu=False)      # a host helper: sizes only
+def _layout(pp, arr, n):
     so, ko, kk = (C.c_int64 * (n + 1))(), (C.c_int64 * (n + 1))(), (C.c_int32 * n)()
     _check(_lib.compactor_layout(pp, arr, n, so, ko, kk))
     return list(so), list(ko), list(kk)
 
 
-def compactor_workspace_size(params: Params, reqs: Sequence[Request]) -> int:
-    pp, arr, n = _marshal(params, reqs, on_gpu=False)
+def compactor_layout(params: Params, reqs: Sequence[Request]):
+    """-> (score_off[nreq+1], kept_off[nreq+1], k_keep[nreq]) as Python lists."""
+    return _layout(*_marshal(params, reqs, on_gpu=False))      # a host helper: sizes only
+
+
+def _workspace_bytes(pp, arr, n) -> int:
     out = C.c_size_t(0)
     _check(_lib.compactor_workspace_size(pp, arr, n, C.byref(out)))
     return int(out.value)
 
 
-def _workspace(params, reqs, workspace, stream=None):
+def compactor_workspace_size(params: Params, reqs: Sequence[Request]) -> int:
+    return _workspace_bytes(*_marshal(params, reqs, on_gpu=False))
+
+
+def _workspace(call, reqs, workspace, stream=None):
     if workspace is None:
-        nbytes = max(256, compactor_workspace_size(params, reqs))
+        nbytes = max(256, _workspace_bytes(*call))
         workspace = torch.empty(nbytes, dtype=torch.uint8, device=_device(reqs))
         if stream is not None:
             # the block is used on `stream`, not on the stream torch allocated it for: tell the
@@ -328,17 +367,19 @@ def _workspace(params, reqs, workspace, stream=None):
 def compactor_score(params: Params, reqs: Sequence[Request], scores=None, status=None,
                     workspace=None, stream=None):
     """-> (scores fp32 [sum L*H*n], status int32 [nreq*L*H])"""
-    so, _, _ = compactor_layout(params, reqs)
-    dev = _device(reqs)
+    pp, arr, n = call = _marshal(params, reqs, on_gpu=False)
+    so, _, _ = _layout(*call)
+    dev, nh = _device(reqs), n * params.layers * params.kv_heads
+    given = scores, status, workspace          # what is allocated here needs no check
     if scores is None:
         scores = torch.empty(so[-1], dtype=torch.float32, device=dev)
     if status is None:
-        status = torch.empty(len(reqs) * params.layers * params.kv_heads, dtype=torch.int32, device=dev)
-    workspace = _workspace(params, reqs, workspace, stream)
-    pp, arr, n = _marshal(params, reqs)
-    _out(scores, so[-1], torch.float32, "scores")
-    _out(status, n * params.layers * params.kv_heads, torch.int32, "status")
-    _out(workspace, 0, torch.uint8, "workspace")
+        status = torch.empty(nh, dtype=torch.int32, device=dev)
+    workspace = _workspace(call, reqs, workspace, stream)
+    _check_gpu(params, reqs)
+    _out(given[0], so[-1], torch.float32, "scores")
+    _out(given[1], nh, torch.int32, "status")
+    _out(given[2], 0, torch.uint8, "workspace")
     _check(_lib.compactor_score(pp, arr, n, _ptr(scores), _ptr(status), _ptr(workspace),
                                 workspace.numel(), _stream(stream)))
     return scores, status
@@ -347,18 +388,18 @@ def compactor_score(params: Params, reqs: Sequence[Request], scores=None, status
 def compactor_select(params: Params, reqs: Sequence[Request], scores: torch.Tensor,
                      kept_idx=None, kept_cnt=None, workspace=None, stream=None):
     """-> (kept_idx int32 [sum L*H*k_keep], kept_cnt int32 [nreq*L*H])"""
-    _, ko, _ = compactor_layout(params, reqs)
-    dev = scores.device
+    pp, arr, n = call = _marshal(params, reqs, on_gpu=False)
+    so, ko, _ = _layout(*call)
+    dev, nh = scores.device, n * params.layers * params.kv_heads
     if kept_idx is None:
         kept_idx = torch.empty(ko[-1], dtype=torch.int32, device=dev)
     if kept_cnt is None:
-        kept_cnt = torch.empty(len(reqs) * params.layers * params.kv_heads, dtype=torch.int32, device=dev)
-    pp, arr, n = _marshal(params, reqs)
-    workspace = _workspace(params, reqs, workspace, stream)
-    so, _, _ = compactor_layout(params, reqs)
-    _out(scores, so[-1], torch.float32, "scores")
+        kept_cnt = torch.empty(nh, dtype=torch.int32, device=dev)
+    _check_gpu(params, reqs)
+    workspace = _workspace(call, reqs, workspace, stream)
+    _out(scores, so[-1], torch.float32, "scores")       # the scores' device decides where the others live
     _out(kept_idx, ko[-1], torch.int32, "kept_idx")
-    _out(kept_cnt, n * params.layers * params.kv_heads, torch.int32, "kept_cnt")
+    _out(kept_cnt, nh, torch.int32, "kept_cnt")
     _out(workspace, 0, torch.uint8, "workspace")
     _check(_lib.compactor_select(pp, arr, n, _ptr(scores), _ptr(kept_idx), _ptr(kept_cnt),
                                  _ptr(workspace), workspace.numel(), _stream(stream)))
@@ -368,13 +409,14 @@ def compactor_select(params: Params, reqs: Sequence[Request], scores: torch.Tens
 def compactor_compact(params: Params, reqs: Sequence[Request], kept_idx: torch.Tensor,
                       kept_cnt: torch.Tensor, k_packed=None, v_packed=None, stream=None):
     """-> (k_packed, v_packed) bf16 [sum L*H*k_keep, d]"""
-    _, ko, _ = compactor_layout(params, reqs)
+    pp, arr, n = call = _marshal(params, reqs, on_gpu=False)
+    _, ko, _ = _layout(*call)
     dev = _device(reqs)
     if k_packed is None:
         k_packed = torch.empty(ko[-1], params.head_dim, dtype=torch.bfloat16, device=dev)
     if v_packed is None:
         v_packed = torch.empty(ko[-1], params.head_dim, dtype=torch.bfloat16, device=dev)
-    pp, arr, n = _marshal(params, reqs)
+    _check_gpu(params, reqs)
     _out(kept_idx, ko[-1], torch.int32, "kept_idx")
     _out(kept_cnt, n * params.layers * params.kv_heads, torch.int32, "kept_cnt")
     _out(k_packed, ko[-1] * params.head_dim, torch.bfloat16, "k_packed")
@@ -406,9 +448,9 @@ def compactor_compact_paged(params: Params, reqs: Sequence[Request], kept_idx: t
     for t in tables:
         _out(t, 0, torch.int32, "a block table")
     tabs = (_PageTable * len(tables))(*[_PageTable(t.data_ptr(), t.numel()) for t in tables])
-    pp, arr, n = _marshal(params, reqs)
+    pp, arr, n = call = _marshal(params, reqs)
     _require(len(tables) == n, "one block table per request is needed")
-    _, ko, _ = compactor_layout(params, reqs)
+    _, ko, _ = _layout(*call)
     _out(kept_idx, ko[-1], torch.int32, "kept_idx")
     _out(kept_cnt, n * params.layers * params.kv_heads, torch.int32, "kept_cnt")
     _check(_lib.compactor_compact_paged(pp, arr, n, _ptr(kept_idx), _ptr(kept_cnt), C.byref(pool),
@@ -419,9 +461,12 @@ def compactor_compress(params: Params, reqs: Sequence[Request], want_scores: boo
                        scores=None, kept_idx=None, kept_cnt=None, k_packed=None, v_packed=None,
                        status=None, workspace=None, stream=None):
     """Fused score -> select -> compact.  -> dict of the output tensors."""
-    so, ko, _ = compactor_layout(params, reqs)
+    pp, arr, n = call = _marshal(params, reqs, on_gpu=False)
+    so, ko, _ = _layout(*call)
     dev = _device(reqs)
-    nh = len(reqs) * params.layers * params.kv_heads
+    nh = n * params.layers * params.kv_heads
+    # what is allocated here needs no check
+    given = scores, kept_idx, kept_cnt, k_packed, v_packed, status, workspace
     if scores is None and want_scores:
         scores = torch.empty(so[-1], dtype=torch.float32, device=dev)
     if kept_idx is None:
@@ -434,15 +479,14 @@ def compactor_compress(params: Params, reqs: Sequence[Request], want_scores: boo
         v_packed = torch.empty(ko[-1], params.head_dim, dtype=torch.bfloat16, device=dev)
     if status is None:
         status = torch.empty(nh, dtype=torch.int32, device=dev)
-    workspace = _workspace(params, reqs, workspace, stream)
-    pp, arr, n = _marshal(params, reqs)
-    _out(scores, so[-1], torch.float32, "scores")
-    _out(kept_idx, ko[-1], torch.int32, "kept_idx")
-    _out(kept_cnt, nh, torch.int32, "kept_cnt")
-    _out(k_packed, ko[-1] * params.head_dim, torch.bfloat16, "k_packed")
-    _out(v_packed, ko[-1] * params.head_dim, torch.bfloat16, "v_packed")
-    _out(status, nh, torch.int32, "status")
-    _out(workspace, 0, torch.uint8, "workspace")
+    workspace = _workspace(call, reqs, workspace, stream)
+    _check_gpu(params, reqs)
+    for t, numel, dtype, name in zip(
+            given, (so[-1], ko[-1], nh, ko[-1] * params.head_dim, ko[-1] * params.head_dim, nh, 0),
+            (torch.float32, torch.int32, torch.int32, torch.bfloat16, torch.bfloat16, torch.int32, torch.uint8),
+            ("scores", "kept_idx", "kept_cnt", "k_packed", "v_packed", "status", "workspace")):
+        if t is not None:
+            _out(t, numel, dtype, name)
     _check(_lib.compactor_compress(pp, arr, n, _ptr(scores), _ptr(kept_idx), _ptr(kept_cnt),
                                    _ptr(k_packed), _ptr(v_packed), _ptr(status), _ptr(workspace),
                                    workspace.numel(), _stream(stream)))
@@ -457,9 +501,10 @@ def compactor_compress_static(params: Params, reqs: Sequence[Request], scores, k
                               k_packed, v_packed, status, stream=None):
     """compactor_compress on the library's own static scratch: every buffer is the caller's (none
     is allocated here, `scores` may be None) and no workspace is passed."""
-    so, ko, _ = compactor_layout(params, reqs)
-    nh = len(reqs) * params.layers * params.kv_heads
-    pp, arr, n = _marshal(params, reqs)
+    pp, arr, n = call = _marshal(params, reqs, on_gpu=False)
+    so, ko, _ = _layout(*call)
+    nh = n * params.layers * params.kv_heads
+    _check_gpu(params, reqs)
     _out(scores, so[-1], torch.float32, "scores")
     for t, name in ((kept_idx, "kept_idx"), (kept_cnt, "kept_cnt"), (k_packed, "k_packed"),
                     (v_packed, "v_packed"), (status, "status")):
@@ -499,17 +544,15 @@ class AttnRequest:
         _require(q.dtype == torch.bfloat16 and k.dtype == torch.bfloat16, "q and k must be bfloat16")
         _require(q.dim() == 4 and k.dim() == 4 and q.stride(3) == 1 and k.stride(3) == 1,
                  "q and k must be [L, heads, n, d] with d contiguous")
-        _require(q.shape[2] == k.shape[2], "q and k must cover the same tokens")
-        if params is not None:
-            _require(tuple(q.shape[:2]) == (params.layers, params.q_heads) and
-                     tuple(k.shape[:2]) == (params.layers, params.kv_heads) and
-                     q.shape[3] == params.head_dim and k.shape[3] == params.head_dim,
-                     "q %s / k %s do not match the parameters [%d, %d | %d, n, %d]"
-                     % (tuple(q.shape), tuple(k.shape), params.layers, params.q_heads,
-                        params.kv_heads, params.head_dim))
+        qs, ks = tuple(q.shape), tuple(k.shape)
+        _require(qs[2] == ks[2], "q and k must cover the same tokens")
+        if params is not None and not (qs[:2] == (params.layers, params.q_heads) and
+                                       ks[:2] == (params.layers, params.kv_heads) and
+                                       qs[3] == params.head_dim and ks[3] == params.head_dim):
+            _refuse("q %s / k %s do not match the parameters [%d, %d | %d, n, %d]"
+                    % (qs, ks, params.layers, params.q_heads, params.kv_heads, params.head_dim))
         _require(q.is_cuda and k.is_cuda, "q and k must live on the GPU")
-        return _AttnRequest(q.data_ptr(), k.data_ptr(), q.stride(0), q.stride(1), q.stride(2),
-                            k.stride(0), k.stride(1), k.stride(2), k.shape[2])
+        return _AttnRequest(q.data_ptr(), k.data_ptr(), *q.stride()[:3], *k.stride()[:3], ks[2])
 
 
 def compactor_attention_workspace_size(params: AttnParams, reqs: Sequence[AttnRequest]) -> int:
@@ -524,6 +567,7 @@ def compactor_attention_scores(params: AttnParams, reqs: Sequence[AttnRequest], 
     """-> attn fp32 [sum_b L*H*n_b]; request b starts at the prefix sum of L*H*n_b."""
     dev = reqs[0].k.device
     total = sum(params.layers * params.kv_heads * r.k.shape[2] for r in reqs)
+    given = attn, workspace                    # what is allocated here needs no check
     if attn is None:
         attn = torch.empty(total, dtype=torch.float32, device=dev)
     if workspace is None:
@@ -532,8 +576,8 @@ def compactor_attention_scores(params: AttnParams, reqs: Sequence[AttnRequest], 
         if stream is not None:
             workspace.record_stream(stream)
     arr = (_AttnRequest * len(reqs))(*[r.c(params) for r in reqs])
-    _out(attn, total, torch.float32, "attn")
-    _out(workspace, 0, torch.uint8, "workspace")
+    _out(given[0], total, torch.float32, "attn")
+    _out(given[1], 0, torch.uint8, "workspace")
     _check(_lib.compactor_attention_scores(C.byref(params.c()), arr, len(reqs), _ptr(attn),
                                            _ptr(workspace), workspace.numel(), _stream(stream)))
     return attn
