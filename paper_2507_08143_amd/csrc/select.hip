@@ -12,17 +12,25 @@
 
 namespace cmp {
 
+// Inclusive prefix sum over the lanes of a wave, by moves within and across the 16-lane rows: a move costs
+// a vector instruction, where a shuffle is an LDS round trip.
+__device__ __forceinline__ int wave_inclusive_scan(int v) {
+  constexpr int ROW_SHR = 0x110, ROW_BCAST15 = 0x142, ROW_BCAST31 = 0x143;
+  v += __builtin_amdgcn_update_dpp(0, v, ROW_SHR + 1, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, ROW_SHR + 2, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, ROW_SHR + 4, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, ROW_SHR + 8, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, ROW_BCAST15, 0xa, 0xf, false);   // lane 15 to row 1, 47 to row 3
+  v += __builtin_amdgcn_update_dpp(0, v, ROW_BCAST31, 0xc, 0xf, false);   // lane 31 to rows 2 and 3
+  return v;
+}
+
 // Exclusive prefix sum of one int per thread over a workgroup of NT threads; *total gets the
 // workgroup sum.  wsum is NT / 64 ints of LDS.
 template <int NT = SELECT_THREADS>
 __device__ __forceinline__ int block_exclusive_scan(int v, int *wsum, int *total) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int inc = v;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const int o = __shfl_up(inc, d);
-    if (lane >= d) inc += o;
-  }
+  const int inc = wave_inclusive_scan(v);
   __syncthreads();                       // wsum may still be read from a previous call
   if (lane == 63) wsum[wave] = inc;
   __syncthreads();
@@ -155,12 +163,7 @@ __device__ void emit_kept_lds(uint32_t *keys, int n, int k, uint32_t thr, int ne
       mine += (v && key[r][q] > thr) ? 1u : 0u;
       mine += (v && key[r][q] == thr) ? 0x10000u : 0u;
     }
-    unsigned inc = mine;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const unsigned o = __shfl_up(inc, d);
-      if (lane >= d) inc += o;
-    }
+    const unsigned inc = (unsigned)wave_inclusive_scan((int)mine);
     before[r] = inc - mine;
     if (lane == 63) table[r * NW + wave] = inc;
   }
@@ -174,12 +177,7 @@ __device__ void emit_kept_lds(uint32_t *keys, int n, int k, uint32_t thr, int ne
       v[i] = idx < R * NW ? table[idx] : 0u;
       sum += v[i];
     }
-    unsigned inc = sum;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const unsigned o = __shfl_up(inc, d);
-      if (lane >= d) inc += o;
-    }
+    const unsigned inc = (unsigned)wave_inclusive_scan((int)sum);
     unsigned run = inc - sum;
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
@@ -511,12 +509,7 @@ __global__ __launch_bounds__(CHUNK_THREADS, 7) void msel_cand_kernel(const SegTa
   // above, at most 2048 each), one LDS add per wave for the wave's share of the list (the order in which
   // waves claim theirs does not matter).
   const int mine = __popc(in);
-  int inc = mine | (__popc(above) << 16);
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const int o = __shfl_up(inc, d);
-    if (lane >= d) inc += o;
-  }
+  const int inc = wave_inclusive_scan(mine | (__popc(above) << 16));
   int base = 0;
   if (lane == 63) {
     if (inc & 0xffff) base = atomicAdd(&ncand_s, inc & 0xffff);
@@ -817,12 +810,7 @@ __global__ __launch_bounds__(CHUNK_THREADS, 8) void msel_emit_kernel(const SegTa
   unsigned keep = nibbles(by.x, by.y);
   unsigned ties = nibbles(by.x >> 4, by.y >> 4);
   const unsigned mine = (unsigned)__popc(keep) | (unsigned)__popc(ties) << 16;
-  unsigned inc = mine;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const unsigned o = __shfl_up(inc, d);
-    if (lane >= d) inc += o;
-  }
+  const unsigned inc = (unsigned)wave_inclusive_scan((int)mine);
   if (lane == 63) wtot[wave] = inc;
   __syncthreads();
   unsigned before = inc - mine, all = 0;
