@@ -891,54 +891,54 @@ struct OstatIndex {
   long long first[MAX_SEG];
   int per_head[MAX_SEG];
 };
+// A workgroup takes BLEND_ROUNDS of the SEL_ROUNDS rounds of a chunk (half of it): a call of few heads has
+// too few whole chunks to fill the chip, and the scores are requested before the head's sums are added up,
+// which hides a load latency (32 heads of 16383 tokens: 10.2 us, with whole chunks
+// and the loads behind the sums 15.2).
+constexpr int BLEND_ROUNDS = SEL_ROUNDS / 2;
 __global__ __launch_bounds__(CHUNK_THREADS) void blend_apply_kernel(
     const SegTable T, const OstatIndex X, float lambda, float *__restrict__ scores,
     const double *__restrict__ ostat, int *__restrict__ hist1) {
   __shared__ double wd[CHUNK_THREADS / 64][4];
   __shared__ int hist[HIST1_BINS];
-  const SelWhere q = sel_locate(T, blockIdx.x);
+  const SelWhere q = sel_locate(T, blockIdx.x / (SEL_ROUNDS / BLEND_ROUNDS));
+  const int r0 = blockIdx.x % (SEL_ROUNDS / BLEND_ROUNDS) * BLEND_ROUNDS;
   const Seg &s = T.s[q.seg];
-  if (s.attn == nullptr) return;
+  if (s.attn == nullptr || q.tok_begin + 4 * r0 * CHUNK_THREADS >= q.tok_end) return;     // uniform
   const int n = s.n, tid = threadIdx.x;
   float *o = scores + s.score_off + (long long)q.head * n;
   const float *a = s.attn + (long long)q.head * n;
+  const float a0 = a[0];
+  float fa[BLEND_ROUNDS][4], fo[BLEND_ROUNDS][4];
+  const unsigned valid = load_scores_part<BLEND_ROUNDS>(a, q, r0, fa);
+  load_scores_part<BLEND_ROUNDS>(o, q, r0, fo);
   // where the head's sums start: its first score workgroup
   const int obph = X.per_head[q.seg];
   const long long ob = X.first[q.seg] + (long long)(q.head - s.head_begin) * obph;
   if (hist1 != nullptr)
     for (int i = tid; i < HIST1_BINS; i += CHUNK_THREADS) hist[i] = 0;
-  const Moments M = moments(ostat + 4 * ob, obph, n, (double)a[0], wd);     // has a barrier
+  const Moments M = moments(ostat + 4 * ob, obph, n, (double)a0, wd);     // has a barrier
   const double mo = M.mo, ma = M.ma, ia = M.ia, io = M.io * (double)lambda;
   typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
-  // the chunk in parts of PART rounds: the fp64 arithmetic of a whole chunk at once would take
-  // so many registers that only three workgroups fit a CU
-  constexpr int PART = 4;
-#pragma unroll 1
-  for (int r0 = 0; r0 < SEL_ROUNDS; r0 += PART) {
-    if (q.tok_begin + 4 * r0 * CHUNK_THREADS >= q.tok_end) break;       // uniform
-    float fa[PART][4], fo[PART][4];
-    const unsigned valid = load_scores_part<PART>(a, q, r0, fa);
-    load_scores_part<PART>(o, q, r0, fo);
 #pragma unroll
-    for (int r = 0; r < PART; ++r) {
-      const unsigned m = (valid >> (4 * r)) & 0xfu;
-      if (m == 0) continue;
-      float v[4];
+  for (int r = 0; r < BLEND_ROUNDS; ++r) {
+    const unsigned m = (valid >> (4 * r)) & 0xfu;
+    if (m == 0) continue;
+    float v[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        v[e] = (float)(((double)fa[r][e] - ma) * ia + ((double)fo[r][e] - mo) * io);
-        if (hist1 != nullptr && (m >> e & 1)) atomicAdd(&hist[score_key(v[e]) >> 20], 1);
-      }
-      const int i0 = q.tok_begin + 4 * ((r0 + r) * CHUNK_THREADS + tid);
-      if (m == 0xfu) {
-        f32x4_any t;
-        t.x = v[0]; t.y = v[1]; t.z = v[2]; t.w = v[3];
-        *reinterpret_cast<f32x4_any *>(o + i0) = t;
-      } else {
+    for (int e = 0; e < 4; ++e) {
+      v[e] = (float)(((double)fa[r][e] - ma) * ia + ((double)fo[r][e] - mo) * io);
+      if (hist1 != nullptr && (m >> e & 1)) atomicAdd(&hist[score_key(v[e]) >> 20], 1);
+    }
+    const int i0 = q.tok_begin + 4 * ((r0 + r) * CHUNK_THREADS + tid);
+    if (m == 0xfu) {
+      f32x4_any t;
+      t.x = v[0]; t.y = v[1]; t.z = v[2]; t.w = v[3];
+      *reinterpret_cast<f32x4_any *>(o + i0) = t;
+    } else {
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (m >> e & 1) o[i0 + e] = v[e];
-      }
+      for (int e = 0; e < 4; ++e)
+        if (m >> e & 1) o[i0 + e] = v[e];
     }
   }
   if (hist1 != nullptr) {
@@ -1021,7 +1021,7 @@ bool blend_wanted(const SegTable &T) {
 hipError_t launch_blend(const SegTable &T, float lambda, int score_tokens, float *scores,
                         const double *ostat, int *hist1, hipStream_t st) {
   if (!blend_wanted(T) || T.nheads <= 0) return hipSuccess;
-  const long long nb = select_chunks(T);
+  const long long nb = select_chunks(T) * (SEL_ROUNDS / BLEND_ROUNDS);
   if (nb > 0x7fffffffll) return hipErrorInvalidValue;
   OstatIndex X;
   long long ob = 0;
