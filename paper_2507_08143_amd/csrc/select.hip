@@ -577,10 +577,13 @@ __device__ __forceinline__ void for_each_cand(const uint32_t *__restrict__ l, in
 // known, every chunk's counts above and at the threshold follow.  If the list overflows (heavily
 // tied scores) or the pool has more than THR_BLOCK chunks, a third pass counts instead.
 // The chunks' records are fetched into LDS in blocks of THR_BLOCK (a load per chunk in turn
-// would string their latencies together); inside a block a wave takes every 16th chunk.  The passes
-// wait for loads, not for arithmetic: with 4 waves a wave went through four chunks of a head of 131072
-// tokens one after the other (13.3 us for the kernel, now 11.3; 112 such heads 15.8 and 11.3).
-constexpr int THR_THREADS = 1024, THR_BLOCK = 512, THR_SHORT = 2048;
+// would string their latencies together); inside a block the waves take the chunks in turn.  The passes
+// wait for loads, not for arithmetic: with 4 waves a wave goes through four chunks of a head of 131072
+// tokens one after the other (8 such heads: 13.3 us with 4 waves, 11.3 with 16; 112: 15.8 and 11.3; 512
+// of 100000 48 and 30).  Many pools fill the chip as they are, and 16 waves only wait for each other
+// (4096 heads of 8192 to 65536 tokens: 102 us with 4 waves, 230 with 16).
+constexpr int THR_BLOCK = 512, THR_SHORT = 2048;
+template <int THR_THREADS>
 __global__ __launch_bounds__(THR_THREADS) void msel_thr_kernel(const SegTable T, int fine,
                                                                const uint32_t *__restrict__ cand,
                                                                const int *__restrict__ rec,
@@ -698,29 +701,35 @@ __global__ __launch_bounds__(THR_THREADS) void msel_thr_kernel(const SegTable T,
       }
     }
     __syncthreads();
-    const int cc = cb + tid;
-    const bool mine = tid < THR_BLOCK && cc < nchunks;
-    const int eq = mine ? eq_c[tid] : 0;
-    int eq_all, kept_all;
-    const int eq0 = eq_before + block_exclusive_scan<THR_THREADS>(eq, wsum, &eq_all);
-    const int allow = max(0, min(eq, tie_keep - eq0));
-    const int kept = mine ? above_c[tid] + gt_c[tid] + allow : 0;
-    const int at = pos + block_exclusive_scan<THR_THREADS>(kept, wsum, &kept_all);
-    if (mine) {
-      *reinterpret_cast<int2 *>(coff + 2 * (chunk0 + cc)) = make_int2(at, allow);
-      eq_c[tid] = at;                    // this chunk's count has been read
+    // THR_THREADS chunks at a time
+    for (int u0 = 0; u0 < THR_BLOCK && cb + u0 < nchunks; u0 += THR_THREADS) {
+      const int u = u0 + tid, cc = cb + u;
+      const bool mine = u < THR_BLOCK && cc < nchunks;
+      const int eq = mine ? eq_c[u] : 0;
+      int eq_all, kept_all;
+      const int eq0 = eq_before + block_exclusive_scan<THR_THREADS>(eq, wsum, &eq_all);
+      const int allow = max(0, min(eq, tie_keep - eq0));
+      const int kept = mine ? above_c[u] + gt_c[u] + allow : 0;
+      const int at = pos + block_exclusive_scan<THR_THREADS>(kept, wsum, &kept_all);
+      if (mine) {
+        *reinterpret_cast<int2 *>(coff + 2 * (chunk0 + cc)) = make_int2(at, allow);
+        eq_c[u] = at;                    // this chunk's count has been read
+        gt_c[u] = at + kept;
+      }
+      pos += kept_all;
+      eq_before += eq_all;
     }
     __syncthreads();
-    const int hc = cc - cc % bph;        // first chunk of the head
-    if (mine && cc - hc == bph - 1) {    // its last
-      const int start = hc >= cb ? eq_c[hc - cb] : head_pos;
-      kept_cnt[s.ghead0 + head0 + cc / bph] = T.layer_scope ? at + kept - start : s.k_keep;
+    for (int u = tid; u < THR_BLOCK && cb + u < nchunks; u += THR_THREADS) {
+      const int cc = cb + u, hc = cc - cc % bph;        // first chunk of the head
+      if (cc - hc == bph - 1) {                         // its last
+        const int start = hc >= cb ? eq_c[hc - cb] : head_pos;
+        kept_cnt[s.ghead0 + head0 + cc / bph] = T.layer_scope ? gt_c[u] - start : s.k_keep;
+      }
     }
     const int open = (cb + THR_BLOCK) / bph * bph;      // the head that the next block begins in
-    if (open >= cb + THR_BLOCK) head_pos = pos + kept_all;
+    if (open >= cb + THR_BLOCK) head_pos = pos;
     else if (open >= cb && open < nchunks) head_pos = eq_c[open - cb];
-    pos += kept_all;
-    eq_before += eq_all;
   }
 }
 
@@ -891,27 +900,32 @@ struct OstatIndex {
   long long first[MAX_SEG];
   int per_head[MAX_SEG];
 };
-// A workgroup takes BLEND_ROUNDS of the SEL_ROUNDS rounds of a chunk (half of it): a call of few heads has
-// too few whole chunks to fill the chip, and the scores are requested before the head's sums are added up,
-// which hides a load latency (32 heads of 16383 tokens: 10.2 us, with whole chunks
-// and the loads behind the sums 15.2).
-constexpr int BLEND_ROUNDS = SEL_ROUNDS / 2;
+// A workgroup takes a chunk in parts of PART rounds: the fp64 arithmetic of a whole chunk at once would take
+// so many registers that only three workgroups fit a CU.  HALF: one part each, where whole chunks are too
+// few to fill the chip; its scores are requested before the head's sums are added up, which hides a load
+// latency.  32 heads of 16383 tokens (64 chunks): 15.2 us whole, 10.2 halved; 256 heads of 32768 (1024
+// chunks): 26.7 and 31.3.
+template <bool HALF>
 __global__ __launch_bounds__(CHUNK_THREADS) void blend_apply_kernel(
     const SegTable T, const OstatIndex X, float lambda, float *__restrict__ scores,
     const double *__restrict__ ostat, int *__restrict__ hist1) {
   __shared__ double wd[CHUNK_THREADS / 64][4];
   __shared__ int hist[HIST1_BINS];
-  const SelWhere q = sel_locate(T, blockIdx.x / (SEL_ROUNDS / BLEND_ROUNDS));
-  const int r0 = blockIdx.x % (SEL_ROUNDS / BLEND_ROUNDS) * BLEND_ROUNDS;
+  constexpr int PART = SEL_ROUNDS / 2;
+  const SelWhere q = sel_locate(T, HALF ? blockIdx.x >> 1 : blockIdx.x);
+  const int r_first = HALF ? (int)(blockIdx.x & 1) * PART : 0;
   const Seg &s = T.s[q.seg];
-  if (s.attn == nullptr || q.tok_begin + 4 * r0 * CHUNK_THREADS >= q.tok_end) return;     // uniform
+  if (s.attn == nullptr || q.tok_begin + 4 * r_first * CHUNK_THREADS >= q.tok_end) return;     // uniform
   const int n = s.n, tid = threadIdx.x;
   float *o = scores + s.score_off + (long long)q.head * n;
   const float *a = s.attn + (long long)q.head * n;
   const float a0 = a[0];
-  float fa[BLEND_ROUNDS][4], fo[BLEND_ROUNDS][4];
-  const unsigned valid = load_scores_part<BLEND_ROUNDS>(a, q, r0, fa);
-  load_scores_part<BLEND_ROUNDS>(o, q, r0, fo);
+  float fa[PART][4], fo[PART][4];
+  unsigned valid = 0;
+  if (HALF) {
+    valid = load_scores_part<PART>(a, q, r_first, fa);
+    load_scores_part<PART>(o, q, r_first, fo);
+  }
   // where the head's sums start: its first score workgroup
   const int obph = X.per_head[q.seg];
   const long long ob = X.first[q.seg] + (long long)(q.head - s.head_begin) * obph;
@@ -920,25 +934,33 @@ __global__ __launch_bounds__(CHUNK_THREADS) void blend_apply_kernel(
   const Moments M = moments(ostat + 4 * ob, obph, n, (double)a0, wd);     // has a barrier
   const double mo = M.mo, ma = M.ma, ia = M.ia, io = M.io * (double)lambda;
   typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
-#pragma unroll
-  for (int r = 0; r < BLEND_ROUNDS; ++r) {
-    const unsigned m = (valid >> (4 * r)) & 0xfu;
-    if (m == 0) continue;
-    float v[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      v[e] = (float)(((double)fa[r][e] - ma) * ia + ((double)fo[r][e] - mo) * io);
-      if (hist1 != nullptr && (m >> e & 1)) atomicAdd(&hist[score_key(v[e]) >> 20], 1);
+#pragma unroll 1
+  for (int r0 = r_first; r0 < (HALF ? r_first + PART : SEL_ROUNDS); r0 += PART) {
+    if (!HALF) {
+      if (q.tok_begin + 4 * r0 * CHUNK_THREADS >= q.tok_end) break;       // uniform
+      valid = load_scores_part<PART>(a, q, r0, fa);
+      load_scores_part<PART>(o, q, r0, fo);
     }
-    const int i0 = q.tok_begin + 4 * ((r0 + r) * CHUNK_THREADS + tid);
-    if (m == 0xfu) {
-      f32x4_any t;
-      t.x = v[0]; t.y = v[1]; t.z = v[2]; t.w = v[3];
-      *reinterpret_cast<f32x4_any *>(o + i0) = t;
-    } else {
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (m >> e & 1) o[i0 + e] = v[e];
+    for (int r = 0; r < PART; ++r) {
+      const unsigned m = (valid >> (4 * r)) & 0xfu;
+      if (m == 0) continue;
+      float v[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        v[e] = (float)(((double)fa[r][e] - ma) * ia + ((double)fo[r][e] - mo) * io);
+        if (hist1 != nullptr && (m >> e & 1)) atomicAdd(&hist[score_key(v[e]) >> 20], 1);
+      }
+      const int i0 = q.tok_begin + 4 * ((r0 + r) * CHUNK_THREADS + tid);
+      if (m == 0xfu) {
+        f32x4_any t;
+        t.x = v[0]; t.y = v[1]; t.z = v[2]; t.w = v[3];
+        *reinterpret_cast<f32x4_any *>(o + i0) = t;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (m >> e & 1) o[i0 + e] = v[e];
+      }
     }
   }
   if (hist1 != nullptr) {
@@ -995,8 +1017,12 @@ hipError_t launch_select_pools(const SegTable &T, const float *scores, int *hist
   hipLaunchKernelGGL(msel_cand_kernel, dim3(nb), dim3(CHUNK_THREADS), 0, st, T, fine, scores, hist1,
                      cand, rec, state);
   if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
-  hipLaunchKernelGGL(msel_thr_kernel, dim3((unsigned)z.pools), dim3(THR_THREADS), 0, st, T, fine, cand,
-                     rec, coff, state, kept_cnt);
+  if (z.pools <= 1024)          // see msel_thr_kernel
+    hipLaunchKernelGGL(msel_thr_kernel<1024>, dim3((unsigned)z.pools), dim3(1024), 0, st, T, fine, cand,
+                       rec, coff, state, kept_cnt);
+  else
+    hipLaunchKernelGGL(msel_thr_kernel<256>, dim3((unsigned)z.pools), dim3(256), 0, st, T, fine, cand,
+                       rec, coff, state, kept_cnt);
   if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
   hipLaunchKernelGGL(msel_emit_kernel, dim3(nb), dim3(CHUNK_THREADS), 0, st, T, scores, cand, rec,
                      coff, state, kept_idx);
@@ -1021,7 +1047,8 @@ bool blend_wanted(const SegTable &T) {
 hipError_t launch_blend(const SegTable &T, float lambda, int score_tokens, float *scores,
                         const double *ostat, int *hist1, hipStream_t st) {
   if (!blend_wanted(T) || T.nheads <= 0) return hipSuccess;
-  const long long nb = select_chunks(T) * (SEL_ROUNDS / BLEND_ROUNDS);
+  const bool half = select_chunks(T) <= 512;        // see blend_apply_kernel
+  const long long nb = select_chunks(T) * (half ? 2 : 1);
   if (nb > 0x7fffffffll) return hipErrorInvalidValue;
   OstatIndex X;
   long long ob = 0;
@@ -1030,8 +1057,12 @@ hipError_t launch_blend(const SegTable &T, float lambda, int score_tokens, float
     X.per_head[i] = i < T.nseg ? blocks_per_head(T.s[i].n, score_tokens, SCORE_STEP) : 0;
     if (i < T.nseg) ob += (long long)X.per_head[i] * T.s[i].head_count;
   }
-  hipLaunchKernelGGL(blend_apply_kernel, dim3((unsigned)nb), dim3(CHUNK_THREADS), 0, st, T, X, lambda,
-                     scores, ostat, hist1);
+  if (half)
+    hipLaunchKernelGGL(blend_apply_kernel<true>, dim3((unsigned)nb), dim3(CHUNK_THREADS), 0, st, T, X, lambda,
+                       scores, ostat, hist1);
+  else
+    hipLaunchKernelGGL(blend_apply_kernel<false>, dim3((unsigned)nb), dim3(CHUNK_THREADS), 0, st, T, X, lambda,
+                       scores, ostat, hist1);
   return hipGetLastError();
 }
 

@@ -143,6 +143,20 @@ def test_select_many_chunks_all_equal(C):
     _select_case(C, [17001], [0.4], 1, 180, lambda r, m: np.full(m, -0.5), 9, scope=C.SCOPE_LAYER)
 
 
+
+# more than 1024 pools take the threshold kernel of 4 waves; 600 chunks a pool are more than it scans at once
+@pytest.mark.parametrize("H,n", [(3, 50), (600, 2)])
+def test_select_many_pools(C, H, n):
+    _select_case(C, [n], [0.3], 1030, H, lambda r, m: r.integers(0, 9, m) / 8.0, 10, scope=C.SCOPE_LAYER)
+
+
+@pytest.mark.parametrize("L", [64, 65])      # 512 chunks are blended in halves, 520 whole
+def test_blend_of_many_chunks(C, L):
+    w = W.config1(DEV, L=L, H=8, n=200)
+    w.requests[0].attn = W.synthetic_attention_scores(L, 8, 200, device=DEV, seed=L)
+    U.run_and_check(C, w, DEV, heads=[(0, 0, 0), (0, L // 2, 3), (0, L - 1, 7)])
+
+
 def test_layer_scope_compress_end_to_end(C):
     _say("compress, layer scope: config 2 shape (L=2, H=4, n=3000) and a ragged batch")
     for w in (W.config2(DEV, L=2, H=4, n=3000), W.config4(DEV, L=1, H=3, n_req=3, n_lo=500, n_hi=2500)):
