@@ -68,8 +68,8 @@ __device__ __forceinline__ void wave_fence() {
 // Inverse of the Cholesky factor of a 16 x 16 diagonal block, by one wave.  Lane i of every
 // 16-lane row holds row i of the block (row[], the lanes above 15 repeat what lanes 0..15 do) and
 // the ridged diagonal entry d0 of its row; on return x[i] of lane j is X[i][j], X = L^{-1}.  A
-// pivot that is not above PIVOT_REL d0 is dropped (row and column of X zero); returns whether
-// none was.
+// pivot that is not above PIVOT_REL d0 is dropped (row and column of X zero, or NaN where the block
+// is not finite: such a head's scores have to come out as NaN); returns whether none was.
 // Bound: the dependent chain of 16 pivots and the 120 broadcasts; three panels take about 6 us
 // where an elimination through LDS and scalar registers, with its square root on the chain, took
 // 15.6 us (k_s = 48).  The elimination is the square-root free one (u_i the
@@ -122,8 +122,7 @@ __device__ __forceinline__ bool chol16_inverse(double (&row)[16], double d0, dou
   const double rs = ok_mine ? rsqrt(d_mine) : 0.0;
   static_for<0, 16>([&](auto ic) {
     constexpr int i = decltype(ic)::value;
-    const double ri = bcast16<i>(rs);
-    x[i] = ri == 0.0 ? 0.0 : x[i] * ri;
+    x[i] *= bcast16<i>(rs);
   });
   return all_ok;
 }

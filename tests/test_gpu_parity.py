@@ -503,6 +503,31 @@ def test_degenerate_inputs_are_flagged_not_fatal(C):
     assert np.all(np.diff(kept[300:]) > 0)
 
 
+@pytest.mark.parametrize("ks", [16, 32, 48, 64, 0])
+@pytest.mark.parametrize("what", ["nan", "inf", "overflow"])
+def test_non_finite_keys_poison_their_head_only(C, ks, what):
+    """A NaN or infinity among a head's keys, or keys whose Gram matrix overflows, leave no pivot to
+    divide by: every score of that head is NaN and flagged, whatever the number of panels (k_s = 16 is
+    one, exact mode eight), and the head beside it scores as it does alone."""
+    n = 700
+    w = W.config1(device=DEV, L=1, H=2, n=n, ratio=0.5)
+    w.sketch_dim, w.ridge_rel = ks, 0.0 if ks else 1e-4
+    params, reqs = U.make_call(C, w, DEV)
+    want, _ = C.compactor_score(params, reqs)
+    if what == "overflow":
+        w.requests[0].k[0, 0] *= 1e20
+    else:
+        w.requests[0].k[0, 0, 17, 5] = float(what)
+    out = C.compactor_compress(params, reqs, want_scores=True)
+    torch.cuda.synchronize()
+    s, status = out["scores"], out["status"].cpu().numpy()
+    assert bool(torch.isnan(s[:n]).all())
+    assert status[0] == C.STATUS_PIVOT | C.STATUS_NONFINITE and status[1] == C.STATUS_OK
+    assert torch.equal(s[n:].view(torch.int32), want[n:].view(torch.int32))
+    kept = out["kept_idx"].cpu().numpy()
+    assert np.array_equal(kept[:n // 2], np.arange(n // 2))        # all tie: lowest indices win
+
+
 def test_error_codes_reach_python(C):
     w = W.config1(device=DEV, L=1, H=1, n=64)
     params, reqs = U.make_call(C, w, DEV)
