@@ -395,6 +395,18 @@ struct PagePool {
   int page_size, num_pages;
   PageTab t[MAX_SEG];     // by segment of the launch
 };
+// Rows of an in-place compaction, in runs of run_rows.  Indices and page entries are fetched up to three
+// runs ahead, past the end of the list: rows are numbered in 64 bits, so that a list of nearly 2^31 rows
+// does not wrap round into negative numbers that pass for rows of it.
+__host__ __device__ __forceinline__ long long inplace_row(int run, int run_rows, int row_of_run) {
+  return (long long)run * run_rows + row_of_run;
+}
+__host__ __device__ __forceinline__ int inplace_runs(int rows, int run_rows) {
+  return rows > 0 ? (int)(((long long)rows + run_rows - 1) / run_rows) : 0;
+}
+// Token tok (-1: none fetched) moves to the place of row j: not where it lies already or would move back.
+__host__ __device__ __forceinline__ bool inplace_moves(int tok, long long j, int n) { return tok > j && tok < n; }
+
 // in_place: the rows are read from the pages themselves (token t at logical slot t).
 hipError_t launch_gather_paged(const SegTable &T, const PagePool &P, const int32_t *kept_idx,
                                const int32_t *kept_cnt, bool in_place, hipStream_t st);

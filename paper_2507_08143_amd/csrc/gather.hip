@@ -287,9 +287,9 @@ __global__ __launch_bounds__(INPLACE_THREADS) void compact_inplace_kernel(
 #pragma unroll
     for (int o = 0; o < I::OWN; ++o) {
       const int jr = o * INPLACE_THREADS + tid;
-      const unsigned j = (unsigned)run * I::RUN + jr;       // runs past the end may pass 2^31
+      const long long j = inplace_row(run, I::RUN, jr);
       tok[o] = -1;
-      if (jr < I::RUN && j < (unsigned)rows) tok[o] = idx[j];
+      if (jr < I::RUN && j < rows) tok[o] = idx[j];
     }
   };
   auto split = [&](int j, int &lp, int &slot) {
@@ -299,13 +299,13 @@ __global__ __launch_bounds__(INPLACE_THREADS) void compact_inplace_kernel(
   auto fetch_pages = [&](int run, const int (&tok)[I::OWN], RowPages (&pg)[I::OWN]) {
 #pragma unroll
     for (int o = 0; o < I::OWN; ++o) {
-      const int j = run * I::RUN + o * INPLACE_THREADS + tid;
+      const long long j = inplace_row(run, I::RUN, o * INPLACE_THREADS + tid);
       pg[o] = RowPages{-1, -1, 0, 0};
-      if (tok[o] > j && tok[o] < s.n) {           // tok == j: already in place; below: skipped
+      if (inplace_moves(tok[o], j, s.n)) {
         int lp;
         split(tok[o], lp, pg[o].src_slot);
         if (lp < tlen) pg[o].src = table[lp];
-        split(j, lp, pg[o].dst_slot);
+        split((int)j, lp, pg[o].dst_slot);
         if (lp < tlen) pg[o].dst = table[lp];
       }
     }
@@ -344,7 +344,7 @@ __global__ __launch_bounds__(INPLACE_THREADS) void compact_inplace_kernel(
   int tok[I::OWN];
   RowPages pg[I::OWN];
   uint4 a[I::PASSES], b[I::PASSES];
-  const int runs = (rows + I::RUN - 1) / I::RUN;
+  const int runs = inplace_runs(rows, I::RUN);
   fetch_idx(0, tok);
   fetch_pages(0, tok, pg);
   fetch_idx(1, tok);

@@ -1,0 +1,8 @@
+// The host side of the kernels' index and key arithmetic, for test_device_math.py.
+#include "common.h"
+
+extern "C" {
+long long inplace_row(int run, int run_rows, int row_of_run) { return cmp::inplace_row(run, run_rows, row_of_run); }
+int inplace_runs(int rows, int run_rows) { return cmp::inplace_runs(rows, run_rows); }
+int inplace_moves(int tok, long long j, int n) { return cmp::inplace_moves(tok, j, n); }
+}
