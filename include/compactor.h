@@ -236,6 +236,8 @@ typedef struct compactor_page_table {
  *   requests' tensors are not used and may be NULL); afterwards the first ceil(count / page_size)
  *   logical pages hold the head and the others can be released.  kept_idx must be ascending
  *   per head (as compactor_select writes it); an entry below its own rank is skipped.
+ *   K and V of a slot may share memory (v_pages == k_pages, or v_pages less than head_dim elements
+ *   from k_pages); apart from that no element of the pool may belong to two rows.
  * tables[b].len must cover ceil(rows / page_size) logical pages, rows = n_b when in place, else
  * k_keep_b (layer scope: min(n_b, H*k_keep_b), since one head may take the whole budget).
  * For callers whose cache is paged; no part of the paper. */

@@ -247,17 +247,28 @@ struct Inplace {
   static constexpr int SLICES = 16 / LANES;             // column slices of a row
 };
 
+// Elements between the starts of the K and the V row of a slot that lie inside one another's row (0: the
+// same memory), or -1: K and V rows of a slot are apart, as they nearly always are.  A pool may hold both
+// in one row (V a part of what K is read from); slices of K and of V would then move the shared columns
+// each at its own pace, so the row from the start of the first to the end of the second moves as one.
+__host__ __device__ __forceinline__ int shared_row_shift(const PagePool &P) {
+  const intptr_t d = (reinterpret_cast<intptr_t>(P.v) - reinterpret_cast<intptr_t>(P.k)) / (intptr_t)sizeof(uint16_t);
+  const intptr_t a = d < 0 ? -d : d;
+  return a < D ? (int)a : -1;
+}
+
 // Pages of the rows j (destination) and tok (source), -1 where the row does not move.
 struct RowPages { int src, dst, src_slot, dst_slot; };
 
-template <int LANES>
+// SHARED: K and V lie in one row of `pieces` 16-byte pieces from the lower of their addresses.
+template <int LANES, bool SHARED>
 __global__ __launch_bounds__(INPLACE_THREADS) void compact_inplace_kernel(
-    const SegTable T, const PagePool P, int page_shift, const int32_t *__restrict__ kept_idx,
+    const SegTable T, const PagePool P, int page_shift, int pieces, const int32_t *__restrict__ kept_idx,
     const int32_t *__restrict__ kept_cnt) {
   typedef Inplace<LANES> I;
   __shared__ long long src_l[3][I::RUN], dst_l[3][I::RUN];   // element offsets; -1: does not move
   // blocks b, b + 8, b + 16, .. (one XCD, hence one L2) hold the slices of one head
-  const int parts = 2 * I::SLICES;
+  const int parts = SHARED ? (pieces + LANES - 1) / LANES : 2 * I::SLICES;
   const int part = (blockIdx.x >> 3) % parts, oct = (blockIdx.x >> 3) / parts;
   const int hb = 8 * oct + (blockIdx.x & 7);
   if (hb >= T.nheads) return;
@@ -277,8 +288,10 @@ __global__ __launch_bounds__(INPLACE_THREADS) void compact_inplace_kernel(
   const int tlen = P.t[w.seg].len;
   const int tid = threadIdx.x;
   const int lane = tid & (LANES - 1), sub = tid / LANES;
-  uint16_t *base = (part & 1 ? P.v : P.k) + ((long long)layer * P.layer_stride + (long long)h * P.head_stride) +
-                   (part >> 1) * (LANES * 8) + lane * 8;
+  const int slice = SHARED ? part : part >> 1;
+  uint16_t *base = (SHARED ? (P.v < P.k ? P.v : P.k) : part & 1 ? P.v : P.k) +
+                   ((long long)layer * P.layer_stride + (long long)h * P.head_stride) + slice * (LANES * 8) + lane * 8;
+  const bool have = !SHARED || slice * LANES + lane < pieces;
 
   // The address of a row takes three dependent loads (its index, two table entries); they are
   // spread over the runs before: indices three runs ahead, table entries two.  Each thread does
@@ -328,7 +341,7 @@ __global__ __launch_bounds__(INPLACE_THREADS) void compact_inplace_kernel(
 #pragma unroll
     for (int p = 0; p < I::PASSES; ++p) {
       r[p] = make_uint4(0, 0, 0, 0);
-      if (src[p] >= 0)     // whole rows are read once; a 128-byte line shared by slices may be cached
+      if (src[p] >= 0 && have)     // whole rows are read once; a 128-byte line shared by slices may be cached
         r[p] = LANES == 16 ? load_stream16(base + src[p]) : *reinterpret_cast<const uint4 *>(base + src[p]);
     }
   };
@@ -338,7 +351,7 @@ __global__ __launch_bounds__(INPLACE_THREADS) void compact_inplace_kernel(
     for (int p = 0; p < I::PASSES; ++p) dst[p] = dst_l[slot][p * I::ROWS + sub];
 #pragma unroll
     for (int p = 0; p < I::PASSES; ++p)
-      if (dst[p] >= 0) store_stream16(base + dst[p], r[p]);
+      if (dst[p] >= 0 && have) store_stream16(base + dst[p], r[p]);
   };
 
   int tok[I::OWN];
@@ -372,14 +385,15 @@ __global__ __launch_bounds__(INPLACE_THREADS) void compact_inplace_kernel(
   }
 }
 
-template <int LANES>
+template <int LANES, bool SHARED = false>
 static hipError_t launch_inplace(const SegTable &T, const PagePool &P, const int32_t *kept_idx,
-                                 const int32_t *kept_cnt, hipStream_t st) {
-  const long long nb = ((long long)T.nheads + 7) / 8 * 8 * 2 * Inplace<LANES>::SLICES;
+                                 const int32_t *kept_cnt, hipStream_t st, int pieces = 0) {
+  const int parts = SHARED ? (pieces + LANES - 1) / LANES : 2 * Inplace<LANES>::SLICES;
+  const long long nb = ((long long)T.nheads + 7) / 8 * 8 * parts;
   if (nb > 0x7fffffffll) return hipErrorInvalidValue;
   const int shift = (P.page_size & (P.page_size - 1)) == 0 ? __builtin_ctz((unsigned)P.page_size) : -1;
-  hipLaunchKernelGGL((compact_inplace_kernel<LANES>), dim3((unsigned)nb), dim3(INPLACE_THREADS), 0, st, T, P, shift,
-                     kept_idx, kept_cnt);
+  hipLaunchKernelGGL((compact_inplace_kernel<LANES, SHARED>), dim3((unsigned)nb), dim3(INPLACE_THREADS), 0, st, T, P,
+                     shift, pieces, kept_idx, kept_cnt);
   return hipGetLastError();
 }
 
@@ -387,6 +401,8 @@ hipError_t launch_gather_paged(const SegTable &T, const PagePool &P, const int32
                                const int32_t *kept_cnt, bool in_place, hipStream_t st) {
   if (T.nheads <= 0) return hipSuccess;
   if (in_place) {
+    const int shift = shared_row_shift(P);
+    if (shift >= 0) return launch_inplace<16, true>(T, P, kept_idx, kept_cnt, st, (D + shift) / 8);
     // slices by the number of heads (see compact_inplace_kernel for the times on both sides)
     if (T.nheads <= 16) return launch_inplace<4>(T, P, kept_idx, kept_cnt, st);
     if (T.nheads <= 64) return launch_inplace<8>(T, P, kept_idx, kept_cnt, st);

@@ -890,6 +890,30 @@ def test_compact_in_place_slices(C, L, H, n, ratio, scope, page):
     _paged_case(C, W.config1(DEV, L=L, H=H, n=n, ratio=ratio), scope, page, True, 35)
 
 
+@pytest.mark.parametrize("width,k_at,v_at", [(128, 0, 0), (192, 0, 64), (136, 8, 0), (248, 120, 0)])
+@pytest.mark.parametrize("H,n,page", [(1, 2600, 16), (40, 700, 7)])
+def test_compact_in_place_where_k_and_v_share_a_row(C, width, k_at, v_at, H, n, page):
+    """One row of `width` channels per slot holds both tensors, K from channel k_at, V from v_at: the
+    retained rows move whole, as in the sequential replay of the same list."""
+    rng = np.random.default_rng(36)
+    need = (n + page - 1) // page
+    pool = torch.randint(-30000, 30000, (need + 3, page, 1, H, width), dtype=torch.int16, device=DEV)
+    rows = pool.view(torch.bfloat16).permute(0, 2, 1, 3, 4)
+    table = rng.permutation(need + 3).astype(np.int32)[:need]
+    kept = np.stack([np.sort(rng.choice(n, n // 2, replace=False)) for _ in range(H)]).astype(np.int32)
+    want = pool.cpu().numpy()
+    for h in range(H):
+        O.compact_pages_in_place(want[:, :, 0, h], kept[h], table)
+    k = torch.empty(1, H, n, 128, dtype=torch.bfloat16, device=DEV)              # sizes only
+    C.compactor_compact_paged(C.Params(1, H, sketch_dim=48), [C.Request(k_score=k, v_cache=k, ratio=0.5)],
+                              torch.from_numpy(kept).to(DEV).view(-1),
+                              torch.full((H,), n // 2, dtype=torch.int32, device=DEV),
+                              rows[..., k_at:k_at + 128], rows[..., v_at:v_at + 128],
+                              [torch.from_numpy(table).to(DEV)], in_place=True)
+    torch.cuda.synchronize()
+    assert np.array_equal(pool.cpu().numpy(), want)
+
+
 def test_compact_into_pages_error_codes(C):
     w = W.config2(DEV, L=1, H=2, n=300)
     params, reqs = U.make_call(C, w, DEV)
