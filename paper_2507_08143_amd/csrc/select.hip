@@ -294,6 +294,9 @@ __global__ __launch_bounds__(SELECT_THREADS) void select_kernel(const SegTable T
 constexpr int CHUNK_THREADS = 256;
 constexpr int SEL_ROUNDS = SEL_CHUNK / (4 * CHUNK_THREADS);    // 4-token groups per thread
 constexpr int SEL_STATE = 8;             // ints of state per pool:
+// A chunk's pair of ints in the records and in the offsets.  They stand behind a candidate list of one int
+// per token, so a launch with an odd number of tokens leaves them on 4-byte boundaries only.
+typedef int i32x2_any __attribute__((ext_vector_type(2), aligned(4)));
 enum { ST_BIN = 0, ST_NEED1, ST_THR, ST_TIES };
 static_assert(SEL_ROUNDS >= 1 && SEL_ROUNDS <= 8, "one validity bit per token in 32 bits");
 
@@ -616,7 +619,7 @@ __global__ __launch_bounds__(THR_THREADS) void msel_thr_kernel(const SegTable T,
   auto fetch = [&](int cb) {
     __syncthreads();
     for (int u = tid; u < THR_BLOCK && cb + u < nchunks; u += THR_THREADS) {
-      const int2 r = *reinterpret_cast<const int2 *>(rec + 2 * (chunk0 + cb + u));
+      const i32x2_any r = *reinterpret_cast<const i32x2_any *>(rec + 2 * (chunk0 + cb + u));
       above_c[u] = r.x;
       cnt_c[u] = r.y;
     }
@@ -712,7 +715,7 @@ __global__ __launch_bounds__(THR_THREADS) void msel_thr_kernel(const SegTable T,
       const int kept = mine ? above_c[u] + gt_c[u] + allow : 0;
       const int at = pos + block_exclusive_scan<THR_THREADS>(kept, wsum, &kept_all);
       if (mine) {
-        *reinterpret_cast<int2 *>(coff + 2 * (chunk0 + cc)) = make_int2(at, allow);
+        *reinterpret_cast<i32x2_any *>(coff + 2 * (chunk0 + cc)) = i32x2_any{at, allow};
         eq_c[u] = at;                    // this chunk's count has been read
         gt_c[u] = at + kept;
       }
@@ -764,7 +767,7 @@ __global__ __launch_bounds__(CHUNK_THREADS, 8) void msel_emit_kernel(const SegTa
   const int limit = ph * s.k_keep;                       // rows of the pool's output
   int32_t *out = kept_idx + (s.kept_off + (long long)(q.head / ph) * limit);
   const uint32_t thr = (uint32_t)state[q.pool * SEL_STATE + ST_THR];
-  const int2 pa = *reinterpret_cast<const int2 *>(coff + 2 * blockIdx.x);
+  const i32x2_any pa = *reinterpret_cast<const i32x2_any *>(coff + 2 * blockIdx.x);
   const int pos0 = pa.x, allow = pa.y;
   // key > thr and key == thr as float comparisons; a threshold that is NaN (key 0) equals NaN only and
   // every number lies above it

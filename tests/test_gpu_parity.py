@@ -139,6 +139,13 @@ def test_select_bins_and_marks(C, maker, L, H, ns, ratios, scope):
     _select_case(C, ns, ratios, L, H, maker, 8, scope=scope)
 
 
+# an odd number of tokens in the launch: the chunks' records behind the candidate list are 4-byte aligned
+@pytest.mark.parametrize("L,H,ns,ratios,scope", [(1, 1, [40003], [0.3], 0), (1, 3, [43691], [0.2], 0),
+                                                 (3, 1, [8193, 20001, 41], [0.4, 0.1, 0.9], 1)])
+def test_select_odd_token_totals(C, L, H, ns, ratios, scope):
+    _select_case(C, ns, ratios, L, H, lambda r, m: r.random(m) ** 4, 41, scope)
+
+
 def test_select_many_chunks_all_equal(C):
     _select_case(C, [17001], [0.4], 1, 180, lambda r, m: np.full(m, -0.5), 9, scope=C.SCOPE_LAYER)
 
