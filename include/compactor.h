@@ -260,9 +260,11 @@ int compactor_compress(const compactor_params_t *p, const compactor_request_t *r
  * library runs on holds its own copy from the first use until the process ends.  The call
  * allocates and frees nothing (no hipMalloc, no hipFree, no allocating library routine); inputs
  * and outputs are the caller's, as in compactor_compress, and the results are the same bits.
- * A batch whose scratch (compactor_workspace_size; pass scores != NULL to keep the scores out of
- * it) exceeds COMPACTOR_STATIC_SCRATCH_BYTES is refused with COMPACTOR_EWORKSPACE before anything
- * is enqueued; params.group_bytes bounds the scratch of a large batch.  All calls on one GPU share
+ * A batch whose scratch exceeds COMPACTOR_STATIC_SCRATCH_BYTES is refused with COMPACTOR_EWORKSPACE
+ * before anything is enqueued.  Only the scratch that the call cannot do without counts, which is what
+ * compactor_workspace_size reports less the part that merely speeds the factorisation up (and less
+ * the scores, if scores != NULL): a batch whose compactor_workspace_size fits is always accepted, one
+ * somewhat larger may be.  params.group_bytes bounds the scratch of a large batch.  All calls on one GPU share
  * that GPU's buffer: calls that overlap in time on one GPU (two streams, two threads) race on it
  * and must be serialised by the caller.  The buffer keeps the last call's contents; whatever has
  * to start at zero is cleared by the call's own kernels.  The first call on a device looks the

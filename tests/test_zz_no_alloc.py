@@ -77,6 +77,16 @@ def test_static_scratch_compress_equals_compress():
     _same(ref, got, "first shape again")
 
 
+def test_static_scratch_needs_no_room_for_what_only_speeds_a_call_up():
+    C = U.binding()
+    _say("compress on the static scratch: a batch that fits it without the factorisation's shares")
+    w = W.config1(DEV, L=1, H=256, n=1000)
+    w.sketch_dim = 64
+    params, reqs = U.make_call(C, w, DEV)
+    assert C.compactor_workspace_size(params, reqs) > C.STATIC_SCRATCH_BYTES
+    _case(C, w, "256 heads, k_s = 64")
+
+
 def test_static_scratch_refuses_what_does_not_fit():
     C = U.binding()
     _say("compress on the static scratch: a batch whose scratch exceeds the buffer is refused")
