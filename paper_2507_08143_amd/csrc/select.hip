@@ -581,11 +581,14 @@ __device__ __forceinline__ void for_each_cand(const uint32_t *__restrict__ l, in
 // tied scores) or the pool has more than THR_BLOCK chunks, a third pass counts instead.
 // The chunks' records are fetched into LDS in blocks of THR_BLOCK (a load per chunk in turn
 // would string their latencies together); inside a block the waves take the chunks in turn.  The passes
-// wait for loads, not for arithmetic: with 4 waves a wave goes through four chunks of a head of 131072
-// tokens one after the other (8 such heads: 13.3 us with 4 waves, 11.3 with 16; 112: 15.8 and 11.3; 512
-// of 100000 48 and 30).  Many pools fill the chip as they are, and 16 waves only wait for each other
-// (4096 heads of 8192 to 65536 tokens: 102 us with 4 waves, 230 with 16).
-constexpr int THR_BLOCK = 512, THR_SHORT = 2048;
+// wait for loads, not for arithmetic: with 4 waves a wave goes through several chunks of a pool one
+// after the other, so 16 waves take a pool while every pool has a compute unit to itself.  With more pools
+// the 16 waves only wait for each other.  Whole selection on given scores on MI355X, us with 16 / 4 waves: heads
+// of 40003 tokens, 128 of them 49.1 / 52.0, 256 66 / 67, 384 92 / 88, 512 105 / 100, 768 144 / 133, 1024
+// 184 / 166; of 131072, 256 131 / 138, 384 185 / 184, 640 296 / 288; layers of 8 x 8192, 256 86.6 / 88.8,
+// 384 117 / 113; of 8 x 32768, 256 224 / 240, 384 345 / 349.  Behind the score kernel, selection
+// alone: 256 heads of 66000 55 / 61, 384 76 / 74, 640 of 100000 130 / 121, 1536 of 40003 150 / 122.
+constexpr int THR_BLOCK = 512, THR_SHORT = 2048, THR_WIDE_POOLS = 256;
 template <int THR_THREADS>
 __global__ __launch_bounds__(THR_THREADS) void msel_thr_kernel(const SegTable T, int fine,
                                                                const uint32_t *__restrict__ cand,
@@ -1020,7 +1023,7 @@ hipError_t launch_select_pools(const SegTable &T, const float *scores, int *hist
   hipLaunchKernelGGL(msel_cand_kernel, dim3(nb), dim3(CHUNK_THREADS), 0, st, T, fine, scores, hist1,
                      cand, rec, state);
   if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
-  if (z.pools <= 1024)          // see msel_thr_kernel
+  if (z.pools <= THR_WIDE_POOLS)          // see msel_thr_kernel
     hipLaunchKernelGGL(msel_thr_kernel<1024>, dim3((unsigned)z.pools), dim3(1024), 0, st, T, fine, cand,
                        rec, coff, state, kept_cnt);
   else

@@ -151,10 +151,15 @@ def test_select_many_chunks_all_equal(C):
 
 
 
-# more than 1024 pools take the threshold kernel of 4 waves; 600 chunks a pool are more than it scans at once
+# more than 256 pools take the threshold kernel of 4 waves; 600 chunks a pool are more than it scans at once
 @pytest.mark.parametrize("H,n", [(3, 50), (600, 2)])
 def test_select_many_pools(C, H, n):
     _select_case(C, [n], [0.3], 1030, H, lambda r, m: r.integers(0, 9, m) / 8.0, 10, scope=C.SCOPE_LAYER)
+
+
+@pytest.mark.parametrize("L", [256, 257])    # 16 waves a pool, then 4
+def test_select_pools_at_the_limit_of_the_wide_threshold_kernel(C, L):
+    _select_case(C, [8200], [0.2], L, 2, lambda r, m: np.round(r.random(m) ** 4, 4), 42, scope=C.SCOPE_LAYER)
 
 
 @pytest.mark.parametrize("L", [64, 65])      # 512 chunks are blended in halves, 520 whole
