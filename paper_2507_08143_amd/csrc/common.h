@@ -138,24 +138,33 @@ __device__ __forceinline__ uint32_t score_key(float s) {
 
 // First digit of the selection, two ways.  Scores that leave the scoring kernels are tallied there by
 // their top 12 key bits (8 bins an octave).  Scores of a separate selection call are tallied by
-// score_bin, a monotone map of the keys to 3536 bins: magnitudes from 2^-20 up to 2^4, where leverage
-// scores and z-scores lie, have 64 bins an octave, the octaves outside one bin each; negative numbers
+// score_bin, a monotone map of the keys that is finer where thresholds lie: magnitudes from 2^-18 up to
+// 2^4, where leverage scores and z-scores have them, have 64 bins an octave, 24 octaves on either side 8,
+// and those beyond (below 2^-42, from 2^28 on) one each; negative numbers
 // mirror the positive ones, and NaN shares the lowest bin with -inf (whose keys are larger).  Eight bins
 // an octave put a fifth to a quarter of a head's scores into the threshold's bin, and so many lanes of a
 // wave onto one LDS counter that a tally is bound by it (112 heads of 131072 tokens: tally 22 us against
-// 18, threshold 25 against 16).  A scoring workgroup has more to do than tally, and it adds its histogram
-// to the pool's: 64 bins an octave are eight times the adds, and the fused calls take 0.2 to 0.5 %
-// longer with them.
-constexpr int HIST1_BINS = 4096;      // either way (score_bin never counts 3536 ..)
-constexpr uint32_t BIN_LO = 107u << 6, BIN_HI = 131u << 6;   // the fine range, in float bits >> 17
-constexpr int BIN_SIDE = 1768;        // bins of either sign: 107 + 24 * 64 + 125
+// 18, threshold 25 against 16).  One bin an octave, which an earlier map had for everything outside the
+// fine range, puts half of evenly spread scores into it: 112 heads of 131072 scores up to 1000 took 125 us and
+// take 76 now, 600 of 40003 182 and 101, with the top 12 key bits 103 and 122.  A scoring workgroup has
+// more to do than tally, and it adds its histogram to the pool's: 64 bins an octave are eight times the
+// adds, and the fused calls take 0.2 to 0.5 % longer with them.
+constexpr int HIST1_BINS = 4096;      // either way
+constexpr int BIN_SIDE = HIST1_BINS / 2;      // bins of either sign
+// Octaves (exponents of the float) where the density changes.  With x = the float's bits >> 17 (64 to an
+// octave) the bin is the sum of x >> 6, of x >> 3 over the two middle ranges and of x over the fine one,
+// which takes six instructions; every ninth bin of the middle and every 65th of the fine range stays empty.
+constexpr int OCT_A = 85, OCT_B = 109, OCT_C = 131, OCT_D = 155;
+static_assert(256 + 8 * (OCT_B - OCT_A + OCT_D - OCT_C) + 64 * (OCT_C - OCT_B) == BIN_SIDE, "bins for every octave");
+__host__ __device__ __forceinline__ int bin_clamp(int x, int lo, int hi) { return x < lo ? lo : (x > hi ? hi : x); }
 __host__ __device__ __forceinline__ int score_bin(uint32_t key) {
-  const bool pos = (key & 0x80000000u) != 0;
-  const uint32_t x = ((pos ? key : ~key) & 0x7fffffffu) >> 17;
-  const uint32_t lo = x < BIN_LO ? x : BIN_LO, hi = x > BIN_HI ? x : BIN_HI;
-  const uint32_t in = x < BIN_LO ? BIN_LO : (x > BIN_HI ? BIN_HI : x);
-  const int m = (int)((lo >> 6) + (in - BIN_LO) + (hi >> 6) - (BIN_HI >> 6));
-  return pos ? BIN_SIDE + m : BIN_SIDE - 1 - m;
+  const uint32_t neg = ~(uint32_t)((int32_t)key >> 31);      // all ones below zero
+  const uint32_t u = key ^ neg;
+  const int x = (int)(u >> 17 & 0x3fffu), octave = (int)(u >> 23 & 0xffu);
+  const int fine = bin_clamp(x, 64 * OCT_B, 64 * OCT_C);
+  const int mid = bin_clamp(x, 64 * OCT_A, 64 * OCT_D) - fine;       // negative below the fine range
+  const int m = octave + (mid >> 3) + fine - (64 * OCT_B - 8 * (OCT_B - OCT_A));
+  return (m ^ (int)neg) + BIN_SIDE;                          // -1 - m below zero
 }
 // Place of a bin in a pool's histogram in memory: groups of 4 bins stand 256 bytes apart, in different
 // memory channels, because many workgroups add to the same few dozen bins at the same time.
@@ -163,17 +172,32 @@ __host__ __device__ __forceinline__ int hist_at(int bin) {
   return (bin >> 2 & 63) << 6 | bin >> 8 << 2 | (bin & 3);
 }
 
-// Smallest key of a bin and the number of low bits in which the bin's keys differ.
+// Smallest key of a bin that holds keys and the number of low bits in which the bin's keys differ.
 struct BinKeys { uint32_t lo; int bits; };
 __host__ __device__ __forceinline__ BinKeys bin_keys(int bin, bool fine) {
   if (!fine) return BinKeys{(uint32_t)bin << 20, 20};
   const bool pos = bin >= BIN_SIDE;
-  const int m = pos ? bin - BIN_SIDE : BIN_SIDE - 1 - bin;
-  const int fine_lo = (int)(BIN_LO >> 6), fine_hi = fine_lo + (int)(BIN_HI - BIN_LO);
-  const bool in = m >= fine_lo && m < fine_hi;
-  const int bits = in ? 17 : 23;
-  const uint32_t u = in ? (BIN_LO + (uint32_t)(m - fine_lo)) << 17
-                        : (uint32_t)(m < fine_lo ? m : m - fine_hi + (int)(BIN_HI >> 6)) << 23;
+  int m = pos ? bin - BIN_SIDE : BIN_SIDE - 1 - bin;
+  // the ranges of m, each as (first octave, bins an octave, key bits)
+  int x, bits;
+  const int low = 9 * (OCT_B - OCT_A), mid = 65 * (OCT_C - OCT_B), high = 9 * (OCT_D - OCT_C);
+  if (m < OCT_A) {
+    x = 64 * m;
+    bits = 23;
+  } else if ((m -= OCT_A) < low) {
+    x = 64 * (OCT_A + m / 9) + 8 * (m % 9);
+    bits = 20;
+  } else if ((m -= low) < mid) {
+    x = 64 * (OCT_B + m / 65) + m % 65;
+    bits = 17;
+  } else if ((m -= mid) < high) {
+    x = 64 * (OCT_C + m / 9) + 8 * (m % 9);
+    bits = 20;
+  } else {
+    x = 64 * (OCT_D + m - high);
+    bits = 23;
+  }
+  const uint32_t u = (uint32_t)x << 17;
   return BinKeys{pos ? 0x80000000u | u : (0x7fffffffu - u) & ~((1u << bits) - 1u), bits};
 }
 

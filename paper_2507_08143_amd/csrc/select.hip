@@ -575,7 +575,7 @@ __device__ __forceinline__ void for_each_cand(const uint32_t *__restrict__ l, in
 // the pool (in head, token order) the position of its first retained token in the pool's
 // output and how many threshold ties it may keep; the per-head counts.
 // Two passes over the candidates: (1) histogram of the upper 12 bits in which they differ -> second
-// digit d2; (2) per chunk the count above d2, a histogram of the low bits (5 or 11) of those inside d2,
+// digit d2; (2) per chunk the count above d2, a histogram of the low bits (5, 8 or 11) of those inside d2,
 // and those few themselves as (chunk, low bits) in a short LDS list, from which, once the last digit is
 // known, every chunk's counts above and at the threshold follow.  If the list overflows (heavily
 // tied scores) or the pool has more than THR_BLOCK chunks, a third pass counts instead.

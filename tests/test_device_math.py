@@ -4,6 +4,7 @@ import ctypes as C
 import os
 import subprocess
 
+import numpy as np
 import pytest
 
 from paper_2507_08143_amd import build
@@ -38,3 +39,29 @@ def test_in_place_rows_up_to_the_largest_context(M, run_rows):
                 if 0 <= j < most:
                     assert not M.inplace_moves(j, j, most) and (j == 0 or not M.inplace_moves(j - 1, j, most))
                     assert bool(M.inplace_moves(j + 1, j, most)) == (j + 1 < most)
+
+
+def _key(x):
+    u = int(np.float32(x).view(np.uint32))
+    return ~u & 0xffffffff if u >> 31 else u | 0x80000000
+
+
+def test_selection_bins_partition_the_keys(M):
+    """From the first key of one bin to the first of the next, through all 2^32: a bin's keys are those that
+    bin_keys says, bins rise with the keys and fit the histogram, and none of scores that occur (magnitudes
+    2^-42 to 2^28) is wider than the eighth of an octave that the top 12 key bits are."""
+    lo, at, last = C.c_uint(), 0, -1
+    while at < 2 ** 32:
+        b = M.score_bin(at)
+        assert last < b < 4096
+        bits = M.bin_bits(b, 1, C.byref(lo))
+        assert lo.value == at and 17 <= bits <= 23 and M.score_bin(at + (1 << bits) - 1) == b
+        last, at = b, at + (1 << bits)
+    assert M.score_bin(0) == 0 and M.score_bin(_key(-np.inf)) == 0 and M.score_bin(_key(np.inf)) == 4095
+    for sign in (1.0, -1.0):
+        for e in range(-42, 28):
+            for f in (1.0, 1.3, 1.999):
+                bits = M.bin_bits(M.score_bin(_key(sign * np.ldexp(f, e))), 1, C.byref(lo))
+                assert bits == (17 if -18 <= e < 4 else 20)
+    for b in (0, 1, 2047, 2048, 4095):
+        assert M.bin_bits(b, 0, C.byref(lo)) == 20 and lo.value == b << 20

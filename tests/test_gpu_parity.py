@@ -139,6 +139,13 @@ def test_select_bins_and_marks(C, maker, L, H, ns, ratios, scope):
     _select_case(C, ns, ratios, L, H, maker, 8, scope=scope)
 
 
+# thresholds where bins are an eighth of an octave wide, and where they are a whole one, of either sign
+@pytest.mark.parametrize("scale", [1e3, -1e7, 1e12, 1e-9, -1e-11, 1e-20])
+@pytest.mark.parametrize("L,H,ns,ratios,scope", [(1, 2, [9001, 40003], [0.3, 0.6], 0), (1, 3, [8193], [0.45], 1)])
+def test_select_scores_of_any_scale(C, scale, L, H, ns, ratios, scope):
+    _select_case(C, ns, ratios, L, H, lambda r, m: scale * r.random(m), 43, scope)
+
+
 # an odd number of tokens in the launch: the chunks' records behind the candidate list are 4-byte aligned
 @pytest.mark.parametrize("L,H,ns,ratios,scope", [(1, 1, [40003], [0.3], 0), (1, 3, [43691], [0.2], 0),
                                                  (3, 1, [8193, 20001, 41], [0.4, 0.1, 0.9], 1)])
