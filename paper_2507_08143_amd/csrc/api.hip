@@ -76,14 +76,23 @@ int compute_units() {
 
 // Gram: a persistent launch of 2 workgroups per compute unit (or as many as there are tiles),
 // each taking an equal run of 64-row tiles; of 1 where few heads' partials weigh more in the
-// factorisation than the second workgroup saves.  Whole call on MI355X, us with 1 / 2 workgroups a unit:
-// 8 heads of 20000 tokens 85.6 / 90.2, 32768 101.3 / 104.2, 40007 113.2 / 116.9, 49152 120.6 / 120.7,
-// 65536 135.7 / 134.9, 98304 170.8 / 167.6; 64 heads of 4000 91.8 / 90.1; exact mode, 8 heads of
-// 32768 127.1 / 137.2, 65536 161.2 / 167.4, 98304 196.9 / 200.6, 32 heads of 50001 322 / 313.
+// factorisation than the second workgroup saves: up to longer runs the fewer heads share the partials.
+// compactor_score on MI355X, % more (+) or less (-) time with 1 than with 2 workgroups a unit, by tiles a
+// unit (k_s = 16 and 64 lie within 3 % of 48; 1 to 4 heads gain more than 8: exact mode 21 to 5 at 62 tiles):
+//   exact mode, tiles    8     16     24    32    48    62     k_s = 48, tiles    8     14    20    23
+//      8 heads         -12.9  -9.2  -6.7  -5.4  -3.2  -1.0                      -6.4  -3.5  -0.2  -2.7
+//     16 heads          -8.0  -4.5  -2.3  -2.5  +0.3  +2.0                      -7.3  -3.0  -1.2  -1.7
+//     24 heads          -1.6  +0.7  -0.5  +0.8  +0.6  +3.5                      -0.3  -0.3  +1.7  +2.0
+//     32 heads          -2.4  -1.9  -0.6  -0.3  +1.5  +3.5                      -6.0  -0.9  +1.7  +2.1
 struct GramPlan { int nwg, tiles_per_wg; };
 GramPlan gram_plan(const compactor_params_t *p, const SegTable &T, int cus) {
   const long long total = total_tiles(T);
-  const bool few = T.nheads <= 32 && total < (p->sketch_dim > 0 ? 24ll : 64ll) * cus;
+  const bool exact = p->sketch_dim == 0;
+  const long long most = T.nheads <= 8    ? (exact ? 64 : 24)
+                         : T.nheads <= 16 ? (exact ? 48 : 24)
+                         : T.nheads <= 32 ? (exact ? 32 : 16)
+                                          : 0;
+  const bool few = total < most * cus;
   long long want = p->gram_wgs > 0 ? p->gram_wgs : (few ? 1ll : 2ll) * cus;
   if (want > total) want = total;
   if (want < 1) want = 1;

@@ -325,11 +325,14 @@ def test_factorisation_with_and_without_shares(C, ks, n, gram_wgs):
 
 
 # few heads: score runs of 256 to 1024 tokens up to 1024 tokens a compute unit, and one Gram workgroup a
-# unit up to 24 (exact mode: 64) tiles each; a step to either side of both limits, a short head, blended scores
+# unit below 24 (exact mode: 64) tiles each up to 8 heads, fewer up to 16 and up to 32; a step to either side
+# of the limits, a short head, blended scores
 @pytest.mark.parametrize("H,n,exact,blend", [(1, 130, False, False), (3, 257, False, True), (8, 8191, False, True),
                                              (2, 131071, False, False), (2, 131073, False, False),
                                              (8, 49089, False, False), (8, 49153, False, False),
-                                             (3, 43691, True, False)])
+                                             (3, 43691, True, False), (32, 8191, False, False),
+                                             (32, 8193, False, False), (16, 49089, True, False),
+                                             (16, 49153, True, False)])
 def test_launch_shapes_of_few_heads(C, H, n, exact, blend):
     w = W.config5(DEV, L=1, H=H, n=n, exact=True) if exact else W.config1(DEV, L=1, H=H, n=n)
     if blend:
