@@ -164,12 +164,18 @@ GroupBytes group_bytes_needed(const compactor_params_t *p, const SegTable &T, bo
   const GramPlan gp = gram_plan(p, T, cus);
   GroupBytes g;
   g.partials = align_up(((size_t)gp.nwg + T.nheads) * GRAM_PARTIAL_FLOATS * sizeof(float));
-  // Many workgroups per head form S = Phi^T G Phi only where the heads alone do not fill the chip.
-  // Factorisation stage with / without shares on MI355X, k_s = 48, n = 2048: 8 heads 25 / 40 us,
-  // 128 heads 34 / 42, 256 heads 41 / 42 (40 against 52 us with two and more partials a head),
-  // 512 heads 61 / 55, 4096 heads 376 / 393 (k_s = 64: 662 / 583); one head of n = 131072 brings
-  // 64 partials, 27 us against 210.
-  g.shares = T.nheads <= cus ? align_up(solve_plan(T, ks, gp.tiles_per_wg).share_bytes) : 0;
+  // Many workgroups per head form S = Phi^T G Phi (exact mode: G) only where the heads alone do not fill
+  // the chip.  Factorisation stage on MI355X, us with / without shares, n = 2048:
+  //   heads         8           64          128         256         512         1024       2048       4096
+  //   k_s = 16  12.7/18.9   14.6/19.6   16.4/20.2   18.0/18.4   21.7/20.0   33.2/32.2  60.0/56.2   110/105
+  //   k_s = 48  22.8/37.6   27.5/39.3   30.9/39.5   36.9/38.9   54.9/51.5   95.3/94.0   176/182    336/358
+  //   k_s = 64  30.4/52.0   36.6/54.0   43.8/54.0   54.4/52.6   85.8/76.4    157/142    309/277    596/534
+  //   exact     37.7/38.9   40.0/40.2   43.4/41.4   46.4/38.4   81.9/69.6    156/135    303/271    600/532
+  // and in exact mode 41.8/45.8 at 64 heads of 4096, 42.5/43.4 at 96, 42.9/41.2 at 128; k_s = 48, one head
+  // of n = 131072, which brings 64 partials: 27 against 210.  At 2048 heads and more k_s = 32 and 48 would
+  // be 4 to 9 % of this stage faster with shares, for 60 KB of scratch a head: the stage is 2 % of such calls.
+  const int most_heads = ks > 0 ? cus : 3 * cus / 8;
+  g.shares = T.nheads <= most_heads ? align_up(solve_plan(T, ks, gp.tiles_per_wg).share_bytes) : 0;
   g.wt = align_up((size_t)T.nheads * W_TERMS * m * D * sizeof(uint16_t));
   g.hist1 = align_up((size_t)T.nheads * HIST1_BINS * sizeof(int));
   g.sel = select_needs_pools(T) ? align_up((size_t)select_scratch(T).ints() * sizeof(int)) : 0;

@@ -324,6 +324,12 @@ def test_factorisation_with_and_without_shares(C, ks, n, gram_wgs):
     _say("  workspace %d of %d bytes; max rel err %.3g" % (hi, full, stats["max_rel"]))
 
 
+@pytest.mark.parametrize("L", [96, 97])      # G summed by workgroups of their own up to 96 heads
+def test_exact_mode_around_the_limit_of_the_shares(C, L):
+    w = W.config5(DEV, L=L, H=1, n=333, exact=True)
+    U.run_and_check(C, w, DEV, heads=[(0, 0, 0), (0, L // 2, 0), (0, L - 1, 0)])
+
+
 # few heads: score runs of 256 to 1024 tokens up to 1024 tokens a compute unit, and one Gram workgroup a
 # unit below 24 (exact mode: 64) tiles each up to 8 heads, fewer up to 16 and up to 32; a step to either side
 # of the limits, a short head, blended scores
