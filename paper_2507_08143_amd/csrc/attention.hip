@@ -85,7 +85,7 @@ struct AttnLds {
 // The products are 32x32x16 MFMAs: D[key][query] leaves lane l with 16 keys of query l & 31
 // (keys 8*(v>>2) + 4*(l>>5) + (v&3), v = 0..15), so a query's 64 keys of this wave are the 32
 // registers of two key tiles in lanes l and l ^ 32.
-template <bool RAGGED>
+template <bool RAGGED, bool LONG>
 __device__ __forceinline__ void attn_block(const AttnSeg &s, float scale, int head, int c0, int step0,
                                            int nsteps, AttnLds &L, float *__restrict__ raw) {
   const int n = s.n;
@@ -190,9 +190,13 @@ __device__ __forceinline__ void attn_block(const AttnSeg &s, float scale, int he
     // e = 2^(c*s - m) with c = scale * log2(e), so an element costs half a max3, one fma, one
     // exp and one add.  The product of the second query tile is issued ahead of the arithmetic
     // of the first.
-    // A wave in this stretch goes first, so that the other one of its SIMD is left to wait at its barrier
-    // or for its products (4 layers of 32768 tokens 412 us without and 409 with it).
-    __builtin_amdgcn_s_setprio(1);
+    // LONG: a wave in this stretch goes first, so that the other one of its SIMD is left to wait at its
+    // barrier or for its products.  Where a block is only the four steps of one query head, loading the
+    // keys and reducing the sums are half of it, and they then wait for the other wave.
+    // us without / with on MI355X, 1, 2, 4, 7 and 8 query heads a kv head: layers of 8 x 65536 tokens, two
+    // of them, 142 / 149, 231 / 228, 402 / 399, 665 / 651, 750 / 737; 8 layers of 8192 70 / 72, 122 / 121, 207 / 204,
+    // 337 / 326, 379 / 370; 16 of 32768 530 / 548, 904 / 885, 1590 / 1594; 32 of 32768, 4 query heads, 3171 / 3181.
+    if (LONG) __builtin_amdgcn_s_setprio(1);
     float m_mine = 0.f, l_mine = 0.f;    // statistics of query `lane` of the step (tile lh)
 #pragma unroll
     for (int qt = 0; qt < 2; ++qt) {
@@ -232,7 +236,7 @@ __device__ __forceinline__ void attn_block(const AttnSeg &s, float scale, int he
         l_mine = l;
       }
     }
-    __builtin_amdgcn_s_setprio(0);
+    if (LONG) __builtin_amdgcn_s_setprio(0);
     L.st_m[sb][wave][lane] = m_mine;
     L.st_l[sb][wave][lane] = l_mine;
 
@@ -296,8 +300,8 @@ __device__ __forceinline__ void attn_block(const AttnSeg &s, float scale, int he
 }
 
 // SHARED: a block's queries are dealt out to T.parts workgroups (its own instance: the counters that
-// the general start needs cost the full-size call 0.8 %).
-template <bool SHARED>
+// the general start needs cost the full-size call 0.8 %).  LONG: more than one query head a kv head.
+template <bool SHARED, bool LONG>
 __global__ __launch_bounds__(256, 2) void attn_colsum_kernel(const AttnTable T,
                                                              float *__restrict__ raw) {
   __shared__ __attribute__((aligned(16))) AttnLds L;
@@ -331,9 +335,9 @@ __global__ __launch_bounds__(256, 2) void attn_colsum_kernel(const AttnTable T,
     raw += part * T.part_floats;
   }
   if (c0 + ATT_C > s.n)
-    attn_block<true>(s, T.scale, head, c0, step0, nsteps, L, raw);
+    attn_block<true, LONG>(s, T.scale, head, c0, step0, nsteps, L, raw);
   else
-    attn_block<false>(s, T.scale, head, c0, step0, nsteps, L, raw);
+    attn_block<false, LONG>(s, T.scale, head, c0, step0, nsteps, L, raw);
 }
 
 // Mean pooling along the sequence: window `pool` (odd), zero padding, divided by `pool`.
@@ -480,10 +484,10 @@ int compactor_attention_scores(const compactor_attn_params_t *p,
     }
     nb_col *= parts;
     if (nb_col > 0x7fffffffll) return COMPACTOR_EINVAL;
-    if (parts > 1)
-      hipLaunchKernelGGL(attn_colsum_kernel<true>, dim3((unsigned)nb_col), dim3(256), 0, st, T, raw);
-    else
-      hipLaunchKernelGGL(attn_colsum_kernel<false>, dim3((unsigned)nb_col), dim3(256), 0, st, T, raw);
+    const bool several = p->q_heads > p->kv_heads;
+    const auto kernel = parts > 1 ? (several ? attn_colsum_kernel<true, true> : attn_colsum_kernel<true, false>)
+                                  : (several ? attn_colsum_kernel<false, true> : attn_colsum_kernel<false, false>);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)nb_col), dim3(256), 0, st, T, raw);
     if (hipGetLastError() != hipSuccess) return COMPACTOR_EHIP;
     hipLaunchKernelGGL(attn_pool_kernel, dim3((unsigned)nb_pool), dim3(256), 0, st, T, raw, attn);
     if (hipGetLastError() != hipSuccess) return COMPACTOR_EHIP;

@@ -791,6 +791,12 @@ def test_attention_scores_group_sizes_strided_views_and_batches(C, G, n):
 
 # few blocks: their queries are shared by 2 to 4 workgroups where the workspace has room for the sums of
 # each; 4 * G steps are dealt out evenly or not, a part may get a single step, blocks may be ragged
+@pytest.mark.parametrize("L,H,G,n", [(2, 8, 1, 2301), (1, 2, 1, 255), (2, 8, 2, 2301)])
+def test_attention_scores_of_one_and_two_query_heads(C, L, H, G, n):
+    """One query head a kv head has instances of its own, with blocks of few queries shared and not."""
+    _attention_case(C, L, H, G, n, W.config1, seed=n)
+
+
 @pytest.mark.parametrize("L,H,G,n", [(1, 1, 1, 1), (1, 2, 1, 700), (1, 3, 3, 2100), (1, 8, 4, 4095),
                                      (2, 8, 7, 1792)])
 def test_attention_scores_in_parts(C, L, H, G, n):
