@@ -459,6 +459,48 @@ def test_blend_with_selection_by_several_workgroups(C):
             assert np.all(np.abs(sb[g * r.n:(g + 1) * r.n] - want) <= U.blend_bound(o, W.LAMBDA_BLEND))
 
 
+@pytest.mark.parametrize("scope,H,n,ratio", [(1, 2, 9000, 0.7), (1, 2, 9000, 0.3), (0, 2, 40003, 0.3)])
+def test_fused_selection_with_a_threshold_among_nans(C, scope, H, n, ratio):
+    """The fused call's histogram (the top 12 key bits) with a head of NaN scores: the threshold lies among
+    them for that head, and for the layer where its budget exceeds the other head's tokens."""
+    w = W.config1(device=DEV, L=1, H=H, n=n, ratio=ratio)
+    w.requests[0].k[0, 0, 17, 5] = float("nan")
+    params, reqs = U.make_call(C, w, DEV)
+    params.select_scope = scope
+    out = C.compactor_compress(params, reqs, want_scores=True)
+    torch.cuda.synchronize()
+    s, kept, cnt = (out[k].cpu().numpy() for k in ("scores", "kept_idx", "kept_cnt"))
+    assert np.isnan(s[:n]).all() and not np.isnan(s[n:]).any()
+    k = C.compactor_layout(params, reqs)[2][0]
+    if scope:
+        _check_layer_selection(C, s, kept, cnt, 0, k, 0, 1, H, n, "NaN threshold")
+    else:
+        for h in range(H):
+            assert np.array_equal(kept[h * k:(h + 1) * k], O.select_topk(s[h * n:(h + 1) * n], k))
+
+
+@pytest.mark.parametrize("scope,H,n", [(1, 2, 9000), (0, 1, 40003)])
+def test_fused_selection_with_a_threshold_just_below_zero(C, scope, H, n):
+    """Attention scores of one +1, one -1 and one tiny value per head: the z-score of all the others is a
+    denormal just below zero, whose bin of the top 12 key bits ends at the key that no score has."""
+    w = W.config1(device=DEV, L=1, H=H, n=n, ratio=0.4)
+    a = torch.zeros(1, H, n, device=DEV)
+    a[..., 10], a[..., 11], a[..., n - 1] = 1.0, -1.0, 2e-38
+    w.requests[0].attn = a
+    params, reqs = U.make_call(C, w, DEV)
+    params.select_scope, params.lambda_blend = scope, 0.0
+    out = C.compactor_compress(params, reqs, want_scores=True)
+    torch.cuda.synchronize()
+    s, kept, cnt = (out[k].cpu().numpy() for k in ("scores", "kept_idx", "kept_cnt"))
+    rest = np.delete(s.reshape(H, n), [10, 11, n - 1], axis=1)
+    assert (rest < 0).all() and (rest > -1.4e-39).all()          # bits 0x80000001 .. 0x800fffff
+    k = C.compactor_layout(params, reqs)[2][0]
+    if scope:
+        _check_layer_selection(C, s, kept, cnt, 0, k, 0, 1, H, n, "threshold below zero")
+    else:
+        assert np.array_equal(kept[:k], O.select_topk(s, k))
+
+
 def _same_up_to_rounding(C, w, params, reqs, ref, other, what):
     """A different launch partition changes the fp32 summation order of the Gram matrix, so
     scores may move in their last bits: they must agree to 1e-5 relative, and the selections
