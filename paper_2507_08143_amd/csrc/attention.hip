@@ -18,6 +18,8 @@
 #include <math.h>
 #include <string.h>
 
+#include <type_traits>
+
 #include "common.h"
 
 namespace cmp {
@@ -342,12 +344,17 @@ __global__ __launch_bounds__(256, 2) void attn_colsum_kernel(const AttnTable T,
 
 // Mean pooling along the sequence: window `pool` (odd), zero padding, divided by `pool`.
 // A workgroup stages its 1024 positions and the halo once in LDS, adding the parts' sums.  In fp64, so that
-// adding parts costs no precision (the kernel waits for memory either way).
+// adding parts costs no precision.  PARTS: the sums are of several parts, and wait as doubles; those of one
+// part are floats as they are, and a wide window is bound by its LDS reads: 32 layers of 8 x 32768 tokens
+// with one query head, pool = 1 / 7 / 31 / 63, 1073 / 1077 / 1091 / 1114 us with doubles, 1071 / 1074 /
+// 1086 / 1100 with floats (all in fp32, less exact: 1068 / 1073 / 1079 / 1086).
+template <bool PARTS>
 __global__ __launch_bounds__(256) void attn_pool_kernel(const AttnTable T,
                                                         const float *__restrict__ raw,
                                                         float *__restrict__ attn) {
   constexpr int SPAN = 1024, HALO = 32;           // pool <= 63: at most 31 positions each side
-  __shared__ double tile[SPAN + 2 * HALO];
+  typedef typename std::conditional<PARTS, double, float>::type sum_t;
+  __shared__ sum_t tile[SPAN + 2 * HALO];
   int seg = 0, head = 0, blk = 0;
   {
     int base = 0;
@@ -371,10 +378,11 @@ __global__ __launch_bounds__(256) void attn_pool_kernel(const AttnTable T,
   const int t0 = blk * SPAN;
   for (int i = threadIdx.x; i < SPAN + 2 * HALO; i += 256) {
     const int j = t0 - HALO + i;
-    double x = 0.0;                               // zero padding at both ends of the sequence
+    sum_t x = 0;                                  // zero padding at both ends of the sequence
     if (j >= 0 && j < n) {
-      x = (double)src[j];
-      for (int p = 1; p < T.parts; ++p) x += (double)src[p * T.part_floats + j];
+      x = src[j];
+      if (PARTS)
+        for (int p = 1; p < T.parts; ++p) x += (sum_t)src[p * T.part_floats + j];
     }
     tile[i] = x;
   }
@@ -382,7 +390,7 @@ __global__ __launch_bounds__(256) void attn_pool_kernel(const AttnTable T,
   const double inv = 1.0 / (double)T.pool;
   for (int i = threadIdx.x; i < SPAN && t0 + i < n; i += 256) {
     double acc = 0.0;
-    for (int u = -h; u <= h; ++u) acc += tile[HALO + i + u];
+    for (int u = -h; u <= h; ++u) acc += (double)tile[HALO + i + u];
     dst[t0 + i] = (float)(acc * inv);
   }
 }
@@ -393,7 +401,8 @@ __global__ __launch_bounds__(256) void attn_pool_kernel(const AttnTable T,
 // down, so a block is shared only up to one workgroup per unit.  Whole call of 4 query heads a kv head on
 // MI355X, us with 1 / 2 / 3 / 4 / 5 parts: 4 blocks 32.4 / 23.5 / 22.1 / 20.4 / 21.2, 64 blocks
 // 33.4 / 24.0 / 23.2 / 21.8 / 27.7, 128 blocks 36.5 / 27.6 / 31.8 / 32.4 / 35.4, 200 blocks
-// 34.5 / 34.6 / 40.0 / 41.5, 512 blocks 56.4 / 61.6 / 66.8 / 70.1 (the host alone needs 18).
+// 34.5 / 34.6 / 40.0 / 41.5, 512 blocks 56.4 / 61.6 / 66.8 / 70.1 (of which the host
+// alone needed 18 then; 12 now).
 constexpr int ATT_MAX_PARTS = 4;
 static int query_parts(const compactor_attn_params_t *p, const compactor_attn_request_t *reqs, int32_t nreq) {
   long long blocks = 0;
@@ -489,7 +498,7 @@ int compactor_attention_scores(const compactor_attn_params_t *p,
                                   : (several ? attn_colsum_kernel<false, true> : attn_colsum_kernel<false, false>);
     hipLaunchKernelGGL(kernel, dim3((unsigned)nb_col), dim3(256), 0, st, T, raw);
     if (hipGetLastError() != hipSuccess) return COMPACTOR_EHIP;
-    hipLaunchKernelGGL(attn_pool_kernel, dim3((unsigned)nb_pool), dim3(256), 0, st, T, raw, attn);
+    hipLaunchKernelGGL(parts > 1 ? attn_pool_kernel<true> : attn_pool_kernel<false>, dim3((unsigned)nb_pool), dim3(256), 0, st, T, raw, attn);
     if (hipGetLastError() != hipSuccess) return COMPACTOR_EHIP;
   }
   return COMPACTOR_OK;
