@@ -190,7 +190,8 @@ __global__ __launch_bounds__(256, 2) void score_kernel(
     for (int p = 0; p < NS; ++p)
 #pragma unroll
       for (int st = 0; st < NSUB; ++st) sums[p][st] = 0.f;
-#pragma unroll (M <= 48 ? M / 16 : 1)
+    constexpr int JB_UNROLL = M <= 48 ? M / 16 : 1;
+#pragma unroll JB_UNROLL
     for (int jb = 0; jb < M / 16; ++jb) {   // rolled for many rows: unrolling hoists their operands
       f32x4 acc[NS][NSUB];
 #pragma unroll

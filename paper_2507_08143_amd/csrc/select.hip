@@ -297,7 +297,7 @@ constexpr int SEL_STATE = 8;             // ints of state per pool:
 // A chunk's pair of ints in the records and in the offsets.  They stand behind a candidate list of one int
 // per token, so a launch with an odd number of tokens leaves them on 4-byte boundaries only.
 typedef int i32x2_any __attribute__((ext_vector_type(2), aligned(4)));
-enum { ST_BIN = 0, ST_NEED1, ST_THR, ST_TIES };
+enum { ST_BIN = 0, ST_NEED1, ST_THR };
 static_assert(SEL_ROUNDS >= 1 && SEL_ROUNDS <= 8, "one validity bit per token in 32 bits");
 
 struct SelWhere {
@@ -672,10 +672,7 @@ __global__ __launch_bounds__(THR_THREADS) void msel_thr_kernel(const SegTable T,
   const uint32_t d3 = (uint32_t)find_digit<THR_THREADS>(hist, 1 << rest, &need, wsum, found);
   const int tie_keep = need;             // keys equal to the threshold that are retained
   const uint32_t thr = key1 | (d2 << rest) | d3, thr23 = thr & 0x7fffffu;
-  if (tid == 0) {
-    state[pool * SEL_STATE + ST_THR] = (int)thr;
-    state[pool * SEL_STATE + ST_TIES] = tie_keep;
-  }
+  if (tid == 0) state[pool * SEL_STATE + ST_THR] = (int)thr;
   const bool from_short = single && nshort <= THR_SHORT;
   if (from_short) {                      // the chunks' counts at the last digit, from the short list
     for (int i = tid; i < nshort; i += THR_THREADS) {

@@ -16,7 +16,7 @@ namespace cmp {
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ Where locate_head(const SegTable &T, int lhead) {
-  Where w{0, 0, lhead, 0};
+  Where w{0, 0, lhead, 0, 0};
   for (int i = 0; i < T.nseg; ++i) {
     const int hh = lhead - T.s[i].lhead0;
     if (hh < T.s[i].head_count || i == T.nseg - 1) {
@@ -417,8 +417,8 @@ __device__ __forceinline__ void fetch_phi(const float *__restrict__ phi, float4 
   for (int i = 0; i < N; ++i) r[i] = reinterpret_cast<const float4 *>(phi)[threadIdx.x + 256 * i];
 }
 
-// One workgroup (4 waves) per head, steps 2 to 4; step 1 from the shares, or from
-// the partials.
+// One workgroup (4 waves) per head, steps 2 to 4; step 1 from the shares (partials and zero are not used
+// then: the share kernel has cleared it), or from the partials.
 template <int M, bool SHARES>
 __global__ __launch_bounds__(256, 2) void sketch_solve_kernel(
     const SegTable T, int tiles_per_wg, int parts, const float *__restrict__ partials,
@@ -436,7 +436,7 @@ __global__ __launch_bounds__(256, 2) void sketch_solve_kernel(
   __shared__ int flag_s;
 
   const int lhead = blockIdx.x;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l16 = lane & 15, lq = lane >> 4;
+  const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lq = lane >> 4;
   if (tid == 0) flag_s = 0;
 
   constexpr int PHN = D * M / 4 / 256;
@@ -715,7 +715,7 @@ static hipError_t launch_sketched(const SegTable &T, int tiles_per_wg, const Sol
                        dim3(256), 0, st, T, tiles_per_wg, plan.parts, partials, phi, shares, zero, zero_ints);
     if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
     hipLaunchKernelGGL((sketch_solve_kernel<M, true>), dim3((unsigned)T.nheads), dim3(256), 0, st, T,
-                       tiles_per_wg, plan.parts, partials, shares, phi, ridge_rel, wt, status, zero, zero_ints);
+                       tiles_per_wg, plan.parts, nullptr, shares, phi, ridge_rel, wt, status, nullptr, 0);
   } else {
     hipLaunchKernelGGL((sketch_solve_kernel<M, false>), dim3((unsigned)T.nheads), dim3(256), 0, st, T,
                        tiles_per_wg, plan.parts, partials, shares, phi, ridge_rel, wt, status, zero, zero_ints);
@@ -776,7 +776,7 @@ hipError_t launch_exact_solve(const SegTable &T, int tiles_per_wg, const float *
                        partials, shares, zero, zero_ints);
     if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
     hipLaunchKernelGGL((exact_solve_kernel<true>), dim3((unsigned)T.nheads), dim3(EXACT_THREADS), 0, st, T,
-                       tiles_per_wg, partials, shares, ridge_rel, wt, status, zero, zero_ints);
+                       tiles_per_wg, nullptr, shares, ridge_rel, wt, status, nullptr, 0);
   } else {
     hipLaunchKernelGGL((exact_solve_kernel<false>), dim3((unsigned)T.nheads), dim3(EXACT_THREADS), 0, st, T,
                        tiles_per_wg, partials, shares, ridge_rel, wt, status, zero, zero_ints);
