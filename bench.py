@@ -416,7 +416,7 @@ OTHER_CONFIGS = [(3, False), (1, False), (2, False), (5, False), (5, True)]
 def main():
     a = parse()
     if a.gpus != 1:
-        print("bench.py measures one GPU: this build has no multi-GPU path (heads are independent, "
+        print("bench.py measures one GPU: this library has no multi-GPU path (heads are independent, "
               "so more GPUs would each take a share of the heads with no communication). "
               "Run with --gpus 1.", file=sys.stderr)
         sys.exit(2)

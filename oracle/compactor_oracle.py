@@ -1,6 +1,6 @@
 """Float64 CPU oracle for the Compactor hot path (score -> select -> compact).
 
-TEST INFRASTRUCTURE ONLY.  This module is the independent checker for the HIP
+TEST INFRASTRUCTURE ONLY.  This module is the independent reference for the HIP
 library: it may be imported by tests/, by __graft_entry__.smoke() and by the
 cpu_baseline leg of bench.py, and by nothing on the product path.  It shares no
 code with the HIP kernels or their Python binding and imports neither.
@@ -263,7 +263,7 @@ def attention_scores(Q_heads, K: np.ndarray, chunk: int = 256, pool: int = 7,
 
     The paper leaves the reduction over a group's query heads and the pooling width open;
     mean over the group and an odd width (default 7), zero padding at both ends of the
-    sequence and division by the full width are this build's readings.
+    sequence and division by the full width are this project's readings.
     """
     raw = np.mean([attention_scores_raw(Q, K, chunk, scale) for Q in Q_heads], axis=0)
     return mean_pool(raw, pool)

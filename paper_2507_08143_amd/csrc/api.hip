@@ -118,12 +118,16 @@ int score_tokens_for(const compactor_params_t *p, const SegTable &T, int cus) {
   // workgroup and gains 4 % from runs of 16384 tokens.
   const int cap = p->sketch_dim == 0 ? 16384 : SCORE_BURST;
   const int slots = 2 * cus;
-  // A call of few heads that gives a compute unit less than 1024 tokens is all latency: one workgroup per unit, but not
-  // below 256 tokens, where staging W^T and adding the histograms outweigh the steps saved.  Whole
-  // call on MI355X, us with runs of 128 / 256 / 512 / 768 / 1024 tokens: 8 heads of 4096 tokens 53.8 / 54.6 /
-  // 56.6 / 59.2 / 60.9, 8192 63.1 / 62.7 / 62.9 / 64.8 / 67.8, 16384 86.6 / 78.4 / 76.3 / 78.8 / 79.6, 24000
+  // A call of few heads that gives a compute unit less than 1024 tokens is all latency: one workgroup per
+  // unit, but not below 256 tokens, where half the run changes nothing any more: staging W^T and adding the
+  // histograms weigh as much as the steps saved (128 against 256 tokens: 1.5 % less at 8 heads of 4096, the
+  // same at one of 2048).  Whole call on MI355X, us with runs of 128 / 256 / 512 / 768 / 1024 tokens: 8
+  // heads of 4096 tokens 53.8 / 54.6 / 56.6 / 59.2 / 60.9, 8192 63.1 / 62.7 / 62.9 / 64.8 / 67.8, 16384 86.6 / 78.4 / 76.3 / 78.8 / 79.6, 24000
   // 113.8 / 101.5 / 93.6 / 92.8 / 94.2, 32768 141 / 118 / 107.4 / 108.2 / 106.8, one head of 2048 51.2 / 51.3 /
-  // 51.8 / 54.2 / 55.7; exact mode, 8 heads of 8192 80.0 / 79.8 / 82.1 / 86.5 / 90.3.
+  // 51.8 / 54.2 / 55.7; exact mode, 8 heads of 8192 80.0 / 79.8 / 82.1 / 86.5 / 90.3.  Beyond 1024 tokens a unit
+  // the search below takes over; compactor_score with what it chooses and with runs of 512 / 640 / 768: 8 heads of
+  // 33000 69.0, 68.7 / 64.3 / 66.2, 40007 70.6, 74.5 / 67.6 / 68.3, 50000 78.0, 83.0 / 83.4 / 83.2, 65000 87.9,
+  // 90.0 / 89.7 / 89.4 (up to 1300 tokens a unit two full rounds of about 640 would be 4 to 7 % faster).
   long long rows = 0;
   for (int i = 0; i < T.nseg; ++i) rows += (long long)T.s[i].n * T.s[i].head_count;
   if (T.nheads <= cus && rows < 1024ll * cus) {

@@ -906,8 +906,10 @@ struct OstatIndex {
 // A workgroup takes a chunk in parts of PART rounds: the fp64 arithmetic of a whole chunk at once would take
 // so many registers that only three workgroups fit a CU.  HALF: one part each, where whole chunks are too
 // few to fill the chip; its scores are requested before the head's sums are added up, which hides a load
-// latency.  32 heads of 16383 tokens (64 chunks): 15.2 us whole, 10.2 halved; 256 heads of 32768 (1024
-// chunks): 26.7 and 31.3.
+// latency.  Stage on MI355X, us whole / halved, heads of 16383 tokens: 64 chunks 15.7 / 10.8, 256
+// 17.0 / 12.2, 512 20.1 / 16.3, 640 22.2 / 18.5, 768 23.3 / 23.1, 1024 27.3 / 27.6; heads of 8292, where the
+// second half of every chunk is nearly empty: 64 12.7 / 10.8, 256 13.2 / 11.9, 512 15.0 / 14.9, 640 16.5 / 16.6,
+// 768 17.6 / 21.1.  Hence halves up to 512 chunks.
 template <bool HALF>
 __global__ __launch_bounds__(CHUNK_THREADS) void blend_apply_kernel(
     const SegTable T, const OstatIndex X, float lambda, float *__restrict__ scores,

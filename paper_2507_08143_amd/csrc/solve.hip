@@ -389,7 +389,7 @@ __device__ __forceinline__ void split_part(int nsplit, int parts, int r, int &fi
 // One workgroup per (head, part, share).  Bound by latency: one batch of partials after the
 // other, 60 MFMAs (k_s = 48) a wave, two barriers: 7 to 10 us for 8 heads with 8 to 64 partials
 // each, where one workgroup per head took 34 (8 partials, 4-byte loads) to 185 us (64) for this
-// step.  From 256 heads on (20 us) the fp64 matrix cores count: 1200 MFMAs of 64 clocks a head.
+// step.  From 256 heads on (24 us) the fp64 matrix cores count: 1200 MFMAs of 64 clocks a head.
 template <int M>
 __global__ __launch_bounds__(256, 2) void sketch_share_kernel(
     const SegTable T, int tiles_per_wg, int parts, const float *__restrict__ partials,
