@@ -137,16 +137,14 @@ __device__ __forceinline__ uint32_t score_key(float s) {
 }
 
 // First digit of the selection, two ways.  Scores that leave the scoring kernels are tallied there by
-// their top 12 key bits (8 bins an octave).  Scores of a separate selection call are tallied by
+// their top 12 key bits (8 bins an octave).  Scores of a separate selection call (all of a head in select_kernel,
+// a sample of a pool in msel_sample_kernel) are tallied by
 // score_bin, a monotone map of the keys that is finer where thresholds lie: magnitudes from 2^-18 up to
 // 2^4, where leverage scores and z-scores have them, have 64 bins an octave, 24 octaves on either side 8,
 // and those beyond (below 2^-42, from 2^28 on) one each; negative numbers
 // mirror the positive ones, and NaN shares the lowest bin with -inf (whose keys are larger).  Eight bins
 // an octave put a fifth to a quarter of a head's scores into the threshold's bin, and so many lanes of a
-// wave onto one LDS counter that a tally is bound by it (112 heads of 131072 tokens: tally 22 us against
-// 18, threshold 25 against 16).  One bin an octave, which an earlier map had for everything outside the
-// fine range, puts half of evenly spread scores into it: 112 heads of 131072 scores up to 1000 took 125 us and
-// take 76 now, 600 of 40003 182 and 101, with the top 12 key bits 103 and 122.  A scoring workgroup has
+// wave onto one LDS counter that a tally is bound by it.  A scoring workgroup has
 // more to do than tally, and it adds its histogram to the pool's: 64 bins an octave are eight times the
 // adds, and the fused calls take 0.2 to 0.5 % longer with them.
 constexpr int HIST1_BINS = 4096;      // either way
@@ -199,6 +197,15 @@ __host__ __device__ __forceinline__ BinKeys bin_keys(int bin, bool fine) {
   }
   const uint32_t u = (uint32_t)x << 17;
   return BinKeys{pos ? 0x80000000u | u : (0x7fffffffu - u) & ~((1u << bits) - 1u), bits};
+}
+
+// Sample of a pool of more than SAMPLE_WHOLE scores (see msel_sample_kernel): the g-th of SAMPLE_LINES lines
+// out of `lines`, at a hashed place in the g-th of as many equal stretches.
+constexpr int SAMPLE_WHOLE = 8192, SAMPLE_LINES = SAMPLE_WHOLE / 16;
+__host__ __device__ __forceinline__ int sample_line(int g, int lines) {
+  const uint32_t hash = ((uint32_t)g * 2654435761u ^ 0x9e3779b9u) * 2246822519u >> 16;
+  const uint64_t place = (uint64_t)g << 16 | hash;       // of SAMPLE_LINES << 16
+  return (int)(place * (uint64_t)lines / ((uint64_t)SAMPLE_LINES << 16));
 }
 
 // Streaming (non-temporal) 16-byte accesses for data that is touched once per pass: they do
@@ -389,8 +396,7 @@ hipError_t launch_select(const SegTable &T, const float *scores, const int *hist
                          int32_t *kept_idx, int32_t *kept_cnt, hipStream_t st);
 
 // Selection by several workgroups per pool (long heads, or layer scope).  hist1: pools x 4096
-// ints; hist1_ready: it holds the histogram of the scores' top 12 key bits already (otherwise it
-// is cleared and tallied here, by score_bin).  sel: scratch of select_scratch(T).ints() ints (candidate lists,
+// ints, the histogram of the scores' top 12 key bits, or null.  sel: scratch of select_scratch(T).ints() ints (candidate lists,
 // one slot per token of the launch; per-chunk records and offsets; per-pool state), none of which
 // needs clearing.
 struct SelectScratch {
@@ -400,8 +406,8 @@ struct SelectScratch {
 };
 SelectScratch select_scratch(const SegTable &T);
 bool select_needs_pools(const SegTable &T);
-hipError_t launch_select_pools(const SegTable &T, const float *scores, int *hist1, bool hist1_ready,
-                               int *sel, int32_t *kept_idx, int32_t *kept_cnt, hipStream_t st);
+hipError_t launch_select_pools(const SegTable &T, const float *scores, const int *hist1, int *sel,
+                               int32_t *kept_idx, int32_t *kept_cnt, hipStream_t st);
 
 // kept_cnt is read in layer scope only (ragged heads inside a layer's region).
 hipError_t launch_gather(const SegTable &T, const int32_t *kept_idx, const int32_t *kept_cnt,

@@ -275,10 +275,12 @@ __global__ __launch_bounds__(SELECT_THREADS) void select_kernel(const SegTable T
 // the top scores "across all heads"; scoring stays per head).  The same radix select and ordered
 // emit as above, with the scores read once or twice in all.  A pool (head or layer) is cut into chunks of
 // up to 8192 tokens of one head, one workgroup each; three launches:
-//   cand   the threshold's bin comes from the pool's histogram (made by the score kernel, the blend,
-//          or msel_hist1_kernel).  Keys above the bin are retained for sure and only marked and
+//   cand   a range of keys that holds the threshold: a bin of the pool's histogram (made by the score
+//          kernel or the blend), or, for scores that come without one, a bracket from a sample
+//          (msel_sample_kernel).  Keys above the range are retained for sure and only marked and
 //          counted; the keys inside it (the candidates: 2 to 25 % of the pool unless the
-//          scores are heavily tied) are marked and leave their low 23 bits in a per-chunk list
+//          scores are heavily tied) are marked and leave their distance from its lower end in a
+//          per-chunk list
 //   thr    one workgroup per pool finds the remaining bits of the threshold among the
 //          candidates and derives, chunk by chunk in (head, token) order, every chunk's output
 //          position and its allowance of threshold ties
@@ -297,7 +299,8 @@ constexpr int SEL_STATE = 8;             // ints of state per pool:
 // A chunk's pair of ints in the records and in the offsets.  They stand behind a candidate list of one int
 // per token, so a launch with an odd number of tokens leaves them on 4-byte boundaries only.
 typedef int i32x2_any __attribute__((ext_vector_type(2), aligned(4)));
-enum { ST_BIN = 0, ST_NEED1, ST_THR };
+// the keys [ST_LO, ST_HI] hold the threshold, which becomes ST_THR; ST_FULL: they did not
+enum { ST_LO = 0, ST_HI, ST_THR, ST_FULL };
 static_assert(SEL_ROUNDS >= 1 && SEL_ROUNDS <= 8, "one validity bit per token in 32 bits");
 
 struct SelWhere {
@@ -339,36 +342,47 @@ __device__ __forceinline__ long long chunk_token_base(const SegTable &T, const S
 // tok_begin + 4 * (r * CHUNK_THREADS + tid) + e); bit 4r+e of the result says that the token
 // exists.  The loads are only issued here: whoever calls this first and converts to keys later
 // has the latency of everything in between for free.
+// One 16-byte load per 4 tokens also where a head's scores start off a 16-byte boundary (odd n): global memory
+// takes vector loads at any 4-byte address.  No branch around a single load: each would wait for the one
+// before it (112 heads of 131072 tokens, candidates 17 us with and 13 without; blend of 4 layers of 8 x 16383
+// 10.3 and 7.4).  Four tokens that reach past a chunk's end are read from its last four on
+// and moved into place by place_scores_part, after which the loads are waited for.
 template <int R>
-__device__ __forceinline__ unsigned load_scores_part(const float *__restrict__ sp, const SelWhere &q,
-                                                     int r0, float (&f)[R][4]) {
-  // one 16-byte load per 4 tokens also where a head's scores start off a 16-byte boundary (odd
-  // n): global memory takes vector loads at any 4-byte address
+__device__ __forceinline__ void load_scores_part(const float *__restrict__ sp, const SelWhere &q, int r0,
+                                                 float (&f)[R][4]) {
   typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
-  unsigned valid = 0;
+  const int i0 = q.tok_begin + 4 * (r0 * CHUNK_THREADS + (int)threadIdx.x);
+  const int last4 = q.tok_end - 4;
+  if (last4 >= 0) {                      // uniform
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int i0 = q.tok_begin + 4 * ((r0 + r) * CHUNK_THREADS + (int)threadIdx.x);
-    if (i0 + 3 < q.tok_end) {
-      const f32x4_any v = *reinterpret_cast<const f32x4_any *>(sp + i0);
+    for (int r = 0; r < R; ++r) {
+      const f32x4_any v = *reinterpret_cast<const f32x4_any *>(sp + min(i0 + 4 * r * CHUNK_THREADS, last4));
       f[r][0] = v.x; f[r][1] = v.y; f[r][2] = v.z; f[r][3] = v.w;
-      valid |= 0xfu << (4 * r);
-    } else {
+    }
+  } else {                               // a head of up to three tokens
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        f[r][e] = 0.f;
-        if (i0 + e < q.tok_end) {
-          f[r][e] = sp[i0 + e];
-          valid |= 1u << (4 * r + e);
-        }
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) f[r][e] = r == 0 && i0 + e < q.tok_end ? sp[e] : 0.f;
+  }
+}
+// Returns the bits of the tokens that exist; what f holds of others is any number.
+template <int R>
+__device__ __forceinline__ unsigned place_scores_part(const SelWhere &q, int r0, float (&f)[R][4]) {
+  unsigned valid = 0xffffffffu >> (32 - 4 * R);
+  if (q.tok_begin + 4 * (r0 + R) * CHUNK_THREADS > q.tok_end) {          // uniform: some do not exist
+    valid = 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int have = q.tok_end - (q.tok_begin + 4 * ((r0 + r) * CHUNK_THREADS + (int)threadIdx.x));
+      valid |= ((1u << min(max(have, 0), 4)) - 1u) << (4 * r);
+      if (have > 0 && have < 4 && q.tok_end >= 4) {
+        if (have < 3) { f[r][0] = f[r][2]; f[r][1] = f[r][3]; }
+        if (have != 2) { f[r][0] = f[r][1]; f[r][1] = f[r][2]; f[r][2] = f[r][3]; }
       }
     }
   }
   return valid;
-}
-__device__ __forceinline__ unsigned load_chunk_scores(const float *__restrict__ sp, const SelWhere &q,
-                                                      float (&f)[SEL_ROUNDS][4]) {
-  return load_scores_part<SEL_ROUNDS>(sp, q, 0, f);
 }
 
 // The float of a key (score_key's inverse; -0.0 has no key of its own).
@@ -376,48 +390,47 @@ __device__ __forceinline__ float key_score(uint32_t key) {
   return __uint_as_float((key & 0x80000000u) ? key ^ 0x80000000u : ~key);
 }
 
-// Classification of scores against a key interval [lo, hi] (the threshold's bin): float comparisons where
-// they give the order of the keys, which is everywhere but at NaN (key 0, below every number) and just
-// below zero (-0.0 is compared as +0.0 but a float equal to it).
-struct KeyRange {
-  uint32_t lo, hi;
-  float flo, fhi;
-  bool plain;
-  __device__ __forceinline__ KeyRange(uint32_t l, uint32_t h) : lo(l), hi(h), flo(key_score(l)), fhi(key_score(h)) {
-    plain = l >= 0x007fffffu && h <= 0xff800000u && h != 0x7fffffffu;      // -inf .. +inf
-  }
-};
-
-// bits of the tokens of f (see load_scores_part) above the range and inside it
-__device__ __forceinline__ void classify(const float (&f)[SEL_ROUNDS][4], unsigned valid, const KeyRange &k,
-                                         unsigned &above, unsigned &in) {
+// Classification of scores against a key interval [lo, hi]: bits of the tokens of f (see load_scores_part)
+// above it and inside it; f becomes the keys' distances from lo (of those inside).  Keys of one sign are the
+// float's bits with the sign set, or their complement; what lies outside wraps round to a distance beyond the
+// interval.  Float comparison gives the order of the keys everywhere but at NaN (key 0, below every number)
+// and just below zero (-0.0 is +0.0 but compares equal to it), and those have the general path.
+template <class ABOVE, class DIST>
+__device__ __forceinline__ void classify_by(float (&f)[SEL_ROUNDS][4], uint32_t span, unsigned &above, unsigned &in,
+                                            ABOVE &&is_above, DIST &&distance) {
   above = in = 0;
-  if (k.plain) {
 #pragma unroll
-    for (int r = 0; r < SEL_ROUNDS; ++r)
+  for (int r = SEL_ROUNDS - 1; r >= 0; --r)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        above |= f[r][e] > k.fhi ? 1u << (4 * r + e) : 0u;
-        in |= f[r][e] >= k.flo ? 1u << (4 * r + e) : 0u;
-      }
+    for (int e = 3; e >= 0; --e) {
+      above = above + above + (is_above(f[r][e]) ? 1u : 0u);
+      const uint32_t v = distance(f[r][e]);
+      in = in + in + (v <= span ? 1u : 0u);
+      f[r][e] = __uint_as_float(v);
+    }
+}
+__device__ __forceinline__ void classify(float (&f)[SEL_ROUNDS][4], unsigned valid, uint32_t lo, uint32_t hi,
+                                         unsigned &above, unsigned &in) {
+  const bool positive = lo > 0x80000000u && hi <= 0xff800000u, negative = lo >= 0x007fffffu && hi < 0x7fffffffu;
+  if (positive || negative) {
+    const float fhi = key_score(hi);
+    const uint32_t flip = positive ? 0x80000000u : 0xffffffffu;
+    classify_by(f, hi - lo, above, in, [&](float x) { return x > fhi; },
+                [&](float x) { return (__float_as_uint(x) ^ flip) - lo; });
   } else {
-#pragma unroll
-    for (int r = 0; r < SEL_ROUNDS; ++r)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const uint32_t q = score_key(f[r][e]);
-        above |= q > k.hi ? 1u << (4 * r + e) : 0u;
-        in |= q >= k.lo ? 1u << (4 * r + e) : 0u;
-      }
+    classify_by(f, hi - lo, above, in, [&](float x) { return score_key(x) > hi; },
+                [&](float x) { return score_key(x) - lo; });
   }
   above &= valid;
-  in &= valid & ~above;
+  in &= valid;
 }
 
-// Room for the marks of a chunk of `tokens` tokens: a pair of words (above the bin, inside it) per thread
-// that has tokens.  They stand at the end of the chunk's part of the candidate list, where the candidates
-// leave that much room (otherwise the emit reads the scores again).
-__device__ __forceinline__ int mark_ints(int tokens) { return 2 * min(CHUNK_THREADS, (tokens + 3) >> 2); }
+// Room for the marks of a chunk of `tokens` tokens: where each wave's candidates begin in the list, then a pair
+// of words (above the range, inside it) per thread that has tokens.  They stand at the end of the chunk's part
+// of the candidate list, where the candidates leave that much room (otherwise the emit reads the scores again).
+__device__ __forceinline__ int mark_ints(int tokens) {
+  return CHUNK_THREADS / 64 + 2 * min(CHUNK_THREADS, (tokens + 3) >> 2);
+}
 
 // find_digit on the 4096-digit histogram of a pool in global memory (16-byte aligned), by a
 // workgroup of CHUNK_THREADS.
@@ -456,31 +469,193 @@ __device__ __forceinline__ void flush_hist(const int *hist, int nb, int *__restr
   }
 }
 
-// First digit, for scores that did not come with a histogram (hist1 zero on entry).
-__global__ __launch_bounds__(CHUNK_THREADS, 8) void msel_hist1_kernel(const SegTable T,
-                                                                    const float *__restrict__ scores,
-                                                                    int *__restrict__ hist1) {
-  __shared__ int hist[4096];
-  const SelWhere q = sel_locate(T, blockIdx.x);
-  const Seg &s = T.s[q.seg];
-  const float *sp = scores + s.score_off + (long long)q.head * s.n;
-  float f[SEL_ROUNDS][4];
-  const unsigned valid = load_chunk_scores(sp, q, f);
-  for (int i = threadIdx.x; i < 4096; i += CHUNK_THREADS) hist[i] = 0;
+// ---- scores that came without a histogram: a bracket of the threshold from a sample ----
+// The threshold is the K-th largest of a pool's N scores (contiguous in memory: a pool is whole heads).
+// One workgroup per pool reads a sample of m scores, half a 128-byte line at a hashed place in each of
+// equal stretches, and takes the order statistics of the sample `margin` places on either side of
+// rank K m / N.  margin is 4.5 standard deviations of the number of sampled scores above the threshold,
+// estimated from the half lines themselves (their counts above either end of the threshold's bin), since
+// neighbouring scores may be alike: half a line then says no more than one score.  A bracket that misses all
+// the same costs time and not exactness: msel_thr_kernel counts what lies above and inside it, and looks at
+// all scores of a pool where the threshold is in neither.  Pools of up to SAMPLE_WHOLE scores are read whole.
+// Half lines, because a compute unit takes about 7 ns a line from memory however much of it is used (112 heads
+// of 131072 tokens: 15 us for this kernel with 2048 groups of four, 8192 scores either way, against 11).
+// Against a histogram over all scores, which was another pass over them, as long as the candidates', with a
+// launch to clear it, and 16 KB that every chunk searched: whole selection on MI355X, us before / now,
+// leverage scores, 112 heads of 131072 tokens 57.5 / 43.3; 8 heads of 131072 32 / 33; heads of 40003, 128 of them
+// 40.6 / 37.0, 600 88.6 / 75.7, 4096 of 33000 426 / 356; layers of 8 x 8192, 256 of them 67.5 / 49.7, of
+// 8 x 131072, one 53.1 / 52.6.  Scores averaged over 7 neighbours, the same: 32.8 / 33.4, 41.5 / 37.8, 87.7 /
+// 80.6, 419 / 376, 66.5 / 53.5, 54.7 / 55.7; over 63 neighbours the bracket is wider: 33.5 / 36.4, 42.9 / 40.6,
+// 94.1 / 87.5, 442 / 413, 72.2 / 58.9, and 53.9 / 73.6, where one pool has a quarter of a million candidates.
+constexpr int SAMPLE_THREADS = 1024, SAMPLE_ROUNDS = 2, SAMPLE_WAVES = SAMPLE_THREADS / 64;
+static_assert(SAMPLE_ROUNDS * SAMPLE_THREADS * 4 == SAMPLE_WHOLE, "a whole pool fits the registers");
+
+// Like find_digit on 4096 digits, for two ranks at once.
+__device__ __forceinline__ void find_two(const int *hist, const int (&want)[2], int *wsum, int *found, int (&digit)[2],
+                                         int (&need)[2]) {
+  constexpr int PER = 4096 / SAMPLE_THREADS;
+  static_assert(PER == 4, "one 16-byte read");
+  const int t0 = PER * (int)threadIdx.x;                 // digits 4095 - t0 .. , descending
+  const int4 v = *reinterpret_cast<const int4 *>(&hist[4096 - PER - t0]);
+  const int c[PER] = {v.w, v.z, v.y, v.x};
+  int total;
+  int before = block_exclusive_scan<SAMPLE_THREADS>(v.x + v.y + v.z + v.w, wsum, &total);
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      if (before < want[i] && want[i] <= before + c[q]) {        // exactly one (thread, q) matches
+        found[2 * i] = 4095 - (t0 + q);
+        found[2 * i + 1] = want[i] - before;
+      }
+    before += c[q];
+  }
   __syncthreads();
 #pragma unroll
-  for (int r = 0; r < SEL_ROUNDS; ++r)
+  for (int i = 0; i < 2; ++i) { digit[i] = found[2 * i]; need[i] = found[2 * i + 1]; }
+}
+
+__global__ __launch_bounds__(SAMPLE_THREADS) void msel_sample_kernel(const SegTable T,
+                                                                     const float *__restrict__ scores,
+                                                                     int *__restrict__ state) {
+  __shared__ __attribute__((aligned(16))) int hist[HIST1_BINS], sub[2][4096];
+  __shared__ int wsum[SAMPLE_WAVES], sums[SAMPLE_WAVES][4];
+  __shared__ int found[4];
+  const int pool = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int seg = 0;
+  for (int i = 1; i < T.nseg; ++i) seg += pool >= T.s[i].pool0;
+  const Seg &s = T.s[seg];
+  const int ph = pool_heads(T, s);
+  const int n = ph * s.n, k = ph * s.k_keep;             // of the pool; below 2^31 - 64
+  const float *sp = scores + s.score_off + (long long)(s.head_begin + (pool - s.pool0) * ph) * s.n;
+  const bool whole = n <= SAMPLE_WHOLE;
+  float f[SAMPLE_ROUNDS][4];
+  unsigned valid = 0;
+  if (!whole) {
+    const int first = (int)(-(reinterpret_cast<uintptr_t>(sp) >> 2) & 15u), lines = (n - first) >> 4;
+#pragma unroll
+    for (int r = 0; r < SAMPLE_ROUNDS; ++r) {
+      const int at = first + 16 * sample_line(r * (SAMPLE_THREADS / 4) + (tid >> 2), lines) + 4 * (tid & 3);
+      const float4 v = *reinterpret_cast<const float4 *>(sp + at);
+      f[r][0] = v.x; f[r][1] = v.y; f[r][2] = v.z; f[r][3] = v.w;
+    }
+    valid = (1u << (4 * SAMPLE_ROUNDS)) - 1u;
+  } else {
+#pragma unroll
+    for (int r = 0; r < SAMPLE_ROUNDS; ++r)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int at = (4 * r + e) * SAMPLE_THREADS + tid;
+        f[r][e] = 0.f;
+        if (at < n) {
+          f[r][e] = sp[at];
+          valid |= 1u << (4 * r + e);
+        }
+      }
+  }
+  const int m = min(n, SAMPLE_WHOLE);
+  for (int i = 4 * tid; i < HIST1_BINS; i += 4 * SAMPLE_THREADS)
+    *reinterpret_cast<int4 *>(&hist[i]) = *reinterpret_cast<int4 *>(&sub[0][i]) =
+        *reinterpret_cast<int4 *>(&sub[1][i]) = make_int4(0, 0, 0, 0);
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < SAMPLE_ROUNDS; ++r)
 #pragma unroll
     for (int e = 0; e < 4; ++e)
       if (valid >> (4 * r + e) & 1) atomicAdd(&hist[score_bin(score_key(f[r][e]))], 1);
   __syncthreads();
-  flush_hist<CHUNK_THREADS>(hist, 4096, hist1 + (size_t)q.pool * 4096);
+  // descending ranks (1 .. m) of the two ends of the bracket
+  int rank[2] = {k, k};
+  if (!whole) {
+    const double mid = (double)k * m / n;
+    int need = max(1, min(m, (int)(mid + 0.5)));
+    const BinKeys bk = bin_keys(find_digit<SAMPLE_THREADS>(hist, HIST1_BINS, &need, wsum, found), true);
+    const uint32_t last = bk.lo | ((1u << bk.bits) - 1u);
+    // per line the scores above the bin, and those from its lower end on in the upper half of the word;
+    // then sums (at most 2^13) and sums of squares (at most 2^17) of both over the lines
+    int ab = 0, q0 = 0, q1 = 0;
+#pragma unroll
+    for (int r = 0; r < SAMPLE_ROUNDS; ++r) {
+      int c = 0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const uint32_t key = score_key(f[r][e]);
+        c += (key > last ? 1 : 0) + (key >= bk.lo ? 0x10000 : 0);
+      }
+      constexpr int XOR1 = 0xb1, XOR2 = 0x4e;
+      c += __builtin_amdgcn_update_dpp(0, c, XOR1, 0xf, 0xf, false);
+      c += __builtin_amdgcn_update_dpp(0, c, XOR2, 0xf, 0xf, false);
+      if ((lane & 3) == 0) {
+        ab += c;
+        q0 += (c & 0xffff) * (c & 0xffff);
+        q1 += (c >> 16) * (c >> 16);
+      }
+    }
+    ab = wave_inclusive_scan(ab);
+    q0 = wave_inclusive_scan(q0);
+    q1 = wave_inclusive_scan(q1);
+    if (lane == 63) { sums[wave][0] = ab; sums[wave][1] = q0; sums[wave][2] = q1; }
+    __syncthreads();
+    ab = q0 = q1 = 0;
+#pragma unroll
+    for (int w = 0; w < SAMPLE_WAVES; ++w) { ab += sums[w][0]; q0 += sums[w][1]; q1 += sums[w][2]; }
+    constexpr float per_line = 1.f / (float)SAMPLE_LINES;
+    const float s0 = (float)(ab & 0xffff), s1 = (float)(ab >> 16);
+    const float var = fmaxf((float)q0 - s0 * s0 * per_line, (float)q1 - s1 * s1 * per_line);
+    const int margin = (int)(4.5f * sqrtf(fmaxf(var, 0.f))) + 3;
+    rank[0] = (int)mid - margin;
+    rank[1] = (int)mid + 1 + margin;
+  }
+  // Either end: its bin, then the 12 bits below the bin's.  No end above rank 1 or below rank m.
+  const bool has_hi = rank[0] >= 1, has_lo = rank[1] <= m;
+  const int want[2] = {max(1, rank[0]), min(m, rank[1])};
+  int bin[2], need[2], dig[2];           // dig: below the bin's
+  find_two(hist, want, wsum, found, bin, need);
+  const BinKeys bh = bin_keys(bin[0], true), bl = bin_keys(bin[1], true);
+#pragma unroll
+  for (int r = 0; r < SAMPLE_ROUNDS; ++r)
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (valid >> (4 * r + e) & 1) {
+        const uint32_t key = score_key(f[r][e]);
+        if (key >> bh.bits == bh.lo >> bh.bits) atomicAdd(&sub[0][key >> (bh.bits - 12) & 0xfffu], 1);
+        if (key >> bl.bits == bl.lo >> bl.bits) atomicAdd(&sub[1][key >> (bl.bits - 12) & 0xfffu], 1);
+      }
+  __syncthreads();
+  {
+    // both digits by one scan: half of the threads have eight digits each of sub[0], the others of sub[1]
+    const int half = wave / (SAMPLE_WAVES / 2), t0 = 8 * (tid & (SAMPLE_THREADS / 2 - 1));
+    const int4 a = *reinterpret_cast<const int4 *>(&sub[half][4092 - t0]);
+    const int4 b = *reinterpret_cast<const int4 *>(&sub[half][4088 - t0]);
+    const int c[8] = {a.w, a.z, a.y, a.x, b.w, b.z, b.y, b.x};
+    int total;
+    int before = block_exclusive_scan<SAMPLE_THREADS>(a.x + a.y + a.z + a.w + b.x + b.y + b.z + b.w, wsum, &total);
+    if (half)
+#pragma unroll
+      for (int w = 0; w < SAMPLE_WAVES / 2; ++w) before -= wsum[w];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      if (before < need[half] && need[half] <= before + c[q]) found[half] = 4095 - (t0 + q);
+      before += c[q];
+    }
+    __syncthreads();
+    dig[0] = found[0];
+    dig[1] = found[1];
+  }
+  if (tid == 0) {
+    int *st = state + pool * SEL_STATE;
+    const int rh = bh.bits - 12, rl = bl.bits - 12;
+    st[ST_LO] = has_lo ? (int)(bl.lo | (uint32_t)dig[1] << rl) : 0;
+    st[ST_HI] = has_hi ? (int)(bh.lo | (uint32_t)dig[0] << rh | ((1u << rh) - 1u)) : (int)0xff800000u;      // +inf
+  }
 }
 
-// Candidates of a chunk: counts the keys above the threshold's bin and lists the low 23 bits of the
-// keys inside it (cand, at the chunk's position in the launch's token sequence, so a list can never
-// outgrow its room), and marks both kinds for the emit.  rec[chunk] = (keys above, candidates listed).
-__global__ __launch_bounds__(CHUNK_THREADS, 7) void msel_cand_kernel(const SegTable T, int fine,
+// Candidates of a chunk: counts the keys above the range that holds the threshold and lists the
+// keys inside it, less its lowest (cand, at the chunk's position in the launch's token sequence, so a list can
+// never outgrow its room), and marks both kinds for the emit.  rec[chunk] = (keys above, candidates listed).
+// SAMPLED: the range comes from msel_sample_kernel, else from the pool's histogram.
+template <bool SAMPLED>
+__global__ __launch_bounds__(CHUNK_THREADS, 7) void msel_cand_kernel(const SegTable T,
                                                                   const float *__restrict__ scores,
                                                                   const int *__restrict__ hist1,
                                                                   uint32_t *__restrict__ cand,
@@ -489,56 +664,91 @@ __global__ __launch_bounds__(CHUNK_THREADS, 7) void msel_cand_kernel(const SegTa
   __shared__ int wsum[CHUNK_THREADS / 64];
   __shared__ int found[2];
   __shared__ int above_s, ncand_s;
+  constexpr int CAND_STAGE = 768;        // of at most 2048 a wave
+  __shared__ __attribute__((aligned(16))) uint32_t stage[CHUNK_THREADS / 64][CAND_STAGE];
   const SelWhere q = sel_locate(T, blockIdx.x);
   const Seg &s = T.s[q.seg];
   const float *sp = scores + s.score_off + (long long)q.head * s.n;
   float f[SEL_ROUNDS][4];
-  const unsigned valid = load_chunk_scores(sp, q, f);    // in flight while the digit is found
+  load_scores_part<SEL_ROUNDS>(sp, q, 0, f);             // in flight while the digit is found
   if (threadIdx.x == 0) { above_s = 0; ncand_s = 0; }
-  const int ph = pool_heads(T, s);
-  int need = ph * s.k_keep;
-  const int bin = find_digit_global(hist1 + (size_t)q.pool * HIST1_BINS, &need, wsum, found);
-  if (q.tile == 0 && q.lhead % ph == 0 && threadIdx.x == 0) {   // the pool's first chunk
-    state[q.pool * SEL_STATE + ST_BIN] = bin;
-    state[q.pool * SEL_STATE + ST_NEED1] = need;
+  uint32_t lo, hi;
+  if constexpr (SAMPLED) {
+    __syncthreads();                     // the counters are zero
+    lo = (uint32_t)state[q.pool * SEL_STATE + ST_LO];
+    hi = (uint32_t)state[q.pool * SEL_STATE + ST_HI];
+  } else {
+    const int ph = pool_heads(T, s);
+    int need = ph * s.k_keep;
+    const BinKeys bk = bin_keys(find_digit_global(hist1 + (size_t)q.pool * HIST1_BINS, &need, wsum, found), false);
+    lo = bk.lo;
+    hi = bk.lo | ((1u << bk.bits) - 1u);
+    if (q.tile == 0 && q.lhead % ph == 0 && threadIdx.x == 0) {   // the pool's first chunk
+      state[q.pool * SEL_STATE + ST_LO] = (int)lo;
+      state[q.pool * SEL_STATE + ST_HI] = (int)hi;
+    }
   }
-  const BinKeys bk = bin_keys(bin, fine != 0);
-  const KeyRange range(bk.lo, bk.lo | ((1u << bk.bits) - 1u));
   unsigned above, in;
-  classify(f, valid, range, above, in);
+  const unsigned valid = place_scores_part<SEL_ROUNDS>(q, 0, f);
+  classify(f, valid, lo, hi, above, in);
   uint32_t *list = cand + chunk_token_base(T, q);
   const int lane = threadIdx.x & 63;
-  // A thread's candidates go to consecutive slots: count, scan inside the wave (packed with the count
-  // above, at most 2048 each), one LDS add per wave for the wave's share of the list (the order in which
-  // waves claim theirs does not matter).
-  const int mine = __popc(in);
-  const int inc = wave_inclusive_scan(mine | (__popc(above) << 16));
+  // A wave's candidates stand in thread order, a thread's in consecutive slots, so that the emit finds them
+  // again by the same sums of the marks; the order in which waves claim their share of the list does not
+  // matter.  Counts are packed with those above (at most 2048 each).
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int both = __popc(in) | (__popc(above) << 16);
+  const int inc = wave_inclusive_scan(both);
+  const int mine = __builtin_amdgcn_readlane(inc, 63) & 0xffff;          // of the wave
   int base = 0;
   if (lane == 63) {
-    if (inc & 0xffff) base = atomicAdd(&ncand_s, inc & 0xffff);
+    if (mine) base = atomicAdd(&ncand_s, mine);
     if (inc >> 16) atomicAdd(&above_s, inc >> 16);
   }
-  int off = __shfl(base, 63) + (inc & 0xffff) - mine;
-  // the keys of a bin share their sign: below it, a key's low bits are the complement of the float's
-  const uint32_t flip = (bk.lo & 0x80000000u) ? 0u : 0x7fffffu;
+  base = __builtin_amdgcn_readlane(base, 63);
+  auto put = [&](uint32_t *to) {
+    to += (inc - both) & 0xffff;
 #pragma unroll
-  for (int r = 0; r < SEL_ROUNDS; ++r)
+    for (int r = 0; r < SEL_ROUNDS; ++r)
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if (in >> (4 * r + e) & 1) {
-        uint32_t v = (__float_as_uint(f[r][e]) & 0x7fffffu) ^ flip;
-        if (!range.plain) v = score_key(f[r][e]) & 0x7fffffu;
-        list[off++] = v;
+      for (int e = 0; e < 4; ++e)
+        if (in >> (4 * r + e) & 1) *to++ = __float_as_uint(f[r][e]);
+  };
+  if (SAMPLED && mine <= CAND_STAGE) {   // they leave as one run
+    typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+    put(stage[wave]);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    for (int i = 4 * lane; i < mine; i += 256) {
+      const uint4 v = *reinterpret_cast<const uint4 *>(&stage[wave][i]);
+      uint32_t *to = list + base + i;
+      if (i + 3 < mine) {
+        *reinterpret_cast<u32x4_any *>(to) = u32x4_any{v.x, v.y, v.z, v.w};
+      } else {
+        to[0] = v.x;
+        if (i + 1 < mine) to[1] = v.y;
+        if (i + 2 < mine) to[2] = v.z;
       }
+    }
+  } else {
+    put(list + base);
+  }
   __syncthreads();
   const int tokens = q.tok_end - q.tok_begin, marks = mark_ints(tokens);
-  if (ncand_s <= tokens - marks && 2 * (int)threadIdx.x < marks) {
-    list[tokens - marks + 2 * threadIdx.x] = above;
-    list[tokens - marks + 2 * threadIdx.x + 1] = in;
+  const int ncand = ncand_s;
+  if (ncand <= tokens - marks) {
+    constexpr int NW = CHUNK_THREADS / 64;
+    uint32_t *mark = list + (tokens - marks);
+    if (lane == 0) mark[wave] = (uint32_t)base;
+    if (NW + 2 * (int)threadIdx.x < marks) {
+      mark[NW + 2 * threadIdx.x] = above;
+      mark[NW + 2 * threadIdx.x + 1] = in;
+    }
   }
   if (threadIdx.x == 0) {
     rec[2 * blockIdx.x] = above_s;
-    rec[2 * blockIdx.x + 1] = ncand_s;
+    rec[2 * blockIdx.x + 1] = ncand;
   }
 }
 
@@ -573,7 +783,9 @@ __device__ __forceinline__ void for_each_cand(const uint32_t *__restrict__ l, in
 
 // One workgroup per pool: the threshold key from the pool's candidates, then for every chunk of
 // the pool (in head, token order) the position of its first retained token in the pool's
-// output and how many threshold ties it may keep; the per-head counts.
+// output and how many threshold ties it may keep; the per-head counts.  The candidates' rank comes from the
+// chunks' counts; where it says that the threshold is none of them (a sampled bracket that missed), the
+// threshold and the counts come from all scores of the pool instead (ST_FULL), in five more passes.
 // Two passes over the candidates: (1) histogram of the upper 12 bits in which they differ -> second
 // digit d2; (2) per chunk the count above d2, a histogram of the low bits (5, 8 or 11) of those inside d2,
 // and those few themselves as (chunk, low bits) in a short LDS list, from which, once the last digit is
@@ -588,9 +800,11 @@ __device__ __forceinline__ void for_each_cand(const uint32_t *__restrict__ l, in
 // 184 / 166; of 131072, 256 131 / 138, 384 185 / 184, 640 296 / 288; layers of 8 x 8192, 256 86.6 / 88.8,
 // 384 117 / 113; of 8 x 32768, 256 224 / 240, 384 345 / 349.  Behind the score kernel, selection
 // alone: 256 heads of 66000 55 / 61, 384 76 / 74, 640 of 100000 130 / 121, 1536 of 40003 150 / 122.
+// SAMPLED: the range of the candidates' values is any, and the threshold may be none of them.
 constexpr int THR_BLOCK = 512, THR_SHORT = 2048, THR_WIDE_POOLS = 256;
-template <int THR_THREADS>
-__global__ __launch_bounds__(THR_THREADS) void msel_thr_kernel(const SegTable T, int fine,
+template <int THR_THREADS, bool SAMPLED>
+__global__ __launch_bounds__(THR_THREADS) void msel_thr_kernel(const SegTable T,
+                                                               const float *__restrict__ scores,
                                                                const uint32_t *__restrict__ cand,
                                                                const int *__restrict__ rec,
                                                                int *__restrict__ coff,
@@ -629,51 +843,116 @@ __global__ __launch_bounds__(THR_THREADS) void msel_thr_kernel(const SegTable T,
     __syncthreads();
   };
 
-  const BinKeys bk = bin_keys(state[pool * SEL_STATE + ST_BIN], fine != 0);
-  const uint32_t key1 = bk.lo;
-  const int rest = bk.bits - 12;
-  const uint32_t low = (1u << rest) - 1u;
-  int need = state[pool * SEL_STATE + ST_NEED1];
-
-  // pass 1: the upper 12 bits of every candidate
+  const uint32_t lo = (uint32_t)state[pool * SEL_STATE + ST_LO];
+  const uint32_t span = (uint32_t)state[pool * SEL_STATE + ST_HI] - lo;
+  int bits = span ? 32 - __clz((int)span) : 0;           // of a candidate's value
+  // the candidates of rank 1 .. inside are inside
+  int need = ph * s.k_keep;
+  bool full = false;
   for (int i = tid; i < 4096; i += THR_THREADS) hist[i] = 0;
   if (tid == 0) nshort = 0;
-  for (int cb = 0; cb < nchunks; cb += THR_BLOCK) {
-    fetch(cb);
-    for (int u = wave; u < THR_BLOCK && cb + u < nchunks; u += NW)
-      for_each_cand(list_of(cb + u), cnt_c[u], lane,
-                    [&](uint32_t v) { atomicAdd(&hist[(v >> rest) & 0xfffu], 1); });
+  {
+    int above = 0, inside = 0;
+    for (int cb = 0; cb < nchunks; cb += THR_BLOCK) {
+      fetch(cb);
+      for (int u = tid; u < THR_BLOCK && cb + u < nchunks; u += THR_THREADS) {
+        above += above_c[u];
+        inside += cnt_c[u];
+      }
+    }
+    int all;
+    block_exclusive_scan<THR_THREADS>(above, wsum, &all);
+    need -= all;
+    if constexpr (SAMPLED) {
+      block_exclusive_scan<THR_THREADS>(inside, wsum, &all);
+      full = need < 1 || need > all;
+    }
   }
+  uint32_t base = 0;                                     // the threshold's value lies in [base, base + 2^bits)
+  const int npool = ph * s.n;
+  const float *sp = scores + s.score_off + (long long)head0 * s.n;
+  // the 12 bits from `rest` on of the values (or, full, of the keys) in [base, base + 2^(rest + 12))
+  auto tally = [&](int rest) {
+    if (SAMPLED && full) {
+      for (int i = tid; i < npool; i += THR_THREADS) {
+        const uint32_t d = (score_key(sp[i]) - base) >> rest;
+        if (d < 4096) atomicAdd(&hist[d], 1);
+      }
+      return;
+    }
+    for (int cb = 0; cb < nchunks; cb += THR_BLOCK) {
+      if (!single) fetch(cb);
+      for (int u = wave; u < THR_BLOCK && cb + u < nchunks; u += NW)
+        for_each_cand(list_of(cb + u), cnt_c[u], lane, [&](uint32_t v) {
+          const uint32_t d = (v - base) >> rest;
+          if (!SAMPLED || d < 4096) atomicAdd(&hist[d], 1);
+        });
+    }
+  };
+  if (SAMPLED && full) {
+    bits = 32;
+    need = ph * s.k_keep;
+  }
+  if (SAMPLED && bits > 23) {                            // one pass more
+    tally(bits - 12);
+    __syncthreads();
+    bits -= 12;
+    base = (uint32_t)find_digit<THR_THREADS>(hist, 4096, &need, wsum, found) << bits;
+    __syncthreads();
+    for (int i = tid; i < 4096; i += THR_THREADS) hist[i] = 0;
+    __syncthreads();
+  }
+  const int rest = bits > 12 ? bits - 12 : 0;
+  const uint32_t low = (1u << rest) - 1u;
+  // pass 1: the upper 12 bits of every candidate
+  tally(rest);
   __syncthreads();
   const uint32_t d2 = (uint32_t)find_digit<THR_THREADS>(hist, 4096, &need, wsum, found);
+  base += d2 << rest;
+  const uint32_t top = base | low;
   // pass 2: the low bits of the candidates that share the second digit; per chunk those above it
-  for (int i = tid; i <= (int)low; i += THR_THREADS) hist[i] = 0;
-  for (int cb = 0; cb < nchunks; cb += THR_BLOCK) {
-    if (!single) fetch(cb); else __syncthreads();
-    for (int u = wave; u < THR_BLOCK && cb + u < nchunks; u += NW) {
-      int gt = 0;
-      for_each_cand(list_of(cb + u), cnt_c[u], lane, [&](uint32_t v) {
-        const uint32_t top = (v >> rest) & 0xfffu;
-        gt += top > d2;
-        if (top == d2) {
-          atomicAdd(&hist[v & low], 1);
-          if (single) {
-            const int at = atomicAdd(&nshort, 1);
-            if (at < THR_SHORT) short_l[at] = ((uint32_t)u << 11) | (v & low);
+  // (none: d2 is the whole value, and the third pass counts)
+  const bool third = SAMPLED && rest == 0;
+  if (!third)
+    for (int i = tid; i <= (int)low; i += THR_THREADS) hist[i] = 0;
+  if (third) {
+  } else if (SAMPLED && full) {
+    __syncthreads();
+    for (int i = tid; i < npool; i += THR_THREADS) {
+      const uint32_t v = score_key(sp[i]) - base;
+      if (v <= low) atomicAdd(&hist[v], 1);
+    }
+  } else {
+    for (int cb = 0; cb < nchunks; cb += THR_BLOCK) {
+      if (!single) fetch(cb); else __syncthreads();
+      for (int u = wave; u < THR_BLOCK && cb + u < nchunks; u += NW) {
+        int gt = 0;
+        for_each_cand(list_of(cb + u), cnt_c[u], lane, [&](uint32_t v) {
+          gt += v > top;
+          if (v - base <= low) {
+            atomicAdd(&hist[v - base], 1);
+            if (single) {
+              const int at = atomicAdd(&nshort, 1);
+              if (at < THR_SHORT) short_l[at] = ((uint32_t)u << 11) | (v - base);
+            }
           }
-        }
-      });
+        });
 #pragma unroll
-      for (int d = 32; d >= 1; d >>= 1) gt += __shfl_xor(gt, d);
-      if (lane == 0) { gt_c[u] = gt; eq_c[u] = 0; }
+        for (int d = 32; d >= 1; d >>= 1) gt += __shfl_xor(gt, d);
+        if (lane == 0) { gt_c[u] = gt; eq_c[u] = 0; }
+      }
     }
   }
   __syncthreads();
-  const uint32_t d3 = (uint32_t)find_digit<THR_THREADS>(hist, 1 << rest, &need, wsum, found);
+  const uint32_t d3 = third ? 0u : (uint32_t)find_digit<THR_THREADS>(hist, 1 << rest, &need, wsum, found);
   const int tie_keep = need;             // keys equal to the threshold that are retained
-  const uint32_t thr = key1 | (d2 << rest) | d3, thr23 = thr & 0x7fffffu;
-  if (tid == 0) state[pool * SEL_STATE + ST_THR] = (int)thr;
-  const bool from_short = single && nshort <= THR_SHORT;
+  const bool all_ties = hist[third ? d2 : d3] == need;
+  const uint32_t at_v = base + d3, thr = SAMPLED && full ? at_v : lo + at_v;     // the threshold's value and key
+  if (tid == 0) {
+    state[pool * SEL_STATE + ST_THR] = (int)thr;
+    state[pool * SEL_STATE + ST_FULL] = full;
+  }
+  const bool from_short = single && !full && !third && nshort <= THR_SHORT;
   if (from_short) {                      // the chunks' counts at the last digit, from the short list
     for (int i = tid; i < nshort; i += THR_THREADS) {
       const uint32_t e = short_l[i];
@@ -691,10 +970,20 @@ __global__ __launch_bounds__(THR_THREADS) void msel_thr_kernel(const SegTable T,
       if (!single) fetch(cb); else __syncthreads();
       for (int u = wave; u < THR_BLOCK && cb + u < nchunks; u += NW) {
         int gt = 0, eq = 0;
-        for_each_cand(list_of(cb + u), cnt_c[u], lane, [&](uint32_t v) {
-          gt += v > thr23;
-          eq += v == thr23;
-        });
+        if (SAMPLED && full) {
+          const int t0 = (cb + u) % bph * csize, cnt = min(csize, s.n - t0);
+          const float *cp = sp + (long long)((cb + u) / bph) * s.n + t0;
+          for (int i = lane; i < cnt; i += 64) {
+            const uint32_t key = score_key(cp[i]);
+            gt += key > thr;
+            eq += key == thr;
+          }
+        } else {
+          for_each_cand(list_of(cb + u), cnt_c[u], lane, [&](uint32_t v) {
+            gt += v > at_v;
+            eq += v == at_v;
+          });
+        }
 #pragma unroll
         for (int d = 32; d >= 1; d >>= 1) {
           gt += __shfl_xor(gt, d);
@@ -709,10 +998,12 @@ __global__ __launch_bounds__(THR_THREADS) void msel_thr_kernel(const SegTable T,
       const int u = u0 + tid, cc = cb + u;
       const bool mine = u < THR_BLOCK && cc < nchunks;
       const int eq = mine ? eq_c[u] : 0;
-      int eq_all, kept_all;
-      const int eq0 = eq_before + block_exclusive_scan<THR_THREADS>(eq, wsum, &eq_all);
-      const int allow = max(0, min(eq, tie_keep - eq0));
-      const int kept = mine ? above_c[u] + gt_c[u] + allow : 0;
+      int eq_all = 0, kept_all, allow = eq;
+      if (!all_ties) {                   // uniform
+        const int eq0 = eq_before + block_exclusive_scan<THR_THREADS>(eq, wsum, &eq_all);
+        allow = max(0, min(eq, tie_keep - eq0));
+      }
+      const int kept = mine ? (full ? 0 : above_c[u]) + gt_c[u] + allow : 0;
       const int at = pos + block_exclusive_scan<THR_THREADS>(kept, wsum, &kept_all);
       if (mine) {
         *reinterpret_cast<i32x2_any *>(coff + 2 * (chunk0 + cc)) = i32x2_any{at, allow};
@@ -737,9 +1028,10 @@ __global__ __launch_bounds__(THR_THREADS) void msel_thr_kernel(const SegTable T,
 }
 
 // Ordered emit of one chunk.  The marks of the candidate pass say which tokens lie above the threshold's
-// bin and which inside it; only the scores of the latter are read again and compared with the threshold
-// (few with 64 bins an octave; with 8, or with heavy ties, most threads have some and whole rows are read,
-// as they are where the candidates left no room for marks).  Four tokens per thread and round come in:
+// range and which inside it; the latter's values stand in the list in the order of the marks, and the scores
+// are only read again where the candidates left no room for marks, or the range missed the threshold.
+//  (It used to read the candidates' scores, one line of memory for each, or whole rows: 112 heads of 131072
+// tokens 11.3 us, 9.1 now.)  Four tokens per thread and round come in:
 // a byte per such group passes through LDS, so that a thread then holds 32 consecutive tokens and one scan
 // over the workgroup gives every position.  Counts are packed as (above | equal << 16), at most 8192 each.
 __global__ __launch_bounds__(CHUNK_THREADS, 8) void msel_emit_kernel(const SegTable T,
@@ -759,14 +1051,19 @@ __global__ __launch_bounds__(CHUNK_THREADS, 8) void msel_emit_kernel(const SegTa
   const float *sp = scores + s.score_off + (long long)q.head * s.n;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int tokens = q.tok_end - q.tok_begin, marks = mark_ints(tokens);
-  const uint32_t *mark = cand + chunk_token_base(T, q) + (tokens - marks);
+  const uint32_t *list = cand + chunk_token_base(T, q), *mark = list + (tokens - marks);
   unsigned gt = 0, in = 0, eq = 0;
-  if (2 * tid < marks && marks <= tokens) { gt = mark[2 * tid]; in = mark[2 * tid + 1]; }
+  int off = 0;                           // of the wave's candidates in the list
+  if (marks <= tokens) {
+    off = (int)mark[wave];
+    if (NW + 2 * tid < marks) { gt = mark[NW + 2 * tid]; in = mark[NW + 2 * tid + 1]; }
+  }
   const int ncand = rec[2 * blockIdx.x + 1];
   const int ph = pool_heads(T, s);
   const int limit = ph * s.k_keep;                       // rows of the pool's output
   int32_t *out = kept_idx + (s.kept_off + (long long)(q.head / ph) * limit);
   const uint32_t thr = (uint32_t)state[q.pool * SEL_STATE + ST_THR];
+  const bool no_marks = ncand > tokens - marks || state[q.pool * SEL_STATE + ST_FULL] != 0;
   const i32x2_any pa = *reinterpret_cast<const i32x2_any *>(coff + 2 * blockIdx.x);
   const int pos0 = pa.x, allow = pa.y;
   // key > thr and key == thr as float comparisons; a threshold that is NaN (key 0) equals NaN only and
@@ -774,35 +1071,38 @@ __global__ __launch_bounds__(CHUNK_THREADS, 8) void msel_emit_kernel(const SegTa
   const float fthr = key_score(thr);
   auto is_gt = [&](float x) { return thr ? x > fthr : x == x; };
   auto is_eq = [&](float x) { return thr ? x == fthr : x != x; };
-  auto token_of = [&](int bit) { return q.tok_begin + 4 * ((bit >> 2) * CHUNK_THREADS + tid) + (bit & 3); };
-  constexpr int FEW = 4;
-  if (ncand > tokens - marks || __any(__popc(in) > FEW)) {
-    if (ncand > tokens - marks) gt = 0;
+  if (no_marks) {                                        // uniform
+    gt = 0;
     float f[SEL_ROUNDS][4];
-    const unsigned valid = load_chunk_scores(sp, q, f);
-    const unsigned look = ncand > tokens - marks ? valid : in;
+    load_scores_part<SEL_ROUNDS>(sp, q, 0, f);
+    const unsigned valid = place_scores_part<SEL_ROUNDS>(q, 0, f);
 #pragma unroll
     for (int r = 0; r < SEL_ROUNDS; ++r)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const unsigned bit = look & (1u << (4 * r + e));
+        const unsigned bit = valid & (1u << (4 * r + e));
         gt |= is_gt(f[r][e]) ? bit : 0u;
         eq |= is_eq(f[r][e]) ? bit : 0u;
       }
   } else {
-    float f[FEW];
-    unsigned bit[FEW];
+    off += wave_inclusive_scan(__popc(in)) - __popc(in);
+    const uint32_t thr_v = thr - (uint32_t)state[q.pool * SEL_STATE + ST_LO];
+    constexpr int FLIGHT = 4;
+    while (__any(in != 0)) {
+      uint32_t v[FLIGHT];
+      unsigned bit[FLIGHT];
 #pragma unroll
-    for (int j = 0; j < FEW; ++j) {
-      bit[j] = in & (0u - in);
-      f[j] = 0.f;
-      if (in) f[j] = sp[token_of(__ffs(in) - 1)];
-      in &= in - 1;
-    }
+      for (int j = 0; j < FLIGHT; ++j) {
+        bit[j] = in & (0u - in);
+        in ^= bit[j];
+        v[j] = 0;
+        if (bit[j]) v[j] = list[off++];
+      }
 #pragma unroll
-    for (int j = 0; j < FEW; ++j) {
-      gt |= is_gt(f[j]) ? bit[j] : 0u;
-      eq |= is_eq(f[j]) ? bit[j] : 0u;
+      for (int j = 0; j < FLIGHT; ++j) {
+        gt |= v[j] > thr_v ? bit[j] : 0u;
+        eq |= v[j] == thr_v ? bit[j] : 0u;
+      }
     }
   }
 #pragma unroll
@@ -926,9 +1226,8 @@ __global__ __launch_bounds__(CHUNK_THREADS) void blend_apply_kernel(
   const float *a = s.attn + (long long)q.head * n;
   const float a0 = a[0];
   float fa[PART][4], fo[PART][4];
-  unsigned valid = 0;
   if (HALF) {
-    valid = load_scores_part<PART>(a, q, r_first, fa);
+    load_scores_part<PART>(a, q, r_first, fa);
     load_scores_part<PART>(o, q, r_first, fo);
   }
   // where the head's sums start: its first score workgroup
@@ -943,9 +1242,11 @@ __global__ __launch_bounds__(CHUNK_THREADS) void blend_apply_kernel(
   for (int r0 = r_first; r0 < (HALF ? r_first + PART : SEL_ROUNDS); r0 += PART) {
     if (!HALF) {
       if (q.tok_begin + 4 * r0 * CHUNK_THREADS >= q.tok_end) break;       // uniform
-      valid = load_scores_part<PART>(a, q, r0, fa);
+      load_scores_part<PART>(a, q, r0, fa);
       load_scores_part<PART>(o, q, r0, fo);
     }
+    place_scores_part<PART>(q, r0, fa);
+    const unsigned valid = place_scores_part<PART>(q, r0, fo);
 #pragma unroll
     for (int r = 0; r < PART; ++r) {
       const unsigned m = (valid >> (4 * r)) & 0xfu;
@@ -974,10 +1275,6 @@ __global__ __launch_bounds__(CHUNK_THREADS) void blend_apply_kernel(
   }
 }
 
-__global__ __launch_bounds__(256) void fill_zero_kernel(int *__restrict__ z, long long count) {
-  zero_slice(z, count);
-}
-
 bool select_needs_pools(const SegTable &T) {
   if (T.layer_scope) return true;
   for (int i = 0; i < T.nseg; ++i)
@@ -1003,31 +1300,26 @@ SelectScratch select_scratch(const SegTable &T) {
 
 long long select_chunks(const SegTable &T) { return total_blocks(T, SEL_CHUNK, 4, false); }
 
-hipError_t launch_select_pools(const SegTable &T, const float *scores, int *hist1, bool hist1_ready,
-                               int *sel, int32_t *kept_idx, int32_t *kept_cnt, hipStream_t st) {
+hipError_t launch_select_pools(const SegTable &T, const float *scores, const int *hist1, int *sel,
+                               int32_t *kept_idx, int32_t *kept_cnt, hipStream_t st) {
   if (T.nheads <= 0) return hipSuccess;
   const SelectScratch z = select_scratch(T);
   if (z.chunks > 0x7fffffffll) return hipErrorInvalidValue;
   uint32_t *cand = reinterpret_cast<uint32_t *>(sel);
   int *rec = sel + z.cand_ints, *coff = rec + z.rec_ints, *state = coff + z.coff_ints;
   const unsigned nb = (unsigned)z.chunks;
-  const int fine = hist1_ready ? 0 : 1;      // see score_bin
-  if (!hist1_ready) {
-    hipLaunchKernelGGL(fill_zero_kernel, dim3(256), dim3(256), 0, st, hist1,
-                       (long long)z.pools * HIST1_BINS);
-    if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
-    hipLaunchKernelGGL(msel_hist1_kernel, dim3(nb), dim3(CHUNK_THREADS), 0, st, T, scores, hist1);
+  const bool sampled = hist1 == nullptr;
+  if (sampled) {
+    hipLaunchKernelGGL(msel_sample_kernel, dim3((unsigned)z.pools), dim3(SAMPLE_THREADS), 0, st, T, scores, state);
     if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
   }
-  hipLaunchKernelGGL(msel_cand_kernel, dim3(nb), dim3(CHUNK_THREADS), 0, st, T, fine, scores, hist1,
-                     cand, rec, state);
+  hipLaunchKernelGGL(sampled ? msel_cand_kernel<true> : msel_cand_kernel<false>, dim3(nb), dim3(CHUNK_THREADS), 0, st,
+                     T, scores, hist1, cand, rec, state);
   if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
-  if (z.pools <= THR_WIDE_POOLS)          // see msel_thr_kernel
-    hipLaunchKernelGGL(msel_thr_kernel<1024>, dim3((unsigned)z.pools), dim3(1024), 0, st, T, fine, cand,
-                       rec, coff, state, kept_cnt);
-  else
-    hipLaunchKernelGGL(msel_thr_kernel<256>, dim3((unsigned)z.pools), dim3(256), 0, st, T, fine, cand,
-                       rec, coff, state, kept_cnt);
+  const int threads = z.pools <= THR_WIDE_POOLS ? 1024 : 256;          // see msel_thr_kernel
+  const auto thr = threads == 1024 ? (sampled ? msel_thr_kernel<1024, true> : msel_thr_kernel<1024, false>)
+                                   : (sampled ? msel_thr_kernel<256, true> : msel_thr_kernel<256, false>);
+  hipLaunchKernelGGL(thr, dim3((unsigned)z.pools), dim3(threads), 0, st, T, scores, cand, rec, coff, state, kept_cnt);
   if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
   hipLaunchKernelGGL(msel_emit_kernel, dim3(nb), dim3(CHUNK_THREADS), 0, st, T, scores, cand, rec,
                      coff, state, kept_idx);

@@ -153,6 +153,39 @@ def test_select_odd_token_totals(C, L, H, ns, ratios, scope):
     _select_case(C, ns, ratios, L, H, lambda r, m: r.random(m) ** 4, 41, scope)
 
 
+def _sampled(n, first):
+    """Which of a pool's n scores the selection samples: lines of 32 at hashed places of equal stretches, counted
+    from the first 128-byte boundary in it."""
+    g = np.arange(256, dtype=np.uint64)
+    h = (((g * 2654435761 & 0xffffffff) ^ 0x9e3779b9) * 2246822519 & 0xffffffff) >> np.uint64(16)
+    line = (((g << np.uint64(16)) | h) * np.uint64((n - first) // 32)) >> np.uint64(24)
+    return first + 32 * line.astype(np.int64)[:, None] + np.arange(32)
+
+
+# scores that say something else where they are sampled than elsewhere: the bracket misses, above or below
+# the threshold, by little and by much, and the range of what lies between is any; scores that come in runs;
+# brackets that are wider than a bin, and that reach the last key of either end
+@pytest.mark.parametrize("kind", ["high", "low", "nan", "runs", "two", "signs"])
+@pytest.mark.parametrize("H,n,ratio,scope", [(1, 40003, 0.3, 0), (2, 70001, 0.05, 0), (3, 50000, 0.5, 1),
+                                             (1, 33000, 0.999, 0), (1, 33000, 0.0001, 0), (200, 8200, 0.4, 1)])
+def test_select_where_the_sample_misleads(C, kind, H, n, ratio, scope):
+    pool = H * n if scope else n
+
+    def maker(r, m):
+        s = r.random(m).reshape(-1, pool)
+        if kind == "runs":
+            s = np.repeat(r.random((s.shape[0], pool // 64 + 1)), 64, axis=1)[:, :pool] + 1e-4 * s
+        elif kind == "two":
+            s = np.where(s < ratio, 1e10, 1e-10)
+        elif kind == "signs":
+            s -= 1.0 - ratio
+        else:
+            for i in range(s.shape[0]):
+                s[i, _sampled(pool, -(i * pool) % 32)] = {"high": 7.0, "low": -3.0, "nan": np.nan}[kind]
+        return s.ravel()
+    _select_case(C, [n], [ratio], 1, H, maker, 44, scope)
+
+
 def test_select_many_chunks_all_equal(C):
     _select_case(C, [17001], [0.4], 1, 180, lambda r, m: np.full(m, -0.5), 9, scope=C.SCOPE_LAYER)
 
