@@ -69,12 +69,12 @@ def test_selection_bins_partition_the_keys(M):
 
 @pytest.mark.parametrize("n", [8224, 8300, 16385, 1000003, 2 ** 31 - 65])
 def test_sampled_lines_lie_inside_the_pool(M, n):
-    """Lines of 32 scores, one in each of the equal stretches of the pool, from any alignment of its start."""
+    """Half lines of 16 scores, one in each of the equal stretches of the pool, from any alignment of its start."""
     groups = M.sample_lines()
-    assert groups == 256
-    for first in (0, 1, 31):
-        lines = (n - first) // 32
+    assert groups == 512
+    for first in (0, 1, 15):
+        lines = (n - first) // 16
         at = np.array([M.sample_line(g, lines) for g in range(groups)], dtype=np.int64)
-        assert at[0] >= 0 and first + 32 * at[-1] + 32 <= n and np.all(np.diff(at) >= 0)
+        assert at[0] >= 0 and first + 16 * at[-1] + 16 <= n and np.all(np.diff(at) >= 0)
         stretch = lines / groups
         assert np.all(np.abs(at + 0.5 - (np.arange(groups) + 0.5) * stretch) <= 0.5 * stretch + 1)

@@ -154,12 +154,12 @@ def test_select_odd_token_totals(C, L, H, ns, ratios, scope):
 
 
 def _sampled(n, first):
-    """Which of a pool's n scores the selection samples: lines of 32 at hashed places of equal stretches, counted
-    from the first 128-byte boundary in it."""
-    g = np.arange(256, dtype=np.uint64)
+    """Which of a pool's n scores the selection samples: half lines of 16 at hashed places of equal stretches,
+    counted from the first 64-byte boundary in it."""
+    g = np.arange(512, dtype=np.uint64)
     h = (((g * 2654435761 & 0xffffffff) ^ 0x9e3779b9) * 2246822519 & 0xffffffff) >> np.uint64(16)
-    line = (((g << np.uint64(16)) | h) * np.uint64((n - first) // 32)) >> np.uint64(24)
-    return first + 32 * line.astype(np.int64)[:, None] + np.arange(32)
+    line = (((g << np.uint64(16)) | h) * np.uint64((n - first) // 16)) >> np.uint64(25)
+    return first + 16 * line.astype(np.int64)[:, None] + np.arange(16)
 
 
 # scores that say something else where they are sampled than elsewhere: the bracket misses, above or below
@@ -181,7 +181,7 @@ def test_select_where_the_sample_misleads(C, kind, H, n, ratio, scope):
             s -= 1.0 - ratio
         else:
             for i in range(s.shape[0]):
-                s[i, _sampled(pool, -(i * pool) % 32)] = {"high": 7.0, "low": -3.0, "nan": np.nan}[kind]
+                s[i, _sampled(pool, -(i * pool) % 16)] = {"high": 7.0, "low": -3.0, "nan": np.nan}[kind]
         return s.ravel()
     _select_case(C, [n], [ratio], 1, H, maker, 44, scope)
 
