@@ -437,6 +437,10 @@ __host__ __device__ __forceinline__ int inplace_runs(int rows, int run_rows) {
 // Token tok (-1: none fetched) moves to the place of row j: not where it lies already or would move back.
 __host__ __device__ __forceinline__ bool inplace_moves(int tok, long long j, int n) { return tok > j && tok < n; }
 
+// Token tok of a head that keeps `rows` rows lies beyond their destinations, the slots 0 .. rows - 1, so that no move
+// of the head overwrites it.  Tokens ascend, so these are the last rows of the list.
+__host__ __device__ __forceinline__ bool inplace_late(int tok, int rows) { return tok >= rows; }
+
 // in_place: the rows are read from the pages themselves (token t at logical slot t).
 hipError_t launch_gather_paged(const SegTable &T, const PagePool &P, const int32_t *kept_idx,
                                const int32_t *kept_cnt, bool in_place, hipStream_t st);

@@ -152,6 +152,9 @@ __device__ __forceinline__ long long page_slot(const PagePool &P, int seg, int l
 
 // Retained rows from the dense source tensors into pages: retained token j of a head goes to
 // logical slot j of that head.  Workgroups are dealt as in the dense gathers.
+// FROM_PAGES: the second part of a compaction in place, the rows whose tokens lie beyond all destinations of their
+// head (see compact_inplace_kernel).
+template <bool FROM_PAGES>
 __global__ __launch_bounds__(GATHER_THREADS) void gather_paged_kernel(const SegTable T, const PagePool P,
                                                            const int32_t *__restrict__ kept_idx,
                                                            const int32_t *__restrict__ kept_cnt) {
@@ -182,32 +185,46 @@ __global__ __launch_bounds__(GATHER_THREADS) void gather_paged_kernel(const SegT
   const int layer = head0 / s.H;
 
   uint4 kv[GATHER_PASSES], vv[GATHER_PASSES];
-  long long dst[GATHER_PASSES];
+  long long dst[GATHER_PASSES], src[GATHER_PASSES];
 #pragma unroll
   for (int p = 0; p < GATHER_PASSES; ++p) {
     const int j = tile * GATHER_ROWS + p * GATHER_GROUPS + sub;
-    dst[p] = -1;
+    dst[p] = src[p] = -1;
     kv[p] = make_uint4(0, 0, 0, 0);
     vv[p] = make_uint4(0, 0, 0, 0);
     if (j < rows) {
-      int head = head0, jh = j;                      // head of the row and its rank in that head
+      int head = head0, jh = j, held = rows;         // head of the row, its rank and the rows of that head
       if (T.layer_scope) {
         head = -1;
         int run = 0;
         for (int hh = 0; hh < s.H; ++hh) {
           const int c = cnt[hh];
-          if (j < run + c) { head = head0 + hh; jh = j - run; break; }
+          if (j < run + c) { head = head0 + hh; jh = j - run; held = c; break; }
           run += c;
         }
       }
       const int tok = idx[j];
-      if (head >= 0 && tok >= 0 && tok < s.n) {
+      if (FROM_PAGES) {
+        if (head >= 0 && inplace_late(tok, held) && inplace_moves(tok, jh, s.n)) {
+          src[p] = page_slot(P, seg, layer, head - layer * s.H, tok);
+          dst[p] = page_slot(P, seg, layer, head - layer * s.H, jh);
+          if (src[p] < 0) dst[p] = -1;
+        }
+      } else if (head >= 0 && tok >= 0 && tok < s.n) {
         const long long off = (long long)tok * s.stride_t + chunk * 8;
         kv[p] = load_stream16(head_ptr(s.k_cache ? s.k_cache : s.k_score, s, head) + off);
         vv[p] = load_stream16(head_ptr(s.v_cache, s, head) + off);
         dst[p] = page_slot(P, seg, layer, head - layer * s.H, jh);
       }
     }
+  }
+  if (FROM_PAGES) {
+#pragma unroll
+    for (int p = 0; p < GATHER_PASSES; ++p)
+      if (dst[p] >= 0) {
+        kv[p] = load_stream16(P.k + src[p] + chunk * 8);
+        vv[p] = load_stream16(P.v + src[p] + chunk * 8);
+      }
   }
 #pragma unroll
   for (int p = 0; p < GATHER_PASSES; ++p) {
@@ -236,6 +253,10 @@ __global__ __launch_bounds__(GATHER_THREADS) void gather_paged_kernel(const SegT
 // 175 / 197 / 254 (799), 16 heads of 40007 101 / 108 / 137 (376), 32 heads 55 / 55 / 68 (158; with
 // part of the pool in the last-level cache 40 / 43 / 46), 64 heads 102 / 77 / 82, 96 heads of 30000
 // (50 %) 448 / 377 / 319, 128 heads 194 / 153 / 137 (211), 256 heads of 32768 708 / 588 / 527 (536).
+//
+// A head that keeps k rows writes its slots 0 .. k - 1 only.  Rows whose tokens lie behind those (late rows: of n
+// tokens, 1 - k/n of the list, and its end) are overwritten by nothing, so where there are enough of them they move
+// by a launch of their own that deals them out like a dense gather, once the early rows have been moved in order.
 constexpr int INPLACE_THREADS = 512;
 template <int LANES>
 struct Inplace {
@@ -261,12 +282,15 @@ __host__ __device__ __forceinline__ int shared_row_shift(const PagePool &P) {
 struct RowPages { int src, dst, src_slot, dst_slot; };
 
 // SHARED: K and V lie in one row of `pieces` 16-byte pieces from the lower of their addresses.
-template <int LANES, bool SHARED>
+// EARLY: only rows whose tokens lie below the head's row count, which are those that destinations can overwrite
+// and the first of the list; all others are left to gather_paged_kernel<true>.
+template <int LANES, bool SHARED, bool EARLY>
 __global__ __launch_bounds__(INPLACE_THREADS) void compact_inplace_kernel(
     const SegTable T, const PagePool P, int page_shift, int pieces, const int32_t *__restrict__ kept_idx,
     const int32_t *__restrict__ kept_cnt) {
   typedef Inplace<LANES> I;
   __shared__ long long src_l[3][I::RUN], dst_l[3][I::RUN];   // element offsets; -1: does not move
+  __shared__ int more_l[3];                                  // EARLY: the run has rows to move
   // blocks b, b + 8, b + 16, .. (one XCD, hence one L2) hold the slices of one head
   const int parts = SHARED ? (pieces + LANES - 1) / LANES : 2 * I::SLICES;
   const int part = (blockIdx.x >> 3) % parts, oct = (blockIdx.x >> 3) / parts;
@@ -302,7 +326,10 @@ __global__ __launch_bounds__(INPLACE_THREADS) void compact_inplace_kernel(
       const int jr = o * INPLACE_THREADS + tid;
       const long long j = inplace_row(run, I::RUN, jr);
       tok[o] = -1;
-      if (jr < I::RUN && j < rows) tok[o] = idx[j];
+      if (jr < I::RUN && j < rows) {
+        tok[o] = idx[j];
+        if (EARLY && inplace_late(tok[o], rows)) tok[o] = -1;
+      }
     }
   };
   auto split = [&](int j, int &lp, int &slot) {
@@ -323,7 +350,9 @@ __global__ __launch_bounds__(INPLACE_THREADS) void compact_inplace_kernel(
       }
     }
   };
-  auto put_moves = [&](int slot, const RowPages (&pg)[I::OWN]) {
+  // `more`: the first row of the run is one to look at, and so are all before it (ascending tokens)
+  auto put_moves = [&](int slot, const RowPages (&pg)[I::OWN], bool more) {
+    if (EARLY && tid == 0) more_l[slot] = more;
 #pragma unroll
     for (int o = 0; o < I::OWN; ++o) {
       const int jr = o * INPLACE_THREADS + tid;
@@ -360,41 +389,63 @@ __global__ __launch_bounds__(INPLACE_THREADS) void compact_inplace_kernel(
   const int runs = inplace_runs(rows, I::RUN);
   fetch_idx(0, tok);
   fetch_pages(0, tok, pg);
+  bool more = tok[0] >= 0;               // of the run whose pages pg holds (thread 0: its first row)
   fetch_idx(1, tok);
-  put_moves(0, pg);
+  put_moves(0, pg, more);
   fetch_pages(1, tok, pg);
+  more = tok[0] >= 0;
   fetch_idx(2, tok);
   __syncthreads();
   load_rows(0, a);
   // on entry of step r: the rows of run r are being read, pg holds run r + 1, tok run r + 2
   auto step = [&](int r, uint4 (&cur)[I::PASSES], uint4 (&next)[I::PASSES]) {
-    put_moves((r + 1) % 3, pg);
+    put_moves((r + 1) % 3, pg, more);
     // every wave waits for its own rows of run r before it meets the others (a barrier by itself
     // does not wait for loads): behind the barrier all of them have been read
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     fetch_pages(r + 2, tok, pg);
+    more = tok[0] >= 0;
     fetch_idx(r + 3, tok);
     load_rows((r + 1) % 3, next);
     store_rows(r % 3, cur);
+    return r + 1 < runs && (!EARLY || more_l[(r + 1) % 3]);        // uniform, behind the barrier
   };
   for (int r = 0; r < runs; r += 2) {
-    step(r, a, b);
-    if (r + 1 >= runs) break;                      // uniform
-    step(r + 1, b, a);
+    if (!step(r, a, b)) break;
+    if (!step(r + 1, b, a)) break;
   }
 }
 
-template <int LANES, bool SHARED = false>
+template <int LANES, bool SHARED, bool EARLY>
 static hipError_t launch_inplace(const SegTable &T, const PagePool &P, const int32_t *kept_idx,
-                                 const int32_t *kept_cnt, hipStream_t st, int pieces = 0) {
+                                 const int32_t *kept_cnt, hipStream_t st, int pieces) {
   const int parts = SHARED ? (pieces + LANES - 1) / LANES : 2 * Inplace<LANES>::SLICES;
   const long long nb = ((long long)T.nheads + 7) / 8 * 8 * parts;
   if (nb > 0x7fffffffll) return hipErrorInvalidValue;
   const int shift = (P.page_size & (P.page_size - 1)) == 0 ? __builtin_ctz((unsigned)P.page_size) : -1;
-  hipLaunchKernelGGL((compact_inplace_kernel<LANES, SHARED>), dim3((unsigned)nb), dim3(INPLACE_THREADS), 0, st, T, P,
+  hipLaunchKernelGGL((compact_inplace_kernel<LANES, SHARED, EARLY>), dim3((unsigned)nb), dim3(INPLACE_THREADS), 0, st, T, P,
                      shift, pieces, kept_idx, kept_cnt);
   return hipGetLastError();
+}
+
+// Whether a compaction in place is cut in two (see compact_inplace_kernel): by the rows of a head that are late if
+// the retained ones are spread evenly, k (1 - k / n).  The second launch costs 3 to 6 us and lets every compute
+// unit take part.  us in one / in two on MI355X, pages of 16: heads of 131072 tokens, 8 heads, 10 % retained 55 / 36, 30 %
+// 199 / 134, 50 % 393 / 283, 80 % 663 / 592; 24 heads, 30 % 373 / 257; heads of 65536, 8 of them, 10 % 28 / 22, 32 of
+// them 43 / 54, 30 % 200 / 158, 64 of them 89 / 94, 300 / 272, 128 of them 182 / 176, 534 / 519; 24 of 40000, 10 % 24 / 28, 30 %
+// 91 / 84; 16 of 24000 48 / 43; heads of 16384, 8 of them 18 / 23, 32 42 / 46, 64 55 / 74, 96 105 / 102; 80 %
+// retained, 8 of 32768 109 / 119, 16 of 40007 230 / 228, 96 of 30000 502 / 526.
+static bool inplace_in_two(const SegTable &T) {
+  long long late = 0, kept = 0, rows = 0;
+  for (int i = 0; i < T.nseg; ++i) {
+    const Seg &s = T.s[i];
+    late += s.head_count * ((long long)s.k_keep * (s.n - s.k_keep) / s.n);
+    kept += (long long)s.head_count * s.k_keep;
+    rows += (long long)s.head_count * s.n;
+  }
+  const int least = T.nheads <= 16 ? 4800 : T.nheads <= 64 ? 8192 : 3400;
+  return late >= (long long)least * T.nheads && 8 * kept <= 5 * rows;
 }
 
 hipError_t launch_gather_paged(const SegTable &T, const PagePool &P, const int32_t *kept_idx,
@@ -402,11 +453,14 @@ hipError_t launch_gather_paged(const SegTable &T, const PagePool &P, const int32
   if (T.nheads <= 0) return hipSuccess;
   if (in_place) {
     const int shift = shared_row_shift(P);
-    if (shift >= 0) return launch_inplace<16, true>(T, P, kept_idx, kept_cnt, st, (D + shift) / 8);
+    if (shift >= 0) return launch_inplace<16, true, false>(T, P, kept_idx, kept_cnt, st, (D + shift) / 8);
     // slices by the number of heads (see compact_inplace_kernel for the times on both sides)
-    if (T.nheads <= 16) return launch_inplace<4>(T, P, kept_idx, kept_cnt, st);
-    if (T.nheads <= 64) return launch_inplace<8>(T, P, kept_idx, kept_cnt, st);
-    return launch_inplace<16>(T, P, kept_idx, kept_cnt, st);
+    const bool two = inplace_in_two(T);
+    const auto launch = T.nheads <= 16   ? (two ? launch_inplace<4, false, true> : launch_inplace<4, false, false>)
+                        : T.nheads <= 64 ? (two ? launch_inplace<8, false, true> : launch_inplace<8, false, false>)
+                                         : (two ? launch_inplace<16, false, true> : launch_inplace<16, false, false>);
+    const hipError_t rc = launch(T, P, kept_idx, kept_cnt, st, 0);
+    if (rc != hipSuccess || !two) return rc;
   }
   long long nb = 0;
   if (T.layer_scope) {
@@ -418,8 +472,8 @@ hipError_t launch_gather_paged(const SegTable &T, const PagePool &P, const int32
   }
   if (nb <= 0) return hipSuccess;
   if (nb > 0x7fffffffll) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(gather_paged_kernel, dim3((unsigned)nb), dim3(GATHER_THREADS), 0, st, T, P, kept_idx,
-                     kept_cnt);
+  hipLaunchKernelGGL(in_place ? gather_paged_kernel<true> : gather_paged_kernel<false>, dim3((unsigned)nb),
+                     dim3(GATHER_THREADS), 0, st, T, P, kept_idx, kept_cnt);
   return hipGetLastError();
 }
 

@@ -980,6 +980,18 @@ def _paged_case(C, w, scope, page_size, in_place, seed):
     assert np.array_equal(got_v, v_ref), "paged V differs (scope %d, in_place %s)" % (scope, in_place)
 
 
+# early rows in order, late rows by a launch of their own: every slice width, late rows that begin in mid-run, layers
+# whose heads keep from few rows to nearly all, two requests of which one alone would move in one launch
+@pytest.mark.parametrize("L,H,n,ratio,scope", [(1, 2, 24001, 0.31, 0), (2, 3, 50007, 0.5, 1), (1, 17, 41000, 0.3, 0),
+                                               (1, 65, 16411, 0.33, 0)])
+def test_compact_in_place_in_two_launches(C, L, H, n, ratio, scope):
+    w = W.config1(DEV, L=L, H=H, n=n, ratio=ratio)
+    if L == 2:
+        w.requests.append(W.config1(DEV, L=L, H=H, n=3000, ratio=0.9).requests[0])
+        w.requests[0].k[:, 1] *= 0.01      # a head of small keys beside others: scores are relative to the head
+    _paged_case(C, w, scope, 16, True, 35)
+
+
 @pytest.mark.parametrize("in_place", [False, True])
 def test_compact_into_pages(C, in_place):
     _say("paged target, in_place=%s: head scope and layer scope, ragged batch, page sizes 16 and 7" % in_place)
