@@ -123,7 +123,7 @@ typedef struct compactor_params {
 /* stage indices for compactor_params_t.stage_events */
 #define COMPACTOR_STAGE_GRAM     0   /* partial Gram matrices K^T K (MFMA) */
 #define COMPACTOR_STAGE_REDUCE   1   /* fp64 sum of the partials */
-#define COMPACTOR_STAGE_SOLVE    2   /* sketch, Cholesky, W */
+#define COMPACTOR_STAGE_SOLVE    2   /* sketch, Cholesky, W (calls of few heads: the sketch; the rest is in the next) */
 #define COMPACTOR_STAGE_SCORE    3   /* o_i = ||W^T k_i||^2 (MFMA) */
 #define COMPACTOR_STAGE_BLEND    4   /* Eq. "scoring" (only with attn) */
 #define COMPACTOR_STAGE_SELECT   5   /* per-head top-k */

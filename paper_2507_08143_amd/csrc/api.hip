@@ -118,18 +118,27 @@ int score_tokens_for(const compactor_params_t *p, const SegTable &T, int cus) {
   // workgroup and gains 4 % from runs of 16384 tokens.
   const int cap = p->sketch_dim == 0 ? 16384 : SCORE_BURST;
   const int slots = 2 * cus;
-  // A call of few heads that gives a compute unit less than 1024 tokens is all latency: one workgroup per
-  // unit, but not below 256 tokens, where half the run changes nothing any more: staging W^T and adding the
-  // histograms weigh as much as the steps saved (128 against 256 tokens: 1.5 % less at 8 heads of 4096, the
-  // same at one of 2048).  Whole call on MI355X, us with runs of 128 / 256 / 512 / 768 / 1024 tokens: 8
-  // heads of 4096 tokens 53.8 / 54.6 / 56.6 / 59.2 / 60.9, 8192 63.1 / 62.7 / 62.9 / 64.8 / 67.8, 16384 86.6 / 78.4 / 76.3 / 78.8 / 79.6, 24000
-  // 113.8 / 101.5 / 93.6 / 92.8 / 94.2, 32768 141 / 118 / 107.4 / 108.2 / 106.8, one head of 2048 51.2 / 51.3 /
-  // 51.8 / 54.2 / 55.7; exact mode, 8 heads of 8192 80.0 / 79.8 / 82.1 / 86.5 / 90.3.  Beyond 1024 tokens a unit
-  // the search below takes over; compactor_score with what it chooses and with runs of 512 / 640 / 768: 8 heads of
-  // 33000 69.0, 68.7 / 64.3 / 66.2, 40007 70.6, 74.5 / 67.6 / 68.3, 50000 78.0, 83.0 / 83.4 / 83.2, 65000 87.9,
-  // 90.0 / 89.7 / 89.4 (up to 1300 tokens a unit two full rounds of about 640 would be 4 to 7 % faster).
   long long rows = 0;
   for (int i = 0; i < T.nseg; ++i) rows += (long long)T.s[i].n * T.s[i].head_count;
+  // Sketched mode, few heads: one workgroup per unit, which then factors its head itself (score_solves), as long as
+  // no run is much longer than the even share of a unit; not below 256 tokens, where half the run changes nothing any
+  // more.  compactor_score on MI355X, us with runs of 128 / 256 / 384 / 512 / 768 / 1024 tokens, k_s = 48: one head of 8192
+  // 30.2 / 31.4 / 32.8 / 33.4 / 35.8 / 38.0, 8 heads of 4096 32.3 / 32.7 / 33.8 / 34.5 / 36.6 / 38.4, 8192 37.9 / 36.3 / 36.6 /
+  // 37.5 / 39.5 / 41.1, 16384 48.1 / 45.0 / 47.3 / 42.3 / 44.7 / 46.4, 32768 63.4 / 60.2 / 62.5 / 55.7 / 57.7 / 53.4.  Against
+  // the search below, whose workgroups get W^T from a kernel of its own, with k_s = 16, 48 and 64: 8 heads of 40007 50.3 / 54.7,
+  // 60.0 / 65.0, 69.6 / 74.5, 65536 65.3 / 67.5, 76.0 / 79.1, 87.9 / 87.5, 100000 89.6 / 92.4, 99.3 / 102.3, 112.3 / 112.3,
+  // 32 heads of 30000 99.6 / 99.2, 111.0 / 110.7, 125.4 / 119.5.
+  if (p->sketch_dim > 0 && T.nheads <= cus) {
+    const int most = p->sketch_dim <= 48 ? SCORE_BURST : 1536;
+    const long long even = (rows + cus - 1) / cus;
+    int run = even > most ? most + 1 : (int)(even + SCORE_STEP - 1) / SCORE_STEP * SCORE_STEP;
+    if (run < 256) run = 256;
+    while (run <= most && total_blocks(T, run, SCORE_STEP, false) > cus) run += SCORE_STEP;
+    if (run <= most && (run == 256 || (run - 256ll) * cus <= rows)) return run;
+  }
+  // A call of few heads that gives a compute unit less than 1024 tokens is all latency: one workgroup per
+  // unit.  Whole call on MI355X, exact mode, us with runs of 128 / 256 / 512 / 768 / 1024 tokens, 8 heads of 8192
+  // 80.0 / 79.8 / 82.1 / 86.5 / 90.3.
   if (T.nheads <= cus && rows < 1024ll * cus) {
     const int even = (int)((rows + cus - 1) / cus + SCORE_STEP - 1) / SCORE_STEP * SCORE_STEP;
     return even < 256 ? 256 : even;
@@ -316,15 +325,19 @@ int enqueue_score(const compactor_params_t *p, const SegTable &T, const GroupByt
   MARK(m, COMPACTOR_STAGE_REDUCE + 1);       // the fp64 sum of the partials is part of the next kernel
   double *shares =
       gb.shares > 0 && ws_bytes >= gb.wanted() ? reinterpret_cast<double *>(ws + gb.off_shares()) : nullptr;
+  const int score_tokens = score_tokens_for(p, T, cus);
+  const SolvePlan plan = solve_plan(T, p->sketch_dim, rpw);
+  const bool in_score = shares != nullptr && score_solves(T, p->sketch_dim, score_tokens, cus);
   if (p->sketch_dim > 0) {
-    HIP_TRY(launch_sketch_solve(T, p->sketch_dim, rpw, solve_plan(T, p->sketch_dim, rpw), partials, shares,
-                                p->phi, p->ridge_rel, wt, status, zero, zero_ints, st));
+    HIP_TRY(launch_sketch_solve(T, p->sketch_dim, rpw, plan, partials, shares, p->phi, p->ridge_rel,
+                                in_score ? nullptr : wt, status, zero, zero_ints, st));
   } else {
     HIP_TRY(launch_exact_solve(T, rpw, partials, shares, p->ridge_rel, wt, status, zero, zero_ints, st));
   }
   MARK(m, COMPACTOR_STAGE_SOLVE + 1);
-  const int score_tokens = score_tokens_for(p, T, cus);
-  HIP_TRY(launch_score(T, p->sketch_dim, score_tokens, wt, scores, status, hist1, ostat, st));
+  const ScoreSolve solve{shares, plan.nshares, p->phi, p->ridge_rel};
+  HIP_TRY(launch_score(T, p->sketch_dim, score_tokens, wt, in_score ? &solve : nullptr, scores, status, hist1, ostat,
+                       st));
   MARK(m, COMPACTOR_STAGE_SCORE + 1);
   if (ostat != nullptr) {
     HIP_TRY(launch_blend(T, p->lambda_blend, score_tokens, scores, ostat, hist1, st));

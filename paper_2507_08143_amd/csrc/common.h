@@ -353,8 +353,10 @@ hipError_t launch_gram(const SegTable &T, int nwg, int tiles_per_wg, float *part
 // zero[0, zero_ints) is cleared on the way (selection histograms), if not null.
 // shares: plan.share_bytes of scratch, which lets many workgroups per head add the partials up (one
 // launch more), or null: one workgroup per head does it (the same bits).
+// wt null: the shares only, with the status words set to 0 (see launch_score).
 struct SolvePlan {
   int parts;             // the partials of a head are added in this many runs (sketched mode)
+  int nshares;           // shares of a head (sketched mode)
   size_t share_bytes;
 };
 SolvePlan solve_plan(const SegTable &T, int ks, int tiles_per_wg);
@@ -380,7 +382,16 @@ hipError_t launch_srht_phi(int ks, const uint8_t *signs, const int32_t *cols, fl
 // entry; hist1 may be null.  ostat, if not null, receives four doubles per workgroup of the launch
 // (for the blend): sum and sum of squares of its scores, and of the attention scores a of the same
 // tokens (less the head's first element), for heads whose request has attn.
-hipError_t launch_score(const SegTable &T, int ks, int tokens_per_wg, const uint16_t *wt,
+// solve, if not null: wt is not read, the workgroups factor their heads themselves from the shares of
+// launch_sketch_solve(.., wt = nullptr, ..), which has set the status words to 0; only where score_solves() holds.
+struct ScoreSolve {
+  const double *shares;
+  int nshares;           // per head
+  const float *phi;
+  float ridge_rel;
+};
+bool score_solves(const SegTable &T, int ks, int tokens_per_wg, int cus);
+hipError_t launch_score(const SegTable &T, int ks, int tokens_per_wg, const uint16_t *wt, const ScoreSolve *solve,
                         float *scores, int32_t *status, int *hist1, double *ostat, hipStream_t st);
 
 // s = z(a) + lambda z(o) in place over the scores of heads whose request has attn; their first

@@ -1,0 +1,415 @@
+// The factorisation of S = Phi^T G Phi + rho I, from the shares of S to the bf16 planes of W^T = L^{-1} Phi^T: for a
+// kernel of its own (solve.hip) and for score workgroups that factor their head themselves (score.hip).
+#pragma once
+
+#include <type_traits>
+
+#include "common.h"
+
+namespace cmp {
+
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ uint16_t bf16_rne(float x) {
+  uint32_t u = __float_as_uint(x);
+  if ((u & 0x7f800000u) == 0x7f800000u) return (uint16_t)(u >> 16);   // inf / nan: truncate
+  u += 0x7fffu + ((u >> 16) & 1u);
+  return (uint16_t)(u >> 16);
+}
+__device__ __forceinline__ float bf16_to_f32(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
+
+// A pivot below this fraction of its own (ridged) diagonal entry is below what the fp32-
+// accumulated Gram matrix resolves: the direction is dropped and the head flagged.
+constexpr double PIVOT_REL = 1.4901161193847656e-08;   // 2^-26
+
+// All lanes of a wave's 16-lane row get the value of lane K of that row.
+template <int K>
+__device__ __forceinline__ double bcast16(double x) {
+  constexpr int ROW_NEWBCAST = 0x150;
+  return __builtin_amdgcn_mov_dpp(x, ROW_NEWBCAST + K, 0xf, 0xf, true);
+}
+
+// Compile-time loop: f(integral_constant<int, B>) ... f(integral_constant<int, E - 1>).
+template <int B, int E, class F>
+__device__ __forceinline__ void static_for(F &&f) {
+  if constexpr (B < E) {
+    f(std::integral_constant<int, B>{});
+    static_for<B + 1, E>(f);
+  }
+}
+
+// Stops the compiler from moving the computation of x past this point.
+__device__ __forceinline__ void computed_here(double &x) { asm volatile("" : "+v"(x)); }
+
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Inverse of the Cholesky factor of a 16 x 16 diagonal block, by one wave.  Lane i of every
+// 16-lane row holds row i of the block (row[], the lanes above 15 repeat what lanes 0..15 do) and
+// the ridged diagonal entry d0 of its row; on return x[i] of lane j is X[i][j], X = L^{-1}.  A
+// pivot that is not above PIVOT_REL d0 is dropped (row and column of X zero, or NaN where the block
+// is not finite: such a head's scores have to come out as NaN); returns whether none was.
+// Bound: the dependent chain of 16 pivots and the 120 broadcasts; three panels take about 6 us
+// where an elimination through LDS and scalar registers, with its square root on the chain, took
+// 15.6 us (k_s = 48).  The elimination is the square-root free one (u_i the
+// column before scaling, t_i = u_i / d): what the next pivot waits for is a lane broadcast, a
+// reciprocal with two Newton steps, a product and an fma; the broadcast of u_{k+1} runs beside the
+// reciprocal and the square roots of all 16 pivots are taken at once at the end.  Broadcasts are
+// row_newbcast moves, so nothing passes through LDS or scalar registers.  The inverse takes the
+// same broadcasts in the same pass (lane j solves column j).
+__device__ __forceinline__ bool chol16_inverse(double (&row)[16], double d0, double (&x)[16]) {
+  const int l16 = threadIdx.x & 15;
+  bool all_ok = true;
+  double d_mine = 0.0;
+  bool ok_mine = false;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) x[i] = (i == l16) ? 1.0 : 0.0;
+  double u_prev = 0.0, t_prev = 0.0;               // column k - 1
+  const double least = PIVOT_REL * d0;
+  static_for<0, 16>([&](auto kc) {
+    constexpr int k = decltype(kc)::value;
+    const double d = bcast16<k>(row[k]);
+    double r = __builtin_amdgcn_rcp(d);
+    computed_here(r);
+    __builtin_amdgcn_sched_barrier(0);
+    const bool ok = d > bcast16<k>(least) && d < 1.0e300;      // false for NaN too
+    // what pivot k - 1 still owes the columns behind this one, in the shadow of the reciprocal
+    if constexpr (k > 0) {
+      static_for<k, 16>([&](auto jc) {
+        constexpr int j = decltype(jc)::value;
+        const double tj = bcast16<j>(t_prev);
+        if constexpr (j > k) row[j] = fma(-tj, u_prev, row[j]);
+        x[j] = fma(-tj, x[k - 1], x[j]);
+      });
+    }
+    r = fma(r, fma(-d, r, 1.0), r);
+    r = fma(r, fma(-d, r, 1.0), r);
+    if (!ok) r = 0.0;
+    all_ok &= ok;
+    if (l16 == k) {
+      d_mine = d;
+      ok_mine = ok;
+    }
+    u_prev = row[k];
+    t_prev = u_prev * r;                           // lane i: L[i][k] / L[k][k] for i > k
+    if constexpr (k < 15) row[k + 1] = fma(-bcast16<k + 1>(u_prev), t_prev, row[k + 1]);
+    // Keeps a pivot's updates with the pivot.  The compiler would otherwise collect the updates of
+    // x behind the last pivot (where x is stored) and hold all 120 broadcasts for them.
+    static_for<k, 16>([&](auto jc) { computed_here(x[decltype(jc)::value]); });
+    __builtin_amdgcn_sched_barrier(0);
+  });
+  const double rs = ok_mine ? rsqrt(d_mine) : 0.0;
+  static_for<0, 16>([&](auto ic) {
+    constexpr int i = decltype(ic)::value;
+    x[i] *= bcast16<i>(rs);
+  });
+  return all_ok;
+}
+
+// Steps 2 and 3 for a matrix of P panels, by NW waves.  Ss (16P rows of pitch 16P + 1 doubles) holds
+// S + rho I in its lower 16 x 16 blocks; on return L is below the diagonal blocks, the diagonal
+// blocks of X = L^{-1} are in Xd and the blocks of X below the diagonal, transposed, in the upper
+// blocks of Ss (element X[j][c], block of j below block of c, is at Ss[c][j]).
+// The serial chain is wave 0's: the diagonal block takes its last update and is eliminated.  In
+// its shadow the other waves apply what the previous panel owes the trailing matrix and X (Y_qc =
+// sum over r of L_qr X_rc grows in the place of X_qc) and hand on finished rows of X: row_done(p,
+// i, n) is called by n waves, i = 0 .. n - 1, when block row p of X is complete.  With three panels
+// that takes 1.2 us off the 13.8 us of one head, with eight (exact mode) 22 us off 52.
+// !INVERSE: X is not wanted, only L and the diagonal blocks of X; waves 1 .. NW - 1 call row_done(p) (a compile-time
+// p) when X_pp and the blocks of L below it are complete.
+template <int P, int NW, bool INVERSE, class F>
+__device__ __forceinline__ void factor_panels(double *Ss, double (*Xd)[16][17], const double *d0_s,
+                                              int *flag, F &&row_done) {
+  constexpr int SP = 16 * P + 1;
+  const int lane = threadIdx.x & 63, l16 = lane & 15, lq = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  // A_qr -= L_qp L_rp^T
+  auto trail = [&](int q, int r, int p) {
+    f64x4 acc;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) acc[v] = Ss[(16 * q + 4 * v + lq) * SP + 16 * r + l16];
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      const double a = -Ss[(16 * q + l16) * SP + 16 * p + 4 * ks + lq];
+      const double b = Ss[(16 * r + l16) * SP + 16 * p + 4 * ks + lq];
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) Ss[(16 * q + 4 * v + lq) * SP + 16 * r + l16] = acc[v];
+  };
+  // Y_qc += L_qp X_pc, c <= p
+  auto grow = [&](int q, int c, int p) {
+    double *y = &Ss[(16 * c + l16) * SP + 16 * q + lq];        // transposed: row 4v + lq, column l16
+    f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+    if (c < p) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) acc[v] = y[4 * v];
+    }
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      const double a = Ss[(16 * q + l16) * SP + 16 * p + 4 * ks + lq];
+      const double b = c == p ? Xd[p][4 * ks + lq][l16] : Ss[(16 * c + l16) * SP + 16 * p + 4 * ks + lq];
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) y[4 * v] = acc[v];
+  };
+  // wave 0: the diagonal block
+  auto pivots = [&](int p) {
+    if (p > 0) {
+      trail(p, p, p - 1);
+      wave_fence();
+    }
+    double row[16], x[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) row[j] = Ss[(16 * p + l16) * SP + 16 * p + j];
+    if (!chol16_inverse(row, d0_s[16 * p + l16], x) && lane == 0) *flag = COMPACTOR_STATUS_PIVOT;
+    if (lane < 16) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) Xd[p][i][lane] = x[i];
+    }
+  };
+  // the others meanwhile: what panel p - 1 owes, without block (p, p)
+  auto owed = [&](int p) {
+    int t = 1;
+    for (int q = p; q < P; ++q) {
+      for (int r = p; r <= q; ++r) {
+        if (r == p && q == p) continue;
+        if (t == wave) trail(q, r, p - 1);
+        t = t == NW - 1 ? 1 : t + 1;
+      }
+      for (int c = 0; INVERSE && c < p; ++c) {
+        if (t == wave) grow(q, c, p - 1);
+        t = t == NW - 1 ? 1 : t + 1;
+      }
+    }
+  };
+  // all: the panel below the diagonal block, L_qp = A_qp X_pp^T, and row p of X, X_pc = -X_pp Y_pc
+  auto panel = [&](int p) {
+    __syncthreads();
+    for (int i = wave; i < P; i += NW) {
+      if (i == p || (!INVERSE && i < p)) continue;
+      f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+      if (i > p) {
+        double *l = &Ss[(16 * i) * SP + 16 * p];
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(l[l16 * SP + 4 * ks + lq], Xd[p][l16][4 * ks + lq],
+                                                     acc, 0, 0, 0);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) l[(4 * v + lq) * SP + l16] = acc[v];
+      } else {
+        double *y = &Ss[(16 * i + l16) * SP + 16 * p + lq];
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-Xd[p][l16][4 * ks + lq], y[4 * ks], acc, 0, 0, 0);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) y[4 * v] = acc[v];
+      }
+    }
+    __syncthreads();
+  };
+  // Every wave passes the same barriers, wave 0 in code of its own: registers that row_done keeps from row to row are
+  // not held through the pivots.
+  if constexpr (INVERSE) {
+#pragma unroll 1
+    for (int p = 0; p < P; ++p) {
+      if (wave == 0) {
+        pivots(p);
+      } else if (p > 0) {
+        owed(p);
+        row_done(p - 1, wave - 1, NW - 1);
+      }
+      panel(p);
+    }
+    row_done(P - 1, wave, NW);
+  } else if (wave == 0) {
+#pragma unroll 1
+    for (int p = 0; p < P; ++p) {
+      pivots(p);
+      panel(p);
+    }
+  } else {
+    static_for<0, P>([&](auto pc) {
+      constexpr int p = decltype(pc)::value;
+      if constexpr (p > 0) {
+        owed(p);
+        row_done(std::integral_constant<int, p - 1>{});
+      }
+      panel(p);
+    });
+    row_done(std::integral_constant<int, P - 1>{});
+  }
+}
+
+constexpr int SHARE_BLOCKS = 5;
+template <int M>
+struct Share {
+  static constexpr int P = M / 16, TILES = P * (P + 1) / 2;     // lower 16 x 16 tiles of S
+  static constexpr int DOUBLES = TILES * 256;                   // thread e of tile t: t * 256 + e
+};
+
+// f(t, row, column) for the lower tiles t of S, with the element of each that this thread has.
+template <int M, class F>
+__device__ __forceinline__ void for_lower_tiles(F &&f) {
+  const int r = threadIdx.x >> 4, c = threadIdx.x & 15;
+  int t = 0;
+#pragma unroll
+  for (int a = 0; a < M / 16; ++a)
+#pragma unroll
+    for (int b = 0; b <= a; ++b, ++t) f(t, 16 * a + r, 16 * b + c);
+}
+
+// Phi on its way to LDS, in registers of a workgroup of 256.
+template <int M>
+struct PhiRegs {
+  static constexpr int N = D * M / 4 / 256;
+  typedef float quad __attribute__((ext_vector_type(4)));
+  quad v[N];
+  __device__ __forceinline__ void fetch(const float *__restrict__ phi) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = reinterpret_cast<const quad *>(phi)[threadIdx.x + 256 * i];
+  }
+};
+
+// The lower tiles of S from the shares of a head, added in their order, SHARE_BLOCKS at a time: fetch() requests the
+// first ones, add() adds them and all others; sum[t] is this thread's element of tile t.
+template <int M>
+struct ShareSum {
+  static constexpr int TILES = Share<M>::TILES;
+  double v[SHARE_BLOCKS][TILES];
+  __device__ __forceinline__ void fetch(const double *__restrict__ shares) {
+#pragma unroll
+    for (int u = 0; u < SHARE_BLOCKS; ++u)
+#pragma unroll
+      for (int t = 0; t < TILES; ++t) v[u][t] = shares[u * Share<M>::DOUBLES + t * 256 + threadIdx.x];
+  }
+  __device__ __forceinline__ void add(const double *__restrict__ shares, int nshares, double (&sum)[TILES]) const {
+#pragma unroll
+    for (int t = 0; t < TILES; ++t) sum[t] = 0.0;
+#pragma unroll
+    for (int u = 0; u < SHARE_BLOCKS; ++u)
+#pragma unroll
+      for (int t = 0; t < TILES; ++t) sum[t] += v[u][t];
+#pragma unroll 1
+    for (int s0 = SHARE_BLOCKS; s0 < nshares; s0 += SHARE_BLOCKS) {
+      double x[SHARE_BLOCKS][TILES];
+#pragma unroll
+      for (int u = 0; u < SHARE_BLOCKS; ++u)
+#pragma unroll
+        for (int t = 0; t < TILES; ++t) x[u][t] = shares[(long long)(s0 + u) * Share<M>::DOUBLES + t * 256 + threadIdx.x];
+#pragma unroll
+      for (int u = 0; u < SHARE_BLOCKS; ++u)
+#pragma unroll
+        for (int t = 0; t < TILES; ++t) sum[t] += x[u][t];
+    }
+  }
+};
+
+// Scratch of sketch_factor in LDS.
+template <int M>
+struct SketchFactor {
+  double Ss[M * (M + 1)];                          // S, then L (factor_panels)
+  double Xd[M / 16][16][17];
+  double d0[M];
+  static constexpr int PP = M + 4;                 // pitch of Phi: conflict-free reads
+  float PH[D * PP];
+  int flag;
+};
+
+// One workgroup of 256: steps 2 to 4 (see solve.hip) from S in lower tiles and Phi.  store(plane, row, channel, bf16)
+// gets the planes of W^T; F.flag is the status, complete for all threads after a barrier.
+// W^T = L^{-1} Phi^T by forward substitution, row blocks of 16: W_p = X_pp R_p with R_q = Phi_q^T - sum over r < q of
+// L_qr W_r, which wants no more of L^{-1} than its diagonal blocks X_pp.  Waves 1 to 3 do it in the shadow of the next
+// panel's pivots, each for its channels: a product's accumulators are the next one's operand as they are, so that
+// nothing of R or W passes through LDS, and behind the last pivot there are 12 products (k_s = 48; with rows of
+// L^{-1} times Phi^T there were 24: factorisation of 256 heads 18.5 us before, 16 now).
+template <int M, class STORE>
+__device__ __forceinline__ void sketch_factor(SketchFactor<M> &F, const double (&sum)[Share<M>::TILES],
+                                              const PhiRegs<M> &ph, float ridge_rel, STORE &&store) {
+  constexpr int P = M / 16, SP = M + 1, PP = SketchFactor<M>::PP;
+  constexpr int OWN = 3;                           // channel tiles of a wave: w - 1, w + 2, w + 5
+  const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lq = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  double *Ss = F.Ss;
+  if (tid == 0) F.flag = 0;
+  for_lower_tiles<M>([&](int t, int a, int b) {
+    Ss[a * SP + b] = sum[t];
+    if (a == b) F.d0[a] = sum[t];
+  });
+#pragma unroll
+  for (int i = 0; i < PhiRegs<M>::N; ++i) {
+    const int c4 = tid + 256 * i;
+    *reinterpret_cast<typename PhiRegs<M>::quad *>(&F.PH[c4 / (M / 4) * PP + c4 % (M / 4) * 4]) = ph.v[i];
+  }
+  __syncthreads();
+
+  // ridge: rho = ridge_rel * trace(S) / M (every wave sums in the same order); without one, 0 unless S is not finite
+  double tr = lane < M ? F.d0[lane] : 0.0;
+  if (ridge_rel != 0.f || __any(!(fabs(tr) < 1.0e300))) {
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) tr += __shfl_xor(tr, d);
+    const double rho = (double)ridge_rel * tr / (double)M;
+    __syncthreads();
+    if (tid < M) {
+      const double v = F.d0[tid] + rho;
+      Ss[tid * SP + tid] = v;
+      F.d0[tid] = v;
+    }
+    __syncthreads();
+  }
+
+  f64x4 R[OWN][P];
+#pragma unroll
+  for (int u = 0; u < OWN; ++u)
+#pragma unroll
+    for (int q = 0; q < P; ++q)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)                  // as a 16x16x4 product leaves it: row 4v + lq, channel l16
+        R[u][q][v] = wave > 0 ? (double)F.PH[(16 * min(wave - 1 + 3 * u, D / 16 - 1) + l16) * PP + 16 * q + 4 * v + lq] : 0.0;
+  const bool third = wave + 5 < D / 16;            // its third tile exists
+  factor_panels<P, 4, false>(Ss, F.Xd, F.d0, &F.flag, [&](auto pc) {
+    constexpr int pp = decltype(pc)::value;
+    double a[4];
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) a[ks] = F.Xd[pp][l16][4 * ks + lq];
+    f64x4 w[OWN];
+#pragma unroll
+    for (int u = 0; u < OWN; ++u) w[u] = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+      for (int u = 0; u < OWN; ++u)
+        if (u < 2 || third) w[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[ks], R[u][pp][ks], w[u], 0, 0, 0);
+    static_for<pp + 1, P>([&](auto qc) {
+      constexpr int q = decltype(qc)::value;
+      double l[4];
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) l[ks] = -Ss[(16 * q + l16) * SP + 16 * pp + 4 * ks + lq];
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+        for (int u = 0; u < OWN; ++u)
+          if (u < 2 || third) R[u][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(l[ks], w[u][ks], R[u][q], 0, 0, 0);
+    });
+#pragma unroll
+    for (int u = 0; u < OWN; ++u) {
+      if (u == 2 && !third) continue;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        float x = (float)w[u][v];
+#pragma unroll
+        for (int tt = 0; tt < W_TERMS; ++tt) {
+          const uint16_t b = bf16_rne(x);
+          x -= bf16_to_f32(b);
+          store(tt, 16 * pp + 4 * v + lq, 16 * (wave - 1 + 3 * u) + l16, b);
+        }
+      }
+    }
+  });
+}
+
+}  // namespace cmp

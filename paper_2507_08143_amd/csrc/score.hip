@@ -10,9 +10,7 @@
 // W^T reaches the MFMA as a sum of bf16 planes (hi + lo = 16 mantissa bits with two planes):
 // bf16 x bf16 products are exact in the fp32 accumulator, so the only rounding besides the
 // accumulation itself is the 2^-17 relative error of the split.
-#include <type_traits>
-
-#include "common.h"
+#include "factor.h"
 
 namespace cmp {
 
@@ -54,6 +52,14 @@ struct WLayout<128> {
   }
 };
 
+// The sum of a lane and the lane 32 away, in both: after swapping the upper half of one copy with the lower half of
+// the other the two results of a lane are its own value and the other's.
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ float halves_sum(float x) {
+  const u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
 __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
@@ -69,26 +75,42 @@ __device__ __forceinline__ void wave_lds_fence() {
 // SCORE_MAX_RUN tokens), so that what a workgroup pays once (staging W^T, the histogram, filling
 // and draining its load pipeline) is spread over more rows; the loads of the steps that follow a
 // burst are already in flight while it is written.
-template <int M>
+//
+// SOLVE: every workgroup factors its head itself, from the shares of S, and W^T goes straight into its LDS.  The
+// work is done many times over, but by compute units that would wait for it, and a launch and two passes of W^T
+// through memory are saved (see score_solves).
+template <int M, bool SOLVE>
 __global__ __launch_bounds__(256, 2) void score_kernel(
-    const SegTable T, const uint16_t *__restrict__ wt, float *__restrict__ scores,
+    const SegTable T, const uint16_t *__restrict__ wt, const ScoreSolve V, float *__restrict__ scores,
     int32_t *__restrict__ status, int *__restrict__ hist1, double *__restrict__ ostat) {
   constexpr int NSUB = 2, WTOK = 16 * NSUB, STEP = 4 * WTOK;     // tokens per wave / per WG step
   constexpr int NLD = WTOK * 16 / 64;                            // 16-B loads per lane per step
   typedef WLayout<M> WL;
   __shared__ __attribute__((aligned(16))) uint16_t wl[W_TERMS * WL::PLANE];
-  // a wave stages 16 tokens at a time (its 32 tokens of a step in two halves); measured, a third
-  // workgroup per CU does not pay, the smaller staging buffer does on the long-context shapes
-  __shared__ __attribute__((aligned(16))) uint16_t kl[4][16 * WPITCH];
-  // first radix digit of the selection, tallied on the way out: two 16-bit counters per word
-  __shared__ __attribute__((aligned(16))) unsigned hl[HIST1_BINS / 2];
-  // The scores collect here and leave in bursts: 4-byte stores trickling out between the
-  // streaming reads cost 12 % of the kernel's time.
   constexpr int BURST = WL::BURST, BSTEPS = BURST / STEP;
   static_assert((BURST & (BURST - 1)) == 0 && BSTEPS % 2 == 0, "bursts end on even steps");
-  __shared__ __attribute__((aligned(16))) float sc_l[BURST];
+  struct Stream {
+    // a wave stages 16 tokens at a time (its 32 tokens of a step in two halves); measured, a third
+    // workgroup per CU does not pay, the smaller staging buffer does on the long-context shapes
+    uint16_t kl[4][16 * WPITCH];
+    // first radix digit of the selection, tallied on the way out: two 16-bit counters per word
+    unsigned hl[HIST1_BINS / 2];
+    // The scores collect here and leave in bursts: 4-byte stores trickling out between the
+    // streaming reads cost 12 % of the kernel's time.
+    float sc_l[BURST];
+  };
+  union Lds {                            // the factorisation is over when the first key is staged
+    Stream s;
+    SketchFactor<SOLVE ? M : 16> f;
+  };
+  __shared__ __attribute__((aligned(16))) Lds lds;
+  auto &kl = lds.s.kl;
+  auto &hl = lds.s.hl;
+  auto &sc_l = lds.s.sc_l;
   __shared__ double red[4][4];
 
+  PhiRegs<SOLVE ? M : 16> ph;
+  if constexpr (SOLVE) ph.fetch(V.phi);
   // Where this workgroup works.  Every wave does this scalar work before its first load can
   // leave, so the per-segment numbers come precomputed in the table (index_score_blocks) and
   // one division remains.
@@ -135,6 +157,14 @@ __global__ __launch_bounds__(256, 2) void score_kernel(
     }
   };
 
+  // the shares of S are wanted first, and loads arrive in order
+  ShareSum<SOLVE ? M : 16> ss;
+  const double *shares = nullptr;
+  if constexpr (SOLVE) {
+    shares = V.shares + (long long)w.lhead * V.nshares * Share<M>::DOUBLES;
+    ss.fetch(shares);
+    __builtin_amdgcn_sched_barrier(0);
+  }
   uint4 stA[NLD], stB[NLD];
   load_step(0, stA);
   load_step(1, stB);
@@ -143,9 +173,18 @@ __global__ __launch_bounds__(256, 2) void score_kernel(
   // once W^T is in LDS: a workgroup starts with three steps in flight
   constexpr int WN = (W_TERMS * WL::CHUNKS + 255) / 256;
   uint4 wreg[WN];
+  if constexpr (SOLVE) {
+    double sum[Share<M>::TILES];
+    ss.add(shares, V.nshares, sum);
+    sketch_factor<M>(lds.f, sum, ph, V.ridge_rel,
+                     [&](int t, int row, int ch, uint16_t v) { wl[t * WL::PLANE + WL::row(row) + ch] = v; });
+    __syncthreads();
+    if (w.tile == 0 && tid == 0 && lds.f.flag) atomicOr(&status[s.ghead0 + w.head], lds.f.flag);
+    __syncthreads();
+  }
   const uint16_t *wh = wt + (size_t)w.lhead * (W_TERMS * M * D);
 #pragma unroll
-  for (int i = 0; i < WN; ++i) {
+  for (int i = 0; i < (SOLVE ? 0 : WN); ++i) {
     const int cidx = tid + 256 * i;
     wreg[i] = make_uint4(0, 0, 0, 0);
     if (cidx < W_TERMS * WL::CHUNKS) {
@@ -224,11 +263,10 @@ __global__ __launch_bounds__(256, 2) void score_kernel(
     for (int p = 0; p < NS; ++p) {
       // lanes (t16, g = 0..3) hold the four quarter-sums of token t16 of both sub-tiles; after
       // the exchange lanes with g < 2 hold the full sum of sub-tile g
-      float x0 = sums[p][0] + __shfl_xor(sums[p][0], 32);
-      float x1 = sums[p][1] + __shfl_xor(sums[p][1], 32);
-      const bool up = g & 1;
-      float x = up ? x1 : x0;
-      x += __shfl_xor(up ? x0 : x1, 16);
+      // (row swaps: two shuffles, round trips through LDS, took 0.2 us a step)
+      const float x0 = halves_sum(sums[p][0]), x1 = halves_sum(sums[p][1]);
+      const u32x2 r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x0), __float_as_uint(x1), false, false);
+      const float x = __uint_as_float(r[0]) + __uint_as_float(r[1]);
       const int tok = tok_begin + (it + p) * STEP + wave * WTOK + (lane & 31);   // 16*(g&1) + t16
       if (g < 2 && tok < tok_end) {
         sc_l[(tok - tok_begin) & (BURST - 1)] = x;
@@ -291,7 +329,7 @@ __global__ __launch_bounds__(256, 2) void score_kernel(
   redistribute(stA);            // waits for the first step of keys only
   load_step(2, stA);
 #pragma unroll
-  for (int i = 0; i < WN; ++i) {
+  for (int i = 0; i < (SOLVE ? 0 : WN); ++i) {
     const int cidx = tid + 256 * i;
     if (cidx < W_TERMS * WL::CHUNKS) {
       const int t = cidx / WL::CHUNKS;
@@ -365,29 +403,38 @@ __global__ __launch_bounds__(256, 2) void score_kernel(
   }
 }
 
-template <int M>
-static hipError_t launch_m(const SegTable &T, int tokens_per_wg, const uint16_t *wt,
+// Whether the score workgroups of a launch factor their heads themselves: where each has a compute unit of its own.
+// The pivots of two on a unit, and the shares that all of them read, take longer than what is saved (8 heads of
+// 131072 tokens in 512 workgroups: 36 us before the first score, against 16 for the kernel that does it once).  With 64
+// sketch rows up to runs of 1536 tokens: 32 heads of 30000, 256 workgroups, 125 against 119 us.
+bool score_solves(const SegTable &T, int ks, int tokens_per_wg, int cus) {
+  if (ks == 0 || (ks > 48 && tokens_per_wg > 1536)) return false;
+  return total_blocks(T, tokens_per_wg, SCORE_STEP, false) <= cus;
+}
+
+template <int M, bool SOLVE>
+static hipError_t launch_m(const SegTable &T, int tokens_per_wg, const uint16_t *wt, const ScoreSolve &V,
                            float *scores, int32_t *status, int *hist1, double *ostat,
                            hipStream_t st) {
   SegTable Ti = T;
   const long long nb = index_score_blocks(Ti, tokens_per_wg);
   if (nb <= 0) return hipSuccess;
   if (nb > 0x7fffffffll) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((score_kernel<M>), dim3((unsigned)nb), dim3(256), 0, st, Ti, wt, scores, status,
+  hipLaunchKernelGGL((score_kernel<M, SOLVE>), dim3((unsigned)nb), dim3(256), 0, st, Ti, wt, V, scores, status,
                      hist1, ostat);
   return hipGetLastError();
 }
 
-hipError_t launch_score(const SegTable &T, int ks, int tokens_per_wg, const uint16_t *wt,
+hipError_t launch_score(const SegTable &T, int ks, int tokens_per_wg, const uint16_t *wt, const ScoreSolve *solve,
                         float *scores, int32_t *status, int *hist1, double *ostat, hipStream_t st) {
-  switch (ks) {
-    case 16: return launch_m<16>(T, tokens_per_wg, wt, scores, status, hist1, ostat, st);
-    case 32: return launch_m<32>(T, tokens_per_wg, wt, scores, status, hist1, ostat, st);
-    case 48: return launch_m<48>(T, tokens_per_wg, wt, scores, status, hist1, ostat, st);
-    case 64: return launch_m<64>(T, tokens_per_wg, wt, scores, status, hist1, ostat, st);
-    case 0:  return launch_m<128>(T, tokens_per_wg, wt, scores, status, hist1, ostat, st);
-    default: return hipErrorInvalidValue;
-  }
+  const ScoreSolve V = solve ? *solve : ScoreSolve{nullptr, 0, nullptr, 0.f};
+  const auto launch = ks == 16   ? (solve ? launch_m<16, true> : launch_m<16, false>)
+                      : ks == 32 ? (solve ? launch_m<32, true> : launch_m<32, false>)
+                      : ks == 48 ? (solve ? launch_m<48, true> : launch_m<48, false>)
+                      : ks == 64 ? (solve ? launch_m<64, true> : launch_m<64, false>)
+                                 : launch_m<128, false>;
+  if (!(ks == 16 || ks == 32 || ks == 48 || ks == 64 || (ks == 0 && !solve))) return hipErrorInvalidValue;
+  return launch(T, tokens_per_wg, wt, V, scores, status, hist1, ostat, st);
 }
 
 }  // namespace cmp

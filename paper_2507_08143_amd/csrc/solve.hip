@@ -7,13 +7,9 @@
 // so that the score of a token is o_i = || W^T k_i ||^2 = k^_i^T S^{-1} k^_i, which equals
 // diag(U~ U~^T) of Algorithm 1 lines 5-6 when rho = 0.  All arithmetic here is fp64; W^T leaves
 // as a sum of bf16 planes for the MFMA score pass.
-#include <type_traits>
-
-#include "common.h"
+#include "factor.h"
 
 namespace cmp {
-
-typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ Where locate_head(const SegTable &T, int lhead) {
   Where w{0, 0, lhead, 0, 0};
@@ -28,105 +24,6 @@ __device__ __forceinline__ Where locate_head(const SegTable &T, int lhead) {
   return w;
 }
 
-__device__ __forceinline__ uint16_t bf16_rne(float x) {
-  uint32_t u = __float_as_uint(x);
-  if ((u & 0x7f800000u) == 0x7f800000u) return (uint16_t)(u >> 16);   // inf / nan: truncate
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
-}
-__device__ __forceinline__ float bf16_to_f32(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
-
-// A pivot below this fraction of its own (ridged) diagonal entry is below what the fp32-
-// accumulated Gram matrix resolves: the direction is dropped and the head flagged.
-constexpr double PIVOT_REL = 1.4901161193847656e-08;   // 2^-26
-
-// All lanes of a wave's 16-lane row get the value of lane K of that row.
-template <int K>
-__device__ __forceinline__ double bcast16(double x) {
-  constexpr int ROW_NEWBCAST = 0x150;
-  return __builtin_amdgcn_mov_dpp(x, ROW_NEWBCAST + K, 0xf, 0xf, true);
-}
-
-// Compile-time loop: f(integral_constant<int, B>) ... f(integral_constant<int, E - 1>).
-template <int B, int E, class F>
-__device__ __forceinline__ void static_for(F &&f) {
-  if constexpr (B < E) {
-    f(std::integral_constant<int, B>{});
-    static_for<B + 1, E>(f);
-  }
-}
-
-// Stops the compiler from moving the computation of x past this point.
-__device__ __forceinline__ void computed_here(double &x) { asm volatile("" : "+v"(x)); }
-
-__device__ __forceinline__ void wave_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// Inverse of the Cholesky factor of a 16 x 16 diagonal block, by one wave.  Lane i of every
-// 16-lane row holds row i of the block (row[], the lanes above 15 repeat what lanes 0..15 do) and
-// the ridged diagonal entry d0 of its row; on return x[i] of lane j is X[i][j], X = L^{-1}.  A
-// pivot that is not above PIVOT_REL d0 is dropped (row and column of X zero, or NaN where the block
-// is not finite: such a head's scores have to come out as NaN); returns whether none was.
-// Bound: the dependent chain of 16 pivots and the 120 broadcasts; three panels take about 6 us
-// where an elimination through LDS and scalar registers, with its square root on the chain, took
-// 15.6 us (k_s = 48).  The elimination is the square-root free one (u_i the
-// column before scaling, t_i = u_i / d): what the next pivot waits for is a lane broadcast, a
-// reciprocal with two Newton steps, a product and an fma; the broadcast of u_{k+1} runs beside the
-// reciprocal and the square roots of all 16 pivots are taken at once at the end.  Broadcasts are
-// row_newbcast moves, so nothing passes through LDS or scalar registers.  The inverse takes the
-// same broadcasts in the same pass (lane j solves column j).
-__device__ __forceinline__ bool chol16_inverse(double (&row)[16], double d0, double (&x)[16]) {
-  const int l16 = threadIdx.x & 15;
-  bool all_ok = true;
-  double d_mine = 0.0;
-  bool ok_mine = false;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) x[i] = (i == l16) ? 1.0 : 0.0;
-  double u_prev = 0.0, t_prev = 0.0;               // column k - 1
-  const double least = PIVOT_REL * d0;
-  static_for<0, 16>([&](auto kc) {
-    constexpr int k = decltype(kc)::value;
-    const double d = bcast16<k>(row[k]);
-    double r = __builtin_amdgcn_rcp(d);
-    computed_here(r);
-    __builtin_amdgcn_sched_barrier(0);
-    const bool ok = d > bcast16<k>(least) && d < 1.0e300;      // false for NaN too
-    // what pivot k - 1 still owes the columns behind this one, in the shadow of the reciprocal
-    if constexpr (k > 0) {
-      static_for<k, 16>([&](auto jc) {
-        constexpr int j = decltype(jc)::value;
-        const double tj = bcast16<j>(t_prev);
-        if constexpr (j > k) row[j] = fma(-tj, u_prev, row[j]);
-        x[j] = fma(-tj, x[k - 1], x[j]);
-      });
-    }
-    r = fma(r, fma(-d, r, 1.0), r);
-    r = fma(r, fma(-d, r, 1.0), r);
-    if (!ok) r = 0.0;
-    all_ok &= ok;
-    if (l16 == k) {
-      d_mine = d;
-      ok_mine = ok;
-    }
-    u_prev = row[k];
-    t_prev = u_prev * r;                           // lane i: L[i][k] / L[k][k] for i > k
-    if constexpr (k < 15) row[k + 1] = fma(-bcast16<k + 1>(u_prev), t_prev, row[k + 1]);
-    // Keeps a pivot's updates with the pivot.  The compiler would otherwise collect the updates of
-    // x behind the last pivot (where x is stored) and hold all 120 broadcasts for them.
-    static_for<k, 16>([&](auto jc) { computed_here(x[decltype(jc)::value]); });
-    __builtin_amdgcn_sched_barrier(0);
-  });
-  const double rs = ok_mine ? rsqrt(d_mine) : 0.0;
-  static_for<0, 16>([&](auto ic) {
-    constexpr int i = decltype(ic)::value;
-    x[i] *= bcast16<i>(rs);
-  });
-  return all_ok;
-}
-
 // ---- sketched mode: partial Gram blocks -> S -> L -> L^{-1} -> W^T ------------------------------
 // Every O(n^3)-ish piece runs on the fp64 matrix cores (16x16x4 MFMA: A[i][k] in lane (i = l & 15,
 // k = l >> 4), B[k][j] in lane (j = l & 15, k = l >> 4), register v of lane l of the result is
@@ -135,8 +32,9 @@ __device__ __forceinline__ bool chol16_inverse(double (&row)[16], double d0, dou
 //   2. blocked right-looking Cholesky of S + rho I with 16-wide panels: wave 0 inverts the factor
 //      of the diagonal block in registers (the only serial part, 16 pivots), the panel below is
 //      L_qp = A_qp X_pp^T and the trailing blocks get A_qr -= L_qp L_rp^T
-//   3. X = L^{-1} block by block (X_qp = -X_qq sum_r L_qr X_rp), one wave per block column
-//   4. W^T = X Phi^T, split into bf16 planes
+//   3. W^T = L^{-1} Phi^T by forward substitution (sketch_factor; exact mode: X = L^{-1} itself, block by block)
+//   4. W^T split into bf16 planes
+// Steps 2 to 4 stand in factor.h.
 //
 // Step 1 is linear in the blocks and in the partials of a head, so it is cut into shares: share
 // (r, w) is the contribution of stored blocks 2w and 2w + 1 of the r-th part of the head's
@@ -145,116 +43,6 @@ __device__ __forceinline__ bool chol16_inverse(double (&row)[16], double d0, dou
 // computes them: with room in the workspace they are computed by workgroups of their own
 // (sketch_share_kernel) and added by the factorisation, otherwise one workgroup per head computes
 // them one after the other.  Both give the same bits.
-// Steps 2 and 3 for a matrix of P panels, by NW waves.  Ss (16P rows of pitch 16P + 1 doubles) holds
-// S + rho I in its lower 16 x 16 blocks; on return L is below the diagonal blocks, the diagonal
-// blocks of X = L^{-1} are in Xd and the blocks of X below the diagonal, transposed, in the upper
-// blocks of Ss (element X[j][c], block of j below block of c, is at Ss[c][j]).
-// The serial chain is wave 0's: the diagonal block takes its last update and is eliminated.  In
-// its shadow the other waves apply what the previous panel owes the trailing matrix and X (Y_qc =
-// sum over r of L_qr X_rc grows in the place of X_qc) and hand on finished rows of X: row_done(p,
-// i, n) is called by n waves, i = 0 .. n - 1, when block row p of X is complete.  With three panels
-// that takes 1.2 us off the 13.8 us of one head, with eight (exact mode) 22 us off 52.
-template <int P, int NW, class F>
-__device__ __forceinline__ void factor_panels(double *Ss, double (*Xd)[16][17], const double *d0_s,
-                                              int *flag, F &&row_done) {
-  constexpr int SP = 16 * P + 1;
-  const int lane = threadIdx.x & 63, l16 = lane & 15, lq = lane >> 4;
-  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  // A_qr -= L_qp L_rp^T
-  auto trail = [&](int q, int r, int p) {
-    f64x4 acc;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) acc[v] = Ss[(16 * q + 4 * v + lq) * SP + 16 * r + l16];
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      const double a = -Ss[(16 * q + l16) * SP + 16 * p + 4 * ks + lq];
-      const double b = Ss[(16 * r + l16) * SP + 16 * p + 4 * ks + lq];
-      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
-    }
-#pragma unroll
-    for (int v = 0; v < 4; ++v) Ss[(16 * q + 4 * v + lq) * SP + 16 * r + l16] = acc[v];
-  };
-  // Y_qc += L_qp X_pc, c <= p
-  auto grow = [&](int q, int c, int p) {
-    double *y = &Ss[(16 * c + l16) * SP + 16 * q + lq];        // transposed: row 4v + lq, column l16
-    f64x4 acc = {0.0, 0.0, 0.0, 0.0};
-    if (c < p) {
-#pragma unroll
-      for (int v = 0; v < 4; ++v) acc[v] = y[4 * v];
-    }
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      const double a = Ss[(16 * q + l16) * SP + 16 * p + 4 * ks + lq];
-      const double b = c == p ? Xd[p][4 * ks + lq][l16] : Ss[(16 * c + l16) * SP + 16 * p + 4 * ks + lq];
-      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
-    }
-#pragma unroll
-    for (int v = 0; v < 4; ++v) y[4 * v] = acc[v];
-  };
-#pragma unroll 1
-  for (int p = 0; p < P; ++p) {
-    if (wave == 0) {
-      if (p > 0) {
-        trail(p, p, p - 1);
-        wave_fence();
-      }
-      double row[16], x[16];
-#pragma unroll
-      for (int j = 0; j < 16; ++j) row[j] = Ss[(16 * p + l16) * SP + 16 * p + j];
-      if (!chol16_inverse(row, d0_s[16 * p + l16], x) && lane == 0) *flag = COMPACTOR_STATUS_PIVOT;
-      if (lane < 16) {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) Xd[p][i][lane] = x[i];
-      }
-    } else if (p > 0) {
-      int t = 1;
-      for (int q = p; q < P; ++q) {
-        for (int r = p; r <= q; ++r) {
-          if (r == p && q == p) continue;                       // wave 0's
-          if (t == wave) trail(q, r, p - 1);
-          t = t == NW - 1 ? 1 : t + 1;
-        }
-        for (int c = 0; c < p; ++c) {
-          if (t == wave) grow(q, c, p - 1);
-          t = t == NW - 1 ? 1 : t + 1;
-        }
-      }
-      row_done(p - 1, wave - 1, NW - 1);
-    }
-    __syncthreads();
-    // the panel below the diagonal block, L_qp = A_qp X_pp^T, and row p of X, X_pc = -X_pp Y_pc
-    for (int i = wave; i < P; i += NW) {
-      if (i == p) continue;
-      f64x4 acc = {0.0, 0.0, 0.0, 0.0};
-      if (i > p) {
-        double *l = &Ss[(16 * i) * SP + 16 * p];
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks)
-          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(l[l16 * SP + 4 * ks + lq], Xd[p][l16][4 * ks + lq],
-                                                     acc, 0, 0, 0);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) l[(4 * v + lq) * SP + l16] = acc[v];
-      } else {
-        double *y = &Ss[(16 * i + l16) * SP + 16 * p + lq];
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks)
-          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-Xd[p][l16][4 * ks + lq], y[4 * ks], acc, 0, 0, 0);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) y[4 * v] = acc[v];
-      }
-    }
-    __syncthreads();
-  }
-  row_done(P - 1, wave, NW);
-}
-
-constexpr int SHARE_BLOCKS = 5;
-template <int M>
-struct Share {
-  static constexpr int P = M / 16, TILES = P * (P + 1) / 2;     // lower 16 x 16 tiles of S
-  static constexpr int DOUBLES = TILES * 256;                   // thread e of tile t: t * 256 + e
-};
-
 // The stored upper block number b is block (I, J) of G.
 __device__ __forceinline__ void upper_block_pos(int b, int &I, int &J) {
   I = (b >= 4) + (b >= 7) + (b >= 9);
@@ -368,17 +156,6 @@ __device__ __forceinline__ void sketch_share(const float *__restrict__ src, int 
   }
 }
 
-// f(t, row, column) for the lower tiles t of S, with the element of each that this thread has.
-template <int M, class F>
-__device__ __forceinline__ void for_lower_tiles(F &&f) {
-  const int r = threadIdx.x >> 4, c = threadIdx.x & 15;
-  int t = 0;
-#pragma unroll
-  for (int a = 0; a < M / 16; ++a)
-#pragma unroll
-    for (int b = 0; b <= a; ++b, ++t) f(t, 16 * a + r, 16 * b + c);
-}
-
 // Part r of `parts` of a head's nsplit partials.
 __device__ __forceinline__ void split_part(int nsplit, int parts, int r, int &first, int &count) {
   const int per = (nsplit + parts - 1) / parts;
@@ -393,12 +170,16 @@ __device__ __forceinline__ void split_part(int nsplit, int parts, int r, int &fi
 template <int M>
 __global__ __launch_bounds__(256, 2) void sketch_share_kernel(
     const SegTable T, int tiles_per_wg, int parts, const float *__restrict__ partials,
-    const float *__restrict__ phi, double *__restrict__ shares, int *__restrict__ zero,
-    long long zero_ints) {
+    const float *__restrict__ phi, double *__restrict__ shares, int32_t *__restrict__ status,
+    int *__restrict__ zero, long long zero_ints) {
   constexpr int SP = M + 1;
   __shared__ double ba[M * SP], bb[M * SP];
   const int unit = blockIdx.x / SHARE_BLOCKS, w = blockIdx.x - unit * SHARE_BLOCKS;
   const int lhead = unit / parts, r = unit - lhead * parts;
+  if (status != nullptr && r == 0 && w == 0 && threadIdx.x == 0) {
+    const Where at = locate_head(T, lhead);
+    status[T.s[at.seg].ghead0 + at.head] = 0;
+  }
   int nsplit, first, count;
   const long long pb = partial_base(T, lhead, tiles_per_wg, nsplit);
   split_part(nsplit, parts, r, first, count);
@@ -411,12 +192,6 @@ __global__ __launch_bounds__(256, 2) void sketch_share_kernel(
   });
 }
 
-template <int N>
-__device__ __forceinline__ void fetch_phi(const float *__restrict__ phi, float4 (&r)[N]) {
-#pragma unroll
-  for (int i = 0; i < N; ++i) r[i] = reinterpret_cast<const float4 *>(phi)[threadIdx.x + 256 * i];
-}
-
 // One workgroup (4 waves) per head, steps 2 to 4; step 1 from the shares (partials and zero are not used
 // then: the share kernel has cleared it), or from the partials.
 template <int M, bool SHARES>
@@ -425,23 +200,20 @@ __global__ __launch_bounds__(256, 2) void sketch_solve_kernel(
     const double *__restrict__ shares, const float *__restrict__ phi, float ridge_rel,
     uint16_t *__restrict__ wt, int32_t *__restrict__ status, int *__restrict__ zero,
     long long zero_ints) {
-  constexpr int P = M / 16, SP = M + 1, TILES = Share<M>::TILES;
-  __shared__ double Ss[M * SP];        // S, then L and X = L^{-1} (factor_panels)
-  __shared__ double Xd[P][16][17];
-  // Phi, rows of pitch M + 4 (conflict-free operand reads); before that the second half of a share
-  constexpr int PP = M + 4, BB = D * PP / 2 > M * SP ? D * PP / 2 : M * SP;
-  __shared__ __attribute__((aligned(16))) double bb[SHARES ? D * PP / 2 : BB];
-  float *PH = reinterpret_cast<float *>(bb);
-  __shared__ double d0_s[M];
-  __shared__ int flag_s;
+  constexpr int SP = M + 1, TILES = Share<M>::TILES;
+  // before the factorisation, the two halves of a share
+  union Lds {
+    SketchFactor<M> f;
+    double halves[2][SHARES ? 1 : M * SP];
+  };
+  __shared__ __attribute__((aligned(16))) Lds lds;
+  SketchFactor<M> &F = lds.f;
 
   const int lhead = blockIdx.x;
-  const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lq = lane >> 4;
-  if (tid == 0) flag_s = 0;
+  const int tid = threadIdx.x;
 
-  constexpr int PHN = D * M / 4 / 256;
-  float4 ph_reg[PHN];                              // Phi on its way to LDS
-  if constexpr (SHARES) fetch_phi<PHN>(phi, ph_reg);
+  PhiRegs<M> ph;
+  if constexpr (SHARES) ph.fetch(phi);
 
   // ---- 1. S = Phi^T G Phi ----
   double sum[TILES];
@@ -449,19 +221,12 @@ __global__ __launch_bounds__(256, 2) void sketch_solve_kernel(
   for (int t = 0; t < TILES; ++t) sum[t] = 0.0;
   const int nshares = parts * SHARE_BLOCKS;
   if constexpr (SHARES) {
-    const double *in = shares + (long long)lhead * nshares * Share<M>::DOUBLES + tid;
-    for (int s0 = 0; s0 < nshares; s0 += SHARE_BLOCKS) {
-      double v[SHARE_BLOCKS][TILES];
-#pragma unroll
-      for (int u = 0; u < SHARE_BLOCKS; ++u)
-#pragma unroll
-        for (int t = 0; t < TILES; ++t) v[u][t] = in[(long long)(s0 + u) * Share<M>::DOUBLES + t * 256];
-#pragma unroll
-      for (int u = 0; u < SHARE_BLOCKS; ++u)
-#pragma unroll
-        for (int t = 0; t < TILES; ++t) sum[t] += v[u][t];
-    }
+    const double *in = shares + (long long)lhead * nshares * Share<M>::DOUBLES;
+    ShareSum<M> ss;
+    ss.fetch(in);
+    ss.add(in, nshares, sum);
   } else {
+    double *ba = lds.halves[0], *bb = lds.halves[1];
     int nsplit;
     const long long pb = partial_base(T, lhead, tiles_per_wg, nsplit);
 #pragma unroll 1
@@ -469,83 +234,22 @@ __global__ __launch_bounds__(256, 2) void sketch_solve_kernel(
       const int r = s / SHARE_BLOCKS, w = s - r * SHARE_BLOCKS;
       int first, count;
       split_part(nsplit, parts, r, first, count);
-      sketch_share<M>(partials + (pb + first) * GRAM_PARTIAL_FLOATS, count, w, phi, Ss, bb);
+      sketch_share<M>(partials + (pb + first) * GRAM_PARTIAL_FLOATS, count, w, phi, ba, bb);
       __syncthreads();
       for_lower_tiles<M>([&](int t, int a, int b) {
-        sum[t] += (Ss[a * SP + b] + bb[a * SP + b]) + (Ss[b * SP + a] + bb[b * SP + a]);
+        sum[t] += (ba[a * SP + b] + bb[a * SP + b]) + (ba[b * SP + a] + bb[b * SP + a]);
       });
       __syncthreads();
     }
-    fetch_phi<PHN>(phi, ph_reg);
+    ph.fetch(phi);
     zero_slice(zero, zero_ints);
   }
-  for_lower_tiles<M>([&](int t, int a, int b) { Ss[a * SP + b] = sum[t]; });
-#pragma unroll
-  for (int i = 0; i < PHN; ++i) {
-    const int c4 = tid + 256 * i;
-    *reinterpret_cast<float4 *>(&PH[c4 / (M / 4) * PP + c4 % (M / 4) * 4]) = ph_reg[i];
-  }
-  __syncthreads();
-
-  // ridge: rho = ridge_rel * trace(S) / M (every wave sums in the same order)
-  double tr = lane < M ? Ss[lane * SP + lane] : 0.0;
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) tr += __shfl_xor(tr, d);
-  const double rho = (double)ridge_rel * tr / (double)M;
-  __syncthreads();
-  if (tid < M) {
-    const double v = Ss[tid * SP + tid] + rho;
-    Ss[tid * SP + tid] = v;
-    d0_s[tid] = v;
-  }
-  __syncthreads();
-
-  // ---- 2, 3, and 4 row by row: W = Phi X^T (128 x M), lower block triangle of X only; stored as W^T
   uint16_t *wh = wt + (size_t)lhead * (W_TERMS * M * D);
-  auto emit = [&](int mt, int ct, const f64x4 &acc) {
-    float x[4];
-#pragma unroll
-    for (int v = 0; v < 4; ++v) x[v] = (float)acc[v];
-#pragma unroll
-    for (int tt = 0; tt < W_TERMS; ++tt) {
-      uint16_t b[4];
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        b[v] = bf16_rne(x[v]);
-        x[v] -= bf16_to_f32(b[v]);
-      }
-      *reinterpret_cast<uint2 *>(&wh[(tt * M + 16 * mt + l16) * D + 16 * ct + 4 * lq]) =
-          make_uint2((unsigned)b[0] | (unsigned)b[1] << 16, (unsigned)b[2] | (unsigned)b[3] << 16);
-    }
-  };
-  // Phi is the A operand: row i of a 16-channel tile holds channel 4 (i & 3) + (i >> 2), so that the
-  // four result registers of a lane are four consecutive channels
-  const float *phi_w = PH + (4 * (l16 & 3) + (l16 >> 2)) * PP + lq;
-  factor_panels<P, 4>(Ss, Xd, d0_s, &flag_s, [&](int mt, int i, int nw) {
-    constexpr int OWN = (D / 16 + 2) / 3;          // channel tiles of a wave, of three or four waves
-    f64x4 acc[OWN];
-#pragma unroll
-    for (int u = 0; u < OWN; ++u) acc[u] = f64x4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll 1
-    for (int kb = 0; kb <= mt; ++kb) {
-#pragma unroll
-      for (int k4 = 0; k4 < 4; ++k4) {
-        const int k = 16 * kb + 4 * k4;
-        const double x = kb == mt ? Xd[mt][l16][4 * k4 + lq] : Ss[(k + lq) * SP + 16 * mt + l16];
-#pragma unroll
-        for (int u = 0; u < OWN; ++u)
-          if (i + nw * u < D / 16)                 // uniform
-            acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)phi_w[16 * (i + nw * u) * PP + k], x,
-                                                          acc[u], 0, 0, 0);
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < OWN; ++u)
-      if (i + nw * u < D / 16) emit(mt, i + nw * u, acc[u]);
-  });
+  sketch_factor<M>(F, sum, ph, ridge_rel, [&](int tt, int row, int ch, uint16_t v) { wh[(tt * M + row) * D + ch] = v; });
+  __syncthreads();
   if (tid == 0) {
     const Where w = locate_head(T, lhead);
-    status[T.s[w.seg].ghead0 + w.head] = flag_s;
+    status[T.s[w.seg].ghead0 + w.head] = F.flag;
   }
 }
 
@@ -650,7 +354,7 @@ __global__ __launch_bounds__(EXACT_THREADS) void exact_solve_kernel(
   // ---- 2 and 3, W^T = X split into bf16 planes row by row.  The score kernel reads of row j the
   // channels of its group of 32 and of the groups before it. ----
   uint16_t *wh = wt + (size_t)lhead * (W_TERMS * M * D);
-  factor_panels<P, NW>(Ss, Xd, d0_s, &flag_s, [&](int p, int i, int nw) {
+  factor_panels<P, NW, true>(Ss, Xd, d0_s, &flag_s, [&](int p, int i, int nw) {
     // a wave: 16 rows x 32 channels, a lane 8 consecutive channels of one row
     const int r = lane & 15, c8 = 8 * (lane >> 4);
     for (int g32 = i; g32 <= p >> 1; g32 += nw) {
@@ -689,6 +393,7 @@ constexpr int SHARE_SPLITS = 64, SHARE_PARTS_MAX = 8;
 SolvePlan solve_plan(const SegTable &T, int ks, int tiles_per_wg) {
   SolvePlan p;
   p.parts = 1;
+  p.nshares = 0;
   if (ks == 0) {
     p.share_bytes = (size_t)T.nheads * 10 * 1024 * sizeof(double);
     return p;
@@ -701,7 +406,8 @@ SolvePlan solve_plan(const SegTable &T, int ks, int tiles_per_wg) {
   p.parts = (most + SHARE_SPLITS - 1) / SHARE_SPLITS;
   if (p.parts > SHARE_PARTS_MAX) p.parts = SHARE_PARTS_MAX;
   const int P = ks / 16;
-  p.share_bytes = (size_t)T.nheads * p.parts * SHARE_BLOCKS * (P * (P + 1) / 2 * 256) * sizeof(double);
+  p.nshares = p.parts * SHARE_BLOCKS;
+  p.share_bytes = (size_t)T.nheads * p.nshares * (P * (P + 1) / 2 * 256) * sizeof(double);
   return p;
 }
 
@@ -712,7 +418,9 @@ static hipError_t launch_sketched(const SegTable &T, int tiles_per_wg, const Sol
                                   long long zero_ints, hipStream_t st) {
   if (shares != nullptr) {
     hipLaunchKernelGGL((sketch_share_kernel<M>), dim3((unsigned)(T.nheads * plan.parts * SHARE_BLOCKS)),
-                       dim3(256), 0, st, T, tiles_per_wg, plan.parts, partials, phi, shares, zero, zero_ints);
+                       dim3(256), 0, st, T, tiles_per_wg, plan.parts, partials, phi, shares,
+                       wt == nullptr ? status : nullptr, zero, zero_ints);
+    if (wt == nullptr) return hipGetLastError();
     if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
     hipLaunchKernelGGL((sketch_solve_kernel<M, true>), dim3((unsigned)T.nheads), dim3(256), 0, st, T,
                        tiles_per_wg, plan.parts, nullptr, shares, phi, ridge_rel, wt, status, nullptr, 0);
@@ -723,12 +431,13 @@ static hipError_t launch_sketched(const SegTable &T, int tiles_per_wg, const Sol
   return hipGetLastError();
 }
 
-// Sketched mode: partial Gram blocks -> W^T (see above).
+// Sketched mode: partial Gram blocks -> W^T (see above); wt null: the shares only.
 hipError_t launch_sketch_solve(const SegTable &T, int ks, int tiles_per_wg, const SolvePlan &plan,
                                const float *partials, double *shares, const float *phi,
                                float ridge_rel, uint16_t *wt, int32_t *status, int *zero,
                                long long zero_ints, hipStream_t st) {
   if (T.nheads <= 0) return hipSuccess;
+  if (shares == nullptr && wt == nullptr) return hipErrorInvalidValue;
   switch (ks) {
     case 16: return launch_sketched<16>(T, tiles_per_wg, plan, partials, shares, phi, ridge_rel, wt, status, zero, zero_ints, st);
     case 32: return launch_sketched<32>(T, tiles_per_wg, plan, partials, shares, phi, ridge_rel, wt, status, zero, zero_ints, st);
