@@ -6,7 +6,7 @@
 // key, plus the lowest-indexed tokens equal to it until k_keep is reached, written in
 // ascending token order.  Ties therefore go to the lower index, deterministically.
 // Heads of up to 32768 tokens get one workgroup of 1024 threads each, which reads the scores
-// once and keeps the keys in LDS (128 KB) for the later passes; longer heads, and selection
+// once and holds them in registers; longer heads, and selection
 // across the heads of a layer, are shared by several workgroups (second half of this file).
 #include "common.h"
 
@@ -45,30 +45,24 @@ __device__ __forceinline__ int block_exclusive_scan(int v, int *wsum, int *total
   return base + inc - v;
 }
 
-constexpr int LDS_KEYS = 32768;    // heads up to this many tokens keep their keys in LDS
+constexpr int WHOLE_HEAD = 32768;  // heads up to this many tokens are selected by one workgroup
 
 // Finds, in a histogram of `nb` digits, the digit where the descending cumulative count reaches
 // `need`; returns the digit and leaves in *need the count still wanted inside that digit.
-template <int NT = SELECT_THREADS>
-__device__ __forceinline__ int find_digit(const int *hist, int nb, int *need, int *wsum, int *found) {
-  constexpr int PER = 4096 / NT;     // digits per thread (nb <= 4096)
-  const int tid = threadIdx.x;
-  // thread t owns the PER digits nb-1-PER*t .. (descending), so that an ascending scan over
-  // threads is a descending scan over digits
-  int c[PER], sum = 0;
+// Thread t owns the PER digits first, first - 1, .. (descending, those of thread t + 1 below), so that an ascending scan
+// over threads is a descending scan over digits; c[] are their counts.
+template <int NT, int PER>
+__device__ __forceinline__ int find_counted(const int (&c)[PER], int first, int *need, int *wsum, int *found) {
+  int sum = 0;
 #pragma unroll
-  for (int q = 0; q < PER; ++q) {
-    const int dgt = nb - 1 - (PER * tid + q);
-    c[q] = dgt >= 0 ? hist[dgt] : 0;
-    sum += c[q];
-  }
+  for (int q = 0; q < PER; ++q) sum += c[q];
   int total;
   int before = block_exclusive_scan<NT>(sum, wsum, &total);   // keys in higher digits
   const int want = *need;
 #pragma unroll
   for (int q = 0; q < PER; ++q) {
     if (before < want && want <= before + c[q]) {          // exactly one (thread, q) matches
-      found[0] = nb - 1 - (PER * tid + q);
+      found[0] = first - q;
       found[1] = want - before;
     }
     before += c[q];
@@ -77,196 +71,256 @@ __device__ __forceinline__ int find_digit(const int *hist, int nb, int *need, in
   *need = found[1];
   return found[0];
 }
-
-// One pass of the radix select: histogram of a digit (`nb` values) of the keys, then find_digit.
-// digit(key) gives the digit, or -1 for a key that is out already.  Keys come from LDS (FROM_LDS) or
-// are recomputed from the scores in global memory; with STORE the keys are also parked in LDS.
-template <bool FROM_LDS, bool STORE, class F>
-__device__ int radix_pass(const float *__restrict__ sp, uint32_t *keys, int n, F &&digit, int nb,
-                          int *need, int *hist, int *wsum, int *found) {
-  const int tid = threadIdx.x;
-  for (int i = tid; i < 4096; i += SELECT_THREADS) hist[i] = 0;
-  __syncthreads();
-  auto tally = [&](uint32_t k) {
-    const int d = digit(k);
-    if (d >= 0) atomicAdd(&hist[d], 1);
-  };
-  // 16-byte accesses: the LDS keys are aligned by token; scores in global memory are read from
-  // the first 16-byte boundary on, the `lead` tokens in front of it (and the tail) one by one
-  const int lead = FROM_LDS ? 0 : min(n, (int)((4u - ((reinterpret_cast<uintptr_t>(sp) >> 2) & 3u)) & 3u));
-  const int nv = (n - lead) >> 2;
-  if (tid < lead) {
-    const uint32_t k = score_key(sp[tid]);
-    if (STORE) keys[tid] = k;
-    tally(k);
-  }
-#pragma unroll 8        // a head of 32768 tokens: all of a thread's loads in flight at once
-  for (int i = tid; i < nv; i += SELECT_THREADS) {
-    uint4 k4;
-    if (FROM_LDS) {
-      k4 = reinterpret_cast<const uint4 *>(keys)[i];
-    } else {
-      const float4 f = reinterpret_cast<const float4 *>(sp + lead)[i];
-      k4 = make_uint4(score_key(f.x), score_key(f.y), score_key(f.z), score_key(f.w));
-      if (STORE) {
-        if (lead == 0) {
-          reinterpret_cast<uint4 *>(keys)[i] = k4;
-        } else {
-          uint32_t *kd = keys + lead + 4 * i;
-          kd[0] = k4.x; kd[1] = k4.y; kd[2] = k4.z; kd[3] = k4.w;
-        }
-      }
-    }
-    tally(k4.x); tally(k4.y); tally(k4.z); tally(k4.w);
-  }
-  for (int i = lead + 4 * nv + tid; i < n; i += SELECT_THREADS) {
-    const uint32_t k = FROM_LDS ? keys[i] : score_key(sp[i]);
-    if (STORE) keys[i] = k;
-    tally(k);
-  }
-  __syncthreads();
-  return find_digit(hist, nb, need, wsum, found);
+template <int NT = SELECT_THREADS>
+__device__ __forceinline__ int find_digit(const int *hist, int nb, int *need, int *wsum, int *found) {
+  constexpr int PER = 4096 / NT;     // digits per thread (nb <= 4096)
+  const int first = nb - 1 - PER * (int)threadIdx.x;
+  int c[PER];
+#pragma unroll
+  for (int q = 0; q < PER; ++q) c[q] = first - q >= 0 ? hist[first - q] : 0;
+  return find_counted<NT>(c, first, need, wsum, found);
 }
 
-// Ordered emit for keys resident in LDS (n <= LDS_KEYS).  Token order is (round, wave, lane,
-// element) with 4096 tokens per round, so a token's output position is the sum of the counts of
-// the rounds before it, of the waves before it in its round, of the lanes before it in its wave
-// and of the elements before it in its lane: a wave scan per round plus one scan of the table of
-// (round, wave) counts.  Counts are packed as (above | equal << 16), at most 32768 each.
-// Every thread holds its keys in registers by then, so the key array is free to collect the
-// retained token indices in order; they leave as one coalesced run.
-__device__ void emit_kept_lds(uint32_t *keys, int n, int k, uint32_t thr, int need_eq,
-                              int32_t *__restrict__ out, unsigned *table) {
-  constexpr int NW = SELECT_THREADS / 64, R = LDS_KEYS / (4 * SELECT_THREADS);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  uint32_t key[R][4];
-  unsigned before[R];
+// The scores of tokens [begin, end) of a head, 4 consecutive tokens per thread of NT and round (token of f[r][e]:
+// begin + 4 * ((r0 + r) * NT + tid) + e); bit 4r+e of the result says that the token exists.  The loads are only issued here: whoever calls this first and converts to keys later
+// has the latency of everything in between for free.
+// One 16-byte load per 4 tokens also where a head's scores start off a 16-byte boundary (odd n): global memory
+// takes vector loads at any 4-byte address.  No branch around a single load: each would wait for the one
+// before it (112 heads of 131072 tokens, candidates 17 us with and 13 without; blend of 4 layers of 8 x 16383
+// 10.3 and 7.4).  Four tokens that reach past a chunk's end are read from its last four on
+// and moved into place by place_scores, after which the loads are waited for.
+template <int NT, int R>
+__device__ __forceinline__ void load_scores(const float *__restrict__ sp, int begin, int end, int r0,
+                                            float (&f)[R][4]) {
+  typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+  const int i0 = begin + 4 * (r0 * NT + (int)threadIdx.x);
+  const int last4 = end - 4;
+  if (last4 >= 0) {                      // uniform
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int i0 = 4 * (r * SELECT_THREADS + tid);
-    if (4 * r * SELECT_THREADS >= n) {             // uniform: a round past the end of the head
-      before[r] = 0;
-      if (lane == 63) table[r * NW + wave] = 0;
-      continue;
+    for (int r = 0; r < R; ++r) {
+      const f32x4_any v = *reinterpret_cast<const f32x4_any *>(sp + min(i0 + 4 * r * NT, last4));
+      f[r][0] = v.x; f[r][1] = v.y; f[r][2] = v.z; f[r][3] = v.w;
     }
-    if (i0 + 3 < n) {
-      const uint4 kv = *reinterpret_cast<const uint4 *>(keys + i0);
-      key[r][0] = kv.x; key[r][1] = kv.y; key[r][2] = kv.z; key[r][3] = kv.w;
-    } else {
+  } else {                               // a head of up to three tokens
 #pragma unroll
-      for (int q = 0; q < 4; ++q) key[r][q] = i0 + q < n ? keys[i0 + q] : 0u;
-    }
-    unsigned mine = 0;
+    for (int r = 0; r < R; ++r)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const bool v = i0 + q < n;
-      mine += (v && key[r][q] > thr) ? 1u : 0u;
-      mine += (v && key[r][q] == thr) ? 0x10000u : 0u;
-    }
-    const unsigned inc = (unsigned)wave_inclusive_scan((int)mine);
-    before[r] = inc - mine;
-    if (lane == 63) table[r * NW + wave] = inc;
+      for (int e = 0; e < 4; ++e) f[r][e] = r == 0 && i0 + e < end ? sp[e] : 0.f;
   }
-  __syncthreads();                   // all keys are in registers; the table is complete
-  if (wave == 0) {                   // exclusive scan of the R * NW entries, 2 per lane
-    constexpr int PER = (R * NW + 63) / 64;
-    unsigned v[PER], sum = 0;
+}
+// Returns the bits of the tokens that exist; what f holds of others is any number.
+template <int NT, int R>
+__device__ __forceinline__ unsigned place_scores(int begin, int end, int r0, float (&f)[R][4]) {
+  unsigned valid = 0xffffffffu >> (32 - 4 * R);
+  if (begin + 4 * (r0 + R) * NT > end) {          // uniform: some do not exist
+    valid = 0;
 #pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int idx = lane * PER + i;
-      v[i] = idx < R * NW ? table[idx] : 0u;
-      sum += v[i];
-    }
-    const unsigned inc = (unsigned)wave_inclusive_scan((int)sum);
-    unsigned run = inc - sum;
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int idx = lane * PER + i;
-      if (idx < R * NW) table[idx] = run;
-      run += v[i];
-    }
-  }
-  __syncthreads();
-  int32_t *stage = reinterpret_cast<int32_t *>(keys);
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int i0 = 4 * (r * SELECT_THREADS + tid);
-    if (4 * r * SELECT_THREADS >= n) break;          // uniform
-    const unsigned p = table[r * NW + wave] + before[r];
-    int pg = (int)(p & 0xffffu), pe = (int)(p >> 16);
-    // keys equal to the threshold are rare (one, unless scores tie): a wave whose 256 tokens of
-    // this round hold none only has to place the keys above it
-    bool any_eq = false;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) any_eq |= i0 + q < n && key[r][q] == thr;
-    if (!__any(any_eq)) {
-      const int base = pg + min(pe, need_eq);
-#pragma unroll
-      for (int q = 0, at = base; q < 4; ++q) {
-        const bool is_gt = i0 + q < n && key[r][q] > thr;
-        if (is_gt && at < k) stage[at] = i0 + q;
-        at += is_gt;
-      }
-      continue;
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      if (i0 + q < n) {
-        const bool is_gt = key[r][q] > thr, is_eq = key[r][q] == thr;
-        const int pos = pg + min(pe, need_eq);
-        if ((is_gt || (is_eq && pe < need_eq)) && pos < k) stage[pos] = i0 + q;
-        pg += is_gt;
-        pe += is_eq;
+    for (int r = 0; r < R; ++r) {
+      const int have = end - (begin + 4 * ((r0 + r) * NT + (int)threadIdx.x));
+      valid |= ((1u << min(max(have, 0), 4)) - 1u) << (4 * r);
+      if (have > 0 && have < 4 && end >= 4) {
+        if (have < 3) { f[r][0] = f[r][2]; f[r][1] = f[r][3]; }
+        if (have != 2) { f[r][0] = f[r][1]; f[r][1] = f[r][2]; f[r][2] = f[r][3]; }
       }
     }
   }
-  __syncthreads();
-  for (int j = tid; j < k; j += SELECT_THREADS) out[j] = stage[j];
+  return valid;
 }
 
+// The float of a key (score_key's inverse; -0.0 has no key of its own).
+__device__ __forceinline__ float key_score(uint32_t key) {
+  return __uint_as_float((key & 0x80000000u) ? key ^ 0x80000000u : ~key);
+}
+
+// Classification of scores against a key interval [lo, hi]: bits of the tokens of f (see load_scores)
+// above it and inside it; f becomes the keys' distances from lo (of those inside).  Keys of one sign are the
+// float's bits with the sign set, or their complement; what lies outside wraps round to a distance beyond the
+// interval.  Float comparison gives the order of the keys everywhere but at NaN (key 0, below every number)
+// and just below zero (-0.0 is +0.0 but compares equal to it), and those have the general path.
+template <int R, class ABOVE, class DIST>
+__device__ __forceinline__ void classify_by(float (&f)[R][4], uint32_t span, unsigned &above, unsigned &in,
+                                            ABOVE &&is_above, DIST &&distance) {
+  above = in = 0;
+#pragma unroll
+  for (int r = R - 1; r >= 0; --r)
+#pragma unroll
+    for (int e = 3; e >= 0; --e) {
+      above = above + above + (is_above(f[r][e]) ? 1u : 0u);
+      const uint32_t v = distance(f[r][e]);
+      in = in + in + (v <= span ? 1u : 0u);
+      f[r][e] = __uint_as_float(v);
+    }
+}
+template <int R>
+__device__ __forceinline__ void classify(float (&f)[R][4], unsigned valid, uint32_t lo, uint32_t hi,
+                                         unsigned &above, unsigned &in) {
+  const bool positive = lo > 0x80000000u && hi <= 0xff800000u, negative = lo >= 0x007fffffu && hi < 0x7fffffffu;
+  if (positive || negative) {
+    const float fhi = key_score(hi);
+    const uint32_t flip = positive ? 0x80000000u : 0xffffffffu;
+    classify_by(f, hi - lo, above, in, [&](float x) { return x > fhi; },
+                [&](float x) { return (__float_as_uint(x) ^ flip) - lo; });
+  } else {
+    classify_by(f, hi - lo, above, in, [&](float x) { return score_key(x) > hi; },
+                [&](float x) { return score_key(x) - lo; });
+  }
+  above &= valid;
+  in &= valid;
+}
+
+// The bits of rounds 0 .. R - 1 (4 tokens each, low nibbles of R bytes) in one word.
+template <int R>
+__device__ __forceinline__ unsigned nibbles(const unsigned char *by, int shift) {
+  unsigned w = 0;
+#pragma unroll
+  for (int i = 0; i < R; ++i) w |= ((unsigned)by[i] >> shift & 0xfu) << (4 * i);
+  return w;
+}
+
+// Positions and tokens of what a workgroup of NT retains of the tokens from `base` on.  keep: this thread's tokens above
+// the threshold, of 32 at most that begin `first` tokens behind base; ties: those equal to it, of which the workgroup
+// keeps `allow`, the first ones.  Threads hold their tokens in order.  The retained tokens are consecutive in the
+// output: they are gathered in LDS (16 bits each, as many as the workgroup has tokens) and written out as one run of at
+// most `limit`.
+template <int NT>
+__device__ __forceinline__ void emit_ordered(unsigned keep, unsigned ties, int allow, int base, int first, int limit,
+                                             int *wsum, uint16_t *stage, int32_t *__restrict__ out) {
+  int all_packed;                        // (above | equal << 16), at most 32768 each
+  const unsigned before = (unsigned)block_exclusive_scan<NT>(__popc(keep) | (int)((unsigned)__popc(ties) << 16), wsum,
+                                                             &all_packed);
+  const unsigned all = (unsigned)all_packed;
+  const int ties_before = (int)(before >> 16);
+  for (int left = allow - ties_before; ties && left > 0; --left) {
+    keep |= ties & (0u - ties);
+    ties &= ties - 1;
+  }
+  int at = (int)(before & 0xffffu) + min(ties_before, allow);
+  while (keep) {
+    stage[at++] = (uint16_t)(first + __ffs(keep) - 1);
+    keep &= keep - 1;
+  }
+  __syncthreads();
+  const int total = min((int)(all & 0xffffu) + min((int)(all >> 16), allow), limit);
+  for (int j = threadIdx.x; j < total; j += NT) out[j] = base + stage[j];
+}
+
+// One workgroup per head of up to 4096 R tokens, which hold their scores in registers.  HIST1: the first digit's
+// histogram has come with the scores (top 12 key bits), otherwise it is tallied here by score_bin.  The keys above the
+// threshold's bin and inside it become bits of two words per thread, those inside it their distance from its lowest key;
+// the next digits are tallied from the latter, and a round's 4 tokens of a thread pass through LDS as a byte so that a
+// thread then holds 4 R consecutive tokens and one scan gives every position.
+// Bound: a chain of barriers (three for a digit) for few heads, vector issue for long ones.  Against keys in LDS, read
+// again for every digit, which left room for one workgroup on a compute unit: behind the score kernel, one head of 4096
+// tokens 9.6 us before and 7.0 now, 256 heads of 32768 27.1 and 23.6; on given scores, 256 heads of 32768 24.0 / 21.6,
+// 512 45.9 / 43.9, 1024 of 8192 42.4 / 24.3, 2048 of 4096 67.5 / 35.2.
+template <int R, bool HIST1>
 __global__ __launch_bounds__(SELECT_THREADS) void select_kernel(const SegTable T,
                                                                 const float *__restrict__ scores,
                                                                 const int *__restrict__ hist1,
                                                                 int32_t *__restrict__ kept_idx,
                                                                 int32_t *__restrict__ kept_cnt) {
-  __shared__ __attribute__((aligned(16))) uint32_t keys[LDS_KEYS];
-  __shared__ __attribute__((aligned(16))) int hist[4096];
-  __shared__ int wsum[SELECT_THREADS / 64];
+  constexpr int NT = SELECT_THREADS;
+  union Big {
+    int first[HIST1 ? 4 : HIST1_BINS];
+    uint16_t stage[4 * R * NT];
+  };
+  union Second {
+    int hist[4096];
+    unsigned char quad[R * NT];
+  };
+  __shared__ __attribute__((aligned(16))) Big big;
+  __shared__ __attribute__((aligned(16))) Second second;
+  __shared__ __attribute__((aligned(16))) int third[2048];
+  __shared__ int wsum[NT / 64];
   __shared__ int found[2];
 
   const Where w = locate_block(T, blockIdx.x, 0, 1, false);
   const Seg &s = T.s[w.seg];
   const int n = s.n, k = s.k_keep;
   const float *sp = scores + s.score_off + (long long)w.head * n;
-  int32_t *out = kept_idx + (s.kept_off + (long long)w.head * k);
   const int tid = threadIdx.x;
+  float f[R][4];
+  load_scores<NT, R>(sp, 0, n, 0, f);    // in flight while the first digit is found
+  const int4 h1 = HIST1 ? *reinterpret_cast<const int4 *>(hist1 + (size_t)w.lhead * HIST1_BINS + hist_at(4092 - 4 * tid))
+                        : make_int4(0, 0, 0, 0);
   if (tid == 0) kept_cnt[s.ghead0 + w.head] = k;
-  // threshold key = the k-th largest, by three radix passes (bin, 12 bits, the rest); the scores are
-  // read once and their keys stay in LDS for the later passes (n <= LDS_KEYS, checked on the host)
+  *reinterpret_cast<int4 *>(&second.hist[4 * tid]) = make_int4(0, 0, 0, 0);
+  *reinterpret_cast<int2 *>(&third[2 * tid]) = make_int2(0, 0);
   int need = k;
-  if (hist1 != nullptr) {                // bins already tallied by the score kernel
-    const int *h1 = hist1 + (size_t)w.lhead * HIST1_BINS;
-    static_assert(HIST1_BINS == 4 * SELECT_THREADS, "four bins per thread");
-    *reinterpret_cast<int4 *>(&hist[4 * tid]) = *reinterpret_cast<const int4 *>(h1 + hist_at(4 * tid));
+  unsigned valid;
+  int bin;
+  if constexpr (HIST1) {
+    const int c[4] = {h1.w, h1.z, h1.y, h1.x};
+    bin = find_counted<NT>(c, 4095 - 4 * tid, &need, wsum, found);
+    valid = place_scores<NT, R>(0, n, 0, f);
+  } else {
+    *reinterpret_cast<int4 *>(&big.first[4 * tid]) = make_int4(0, 0, 0, 0);
     __syncthreads();
+    valid = place_scores<NT, R>(0, n, 0, f);
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (valid >> (4 * r + e) & 1) atomicAdd(&big.first[score_bin(score_key(f[r][e]))], 1);
+    __syncthreads();
+    bin = find_digit<NT>(big.first, HIST1_BINS, &need, wsum, found);
   }
-  const int bin = hist1 != nullptr
-                      ? find_digit(hist, HIST1_BINS, &need, wsum, found)
-                      : radix_pass<false, true>(sp, keys, n, [](uint32_t q) { return score_bin(q); },
-                                                HIST1_BINS, &need, hist, wsum, found);
-  const BinKeys bk = bin_keys(bin, hist1 == nullptr);
-  const int bits = bk.bits, rest = bits - 12;
-  const uint32_t key1 = bk.lo;
-  auto digit2 = [&](uint32_t q) { return (q >> bits) == (key1 >> bits) ? (int)((q >> rest) & 0xfffu) : -1; };
-  const int d2 = hist1 != nullptr
-                     ? radix_pass<false, true>(sp, keys, n, digit2, 4096, &need, hist, wsum, found)
-                     : radix_pass<true, false>(sp, keys, n, digit2, 4096, &need, hist, wsum, found);
-  const uint32_t key2 = key1 | (uint32_t)d2 << rest;
-  const int d3 = radix_pass<true, false>(
-      sp, keys, n,
-      [&](uint32_t q) { return (q >> rest) == (key2 >> rest) ? (int)(q & ((1u << rest) - 1u)) : -1; },
-      1 << rest, &need, hist, wsum, found);
-  emit_kept_lds(keys, n, k, key2 | (uint32_t)d3, need, out, reinterpret_cast<unsigned *>(hist));
+  const BinKeys bk = bin_keys(bin, !HIST1);
+  const int rest = bk.bits - 12;
+  unsigned above, in;
+  classify<R>(f, valid, bk.lo, bk.lo | ((1u << bk.bits) - 1u), above, in);
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (in >> (4 * r + e) & 1) atomicAdd(&second.hist[__float_as_uint(f[r][e]) >> rest], 1);
+  __syncthreads();
+  const uint32_t d2 = (uint32_t)find_digit<NT>(second.hist, 4096, &need, wsum, found);
+  // Above the second digit, and from it on; few waves have a token inside it, and only they have more to look at.
+  const uint32_t low = (1u << rest) - 1u, base2 = d2 << rest, top2 = base2 | low;
+  unsigned gt = 0, eq = 0;
+#pragma unroll
+  for (int r = R - 1; r >= 0; --r)
+#pragma unroll
+    for (int e = 3; e >= 0; --e) {
+      const uint32_t v = __float_as_uint(f[r][e]);
+      gt = gt + gt + (v > top2 ? 1u : 0u);
+      eq = eq + eq + (v >= base2 ? 1u : 0u);
+    }
+  gt &= in;
+  unsigned at2 = eq & in & ~gt;
+  const bool look = __any(at2 != 0);
+  if (look) {
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (at2 >> (4 * r + e) & 1) atomicAdd(&third[__float_as_uint(f[r][e]) & low], 1);
+  }
+  __syncthreads();
+  const uint32_t thr = base2 | (uint32_t)find_digit<NT>(third, 1 << rest, &need, wsum, found);
+  eq = 0;
+  if (look) {
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const uint32_t v = __float_as_uint(f[r][e]);
+        const unsigned bit = at2 & (1u << (4 * r + e));
+        gt |= v > thr ? bit : 0u;
+        eq |= v == thr ? bit : 0u;
+      }
+  }
+  gt |= above;
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+    second.quad[r * NT + tid] = (unsigned char)((gt >> (4 * r) & 0xfu) | (eq >> (4 * r) & 0xfu) << 4);
+  __syncthreads();
+  unsigned char by[R];
+#pragma unroll
+  for (int i = 0; i < R; ++i) by[i] = second.quad[R * tid + i];
+  emit_ordered<NT>(nibbles<R>(by, 0), nibbles<R>(by, 4), need, 0, 4 * R * tid, k, wsum, big.stage,
+                   kept_idx + (s.kept_off + (long long)w.head * k));
 }
 
 // ---- selection by several workgroups per pool ------------------------------------------------
@@ -336,93 +390,6 @@ __device__ __forceinline__ SelWhere sel_locate(const SegTable &T, int blk) {
 __device__ __forceinline__ long long chunk_token_base(const SegTable &T, const SelWhere &q) {
   const Seg &s = T.s[q.seg];
   return s.tok0 + (long long)(q.head - s.head_begin) * s.n + q.tok_begin;
-}
-
-// The scores of a chunk, 4 consecutive tokens per thread and round (token of f[r][e]:
-// tok_begin + 4 * (r * CHUNK_THREADS + tid) + e); bit 4r+e of the result says that the token
-// exists.  The loads are only issued here: whoever calls this first and converts to keys later
-// has the latency of everything in between for free.
-// One 16-byte load per 4 tokens also where a head's scores start off a 16-byte boundary (odd n): global memory
-// takes vector loads at any 4-byte address.  No branch around a single load: each would wait for the one
-// before it (112 heads of 131072 tokens, candidates 17 us with and 13 without; blend of 4 layers of 8 x 16383
-// 10.3 and 7.4).  Four tokens that reach past a chunk's end are read from its last four on
-// and moved into place by place_scores_part, after which the loads are waited for.
-template <int R>
-__device__ __forceinline__ void load_scores_part(const float *__restrict__ sp, const SelWhere &q, int r0,
-                                                 float (&f)[R][4]) {
-  typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
-  const int i0 = q.tok_begin + 4 * (r0 * CHUNK_THREADS + (int)threadIdx.x);
-  const int last4 = q.tok_end - 4;
-  if (last4 >= 0) {                      // uniform
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const f32x4_any v = *reinterpret_cast<const f32x4_any *>(sp + min(i0 + 4 * r * CHUNK_THREADS, last4));
-      f[r][0] = v.x; f[r][1] = v.y; f[r][2] = v.z; f[r][3] = v.w;
-    }
-  } else {                               // a head of up to three tokens
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) f[r][e] = r == 0 && i0 + e < q.tok_end ? sp[e] : 0.f;
-  }
-}
-// Returns the bits of the tokens that exist; what f holds of others is any number.
-template <int R>
-__device__ __forceinline__ unsigned place_scores_part(const SelWhere &q, int r0, float (&f)[R][4]) {
-  unsigned valid = 0xffffffffu >> (32 - 4 * R);
-  if (q.tok_begin + 4 * (r0 + R) * CHUNK_THREADS > q.tok_end) {          // uniform: some do not exist
-    valid = 0;
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int have = q.tok_end - (q.tok_begin + 4 * ((r0 + r) * CHUNK_THREADS + (int)threadIdx.x));
-      valid |= ((1u << min(max(have, 0), 4)) - 1u) << (4 * r);
-      if (have > 0 && have < 4 && q.tok_end >= 4) {
-        if (have < 3) { f[r][0] = f[r][2]; f[r][1] = f[r][3]; }
-        if (have != 2) { f[r][0] = f[r][1]; f[r][1] = f[r][2]; f[r][2] = f[r][3]; }
-      }
-    }
-  }
-  return valid;
-}
-
-// The float of a key (score_key's inverse; -0.0 has no key of its own).
-__device__ __forceinline__ float key_score(uint32_t key) {
-  return __uint_as_float((key & 0x80000000u) ? key ^ 0x80000000u : ~key);
-}
-
-// Classification of scores against a key interval [lo, hi]: bits of the tokens of f (see load_scores_part)
-// above it and inside it; f becomes the keys' distances from lo (of those inside).  Keys of one sign are the
-// float's bits with the sign set, or their complement; what lies outside wraps round to a distance beyond the
-// interval.  Float comparison gives the order of the keys everywhere but at NaN (key 0, below every number)
-// and just below zero (-0.0 is +0.0 but compares equal to it), and those have the general path.
-template <class ABOVE, class DIST>
-__device__ __forceinline__ void classify_by(float (&f)[SEL_ROUNDS][4], uint32_t span, unsigned &above, unsigned &in,
-                                            ABOVE &&is_above, DIST &&distance) {
-  above = in = 0;
-#pragma unroll
-  for (int r = SEL_ROUNDS - 1; r >= 0; --r)
-#pragma unroll
-    for (int e = 3; e >= 0; --e) {
-      above = above + above + (is_above(f[r][e]) ? 1u : 0u);
-      const uint32_t v = distance(f[r][e]);
-      in = in + in + (v <= span ? 1u : 0u);
-      f[r][e] = __uint_as_float(v);
-    }
-}
-__device__ __forceinline__ void classify(float (&f)[SEL_ROUNDS][4], unsigned valid, uint32_t lo, uint32_t hi,
-                                         unsigned &above, unsigned &in) {
-  const bool positive = lo > 0x80000000u && hi <= 0xff800000u, negative = lo >= 0x007fffffu && hi < 0x7fffffffu;
-  if (positive || negative) {
-    const float fhi = key_score(hi);
-    const uint32_t flip = positive ? 0x80000000u : 0xffffffffu;
-    classify_by(f, hi - lo, above, in, [&](float x) { return x > fhi; },
-                [&](float x) { return (__float_as_uint(x) ^ flip) - lo; });
-  } else {
-    classify_by(f, hi - lo, above, in, [&](float x) { return score_key(x) > hi; },
-                [&](float x) { return score_key(x) - lo; });
-  }
-  above &= valid;
-  in &= valid;
 }
 
 // Room for the marks of a chunk of `tokens` tokens: where each wave's candidates begin in the list, then a pair
@@ -670,7 +637,7 @@ __global__ __launch_bounds__(CHUNK_THREADS, 7) void msel_cand_kernel(const SegTa
   const Seg &s = T.s[q.seg];
   const float *sp = scores + s.score_off + (long long)q.head * s.n;
   float f[SEL_ROUNDS][4];
-  load_scores_part<SEL_ROUNDS>(sp, q, 0, f);             // in flight while the digit is found
+  load_scores<CHUNK_THREADS, SEL_ROUNDS>(sp, q.tok_begin, q.tok_end, 0, f);             // in flight while the digit is found
   if (threadIdx.x == 0) { above_s = 0; ncand_s = 0; }
   uint32_t lo, hi;
   if constexpr (SAMPLED) {
@@ -689,8 +656,8 @@ __global__ __launch_bounds__(CHUNK_THREADS, 7) void msel_cand_kernel(const SegTa
     }
   }
   unsigned above, in;
-  const unsigned valid = place_scores_part<SEL_ROUNDS>(q, 0, f);
-  classify(f, valid, lo, hi, above, in);
+  const unsigned valid = place_scores<CHUNK_THREADS, SEL_ROUNDS>(q.tok_begin, q.tok_end, 0, f);
+  classify<SEL_ROUNDS>(f, valid, lo, hi, above, in);
   uint32_t *list = cand + chunk_token_base(T, q);
   const int lane = threadIdx.x & 63;
   // A wave's candidates stand in thread order, a thread's in consecutive slots, so that the emit finds them
@@ -1042,10 +1009,9 @@ __global__ __launch_bounds__(CHUNK_THREADS, 8) void msel_emit_kernel(const SegTa
                                                                    const int *__restrict__ state,
                                                                    int32_t *__restrict__ kept_idx) {
   constexpr int NW = CHUNK_THREADS / 64;
-  constexpr int EMIT_STAGE = 4096;
-  __shared__ unsigned wtot[NW];
+  __shared__ int wtot[NW];
   __shared__ __attribute__((aligned(8))) unsigned char quad[SEL_ROUNDS * CHUNK_THREADS];
-  __shared__ int stage[EMIT_STAGE];
+  __shared__ uint16_t stage[SEL_CHUNK];
   const SelWhere q = sel_locate(T, blockIdx.x);
   const Seg &s = T.s[q.seg];
   const float *sp = scores + s.score_off + (long long)q.head * s.n;
@@ -1074,8 +1040,8 @@ __global__ __launch_bounds__(CHUNK_THREADS, 8) void msel_emit_kernel(const SegTa
   if (no_marks) {                                        // uniform
     gt = 0;
     float f[SEL_ROUNDS][4];
-    load_scores_part<SEL_ROUNDS>(sp, q, 0, f);
-    const unsigned valid = place_scores_part<SEL_ROUNDS>(q, 0, f);
+    load_scores<CHUNK_THREADS, SEL_ROUNDS>(sp, q.tok_begin, q.tok_end, 0, f);
+    const unsigned valid = place_scores<CHUNK_THREADS, SEL_ROUNDS>(q.tok_begin, q.tok_end, 0, f);
 #pragma unroll
     for (int r = 0; r < SEL_ROUNDS; ++r)
 #pragma unroll
@@ -1111,7 +1077,7 @@ __global__ __launch_bounds__(CHUNK_THREADS, 8) void msel_emit_kernel(const SegTa
   __syncthreads();
   // this thread's tokens are now tok_begin + 32 * tid ..: low and high nibbles of 8 bytes
   const uint2 by = *reinterpret_cast<const uint2 *>(&quad[8 * tid]);
-  auto nibbles = [](unsigned lo, unsigned hi) {          // the low nibbles of 8 bytes, 4 bits each
+  auto packed = [](unsigned lo, unsigned hi) {           // the low nibbles of 8 bytes, 4 bits each
     auto four = [](unsigned x) {
       x &= 0x0f0f0f0fu;
       x = (x | x >> 4) & 0x00ff00ffu;
@@ -1119,38 +1085,8 @@ __global__ __launch_bounds__(CHUNK_THREADS, 8) void msel_emit_kernel(const SegTa
     };
     return four(lo) | four(hi) << 16;
   };
-  unsigned keep = nibbles(by.x, by.y);
-  unsigned ties = nibbles(by.x >> 4, by.y >> 4);
-  const unsigned mine = (unsigned)__popc(keep) | (unsigned)__popc(ties) << 16;
-  const unsigned inc = (unsigned)wave_inclusive_scan((int)mine);
-  if (lane == 63) wtot[wave] = inc;
-  __syncthreads();
-  unsigned before = inc - mine, all = 0;
-#pragma unroll
-  for (int w = 0; w < NW; ++w) {
-    before += w < wave ? wtot[w] : 0u;
-    all += wtot[w];
-  }
-  const int ties_before = (int)(before >> 16);
-  for (int left = allow - ties_before; ties && left > 0; --left) {
-    keep |= ties & (0u - ties);
-    ties &= ties - 1;
-  }
-  // the chunk's retained tokens are consecutive in the output: they are gathered in LDS and
-  // written out as one run (what does not fit the stage goes straight to memory)
-  int at = (int)(before & 0xffffu) + min(ties_before, allow);
-  const int tok0 = q.tok_begin + 32 * tid;
-  while (keep) {
-    const int tok = tok0 + __ffs(keep) - 1;
-    if (at < EMIT_STAGE) stage[at] = tok;
-    else if (pos0 + at < limit) out[pos0 + at] = tok;
-    ++at;
-    keep &= keep - 1;
-  }
-  __syncthreads();
-  const int total = (int)(all & 0xffffu) + min((int)(all >> 16), allow);
-  const int staged = min(min(total, EMIT_STAGE), limit - pos0);
-  for (int j = tid; j < staged; j += CHUNK_THREADS) out[pos0 + j] = stage[j];
+  emit_ordered<CHUNK_THREADS>(packed(by.x, by.y), packed(by.x >> 4, by.y >> 4), allow, q.tok_begin, 32 * tid,
+                              limit - pos0, wtot, stage, out + pos0);
 }
 
 // ---- blend: s = z(a) + lambda z(o) (paper Eq. "scoring"), population standard deviation ------
@@ -1227,8 +1163,8 @@ __global__ __launch_bounds__(CHUNK_THREADS) void blend_apply_kernel(
   const float a0 = a[0];
   float fa[PART][4], fo[PART][4];
   if (HALF) {
-    load_scores_part<PART>(a, q, r_first, fa);
-    load_scores_part<PART>(o, q, r_first, fo);
+    load_scores<CHUNK_THREADS, PART>(a, q.tok_begin, q.tok_end, r_first, fa);
+    load_scores<CHUNK_THREADS, PART>(o, q.tok_begin, q.tok_end, r_first, fo);
   }
   // where the head's sums start: its first score workgroup
   const int obph = X.per_head[q.seg];
@@ -1242,11 +1178,11 @@ __global__ __launch_bounds__(CHUNK_THREADS) void blend_apply_kernel(
   for (int r0 = r_first; r0 < (HALF ? r_first + PART : SEL_ROUNDS); r0 += PART) {
     if (!HALF) {
       if (q.tok_begin + 4 * r0 * CHUNK_THREADS >= q.tok_end) break;       // uniform
-      load_scores_part<PART>(a, q, r0, fa);
-      load_scores_part<PART>(o, q, r0, fo);
+      load_scores<CHUNK_THREADS, PART>(a, q.tok_begin, q.tok_end, r0, fa);
+      load_scores<CHUNK_THREADS, PART>(o, q.tok_begin, q.tok_end, r0, fo);
     }
-    place_scores_part<PART>(q, r0, fa);
-    const unsigned valid = place_scores_part<PART>(q, r0, fo);
+    place_scores<CHUNK_THREADS, PART>(q.tok_begin, q.tok_end, r0, fa);
+    const unsigned valid = place_scores<CHUNK_THREADS, PART>(q.tok_begin, q.tok_end, r0, fo);
 #pragma unroll
     for (int r = 0; r < PART; ++r) {
       const unsigned m = (valid >> (4 * r)) & 0xfu;
@@ -1278,7 +1214,7 @@ __global__ __launch_bounds__(CHUNK_THREADS) void blend_apply_kernel(
 bool select_needs_pools(const SegTable &T) {
   if (T.layer_scope) return true;
   for (int i = 0; i < T.nseg; ++i)
-    if (T.s[i].n > LDS_KEYS) return true;
+    if (T.s[i].n > WHOLE_HEAD) return true;
   return false;
 }
 
@@ -1330,8 +1266,16 @@ hipError_t launch_select(const SegTable &T, const float *scores, const int *hist
                          int32_t *kept_idx, int32_t *kept_cnt, hipStream_t st) {
   if (T.nheads <= 0) return hipSuccess;
   if (select_needs_pools(T)) return hipErrorInvalidValue;     // longer heads: launch_select_pools
-  hipLaunchKernelGGL(select_kernel, dim3((unsigned)T.nheads), dim3(SELECT_THREADS), 0, st, T,
-                     scores, hist1, kept_idx, kept_cnt);
+  int most = 0;
+  for (int i = 0; i < T.nseg; ++i) most = T.s[i].n > most ? T.s[i].n : most;
+  constexpr int ROUND = 4 * SELECT_THREADS;
+  const bool h = hist1 != nullptr;
+  const auto kernel = most <= ROUND       ? (h ? select_kernel<1, true> : select_kernel<1, false>)
+                      : most <= 2 * ROUND ? (h ? select_kernel<2, true> : select_kernel<2, false>)
+                      : most <= 4 * ROUND ? (h ? select_kernel<4, true> : select_kernel<4, false>)
+                                          : (h ? select_kernel<8, true> : select_kernel<8, false>);
+  hipLaunchKernelGGL(kernel, dim3((unsigned)T.nheads), dim3(SELECT_THREADS), 0, st, T, scores, hist1, kept_idx,
+                     kept_cnt);
   return hipGetLastError();
 }
 

@@ -146,6 +146,27 @@ def test_select_scores_of_any_scale(C, scale, L, H, ns, ratios, scope):
     _select_case(C, ns, ratios, L, H, lambda r, m: scale * r.random(m), 43, scope)
 
 
+# heads of one workgroup: rounds of 4096 tokens, and short heads beside long ones
+@pytest.mark.parametrize("maker", [_bin_edges, lambda r, m: np.round(r.random(m), 2), lambda r, m: r.random(m) - 0.7],
+                         ids=["edges", "ties", "signs"])
+@pytest.mark.parametrize("ns", [[4096, 1, 2], [4097], [8192, 3], [8193, 5], [16384], [16385, 4098], [32768, 3], [32767, 17]])
+def test_select_rounds_of_one_workgroup(C, maker, ns):
+    _select_case(C, ns, [0.4, 0.9, 0.5][:len(ns)], 1, 2, maker, 45)
+
+
+@pytest.mark.parametrize("n,ratio", [(4096, 1.0), (4097, 0.3), (8193, 0.02), (16385, 0.9), (32768, 0.6)])
+def test_fused_select_rounds_of_one_workgroup(C, n, ratio):
+    """Every kept index against the oracle's selection of the library's own scores."""
+    w = W.config1(DEV, L=1, H=2, n=n, ratio=ratio)
+    params, reqs = U.make_call(C, w, DEV)
+    out = C.compactor_compress(params, reqs, want_scores=True)
+    torch.cuda.synchronize()
+    k = O.keep_count(n, ratio)
+    for h in range(2):
+        want = O.select_topk(out["scores"][h * n:(h + 1) * n].cpu().numpy(), k)
+        assert np.array_equal(out["kept_idx"][h * k:(h + 1) * k].cpu().numpy(), want)
+
+
 # an odd number of tokens in the launch: the chunks' records behind the candidate list are 4-byte aligned
 @pytest.mark.parametrize("L,H,ns,ratios,scope", [(1, 1, [40003], [0.3], 0), (1, 3, [43691], [0.2], 0),
                                                  (3, 1, [8193, 20001, 41], [0.4, 0.1, 0.9], 1)])
