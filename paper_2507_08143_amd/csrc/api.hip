@@ -74,29 +74,28 @@ int compute_units() {
   return n;
 }
 
-// Gram: a persistent launch of 2 workgroups per compute unit (or as many as there are tiles),
-// each taking an equal run of 64-row tiles; of 1 where few heads' partials weigh more in the
-// factorisation than the second workgroup saves: up to longer runs the fewer heads share the partials.
-// compactor_score on MI355X, % more (+) or less (-) time with 1 than with 2 workgroups a unit, by tiles a
-// unit (k_s = 16 and 64 lie within 3 % of 48; 1 to 4 heads gain more than 8: exact mode 21 to 5 at 62 tiles):
-//   exact mode, tiles    8     16     24    32    48    62     k_s = 48, tiles    8     14    20    23
-//      8 heads         -12.9  -9.2  -6.7  -5.4  -3.2  -1.0                      -6.4  -3.5  -0.2  -2.7
-//     16 heads          -8.0  -4.5  -2.3  -2.5  +0.3  +2.0                      -7.3  -3.0  -1.2  -1.7
-//     24 heads          -1.6  +0.7  -0.5  +0.8  +0.6  +3.5                      -0.3  -0.3  +1.7  +2.0
-//     32 heads          -2.4  -1.9  -0.6  -0.3  +1.5  +3.5                      -6.0  -0.9  +1.7  +2.1
-struct GramPlan { int nwg, tiles_per_wg; };
+// Gram: a persistent launch, each workgroup taking an equal run of 64-row tiles.  Every (workgroup, head) partial costs
+// the factorisation 40 KB, so the fewer heads and tiles, the fewer workgroups: one pair (see gram_kernel) a compute unit,
+// one plain workgroup a unit where a few heads give it 8 to 30 tiles (the pair's end, where its halves meet, is
+// longer than what its loads save), and two plain ones for long runs, which stream a little faster than one pair, and
+// where there are heads for every unit (256 of 1024 tokens 68.8 / 69.1).
+// compactor_score on MI355X, us with the plain / the paired plan, k_s = 48: 8 heads of 32768 54.5 / 54.4, 2 x 4 of 40007
+// 61.5 / 63.2, 24 of 12000 61.8 / 59.6, 128 of 2048 64.5 / 62.1, 21 of 20001 74.4 / 70.7, 8 of 65536 79.4 / 75.2, 8
+// of 100000 105 / 98.5, 128 of 4096 83.1 / 80.4, of 8192 129 / 127, 48 of 32768 161.5 / 165, 64 of 32768 199 / 205, of 65536
+// 357 / 376; exact mode: 8 of 32768 83.6 / 84.7, 21 of 20001 96.5 / 98.2, 8 of 65536 106.4 / 103.3, 64 of 8192 102.6 / 99.4,
+// 32 of 50000 197 / 194, 16 of 131072 234 / 232, 64 of 32768 230 / 235, of 65536 410 / 425; whole calls, one head
+// of 4096 45.5 / 43.4, 8 of 8192 57.6 / 54.4.
+struct GramPlan { int nwg, tiles_per_wg; bool pair; };
 GramPlan gram_plan(const compactor_params_t *p, const SegTable &T, int cus) {
   const long long total = total_tiles(T);
   const bool exact = p->sketch_dim == 0;
-  const long long most = T.nheads <= 8    ? (exact ? 64 : 24)
-                         : T.nheads <= 16 ? (exact ? 48 : 24)
-                         : T.nheads <= 32 ? (exact ? 32 : 16)
-                                          : 0;
-  const bool few = total < most * cus;
-  long long want = p->gram_wgs > 0 ? p->gram_wgs : (few ? 1ll : 2ll) * cus;
+  const int single_most = T.nheads <= 16 ? (exact ? 30 : 24) : T.nheads <= 32 ? (exact ? 30 : 16) : 0;
+  const bool single = total >= 8ll * cus && total < (long long)single_most * cus;
+  GramPlan g;
+  g.pair = !single && T.nheads < cus && total < (exact ? 112ll : 72ll) * cus;
+  long long want = p->gram_wgs > 0 ? p->gram_wgs : (single || g.pair ? 1ll : 2ll) * cus;
   if (want > total) want = total;
   if (want < 1) want = 1;
-  GramPlan g;
   g.tiles_per_wg = (int)((total + want - 1) / want);
   // not below 8 tiles (512 rows) a workgroup: every partial costs a 40 KB round trip
   if (g.tiles_per_wg < 8 && p->gram_wgs <= 0) g.tiles_per_wg = 8;
@@ -320,7 +319,7 @@ int enqueue_score(const compactor_params_t *p, const SegTable &T, const GroupByt
   const int rpw = gp.tiles_per_wg;
   const Marks m{p->stage_events, st};
   MARK(m, 0);
-  HIP_TRY(launch_gram(T, gp.nwg, gp.tiles_per_wg, partials, st));
+  HIP_TRY(launch_gram(T, gp.nwg, gp.tiles_per_wg, gp.pair, partials, st));
   MARK(m, COMPACTOR_STAGE_GRAM + 1);
   MARK(m, COMPACTOR_STAGE_REDUCE + 1);       // the fp64 sum of the partials is part of the next kernel
   double *shares =

@@ -344,8 +344,8 @@ __device__ __forceinline__ long long partial_base(const SegTable &T, int lhead, 
 // All of them enqueue on `st` and return the hipGetLastError() of their launches.
 
 // Partial Gram matrices: the 10 upper 32x32 blocks (fp32) per (workgroup, head) intersection,
-// nwg + nheads slots.
-hipError_t launch_gram(const SegTable &T, int nwg, int tiles_per_wg, float *partials,
+// nwg + nheads slots.  pair: workgroups of twice the waves (the number of partials is the same).
+hipError_t launch_gram(const SegTable &T, int nwg, int tiles_per_wg, bool pair, float *partials,
                        hipStream_t st);
 
 // Factorisation: partial Gram blocks -> W^T ([term][k_s][128] per head as W_TERMS bf16 planes; exact

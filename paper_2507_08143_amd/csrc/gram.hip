@@ -44,17 +44,26 @@ __device__ __forceinline__ bf16x4 lds_read_tr(const unsigned char *p) {
 //   wave 0: (0,0) (0,1) (0,2)   wave 1: (0,3) (1,1) (1,2)   wave 2: (1,3) (2,2)   wave 3: (2,3) (3,3)
 constexpr int GRAM_OCC = 2;         // waves per SIMD the register budget is set for
 constexpr int GRAM_TG_UNROLL = 4;   // 16-token steps unrolled together (more operands in flight)
-// The body is compiled once per wave of the workgroup: which blocks a wave owns is then known
+//
+// PAIR: a workgroup of two such groups of 4 waves, each of which streams half of the run (the first or the second)
+// through tile buffers of its own.  Twice the loads are in flight, as with two
+// workgroups on a compute unit, but what the groups have of the same head leaves as one partial: the second group's
+// waits in LDS for the first's.  Where it pays: gram_plan.
+// The body is compiled once per wave of a group: which blocks a wave owns is then known
 // at compile time, and the accumulators stay in fixed registers (a run-time switch inside the
 // loop makes the compiler copy them at every join).
-template <int wave>
+template <int wave, bool PAIR>
 __device__ __forceinline__ void gram_body(const SegTable &T, int tiles_per_wg, long long total,
-                                          float *__restrict__ partials, unsigned char *smem) {
-  const long long g0 = (long long)blockIdx.x * tiles_per_wg;
-  const int count = (int)min((long long)tiles_per_wg, total - g0);
-  if (count <= 0) return;
+                                          float *__restrict__ partials, unsigned char *lds) {
+  const int group = PAIR ? __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8) : 0;
+  const int steps = PAIR ? (tiles_per_wg + 1) / 2 : tiles_per_wg;          // of a group, all of which meet
+  const long long first_tile = (long long)blockIdx.x * tiles_per_wg;
+  const long long g0 = first_tile + group * steps;
+  const int count = (int)min((long long)(PAIR && group ? tiles_per_wg - steps : steps), total - g0);
+  if (!PAIR && count <= 0) return;       // (a second group without tiles comes along)
+  unsigned char *smem = lds + (PAIR ? group * 2 * TILE_BYTES : 0);
 
-  const int tid = threadIdx.x, lane = tid & 63;
+  const int tid = threadIdx.x & 255, lane = tid & 63;
   const int ld_row = tid >> 4, ld_chunk = tid & 15;   // loader: 16 lanes cover one 256-B row
 
   f32x16 acc[3];
@@ -64,7 +73,7 @@ __device__ __forceinline__ void gram_body(const SegTable &T, int tiles_per_wg, l
     for (int v = 0; v < 16; ++v) acc[b][v] = 0.f;
 
   TileCursor L, C;                 // load cursor runs two tiles ahead of the compute cursor
-  cursor_seek<GRAM_TILE>(T, g0, L);
+  cursor_seek<GRAM_TILE>(T, PAIR ? min(g0, total - 1) : g0, L);
   C = L;
 
   auto load_tile = [&](int t, uint4 (&stage)[4]) {   // t: tile number inside this workgroup
@@ -120,8 +129,10 @@ __device__ __forceinline__ void gram_body(const SegTable &T, int tiles_per_wg, l
   // ends is parked in LDS (each wave its own blocks, no barrier needed) and leaves with the last
   // one; only a workgroup that crosses more than one head boundary writes mid-run, with
   // streaming stores.
-  float *park = reinterpret_cast<float *>(smem + 2 * TILE_BYTES);
+  // PAIR: the place belongs to the second group, for the head that the first one ends in.
+  float *park = reinterpret_cast<float *>(lds + (PAIR ? 4 : 2) * TILE_BYTES);
   int parked_lhead = -1;
+  const int first_lhead = T.s[C.seg].lhead0 + C.hh;      // the group's first head
   enum { TO_GLOBAL, TO_GLOBAL_STREAM, TO_LDS };
   auto flush = [&](int lhead, int how) {
     float *out = how == TO_LDS ? park
@@ -144,11 +155,21 @@ __device__ __forceinline__ void gram_body(const SegTable &T, int tiles_per_wg, l
     }
   };
   bool dirty = false;
+  int keep_lhead = -1;                   // PAIR: the head of what is still in the accumulators, if complete
   auto finish_tile = [&](bool last_of_run) {       // after a tile has been multiplied
     dirty = true;
     if (C.tile + 1 == C.tph) {
       const int lhead = T.s[C.seg].lhead0 + C.hh;
-      if (last_of_run) {
+      if (PAIR) {
+        if (group && lhead == first_lhead) {
+          flush(lhead, TO_LDS);          // where the first group has no part of it, copied from there
+          parked_lhead = lhead;
+        } else if (!last_of_run) {
+          flush(lhead, TO_GLOBAL_STREAM);
+        } else {
+          keep_lhead = lhead;
+        }
+      } else if (last_of_run) {
         flush(lhead, TO_GLOBAL);
       } else if (parked_lhead < 0) {
         flush(lhead, TO_LDS);
@@ -156,7 +177,7 @@ __device__ __forceinline__ void gram_body(const SegTable &T, int tiles_per_wg, l
       } else {
         flush(lhead, TO_GLOBAL_STREAM);
       }
-      dirty = false;
+      if (!PAIR || !last_of_run || parked_lhead == lhead) dirty = false;
     }
     cursor_next<GRAM_TILE>(T, C);
   };
@@ -165,21 +186,55 @@ __device__ __forceinline__ void gram_body(const SegTable &T, int tiles_per_wg, l
   uint4 stA[4], stB[4];
   load_tile(0, stA);
   load_tile(1, stB);
-  for (int t = 0; t < count; t += 2) {
+  // (PAIR: every group passes the barriers of `steps` tiles)
+  const int meet = PAIR ? steps : count;
+  for (int t = 0; t < meet; t += 2) {
     store_tile(smem, stA);
     __syncthreads();
     load_tile(t + 2, stA);
-    compute_tile(smem);
-    finish_tile(t + 1 == count);
-    if (t + 1 < count) {
+    if (!PAIR || t < count) {
+      compute_tile(smem);
+      finish_tile(t + 1 == count);
+    }
+    if (t + 1 < meet) {
       store_tile(smem + TILE_BYTES, stB);
       __syncthreads();
       load_tile(t + 3, stB);
-      compute_tile(smem + TILE_BYTES);
-      finish_tile(t + 2 == count);
+      if (!PAIR || t + 1 < count) {
+        compute_tile(smem + TILE_BYTES);
+        finish_tile(t + 2 == count);
+      }
     }
   }
-  if (dirty) flush(T.s[C.seg].lhead0 + C.hh, TO_GLOBAL);
+  if constexpr (PAIR) {
+    int mine = keep_lhead >= 0 ? keep_lhead : T.s[C.seg].lhead0 + C.hh;   // the head of the accumulators, if dirty
+    if (group && dirty && mine == first_lhead) {         // all of the group's tiles are of one head
+      flush(mine, TO_LDS);
+      parked_lhead = mine;
+      dirty = false;
+    }
+    int *shared = reinterpret_cast<int *>(lds + 4 * TILE_BYTES + GRAM_PARTIAL_FLOATS * 4);
+    if (lane == 0 && wave == 0) shared[group] = group ? parked_lhead : (dirty ? mine : -1);
+    __syncthreads();
+    const bool joined = shared[0] >= 0 && shared[0] == shared[1];
+    if (!group && joined) {
+#pragma unroll
+      for (int b = 0; b < 3; ++b) {
+        if (b < nblk) {
+          const float *ob = park + (first + b) * GBLK;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const float4 v = *reinterpret_cast<const float4 *>(ob + (64 * q + lane) * 4);
+            acc[b][4 * q] += v.x; acc[b][4 * q + 1] += v.y; acc[b][4 * q + 2] += v.z; acc[b][4 * q + 3] += v.w;
+          }
+        }
+      }
+    }
+    if (joined) parked_lhead = -1;
+    if (dirty) flush(mine, TO_GLOBAL);
+  } else {
+    if (dirty) flush(T.s[C.seg].lhead0 + C.hh, TO_GLOBAL);
+  }
   if (parked_lhead >= 0) {         // the parked partial: every lane copies what it wrote itself
     float *out = partials + ((size_t)blockIdx.x + parked_lhead) * GRAM_PARTIAL_FLOATS;
 #pragma unroll
@@ -195,26 +250,30 @@ __device__ __forceinline__ void gram_body(const SegTable &T, int tiles_per_wg, l
   }
 }
 
-__global__ __launch_bounds__(256, GRAM_OCC) void gram_kernel(const SegTable T, int tiles_per_wg,
-                                                             long long total,
-                                                             float *__restrict__ partials) {
-  // two key tiles and room for one parked partial Gram matrix
-  __shared__ __attribute__((aligned(16))) unsigned char smem[2 * TILE_BYTES + GRAM_PARTIAL_FLOATS * 4];
+template <bool PAIR>
+__global__ __launch_bounds__(PAIR ? 512 : 256, GRAM_OCC) void gram_kernel(const SegTable T, int tiles_per_wg,
+                                                                          long long total,
+                                                                          float *__restrict__ partials) {
+  // two key tiles a group and room for one parked partial Gram matrix (and two words)
+  __shared__ __attribute__((aligned(16))) unsigned char
+      smem[(PAIR ? 4 : 2) * TILE_BYTES + GRAM_PARTIAL_FLOATS * 4 + (PAIR ? 16 : 0)];
   // every wave passes the same workgroup barriers, each in its own copy of the loop
-  switch (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) {
-    case 0: gram_body<0>(T, tiles_per_wg, total, partials, smem); break;
-    case 1: gram_body<1>(T, tiles_per_wg, total, partials, smem); break;
-    case 2: gram_body<2>(T, tiles_per_wg, total, partials, smem); break;
-    default: gram_body<3>(T, tiles_per_wg, total, partials, smem); break;
+  switch (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) & 3) {
+    case 0: gram_body<0, PAIR>(T, tiles_per_wg, total, partials, smem); break;
+    case 1: gram_body<1, PAIR>(T, tiles_per_wg, total, partials, smem); break;
+    case 2: gram_body<2, PAIR>(T, tiles_per_wg, total, partials, smem); break;
+    default: gram_body<3, PAIR>(T, tiles_per_wg, total, partials, smem); break;
   }
 }
 
-hipError_t launch_gram(const SegTable &T, int nwg, int tiles_per_wg, float *partials,
+hipError_t launch_gram(const SegTable &T, int nwg, int tiles_per_wg, bool pair, float *partials,
                        hipStream_t st) {
   const long long total = total_tiles(T);
   if (total <= 0 || nwg <= 0) return hipSuccess;
-  hipLaunchKernelGGL(gram_kernel, dim3((unsigned)nwg), dim3(256), 0, st, T, tiles_per_wg, total,
-                     partials);
+  if (pair)
+    hipLaunchKernelGGL(gram_kernel<true>, dim3((unsigned)nwg), dim3(512), 0, st, T, tiles_per_wg, total, partials);
+  else
+    hipLaunchKernelGGL(gram_kernel<false>, dim3((unsigned)nwg), dim3(256), 0, st, T, tiles_per_wg, total, partials);
   return hipGetLastError();
 }
 
