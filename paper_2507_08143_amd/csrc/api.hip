@@ -103,7 +103,7 @@ GramPlan gram_plan(const compactor_params_t *p, const SegTable &T, int cus) {
   return g;
 }
 
-// Score: workgroups of equal token runs inside a head, 2 per compute unit at a time.  A launch
+// Score: workgroups of equal token runs inside a head, 2 (exact mode: 3) per compute unit at a time.  A launch
 // of W workgroups takes ceil(W / slots) rounds; the run length is chosen to keep the last
 // round full and the per-workgroup fixed cost (staging W^T, about 32 KB) small.
 int score_tokens_for(const compactor_params_t *p, const SegTable &T, int cus) {
@@ -113,10 +113,11 @@ int score_tokens_for(const compactor_params_t *p, const SegTable &T, int cus) {
   }
   // Sketched mode: one burst per workgroup (measured on MI355X: runs of two bursts are 2 to 9 %
   // slower, the barriers around a burst in mid-run cost more than the longer run saves, and many
-  // short workgroups balance the CUs better).  Exact mode stages four times as much W^T per
-  // workgroup and gains 4 % from runs of 16384 tokens.
+  // short workgroups balance the CUs better).  Exact mode: three workgroups a unit, runs of up to 16384
+  // tokens; compactor_score, us with runs of 512 / 1024 / 2048 / 4096 / 8192 tokens and those of the search below, 32
+  // heads of 50001 196 / 194 / 202 / 200 / 233 and 189, 256 of 16384 415 / 405 / 397 / 414 / 408 and 397.
   const int cap = p->sketch_dim == 0 ? 16384 : SCORE_BURST;
-  const int slots = 2 * cus;
+  const int slots = (p->sketch_dim == 0 ? 3 : 2) * cus;
   long long rows = 0;
   for (int i = 0; i < T.nseg; ++i) rows += (long long)T.s[i].n * T.s[i].head_count;
   // Sketched mode, few heads: one workgroup per unit, which then factors its head itself (score_solves), as long as

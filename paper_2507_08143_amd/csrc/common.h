@@ -21,7 +21,7 @@ constexpr int GRAM_PARTIAL_FLOATS = 10 * 32 * 32;   // upper blocks of one parti
 constexpr int GRAM_TILE = 64;         // rows staged in LDS per step of the Gram kernel
 constexpr int SCORE_STEP = 128;       // tokens a score workgroup multiplies per step
 constexpr int SCORE_BURST = 4096;     // scores a score workgroup collects in LDS before writing them
-constexpr int SCORE_EXACT_BURST = 2048;   // the same in exact mode, where W^T takes more of the LDS
+constexpr int SCORE_EXACT_BURST = 2048;   // the same in exact mode, where three workgroups share the LDS
 constexpr int SCORE_MAX_RUN = 32768;  // most tokens a score workgroup takes (its histogram counts in
                                       // 16 bits)
 constexpr int SELECT_THREADS = 1024;

@@ -418,6 +418,19 @@ def test_score_runs_of_several_bursts(C, score_tokens):
     _say("  exact ridge 1e-4: max rel err %.3g, swaps %d" % (st["max_rel"], st["swaps"]))
 
 
+# exact mode takes steps of 64 tokens, two at a time, and bursts of 2048: a step to either side, token by token layout
+@pytest.mark.parametrize("n", [129, 191, 193, 2047, 2049, 4160])
+@pytest.mark.parametrize("blend", [False, True])
+def test_exact_scores_at_the_edges_of_steps_and_bursts(C, n, blend):
+    w = W.config5(DEV, L=1, H=3, n=n, exact=True)
+    r = w.requests[0]
+    r.k = r.k.permute(0, 2, 1, 3).contiguous().permute(0, 2, 1, 3)
+    r.v = r.v.permute(0, 2, 1, 3).contiguous().permute(0, 2, 1, 3)
+    if blend:
+        r.attn = W.synthetic_attention_scores(1, 3, n, device=DEV, seed=n)
+    U.run_and_check(C, w, DEV, tune={"score_tokens": 32768})
+
+
 def test_config2_small(C):
     _say("config 2 shape, 2 layers x 8 heads, n=6000")
     st, _ = U.run_and_check(C, W.config2(device=DEV, L=2, H=8, n=6000), DEV)
