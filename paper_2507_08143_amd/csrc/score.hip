@@ -170,6 +170,7 @@ __global__ __launch_bounds__(256, 2) void score_kernel(
     int32_t *__restrict__ status, int *__restrict__ hist1, double *__restrict__ ostat) {
   constexpr int NSUB = 2, WTOK = 16 * NSUB, STEP = 4 * WTOK;     // tokens per wave / per WG step
   constexpr int NLD = WTOK * 16 / 64;                            // 16-B loads per lane per step
+  constexpr int AHEAD = 4;
   typedef WLayout<M> WL;
   __shared__ __attribute__((aligned(16))) uint16_t wl[W_TERMS * WL::PLANE];
   constexpr int BURST = SCORE_BURST, BSTEPS = BURST / STEP;
@@ -249,8 +250,23 @@ __global__ __launch_bounds__(256, 2) void score_kernel(
   if constexpr (SOLVE) {
     double sum[Share<M>::TILES];
     ss.add(shares, V.nshares, sum);
+    // The memory would wait for the factorisation: the wave's rows of the next four steps are brought as far as the L2
+    // by one dword a line.  Four are 128 KB a unit, as much as there is; with eight the first are lost again.
+    // compactor_score on MI355X, us without / with, k_s = 16, 32, 48, 64: 8 heads of 16384 32.4 / 31.1, 36.8 / 35.7, 42.5 /
+    // 41.4, 50.3 / 49.7, 32768 43.6 / 40.2, 47.9 / 45.6, 53.0 / 52.1, 62.3 / 62.3, 131072 102.7 / 99.4, 107.7 / 104.8, 114.0 /
+    // 110.8.  Not for runs of three steps and less, which have one left to bring at most.
+    unsigned ahead[AHEAD] = {};
+    if (nsteps > 3) {
+#pragma unroll
+      for (int u = 0; u < AHEAD; ++u) {
+        const long long row = (long long)tok_begin + (2 + u) * STEP + wave * WTOK + (lane >> 1);
+        ahead[u] = *reinterpret_cast<const unsigned *>(kp + min(row, tok_end - 1ll) * stride_t + 64 * (lane & 1));
+      }
+    }
     sketch_factor<M>(lds.f, sum, ph, V.ridge_rel,
                      [&](int t, int row, int ch, uint16_t v) { wl[t * WL::PLANE + row * WPITCH + ch] = v; });
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u) asm volatile("" ::"v"(ahead[u]));
     __syncthreads();
     if (w.tile == 0 && tid == 0 && lds.f.flag) atomicOr(&status[s.ghead0 + w.head], lds.f.flag);
     __syncthreads();
