@@ -451,6 +451,8 @@ __host__ __device__ __forceinline__ bool inplace_moves(int tok, long long j, int
 // Token tok of a head that keeps `rows` rows lies beyond their destinations, the slots 0 .. rows - 1, so that no move
 // of the head overwrites it.  Tokens ascend, so these are the last rows of the list.
 __host__ __device__ __forceinline__ bool inplace_late(int tok, int rows) { return tok >= rows; }
+// What stands for the token of a late row that somebody else moves: moves nowhere, and is no entry of a list to skip.
+constexpr int INPLACE_LATE = 0x7fffffff;
 
 // in_place: the rows are read from the pages themselves (token t at logical slot t).
 hipError_t launch_gather_paged(const SegTable &T, const PagePool &P, const int32_t *kept_idx,

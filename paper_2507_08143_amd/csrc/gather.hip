@@ -328,7 +328,7 @@ __global__ __launch_bounds__(INPLACE_THREADS) void compact_inplace_kernel(
       tok[o] = -1;
       if (jr < I::RUN && j < rows) {
         tok[o] = idx[j];
-        if (EARLY && inplace_late(tok[o], rows)) tok[o] = -1;
+        if (EARLY && inplace_late(tok[o], rows)) tok[o] = INPLACE_LATE;
       }
     }
   };
@@ -350,7 +350,9 @@ __global__ __launch_bounds__(INPLACE_THREADS) void compact_inplace_kernel(
       }
     }
   };
-  // `more`: the first row of the run is one to look at, and so are all before it (ascending tokens)
+  // `more`: the first row of the run is not late, so that the run may have early rows.  What a list says of that row
+  // decides, not whether it moves: entries below their own rank, negative ones among them, are skipped and do not end
+  // the list.  (Tokens ascend: behind a late row all are.)
   auto put_moves = [&](int slot, const RowPages (&pg)[I::OWN], bool more) {
     if (EARLY && tid == 0) more_l[slot] = more;
 #pragma unroll
@@ -389,11 +391,11 @@ __global__ __launch_bounds__(INPLACE_THREADS) void compact_inplace_kernel(
   const int runs = inplace_runs(rows, I::RUN);
   fetch_idx(0, tok);
   fetch_pages(0, tok, pg);
-  bool more = tok[0] >= 0;               // of the run whose pages pg holds (thread 0: its first row)
+  bool more = tok[0] != INPLACE_LATE;    // of the run whose pages pg holds (thread 0: its first row)
   fetch_idx(1, tok);
   put_moves(0, pg, more);
   fetch_pages(1, tok, pg);
-  more = tok[0] >= 0;
+  more = tok[0] != INPLACE_LATE;
   fetch_idx(2, tok);
   __syncthreads();
   load_rows(0, a);
@@ -405,7 +407,7 @@ __global__ __launch_bounds__(INPLACE_THREADS) void compact_inplace_kernel(
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     fetch_pages(r + 2, tok, pg);
-    more = tok[0] >= 0;
+    more = tok[0] != INPLACE_LATE;
     fetch_idx(r + 3, tok);
     load_rows((r + 1) % 3, next);
     store_rows(r % 3, cur);

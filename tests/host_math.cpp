@@ -5,6 +5,7 @@ extern "C" {
 long long inplace_row(int run, int run_rows, int row_of_run) { return cmp::inplace_row(run, run_rows, row_of_run); }
 int inplace_runs(int rows, int run_rows) { return cmp::inplace_runs(rows, run_rows); }
 int inplace_moves(int tok, long long j, int n) { return cmp::inplace_moves(tok, j, n); }
+int inplace_late_token(void) { return cmp::INPLACE_LATE; }
 int sample_lines(void) { return cmp::SAMPLE_LINES; }
 int sample_line(int g, int lines) { return cmp::sample_line(g, lines); }
 int score_bin(unsigned key) { return cmp::score_bin(key); }

@@ -35,7 +35,7 @@ def test_in_place_rows_up_to_the_largest_context(M, run_rows):
             for jr in (0, 1, run_rows - 1):
                 j = M.inplace_row(run, run_rows, jr)
                 assert j == run * run_rows + jr
-                assert not M.inplace_moves(-1, j, most)
+                assert not M.inplace_moves(-1, j, most) and not M.inplace_moves(M.inplace_late_token(), j, most)
                 if 0 <= j < most:
                     assert not M.inplace_moves(j, j, most) and (j == 0 or not M.inplace_moves(j - 1, j, most))
                     assert bool(M.inplace_moves(j + 1, j, most)) == (j + 1 < most)

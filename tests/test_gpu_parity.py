@@ -1026,6 +1026,39 @@ def test_compact_in_place_in_two_launches(C, L, H, n, ratio, scope):
     _paged_case(C, w, scope, 16, True, 35)
 
 
+# a list may begin with entries below their own rank, which are skipped (here more of them than a run of any slice
+# width has rows): what stands behind them moves all the same, early rows and late ones, in two launches and in one
+@pytest.mark.parametrize("H,n,rows,skipped", [(1, 24001, 7000, 1100), (1, 24001, 7000, 3073), (17, 41000, 12300, 600),
+                                              (65, 16411, 5400, 300), (2, 3000, 1500, 1100)])
+@pytest.mark.parametrize("entry", ["negative", "zero"])
+def test_compact_in_place_skips_entries_below_their_rank(C, H, n, rows, skipped, entry):
+    rng = np.random.default_rng(37)
+    page, pages = 16, (n + 15) // 16
+    pool = torch.randint(-30000, 30000, (2, pages + 3, page, 1, H, 128), dtype=torch.int16, device=DEV)
+    table = rng.permutation(pages + 3).astype(np.int32)[:pages]
+    kept = np.empty((H, rows), np.int32)
+    kept[:, :skipped] = np.arange(-skipped - 4, -4) if entry == "negative" else 0
+    want = pool.cpu().numpy()
+    for h in range(H):
+        kept[h, skipped:] = np.sort(rng.choice(np.arange(skipped, n), rows - skipped, replace=False))
+        moves = np.flatnonzero(kept[h] > np.arange(rows))
+        for t in range(2):               # ascending tokens: a row is read before its slot is reused
+            was = want[t, table, :, 0, h].reshape(-1, 128)
+            now = was.copy()
+            now[moves] = was[kept[h, moves]]
+            want[t, table, :, 0, h] = now.reshape(pages, page, 128)
+    k = torch.empty(1, H, n, 128, dtype=torch.bfloat16, device=DEV)              # sizes only
+    ratio = rows / n
+    assert C.compactor_keep_count(n, ratio) == rows
+    pages_of = [pool[t].view(torch.bfloat16).permute(0, 2, 1, 3, 4) for t in range(2)]
+    C.compactor_compact_paged(C.Params(1, H, sketch_dim=48), [C.Request(k_score=k, v_cache=k, ratio=ratio)],
+                              torch.from_numpy(kept).to(DEV).view(-1),
+                              torch.full((H,), rows, dtype=torch.int32, device=DEV), pages_of[0], pages_of[1],
+                              [torch.from_numpy(table).to(DEV)], in_place=True)
+    torch.cuda.synchronize()
+    assert np.array_equal(pool.cpu().numpy(), want)
+
+
 @pytest.mark.parametrize("in_place", [False, True])
 def test_compact_into_pages(C, in_place):
     _say("paged target, in_place=%s: head scope and layer scope, ragged batch, page sizes 16 and 7" % in_place)
