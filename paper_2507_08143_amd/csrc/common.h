@@ -104,6 +104,19 @@ __host__ __device__ __forceinline__ int blocks_per_head(int units, int per_block
   return (int)((u + c - 1) / c);
 }
 
+// Tokens of a chunk that begins at `begin` of a head of n.  (Differences only: begin + chunk, or a token that far past a
+// head's end, does not fit an int in a head of nearly 2^31.)
+__host__ __device__ __forceinline__ int chunk_tokens(int begin, int chunk, int n) {
+  return chunk < n - begin ? chunk : n - begin;
+}
+// Where the 16-byte load of the four tokens from begin + at on begins, as the place of the chunk's last four tokens or
+// of its first one, and a distance from there: the tokens themselves, or the last four where they reach past the end.
+__host__ __device__ __forceinline__ int quad_base(int begin, int tokens) { return tokens < 4 ? begin + tokens - 4 : begin; }
+__host__ __device__ __forceinline__ int quad_from_base(int at, int tokens) {
+  const int last = tokens < 4 ? 0 : tokens - 4;
+  return at < last ? at : last;
+}
+
 __device__ __forceinline__ Where locate_block(const SegTable &T, int blk, int per_block, int step,
                                               bool by_keep) {
   Where w{0, 0, 0, 0, 0};

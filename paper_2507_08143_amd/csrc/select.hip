@@ -93,30 +93,31 @@ template <int NT, int R>
 __device__ __forceinline__ void load_scores(const float *__restrict__ sp, int begin, int end, int r0,
                                             float (&f)[R][4]) {
   typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
-  const int i0 = begin + 4 * (r0 * NT + (int)threadIdx.x);
-  const int last4 = end - 4;
-  if (last4 >= 0) {                      // uniform
+  const int at = 4 * (r0 * NT + (int)threadIdx.x), tokens = end - begin;
+  if (end >= 4) {                        // uniform
+    const char *base = reinterpret_cast<const char *>(sp + quad_base(begin, tokens));        // uniform
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      const f32x4_any v = *reinterpret_cast<const f32x4_any *>(sp + min(i0 + 4 * r * NT, last4));
+      const f32x4_any v = *reinterpret_cast<const f32x4_any *>(base + 4u * (unsigned)quad_from_base(at + 4 * r * NT, tokens));
       f[r][0] = v.x; f[r][1] = v.y; f[r][2] = v.z; f[r][3] = v.w;
     }
   } else {                               // a head of up to three tokens
 #pragma unroll
     for (int r = 0; r < R; ++r)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) f[r][e] = r == 0 && i0 + e < end ? sp[e] : 0.f;
+      for (int e = 0; e < 4; ++e) f[r][e] = r == 0 && at + e < tokens ? sp[e] : 0.f;
   }
 }
 // Returns the bits of the tokens that exist; what f holds of others is any number.
 template <int NT, int R>
 __device__ __forceinline__ unsigned place_scores(int begin, int end, int r0, float (&f)[R][4]) {
   unsigned valid = 0xffffffffu >> (32 - 4 * R);
-  if (begin + 4 * (r0 + R) * NT > end) {          // uniform: some do not exist
+  const int tokens = end - begin;
+  if (4 * (r0 + R) * NT > tokens) {      // uniform: some do not exist
     valid = 0;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      const int have = end - (begin + 4 * ((r0 + r) * NT + (int)threadIdx.x));
+      const int have = tokens - 4 * ((r0 + r) * NT + (int)threadIdx.x);
       valid |= ((1u << min(max(have, 0), 4)) - 1u) << (4 * r);
       if (have > 0 && have < 4 && end >= 4) {
         if (have < 3) { f[r][0] = f[r][2]; f[r][1] = f[r][3]; }
@@ -381,7 +382,7 @@ __device__ __forceinline__ SelWhere sel_locate(const SegTable &T, int blk) {
   q.tile = local - hh * s.sel_bph;
   q.pool = T.layer_scope ? s.pool0 + hh / s.H : s.pool0 + hh;
   q.tok_begin = q.tile * s.sel_chunk;
-  q.tok_end = min(s.n, q.tok_begin + s.sel_chunk);
+  q.tok_end = q.tok_begin + chunk_tokens(q.tok_begin, s.sel_chunk, s.n);
   return q;
 }
 
@@ -751,8 +752,10 @@ __device__ __forceinline__ void for_each_cand(const uint32_t *__restrict__ l, in
 // One workgroup per pool: the threshold key from the pool's candidates, then for every chunk of
 // the pool (in head, token order) the position of its first retained token in the pool's
 // output and how many threshold ties it may keep; the per-head counts.  The candidates' rank comes from the
-// chunks' counts; where it says that the threshold is none of them (a sampled bracket that missed), the
-// threshold and the counts come from all scores of the pool instead (ST_FULL), in five more passes.
+// chunks' counts; where it says that the threshold is none of them (a sampled bracket that missed), all scores
+// of the pool take their place (ST_FULL), in three passes.  One workgroup reads them then: whole selection on MI355X, us
+// where no bracket misses / where all do, 112 heads of 131072 43.6 / 123, 128 of 40003 34.6 / 64, 16 layers of 8 x 131072
+// 65 / 514 (one 4-byte load in flight a thread: 248, 62 and 1567).
 // Two passes over the candidates: (1) histogram of the upper 12 bits in which they differ -> second
 // digit d2; (2) per chunk the count above d2, a histogram of the low bits (5, 8 or 11) of those inside d2,
 // and those few themselves as (chunk, low bits) in a short LDS list, from which, once the last digit is
@@ -797,25 +800,30 @@ __global__ __launch_bounds__(THR_THREADS) void msel_thr_kernel(const SegTable T,
   const int nchunks = ph * bph;
   const bool single = nchunks <= THR_BLOCK;      // all records fit LDS at once
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  // candidate list of chunk c of the pool
-  auto list_of = [&](int c) { return cand + tok0 + (long long)(c / bph) * s.n + (long long)(c % bph) * csize; };
+  uint32_t lo = (uint32_t)state[pool * SEL_STATE + ST_LO];
+  const uint32_t span = (uint32_t)state[pool * SEL_STATE + ST_HI] - lo;
+  const float *sp = scores + s.score_off + (long long)head0 * s.n;
+  bool full = false;                             // all scores are looked at, as candidates of the range of all keys
+  auto tokens_of = [&](int c) { return chunk_tokens(c % bph * csize, csize, s.n); };
+  // the candidates of chunk c of the pool, or its scores
+  auto list_of = [&](int c) {
+    const long long at = (long long)(c / bph) * s.n + (long long)(c % bph) * csize;
+    return SAMPLED && full ? reinterpret_cast<const uint32_t *>(sp + at) : cand + tok0 + at;
+  };
   // records of the chunks [cb, cb + THR_BLOCK) into LDS
   auto fetch = [&](int cb) {
     __syncthreads();
     for (int u = tid; u < THR_BLOCK && cb + u < nchunks; u += THR_THREADS) {
-      const i32x2_any r = *reinterpret_cast<const i32x2_any *>(rec + 2 * (chunk0 + cb + u));
+      i32x2_any r = *reinterpret_cast<const i32x2_any *>(rec + 2 * (chunk0 + cb + u));
+      if (SAMPLED && full) r = i32x2_any{0, tokens_of(cb + u)};
       above_c[u] = r.x;
       cnt_c[u] = r.y;
     }
     __syncthreads();
   };
 
-  const uint32_t lo = (uint32_t)state[pool * SEL_STATE + ST_LO];
-  const uint32_t span = (uint32_t)state[pool * SEL_STATE + ST_HI] - lo;
-  int bits = span ? 32 - __clz((int)span) : 0;           // of a candidate's value
   // the candidates of rank 1 .. inside are inside
   int need = ph * s.k_keep;
-  bool full = false;
   for (int i = tid; i < 4096; i += THR_THREADS) hist[i] = 0;
   if (tid == 0) nshort = 0;
   {
@@ -835,31 +843,33 @@ __global__ __launch_bounds__(THR_THREADS) void msel_thr_kernel(const SegTable T,
       full = need < 1 || need > all;
     }
   }
+  int bits = span ? 32 - __clz((int)span) : 0;           // of a candidate's value
+  if (SAMPLED && full) {
+    lo = 0;
+    bits = 32;
+    need = ph * s.k_keep;
+    if (single) fetch(0);
+  }
+  // (a word of all ones or none, and not a branch, so that the loops over candidates exist once)
+  const uint32_t keys = SAMPLED && full ? 0xffffffffu : 0u;
+  auto for_each_value = [&](int c, int cnt, auto &&f) {
+    for_each_cand(list_of(c), cnt, lane, [&](uint32_t v) {
+      if (SAMPLED) v ^= (score_key(__uint_as_float(v)) ^ v) & keys;
+      f(v);
+    });
+  };
   uint32_t base = 0;                                     // the threshold's value lies in [base, base + 2^bits)
-  const int npool = ph * s.n;
-  const float *sp = scores + s.score_off + (long long)head0 * s.n;
-  // the 12 bits from `rest` on of the values (or, full, of the keys) in [base, base + 2^(rest + 12))
+  // the 12 bits from `rest` on of the values in [base, base + 2^(rest + 12))
   auto tally = [&](int rest) {
-    if (SAMPLED && full) {
-      for (int i = tid; i < npool; i += THR_THREADS) {
-        const uint32_t d = (score_key(sp[i]) - base) >> rest;
-        if (d < 4096) atomicAdd(&hist[d], 1);
-      }
-      return;
-    }
     for (int cb = 0; cb < nchunks; cb += THR_BLOCK) {
       if (!single) fetch(cb);
       for (int u = wave; u < THR_BLOCK && cb + u < nchunks; u += NW)
-        for_each_cand(list_of(cb + u), cnt_c[u], lane, [&](uint32_t v) {
+        for_each_value(cb + u, cnt_c[u], [&](uint32_t v) {
           const uint32_t d = (v - base) >> rest;
           if (!SAMPLED || d < 4096) atomicAdd(&hist[d], 1);
         });
     }
   };
-  if (SAMPLED && full) {
-    bits = 32;
-    need = ph * s.k_keep;
-  }
   if (SAMPLED && bits > 23) {                            // one pass more
     tally(bits - 12);
     __syncthreads();
@@ -880,21 +890,13 @@ __global__ __launch_bounds__(THR_THREADS) void msel_thr_kernel(const SegTable T,
   // pass 2: the low bits of the candidates that share the second digit; per chunk those above it
   // (none: d2 is the whole value, and the third pass counts)
   const bool third = SAMPLED && rest == 0;
-  if (!third)
+  if (!third) {
     for (int i = tid; i <= (int)low; i += THR_THREADS) hist[i] = 0;
-  if (third) {
-  } else if (SAMPLED && full) {
-    __syncthreads();
-    for (int i = tid; i < npool; i += THR_THREADS) {
-      const uint32_t v = score_key(sp[i]) - base;
-      if (v <= low) atomicAdd(&hist[v], 1);
-    }
-  } else {
     for (int cb = 0; cb < nchunks; cb += THR_BLOCK) {
       if (!single) fetch(cb); else __syncthreads();
       for (int u = wave; u < THR_BLOCK && cb + u < nchunks; u += NW) {
         int gt = 0;
-        for_each_cand(list_of(cb + u), cnt_c[u], lane, [&](uint32_t v) {
+        for_each_value(cb + u, cnt_c[u], [&](uint32_t v) {
           gt += v > top;
           if (v - base <= low) {
             atomicAdd(&hist[v - base], 1);
@@ -914,12 +916,12 @@ __global__ __launch_bounds__(THR_THREADS) void msel_thr_kernel(const SegTable T,
   const uint32_t d3 = third ? 0u : (uint32_t)find_digit<THR_THREADS>(hist, 1 << rest, &need, wsum, found);
   const int tie_keep = need;             // keys equal to the threshold that are retained
   const bool all_ties = hist[third ? d2 : d3] == need;
-  const uint32_t at_v = base + d3, thr = SAMPLED && full ? at_v : lo + at_v;     // the threshold's value and key
+  const uint32_t at_v = base + d3;       // the threshold's value
   if (tid == 0) {
-    state[pool * SEL_STATE + ST_THR] = (int)thr;
+    state[pool * SEL_STATE + ST_THR] = (int)(lo + at_v);
     state[pool * SEL_STATE + ST_FULL] = full;
   }
-  const bool from_short = single && !full && !third && nshort <= THR_SHORT;
+  const bool from_short = single && !third && nshort <= THR_SHORT;
   if (from_short) {                      // the chunks' counts at the last digit, from the short list
     for (int i = tid; i < nshort; i += THR_THREADS) {
       const uint32_t e = short_l[i];
@@ -937,20 +939,10 @@ __global__ __launch_bounds__(THR_THREADS) void msel_thr_kernel(const SegTable T,
       if (!single) fetch(cb); else __syncthreads();
       for (int u = wave; u < THR_BLOCK && cb + u < nchunks; u += NW) {
         int gt = 0, eq = 0;
-        if (SAMPLED && full) {
-          const int t0 = (cb + u) % bph * csize, cnt = min(csize, s.n - t0);
-          const float *cp = sp + (long long)((cb + u) / bph) * s.n + t0;
-          for (int i = lane; i < cnt; i += 64) {
-            const uint32_t key = score_key(cp[i]);
-            gt += key > thr;
-            eq += key == thr;
-          }
-        } else {
-          for_each_cand(list_of(cb + u), cnt_c[u], lane, [&](uint32_t v) {
-            gt += v > at_v;
-            eq += v == at_v;
-          });
-        }
+        for_each_value(cb + u, cnt_c[u], [&](uint32_t v) {
+          gt += v > at_v;
+          eq += v == at_v;
+        });
 #pragma unroll
         for (int d = 32; d >= 1; d >>= 1) {
           gt += __shfl_xor(gt, d);
@@ -970,7 +962,7 @@ __global__ __launch_bounds__(THR_THREADS) void msel_thr_kernel(const SegTable T,
         const int eq0 = eq_before + block_exclusive_scan<THR_THREADS>(eq, wsum, &eq_all);
         allow = max(0, min(eq, tie_keep - eq0));
       }
-      const int kept = mine ? (full ? 0 : above_c[u]) + gt_c[u] + allow : 0;
+      const int kept = mine ? above_c[u] + gt_c[u] + allow : 0;
       const int at = pos + block_exclusive_scan<THR_THREADS>(kept, wsum, &kept_all);
       if (mine) {
         *reinterpret_cast<i32x2_any *>(coff + 2 * (chunk0 + cc)) = i32x2_any{at, allow};
@@ -1156,7 +1148,7 @@ __global__ __launch_bounds__(CHUNK_THREADS) void blend_apply_kernel(
   const SelWhere q = sel_locate(T, HALF ? blockIdx.x >> 1 : blockIdx.x);
   const int r_first = HALF ? (int)(blockIdx.x & 1) * PART : 0;
   const Seg &s = T.s[q.seg];
-  if (s.attn == nullptr || q.tok_begin + 4 * r_first * CHUNK_THREADS >= q.tok_end) return;     // uniform
+  if (s.attn == nullptr || 4 * r_first * CHUNK_THREADS >= q.tok_end - q.tok_begin) return;     // uniform
   const int n = s.n, tid = threadIdx.x;
   float *o = scores + s.score_off + (long long)q.head * n;
   const float *a = s.attn + (long long)q.head * n;
@@ -1177,7 +1169,7 @@ __global__ __launch_bounds__(CHUNK_THREADS) void blend_apply_kernel(
 #pragma unroll 1
   for (int r0 = r_first; r0 < (HALF ? r_first + PART : SEL_ROUNDS); r0 += PART) {
     if (!HALF) {
-      if (q.tok_begin + 4 * r0 * CHUNK_THREADS >= q.tok_end) break;       // uniform
+      if (4 * r0 * CHUNK_THREADS >= q.tok_end - q.tok_begin) break;       // uniform
       load_scores<CHUNK_THREADS, PART>(a, q.tok_begin, q.tok_end, r0, fa);
       load_scores<CHUNK_THREADS, PART>(o, q.tok_begin, q.tok_end, r0, fo);
     }

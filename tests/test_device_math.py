@@ -41,6 +41,28 @@ def test_in_place_rows_up_to_the_largest_context(M, run_rows):
                     assert bool(M.inplace_moves(j + 1, j, most)) == (j + 1 < most)
 
 
+@pytest.mark.parametrize("n", [1, 4, 5, 8192, 8193, 32771, 1000003, 2 ** 31 - 8191, 2 ** 31 - 1100, 2 ** 31 - 65])
+def test_chunks_of_a_head_up_to_the_largest_context(M, n):
+    """The chunks of the pooled selection cover a head's tokens once, and every load of four tokens that a thread
+    issues for its rounds lies inside the head, also where the tokens themselves lie past its end."""
+    blocks, chunk = C.c_int(), C.c_int()
+    M.head_chunks(n, 8192, C.byref(blocks), C.byref(chunk))
+    blocks, chunk = blocks.value, chunk.value
+    assert 0 < chunk <= 8192 and chunk % 4 == 0
+    for tile in {0, 1, blocks // 2, blocks - 2, blocks - 1} & set(range(blocks)):
+        begin = tile * chunk
+        tokens = M.chunk_tokens(begin, chunk, n)
+        assert tokens == (chunk if tile + 1 < blocks else n - begin) and 0 < tokens <= chunk
+        if n >= 4:
+            for at in range(0, 8192, 4):
+                first = M.quad_at(begin, at, tokens)
+                assert 0 <= first <= n - 4
+                if at + 4 <= tokens:
+                    assert first == begin + at
+                elif at < tokens:
+                    assert first + 4 == begin + tokens
+
+
 def _key(x):
     u = int(np.float32(x).view(np.uint32))
     return ~u & 0xffffffff if u >> 31 else u | 0x80000000

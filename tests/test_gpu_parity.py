@@ -207,6 +207,35 @@ def test_select_where_the_sample_misleads(C, kind, H, n, ratio, scope):
     _select_case(C, [n], [ratio], 1, H, maker, 44, scope)
 
 
+# the largest context: tokens are numbered up to the last ints, in the chunks and, where the sample misleads, in
+# the passes over all scores
+@pytest.mark.parametrize("misled", [False, True])
+def test_select_from_the_largest_head(C, misled):
+    n, ratio = 2 ** 31 - 65, 1e-3
+    if torch.cuda.mem_get_info()[0] < 60e9:
+        pytest.skip("needs 60 GB")
+    g = torch.Generator(device=DEV)
+    g.manual_seed(46)
+    s = torch.empty(n, dtype=torch.float32, device=DEV)
+    for i in range(0, n, 1 << 28):
+        s[i:i + (1 << 28)].uniform_(generator=g)
+    if misled:
+        s[torch.from_numpy(_sampled(n, 0)).to(DEV).view(-1)] = 7.0
+    row = torch.zeros(1, 1, 1, 128, dtype=torch.bfloat16, device=DEV).expand(1, 1, n, 128)     # sizes only
+    kept, cnt = C.compactor_select(C.Params(1, 1, sketch_dim=48), [C.Request(k_score=row, v_cache=row, ratio=ratio)], s)
+    k = C.compactor_keep_count(n, ratio)
+    assert int(cnt[0]) == k == kept.numel() and bool((kept[1:] > kept[:-1]).all()) and int(kept[0]) >= 0
+    got = s[kept.long()]
+    thr = got.min()
+    above = eq = 0
+    last = int(kept[got == thr][-1])
+    for i in range(0, n, 1 << 28):
+        x = s[i:i + (1 << 28)]
+        above += int((x > thr).sum())
+        eq += int((x[:max(0, last + 1 - i)] == thr).sum())
+    assert above == int((got > thr).sum()) and eq == k - above       # ties: the lower tokens
+
+
 def test_select_many_chunks_all_equal(C):
     _select_case(C, [17001], [0.4], 1, 180, lambda r, m: np.full(m, -0.5), 9, scope=C.SCOPE_LAYER)
 
