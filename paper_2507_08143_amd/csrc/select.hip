@@ -752,10 +752,11 @@ __device__ __forceinline__ void for_each_cand(const uint32_t *__restrict__ l, in
 // One workgroup per pool: the threshold key from the pool's candidates, then for every chunk of
 // the pool (in head, token order) the position of its first retained token in the pool's
 // output and how many threshold ties it may keep; the per-head counts.  The candidates' rank comes from the
-// chunks' counts; where it says that the threshold is none of them (a sampled bracket that missed), all scores
-// of the pool take their place (ST_FULL), in three passes.  One workgroup reads them then: whole selection on MI355X, us
-// where no bracket misses / where all do, 112 heads of 131072 43.6 / 123, 128 of 40003 34.6 / 64, 16 layers of 8 x 131072
-// 65 / 514 (one 4-byte load in flight a thread: 248, 62 and 1567).
+// chunks' counts; where it says that the threshold is none of them (a sampled bracket that missed), the keys of all scores
+// of the pool take their place (ST_FULL).  One workgroup goes over them then: whole selection on MI355X, us where no
+// bracket misses / where all do, 32 heads of 40003 28.1 / 55.5, 17 layers of 8 x 131072 66.9 / 536 (with the scores
+// themselves, one 4-byte load in flight a thread, in every pass, 1564; the candidates' loops serve both, and a key made of
+// a score in them, where it is not needed, cost 5 to 20 % of a selection of long pools).
 // Two passes over the candidates: (1) histogram of the upper 12 bits in which they differ -> second
 // digit d2; (2) per chunk the count above d2, a histogram of the low bits (5, 8 or 11) of those inside d2,
 // and those few themselves as (chunk, low bits) in a short LDS list, from which, once the last digit is
@@ -775,7 +776,7 @@ constexpr int THR_BLOCK = 512, THR_SHORT = 2048, THR_WIDE_POOLS = 256;
 template <int THR_THREADS, bool SAMPLED>
 __global__ __launch_bounds__(THR_THREADS) void msel_thr_kernel(const SegTable T,
                                                                const float *__restrict__ scores,
-                                                               const uint32_t *__restrict__ cand,
+                                                               uint32_t *__restrict__ cand,
                                                                const int *__restrict__ rec,
                                                                int *__restrict__ coff,
                                                                int *__restrict__ state,
@@ -802,14 +803,11 @@ __global__ __launch_bounds__(THR_THREADS) void msel_thr_kernel(const SegTable T,
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   uint32_t lo = (uint32_t)state[pool * SEL_STATE + ST_LO];
   const uint32_t span = (uint32_t)state[pool * SEL_STATE + ST_HI] - lo;
-  const float *sp = scores + s.score_off + (long long)head0 * s.n;
-  bool full = false;                             // all scores are looked at, as candidates of the range of all keys
+  bool full = false;                             // the keys of all scores are the candidates' values
   auto tokens_of = [&](int c) { return chunk_tokens(c % bph * csize, csize, s.n); };
-  // the candidates of chunk c of the pool, or its scores
-  auto list_of = [&](int c) {
-    const long long at = (long long)(c / bph) * s.n + (long long)(c % bph) * csize;
-    return SAMPLED && full ? reinterpret_cast<const uint32_t *>(sp + at) : cand + tok0 + at;
-  };
+  // where chunk c of the pool begins among the pool's tokens; its candidate list
+  auto token_of = [&](int c) { return (long long)(c / bph) * s.n + (long long)(c % bph) * csize; };
+  auto list_of = [&](int c) { return cand + tok0 + token_of(c); };
   // records of the chunks [cb, cb + THR_BLOCK) into LDS
   auto fetch = [&](int cb) {
     __syncthreads();
@@ -848,23 +846,25 @@ __global__ __launch_bounds__(THR_THREADS) void msel_thr_kernel(const SegTable T,
     lo = 0;
     bits = 32;
     need = ph * s.k_keep;
+    // the lists have room for every token, and the emit does not look at the marks behind them
+    const float *sp = scores + s.score_off + (long long)head0 * s.n;
+    for (int c = wave; c < nchunks; c += NW) {
+      const float *from = sp + token_of(c);
+      uint32_t *to = list_of(c);
+      const int tokens = tokens_of(c);
+#pragma unroll 8
+      for (int i = lane; i < tokens; i += 64) to[i] = score_key(from[i]);
+    }
     if (single) fetch(0);
+    __syncthreads();                                     // the lists are complete
   }
-  // (a word of all ones or none, and not a branch, so that the loops over candidates exist once)
-  const uint32_t keys = SAMPLED && full ? 0xffffffffu : 0u;
-  auto for_each_value = [&](int c, int cnt, auto &&f) {
-    for_each_cand(list_of(c), cnt, lane, [&](uint32_t v) {
-      if (SAMPLED) v ^= (score_key(__uint_as_float(v)) ^ v) & keys;
-      f(v);
-    });
-  };
   uint32_t base = 0;                                     // the threshold's value lies in [base, base + 2^bits)
   // the 12 bits from `rest` on of the values in [base, base + 2^(rest + 12))
   auto tally = [&](int rest) {
     for (int cb = 0; cb < nchunks; cb += THR_BLOCK) {
       if (!single) fetch(cb);
       for (int u = wave; u < THR_BLOCK && cb + u < nchunks; u += NW)
-        for_each_value(cb + u, cnt_c[u], [&](uint32_t v) {
+        for_each_cand(list_of(cb + u), cnt_c[u], lane, [&](uint32_t v) {
           const uint32_t d = (v - base) >> rest;
           if (!SAMPLED || d < 4096) atomicAdd(&hist[d], 1);
         });
@@ -896,7 +896,7 @@ __global__ __launch_bounds__(THR_THREADS) void msel_thr_kernel(const SegTable T,
       if (!single) fetch(cb); else __syncthreads();
       for (int u = wave; u < THR_BLOCK && cb + u < nchunks; u += NW) {
         int gt = 0;
-        for_each_value(cb + u, cnt_c[u], [&](uint32_t v) {
+        for_each_cand(list_of(cb + u), cnt_c[u], lane, [&](uint32_t v) {
           gt += v > top;
           if (v - base <= low) {
             atomicAdd(&hist[v - base], 1);
@@ -939,7 +939,7 @@ __global__ __launch_bounds__(THR_THREADS) void msel_thr_kernel(const SegTable T,
       if (!single) fetch(cb); else __syncthreads();
       for (int u = wave; u < THR_BLOCK && cb + u < nchunks; u += NW) {
         int gt = 0, eq = 0;
-        for_each_value(cb + u, cnt_c[u], [&](uint32_t v) {
+        for_each_cand(list_of(cb + u), cnt_c[u], lane, [&](uint32_t v) {
           gt += v > at_v;
           eq += v == at_v;
         });
