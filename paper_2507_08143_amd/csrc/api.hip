@@ -410,7 +410,7 @@ int enqueue_compress(const compactor_params_t *p, const compactor_request_t *req
     int *hist1 = reinterpret_cast<int *>(ws + gb.off_hist1());
     if (select_needs_pools(T)) {
       int *sel = reinterpret_cast<int *>(ws + gb.off_sel());
-      HIP_TRY(launch_select_pools(T, sc, hist1, sel, kept_idx, kept_cnt, st));
+      HIP_TRY(launch_select_pools(T, sc, hist1, nullptr, sel, kept_idx, kept_cnt, st));
     } else {
       HIP_TRY(launch_select(T, sc, hist1, kept_idx, kept_cnt, st));
     }
@@ -554,8 +554,9 @@ int compactor_select(const compactor_params_t *p, const compactor_request_t *req
   return for_each_group(p, reqs, nreq, grows, false, [&](const SegTable &T, long long) {
     if (select_needs_pools(T)) {
       const GroupBytes gb = group_bytes_needed(p, T, false);
+      int *tally = select_by_tally(T) ? static_cast<int *>(workspace) : nullptr;
       int *sel = reinterpret_cast<int *>(static_cast<unsigned char *>(workspace) + gb.hist1);
-      HIP_TRY(launch_select_pools(T, scores, nullptr, sel, kept_idx, kept_cnt, st));
+      HIP_TRY(launch_select_pools(T, scores, nullptr, tally, sel, kept_idx, kept_cnt, st));
     } else {
       HIP_TRY(launch_select(T, scores, nullptr, kept_idx, kept_cnt, st));
     }

@@ -150,8 +150,8 @@ __device__ __forceinline__ uint32_t score_key(float s) {
 }
 
 // First digit of the selection, two ways.  Scores that leave the scoring kernels are tallied there by
-// their top 12 key bits (8 bins an octave).  Scores of a separate selection call (all of a head in select_kernel,
-// a sample of a pool in msel_sample_kernel) are tallied by
+// their top 12 key bits (8 bins an octave).  Scores of a separate selection call (all of a head or pool in
+// select_kernel and msel_hist1_kernel, a sample of a pool in msel_sample_kernel) are tallied by
 // score_bin, a monotone map of the keys that is finer where thresholds lie: magnitudes from 2^-18 up to
 // 2^4, where leverage scores and z-scores have them, have 64 bins an octave, 24 octaves on either side 8,
 // and those beyond (below 2^-42, from 2^28 on) one each; negative numbers
@@ -420,9 +420,9 @@ hipError_t launch_select(const SegTable &T, const float *scores, const int *hist
                          int32_t *kept_idx, int32_t *kept_cnt, hipStream_t st);
 
 // Selection by several workgroups per pool (long heads, or layer scope).  hist1: pools x 4096
-// ints, the histogram of the scores' top 12 key bits, or null.  sel: scratch of select_scratch(T).ints() ints (candidate lists,
-// one slot per token of the launch; per-chunk records and offsets; per-pool state), none of which
-// needs clearing.
+// ints, the histogram of the scores' top 12 key bits, or null.  tally: room for as many, where select_by_tally()
+// holds and hist1 is null, else null.  sel: scratch of select_scratch(T).ints() ints (candidate lists,
+// one slot per token of the launch; per-chunk records and offsets; per-pool state).  Neither needs clearing.
 struct SelectScratch {
   int pools;
   long long chunks, cand_ints, rec_ints, coff_ints, state_ints;
@@ -430,7 +430,8 @@ struct SelectScratch {
 };
 SelectScratch select_scratch(const SegTable &T);
 bool select_needs_pools(const SegTable &T);
-hipError_t launch_select_pools(const SegTable &T, const float *scores, const int *hist1, int *sel,
+bool select_by_tally(const SegTable &T);
+hipError_t launch_select_pools(const SegTable &T, const float *scores, const int *hist1, int *tally, int *sel,
                                int32_t *kept_idx, int32_t *kept_cnt, hipStream_t st);
 
 // kept_cnt is read in layer scope only (ragged heads inside a layer's region).

@@ -331,8 +331,8 @@ __global__ __launch_bounds__(SELECT_THREADS) void select_kernel(const SegTable T
 // emit as above, with the scores read once or twice in all.  A pool (head or layer) is cut into chunks of
 // up to 8192 tokens of one head, one workgroup each; three launches:
 //   cand   a range of keys that holds the threshold: a bin of the pool's histogram (made by the score
-//          kernel or the blend), or, for scores that come without one, a bracket from a sample
-//          (msel_sample_kernel).  Keys above the range are retained for sure and only marked and
+//          kernel or the blend), or, for scores that come without one, a bin of a tally of all of them
+//          (msel_hist1_kernel) or a bracket from a sample (msel_sample_kernel).  Keys above the range are retained for sure and only marked and
 //          counted; the keys inside it (the candidates: 2 to 25 % of the pool unless the
 //          scores are heavily tied) are marked and leave their distance from its lower end in a
 //          per-chunk list
@@ -437,7 +437,7 @@ __device__ __forceinline__ void flush_hist(const int *hist, int nb, int *__restr
   }
 }
 
-// ---- scores that came without a histogram: a bracket of the threshold from a sample ----
+// ---- scores that came without a histogram: one by a tally, or a bracket of the threshold from a sample ----
 // The threshold is the K-th largest of a pool's N scores (contiguous in memory: a pool is whole heads).
 // One workgroup per pool reads a sample of m scores, half a 128-byte line at a hashed place in each of
 // equal stretches, and takes the order statistics of the sample `margin` places on either side of
@@ -448,13 +448,11 @@ __device__ __forceinline__ void flush_hist(const int *hist, int nb, int *__restr
 // all scores of a pool where the threshold is in neither.  Pools of up to SAMPLE_WHOLE scores are read whole.
 // Half lines, because a compute unit takes about 7 ns a line from memory however much of it is used (112 heads
 // of 131072 tokens: 15 us for this kernel with 2048 groups of four, 8192 scores either way, against 11).
-// Against a histogram over all scores, which was another pass over them, as long as the candidates', with a
-// launch to clear it, and 16 KB that every chunk searched: whole selection on MI355X, us before / now,
-// leverage scores, 112 heads of 131072 tokens 57.5 / 43.3; 8 heads of 131072 32 / 33; heads of 40003, 128 of them
-// 40.6 / 37.0, 600 88.6 / 75.7, 4096 of 33000 426 / 356; layers of 8 x 8192, 256 of them 67.5 / 49.7, of
-// 8 x 131072, one 53.1 / 52.6.  Scores averaged over 7 neighbours, the same: 32.8 / 33.4, 41.5 / 37.8, 87.7 /
-// 80.6, 419 / 376, 66.5 / 53.5, 54.7 / 55.7; over 63 neighbours the bracket is wider: 33.5 / 36.4, 42.9 / 40.6,
-// 94.1 / 87.5, 442 / 413, 72.2 / 58.9, and 53.9 / 73.6, where one pool has a quarter of a million candidates.
+// Against a tally of all scores (msel_hist1_kernel), which is another pass over them, as long as the candidates', with a
+// launch to clear the histogram, and 16 KB that every chunk searches.  Whole selection on MI355X (graph replay), us
+// sampled / tallied, leverage scores, then averaged over 63 neighbours: 128 heads of 40003 32.3 / 36.4, 38.4 / 43.3, 128 layers of
+// 8 x 8192 36.1 / 41.3, 43.3 / 48.9, 256 of 8 x 4096 40.7 / 48.6, 45.5 / 54.3.  Few long pools are tallied all the
+// same: select_by_tally.
 constexpr int SAMPLE_THREADS = 1024, SAMPLE_ROUNDS = 2, SAMPLE_WAVES = SAMPLE_THREADS / 64;
 static_assert(SAMPLE_ROUNDS * SAMPLE_THREADS * 4 == SAMPLE_WHOLE, "a whole pool fits the registers");
 
@@ -618,11 +616,41 @@ __global__ __launch_bounds__(SAMPLE_THREADS) void msel_sample_kernel(const SegTa
   }
 }
 
+// First digit by a tally of all scores, into the pool's histogram (zero on entry).
+__global__ __launch_bounds__(CHUNK_THREADS, 8) void msel_hist1_kernel(const SegTable T,
+                                                                    const float *__restrict__ scores,
+                                                                    int *__restrict__ hist1) {
+  __shared__ int hist[HIST1_BINS];
+  const SelWhere q = sel_locate(T, blockIdx.x);
+  const Seg &s = T.s[q.seg];
+  const float *sp = scores + s.score_off + (long long)q.head * s.n;
+  float f[SEL_ROUNDS][4];
+  load_scores<CHUNK_THREADS, SEL_ROUNDS>(sp, q.tok_begin, q.tok_end, 0, f);
+  for (int i = threadIdx.x; i < HIST1_BINS; i += CHUNK_THREADS) hist[i] = 0;
+  __syncthreads();
+  const unsigned valid = place_scores<CHUNK_THREADS, SEL_ROUNDS>(q.tok_begin, q.tok_end, 0, f);
+#pragma unroll
+  for (int r = 0; r < SEL_ROUNDS; ++r)
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (valid >> (4 * r + e) & 1) atomicAdd(&hist[score_bin(score_key(f[r][e]))], 1);
+  __syncthreads();
+  flush_hist<CHUNK_THREADS>(hist, HIST1_BINS, hist1 + (size_t)q.pool * HIST1_BINS);
+}
+
+// (a small kernel, not a memset: callers may capture the call into a graph)
+__global__ __launch_bounds__(256) void fill_zero_kernel(int *__restrict__ z, long long count) {
+  zero_slice(z, count);
+}
+
+// Where a pool's range of candidates comes from: the histogram that came with the scores (top 12 key bits), one made by
+// msel_hist1_kernel (score_bin), or msel_sample_kernel.
+enum Range { CAME, TALLIED, SAMPLED_RANGE };
+
 // Candidates of a chunk: counts the keys above the range that holds the threshold and lists the
 // keys inside it, less its lowest (cand, at the chunk's position in the launch's token sequence, so a list can
 // never outgrow its room), and marks both kinds for the emit.  rec[chunk] = (keys above, candidates listed).
-// SAMPLED: the range comes from msel_sample_kernel, else from the pool's histogram.
-template <bool SAMPLED>
+template <Range RANGE>
 __global__ __launch_bounds__(CHUNK_THREADS, 7) void msel_cand_kernel(const SegTable T,
                                                                   const float *__restrict__ scores,
                                                                   const int *__restrict__ hist1,
@@ -632,6 +660,7 @@ __global__ __launch_bounds__(CHUNK_THREADS, 7) void msel_cand_kernel(const SegTa
   __shared__ int wsum[CHUNK_THREADS / 64];
   __shared__ int found[2];
   __shared__ int above_s, ncand_s;
+  constexpr bool SAMPLED = RANGE == SAMPLED_RANGE;
   constexpr int CAND_STAGE = 768;        // of at most 2048 a wave
   __shared__ __attribute__((aligned(16))) uint32_t stage[CHUNK_THREADS / 64][CAND_STAGE];
   const SelWhere q = sel_locate(T, blockIdx.x);
@@ -648,7 +677,7 @@ __global__ __launch_bounds__(CHUNK_THREADS, 7) void msel_cand_kernel(const SegTa
   } else {
     const int ph = pool_heads(T, s);
     int need = ph * s.k_keep;
-    const BinKeys bk = bin_keys(find_digit_global(hist1 + (size_t)q.pool * HIST1_BINS, &need, wsum, found), false);
+    const BinKeys bk = bin_keys(find_digit_global(hist1 + (size_t)q.pool * HIST1_BINS, &need, wsum, found), RANGE == TALLIED);
     lo = bk.lo;
     hi = bk.lo | ((1u << bk.bits) - 1u);
     if (q.tile == 0 && q.lhead % ph == 0 && threadIdx.x == 0) {   // the pool's first chunk
@@ -1228,7 +1257,31 @@ SelectScratch select_scratch(const SegTable &T) {
 
 long long select_chunks(const SegTable &T) { return total_blocks(T, SEL_CHUNK, 4, false); }
 
-hipError_t launch_select_pools(const SegTable &T, const float *scores, const int *hist1, int *sel,
+// Whether the first digit of a launch's pools comes from a tally of all scores and not from a sample: few pools, one of
+// them long.  A tally is a pass over the scores and a launch more; a sample's bracket widens with the pool and with
+// how alike neighbouring scores are, and one workgroup looks at what is inside it (and at all scores where it misses).
+// Whole selection on MI355X (graph replay), us sampled / tallied, for leverage scores, the same averaged over 7 and over
+// 63 neighbours: layers of 8 x 131072, 2 of them 49.0 / 47.5, 51.0 / 48.1, 70.2 / 53.7, 8 56.4 / 57.9, 60.2 / 59.0, 79.8 /
+// 66.7, 12 60.9 / 66.9, 64.2 / 67.9, 84.3 / 78.6; of 8 x 65536, 4 37.1 / 36.2, 40.0 / 37.2, 49.3 / 46.5, 12 41.1 /
+// 42.2, 43.9 / 43.3, 54.6 / 55.6; of 8 x 32768, 4 30.9 / 29.8, 32.1 / 30.2, 38.1 / 33.4, 12 31.8 / 32.1, 33.3 / 32.5,
+// 39.7 / 39.4; of 32 x 131072, 4 135 / 143, 142 / 143, 211 / 164, 8 149 / 169, 158 / 169, 232 / 198; heads of 131072, 8
+// of them 27.7 / 26.6, 28.4 / 27.3, 33.1 / 30.7, 32 30.0 / 30.3, 31.9 / 31.2, 37.1 / 35.9, 64 36.3 / 39.5, 38.2 / 40.8,
+// 44.0 / 47.4.  Shorter pools lose in a stream of calls, where the launch counts, what they gain on the card: 8 of 98304
+// 27.6 / 26.7 and 32.6 / 33.3, 8 of 80000 27.5 / 26.8 and 32.1 / 33.8, 8 of 131072 28.3 / 26.8 and 32.3 / 31.8.
+constexpr int TALLY_POOLS = 8, TALLY_POOL = 98304, TALLY_SCORES = 16 << 20;
+bool select_by_tally(const SegTable &T) {
+  long long pools = 0, longest = 0, rows = 0;
+  for (int i = 0; i < T.nseg; ++i) {
+    const Seg &s = T.s[i];
+    const long long pool = (long long)pool_heads(T, s) * s.n;
+    longest = pool > longest ? pool : longest;
+    pools += s.head_count / pool_heads(T, s);
+    rows += (long long)s.n * s.head_count;
+  }
+  return pools <= TALLY_POOLS && longest > TALLY_POOL && rows <= TALLY_SCORES;
+}
+
+hipError_t launch_select_pools(const SegTable &T, const float *scores, const int *hist1, int *tally, int *sel,
                                int32_t *kept_idx, int32_t *kept_cnt, hipStream_t st) {
   if (T.nheads <= 0) return hipSuccess;
   const SelectScratch z = select_scratch(T);
@@ -1236,13 +1289,21 @@ hipError_t launch_select_pools(const SegTable &T, const float *scores, const int
   uint32_t *cand = reinterpret_cast<uint32_t *>(sel);
   int *rec = sel + z.cand_ints, *coff = rec + z.rec_ints, *state = coff + z.coff_ints;
   const unsigned nb = (unsigned)z.chunks;
-  const bool sampled = hist1 == nullptr;
-  if (sampled) {
-    hipLaunchKernelGGL(msel_sample_kernel, dim3((unsigned)z.pools), dim3(SAMPLE_THREADS), 0, st, T, scores, state);
+  const Range range = hist1 != nullptr ? CAME : tally != nullptr ? TALLIED : SAMPLED_RANGE;
+  const bool sampled = range == SAMPLED_RANGE;
+  if (range == TALLIED) {
+    hipLaunchKernelGGL(fill_zero_kernel, dim3(256), dim3(256), 0, st, tally, (long long)z.pools * HIST1_BINS);
     if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
+    hipLaunchKernelGGL(msel_hist1_kernel, dim3(nb), dim3(CHUNK_THREADS), 0, st, T, scores, tally);
+  } else if (sampled) {
+    hipLaunchKernelGGL(msel_sample_kernel, dim3((unsigned)z.pools), dim3(SAMPLE_THREADS), 0, st, T, scores, state);
   }
-  hipLaunchKernelGGL(sampled ? msel_cand_kernel<true> : msel_cand_kernel<false>, dim3(nb), dim3(CHUNK_THREADS), 0, st,
-                     T, scores, hist1, cand, rec, state);
+  if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
+  const auto candidates = range == CAME      ? msel_cand_kernel<CAME>
+                          : range == TALLIED ? msel_cand_kernel<TALLIED>
+                                             : msel_cand_kernel<SAMPLED_RANGE>;
+  hipLaunchKernelGGL(candidates, dim3(nb), dim3(CHUNK_THREADS), 0, st, T, scores, range == TALLIED ? tally : hist1, cand,
+                     rec, state);
   if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
   const int threads = z.pools <= THR_WIDE_POOLS ? 1024 : 256;          // see msel_thr_kernel
   const auto thr = threads == 1024 ? (sampled ? msel_thr_kernel<1024, true> : msel_thr_kernel<1024, false>)

@@ -36,6 +36,11 @@ def _check_layer_selection(C, scores_b, kept, cnt, ko_b, k, b, L, H, n, what):
             pos += c
 
 
+def _smoothed(w):
+    """Leverage-like scores averaged over w neighbours, as a pooling window leaves them."""
+    return lambda r, m: np.convolve(r.chisquare(48, m + w - 1) / m, np.full(w, 1.0 / w), "valid")
+
+
 def _select_case(C, ns, ratios, L, H, maker, seed, scope=0):
     rng = np.random.default_rng(seed)
     params = C.Params(L, H, sketch_dim=48, select_scope=scope)
@@ -207,24 +212,53 @@ def test_select_where_the_sample_misleads(C, kind, H, n, ratio, scope):
     _select_case(C, [n], [ratio], 1, H, maker, 44, scope)
 
 
-# the largest context: tokens are numbered up to the last ints, in the chunks and, where the sample misleads, in
-# the passes over all scores
-@pytest.mark.parametrize("misled", [False, True])
-def test_select_from_the_largest_head(C, misled):
+# up to 8 pools and 2^24 scores, one pool longer than 98304, are tallied, others sampled: both sides of the limits, a long
+# pool beside short ones, scores that have been smoothed
+@pytest.mark.parametrize("maker", [_bin_edges, _smoothed(63)], ids=["edges", "smoothed"])
+@pytest.mark.parametrize("L,H,ns,ratios,scope", [
+    (1, 1, [98304], [0.3], 0), (1, 1, [98305], [0.3], 0), (1, 8, [98307], [0.2], 0), (1, 9, [98307], [0.2], 0),
+    (8, 3, [32769], [0.4], 1), (9, 3, [32769], [0.4], 1), (1, 2, [5, 98309, 9001], [0.5, 0.9, 0.02], 0),
+    (1, 20, [40003], [0.25], 1), (1, 1, [1 << 24], [0.1], 0), (1, 1, [(1 << 24) + 1], [0.1], 0)])
+def test_select_around_the_limits_of_the_tally(C, maker, L, H, ns, ratios, scope):
+    _select_case(C, ns, ratios, L, H, maker, 47, scope)
+
+
+# long pools, too many for a tally, whose samples mislead
+@pytest.mark.parametrize("kind", ["high", "low"])
+def test_select_where_the_samples_of_many_long_pools_mislead(C, kind):
+    n, H = 131075, 9
+
+    def maker(r, m):
+        s = r.random(m).reshape(H, n)
+        for i in range(0, H, 2):
+            s[i, _sampled(n, -(i * n) % 16)] = {"high": 7.0, "low": -3.0}[kind]
+        return s.ravel()
+    _select_case(C, [n], [0.3], 1, H, maker, 48)
+
+
+# the largest context: tokens are numbered up to the last ints, in the chunks and, where the sample misleads, in the
+# pass over all scores
+@pytest.mark.parametrize("others,misled", [(0, False), (0, True), (16, True)])
+def test_select_from_the_largest_head(C, others, misled):
     n, ratio = 2 ** 31 - 65, 1e-3
     if torch.cuda.mem_get_info()[0] < 60e9:
         pytest.skip("needs 60 GB")
     g = torch.Generator(device=DEV)
     g.manual_seed(46)
-    s = torch.empty(n, dtype=torch.float32, device=DEV)
-    for i in range(0, n, 1 << 28):
+    s = torch.empty(n + 3 * others, dtype=torch.float32, device=DEV)
+    for i in range(0, s.numel(), 1 << 28):
         s[i:i + (1 << 28)].uniform_(generator=g)
     if misled:
         s[torch.from_numpy(_sampled(n, 0)).to(DEV).view(-1)] = 7.0
-    row = torch.zeros(1, 1, 1, 128, dtype=torch.bfloat16, device=DEV).expand(1, 1, n, 128)     # sizes only
-    kept, cnt = C.compactor_select(C.Params(1, 1, sketch_dim=48), [C.Request(k_score=row, v_cache=row, ratio=ratio)], s)
+    row = torch.zeros(1, 1, 1, 128, dtype=torch.bfloat16, device=DEV)                          # sizes only
+    reqs = [C.Request(k_score=row.expand(1, 1, m, 128), v_cache=row.expand(1, 1, m, 128), ratio=ratio)
+            for m in [n] + [3] * others]
+    kept, cnt = C.compactor_select(C.Params(1, 1, sketch_dim=48), reqs, s)
     k = C.compactor_keep_count(n, ratio)
-    assert int(cnt[0]) == k == kept.numel() and bool((kept[1:] > kept[:-1]).all()) and int(kept[0]) >= 0
+    assert int(cnt[0]) == k and kept.numel() == k + others
+    assert torch.equal(kept[k:].long(), s[n:].view(others, 3).argmax(1))
+    kept, s = kept[:k], s[:n]
+    assert bool((kept[1:] > kept[:-1]).all()) and int(kept[0]) >= 0
     got = s[kept.long()]
     thr = got.min()
     above = eq = 0
