@@ -534,13 +534,17 @@ int compactor_select(const compactor_params_t *p, const compactor_request_t *req
   rc = check_scope(p, reqs, nreq);
   if (rc) return rc;
   if (!scores || !kept_idx || !kept_cnt) return COMPACTOR_EINVAL;
-  // only a pooled selection (long heads, layer scope) uses the workspace: its histograms
+  // only a pooled selection (long heads, layer scope) uses the workspace: for the tally where there is one, then its
+  // lists, records and states
   const long long grows = group_rows_of(p);
+  auto tally_bytes = [](const SegTable &T) {
+    return select_by_tally(T) ? align_up((size_t)select_scratch(T).pools * HIST1_BINS * sizeof(int)) : 0;
+  };
   size_t need = 0;
   rc = for_each_group(p, reqs, nreq, grows, false, [&](const SegTable &T, long long) {
     if (select_needs_pools(T)) {
-      const GroupBytes gb = group_bytes_needed(p, T, false);
-      if (gb.hist1 + gb.sel > need) need = gb.hist1 + gb.sel;
+      const size_t bytes = tally_bytes(T) + align_up((size_t)select_scratch(T).ints() * sizeof(int));
+      if (bytes > need) need = bytes;
     }
     return COMPACTOR_OK;
   });
@@ -553,9 +557,9 @@ int compactor_select(const compactor_params_t *p, const compactor_request_t *req
   drop_pending_error();
   return for_each_group(p, reqs, nreq, grows, false, [&](const SegTable &T, long long) {
     if (select_needs_pools(T)) {
-      const GroupBytes gb = group_bytes_needed(p, T, false);
-      int *tally = select_by_tally(T) ? static_cast<int *>(workspace) : nullptr;
-      int *sel = reinterpret_cast<int *>(static_cast<unsigned char *>(workspace) + gb.hist1);
+      const size_t tb = tally_bytes(T);
+      int *tally = tb > 0 ? static_cast<int *>(workspace) : nullptr;
+      int *sel = reinterpret_cast<int *>(static_cast<unsigned char *>(workspace) + tb);
       HIP_TRY(launch_select_pools(T, scores, nullptr, tally, sel, kept_idx, kept_cnt, st));
     } else {
       HIP_TRY(launch_select(T, scores, nullptr, kept_idx, kept_cnt, st));

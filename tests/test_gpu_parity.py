@@ -223,6 +223,31 @@ def test_select_around_the_limits_of_the_tally(C, maker, L, H, ns, ratios, scope
     _select_case(C, ns, ratios, L, H, maker, 47, scope)
 
 
+# sampled, tallied, and heads that need none: the workspace that a selection demands holds its lists (a slot a token),
+# records (16 bytes a chunk), states (32 a pool) and tallies (16 KB a pool) and nothing else, and nothing behind it changes
+@pytest.mark.parametrize("L,H,n,scope,tallied", [(4, 6, 40003, 0, 0), (30, 8, 700, 1, 0), (1, 3, 131073, 0, 3),
+                                                 (2, 8, 20000, 1, 2), (2, 8, 20000, 0, 0)])
+def test_select_in_the_smallest_workspace(C, L, H, n, scope, tallied):
+    p = C.Params(L, H, sketch_dim=48, select_scope=scope)
+    row = torch.zeros(1, 1, 1, 128, dtype=torch.bfloat16, device=DEV).expand(L, H, n, 128)      # sizes only
+    reqs = [C.Request(k_score=row, v_cache=row, ratio=0.3)]
+    scores = torch.rand(L * H * n, device=DEV)
+    pools = L if scope else L * H
+    pooled = scope == 1 or n > 32768
+    chunks = L * H * -(-n // 8192)
+    need = -(-(4 * L * H * n + 16 * chunks + 32 * pools) // 256) * 256 + tallied * 16384 if pooled else 0
+    assert need <= C.compactor_workspace_size(p, reqs)
+    ws = torch.full((need + 4096,), 0x5a, dtype=torch.uint8, device=DEV)
+    want = C.compactor_select(p, reqs, scores)
+    got = C.compactor_select(p, reqs, scores, workspace=ws[:need])
+    torch.cuda.synchronize()
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]) and bool((ws[need:] == 0x5a).all())
+    if pooled:
+        with pytest.raises(C.CompactorError) as e:
+            C.compactor_select(p, reqs, scores, workspace=ws[:need - 256])
+        assert e.value.code == C.EWORKSPACE
+
+
 # long pools, too many for a tally, whose samples mislead
 @pytest.mark.parametrize("kind", ["high", "low"])
 def test_select_where_the_samples_of_many_long_pools_mislead(C, kind):
@@ -1316,6 +1341,33 @@ def test_pooled_and_blended_compress_replays_from_a_hip_graph_on_a_side_stream(C
     # and the eager result is the oracle's
     st, _ = U.run_and_check(C, w, DEV)
     _say("  blended score error at most %.3g of its bound, swaps %d" % (st["max_blend_err_over_bound"], st["swaps"]))
+
+
+# tallied (scores that fill a histogram, which the call clears itself) and sampled
+@pytest.mark.parametrize("L,H,n", [(1, 2, 100003), (1, 9, 100003)])
+def test_pooled_select_replays_from_a_hip_graph(C, L, H, n):
+    p = C.Params(L, H, sketch_dim=48)
+    row = torch.zeros(1, 1, 1, 128, dtype=torch.bfloat16, device=DEV).expand(L, H, n, 128)      # sizes only
+    reqs = [C.Request(k_score=row, v_cache=row, ratio=0.3)]
+    scores = torch.zeros(L * H * n, device=DEV)
+    ws = torch.empty(C.compactor_workspace_size(p, reqs), dtype=torch.uint8, device=DEV)
+    ws2 = torch.empty_like(ws)
+    C.compactor_select(p, reqs, scores, workspace=ws)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        kept, cnt = C.compactor_select(p, reqs, scores, workspace=ws)
+    for seed in range(4):
+        torch.manual_seed(seed)
+        scores.copy_(torch.randn(L * H * n, device=DEV) * 10.0 ** (2 * seed))
+        ws.fill_(0xff if seed & 1 else 0x11)
+        graph.replay()
+        want, _ = C.compactor_select(p, reqs, scores, workspace=ws2)
+        torch.cuda.synchronize()
+        assert torch.equal(kept, want)
+        k = C.compactor_keep_count(n, 0.3)
+        for h in range(H):
+            assert np.array_equal(kept[h * k:(h + 1) * k].cpu().numpy(),
+                                  O.select_topk(scores[h * n:(h + 1) * n].cpu().numpy(), k))
 
 
 def test_pooled_select_edges_and_regrouping(C):
