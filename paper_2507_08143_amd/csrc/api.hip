@@ -76,24 +76,34 @@ int compute_units() {
 
 // Gram: a persistent launch, each workgroup taking an equal run of 64-row tiles.  Every (workgroup, head) partial costs
 // the factorisation 40 KB, so the fewer heads and tiles, the fewer workgroups: one pair (see gram_kernel) a compute unit,
-// one plain workgroup a unit where a few heads give it 8 to 30 tiles (the pair's end, where its halves meet, is
-// longer than what its loads save), and two plain ones for long runs, which stream a little faster than one pair, and
+// one plain workgroup a unit where a few heads give it 8 to 24 (exact mode 32) tiles (the pair's end, where its halves meet,
+// is longer than what its loads save), and two plain ones for long runs, which stream a little faster than one pair, and
 // where there are heads for every unit (256 of 1024 tokens 68.8 / 69.1).
-// compactor_score on MI355X, us with the plain / the paired plan, k_s = 48: 8 heads of 32768 54.5 / 54.4, 2 x 4 of 40007
-// 61.5 / 63.2, 24 of 12000 61.8 / 59.6, 128 of 2048 64.5 / 62.1, 21 of 20001 74.4 / 70.7, 8 of 65536 79.4 / 75.2, 8
-// of 100000 105 / 98.5, 128 of 4096 83.1 / 80.4, of 8192 129 / 127, 48 of 32768 161.5 / 165, 64 of 32768 199 / 205, of 65536
-// 357 / 376; exact mode: 8 of 32768 83.6 / 84.7, 21 of 20001 96.5 / 98.2, 8 of 65536 106.4 / 103.3, 64 of 8192 102.6 / 99.4,
-// 32 of 50000 197 / 194, 16 of 131072 234 / 232, 64 of 32768 230 / 235, of 65536 410 / 425; whole calls, one head
-// of 4096 45.5 / 43.4, 8 of 8192 57.6 / 54.4.
-struct GramPlan { int nwg, tiles_per_wg; bool pair; };
+// A pair takes the place of two runs whose partials met in fp64 and therefore folds, except where a workgroup's share is the
+// 8 tiles that it has at least, which a plain one would sum in one run.  For the same reason a plain one a unit is for
+// the heads and tiles at which it always was.
+// compactor_score on MI355X, keys not in the last-level cache, us with one plain workgroup a unit / two / a pair / a pair that
+// folds (- : not measured).  k_s = 48, tiles a unit in brackets: one head of 8192 (0.5) 31.5 / 31.5 / 31.0 / 31.3; 8 heads of
+// 8192 (4) 35.7 / 35.7 / 35.6 / 36.0, 16384 (8) 42.5 / 42.5 / 43.4 / 43.0, 32768 (16) 53.7 / 57.0 / 55.1 / 54.6, 48000 (23)
+// 64.2 / 71.2 / 64.9 / 64.2, 52000 (25) 67.1 / 72.3 / - / 66.2, 65536 (32) 75.5 / 77.9 / 74.3 / 73.5, 131072 (64) 117.9 / 114.3 /
+// 113.6 / 113.0, 147000 (72) 139.9 / 129.2 / - / 128.2, 190000 (93) 167 / 160 / - / 157; 16 of 24000 (23) 63.1 / 67.3 / 63.6 / 63.4,
+// of 26000 (25) 65.9 / 69.1 / - / 65.0; 32 of 4096 (8) 42.8 / 42.7 / 43.3 / 43.5, 8000 (16) 54.5 / 57.2 / 55.1 / 55.3, 10000 (20)
+// 59.7 / 61.3 / - / 59.7, 36000 (70) 133.5 / 126.8 / - / 126.5, 47000 (92) 165 / 153 / - / 153; 64 of 2048 (8) 45.9 / 45.8 / 45.8 /
+// 46.2, 4096 (16) 57.1 / 58.8 / 57.6 / 58.0; 128 of 4096 (32) 80.0 / 82.7 / - / 78.5, 9216 (72) 142 / 134 / - / 134.  Exact mode:
+// 8 of 8192 (4) 56.0 / 56.0 / 55.7 / 56.1, 32768 (16) 82.0 / 93.1 / 84.2 / 83.3, 65536 (32) 101.8 / 117.3 / 103.2 / 102.4, 73728 (36)
+// 111.1 / 117.9 / - / 110.0, 131072 (64) 150.6 / 150.8 / 144.0 / 144.3, 200000 (98) 202 / 196 / - / 189; 32 of 12288 (24) 88.8 /
+// 93.1 / 89.5 / 89.0, 18000 (35) 105.6 / 106.4 / - / 104.2, 57000 (111) 219 / 208 / - / 204; 64 of 8192 (32) 96.7 / 102.0 / 97.1 / 97.1.
+struct GramPlan { int nwg, tiles_per_wg; GramKind kind; };
 GramPlan gram_plan(const compactor_params_t *p, const SegTable &T, int cus) {
   const long long total = total_tiles(T);
   const bool exact = p->sketch_dim == 0;
-  const int single_most = T.nheads <= 16 ? (exact ? 30 : 24) : T.nheads <= 32 ? (exact ? 30 : 16) : 0;
+  const int single_most = T.nheads <= 16 ? (exact ? 32 : 24) : T.nheads <= 32 ? (exact ? 32 : 16) : 0;
   const bool single = total >= 8ll * cus && total < (long long)single_most * cus;
   GramPlan g;
-  g.pair = !single && T.nheads < cus && total < (exact ? 112ll : 72ll) * cus;
-  long long want = p->gram_wgs > 0 ? p->gram_wgs : (single || g.pair ? 1ll : 2ll) * cus;
+  g.kind = single || T.nheads >= cus || total >= (exact ? 112ll : 72ll) * cus ? GRAM_PLAIN
+           : total <= 8ll * cus                                               ? GRAM_PAIR
+                                                                              : GRAM_PAIR_FOLD;
+  long long want = p->gram_wgs > 0 ? p->gram_wgs : (single || g.kind != GRAM_PLAIN ? 1ll : 2ll) * cus;
   if (want > total) want = total;
   if (want < 1) want = 1;
   g.tiles_per_wg = (int)((total + want - 1) / want);
@@ -320,7 +330,7 @@ int enqueue_score(const compactor_params_t *p, const SegTable &T, const GroupByt
   const int rpw = gp.tiles_per_wg;
   const Marks m{p->stage_events, st};
   MARK(m, 0);
-  HIP_TRY(launch_gram(T, gp.nwg, gp.tiles_per_wg, gp.pair, partials, st));
+  HIP_TRY(launch_gram(T, gp.nwg, gp.tiles_per_wg, gp.kind, partials, st));
   MARK(m, COMPACTOR_STAGE_GRAM + 1);
   MARK(m, COMPACTOR_STAGE_REDUCE + 1);       // the fp64 sum of the partials is part of the next kernel
   double *shares =

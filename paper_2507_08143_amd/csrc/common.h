@@ -357,8 +357,10 @@ __device__ __forceinline__ long long partial_base(const SegTable &T, int lhead, 
 // All of them enqueue on `st` and return the hipGetLastError() of their launches.
 
 // Partial Gram matrices: the 10 upper 32x32 blocks (fp32) per (workgroup, head) intersection,
-// nwg + nheads slots.  pair: workgroups of twice the waves (the number of partials is the same).
-hipError_t launch_gram(const SegTable &T, int nwg, int tiles_per_wg, bool pair, float *partials,
+// nwg + nheads slots.  GRAM_PAIR: workgroups of twice the waves, whose halves' sums meet before they leave (the number
+// of partials is the same); GRAM_PAIR_FOLD: the same with sums in more, shorter runs (see gram_kernel).
+enum GramKind { GRAM_PLAIN, GRAM_PAIR, GRAM_PAIR_FOLD };
+hipError_t launch_gram(const SegTable &T, int nwg, int tiles_per_wg, GramKind kind, float *partials,
                        hipStream_t st);
 
 // Factorisation: partial Gram blocks -> W^T ([term][k_s][128] per head as W_TERMS bf16 planes; exact

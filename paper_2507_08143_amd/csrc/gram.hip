@@ -49,10 +49,18 @@ constexpr int GRAM_TG_UNROLL = 4;   // 16-token steps unrolled together (more op
 // through tile buffers of its own.  Twice the loads are in flight, as with two
 // workgroups on a compute unit, but what the groups have of the same head leaves as one partial: the second group's
 // waits in LDS for the first's.  Where it pays: gram_plan.
+// FOLD: two plain workgroups' partials meet in fp64 in the factorisation, those of two groups in fp32 here.  So that
+// nothing is lost by it, a group adds its products up FOLD tiles at a time: a product passes through at most 4 FOLD
+// roundings in the accumulator of the matrix core, one for every FOLD tiles of the rest of the run, and the one of the
+// join, where a plain workgroup's passes through four for every tile behind it.  Relative error of the scores against 64
+// bits, two plain workgroups a unit / folding pairs: exact mode, deficient keys, 64 heads of 8192 9.4e-6 / 7.6e-6, 128 of
+// 4096 9.5e-6 / 7.7e-6, 32 of 32768 9.7e-6 / 7.5e-6; k_s = 48, keys of low rank, 32 of 16384 4.6e-6 / 4.1e-6, 128 of 4096
+// 4.8e-6 / 4.2e-6.  (Time: gram_plan.)
+constexpr int GRAM_FOLD = 4;        // tiles; even, since the loop takes two at a time
 // The body is compiled once per wave of a group: which blocks a wave owns is then known
 // at compile time, and the accumulators stay in fixed registers (a run-time switch inside the
 // loop makes the compiler copy them at every join).
-template <int wave, bool PAIR>
+template <int wave, bool PAIR, int FOLD>
 __device__ __forceinline__ void gram_body(const SegTable &T, int tiles_per_wg, long long total,
                                           float *__restrict__ partials, unsigned char *lds) {
   const int group = PAIR ? __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8) : 0;
@@ -66,11 +74,28 @@ __device__ __forceinline__ void gram_body(const SegTable &T, int tiles_per_wg, l
   const int tid = threadIdx.x & 255, lane = tid & 63;
   const int ld_row = tid >> 4, ld_chunk = tid & 15;   // loader: 16 lanes cover one 256-B row
 
-  f32x16 acc[3];
+  f32x16 acc[3], sum[3];           // sum (FOLD): what the folds have taken out of acc
 #pragma unroll
   for (int b = 0; b < 3; ++b)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) acc[b][v] = 0.f;
+    for (int v = 0; v < 16; ++v) acc[b][v] = sum[b][v] = 0.f;
+  auto &left = FOLD ? sum : acc;   // where the sums of a head are once they are complete
+  const int nblk = wave < 2 ? 3 : 2;
+  const int first = wave == 0 ? 0 : (wave == 1 ? 3 : (wave == 2 ? 6 : 8));
+  auto fold = [&] {
+    if constexpr (FOLD > 0) {
+#pragma unroll
+      for (int b = 0; b < 3; ++b) {
+        if (b < nblk) {
+#pragma unroll
+          for (int v = 0; v < 16; ++v) {
+            sum[b][v] += acc[b][v];
+            acc[b][v] = 0.f;
+          }
+        }
+      }
+    }
+  };
 
   TileCursor L, C;                 // load cursor runs two tiles ahead of the compute cursor
   cursor_seek<GRAM_TILE>(T, PAIR ? min(g0, total - 1) : g0, L);
@@ -119,8 +144,6 @@ __device__ __forceinline__ void gram_body(const SegTable &T, int tiles_per_wg, l
 
   // Each wave writes the blocks it owns: a partial is the 10 upper blocks, each [32][32].
   // 32x32 accumulator layout: register v of lane l is element (8*(v>>2) + 4*(l>>5) + (v&3), l&31).
-  const int nblk = wave < 2 ? 3 : 2;
-  const int first = wave == 0 ? 0 : (wave == 1 ? 3 : (wave == 2 ? 6 : 8));
   // A block is stored in accumulator order: float4 number 64*q + lane of a block holds rows
   // 8q + 4*(lane>>5) .. +3 of column lane & 31, so a flush is 16-byte stores, 1 KB per wave
   // instruction (see partial_quad in common.h for the readers).
@@ -143,21 +166,22 @@ __device__ __forceinline__ void gram_body(const SegTable &T, int tiles_per_wg, l
         float *ob = out + (first + b) * GBLK;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          const float4 v = make_float4(acc[b][4 * q], acc[b][4 * q + 1], acc[b][4 * q + 2], acc[b][4 * q + 3]);
+          const float4 v = make_float4(left[b][4 * q], left[b][4 * q + 1], left[b][4 * q + 2], left[b][4 * q + 3]);
           if (how == TO_GLOBAL_STREAM)
             store_stream16(ob + (64 * q + lane) * 4, make_uint4(__float_as_uint(v.x), __float_as_uint(v.y),
                                                                  __float_as_uint(v.z), __float_as_uint(v.w)));
           else
             *reinterpret_cast<float4 *>(ob + (64 * q + lane) * 4) = v;
-          acc[b][4 * q] = acc[b][4 * q + 1] = acc[b][4 * q + 2] = acc[b][4 * q + 3] = 0.f;
+          left[b][4 * q] = left[b][4 * q + 1] = left[b][4 * q + 2] = left[b][4 * q + 3] = 0.f;
         }
       }
     }
   };
   bool dirty = false;
   int keep_lhead = -1;                   // PAIR: the head of what is still in the accumulators, if complete
-  auto finish_tile = [&](bool last_of_run) {       // after a tile has been multiplied
+  auto finish_tile = [&](bool last_of_run, bool due) {       // after a tile has been multiplied
     dirty = true;
+    if (due || C.tile + 1 == C.tph || last_of_run) fold();
     if (C.tile + 1 == C.tph) {
       const int lhead = T.s[C.seg].lhead0 + C.hh;
       if (PAIR) {
@@ -194,7 +218,7 @@ __device__ __forceinline__ void gram_body(const SegTable &T, int tiles_per_wg, l
     load_tile(t + 2, stA);
     if (!PAIR || t < count) {
       compute_tile(smem);
-      finish_tile(t + 1 == count);
+      finish_tile(t + 1 == count, false);
     }
     if (t + 1 < meet) {
       store_tile(smem + TILE_BYTES, stB);
@@ -202,7 +226,7 @@ __device__ __forceinline__ void gram_body(const SegTable &T, int tiles_per_wg, l
       load_tile(t + 3, stB);
       if (!PAIR || t + 1 < count) {
         compute_tile(smem + TILE_BYTES);
-        finish_tile(t + 2 == count);
+        finish_tile(t + 2 == count, FOLD > 0 && (t + 2) % max(FOLD, 1) == 0);
       }
     }
   }
@@ -225,7 +249,7 @@ __device__ __forceinline__ void gram_body(const SegTable &T, int tiles_per_wg, l
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
             const float4 v = *reinterpret_cast<const float4 *>(ob + (64 * q + lane) * 4);
-            acc[b][4 * q] += v.x; acc[b][4 * q + 1] += v.y; acc[b][4 * q + 2] += v.z; acc[b][4 * q + 3] += v.w;
+            left[b][4 * q] += v.x; left[b][4 * q + 1] += v.y; left[b][4 * q + 2] += v.z; left[b][4 * q + 3] += v.w;
           }
         }
       }
@@ -250,7 +274,7 @@ __device__ __forceinline__ void gram_body(const SegTable &T, int tiles_per_wg, l
   }
 }
 
-template <bool PAIR>
+template <bool PAIR, int FOLD>
 __global__ __launch_bounds__(PAIR ? 512 : 256, GRAM_OCC) void gram_kernel(const SegTable T, int tiles_per_wg,
                                                                           long long total,
                                                                           float *__restrict__ partials) {
@@ -259,21 +283,22 @@ __global__ __launch_bounds__(PAIR ? 512 : 256, GRAM_OCC) void gram_kernel(const 
       smem[(PAIR ? 4 : 2) * TILE_BYTES + GRAM_PARTIAL_FLOATS * 4 + (PAIR ? 16 : 0)];
   // every wave passes the same workgroup barriers, each in its own copy of the loop
   switch (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) & 3) {
-    case 0: gram_body<0, PAIR>(T, tiles_per_wg, total, partials, smem); break;
-    case 1: gram_body<1, PAIR>(T, tiles_per_wg, total, partials, smem); break;
-    case 2: gram_body<2, PAIR>(T, tiles_per_wg, total, partials, smem); break;
-    default: gram_body<3, PAIR>(T, tiles_per_wg, total, partials, smem); break;
+    case 0: gram_body<0, PAIR, FOLD>(T, tiles_per_wg, total, partials, smem); break;
+    case 1: gram_body<1, PAIR, FOLD>(T, tiles_per_wg, total, partials, smem); break;
+    case 2: gram_body<2, PAIR, FOLD>(T, tiles_per_wg, total, partials, smem); break;
+    default: gram_body<3, PAIR, FOLD>(T, tiles_per_wg, total, partials, smem); break;
   }
 }
 
-hipError_t launch_gram(const SegTable &T, int nwg, int tiles_per_wg, bool pair, float *partials,
+hipError_t launch_gram(const SegTable &T, int nwg, int tiles_per_wg, GramKind kind, float *partials,
                        hipStream_t st) {
   const long long total = total_tiles(T);
   if (total <= 0 || nwg <= 0) return hipSuccess;
-  if (pair)
-    hipLaunchKernelGGL(gram_kernel<true>, dim3((unsigned)nwg), dim3(512), 0, st, T, tiles_per_wg, total, partials);
-  else
-    hipLaunchKernelGGL(gram_kernel<false>, dim3((unsigned)nwg), dim3(256), 0, st, T, tiles_per_wg, total, partials);
+  const auto kernel = kind == GRAM_PLAIN  ? gram_kernel<false, 0>
+                      : kind == GRAM_PAIR ? gram_kernel<true, 0>
+                                          : gram_kernel<true, GRAM_FOLD>;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)nwg), dim3(kind == GRAM_PLAIN ? 256 : 512), 0, st, T, tiles_per_wg, total,
+                     partials);
   return hipGetLastError();
 }
 

@@ -428,13 +428,50 @@ def test_ragged_token_counts(C, n):
 
 @pytest.mark.parametrize("gram_wgs", [1, 2, 5, 12])
 def test_gram_partitions_that_cross_heads(C, gram_wgs):
-    """The Gram kernel deals 64-row tiles out evenly, across head boundaries.  One workgroup for
-    six heads of 11 tiles crosses five boundaries (one partial parked in LDS, four written mid-run);
-    5 workgroups of 14 tiles cross one or two; 12 cross none or one.  All must match the oracle."""
+    """The Gram kernel deals 64-row tiles out evenly, across head boundaries, here to pairs of wave groups that halve
+    a workgroup's run.  One workgroup for six heads of 11 tiles crosses five boundaries (the halves meet where a
+    head ends, the other partials are written mid-run); 5 workgroups of 14 tiles cross one or two, the halves of
+    7 tiles share a head or not; 12 cross none or one.  All must match the oracle."""
     _say("Gram partition with %d workgroup(s) over 6 heads of 700 tokens" % gram_wgs)
     w = W.config2(DEV, L=2, H=3, n=700)
     st, _ = U.run_and_check(C, w, DEV, tune={"gram_wgs": gram_wgs})
     _say("  max rel err %.3g, swaps %d" % (st["max_rel"], st["swaps"]))
+
+
+@pytest.mark.parametrize("L,H,n,gram_wgs", [(32, 8, 100, 0), (17, 15, 100, 0), (24, 12, 129, 0), (32, 9, 60, 3)])
+def test_gram_of_many_short_heads(C, L, H, n, gram_wgs):
+    """From 256 heads on plain workgroups, below pairs: 8 tiles hold four heads (the first one's partial waits in LDS, two
+    are written mid-run, the last at the end), or begin and end inside a head; 96 heads in a row."""
+    _say("%d heads of %d tokens" % (L * H, n))
+    st, _ = U.run_and_check(C, W.config2(DEV, L=L, H=H, n=n), DEV, tune={"gram_wgs": gram_wgs})
+    _say("  max rel err %.3g, swaps %d" % (st["max_rel"], st["swaps"]))
+
+
+@pytest.mark.parametrize("L,H,n,ks", [(16, 8, 4096, 0), (1, 8, 73728, 0), (4, 8, 16384, 48)])
+def test_gram_pairs_keep_the_bits_of_short_sums(C, L, H, n, ks):
+    """A pair of wave groups whose halves meet in fp32 adds its products up in short runs first: against partials of two
+    tiles, which the factorisation adds in fp64, the error of the scores grows by a few rounding steps in 16 (the
+    products of four tiles) and not by those of a run of 16 tiles (a fifth more, measured)."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(49)
+    make = W.lowrank_outlier_keys if ks else lambda *a: W.rank_deficient_duplicate_keys(*a, dup_frac=0.0)
+    k = make(L, H, n, 128, g, DEV)
+    ridge = 0.0 if ks else 1e-4
+    p = C.Params(L, H, sketch_dim=ks, phi=W.make_phi(ks=ks, device=DEV) if ks else None, ridge_rel=ridge)
+    got = []
+    for p.gram_wgs in (0, 64 * 256):
+        got.append(C.compactor_score(p, [C.Request(k_score=k, v_cache=k, ratio=0.3)])[0].view(L * H, n).double())
+    err = [0.0, 0.0]
+    for h in range(L * H):
+        x = k[h // H, h % H].double()
+        x = x @ p.phi.double() if ks else x
+        S = x.t() @ x
+        S = S.cpu() + ridge * S.trace().cpu() / S.shape[0] * torch.eye(S.shape[0], dtype=torch.float64)
+        o = (x @ torch.linalg.inv(torch.linalg.cholesky(S)).t().contiguous().to(DEV)).square().sum(1)
+        for i in range(2):
+            err[i] += float((got[i][h] - o).square().sum() / o.square().sum()) / (L * H)
+    _say("  relative error %.3g, with partials of two tiles %.3g" % (err[0] ** 0.5, err[1] ** 0.5))
+    assert err[0] ** 0.5 <= 1.08 * err[1] ** 0.5
 
 
 @pytest.mark.parametrize("ks,n,gram_wgs", [(16, 700, 0), (32, 1000, 5), (48, 8192, 128), (64, 5000, 70),
@@ -472,15 +509,19 @@ def test_exact_mode_around_the_limit_of_the_shares(C, L):
     U.run_and_check(C, w, DEV, heads=[(0, 0, 0), (0, L // 2, 0), (0, L - 1, 0)])
 
 
-# few heads: score runs of 256 to 1024 tokens up to 1024 tokens a compute unit, and one Gram workgroup a
-# unit below 24 (exact mode: 64) tiles each up to 8 heads, fewer up to 16 and up to 32; a step to either side
-# of the limits, a short head, blended scores
+# Score runs: one workgroup a compute unit as long as runs stay even and short.  Gram: a pair a unit up to 8 tiles each, one
+# plain workgroup up to 24 (17 to 32 heads: 16; exact mode: 32), pairs that fold up to 72 (exact mode: 112), two plain
+# ones beyond: a step to either side of the limits, a short head, blended scores
 @pytest.mark.parametrize("H,n,exact,blend", [(1, 130, False, False), (3, 257, False, True), (8, 8191, False, True),
                                              (2, 131071, False, False), (2, 131073, False, False),
                                              (8, 49089, False, False), (8, 49153, False, False),
                                              (3, 43691, True, False), (32, 8191, False, False),
                                              (32, 8193, False, False), (16, 49089, True, False),
-                                             (16, 49153, True, False)])
+                                             (16, 49153, True, False), (8, 16320, False, False),
+                                             (8, 16384, False, False), (8, 49088, False, True), (32, 8128, False, False),
+                                             (64, 2048, False, False), (64, 2049, False, False), (8, 147392, False, False),
+                                             (8, 147456, False, False), (16, 32704, True, False),
+                                             (16, 32768, True, False), (32, 57280, True, False), (32, 57344, True, False)])
 def test_launch_shapes_of_few_heads(C, H, n, exact, blend):
     w = W.config5(DEV, L=1, H=H, n=n, exact=True) if exact else W.config1(DEV, L=1, H=H, n=n)
     if blend:
