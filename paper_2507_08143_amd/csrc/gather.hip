@@ -433,11 +433,20 @@ static hipError_t launch_inplace(const SegTable &T, const PagePool &P, const int
 
 // Whether a compaction in place is cut in two (see compact_inplace_kernel): by the rows of a head that are late if
 // the retained ones are spread evenly, k (1 - k / n).  The second launch costs 3 to 6 us and lets every compute
-// unit take part.  us in one / in two on MI355X, pages of 16: heads of 131072 tokens, 8 heads, 10 % retained 55 / 36, 30 %
-// 199 / 134, 50 % 393 / 283, 80 % 663 / 592; 24 heads, 30 % 373 / 257; heads of 65536, 8 of them, 10 % 28 / 22, 32 of
-// them 43 / 54, 30 % 200 / 158, 64 of them 89 / 94, 300 / 272, 128 of them 182 / 176, 534 / 519; 24 of 40000, 10 % 24 / 28, 30 %
-// 91 / 84; 16 of 24000 48 / 43; heads of 16384, 8 of them 18 / 23, 32 42 / 46, 64 55 / 74, 96 105 / 102; 80 %
-// retained, 8 of 32768 109 / 119, 16 of 40007 230 / 228, 96 of 30000 502 / 526.
+// unit take part, which is worth most to few heads and nothing around 64, where the slices of one launch are a workgroup
+// for every unit as it is; more heads take several rounds of workgroups, and two launches fill the last of them better.
+// MI355X, pages of 16, time in two launches over time in one, pool in memory / in the last-level cache, by late rows a head:
+//   8 heads   1721 1.13 / 1.02, 3441 0.74 / 1.13, 4096 0.70 / 1.06, 5040 0.65 / 0.90, 6882 0.63 / 0.80, 15729 0.61 / 0.73
+//   16        1721 0.94 / 1.15, 3441 0.79 / 0.96, 4096 0.79 / 0.96, 5040 0.73 / 0.86, 8192 0.77 / 0.88
+//   24        3441 0.86 / 0.94, 5040 0.81 / 0.91, 6882 0.81 / 0.90, 8400 0.76 / 0.90
+//   32        1476 1.35 / 1.06, 3441 0.92 / 1.01, 4096 0.90 / 1.00, 6000 0.87 / 0.96, 6882 0.80 / 0.95, 8192 0.87 / 0.92
+//   48        6000 0.93 / 0.97, 8192 0.97 / 0.97
+//   64        3441 1.04 / 1.26, 5899 1.03 / 1.04, 6882 1.04 / 1.04, 8192 0.96 / 0.96, 13763 0.92 / 0.92
+//   65        2880 1.10, 3441 1.07 / 1.07;  72  3441 0.95 / 0.96, 7200 0.97;  96  2880 0.98, 3441 0.97 / 0.97, 7200 0.99
+//   128       2400 1.01, 2880 1.00 / 1.00, 3441 0.99 / 0.99, 4096 1.01 / 1.01;  256  2880 0.98, 4096 0.99
+// The more is retained, the less the late rows weigh: 8 heads of 65536, 60, 65 and 70 % 0.70, 0.74, 0.78, 16 of 40007, 60 and
+// 70 % 0.81, 0.87 (80 % 0.99), 64 of 32768, 65 % 0.98, 128 of 16384, 65 % 1.02, 8 of 32768, 80 % 1.09, 96 of 30000, 60 and
+// 80 % 0.99, 1.05.
 static bool inplace_in_two(const SegTable &T) {
   long long late = 0, kept = 0, rows = 0;
   for (int i = 0; i < T.nseg; ++i) {
@@ -446,7 +455,7 @@ static bool inplace_in_two(const SegTable &T) {
     kept += (long long)s.head_count * s.k_keep;
     rows += (long long)s.head_count * s.n;
   }
-  const int least = T.nheads <= 16 ? 4800 : T.nheads <= 64 ? 8192 : 3400;
+  const int least = T.nheads <= 48 ? 4800 : T.nheads <= 64 ? 8192 : 3400;
   return late >= (long long)least * T.nheads && 8 * kept <= 5 * rows;
 }
 

@@ -1146,7 +1146,8 @@ def _paged_case(C, w, scope, page_size, in_place, seed):
 # early rows in order, late rows by a launch of their own: every slice width, late rows that begin in mid-run, layers
 # whose heads keep from few rows to nearly all, two requests of which one alone would move in one launch
 @pytest.mark.parametrize("L,H,n,ratio,scope", [(1, 2, 24001, 0.31, 0), (2, 3, 50007, 0.5, 1), (1, 17, 41000, 0.3, 0),
-                                               (1, 65, 16411, 0.33, 0)])
+                                               (1, 65, 16411, 0.33, 0), (1, 17, 23001, 0.31, 0), (6, 8, 23001, 0.31, 1),
+                                               (7, 7, 23001, 0.31, 0)])
 def test_compact_in_place_in_two_launches(C, L, H, n, ratio, scope):
     w = W.config1(DEV, L=L, H=H, n=n, ratio=ratio)
     if L == 2:
