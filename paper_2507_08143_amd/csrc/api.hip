@@ -138,6 +138,11 @@ int score_tokens_for(const compactor_params_t *p, const SegTable &T, int cus) {
   // the search below, whose workgroups get W^T from a kernel of its own, with k_s = 16, 48 and 64: 8 heads of 40007 50.3 / 54.7,
   // 60.0 / 65.0, 69.6 / 74.5, 65536 65.3 / 67.5, 76.0 / 79.1, 87.9 / 87.5, 100000 89.6 / 92.4, 99.3 / 102.3, 112.3 / 112.3,
   // 32 heads of 30000 99.6 / 99.2, 111.0 / 110.7, 125.4 / 119.5.
+  // The same runs where the workspace has no room for the shares (the sums of a blend are parted as the runs are, and its
+  // scores are the same bits either way): the factorisation then costs 15 to 27 us more whatever the runs.  us without room with
+  // these runs / the best of 512 to 4096 tokens, k_s = 48: 8 heads of 8192 55.7 / 57.2, 16384 68.8 / 68.8, 32768 79.6 / 79.5,
+  // 40007 86.6 / 86.4, 65536 99.8 / 99.7, 100000 125.4 / 126.5, 32 of 8192 70.4 / 70.4, 30000 128.8 / 128.2, 128 of 4096 90.7 /
+  // 90.4.
   if (p->sketch_dim > 0 && T.nheads <= cus) {
     const int most = p->sketch_dim <= 48 ? SCORE_BURST : 1536;
     const long long even = (rows + cus - 1) / cus;
