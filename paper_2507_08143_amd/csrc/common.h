@@ -213,7 +213,9 @@ __host__ __device__ __forceinline__ BinKeys bin_keys(int bin, bool fine) {
 }
 
 // Sample of a pool of more than SAMPLE_WHOLE scores (see msel_sample_kernel): the g-th of SAMPLE_LINES lines
-// out of `lines`, at a hashed place in the g-th of as many equal stretches.
+// out of `lines`, at a hashed place in the g-th of as many equal stretches.  (Well-known constants of integer
+// hashes: 0x9e3779b9 is 2^32 over the golden ratio, 2654435761 the prime near it of Knuth's multiplicative hashing,
+// 2246822519 one of the primes of xxHash.)
 constexpr int SAMPLE_WHOLE = 8192, SAMPLE_LINES = SAMPLE_WHOLE / 16;
 __host__ __device__ __forceinline__ int sample_line(int g, int lines) {
   const uint32_t hash = ((uint32_t)g * 2654435761u ^ 0x9e3779b9u) * 2246822519u >> 16;
@@ -358,7 +360,7 @@ __device__ __forceinline__ long long partial_base(const SegTable &T, int lhead, 
 
 // Partial Gram matrices: the 10 upper 32x32 blocks (fp32) per (workgroup, head) intersection,
 // nwg + nheads slots.  GRAM_PAIR: workgroups of twice the waves, whose halves' sums meet before they leave (the number
-// of partials is the same); GRAM_PAIR_FOLD: the same with sums in more, shorter runs (see gram_kernel).
+// of partials is the same); GRAM_PAIR_FOLD: the same with every tile added up by itself (see gram_kernel).
 enum GramKind { GRAM_PLAIN, GRAM_PAIR, GRAM_PAIR_FOLD };
 hipError_t launch_gram(const SegTable &T, int nwg, int tiles_per_wg, GramKind kind, float *partials,
                        hipStream_t st);

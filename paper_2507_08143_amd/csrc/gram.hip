@@ -50,17 +50,17 @@ constexpr int GRAM_TG_UNROLL = 4;   // 16-token steps unrolled together (more op
 // workgroups on a compute unit, but what the groups have of the same head leaves as one partial: the second group's
 // waits in LDS for the first's.  Where it pays: gram_plan.
 // FOLD: two plain workgroups' partials meet in fp64 in the factorisation, those of two groups in fp32 here.  So that
-// nothing is lost by it, a group adds its products up FOLD tiles at a time: a product passes through at most 4 FOLD
-// roundings in the accumulator of the matrix core, one for every FOLD tiles of the rest of the run, and the one of the
-// join, where a plain workgroup's passes through four for every tile behind it.  Relative error of the scores against 64
-// bits, two plain workgroups a unit / folding pairs: exact mode, deficient keys, 64 heads of 8192 9.4e-6 / 7.6e-6, 128 of
-// 4096 9.5e-6 / 7.7e-6, 32 of 32768 9.7e-6 / 7.5e-6; k_s = 48, keys of low rank, 32 of 16384 4.6e-6 / 4.1e-6, 128 of 4096
-// 4.8e-6 / 4.2e-6.  (Time: gram_plan.)
-constexpr int GRAM_FOLD = 4;        // tiles; even, since the loop takes two at a time
+// nothing is lost by it, a group adds every tile's products up by themselves and then to its sums: a product passes through
+// four roundings in the accumulator of the matrix core, one for every tile behind it, and the one of the join, where
+// a plain workgroup's passes through four for every tile behind it.  Relative error of the scores against 64 bits, two
+// plain workgroups a unit / folding pairs: exact mode, deficient keys, 64 heads of 8192 9.4e-6 / 7.6e-6, 128 of 4096 9.5e-6 /
+// 7.7e-6, 32 of 32768 9.7e-6 / 7.5e-6; k_s = 48, keys of low rank, 32 of 16384 4.6e-6 / 4.1e-6, 128 of 4096 4.8e-6 /
+// 4.2e-6.  At every tile and not at every fourth, say, because a fold under a condition makes the compiler copy the
+// accumulators where the paths join (8 heads of 131072, whole call 172.0 us, 171.6 so, 170.4 without folds).  (Time: gram_plan.)
 // The body is compiled once per wave of a group: which blocks a wave owns is then known
 // at compile time, and the accumulators stay in fixed registers (a run-time switch inside the
 // loop makes the compiler copy them at every join).
-template <int wave, bool PAIR, int FOLD>
+template <int wave, bool PAIR, bool FOLD>
 __device__ __forceinline__ void gram_body(const SegTable &T, int tiles_per_wg, long long total,
                                           float *__restrict__ partials, unsigned char *lds) {
   const int group = PAIR ? __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8) : 0;
@@ -74,7 +74,7 @@ __device__ __forceinline__ void gram_body(const SegTable &T, int tiles_per_wg, l
   const int tid = threadIdx.x & 255, lane = tid & 63;
   const int ld_row = tid >> 4, ld_chunk = tid & 15;   // loader: 16 lanes cover one 256-B row
 
-  f32x16 acc[3], sum[3];           // sum (FOLD): what the folds have taken out of acc
+  f32x16 acc[3], sum[3];           // sum: with FOLD, the tiles before
 #pragma unroll
   for (int b = 0; b < 3; ++b)
 #pragma unroll
@@ -83,7 +83,7 @@ __device__ __forceinline__ void gram_body(const SegTable &T, int tiles_per_wg, l
   const int nblk = wave < 2 ? 3 : 2;
   const int first = wave == 0 ? 0 : (wave == 1 ? 3 : (wave == 2 ? 6 : 8));
   auto fold = [&] {
-    if constexpr (FOLD > 0) {
+    if constexpr (FOLD) {
 #pragma unroll
       for (int b = 0; b < 3; ++b) {
         if (b < nblk) {
@@ -179,9 +179,9 @@ __device__ __forceinline__ void gram_body(const SegTable &T, int tiles_per_wg, l
   };
   bool dirty = false;
   int keep_lhead = -1;                   // PAIR: the head of what is still in the accumulators, if complete
-  auto finish_tile = [&](bool last_of_run, bool due) {       // after a tile has been multiplied
+  auto finish_tile = [&](bool last_of_run) {       // after a tile has been multiplied
     dirty = true;
-    if (due || C.tile + 1 == C.tph || last_of_run) fold();
+    fold();
     if (C.tile + 1 == C.tph) {
       const int lhead = T.s[C.seg].lhead0 + C.hh;
       if (PAIR) {
@@ -218,7 +218,7 @@ __device__ __forceinline__ void gram_body(const SegTable &T, int tiles_per_wg, l
     load_tile(t + 2, stA);
     if (!PAIR || t < count) {
       compute_tile(smem);
-      finish_tile(t + 1 == count, false);
+      finish_tile(t + 1 == count);
     }
     if (t + 1 < meet) {
       store_tile(smem + TILE_BYTES, stB);
@@ -226,7 +226,7 @@ __device__ __forceinline__ void gram_body(const SegTable &T, int tiles_per_wg, l
       load_tile(t + 3, stB);
       if (!PAIR || t + 1 < count) {
         compute_tile(smem + TILE_BYTES);
-        finish_tile(t + 2 == count, FOLD > 0 && (t + 2) % max(FOLD, 1) == 0);
+        finish_tile(t + 2 == count);
       }
     }
   }
@@ -274,7 +274,7 @@ __device__ __forceinline__ void gram_body(const SegTable &T, int tiles_per_wg, l
   }
 }
 
-template <bool PAIR, int FOLD>
+template <bool PAIR, bool FOLD>
 __global__ __launch_bounds__(PAIR ? 512 : 256, GRAM_OCC) void gram_kernel(const SegTable T, int tiles_per_wg,
                                                                           long long total,
                                                                           float *__restrict__ partials) {
@@ -294,9 +294,9 @@ hipError_t launch_gram(const SegTable &T, int nwg, int tiles_per_wg, GramKind ki
                        hipStream_t st) {
   const long long total = total_tiles(T);
   if (total <= 0 || nwg <= 0) return hipSuccess;
-  const auto kernel = kind == GRAM_PLAIN  ? gram_kernel<false, 0>
-                      : kind == GRAM_PAIR ? gram_kernel<true, 0>
-                                          : gram_kernel<true, GRAM_FOLD>;
+  const auto kernel = kind == GRAM_PLAIN  ? gram_kernel<false, false>
+                      : kind == GRAM_PAIR ? gram_kernel<true, false>
+                                          : gram_kernel<true, true>;
   hipLaunchKernelGGL(kernel, dim3((unsigned)nwg), dim3(kind == GRAM_PLAIN ? 256 : 512), 0, st, T, tiles_per_wg, total,
                      partials);
   return hipGetLastError();

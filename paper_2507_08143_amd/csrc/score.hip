@@ -164,8 +164,9 @@ __device__ __forceinline__ void leave_hist(const SegTable &T, const Seg &s, cons
 // SOLVE: every workgroup factors its head itself, from the shares of S, and W^T goes straight into its LDS.  The
 // work is done many times over, but by compute units that would wait for it, and a launch and two passes of W^T
 // through memory are saved (see score_solves).
+// (At M = 64 its LDS leaves room for one on a unit, which is also all that score_solves asks for.)
 template <int M, bool SOLVE>
-__global__ __launch_bounds__(256, 2) void score_kernel(
+__global__ __launch_bounds__(256, SOLVE && M == 64 ? 1 : 2) void score_kernel(
     const SegTable T, const uint16_t *__restrict__ wt, const ScoreSolve V, float *__restrict__ scores,
     int32_t *__restrict__ status, int *__restrict__ hist1, double *__restrict__ ostat) {
   constexpr int NSUB = 2, WTOK = 16 * NSUB, STEP = 4 * WTOK;     // tokens per wave / per WG step

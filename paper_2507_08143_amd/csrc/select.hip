@@ -325,7 +325,7 @@ __global__ __launch_bounds__(SELECT_THREADS) void select_kernel(const SegTable T
 }
 
 // ---- selection by several workgroups per pool ------------------------------------------------
-// Used when a head is too long for one workgroup's LDS, and for head-adaptive selection, where
+// Used when a head has more scores than one workgroup holds in registers, and for head-adaptive selection, where
 // the pool is the H kv heads of a layer that share one budget of H * k_keep tokens (paper Sec. 3.3:
 // the top scores "across all heads"; scoring stays per head).  The same radix select and ordered
 // emit as above, with the scores read once or twice in all.  A pool (head or layer) is cut into chunks of

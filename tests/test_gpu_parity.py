@@ -449,9 +449,10 @@ def test_gram_of_many_short_heads(C, L, H, n, gram_wgs):
 
 @pytest.mark.parametrize("L,H,n,ks", [(16, 8, 4096, 0), (1, 8, 73728, 0), (4, 8, 16384, 48)])
 def test_gram_pairs_keep_the_bits_of_short_sums(C, L, H, n, ks):
-    """A pair of wave groups whose halves meet in fp32 adds its products up in short runs first: against partials of two
-    tiles, which the factorisation adds in fp64, the error of the scores grows by a few rounding steps in 16 (the
-    products of four tiles) and not by those of a run of 16 tiles (a fifth more, measured)."""
+    """A pair of wave groups whose halves meet in fp32 adds every tile's products up by themselves: against partials of two
+    tiles, which the factorisation adds in fp64, a product passes through one rounding more for every tile behind it and
+    not through four, and the scores' error, most of which lies elsewhere, hardly grows (runs that go on in one
+    accumulator: a fifth, measured)."""
     g = torch.Generator(device=DEV)
     g.manual_seed(49)
     make = W.lowrank_outlier_keys if ks else lambda *a: W.rank_deficient_duplicate_keys(*a, dup_frac=0.0)
