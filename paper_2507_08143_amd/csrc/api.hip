@@ -83,16 +83,17 @@ int compute_units() {
 // 8 tiles that it has at least, which a plain one would sum in one run.  For the same reason a plain one a unit is for
 // the heads and tiles at which it always was.
 // compactor_score on MI355X, keys not in the last-level cache, us with one plain workgroup a unit / two / a pair / a pair that
-// folds (- : not measured).  k_s = 48, tiles a unit in brackets: one head of 8192 (0.5) 31.5 / 31.5 / 31.0 / 31.3; 8 heads of
-// 8192 (4) 35.7 / 35.7 / 35.6 / 36.0, 16384 (8) 42.5 / 42.5 / 43.4 / 43.0, 32768 (16) 53.7 / 57.0 / 55.1 / 54.6, 48000 (23)
-// 64.2 / 71.2 / 64.9 / 64.2, 52000 (25) 67.1 / 72.3 / - / 66.2, 65536 (32) 75.5 / 77.9 / 74.3 / 73.5, 131072 (64) 117.9 / 114.3 /
-// 113.6 / 113.0, 147000 (72) 139.9 / 129.2 / - / 128.2, 190000 (93) 167 / 160 / - / 157; 16 of 24000 (23) 63.1 / 67.3 / 63.6 / 63.4,
-// of 26000 (25) 65.9 / 69.1 / - / 65.0; 32 of 4096 (8) 42.8 / 42.7 / 43.3 / 43.5, 8000 (16) 54.5 / 57.2 / 55.1 / 55.3, 10000 (20)
-// 59.7 / 61.3 / - / 59.7, 36000 (70) 133.5 / 126.8 / - / 126.5, 47000 (92) 165 / 153 / - / 153; 64 of 2048 (8) 45.9 / 45.8 / 45.8 /
-// 46.2, 4096 (16) 57.1 / 58.8 / 57.6 / 58.0; 128 of 4096 (32) 80.0 / 82.7 / - / 78.5, 9216 (72) 142 / 134 / - / 134.  Exact mode:
-// 8 of 8192 (4) 56.0 / 56.0 / 55.7 / 56.1, 32768 (16) 82.0 / 93.1 / 84.2 / 83.3, 65536 (32) 101.8 / 117.3 / 103.2 / 102.4, 73728 (36)
-// 111.1 / 117.9 / - / 110.0, 131072 (64) 150.6 / 150.8 / 144.0 / 144.3, 200000 (98) 202 / 196 / - / 189; 32 of 12288 (24) 88.8 /
-// 93.1 / 89.5 / 89.0, 18000 (35) 105.6 / 106.4 / - / 104.2, 57000 (111) 219 / 208 / - / 204; 64 of 8192 (32) 96.7 / 102.0 / 97.1 / 97.1.
+// folds, tiles a unit in brackets.  k_s = 48: one head of 8192 (0.5) 31.6 / 31.5 / 31.1 / 31.4; 8 heads of 8192 (4) 35.9 / 36.1 /
+// 35.4 / 36.0, 16384 (8) 42.3 / 42.4 / 43.9 / 44.2, 32768 (16) 54.0 / 57.6 / 55.6 / 56.0, 48000 (23) 64.0 / 69.9 / 65.8 / 65.4,
+// 52000 (25) 67.4 / 72.6 / 67.7 / 67.9, 65536 (32) 75.3 / 79.3 / 74.5 / 75.0, 131072 (64) 118.7 / 114.7 / 112.6 / 113.9, 147000
+// (72) 135.9 / 131.6 / 128.2 / 128.8; 16 of 24000 (23) 63.5 / 65.5 / 62.7 / 63.6, 26000 (25) 65.4 / 67.9 / 65.1 / 66.0; 32 of 4096
+// (8) 42.6 / 42.6 / 42.7 / 43.4, 8000 (16) 54.5 / 57.6 / 55.2 / 55.8, 10000 (20) 59.3 / 62.2 / 60.7 / 61.4, 36000 (70) 134.6 /
+// 126.4 / 125.7 / 126.8, 47000 (92) 163.6 / 153.1 / 152.0 / 153.3; 64 of 2048 (8) 46.0 / 46.0 / 46.3 / 47.3, 4096 (16) 57.3 /
+// 59.3 / 58.8 / 59.2; 128 of 4096 (32) 80.5 / 83.3 / 79.9 / 81.3, 9216 (72) 143.4 / 134.7 / 133.6 / 135.1.  Exact mode: 8 of 8192
+// (4) 56.1 / 55.9 / 55.8 / 56.0, 32768 (16) 81.9 / 92.8 / 84.1 / 84.1, 65536 (32) 102.2 / 112.7 / 104.1 / 103.6, 73728 (36)
+// 113.3 / 119.3 / 112.0 / 111.4, 131072 (64) 153.7 / 154.8 / 145.9 / 147.8, 200000 (98) 207 / 203 / 195 / 197; 32 of 12288 (24) 89.2 /
+// 93.1 / 89.6 / 90.5, 18000 (35) 107.2 / 107.8 / 104.6 / 105.8, 57000 (111) 223.1 / 206.6 / 205.8 / 205.2; 64 of 8192 (32) 96.8 /
+// 100.4 / 96.5 / 98.4.
 struct GramPlan { int nwg, tiles_per_wg; GramKind kind; };
 GramPlan gram_plan(const compactor_params_t *p, const SegTable &T, int cus) {
   const long long total = total_tiles(T);
