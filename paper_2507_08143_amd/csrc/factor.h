@@ -10,13 +10,18 @@ namespace cmp {
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ uint16_t bf16_rne(float x) {
-  uint32_t u = __float_as_uint(x);
-  if ((u & 0x7f800000u) == 0x7f800000u) return (uint16_t)(u >> 16);   // inf / nan: truncate
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
+// Two floats as bf16, round to nearest even, the first in the lower half; split_bf16 also leaves what that misses of them.
+__device__ __forceinline__ unsigned pack_bf16(float x, float y) {
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2{x, y}), bf16x2));
 }
-__device__ __forceinline__ float bf16_to_f32(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
+__device__ __forceinline__ unsigned split_bf16(float &x, float &y) {
+  const unsigned p = pack_bf16(x, y);
+  x -= __uint_as_float(p << 16);
+  y -= __uint_as_float(p & 0xffff0000u);
+  return p;
+}
 
 // A pivot below this fraction of its own (ridged) diagonal entry is below what the fp32-
 // accumulated Gram matrix resolves: the direction is dropped and the head flagged.
@@ -47,69 +52,105 @@ __device__ __forceinline__ void wave_fence() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// acc -= (a of lane K of the row) * b in one instruction.  The compiler does not see that the asm reads a across lanes: two
+// instructions have to lie between what writes a and the first of these (chol16_inverse: the update of the next column and
+// its reciprocal).
+template <int K>
+__device__ __forceinline__ void sub_bcast16(double &acc, double a, double b) {
+  asm volatile("v_fmac_f64_dpp %0, -%1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(a), "v"(b), "n"(K));
+}
+
 // Inverse of the Cholesky factor of a 16 x 16 diagonal block, by one wave.  Lane i of every
 // 16-lane row holds row i of the block (row[], the lanes above 15 repeat what lanes 0..15 do) and
 // the ridged diagonal entry d0 of its row; on return x[i] of lane j is X[i][j], X = L^{-1}.  A
 // pivot that is not above PIVOT_REL d0 is dropped (row and column of X zero, or NaN where the block
 // is not finite: such a head's scores have to come out as NaN); returns whether none was.
-// Bound: the dependent chain of 16 pivots and the 120 broadcasts; three panels take about 6 us
-// where an elimination through LDS and scalar registers, with its square root on the chain, took
-// 15.6 us (k_s = 48).  The elimination is the square-root free one (u_i the
-// column before scaling, t_i = u_i / d): what the next pivot waits for is a lane broadcast, a
-// reciprocal with two Newton steps, a product and an fma; the broadcast of u_{k+1} runs beside the
-// reciprocal and the square roots of all 16 pivots are taken at once at the end.  Broadcasts are
-// row_newbcast moves, so nothing passes through LDS or scalar registers.  The inverse takes the
-// same broadcasts in the same pass (lane j solves column j).
+// Bound: one wave's instructions, one after the other.  The elimination is the square-root free one (u_i the
+// column before scaling, t_i = u_i / d): what the next pivot waits for is a reciprocal (2^-24, then a cubic step), its
+// broadcast, a product and an fma, eight clocks each and the reciprocal 20; an update is four clocks with the broadcast
+// of t_j inside it, and those that the previous pivot still owes the columns behind this one stand between the links of
+// the chain.  The square roots of all 16 pivots are taken at once at the end.  Nothing passes through LDS or scalar
+// registers.  The inverse takes the same broadcasts in the same pass (lane j solves column j).
 __device__ __forceinline__ bool chol16_inverse(double (&row)[16], double d0, double (&x)[16]) {
   const int l16 = threadIdx.x & 15;
-  bool all_ok = true;
   double d_mine = 0.0;
-  bool ok_mine = false;
 #pragma unroll
   for (int i = 0; i < 16; ++i) x[i] = (i == l16) ? 1.0 : 0.0;
   double u_prev = 0.0, t_prev = 0.0;               // column k - 1
   const double least = PIVOT_REL * d0;
   static_for<0, 16>([&](auto kc) {
     constexpr int k = decltype(kc)::value;
-    const double d = bcast16<k>(row[k]);
-    double r = __builtin_amdgcn_rcp(d);
+    // what pivot k - 1 still owes: to x[k], then to row[j] and x[j] of the columns j behind this one
+    constexpr int OWED = k > 0 ? 1 + 2 * (15 - k) : 0;
+    auto owed = [&](auto from, auto to) {
+      static_for<decltype(from)::value, decltype(to)::value>([&](auto ic) {
+        constexpr int i = decltype(ic)::value, j = i == 0 ? k : k + 1 + (i - 1) / 2;
+        if constexpr (i > 0 && (i & 1)) sub_bcast16<j>(row[j], t_prev, u_prev);
+        else sub_bcast16<j>(x[j], t_prev, x[k > 0 ? k - 1 : 0]);
+      });
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    // the last seven between the links, the others behind the reciprocal
+    constexpr int C0 = OWED > 7 ? OWED - 7 : 0;
+    auto cut = [](auto sc) {
+      constexpr int c = C0 + decltype(sc)::value;
+      return std::integral_constant<int, c < OWED ? c : OWED>{};
+    };
+    const double u = row[k];                       // of lane k: the pivot
+    double r = __builtin_amdgcn_rcp(u);
     computed_here(r);
     __builtin_amdgcn_sched_barrier(0);
-    const bool ok = d > bcast16<k>(least) && d < 1.0e300;      // false for NaN too
-    // what pivot k - 1 still owes the columns behind this one, in the shadow of the reciprocal
-    if constexpr (k > 0) {
-      static_for<k, 16>([&](auto jc) {
-        constexpr int j = decltype(jc)::value;
-        const double tj = bcast16<j>(t_prev);
-        if constexpr (j > k) row[j] = fma(-tj, u_prev, row[j]);
-        x[j] = fma(-tj, x[k - 1], x[j]);
-      });
-    }
-    r = fma(r, fma(-d, r, 1.0), r);
-    r = fma(r, fma(-d, r, 1.0), r);
-    if (!ok) r = 0.0;
-    all_ok &= ok;
-    if (l16 == k) {
-      d_mine = d;
-      ok_mine = ok;
-    }
-    u_prev = row[k];
-    t_prev = u_prev * r;                           // lane i: L[i][k] / L[k][k] for i > k
-    if constexpr (k < 15) row[k + 1] = fma(-bcast16<k + 1>(u_prev), t_prev, row[k + 1]);
-    // Keeps a pivot's updates with the pivot.  The compiler would otherwise collect the updates of
-    // x behind the last pivot (where x is stored) and hold all 120 broadcasts for them.
-    static_for<k, 16>([&](auto jc) { computed_here(x[decltype(jc)::value]); });
+    owed(std::integral_constant<int, 0>{}, cut(std::integral_constant<int, 0>{}));
+    double u_next = 0.0;
+    if constexpr (k < 15) u_next = bcast16<k + 1>(u);
+    if (l16 == k) d_mine = u;
+    r = u > least ? r : 0.0;                       // false for NaN too
+    computed_here(r);
+    computed_here(u_next);
     __builtin_amdgcn_sched_barrier(0);
+    owed(cut(std::integral_constant<int, 0>{}), cut(std::integral_constant<int, 1>{}));
+    double e = fma(-u, r, 1.0);
+    computed_here(e);
+    owed(cut(std::integral_constant<int, 1>{}), cut(std::integral_constant<int, 2>{}));
+    e = fma(e, e, e);
+    computed_here(e);
+    owed(cut(std::integral_constant<int, 2>{}), cut(std::integral_constant<int, 3>{}));
+    r = fma(r, e, r);
+    computed_here(r);
+    owed(cut(std::integral_constant<int, 3>{}), cut(std::integral_constant<int, 5>{}));
+    r = bcast16<k>(r);
+    computed_here(r);
+    owed(cut(std::integral_constant<int, 5>{}), cut(std::integral_constant<int, 6>{}));
+    double t = u * r;                              // lane i: L[i][k] / L[k][k] for i > k
+    computed_here(t);
+    owed(cut(std::integral_constant<int, 6>{}), std::integral_constant<int, OWED>{});
+    u_prev = u;
+    t_prev = t;
+    if constexpr (k < 15) row[k + 1] = fma(-u_next, t, row[k + 1]);
   });
-  const double rs = ok_mine ? rsqrt(d_mine) : 0.0;
+  const bool ok = d_mine > least && d_mine < 1.0e300;
+  const double rs = ok ? rsqrt(d_mine) : 0.0;
   static_for<0, 16>([&](auto ic) {
     constexpr int i = decltype(ic)::value;
     x[i] *= bcast16<i>(rs);
   });
-  return all_ok;
+  return __all(ok);
 }
 
-// Steps 2 and 3 for a matrix of P panels, by NW waves.  Ss (16P rows of pitch 16P + 1 doubles) holds
+// Doubles from a row of the factored matrix, and of a diagonal block of X, to the next.  With 2 modulo 16 the 16 rows that a
+// product's operands are read from begin four banks apart, so that neither 8- nor 16-byte reads of them collide (a pitch
+// of 1 modulo 16 does, twofold).
+constexpr int factor_pitch(int m) { return m + 2; }
+constexpr int XD_PITCH = factor_pitch(16);
+// Four consecutive doubles of a row, 16-byte aligned: a lane's part of an operand of a 16 x 16 x 16 product, of which step
+// ks takes element ks in all lanes (so that lane group lq contributes k = 4 lq + ks).
+struct Quad { double v[4]; };
+__device__ __forceinline__ Quad quad_at(const double *p) {
+  const double2 a = *reinterpret_cast<const double2 *>(p), b = *reinterpret_cast<const double2 *>(p + 2);
+  return Quad{{a.x, a.y, b.x, b.y}};
+}
+
+// Steps 2 and 3 for a matrix of P panels, by NW waves.  Ss (16P rows of factor_pitch(16P) doubles) holds
 // S + rho I in its lower 16 x 16 blocks; on return L is below the diagonal blocks, the diagonal
 // blocks of X = L^{-1} are in Xd and the blocks of X below the diagonal, transposed, in the upper
 // blocks of Ss (element X[j][c], block of j below block of c, is at Ss[c][j]).
@@ -121,39 +162,39 @@ __device__ __forceinline__ bool chol16_inverse(double (&row)[16], double d0, dou
 // !INVERSE: X is not wanted, only L and the diagonal blocks of X; waves 1 .. NW - 1 call row_done(p) (a compile-time
 // p) when X_pp and the blocks of L below it are complete.
 template <int P, int NW, bool INVERSE, class F>
-__device__ __forceinline__ void factor_panels(double *Ss, double (*Xd)[16][17], const double *d0_s,
+__device__ __forceinline__ void factor_panels(double *Ss, double (*Xd)[16][XD_PITCH], const double *d0_s,
                                               int *flag, F &&row_done) {
-  constexpr int SP = 16 * P + 1;
+  constexpr int SP = factor_pitch(16 * P);
   const int lane = threadIdx.x & 63, l16 = lane & 15, lq = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   // A_qr -= L_qp L_rp^T
   auto trail = [&](int q, int r, int p) {
+    const Quad a = quad_at(&Ss[(16 * q + l16) * SP + 16 * p + 4 * lq]);
+    const Quad b = quad_at(&Ss[(16 * r + l16) * SP + 16 * p + 4 * lq]);
     f64x4 acc;
 #pragma unroll
     for (int v = 0; v < 4; ++v) acc[v] = Ss[(16 * q + 4 * v + lq) * SP + 16 * r + l16];
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      const double a = -Ss[(16 * q + l16) * SP + 16 * p + 4 * ks + lq];
-      const double b = Ss[(16 * r + l16) * SP + 16 * p + 4 * ks + lq];
-      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
-    }
+    for (int ks = 0; ks < 4; ++ks) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-a.v[ks], b.v[ks], acc, 0, 0, 0);
 #pragma unroll
     for (int v = 0; v < 4; ++v) Ss[(16 * q + 4 * v + lq) * SP + 16 * r + l16] = acc[v];
   };
   // Y_qc += L_qp X_pc, c <= p
   auto grow = [&](int q, int c, int p) {
     double *y = &Ss[(16 * c + l16) * SP + 16 * q + lq];        // transposed: row 4v + lq, column l16
+    const Quad a = quad_at(&Ss[(16 * q + l16) * SP + 16 * p + 4 * lq]);
+    Quad b;
     f64x4 acc = {0.0, 0.0, 0.0, 0.0};
     if (c < p) {
+      b = quad_at(&Ss[(16 * c + l16) * SP + 16 * p + 4 * lq]);
 #pragma unroll
       for (int v = 0; v < 4; ++v) acc[v] = y[4 * v];
+    } else {
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) b.v[ks] = Xd[p][4 * lq + ks][l16];
     }
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      const double a = Ss[(16 * q + l16) * SP + 16 * p + 4 * ks + lq];
-      const double b = c == p ? Xd[p][4 * ks + lq][l16] : Ss[(16 * c + l16) * SP + 16 * p + 4 * ks + lq];
-      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
-    }
+    for (int ks = 0; ks < 4; ++ks) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a.v[ks], b.v[ks], acc, 0, 0, 0);
 #pragma unroll
     for (int v = 0; v < 4; ++v) y[4 * v] = acc[v];
   };
@@ -165,26 +206,38 @@ __device__ __forceinline__ void factor_panels(double *Ss, double (*Xd)[16][17], 
     }
     double row[16], x[16];
 #pragma unroll
-    for (int j = 0; j < 16; ++j) row[j] = Ss[(16 * p + l16) * SP + 16 * p + j];
+    for (int j = 0; j < 16; j += 4) {
+      const Quad r = quad_at(&Ss[(16 * p + l16) * SP + 16 * p + j]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) row[j + e] = r.v[e];
+    }
     if (!chol16_inverse(row, d0_s[16 * p + l16], x) && lane == 0) *flag = COMPACTOR_STATUS_PIVOT;
     if (lane < 16) {
 #pragma unroll
       for (int i = 0; i < 16; ++i) Xd[p][i][lane] = x[i];
     }
   };
-  // the others meanwhile: what panel p - 1 owes, without block (p, p)
+  // The others meanwhile: what panel p - 1 owes, without block (p, p): of every row q >= p the blocks c < p of Y and c >= p of
+  // A, dealt out in turn.
   auto owed = [&](int p) {
-    int t = 1;
-    for (int q = p; q < P; ++q) {
-      for (int r = p; r <= q; ++r) {
-        if (r == p && q == p) continue;
-        if (t == wave) trail(q, r, p - 1);
-        t = t == NW - 1 ? 1 : t + 1;
+    if constexpr (INVERSE) {
+      const int row0 = p * (p + 1) / 2;                        // blocks of the rows before
+      int q = p;
+      for (int i = wave - 1; i < P * (P + 1) / 2 - row0 - 1; i += NW - 1) {
+        const int g = row0 + i + (i >= p);
+        while (g >= (q + 1) * (q + 2) / 2) ++q;
+        const int c = g - q * (q + 1) / 2;
+        if (c < p) grow(q, c, p - 1);
+        else trail(q, c, p - 1);
       }
-      for (int c = 0; INVERSE && c < p; ++c) {
-        if (t == wave) grow(q, c, p - 1);
-        t = t == NW - 1 ? 1 : t + 1;
-      }
+    } else {
+      int t = 1;
+      for (int q = p; q < P; ++q)
+        for (int r = p; r <= q; ++r) {
+          if (r == p && q == p) continue;
+          if (t == wave) trail(q, r, p - 1);
+          t = t == NW - 1 ? 1 : t + 1;
+        }
     }
   };
   // all: the panel below the diagonal block, L_qp = A_qp X_pp^T, and row p of X, X_pc = -X_pp Y_pc
@@ -195,17 +248,16 @@ __device__ __forceinline__ void factor_panels(double *Ss, double (*Xd)[16][17], 
       f64x4 acc = {0.0, 0.0, 0.0, 0.0};
       if (i > p) {
         double *l = &Ss[(16 * i) * SP + 16 * p];
+        const Quad a = quad_at(l + l16 * SP + 4 * lq), b = quad_at(&Xd[p][l16][4 * lq]);
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks)
-          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(l[l16 * SP + 4 * ks + lq], Xd[p][l16][4 * ks + lq],
-                                                     acc, 0, 0, 0);
+        for (int ks = 0; ks < 4; ++ks) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a.v[ks], b.v[ks], acc, 0, 0, 0);
 #pragma unroll
         for (int v = 0; v < 4; ++v) l[(4 * v + lq) * SP + l16] = acc[v];
       } else {
         double *y = &Ss[(16 * i + l16) * SP + 16 * p + lq];
+        const Quad a = quad_at(&Xd[p][l16][4 * lq]), b = quad_at(&Ss[(16 * i + l16) * SP + 16 * p + 4 * lq]);
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks)
-          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-Xd[p][l16][4 * ks + lq], y[4 * ks], acc, 0, 0, 0);
+        for (int ks = 0; ks < 4; ++ks) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-a.v[ks], b.v[ks], acc, 0, 0, 0);
 #pragma unroll
         for (int v = 0; v < 4; ++v) y[4 * v] = acc[v];
       }
@@ -312,8 +364,8 @@ struct ShareSum {
 // Scratch of sketch_factor in LDS.
 template <int M>
 struct SketchFactor {
-  double Ss[M * (M + 1)];                          // S, then L (factor_panels)
-  double Xd[M / 16][16][17];
+  alignas(16) double Ss[M * factor_pitch(M)];      // S, then L (factor_panels)
+  alignas(16) double Xd[M / 16][16][XD_PITCH];
   double d0[M];
   static constexpr int PP = M + 4;                 // pitch of Phi: conflict-free reads
   float PH[D * PP];
@@ -330,7 +382,7 @@ struct SketchFactor {
 template <int M, class STORE>
 __device__ __forceinline__ void sketch_factor(SketchFactor<M> &F, const double (&sum)[Share<M>::TILES],
                                               const PhiRegs<M> &ph, float ridge_rel, STORE &&store) {
-  constexpr int P = M / 16, SP = M + 1, PP = SketchFactor<M>::PP;
+  constexpr int P = M / 16, SP = factor_pitch(M), PP = SketchFactor<M>::PP;
   constexpr int OWN = 3;                           // channel tiles of a wave: w - 1, w + 2, w + 5
   const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lq = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -399,13 +451,13 @@ __device__ __forceinline__ void sketch_factor(SketchFactor<M> &F, const double (
     for (int u = 0; u < OWN; ++u) {
       if (u == 2 && !third) continue;
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        float x = (float)w[u][v];
+      for (int v = 0; v < 4; v += 2) {
+        float x = (float)w[u][v], y = (float)w[u][v + 1];
 #pragma unroll
         for (int tt = 0; tt < W_TERMS; ++tt) {
-          const uint16_t b = bf16_rne(x);
-          x -= bf16_to_f32(b);
-          store(tt, 16 * pp + 4 * v + lq, 16 * (wave - 1 + 3 * u) + l16, b);
+          const unsigned b = split_bf16(x, y);
+          store(tt, 16 * pp + 4 * v + lq, 16 * (wave - 1 + 3 * u) + l16, (uint16_t)b);
+          store(tt, 16 * pp + 4 * v + 4 + lq, 16 * (wave - 1 + 3 * u) + l16, (uint16_t)(b >> 16));
         }
       }
     }

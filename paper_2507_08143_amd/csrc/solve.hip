@@ -296,9 +296,9 @@ __global__ __launch_bounds__(EXACT_THREADS) void exact_solve_kernel(
     const SegTable T, int tiles_per_wg, const float *__restrict__ partials,
     const double *__restrict__ sums, float ridge_rel, uint16_t *__restrict__ wt,
     int32_t *__restrict__ status, int *__restrict__ zero, long long zero_ints) {
-  constexpr int M = D, P = M / 16, SP = M + 1, NW = EXACT_THREADS / 64;
-  __shared__ double Ss[M * SP];        // G, then L and X = L^{-1} (factor_panels)
-  __shared__ double Xd[P][16][17];
+  constexpr int M = D, P = M / 16, SP = factor_pitch(M), NW = EXACT_THREADS / 64;
+  __shared__ __attribute__((aligned(16))) double Ss[M * SP];        // G, then L and X = L^{-1} (factor_panels)
+  __shared__ __attribute__((aligned(16))) double Xd[P][16][XD_PITCH];
   __shared__ double d0_s[M];
   __shared__ int flag_s;
 
@@ -371,11 +371,7 @@ __global__ __launch_bounds__(EXACT_THREADS) void exact_solve_kernel(
       for (int t = 0; t < W_TERMS; ++t) {
         unsigned w[4];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const uint16_t b = bf16_rne(x[e]);
-          w[e >> 1] = (e & 1) ? w[e >> 1] | (unsigned)b << 16 : (unsigned)b;
-          x[e] -= bf16_to_f32(b);
-        }
+        for (int e = 0; e < 8; e += 2) w[e >> 1] = split_bf16(x[e], x[e + 1]);
         *reinterpret_cast<uint4 *>(&wh[(t * M + 16 * p + r) * D + ch0]) = make_uint4(w[0], w[1], w[2], w[3]);
       }
     }
