@@ -278,22 +278,29 @@ __device__ __forceinline__ void factor_panels(double *Ss, double (*Xd)[16][XD_PI
       panel(p);
     }
     row_done(P - 1, wave, NW);
-  } else if (wave == 0) {
-#pragma unroll 1
-    for (int p = 0; p < P; ++p) {
-      pivots(p);
-      panel(p);
-    }
   } else {
-    static_for<0, P>([&](auto pc) {
-      constexpr int p = decltype(pc)::value;
-      if constexpr (p > 0) {
-        owed(p);
-        row_done(std::integral_constant<int, p - 1>{});
+    // Wave 0 first, and not as two sides of one condition: the compiler would join them before wave 0's side, which would
+    // then wait for everything that the other waves have requested by their end and, with it, for all loads of its own.
+    if (wave == 0) {
+#pragma unroll 1
+      for (int p = 0; p < P; ++p) {
+        pivots(p);
+        panel(p);
       }
-      panel(p);
-    });
-    row_done(std::integral_constant<int, P - 1>{});
+    }
+    int other = wave;
+    asm volatile("" : "+s"(other));
+    if (other != 0) {
+      static_for<0, P>([&](auto pc) {
+        constexpr int p = decltype(pc)::value;
+        if constexpr (p > 0) {
+          owed(p);
+          row_done(std::integral_constant<int, p - 1>{});
+        }
+        panel(p);
+      });
+      row_done(std::integral_constant<int, P - 1>{});
+    }
   }
 }
 
@@ -373,15 +380,16 @@ struct SketchFactor {
 };
 
 // One workgroup of 256: steps 2 to 4 (see solve.hip) from S in lower tiles and Phi.  store(plane, row, channel, bf16)
-// gets the planes of W^T; F.flag is the status, complete for all threads after a barrier.
+// gets the planes of W^T; F.flag is the status, complete for all threads after a barrier.  shadow(j), j = 0 .. M / 16 - 1, is
+// called by waves 1 to 3 before they wait for the pivots of panel j.
 // W^T = L^{-1} Phi^T by forward substitution, row blocks of 16: W_p = X_pp R_p with R_q = Phi_q^T - sum over r < q of
 // L_qr W_r, which wants no more of L^{-1} than its diagonal blocks X_pp.  Waves 1 to 3 do it in the shadow of the next
 // panel's pivots, each for its channels: a product's accumulators are the next one's operand as they are, so that
 // nothing of R or W passes through LDS, and behind the last pivot there are 12 products (k_s = 48; with rows of
 // L^{-1} times Phi^T there were 24: factorisation of 256 heads 18.5 us before, 16 now).
-template <int M, class STORE>
+template <int M, class STORE, class SHADOW>
 __device__ __forceinline__ void sketch_factor(SketchFactor<M> &F, const double (&sum)[Share<M>::TILES],
-                                              const PhiRegs<M> &ph, float ridge_rel, STORE &&store) {
+                                              const PhiRegs<M> &ph, float ridge_rel, STORE &&store, SHADOW &&shadow) {
   constexpr int P = M / 16, SP = factor_pitch(M), PP = SketchFactor<M>::PP;
   constexpr int OWN = 3;                           // channel tiles of a wave: w - 1, w + 2, w + 5
   const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lq = lane >> 4;
@@ -414,15 +422,25 @@ __device__ __forceinline__ void sketch_factor(SketchFactor<M> &F, const double (
     __syncthreads();
   }
 
-  f64x4 R[OWN][P];
+  f64x4 R[OWN][P] = {};
+  if (wave > 0) {                                  // uniform
+    float r[OWN][P][4];
 #pragma unroll
-  for (int u = 0; u < OWN; ++u)
+    for (int u = 0; u < OWN; ++u)
 #pragma unroll
-    for (int q = 0; q < P; ++q)
+      for (int q = 0; q < P; ++q)
 #pragma unroll
-      for (int v = 0; v < 4; ++v)                  // as a 16x16x4 product leaves it: row 4v + lq, channel l16
-        R[u][q][v] = wave > 0 ? (double)F.PH[(16 * min(wave - 1 + 3 * u, D / 16 - 1) + l16) * PP + 16 * q + 4 * v + lq] : 0.0;
+        for (int v = 0; v < 4; ++v)                // as a 16x16x4 product leaves it: row 4v + lq, channel l16
+          r[u][q][v] = F.PH[(16 * min(wave - 1 + 3 * u, D / 16 - 1) + l16) * PP + 16 * q + 4 * v + lq];
+#pragma unroll
+    for (int u = 0; u < OWN; ++u)
+#pragma unroll
+      for (int q = 0; q < P; ++q)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) R[u][q][v] = (double)r[u][q][v];
+  }
   const bool third = wave + 5 < D / 16;            // its third tile exists
+  if (wave > 0) shadow(std::integral_constant<int, 0>{});
   factor_panels<P, 4, false>(Ss, F.Xd, F.d0, &F.flag, [&](auto pc) {
     constexpr int pp = decltype(pc)::value;
     double a[4];
@@ -461,6 +479,7 @@ __device__ __forceinline__ void sketch_factor(SketchFactor<M> &F, const double (
         }
       }
     }
+    if constexpr (pp + 1 < P) shadow(std::integral_constant<int, pp + 1>{});
   });
 }
 

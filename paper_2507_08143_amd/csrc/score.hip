@@ -64,13 +64,14 @@ struct RunOut {
   static constexpr int APT = BURST / 256;          // a-values per thread and burst
   bool want_stat;
   const float *ap;                                 // of the workgroup's first token
-  double a_shift, s1 = 0.0, s2 = 0.0, a1 = 0.0, a2 = 0.0;
+  float a_first;                                   // (converted where it is used: not waited for before)
+  double s1 = 0.0, s2 = 0.0, a1 = 0.0, a2 = 0.0;
   float *sp;                                       // of the workgroup's first token
 
   __device__ __forceinline__ RunOut(const Seg &s, const Where &w, int tok_begin, float *scores, const double *ostat) {
     want_stat = ostat != nullptr && s.attn != nullptr;
     const float *head = want_stat ? s.attn + (long long)w.head * s.n : nullptr;
-    a_shift = want_stat ? (double)head[0] : 0.0;
+    a_first = want_stat ? head[0] : 0.f;
     ap = head + tok_begin;
     sp = scores + s.score_off + (long long)w.head * s.n + tok_begin;
   }
@@ -98,6 +99,7 @@ struct RunOut {
     }
     for (int i = lead + ((cnt - lead) & ~3) + tid; i < cnt; i += 256) dst[i] = sc_l[i];
     if (want_stat) {
+      const double a_shift = (double)a_first;
 #pragma unroll
       for (int j = 0; j < APT; ++j) {
         const int i = tid + 256 * j;
@@ -154,7 +156,9 @@ __device__ __forceinline__ void leave_hist(const SegTable &T, const Seg &s, cons
 // Sketched mode.  A workgroup walks tokens_per_wg tokens of one head in steps of 128 (32 per wave, two 16-token
 // sub-tiles).  Key rows arrive with fully coalesced streaming loads (a wave instruction covers
 // four whole 256-byte rows), pass through a wave-private LDS buffer, and are read back in the
-// MFMA B-operand arrangement; two steps of loads are in flight while a third is multiplied.
+// MFMA B-operand arrangement; a step of loads is in flight while the one before is multiplied.  (With two the kernel
+// is 2 to 3 % slower where the memory is busy: 256 heads of 32768 tokens 343 us, 352 with two, 345 where both are waited for
+// together.)
 // The multiply loop needs no workgroup barrier: a wave only reads what it wrote itself.  The
 // scores collect in LDS and leave in bursts of BURST tokens; a run may span several bursts (up to
 // SCORE_MAX_RUN tokens), so that what a workgroup pays once (staging W^T, the histogram, filling
@@ -171,11 +175,10 @@ __global__ __launch_bounds__(256, SOLVE && M == 64 ? 1 : 2) void score_kernel(
     int32_t *__restrict__ status, int *__restrict__ hist1, double *__restrict__ ostat) {
   constexpr int NSUB = 2, WTOK = 16 * NSUB, STEP = 4 * WTOK;     // tokens per wave / per WG step
   constexpr int NLD = WTOK * 16 / 64;                            // 16-B loads per lane per step
-  constexpr int AHEAD = 4;
   typedef WLayout<M> WL;
   __shared__ __attribute__((aligned(16))) uint16_t wl[W_TERMS * WL::PLANE];
   constexpr int BURST = SCORE_BURST, BSTEPS = BURST / STEP;
-  static_assert((BURST & (BURST - 1)) == 0 && BSTEPS % 2 == 0, "bursts end on even steps");
+  static_assert((BURST & (BURST - 1)) == 0, "bursts wrap round in LDS");
   struct Stream {
     // a wave stages 16 tokens at a time (its 32 tokens of a step in two halves); measured, a third
     // workgroup per CU does not pay, the smaller staging buffer does on the long-context shapes
@@ -211,27 +214,28 @@ __global__ __launch_bounds__(256, SOLVE && M == 64 ? 1 : 2) void score_kernel(
   const uint16_t *kp = head_ptr(s.k_score, s, w.head);
   const int ld_row = lane >> 4, ld_chunk = lane & 15;            // loader: 16 lanes per row
 
-  // this lane's piece of its first row; later rows are wave-uniform offsets away
-  const uint16_t *lane_base =
-      kp + (long long)(tok_begin + wave * WTOK + ld_row) * stride_t + ld_chunk * 8;
+  // A run's last step reads copies of its last row, whose scores nobody stores: with a load under a condition the number of
+  // loads under way depends on the way taken, and the wait for the shares of S, requested before, is one for the keys too.
+  const int last_row = tok_end - tok_begin - 1;
+  const uint16_t *run = kp + (long long)tok_begin * stride_t + ld_chunk * 8;
+  const uint16_t *lane_base = run + (long long)(wave * WTOK + ld_row) * stride_t;
   const long long row4 = 4 * stride_t, step_stride = (long long)STEP * stride_t;
-  auto load_step = [&](int it, uint4 (&stg)[NLD]) {
-    const int base = tok_begin + it * STEP + wave * WTOK + ld_row;
-    const uint16_t *p = lane_base + it * step_stride;
-    // wave-uniform: all 32 rows of the wave exist (every step but a head's last)
-    if (it < nsteps && tok_begin + it * STEP + (wave + 1) * WTOK <= tok_end) {
+  auto load_step = [&](int it, uint4 (&to)[NLD]) {
+    const uint16_t *at[NLD];
+    if (it * STEP + (wave + 1) * WTOK <= last_row + 1) {         // uniform: every step but a run's last
+      const uint16_t *p = lane_base + it * step_stride;
 #pragma unroll
-      for (int i = 0; i < NLD; ++i) stg[i] = load_stream16(p + i * row4);
+      for (int i = 0; i < NLD; ++i) at[i] = p + i * row4;
     } else {
 #pragma unroll
-      for (int i = 0; i < NLD; ++i) {
-        const int tok = base + 4 * i;
-        stg[i] = make_uint4(0, 0, 0, 0);
-        if (it < nsteps && tok < tok_end) stg[i] = load_stream16(p + i * row4);
-      }
+      for (int i = 0; i < NLD; ++i) at[i] = run + min(it * STEP + wave * WTOK + ld_row + 4 * i, last_row) * stride_t;
     }
+#pragma unroll
+    for (int i = 0; i < NLD; ++i) to[i] = load_stream16(at[i]);
+    __builtin_amdgcn_sched_barrier(0);             // they leave before what is multiplied meanwhile
   };
 
+  RunOut<BURST> out(s, w, tok_begin, scores, ostat);
   // the shares of S are wanted first, and loads arrive in order
   ShareSum<SOLVE ? M : 16> ss;
   const double *shares = nullptr;
@@ -240,34 +244,36 @@ __global__ __launch_bounds__(256, SOLVE && M == 64 ? 1 : 2) void score_kernel(
     ss.fetch(shares);
     __builtin_amdgcn_sched_barrier(0);
   }
-  uint4 stA[NLD], stB[NLD];
-  load_step(0, stA);
-  load_step(1, stB);
-  // W^T follows the first two steps of keys through the load queue and waits in registers, so
-  // that the third step of keys can be requested as soon as the first has arrived and not only
-  // once W^T is in LDS: a workgroup starts with three steps in flight
+  uint4 stg[NLD];
+  load_step(0, stg);
+  // W^T follows the first step of keys through the load queue and waits in registers, so that the second step can be
+  // requested as soon as the first has arrived and not only once W^T is in LDS
   constexpr int WN = (W_TERMS * WL::CHUNKS + 255) / 256;
   uint4 wreg[WN];
   if constexpr (SOLVE) {
     double sum[Share<M>::TILES];
     ss.add(shares, V.nshares, sum);
-    // The memory would wait for the factorisation: the wave's rows of the next four steps are brought as far as the L2
-    // by one dword a line.  Four are 128 KB a unit, as much as there is; with eight the first are lost again.
-    // compactor_score on MI355X, us without / with, k_s = 16, 32, 48, 64: 8 heads of 16384 32.4 / 31.1, 36.8 / 35.7, 42.5 /
-    // 41.4, 50.3 / 49.7, 32768 43.6 / 40.2, 47.9 / 45.6, 53.0 / 52.1, 62.3 / 62.3, 131072 102.7 / 99.4, 107.7 / 104.8, 114.0 /
-    // 110.8.  Not for runs of three steps and less, which have one left to bring at most.
-    unsigned ahead[AHEAD] = {};
-    if (nsteps > 3) {
-#pragma unroll
-      for (int u = 0; u < AHEAD; ++u) {
-        const long long row = (long long)tok_begin + (2 + u) * STEP + wave * WTOK + (lane >> 1);
-        ahead[u] = *reinterpret_cast<const unsigned *>(kp + min(row, tok_end - 1ll) * stride_t + 64 * (lane & 1));
-      }
-    }
+    // The memory would wait for the factorisation: the rows of the next two steps are brought as far as the L2 by one dword
+    // a line, a few at a time by the waves that wait for pivots.  More, or all at once, keep those waves from their part of the
+    // factorisation.  Whole call on MI355X, us with 0 / 2 / 4 / 5 / 6 steps: scores of 8 heads of 40007, k_s = 32, 48.6 / 47.5 /
+    // 47.7 / 48.6 / 49.7, 4 x 8 x 16383 blended 128.8 / 128.0 / 128.1 / 128.8 / 130.3, 8 heads of 131072 165.4 / 165.5 / 165.9 /
+    // 166.2 / 167.6; four steps by all waves before the factorisation 50.2, 133 and 171.
+    constexpr int AHEAD = 2, POINTS = M / 16, EACH = (AHEAD * STEP / 32 + 3 * POINTS - 1) / (3 * POINTS);
+    unsigned ahead[POINTS * EACH] = {};
     sketch_factor<M>(lds.f, sum, ph, V.ridge_rel,
-                     [&](int t, int row, int ch, uint16_t v) { wl[t * WL::PLANE + row * WPITCH + ch] = v; });
+                     [&](int t, int row, int ch, uint16_t v) { wl[t * WL::PLANE + row * WPITCH + ch] = v; },
+                     [&](auto jc) {
+                       constexpr int j = decltype(jc)::value;
 #pragma unroll
-    for (int u = 0; u < AHEAD; ++u) asm volatile("" ::"v"(ahead[u]));
+                       for (int u = j * EACH; u < (j + 1) * EACH; ++u) {
+                         const int at = STEP + 32 * (3 * u + wave - 1), rows = tok_end - tok_begin;
+                         if (at < min(rows, (1 + AHEAD) * STEP))       // uniform
+                           ahead[u] = *reinterpret_cast<const unsigned *>(
+                               kp + ((long long)tok_begin + min(at + (lane >> 1), rows - 1)) * stride_t + 64 * (lane & 1));
+                       }
+                     });
+#pragma unroll
+    for (int u = 0; u < POINTS * EACH; ++u) asm volatile("" ::"v"(ahead[u]));
     __syncthreads();
     if (w.tile == 0 && tid == 0 && lds.f.flag) atomicOr(&status[s.ghead0 + w.head], lds.f.flag);
     __syncthreads();
@@ -288,7 +294,7 @@ __global__ __launch_bounds__(256, SOLVE && M == 64 ? 1 : 2) void score_kernel(
   bool bad = false;
 
   bf16x8 kb[NSUB][4];
-  auto redistribute = [&](const uint4 (&stg)[NLD]) {
+  auto redistribute = [&](const uint4 (&from)[NLD]) {
     // redistribute through the wave's LDS buffer: rows in, B operands out.  Lanes exchange
     // data here without a workgroup barrier (LDS operations of one wave execute in order), so
     // wave-scope fences keep the compiler from moving the reads and writes across each other.
@@ -297,7 +303,7 @@ __global__ __launch_bounds__(256, SOLVE && M == 64 ? 1 : 2) void score_kernel(
       wave_lds_fence();
 #pragma unroll
       for (int i = 0; i < NLD / NSUB; ++i)
-        *reinterpret_cast<uint4 *>(&kw[(ld_row + 4 * i) * WPITCH + ld_chunk * 8]) = stg[st * (NLD / NSUB) + i];
+        *reinterpret_cast<uint4 *>(&kw[(ld_row + 4 * i) * WPITCH + ld_chunk * 8]) = from[st * (NLD / NSUB) + i];
       wave_lds_fence();
 #pragma unroll
       for (int kk = 0; kk < 4; ++kk)
@@ -345,10 +351,8 @@ __global__ __launch_bounds__(256, SOLVE && M == 64 ? 1 : 2) void score_kernel(
     }
   };
 
-  RunOut<BURST> out(s, w, tok_begin, scores, ostat);
-
-  redistribute(stA);            // waits for the first step of keys only
-  load_step(2, stA);
+  redistribute(stg);
+  if (nsteps > 1) load_step(1, stg);      // uniform
 #pragma unroll
   for (int i = 0; i < (SOLVE ? 0 : WN); ++i) {
     const int cidx = tid + 256 * i;
@@ -359,29 +363,25 @@ __global__ __launch_bounds__(256, SOLVE && M == 64 ? 1 : 2) void score_kernel(
   }
   __syncthreads();
 
-  // on entry of an iteration the operands of step `it` are in registers (kb) and the loads of
-  // steps it + 1 (stB) and it + 2 (stA) are in flight
-  for (int it = 0; it < nsteps; it += 2) {
+  auto leave = [&](int b0) {
+    const int cnt = min(BURST, tok_end - tok_begin - b0);
+    float av[RunOut<BURST>::APT];
+    out.fetch_a(b0, cnt, av);    // on their way while the waves meet
+    __syncthreads();
+    out.burst(sc_l, b0, cnt, av);
+  };
+  // the operands of step `it` are in registers (kb) and the loads of step it + 1 are in flight
+  for (int it = 0; it < nsteps; ++it) {
     multiply(it);
-    if (it + 1 < nsteps) {
-      redistribute(stB);
-      load_step(it + 3, stB);
-      multiply(it + 1);
+    if (it + 1 == nsteps) break;
+    if ((it + 1) % BSTEPS == 0) {                   // uniform: a burst is complete
+      leave((it / BSTEPS) * BURST);
+      __syncthreads();                              // before the next burst's scores overwrite these
     }
-    const bool last = it + 2 >= nsteps;
-    if (last || (it + 2) % BSTEPS == 0) {          // uniform: a burst is complete
-      const int b0 = (it / BSTEPS) * BURST, cnt = min(BURST, tok_end - tok_begin - b0);
-      float av[RunOut<BURST>::APT];
-      out.fetch_a(b0, cnt, av);    // on their way while the waves meet
-      __syncthreads();
-      out.burst(sc_l, b0, cnt, av);
-      if (!last) __syncthreads();                   // before the next burst's scores overwrite these
-    }
-    if (!last) {
-      redistribute(stA);
-      load_step(it + 4, stA);
-    }
+    redistribute(stg);
+    if (it + 2 < nsteps) load_step(it + 2, stg);    // uniform
   }
+  leave((nsteps - 1) / BSTEPS * BURST);
   if (__any(bad)) {
     if (lane == 0) atomicOr(&status[s.ghead0 + w.head], COMPACTOR_STATUS_NONFINITE);
   }

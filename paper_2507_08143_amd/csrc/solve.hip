@@ -245,7 +245,8 @@ __global__ __launch_bounds__(256, 2) void sketch_solve_kernel(
     zero_slice(zero, zero_ints);
   }
   uint16_t *wh = wt + (size_t)lhead * (W_TERMS * M * D);
-  sketch_factor<M>(F, sum, ph, ridge_rel, [&](int tt, int row, int ch, uint16_t v) { wh[(tt * M + row) * D + ch] = v; });
+  sketch_factor<M>(F, sum, ph, ridge_rel, [&](int tt, int row, int ch, uint16_t v) { wh[(tt * M + row) * D + ch] = v; },
+                   [](auto) {});
   __syncthreads();
   if (tid == 0) {
     const Where w = locate_head(T, lhead);

@@ -561,6 +561,20 @@ def test_exact_scores_at_the_edges_of_steps_and_bursts(C, n, blend):
     U.run_and_check(C, w, DEV, tune={"score_tokens": 32768})
 
 
+# Sketched mode takes steps of 128 tokens and reads copies of a run's last row beyond its end; a run may have brought two steps
+# ahead: one to five steps and a token to either side, token by token layout; with W^T from a kernel of its own too
+@pytest.mark.parametrize("ks,n", [(16, 127), (48, 128), (64, 129), (32, 255), (48, 257), (16, 384), (48, 385), (64, 513), (32, 641)])
+@pytest.mark.parametrize("L", [1, 257])
+def test_sketched_scores_at_the_edges_of_steps(C, ks, n, L):
+    w = W.config1(DEV, L=L, H=1, n=n)
+    w.sketch_dim = ks
+    r = w.requests[0]
+    r.k = r.k.expand(L, 2, n, 128).permute(0, 2, 1, 3).contiguous().permute(0, 2, 1, 3)[:, 1:]
+    r.v = r.v.expand(L, 2, n, 128).permute(0, 2, 1, 3).contiguous().permute(0, 2, 1, 3)[:, 1:]
+    stats, _ = U.run_and_check(C, w, DEV, heads=[(0, 0, 0), (0, L - 1, 0)], tune={"score_tokens": 4096})
+    _say("  k_s = %d, %d heads of %d: max rel err %.3g" % (ks, L, n, stats["max_rel"]))
+
+
 def test_config2_small(C):
     _say("config 2 shape, 2 layers x 8 heads, n=6000")
     st, _ = U.run_and_check(C, W.config2(device=DEV, L=2, H=8, n=6000), DEV)
