@@ -75,41 +75,37 @@ int compute_units() {
 }
 
 // Gram: a persistent launch, each workgroup taking an equal run of 64-row tiles.  Every (workgroup, head) partial costs
-// the factorisation 40 KB, so the fewer heads and tiles, the fewer workgroups: one pair (see gram_kernel) a compute unit,
-// one plain workgroup a unit where a few heads give it 8 to 24 (exact mode 32) tiles (the pair's end, where its halves meet,
-// is longer than what its loads save), and two plain ones for long runs, which stream a little faster than one pair, and
-// where there are heads for every unit (256 of 1024 tokens 68.8 / 69.1).
-// A pair takes the place of two runs whose partials met in fp64 and therefore folds, except where a workgroup's share is the
-// 8 tiles that it has at least, which a plain one would sum in one run.  For the same reason a plain one a unit is for
-// the heads and tiles at which it always was.
-// compactor_score on MI355X, keys not in the last-level cache, us with one plain workgroup a unit / two / a pair / a pair that
-// folds, tiles a unit in brackets.  k_s = 48: one head of 8192 (0.5) 31.6 / 31.5 / 31.1 / 31.4; 8 heads of 8192 (4) 35.9 / 36.1 /
-// 35.4 / 36.0, 16384 (8) 42.3 / 42.4 / 43.9 / 44.2, 32768 (16) 54.0 / 57.6 / 55.6 / 56.0, 48000 (23) 64.0 / 69.9 / 65.8 / 65.4,
-// 52000 (25) 67.4 / 72.6 / 67.7 / 67.9, 65536 (32) 75.3 / 79.3 / 74.5 / 75.0, 131072 (64) 118.7 / 114.7 / 112.6 / 113.9, 147000
-// (72) 135.9 / 131.6 / 128.2 / 128.8; 16 of 24000 (23) 63.5 / 65.5 / 62.7 / 63.6, 26000 (25) 65.4 / 67.9 / 65.1 / 66.0; 32 of 4096
-// (8) 42.6 / 42.6 / 42.7 / 43.4, 8000 (16) 54.5 / 57.6 / 55.2 / 55.8, 10000 (20) 59.3 / 62.2 / 60.7 / 61.4, 36000 (70) 134.6 /
-// 126.4 / 125.7 / 126.8, 47000 (92) 163.6 / 153.1 / 152.0 / 153.3; 64 of 2048 (8) 46.0 / 46.0 / 46.3 / 47.3, 4096 (16) 57.3 /
-// 59.3 / 58.8 / 59.2; 128 of 4096 (32) 80.5 / 83.3 / 79.9 / 81.3, 9216 (72) 143.4 / 134.7 / 133.6 / 135.1.  Exact mode: 8 of 8192
-// (4) 56.1 / 55.9 / 55.8 / 56.0, 32768 (16) 81.9 / 92.8 / 84.1 / 84.1, 65536 (32) 102.2 / 112.7 / 104.1 / 103.6, 73728 (36)
-// 113.3 / 119.3 / 112.0 / 111.4, 131072 (64) 153.7 / 154.8 / 145.9 / 147.8, 200000 (98) 207 / 203 / 195 / 197; 32 of 12288 (24) 89.2 /
-// 93.1 / 89.6 / 90.5, 18000 (35) 107.2 / 107.8 / 104.6 / 105.8, 57000 (111) 223.1 / 206.6 / 205.8 / 205.2; 64 of 8192 (32) 96.8 /
-// 100.4 / 96.5 / 98.4.
-struct GramPlan { int nwg, tiles_per_wg; GramKind kind; };
+// the factorisation 40 KB, so there is one workgroup a compute unit as long as its run stays short; long ones stream a little
+// faster with two.
+// Where that one workgroup sums its run as it goes on and where tile by tile (fold, see gram_kernel) goes by precision: as it
+// goes on up to 4 tiles, and up to 24 (17 to 32 heads: 16; exact mode: 32) with few heads and 8 tiles a unit or more; a call of other
+// sizes would else sum twice the rows in one accumulator that it used to.
+// compactor_score on MI355X, keys not in the last-level cache, us with one workgroup a unit / folding / two, tiles a unit in
+// brackets.  k_s = 48: 8 heads of 8192 (4) 30.8 / 31.4 / 30.7, 16384 (8) 37.0 / 37.8 / 37.0, 32768 (16) 46.3 / 47.8 / 51.7, 48000 (23)
+// 55.9 / 56.6 / 62.1, 65536 (32) 64.6 / 65.1 / 70.4, 131072 (64) 102 / 102 / 107, 147000 (72) 118.6 / 119.1 / 121.3; 16 of 32768 (32)
+// 63.6 / 64.2 / 68.8; 32 of 8000 (16) 46.9 / 48.1 / 50.3, 32768 (64) 102 / 102 / 106, 47000 (92) 141 / 142 / 146; 64 of 2048 (8) 40.1 / 40.7 /
+// 40.1, 4096 (16) 49.5 / 50.0 / 52.4; 128 of 4096 (32) 70.1 / 70.8 / 74.9, 16384 (128) 188 / 192 / 193; 192 of 8192 (96) 167 / 164 / 167; 256
+// of 1024 (16) 57.3 / 57.8 / 60.3, 2048 (32) 75.3 / 76.0 / 79.5, 4096 (64) 113 / 113 / 117, 8192 (128) 195 / 198 / 199.  Exact mode: 8 of
+// 65536 (32) 88.8 / 89.9 / 99.6, 131072 (64) 127 / 129 / 138; 32 of 18000 (35) 92 / 94 / 97, 57000 (111) 186 / 188 / 191; 256 of 4096 (64)
+// 126 / 126 / 128, 8192 (128) 206 / 211 / 210.
+struct GramPlan { int nwg, tiles_per_wg; bool fold; };
 GramPlan gram_plan(const compactor_params_t *p, const SegTable &T, int cus) {
   const long long total = total_tiles(T);
   const bool exact = p->sketch_dim == 0;
-  const int single_most = T.nheads <= 16 ? (exact ? 32 : 24) : T.nheads <= 32 ? (exact ? 32 : 16) : 0;
-  const bool single = total >= 8ll * cus && total < (long long)single_most * cus;
+  const int plain_most = T.nheads <= 16 ? (exact ? 32 : 24) : T.nheads <= 32 ? (exact ? 32 : 16) : 0;
+  const bool one = total < 112ll * cus, plain = total >= 8ll * cus && total < (long long)plain_most * cus;
   GramPlan g;
-  g.kind = single || T.nheads >= cus || total >= (exact ? 112ll : 72ll) * cus ? GRAM_PLAIN
-           : total <= 8ll * cus                                               ? GRAM_PAIR
-                                                                              : GRAM_PAIR_FOLD;
-  long long want = p->gram_wgs > 0 ? p->gram_wgs : (single || g.kind != GRAM_PLAIN ? 1ll : 2ll) * cus;
+  long long want = p->gram_wgs > 0 ? p->gram_wgs : (one ? 1ll : 2ll) * cus;
   if (want > total) want = total;
   if (want < 1) want = 1;
   g.tiles_per_wg = (int)((total + want - 1) / want);
-  // not below 8 tiles (512 rows) a workgroup: every partial costs a 40 KB round trip
-  if (g.tiles_per_wg < 8 && p->gram_wgs <= 0) g.tiles_per_wg = 8;
+  // Not below 8 tiles (512 rows) a workgroup: every partial costs a 40 KB round trip; in small calls 4, where the run is what
+  // takes longest.  compactor_score, us with at least 4 / 8 tiles: one head of 2048 24.6 / 27.6, 4096 25.5 / 27.5, 8192 27.0 / 28.3,
+  // 8 of 1024 25.7 / 27.6, 2048 26.3 / 28.3, 4096 (512 tiles) 28.2 / 28.8, 8192 32.8 / 31.7; 64 of 1024 36.0 / 35.4; exact mode, 8 of
+  // 4096 46.5 / 45.6.
+  const int least = !exact && total <= 2ll * cus ? 4 : 8;
+  if (g.tiles_per_wg < least && p->gram_wgs <= 0) g.tiles_per_wg = least;
+  g.fold = one && !plain && g.tiles_per_wg > 4;
   g.nwg = (int)((total + g.tiles_per_wg - 1) / g.tiles_per_wg);
   return g;
 }
@@ -192,7 +188,9 @@ GroupBytes group_bytes_needed(const compactor_params_t *p, const SegTable &T, bo
   const int cus = compute_units();
   const GramPlan gp = gram_plan(p, T, cus);
   GroupBytes g;
-  g.partials = align_up(((size_t)gp.nwg + T.nheads) * GRAM_PARTIAL_FLOATS * sizeof(float));
+  // heads for every unit: room for the two workgroups a unit that they get when they are long, whatever their length
+  const size_t gram_wgs = T.nheads < cus ? gp.nwg : gp.nwg < 2 * cus ? 2 * (size_t)cus : gp.nwg;
+  g.partials = align_up((gram_wgs + T.nheads) * GRAM_PARTIAL_FLOATS * sizeof(float));
   // Many workgroups per head form S = Phi^T G Phi (exact mode: G) only where the heads alone do not fill
   // the chip.  Factorisation stage on MI355X, us with / without shares, n = 2048:
   //   heads         8           64          128         256         512         1024       2048       4096
@@ -336,7 +334,7 @@ int enqueue_score(const compactor_params_t *p, const SegTable &T, const GroupByt
   const int rpw = gp.tiles_per_wg;
   const Marks m{p->stage_events, st};
   MARK(m, 0);
-  HIP_TRY(launch_gram(T, gp.nwg, gp.tiles_per_wg, gp.kind, partials, st));
+  HIP_TRY(launch_gram(T, gp.nwg, gp.tiles_per_wg, gp.fold, partials, st));
   MARK(m, COMPACTOR_STAGE_GRAM + 1);
   MARK(m, COMPACTOR_STAGE_REDUCE + 1);       // the fp64 sum of the partials is part of the next kernel
   double *shares =

@@ -228,7 +228,7 @@ __host__ __device__ __forceinline__ int sample_line(int g, int lines) {
 // about 7.1 TB/s against 6.2 TB/s for a plain slab read on MI355X).
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ uint4 load_stream16(const void *p) {
-  const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
+  const u32x4 v = __builtin_nontemporal_load((const __attribute__((address_space(1))) u32x4 *)p);   // never LDS or scratch
   return make_uint4(v.x, v.y, v.z, v.w);
 }
 __device__ __forceinline__ void store_stream16(void *p, const uint4 &v) {
@@ -359,11 +359,8 @@ __device__ __forceinline__ long long partial_base(const SegTable &T, int lhead, 
 // All of them enqueue on `st` and return the hipGetLastError() of their launches.
 
 // Partial Gram matrices: the 10 upper 32x32 blocks (fp32) per (workgroup, head) intersection,
-// nwg + nheads slots.  GRAM_PAIR: workgroups of twice the waves, whose halves' sums meet before they leave (the number
-// of partials is the same); GRAM_PAIR_FOLD: the same with every tile added up by itself (see gram_kernel).
-enum GramKind { GRAM_PLAIN, GRAM_PAIR, GRAM_PAIR_FOLD };
-hipError_t launch_gram(const SegTable &T, int nwg, int tiles_per_wg, GramKind kind, float *partials,
-                       hipStream_t st);
+// nwg + nheads slots.  fold: every tile is added up by itself (see gram_kernel).
+hipError_t launch_gram(const SegTable &T, int nwg, int tiles_per_wg, bool fold, float *partials, hipStream_t st);
 
 // Factorisation: partial Gram blocks -> W^T ([term][k_s][128] per head as W_TERMS bf16 planes; exact
 // mode: [term][128][128], rows up to the end of their group of 32 channels) and the status word.

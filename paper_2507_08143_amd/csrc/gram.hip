@@ -45,33 +45,30 @@ __device__ __forceinline__ bf16x4 lds_read_tr(const unsigned char *p) {
 constexpr int GRAM_OCC = 2;         // waves per SIMD the register budget is set for
 constexpr int GRAM_TG_UNROLL = 4;   // 16-token steps unrolled together (more operands in flight)
 //
-// PAIR: a workgroup of two such groups of 4 waves, each of which streams half of the run (the first or the second)
-// through tile buffers of its own.  Twice the loads are in flight, as with two
-// workgroups on a compute unit, but what the groups have of the same head leaves as one partial: the second group's
-// waits in LDS for the first's.  Where it pays: gram_plan.
-// FOLD: two plain workgroups' partials meet in fp64 in the factorisation, those of two groups in fp32 here.  So that
-// nothing is lost by it, a group adds every tile's products up by themselves and then to its sums: a product passes through
-// four roundings in the accumulator of the matrix core, one for every tile behind it, and the one of the join, where
-// a plain workgroup's passes through four for every tile behind it.  Relative error of the scores against 64 bits, two
-// plain workgroups a unit / folding pairs: exact mode, deficient keys, 64 heads of 8192 9.4e-6 / 7.6e-6, 128 of 4096 9.5e-6 /
-// 7.7e-6, 32 of 32768 9.7e-6 / 7.5e-6; k_s = 48, keys of low rank, 32 of 16384 4.6e-6 / 4.1e-6, 128 of 4096 4.8e-6 /
-// 4.2e-6.  At every tile and not at every fourth, say, because a fold under a condition makes the compiler copy the
-// accumulators where the paths join (8 heads of 131072, whole call 172.0 us, 171.6 so, 170.4 without folds).  (Time: gram_plan.)
+// FOLD: long runs in one workgroup a compute unit, which leaves half as many partials as two, and no less precise: the
+// products of every two tiles are added up by themselves and then to the sum of those before, so that a product passes
+// through eight roundings in the accumulator of the matrix core and one for every second tile behind it, where without FOLD
+// it passes through four for every tile behind it.  Relative error of the scores against 64 bits,
+// two workgroups a unit that do not / one that folds: exact mode, deficient keys, 64 heads of 8192 9.4e-6 / 7.6e-6, 128 of 4096
+// 9.5e-6 / 7.7e-6, 256 of 1024 7.8e-6 / 7.6e-6; k_s = 48, keys of low rank, 32 of 16384 4.6e-6 / 4.1e-6, 128 of 4096 4.8e-6 / 4.2e-6, 256
+// of 4096 4.6e-6 / 4.2e-6.  At every second tile and not at every fourth, say, because a fold under a condition makes
+// the compiler copy the accumulators where the paths join.
+// Key loads stand under no condition (past a head's end its last row, cleared on the way to LDS; past the run's end one
+// piece for all lanes): two tiles are under way while a third is multiplied only if the number of loads behind the one that
+// is waited for does not depend on the way taken.  With conditions every second tile waited for all loads
+// (one workgroup of 8 waves a unit: 32 heads of 50001 tokens 73 us and 67 now, 8 of 131072 50 and 46; four a unit, 8 of
+// 40007 21 and 18).
 // The body is compiled once per wave of a group: which blocks a wave owns is then known
 // at compile time, and the accumulators stay in fixed registers (a run-time switch inside the
 // loop makes the compiler copy them at every join).
-template <int wave, bool PAIR, bool FOLD>
+template <int wave, bool FOLD>
 __device__ __forceinline__ void gram_body(const SegTable &T, int tiles_per_wg, long long total,
-                                          float *__restrict__ partials, unsigned char *lds) {
-  const int group = PAIR ? __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8) : 0;
-  const int steps = PAIR ? (tiles_per_wg + 1) / 2 : tiles_per_wg;          // of a group, all of which meet
-  const long long first_tile = (long long)blockIdx.x * tiles_per_wg;
-  const long long g0 = first_tile + group * steps;
-  const int count = (int)min((long long)(PAIR && group ? tiles_per_wg - steps : steps), total - g0);
-  if (!PAIR && count <= 0) return;       // (a second group without tiles comes along)
-  unsigned char *smem = lds + (PAIR ? group * 2 * TILE_BYTES : 0);
+                                          float *__restrict__ partials, unsigned char *smem) {
+  const long long g0 = (long long)blockIdx.x * tiles_per_wg;
+  const int count = (int)min((long long)tiles_per_wg, total - g0);
+  if (count <= 0) return;
 
-  const int tid = threadIdx.x & 255, lane = tid & 63;
+  const int tid = threadIdx.x, lane = tid & 63;
   const int ld_row = tid >> 4, ld_chunk = tid & 15;   // loader: 16 lanes cover one 256-B row
 
   f32x16 acc[3], sum[3];           // sum: with FOLD, the tiles before
@@ -79,36 +76,30 @@ __device__ __forceinline__ void gram_body(const SegTable &T, int tiles_per_wg, l
   for (int b = 0; b < 3; ++b)
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[b][v] = sum[b][v] = 0.f;
-  auto &left = FOLD ? sum : acc;   // where the sums of a head are once they are complete
   const int nblk = wave < 2 ? 3 : 2;
   const int first = wave == 0 ? 0 : (wave == 1 ? 3 : (wave == 2 ? 6 : 8));
-  auto fold = [&] {
-    if constexpr (FOLD) {
-#pragma unroll
-      for (int b = 0; b < 3; ++b) {
-        if (b < nblk) {
-#pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            sum[b][v] += acc[b][v];
-            acc[b][v] = 0.f;
-          }
-        }
-      }
-    }
-  };
-
   TileCursor L, C;                 // load cursor runs two tiles ahead of the compute cursor
-  cursor_seek<GRAM_TILE>(T, PAIR ? min(g0, total - 1) : g0, L);
+  cursor_seek<GRAM_TILE>(T, g0, L);
   C = L;
 
   auto load_tile = [&](int t, uint4 (&stage)[4]) {   // t: tile number inside this workgroup
+    const uint16_t *at[4];
+    const int row0 = L.tile * GRAM_TILE;
+    if (t >= count) {                    // uniform: one piece for all lanes, used by nobody
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int row = L.tile * GRAM_TILE + 16 * i + ld_row;
-      stage[i] = make_uint4(0, 0, 0, 0);
-      if (t < count && row < L.n)
-        stage[i] = load_stream16(L.kp + (long long)row * L.stride_t + ld_chunk * 8);
+      for (int i = 0; i < 4; ++i) at[i] = L.kp;
+    } else if (row0 + GRAM_TILE <= L.n) {
+      const uint16_t *p = L.kp + (long long)(row0 + ld_row) * L.stride_t + ld_chunk * 8;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) at[i] = p + 16 * i * L.stride_t;
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        at[i] = L.kp + (long long)min(row0 + 16 * i + ld_row, L.n - 1) * L.stride_t + ld_chunk * 8;
     }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) stage[i] = load_stream16(at[i]);
+    __builtin_amdgcn_sched_barrier(0);
     cursor_next<GRAM_TILE>(T, L);
   };
 
@@ -117,8 +108,9 @@ __device__ __forceinline__ void gram_body(const SegTable &T, int tiles_per_wg, l
   const int c16 = lane & 15, half = (lane >> 4) & 1, g = lane >> 5;
   const int tr_off = ((8 * g + (c16 >> 2)) * PITCH + 16 * half + 4 * (c16 & 3)) * 2;
 
-#define GRAM_MFMA(b, x, y) acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[x], op[y], acc[b], 0, 0, 0)
-  auto compute_tile = [&](const unsigned char *buf) {
+#define GRAM_MFMA(b, x, y) \
+  acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[x], op[y], FOLD && !odd && tg == 0 ? f32x16{} : acc[b], 0, 0, 0)
+  auto compute_tile = [&](const unsigned char *buf, bool odd) {
 #pragma unroll GRAM_TG_UNROLL
     for (int tg = 0; tg < GRAM_TILE / 16; ++tg) {        // 16 tokens per MFMA step
       const unsigned char *p = buf + tr_off + tg * 16 * PITCH * 2;
@@ -134,9 +126,20 @@ __device__ __forceinline__ void gram_body(const SegTable &T, int tiles_per_wg, l
       if constexpr (wave == 2) { GRAM_MFMA(0, 1, 3); GRAM_MFMA(1, 2, 2); }
       if constexpr (wave == 3) { GRAM_MFMA(0, 2, 3); GRAM_MFMA(1, 3, 3); }
     }
+    if (FOLD && odd) {
+#pragma unroll
+      for (int b = 0; b < 3; ++b)
+        if (b < nblk) sum[b] += acc[b];
+    }
   };
 #undef GRAM_MFMA
-  auto store_tile = [&](unsigned char *buf, const uint4 (&stage)[4]) {
+  auto store_tile = [&](unsigned char *buf, uint4 (&stage)[4]) {
+    const int rows = C.n - C.tile * GRAM_TILE;           // of the tile that there are
+    if (rows < GRAM_TILE) {              // uniform
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (16 * i + ld_row >= rows) stage[i] = make_uint4(0, 0, 0, 0);
+    }
 #pragma unroll
     for (int i = 0; i < 4; ++i)
       *reinterpret_cast<uint4 *>(buf + ((ld_row + 16 * i) * PITCH + ld_chunk * 8) * 2) = stage[i];
@@ -152,12 +155,12 @@ __device__ __forceinline__ void gram_body(const SegTable &T, int tiles_per_wg, l
   // ends is parked in LDS (each wave its own blocks, no barrier needed) and leaves with the last
   // one; only a workgroup that crosses more than one head boundary writes mid-run, with
   // streaming stores.
-  // PAIR: the place belongs to the second group, for the head that the first one ends in.
-  float *park = reinterpret_cast<float *>(lds + (PAIR ? 4 : 2) * TILE_BYTES);
+  float *park = reinterpret_cast<float *>(smem + 2 * TILE_BYTES);
   int parked_lhead = -1;
-  const int first_lhead = T.s[C.seg].lhead0 + C.hh;      // the group's first head
   enum { TO_GLOBAL, TO_GLOBAL_STREAM, TO_LDS };
-  auto flush = [&](int lhead, int how) {
+  // odd: with FOLD, the products of the last tile are in the sums
+  auto flush = [&](int lhead, int how, bool odd) {
+    auto left = [&](int b, int v) { return !FOLD ? acc[b][v] : odd ? sum[b][v] : sum[b][v] + acc[b][v]; };
     float *out = how == TO_LDS ? park
                                : partials + ((size_t)blockIdx.x + lhead) * GRAM_PARTIAL_FLOATS;
 #pragma unroll
@@ -166,42 +169,32 @@ __device__ __forceinline__ void gram_body(const SegTable &T, int tiles_per_wg, l
         float *ob = out + (first + b) * GBLK;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          const float4 v = make_float4(left[b][4 * q], left[b][4 * q + 1], left[b][4 * q + 2], left[b][4 * q + 3]);
+          const float4 v = make_float4(left(b, 4 * q), left(b, 4 * q + 1), left(b, 4 * q + 2), left(b, 4 * q + 3));
           if (how == TO_GLOBAL_STREAM)
             store_stream16(ob + (64 * q + lane) * 4, make_uint4(__float_as_uint(v.x), __float_as_uint(v.y),
                                                                  __float_as_uint(v.z), __float_as_uint(v.w)));
           else
             *reinterpret_cast<float4 *>(ob + (64 * q + lane) * 4) = v;
-          left[b][4 * q] = left[b][4 * q + 1] = left[b][4 * q + 2] = left[b][4 * q + 3] = 0.f;
+#pragma unroll
+          for (int e = 4 * q; e < 4 * q + 4; ++e) acc[b][e] = sum[b][e] = 0.f;
         }
       }
     }
   };
   bool dirty = false;
-  int keep_lhead = -1;                   // PAIR: the head of what is still in the accumulators, if complete
-  auto finish_tile = [&](bool last_of_run) {       // after a tile has been multiplied
+  auto finish_tile = [&](bool last_of_run, bool odd) {       // after a tile has been multiplied
     dirty = true;
-    fold();
     if (C.tile + 1 == C.tph) {
       const int lhead = T.s[C.seg].lhead0 + C.hh;
-      if (PAIR) {
-        if (group && lhead == first_lhead) {
-          flush(lhead, TO_LDS);          // where the first group has no part of it, copied from there
-          parked_lhead = lhead;
-        } else if (!last_of_run) {
-          flush(lhead, TO_GLOBAL_STREAM);
-        } else {
-          keep_lhead = lhead;
-        }
-      } else if (last_of_run) {
-        flush(lhead, TO_GLOBAL);
+      if (last_of_run) {
+        flush(lhead, TO_GLOBAL, odd);
       } else if (parked_lhead < 0) {
-        flush(lhead, TO_LDS);
+        flush(lhead, TO_LDS, odd);
         parked_lhead = lhead;
       } else {
-        flush(lhead, TO_GLOBAL_STREAM);
+        flush(lhead, TO_GLOBAL_STREAM, odd);
       }
-      if (!PAIR || !last_of_run || parked_lhead == lhead) dirty = false;
+      dirty = false;
     }
     cursor_next<GRAM_TILE>(T, C);
   };
@@ -210,54 +203,30 @@ __device__ __forceinline__ void gram_body(const SegTable &T, int tiles_per_wg, l
   uint4 stA[4], stB[4];
   load_tile(0, stA);
   load_tile(1, stB);
-  // (PAIR: every group passes the barriers of `steps` tiles)
-  const int meet = PAIR ? steps : count;
-  for (int t = 0; t < meet; t += 2) {
+  // (one way out of the loop, for the same reason)
+  int t = 0;
+  for (; t + 2 <= count; t += 2) {
     store_tile(smem, stA);
     __syncthreads();
     load_tile(t + 2, stA);
-    if (!PAIR || t < count) {
-      compute_tile(smem);
-      finish_tile(t + 1 == count);
-    }
-    if (t + 1 < meet) {
-      store_tile(smem + TILE_BYTES, stB);
-      __syncthreads();
-      load_tile(t + 3, stB);
-      if (!PAIR || t + 1 < count) {
-        compute_tile(smem + TILE_BYTES);
-        finish_tile(t + 2 == count);
-      }
-    }
-  }
-  if constexpr (PAIR) {
-    int mine = keep_lhead >= 0 ? keep_lhead : T.s[C.seg].lhead0 + C.hh;   // the head of the accumulators, if dirty
-    if (group && dirty && mine == first_lhead) {         // all of the group's tiles are of one head
-      flush(mine, TO_LDS);
-      parked_lhead = mine;
-      dirty = false;
-    }
-    int *shared = reinterpret_cast<int *>(lds + 4 * TILE_BYTES + GRAM_PARTIAL_FLOATS * 4);
-    if (lane == 0 && wave == 0) shared[group] = group ? parked_lhead : (dirty ? mine : -1);
+    compute_tile(smem, false);
+    finish_tile(t + 1 == count, false);
+    store_tile(smem + TILE_BYTES, stB);
     __syncthreads();
-    const bool joined = shared[0] >= 0 && shared[0] == shared[1];
-    if (!group && joined) {
-#pragma unroll
-      for (int b = 0; b < 3; ++b) {
-        if (b < nblk) {
-          const float *ob = park + (first + b) * GBLK;
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const float4 v = *reinterpret_cast<const float4 *>(ob + (64 * q + lane) * 4);
-            left[b][4 * q] += v.x; left[b][4 * q + 1] += v.y; left[b][4 * q + 2] += v.z; left[b][4 * q + 3] += v.w;
-          }
-        }
-      }
-    }
-    if (joined) parked_lhead = -1;
-    if (dirty) flush(mine, TO_GLOBAL);
-  } else {
-    if (dirty) flush(T.s[C.seg].lhead0 + C.hh, TO_GLOBAL);
+    load_tile(t + 3, stB);
+    compute_tile(smem + TILE_BYTES, true);
+    finish_tile(t + 2 == count, true);
+  }
+  if (t < count) {
+    store_tile(smem, stA);
+    __syncthreads();
+    compute_tile(smem, false);
+    finish_tile(true, false);
+  }
+  if (dirty) {
+    const int lhead = T.s[C.seg].lhead0 + C.hh;
+    if (t < count) flush(lhead, TO_GLOBAL, false);
+    else flush(lhead, TO_GLOBAL, true);
   }
   if (parked_lhead >= 0) {         // the parked partial: every lane copies what it wrote itself
     float *out = partials + ((size_t)blockIdx.x + parked_lhead) * GRAM_PARTIAL_FLOATS;
@@ -274,31 +243,25 @@ __device__ __forceinline__ void gram_body(const SegTable &T, int tiles_per_wg, l
   }
 }
 
-template <bool PAIR, bool FOLD>
-__global__ __launch_bounds__(PAIR ? 512 : 256, GRAM_OCC) void gram_kernel(const SegTable T, int tiles_per_wg,
-                                                                          long long total,
-                                                                          float *__restrict__ partials) {
-  // two key tiles a group and room for one parked partial Gram matrix (and two words)
-  __shared__ __attribute__((aligned(16))) unsigned char
-      smem[(PAIR ? 4 : 2) * TILE_BYTES + GRAM_PARTIAL_FLOATS * 4 + (PAIR ? 16 : 0)];
+template <bool FOLD>
+__global__ __launch_bounds__(256, GRAM_OCC) void gram_kernel(const SegTable T, int tiles_per_wg, long long total,
+                                                             float *__restrict__ partials) {
+  // two key tiles and room for one parked partial Gram matrix
+  __shared__ __attribute__((aligned(16))) unsigned char smem[2 * TILE_BYTES + GRAM_PARTIAL_FLOATS * 4];
   // every wave passes the same workgroup barriers, each in its own copy of the loop
-  switch (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) & 3) {
-    case 0: gram_body<0, PAIR, FOLD>(T, tiles_per_wg, total, partials, smem); break;
-    case 1: gram_body<1, PAIR, FOLD>(T, tiles_per_wg, total, partials, smem); break;
-    case 2: gram_body<2, PAIR, FOLD>(T, tiles_per_wg, total, partials, smem); break;
-    default: gram_body<3, PAIR, FOLD>(T, tiles_per_wg, total, partials, smem); break;
+  switch (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) {
+    case 0: gram_body<0, FOLD>(T, tiles_per_wg, total, partials, smem); break;
+    case 1: gram_body<1, FOLD>(T, tiles_per_wg, total, partials, smem); break;
+    case 2: gram_body<2, FOLD>(T, tiles_per_wg, total, partials, smem); break;
+    default: gram_body<3, FOLD>(T, tiles_per_wg, total, partials, smem); break;
   }
 }
 
-hipError_t launch_gram(const SegTable &T, int nwg, int tiles_per_wg, GramKind kind, float *partials,
-                       hipStream_t st) {
+hipError_t launch_gram(const SegTable &T, int nwg, int tiles_per_wg, bool fold, float *partials, hipStream_t st) {
   const long long total = total_tiles(T);
   if (total <= 0 || nwg <= 0) return hipSuccess;
-  const auto kernel = kind == GRAM_PLAIN  ? gram_kernel<false, false>
-                      : kind == GRAM_PAIR ? gram_kernel<true, false>
-                                          : gram_kernel<true, true>;
-  hipLaunchKernelGGL(kernel, dim3((unsigned)nwg), dim3(kind == GRAM_PLAIN ? 256 : 512), 0, st, T, tiles_per_wg, total,
-                     partials);
+  hipLaunchKernelGGL(fold ? gram_kernel<true> : gram_kernel<false>, dim3((unsigned)nwg), dim3(256), 0, st, T, tiles_per_wg,
+                     total, partials);
   return hipGetLastError();
 }
 
