@@ -201,6 +201,8 @@ GroupBytes group_bytes_needed(const compactor_params_t *p, const SegTable &T, bo
   // and in exact mode 41.8/45.8 at 64 heads of 4096, 42.5/43.4 at 96, 42.9/41.2 at 128; k_s = 48, one head
   // of n = 131072, which brings 64 partials: 27 against 210.  At 2048 heads and more k_s = 32 and 48 would
   // be 4 to 9 % of this stage faster with shares, for 60 KB of scratch a head: the stage is 2 % of such calls.
+  // (Figures of sketched mode from before sketch_direct_kernel, which takes most calls of more than 128 heads now; their
+  // room stays, since it is the lengths of a call that decide.)
   const int most_heads = ks > 0 ? cus : 3 * cus / 8;
   g.shares = T.nheads <= most_heads ? align_up(solve_plan(T, ks, gp.tiles_per_wg).share_bytes) : 0;
   g.wt = align_up((size_t)T.nheads * W_TERMS * m * D * sizeof(uint16_t));
@@ -341,7 +343,7 @@ int enqueue_score(const compactor_params_t *p, const SegTable &T, const GroupByt
       gb.shares > 0 && ws_bytes >= gb.wanted() ? reinterpret_cast<double *>(ws + gb.off_shares()) : nullptr;
   const int score_tokens = score_tokens_for(p, T, cus);
   const SolvePlan plan = solve_plan(T, p->sketch_dim, rpw);
-  const bool in_score = shares != nullptr && score_solves(T, p->sketch_dim, score_tokens, cus);
+  const bool in_score = shares != nullptr && !plan.direct && score_solves(T, p->sketch_dim, score_tokens, cus);
   if (p->sketch_dim > 0) {
     HIP_TRY(launch_sketch_solve(T, p->sketch_dim, rpw, plan, partials, shares, p->phi, p->ridge_rel,
                                 in_score ? nullptr : wt, status, zero, zero_ints, st));

@@ -369,6 +369,7 @@ hipError_t launch_gram(const SegTable &T, int nwg, int tiles_per_wg, bool fold, 
 // launch more), or null: one workgroup per head does it (the same bits).
 // wt null: the shares only, with the status words set to 0 (see launch_score).
 struct SolvePlan {
+  bool direct;           // sketched mode, many heads: without shares, whatever the room (wt is not null)
   int parts;             // the partials of a head are added in this many runs (sketched mode)
   int nshares;           // shares of a head (sketched mode)
   size_t share_bytes;

@@ -42,7 +42,7 @@ __device__ __forceinline__ Where locate_head(const SegTable &T, int lhead) {
 // blocks halved, gives S = B + B^T.  The shares of a head are added in their order, whoever
 // computes them: with room in the workspace they are computed by workgroups of their own
 // (sketch_share_kernel) and added by the factorisation, otherwise one workgroup per head computes
-// them one after the other.  Both give the same bits.
+// them one after the other.  Both give the same bits.  Many heads go another way whatever the room (sketch_direct_kernel).
 // The stored upper block number b is block (I, J) of G.
 __device__ __forceinline__ void upper_block_pos(int b, int &I, int &J) {
   I = (b >= 4) + (b >= 7) + (b >= 9);
@@ -166,7 +166,7 @@ __device__ __forceinline__ void split_part(int nsplit, int parts, int r, int &fi
 // One workgroup per (head, part, share).  Bound by latency: one batch of partials after the
 // other, 60 MFMAs (k_s = 48) a wave, two barriers: 7 to 10 us for 8 heads with 8 to 64 partials
 // each, where one workgroup per head took 34 (8 partials, 4-byte loads) to 185 us (64) for this
-// step.  From 256 heads on (24 us) the fp64 matrix cores count: 1200 MFMAs of 64 clocks a head.
+// step.  At 256 heads (24 us) the fp64 matrix cores count, 1200 MFMAs of 64 clocks a head: see sketch_direct_kernel.
 template <int M>
 __global__ __launch_bounds__(256, 2) void sketch_share_kernel(
     const SegTable T, int tiles_per_wg, int parts, const float *__restrict__ partials,
@@ -251,6 +251,141 @@ __global__ __launch_bounds__(256, 2) void sketch_solve_kernel(
   if (tid == 0) {
     const Where w = locate_head(T, lhead);
     status[T.s[w.seg].ghead0 + w.head] = F.flag;
+  }
+}
+
+// Many heads (solve_plan): one workgroup per head takes step 1 too, each of its waves half of the columns of two of the four
+// column blocks J of G (0 and 3, or 1 and 2: five stored blocks either way).  A wave sums its blocks over the partials in
+// registers, as in sketch_share, and goes on with all of a column block: T_J = sum over I of G_IJ^T Phi_I in one chain, and one
+// Phi_J^T T_J for it, 192 products (k_s = 48) a wave where the shares, block by block, take 300, and nothing of S passes through
+// memory.  Bound by the fp64 matrix cores (192 x 64 clocks, 5 us) and by the chain of pivots: 2048 heads of 500 tokens, k_s = 48,
+// whole scores 293 -> 231 us, 256 heads of 2048 78.9 -> 69.8.
+template <int M, int FIRST, int SECOND>
+__device__ __forceinline__ void sketch_columns(const double (&g)[5][8], const float *PH, int half, f64x4 (&sacc)[M / 16][M / 16]) {
+  constexpr int CT = M / 16, PP = SketchFactor<M>::PP;
+  const int lane = threadIdx.x & 63, l16 = lane & 15, lq = lane >> 4;
+#pragma unroll
+  for (int at = 0; at < CT; ++at)
+#pragma unroll
+    for (int bt = 0; bt < CT; ++bt) sacc[at][bt] = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int part = 0; part < 2; ++part) {
+    const int J = part ? SECOND : FIRST, b0 = part ? FIRST + 1 : 0;
+    f64x4 tacc[CT];
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) tacc[ct] = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int I = 0; I <= J; ++I)
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const double a = I == J ? 0.5 * g[b0 + I][q] : g[b0 + I][q];
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct)
+          tacc[ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(
+              a, (double)PH[(32 * I + 16 * (q >> 2) + 4 * lq + (q & 3)) * PP + 16 * ct + l16], tacc[ct], 0, 0, 0);
+      }
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+#pragma unroll
+      for (int at = 0; at < CT; ++at) {
+        const double a = (double)PH[(32 * J + 16 * half + 4 * v + lq) * PP + 16 * at + l16];
+#pragma unroll
+        for (int bt = 0; bt < CT; ++bt)
+          sacc[at][bt] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, tacc[bt][v], sacc[at][bt], 0, 0, 0);
+      }
+  }
+}
+
+// (At M = 64 the accumulators of S take 128 registers, so one workgroup on a unit.)
+template <int M>
+__global__ __launch_bounds__(256, M > 48 ? 1 : 2) void sketch_direct_kernel(
+    const SegTable T, int tiles_per_wg, const float *__restrict__ partials, const float *__restrict__ phi, float ridge_rel,
+    uint16_t *__restrict__ wt, int32_t *__restrict__ status, int *__restrict__ zero, long long zero_ints) {
+  constexpr int CT = M / 16, SP = M + 1, PP = SketchFactor<M>::PP, FLIGHT = 2;
+  struct Sketch {
+    double halves[2][M * SP];
+    float PH[D * PP];
+  };
+  union Lds {
+    SketchFactor<M> f;
+    Sketch s;
+  };
+  __shared__ __attribute__((aligned(16))) Lds lds;
+  const int lhead = blockIdx.x, tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lq = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), half = wave & 1;
+  const bool inner = wave >= 2;          // columns of blocks 1 and 2, the others of 0 and 3
+
+  PhiRegs<M> ph;
+  ph.fetch(phi);
+  int nsplit;
+  const long long pb = partial_base(T, lhead, tiles_per_wg, nsplit);
+  const float *p = partials + pb * GRAM_PARTIAL_FLOATS + (32 * lq + 16 * half + l16) * 4;
+  double g[5][8];
+#pragma unroll
+  for (int b = 0; b < 5; ++b)
+#pragma unroll
+    for (int q = 0; q < 8; ++q) g[b][q] = 0.0;
+  for (int sp = 0; sp < nsplit; sp += FLIGHT) {
+    float4 a[FLIGHT][5], c[FLIGHT][5];
+#pragma unroll
+    for (int u = 0; u < FLIGHT; ++u) {
+      const float *pu = p + (long long)min(sp + u, nsplit - 1) * GRAM_PARTIAL_FLOATS;
+#pragma unroll
+      for (int b = 0; b < 5; ++b) {      // stored blocks (0,0) (0,3) (1,3) (2,3) (3,3), or (0,1) (1,1) (0,2) (1,2) (2,2)
+        constexpr int outer_at[5] = {0, 3, 6, 8, 9}, inner_at[5] = {1, 4, 2, 5, 7};
+        const float *pb4 = pu + 1024 * (inner ? inner_at[b] : outer_at[b]);
+        a[u][b] = *reinterpret_cast<const float4 *>(pb4);
+        c[u][b] = *reinterpret_cast<const float4 *>(pb4 + 512);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < FLIGHT; ++u)
+      if (sp + u < nsplit) {             // uniform
+#pragma unroll
+        for (int b = 0; b < 5; ++b) {
+          g[b][0] += a[u][b].x; g[b][1] += a[u][b].y; g[b][2] += a[u][b].z; g[b][3] += a[u][b].w;
+          g[b][4] += c[u][b].x; g[b][5] += c[u][b].y; g[b][6] += c[u][b].z; g[b][7] += c[u][b].w;
+        }
+      }
+  }
+#pragma unroll
+  for (int i = 0; i < PhiRegs<M>::N; ++i) {
+    const int c4 = tid + 256 * i;
+    *reinterpret_cast<typename PhiRegs<M>::quad *>(&lds.s.PH[c4 / (M / 4) * PP + c4 % (M / 4) * 4]) = ph.v[i];
+  }
+  __syncthreads();
+  f64x4 sacc[CT][CT];
+  if (inner) sketch_columns<M, 1, 2>(g, lds.s.PH, half, sacc);
+  else sketch_columns<M, 0, 3>(g, lds.s.PH, half, sacc);
+  zero_slice(zero, zero_ints);   // histograms that the score and selection kernels add into
+  double *dst = lds.s.halves[half];
+  auto each = [&](auto &&f) {
+#pragma unroll
+    for (int at = 0; at < CT; ++at)
+#pragma unroll
+      for (int bt = 0; bt < CT; ++bt)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) f(dst[(16 * at + 4 * v + lq) * SP + 16 * bt + l16], sacc[at][bt][v]);
+  };
+  if (inner) each([](double &d, double x) { d = x; });
+  __syncthreads();
+  if (!inner) each([](double &d, double x) { d += x; });
+  __syncthreads();
+  double sum[Share<M>::TILES];
+  {
+    const double *ba = lds.s.halves[0], *bb = lds.s.halves[1];
+    for_lower_tiles<M>([&](int t, int i, int j) {
+      sum[t] = (ba[i * SP + j] + bb[i * SP + j]) + (ba[j * SP + i] + bb[j * SP + i]);
+    });
+  }
+  __syncthreads();
+  uint16_t *wh = wt + (size_t)lhead * (W_TERMS * M * D);
+  sketch_factor<M>(lds.f, sum, ph, ridge_rel, [&](int tt, int row, int ch, uint16_t v) { wh[(tt * M + row) * D + ch] = v; },
+                   [](auto) {});
+  __syncthreads();
+  if (tid == 0) {
+    const Where w = locate_head(T, lhead);
+    status[T.s[w.seg].ghead0 + w.head] = lds.f.flag;
   }
 }
 
@@ -387,10 +522,24 @@ __global__ __launch_bounds__(EXACT_THREADS) void exact_solve_kernel(
 // a batch of eight is in flight at a time, about 1 us each.
 constexpr int SHARE_SPLITS = 64, SHARE_PARTS_MAX = 8;
 
+// Above DIRECT_HEADS heads, none of them with more than k_s - 4 partials, sketch_direct_kernel forms and factors S.  Scores
+// alone on MI355X, us with shares (or, above a head a unit, with the shares of a head one after the other) / direct:
+//   heads x n  112x2048   128x2048   128x8192    160x2048   256x2048  304x2048   1024x1000  2048x500
+//   k_s = 16   39.4/42.6  40.2/41.6  96.4/98.5   53.0/52.4  60.4/56   81.0/79.3  132/130    164/158
+//   k_s = 32   45.0/47.7  45.5/47.5  103/104     58.9/57.1     -      93.5/86.7  153/141    210/188
+//   k_s = 48   52.7/53.5  53.9/54.0  112/111     68.9/63.0  78.9/69.8 112/97.3   197/165    293/231
+//   k_s = 64   66.9/63.1  68.1/63.9  132/126     82.2/72.8  101/83    134/120    246/217    376/322
+// up to 128 heads the score workgroups factor short heads themselves, and one head among many that is much longer waits for
+// its one workgroup: 192 heads, 8 of them longer, with (partials of a head) k_s = 16 59.2/58.8 (9), 109/106 (7), 114/112 (11),
+// 62.3/68.2 (17), 112/124 (17), 103/121 (47); k_s = 48 77.3/73.3 (17), 82.6/80.9 (33), 91.3/91.7 (47), 125/130 (17), 169/170 (59);
+// k_s = 64 106/101 (47), 183/179 (59).  128 heads, 8 of them longer, k_s = 16 44.7/55.9 (17), k_s = 48 49.8/59.6 (17).
+constexpr int DIRECT_HEADS = 128;
+
 SolvePlan solve_plan(const SegTable &T, int ks, int tiles_per_wg) {
   SolvePlan p;
   p.parts = 1;
   p.nshares = 0;
+  p.direct = false;
   if (ks == 0) {
     p.share_bytes = (size_t)T.nheads * 10 * 1024 * sizeof(double);
     return p;
@@ -400,6 +549,7 @@ SolvePlan solve_plan(const SegTable &T, int ks, int tiles_per_wg) {
     const int splits = (tiles_of(T.s[i].n) + tiles_per_wg - 1) / tiles_per_wg + 1;
     if (splits > most) most = splits;
   }
+  p.direct = T.nheads > DIRECT_HEADS && most <= ks - 4;
   p.parts = (most + SHARE_SPLITS - 1) / SHARE_SPLITS;
   if (p.parts > SHARE_PARTS_MAX) p.parts = SHARE_PARTS_MAX;
   const int P = ks / 16;
@@ -413,7 +563,10 @@ static hipError_t launch_sketched(const SegTable &T, int tiles_per_wg, const Sol
                                   const float *partials, double *shares, const float *phi,
                                   float ridge_rel, uint16_t *wt, int32_t *status, int *zero,
                                   long long zero_ints, hipStream_t st) {
-  if (shares != nullptr) {
+  if (plan.direct) {
+    hipLaunchKernelGGL((sketch_direct_kernel<M>), dim3((unsigned)T.nheads), dim3(256), 0, st, T, tiles_per_wg, partials, phi,
+                       ridge_rel, wt, status, zero, zero_ints);
+  } else if (shares != nullptr) {
     hipLaunchKernelGGL((sketch_share_kernel<M>), dim3((unsigned)(T.nheads * plan.parts * SHARE_BLOCKS)),
                        dim3(256), 0, st, T, tiles_per_wg, plan.parts, partials, phi, shares,
                        wt == nullptr ? status : nullptr, zero, zero_ints);
@@ -434,7 +587,7 @@ hipError_t launch_sketch_solve(const SegTable &T, int ks, int tiles_per_wg, cons
                                float ridge_rel, uint16_t *wt, int32_t *status, int *zero,
                                long long zero_ints, hipStream_t st) {
   if (T.nheads <= 0) return hipSuccess;
-  if (shares == nullptr && wt == nullptr) return hipErrorInvalidValue;
+  if ((shares == nullptr || plan.direct) && wt == nullptr) return hipErrorInvalidValue;
   switch (ks) {
     case 16: return launch_sketched<16>(T, tiles_per_wg, plan, partials, shares, phi, ridge_rel, wt, status, zero, zero_ints, st);
     case 32: return launch_sketched<32>(T, tiles_per_wg, plan, partials, shares, phi, ridge_rel, wt, status, zero, zero_ints, st);

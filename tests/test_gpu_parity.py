@@ -575,6 +575,18 @@ def test_sketched_scores_at_the_edges_of_steps(C, ks, n, L):
     _say("  k_s = %d, %d heads of %d: max rel err %.3g" % (ks, L, n, stats["max_rel"]))
 
 
+# Above 128 heads one workgroup forms and factors S of a head, unless one may have more than k_s - 4 partials (a tile of 64 rows
+# to each Gram workgroup and one more): one to three partials, a step to either side of 12, 25, 41 and 53
+@pytest.mark.parametrize("ks,L,n,gram_wgs", [(16, 128, 700, 0), (16, 129, 700, 0), (32, 130, 64, 0), (48, 131, 2047, 0), (64, 129, 513, 0),
+                                             (48, 257, 65, 0), (16, 129, 760, 100000), (16, 129, 700, 100000), (32, 129, 1500, 100000),
+                                             (48, 129, 2500, 100000), (64, 129, 3300, 100000)])
+def test_sketches_of_many_heads(C, ks, L, n, gram_wgs):
+    w = W.config1(DEV, L=L, H=1, n=n)
+    w.sketch_dim = ks
+    stats, _ = U.run_and_check(C, w, DEV, heads=[(0, 0, 0), (0, L // 2, 0), (0, L - 1, 0)], tune={"gram_wgs": gram_wgs})
+    _say("  k_s = %d, %d heads of %d: max rel err %.3g" % (ks, L, n, stats["max_rel"]))
+
+
 def test_config2_small(C):
     _say("config 2 shape, 2 layers x 8 heads, n=6000")
     st, _ = U.run_and_check(C, W.config2(device=DEV, L=2, H=8, n=6000), DEV)
