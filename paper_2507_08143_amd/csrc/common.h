@@ -292,6 +292,11 @@ __device__ __forceinline__ void cursor_head(const SegTable &T, TileCursor &c) {
   c.kp = head_ptr(s.k_score, s, s.head_begin + c.hh);
 }
 
+// a / b; of 64 bits, which takes some 130 instructions of latency before a kernel's first load, only where it has to be.
+__device__ __forceinline__ long long quotient(long long a, int b) {
+  return (unsigned long long)a >> 32 ? a / b : (long long)((unsigned)a / (unsigned)b);     // uniform
+}
+
 template <int TILE>
 __device__ __forceinline__ void cursor_seek(const SegTable &T, long long g, TileCursor &c) {
   long long base = 0;
@@ -302,7 +307,7 @@ __device__ __forceinline__ void cursor_seek(const SegTable &T, long long g, Tile
     if (g < base + cnt || i == T.nseg - 1) {
       const long long local = g - base;
       c.seg = i;
-      c.hh = (int)(local / tph);
+      c.hh = (int)quotient(local, tph);
       c.tile = (int)(local - (long long)c.hh * tph);
       break;
     }
@@ -345,7 +350,7 @@ __device__ __forceinline__ long long partial_base(const SegTable &T, int lhead, 
     const int hh = lhead - T.s[i].lhead0;
     if (hh < T.s[i].head_count || i == T.nseg - 1) {
       const long long t0 = base + (long long)hh * tph;        // first tile of the head
-      const long long first = t0 / tiles_per_wg, last = (t0 + tph - 1) / tiles_per_wg;
+      const long long first = quotient(t0, tiles_per_wg), last = quotient(t0 + tph - 1, tiles_per_wg);
       nsplit = (int)(last - first + 1);
       return first + lhead;
     }

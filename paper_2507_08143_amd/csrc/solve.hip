@@ -49,6 +49,66 @@ __device__ __forceinline__ void upper_block_pos(int b, int &I, int &J) {
   J = b - upper_block(I, I) + I;
 }
 
+// The fp64 sum, in their order, of Q float4, 512 floats apart, over `count` partials.  A batch costs a round trip of about
+// 1 us, so the next batch leaves before one is added, and no load stands under a condition: each of those would be waited
+// for by itself (a batch repeats the last partial instead, and does not add it; one or two left over go by themselves).  Whole
+// scores on MI355X, us, k_s = 48, 8 heads of 3000 / 10000, 64 of 7000: 28.3 -> 27.4, 35.6 -> 34.2, 66.9 -> 65.4; exact mode, where
+// one load waited for the other, 8 heads of 3000 / 10000: 46.0 -> 44.6, 54.5 -> 49.7.
+template <int Q, int FLIGHT = 8>
+__device__ __forceinline__ void sum_quads(const float *__restrict__ src, int count, double (&g)[4 * Q]) {
+  constexpr int FEW = FLIGHT >= 8 ? 2 : 1;
+  typedef float4 Batch[FLIGHT][Q];
+  auto load = [&](int s0, Batch &v, auto n) {
+#pragma unroll
+    for (int u = 0; u < decltype(n)::value; ++u)
+#pragma unroll
+      for (int q = 0; q < Q; ++q)
+        v[u][q] = *reinterpret_cast<const float4 *>(src + (long long)min(s0 + u, count - 1) * GRAM_PARTIAL_FLOATS + 512 * q);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto add = [&](int u, const Batch &v) {
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      g[4 * q] += v[u][q].x; g[4 * q + 1] += v[u][q].y; g[4 * q + 2] += v[u][q].z; g[4 * q + 3] += v[u][q].w;
+    }
+  };
+  auto add_all = [&](const Batch &v) {
+#pragma unroll
+    for (int u = 0; u < FLIGHT; ++u) add(u, v);
+  };
+  auto add_some = [&](int n, const Batch &v) {
+#pragma unroll
+    for (int u = 0; u < FLIGHT; ++u)
+      if (u < n) add(u, v);                // uniform
+  };
+  const std::integral_constant<int, FLIGHT> all;
+#pragma unroll
+  for (int i = 0; i < 4 * Q; ++i) g[i] = 0.0;
+  if (count <= 0) return;                  // uniform
+  Batch a, b;
+  load(0, a, all);
+  int sp = 0;
+  for (; sp + 2 * FLIGHT < count; sp += 2 * FLIGHT) {
+    load(sp + FLIGHT, b, all);
+    add_all(a);
+    load(sp + 2 * FLIGHT, a, all);
+    add_all(b);
+  }
+  const int left = count - sp - FLIGHT;
+  if (left > FEW) {
+    load(sp + FLIGHT, b, all);
+    add_all(a);
+    add_some(left, b);
+  } else if (left > 0) {
+    load(sp + FLIGHT, b, std::integral_constant<int, FEW>{});
+    add_all(a);
+    add(0, b);
+    if (FEW > 1 && left > 1) add(FEW - 1, b);
+  } else {
+    add_some(count - sp, a);
+  }
+}
+
 // Share w of the partials src[0 .. count): B of it, in two halves, is left in ba and bb (M rows of
 // pitch M + 1; the share is ba + bb), complete after a barrier.  A wave takes 16 columns of a
 // block: lane (l16, lq) reads rows 4lq .. 4lq + 3 and 16 + 4lq .. of column l16 with two 16-byte
@@ -58,7 +118,7 @@ __device__ __forceinline__ void upper_block_pos(int b, int &I, int &J) {
 template <int M>
 __device__ __forceinline__ void sketch_share(const float *__restrict__ src, int count, int w,
                                              const float *__restrict__ phi, double *ba, double *bb) {
-  constexpr int CT = M / 16, SP = M + 1, FLIGHT = 8;
+  constexpr int CT = M / 16, SP = M + 1;
   const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lq = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int b = 2 * w + (wave >> 1), half = wave & 1;
@@ -78,41 +138,7 @@ __device__ __forceinline__ void sketch_share(const float *__restrict__ src, int 
     for (int ct = 0; ct < CT; ++ct)
       pj[v][ct] = phi[(32 * J + 16 * half + 4 * v + lq) * M + 16 * ct + l16];
   double g[8];
-#pragma unroll
-  for (int q = 0; q < 8; ++q) g[q] = 0.0;
-  int sp = 0;
-  for (; sp + FLIGHT <= count; sp += FLIGHT) {
-    float4 a[FLIGHT], c[FLIGHT];
-#pragma unroll
-    for (int u = 0; u < FLIGHT; ++u) {
-      const float *pu = p + (long long)(sp + u) * GRAM_PARTIAL_FLOATS;
-      a[u] = *reinterpret_cast<const float4 *>(pu);
-      c[u] = *reinterpret_cast<const float4 *>(pu + 512);
-    }
-#pragma unroll
-    for (int u = 0; u < FLIGHT; ++u) {
-      g[0] += a[u].x; g[1] += a[u].y; g[2] += a[u].z; g[3] += a[u].w;
-      g[4] += c[u].x; g[5] += c[u].y; g[6] += c[u].z; g[7] += c[u].w;
-    }
-  }
-  if (sp < count) {
-    float4 a[FLIGHT - 1], c[FLIGHT - 1];
-#pragma unroll
-    for (int u = 0; u < FLIGHT - 1; ++u) {
-      const bool have = sp + u < count;              // uniform
-      const float *pu = p + (long long)(sp + (have ? u : 0)) * GRAM_PARTIAL_FLOATS;
-      a[u] = c[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (have) {
-        a[u] = *reinterpret_cast<const float4 *>(pu);
-        c[u] = *reinterpret_cast<const float4 *>(pu + 512);
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < FLIGHT - 1; ++u) {
-      g[0] += a[u].x; g[1] += a[u].y; g[2] += a[u].z; g[3] += a[u].w;
-      g[4] += c[u].x; g[5] += c[u].y; g[6] += c[u].z; g[7] += c[u].w;
-    }
-  }
+  sum_quads<2>(p, count, g);
   f64x4 tacc[CT];
 #pragma unroll
   for (int ct = 0; ct < CT; ++ct) tacc[ct] = f64x4{0.0, 0.0, 0.0, 0.0};
@@ -395,23 +421,6 @@ __global__ __launch_bounds__(256, M > 48 ? 1 : 2) void sketch_direct_kernel(
 // where the workspace has room, with the same bits.
 constexpr int EXACT_THREADS = 512;
 
-// The fp64 sum, in their order, of a thread's float4 of a block over `count` partials.
-__device__ __forceinline__ void sum_quads(const float *__restrict__ src, int count, double (&g)[4]) {
-  constexpr int FLIGHT = 8;
-  g[0] = g[1] = g[2] = g[3] = 0.0;
-  for (int s0 = 0; s0 < count; s0 += FLIGHT) {
-    float4 v[FLIGHT];
-#pragma unroll
-    for (int u = 0; u < FLIGHT; ++u) {
-      v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (s0 + u < count)                                       // uniform
-        v[u] = *reinterpret_cast<const float4 *>(src + (long long)(s0 + u) * GRAM_PARTIAL_FLOATS);
-    }
-#pragma unroll
-    for (int u = 0; u < FLIGHT; ++u) { g[0] += v[u].x; g[1] += v[u].y; g[2] += v[u].z; g[3] += v[u].w; }
-  }
-}
-
 __global__ __launch_bounds__(256) void gram_sum_kernel(const SegTable T, int tiles_per_wg,
                                                        const float *__restrict__ partials,
                                                        double *__restrict__ sums, int *__restrict__ zero,
@@ -420,7 +429,7 @@ __global__ __launch_bounds__(256) void gram_sum_kernel(const SegTable T, int til
   int nsplit;
   const long long pb = partial_base(T, lhead, tiles_per_wg, nsplit);
   double g[4];
-  sum_quads(partials + pb * GRAM_PARTIAL_FLOATS + b * 1024 + threadIdx.x * 4, nsplit, g);
+  sum_quads<1>(partials + pb * GRAM_PARTIAL_FLOATS + b * 1024 + threadIdx.x * 4, nsplit, g);
   zero_slice(zero, zero_ints);   // histograms that the score and selection kernels add into
   double *out = sums + (long long)blockIdx.x * 1024 + threadIdx.x * 4;
 #pragma unroll
@@ -458,7 +467,7 @@ __global__ __launch_bounds__(EXACT_THREADS) void exact_solve_kernel(
     const long long pb = partial_base(T, lhead, tiles_per_wg, nsplit);
     const float *src = partials + pb * GRAM_PARTIAL_FLOATS + half * 1024 + f * 4;
 #pragma unroll
-    for (int i = 0; i < 5; ++i) sum_quads(src + i * 2048, nsplit, g[i]);
+    for (int i = 0; i < 5; ++i) sum_quads<1, 2>(src + i * 2048, nsplit, g[i]);      // heads of a partial or two
     zero_slice(zero, zero_ints);   // histograms that the score and selection kernels add into
   }
   // into the lower triangle: block (I, J), I < J, holds G[32I + r][32J + c] = G[32J + c][32I + r]
