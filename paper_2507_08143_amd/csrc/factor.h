@@ -157,8 +157,8 @@ __device__ __forceinline__ Quad quad_at(const double *p) {
 // The serial chain is wave 0's: the diagonal block takes its last update and is eliminated.  In
 // its shadow the other waves apply what the previous panel owes the trailing matrix and X (Y_qc =
 // sum over r of L_qr X_rc grows in the place of X_qc) and hand on finished rows of X: row_done(p,
-// i, n) is called by n waves, i = 0 .. n - 1, when block row p of X is complete.  With three panels
-// that takes 1.2 us off the 13.8 us of one head, with eight (exact mode) 22 us off 52.
+// i, n) is called by n waves, i = 0 .. n - 1, when block row p of X is complete.  In eight panels
+// (exact mode) the work in the shadow is 22 of 52 us when it is not there (on the slower pivots of an earlier chol16_inverse).
 // !INVERSE: X is not wanted, only L and the diagonal blocks of X; waves 1 .. NW - 1 call row_done(p) (a compile-time
 // p) when X_pp and the blocks of L below it are complete.
 template <int P, int NW, bool INVERSE, class F>
