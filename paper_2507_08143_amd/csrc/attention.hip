@@ -348,11 +348,17 @@ __global__ __launch_bounds__(256, 2) void attn_colsum_kernel(const AttnTable T,
 // part are floats as they are, and a wide window is bound by its LDS reads: 32 layers of 8 x 32768 tokens
 // with one query head, pool = 1 / 7 / 31 / 63, 1073 / 1077 / 1091 / 1114 us with doubles, 1071 / 1074 /
 // 1086 / 1100 with floats (all in fp32, less exact: 1068 / 1073 / 1079 / 1086).
+// Bound by latency: all loads leave at once, at clamped positions and parts, where a position after the other and a part after
+// the other cost a round trip each, and a thread's four windows are added side by side.  Whole call of 4 query heads a
+// kv head on MI355X, us: one head of 1024 20.0 -> 15.4, 8 of 2048 22.0 -> 16.5, 4096 25.8 -> 22.7, 16384 52.1 -> 50.5; pool = 63, 8 of 4096
+// 27.6 -> 24.3; the four calls above 1051 / 1044 / 1056 / 1070 -> 1048 / 1038 / 1050 / 1069.
+constexpr int ATT_MAX_PARTS = 4;       // see query_parts
 template <bool PARTS>
 __global__ __launch_bounds__(256) void attn_pool_kernel(const AttnTable T,
                                                         const float *__restrict__ raw,
                                                         float *__restrict__ attn) {
   constexpr int SPAN = 1024, HALO = 32;           // pool <= 63: at most 31 positions each side
+  constexpr int LOADS = (SPAN + 2 * HALO + 255) / 256, MOST = PARTS ? ATT_MAX_PARTS : 1;
   typedef typename std::conditional<PARTS, double, float>::type sum_t;
   __shared__ sum_t tile[SPAN + 2 * HALO];
   int seg = 0, head = 0, blk = 0;
@@ -376,22 +382,33 @@ __global__ __launch_bounds__(256) void attn_pool_kernel(const AttnTable T,
   const float *src = raw + s.out_off + (long long)head * n;
   float *dst = attn + s.out_off + (long long)head * n;
   const int t0 = blk * SPAN;
-  for (int i = threadIdx.x; i < SPAN + 2 * HALO; i += 256) {
-    const int j = t0 - HALO + i;
-    sum_t x = 0;                                  // zero padding at both ends of the sequence
-    if (j >= 0 && j < n) {
-      x = src[j];
-      if (PARTS)
-        for (int p = 1; p < T.parts; ++p) x += (sum_t)src[p * T.part_floats + j];
-    }
-    tile[i] = x;
+  float v[LOADS][MOST];
+#pragma unroll
+  for (int r = 0; r < LOADS; ++r) {
+    const int j = min(max(t0 - HALO + r * 256 + (int)threadIdx.x, 0), n - 1);
+#pragma unroll
+    for (int p = 0; p < MOST; ++p) v[r][p] = src[(PARTS ? min(p, T.parts - 1) * T.part_floats : 0) + j];
+  }
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int r = 0; r < LOADS; ++r) {
+    const int i = r * 256 + threadIdx.x, j = t0 - HALO + i;
+    sum_t x = v[r][0];
+#pragma unroll
+    for (int p = 1; p < MOST; ++p)
+      if (p < T.parts) x += (sum_t)v[r][p];       // uniform
+    if (i < SPAN + 2 * HALO) tile[i] = j >= 0 && j < n ? x : (sum_t)0;      // zero padding at both ends of the sequence
   }
   __syncthreads();
   const double inv = 1.0 / (double)T.pool;
-  for (int i = threadIdx.x; i < SPAN && t0 + i < n; i += 256) {
-    double acc = 0.0;
-    for (int u = -h; u <= h; ++u) acc += (double)tile[HALO + i + u];
-    dst[t0 + i] = (float)(acc * inv);
+  double acc[SPAN / 256] = {};
+  for (int u = -h; u <= h; ++u)
+#pragma unroll
+    for (int r = 0; r < SPAN / 256; ++r) acc[r] += (double)tile[HALO + r * 256 + (int)threadIdx.x + u];
+#pragma unroll
+  for (int r = 0; r < SPAN / 256; ++r) {
+    const int j = t0 + r * 256 + threadIdx.x;
+    if (j < n) dst[j] = (float)(acc[r] * inv);
   }
 }
 
@@ -402,8 +419,7 @@ __global__ __launch_bounds__(256) void attn_pool_kernel(const AttnTable T,
 // MI355X, us with 1 / 2 / 3 / 4 / 5 parts: 4 blocks 32.4 / 23.5 / 22.1 / 20.4 / 21.2, 64 blocks
 // 33.4 / 24.0 / 23.2 / 21.8 / 27.7, 128 blocks 36.5 / 27.6 / 31.8 / 32.4 / 35.4, 200 blocks
 // 34.5 / 34.6 / 40.0 / 41.5, 512 blocks 56.4 / 61.6 / 66.8 / 70.1 (of which the host
-// alone needed 18 then; 12 now).
-constexpr int ATT_MAX_PARTS = 4;
+// alone needed 18 then; 12 now).  All of them from when the pooling took 3 to 6 us longer with parts than it does now.
 static int query_parts(const compactor_attn_params_t *p, const compactor_attn_request_t *reqs, int32_t nreq) {
   long long blocks = 0;
   for (int b = 0; b < nreq; ++b)

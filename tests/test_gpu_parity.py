@@ -1094,6 +1094,21 @@ def test_attention_scores_in_parts(C, L, H, G, n):
         assert np.all(np.abs(b - a) <= tol * np.abs(a)), (parts, float(np.max(np.abs(b - a) / np.abs(a))))
 
 
+# A pooling workgroup takes 1024 positions and 32 to either side, read at clamped positions and parts: a step to either side of
+# its ends, the widest window and none; the sums of one part and of several
+@pytest.mark.parametrize("n", [31, 1023, 1024, 1025, 1056, 2049])
+@pytest.mark.parametrize("pool", [1, 63])
+def test_attention_pooling_at_the_edges_of_workgroups(C, n, pool):
+    _, w, q, a = _attention_case(C, 1, 2, 1, n, W.config1, pool=pool, seed=n)
+    ap, reqs = C.AttnParams(1, 2, 2, pool=pool), [C.AttnRequest(q, w.requests[0].k)]
+    tol = 2.0 * (8 + 5 + 4 + pool + 2) * 2.0 ** -24             # as in test_attention_scores_in_parts
+    for parts in (1, 3):
+        ws = torch.full((max(256, -(-2 * n * 4 * parts // 256) * 256),), 0xff, dtype=torch.uint8, device=DEV)   # NaN
+        b = C.compactor_attention_scores(ap, reqs, workspace=ws)
+        torch.cuda.synchronize()
+        assert np.all(np.abs(b.view(1, 2, n).cpu().numpy() - a) <= tol * np.abs(a)), parts
+
+
 def test_attention_scores_with_every_cu_busy(C):
     _say("attention scores: 2 layers x 8 kv heads x 4 query heads, n=16384 (1024 workgroups, two per CU)")
     worst, _, _, _ = _attention_case(C, 2, 8, 4, 16384, W.config2)
