@@ -51,7 +51,9 @@ __device__ __forceinline__ void upper_block_pos(int b, int &I, int &J) {
 
 // The fp64 sum, in their order, of Q float4, 512 floats apart, over `count` partials.  A batch costs a round trip of about
 // 1 us, so the next batch leaves before one is added, and no load stands under a condition: each of those would be waited
-// for by itself (a batch repeats the last partial instead, and does not add it; one or two left over go by themselves).  Whole
+// for by itself (a batch repeats the last partial instead, and does not add it; one or two left over go by themselves).  With two
+// float4 a batch is four partials: with eight the share kernel has registers for two workgroups a unit instead of three, 128 heads of
+// 34660, k_s = 48, 393 us and not 390, and eight heads no less.  Whole
 // scores on MI355X, us, k_s = 48, 8 heads of 3000 / 10000, 64 of 7000: 28.3 -> 27.4, 35.6 -> 34.2, 66.9 -> 65.4; exact mode, where
 // one load waited for the other, 8 heads of 3000 / 10000: 46.0 -> 44.6, 54.5 -> 49.7.
 template <int Q, int FLIGHT = 8>
@@ -138,7 +140,7 @@ __device__ __forceinline__ void sketch_share(const float *__restrict__ src, int 
     for (int ct = 0; ct < CT; ++ct)
       pj[v][ct] = phi[(32 * J + 16 * half + 4 * v + lq) * M + 16 * ct + l16];
   double g[8];
-  sum_quads<2>(p, count, g);
+  sum_quads<2, 4>(p, count, g);
   f64x4 tacc[CT];
 #pragma unroll
   for (int ct = 0; ct < CT; ++ct) tacc[ct] = f64x4{0.0, 0.0, 0.0, 0.0};

@@ -504,9 +504,9 @@ def test_factorisation_with_and_without_shares(C, ks, n, gram_wgs):
     _say("  workspace %d of %d bytes; max rel err %.3g" % (hi, full, stats["max_rel"]))
 
 
-# The partials of a head are added in batches of eight (two where one workgroup of an exact head adds them itself, above 96
-# heads), two batches in turn, one or two left over by themselves; one tile of 64 rows a partial here
-@pytest.mark.parametrize("ks,L,partials", [(16, 1, p) for p in (1, 7, 8, 9, 10, 11, 16, 17, 18, 19, 24, 33)] +
+# The partials of a head are added in batches of four (exact mode: eight; two where one workgroup of an exact head adds them
+# itself, above 96 heads), two batches in turn, one or two left over by themselves; one tile of 64 rows a partial here
+@pytest.mark.parametrize("ks,L,partials", [(16, 1, p) for p in (1, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 16, 17, 18, 19, 24, 33)] +
                          [(0, 1, p) for p in (2, 8, 10, 11, 17, 25)] + [(0, 97, p) for p in (2, 3, 4, 5, 6, 7)])
 def test_sums_of_partials_at_the_edges_of_batches(C, ks, L, partials):
     w = W.config1(DEV, L=L, H=1, n=64 * partials)
