@@ -157,9 +157,11 @@ __device__ __forceinline__ void leave_hist(const SegTable &T, const Seg &s, cons
 // sub-tiles).  Key rows arrive with fully coalesced streaming loads (a wave instruction covers
 // four whole 256-byte rows), pass through a wave-private LDS buffer, and are read back in the
 // MFMA B-operand arrangement; a step of loads is in flight while the one before is multiplied.  With two the kernel
-// is 2 to 3 % slower where the memory is busy: 256 heads of 32768 tokens 343 us, 352 with two, 345 where both are waited for
-// together.  At 16 rows a step is over so soon that two pay: whole scores of 512 heads of 8192 353 -> 342 us, 128 heads of 32768
-// 351 -> 340, 256 of 32768 667 both, 512 of 4096 176 -> 180; at 32 rows 346 -> 353, at 48 362 -> 370 (512 of 8192).
+// is 1 to 3 % slower where the memory is busy: 256 heads of 32768 tokens, 48 rows, 343 us, 352 with two, 345 where both are waited
+// for together; 16 rows 326.6, 338.3 and 328.2, 512 of 8192 token by token 169.3, 180.9 and 173.3.
+// Two workgroups a unit, also at 16 rows, where registers and LDS (if not for ROOM) allow three: the third costs as much as
+// a second step in flight, 256 heads of 32768 326.6 -> 337.2, 192 of 34660 token by token 283.6 -> 290.6, 512 of 8192 169.3 ->
+// 180.4.
 // The multiply loop needs no workgroup barrier: a wave only reads what it wrote itself.  The
 // scores collect in LDS and leave in bursts of BURST tokens; a run may span several bursts (up to
 // SCORE_MAX_RUN tokens), so that what a workgroup pays once (staging W^T, the histogram, filling
@@ -176,9 +178,9 @@ __global__ __launch_bounds__(256, SOLVE && M == 64 ? 1 : 2) void score_kernel(
     int32_t *__restrict__ status, int *__restrict__ hist1, double *__restrict__ ostat) {
   constexpr int NSUB = 2, WTOK = 16 * NSUB, STEP = 4 * WTOK;     // tokens per wave / per WG step
   constexpr int NLD = WTOK * 16 / 64;                            // 16-B loads per lane per step
-  constexpr int FLIGHT = SOLVE || M > 16 ? 1 : 2;                // steps of loads in flight
   typedef WLayout<M> WL;
-  __shared__ __attribute__((aligned(16))) uint16_t wl[W_TERMS * WL::PLANE];
+  constexpr int ROOM = W_TERMS * (M < 32 ? WLayout<32>::PLANE : WL::PLANE);      // keeps a third workgroup off a unit
+  __shared__ __attribute__((aligned(16))) uint16_t wl[ROOM];
   constexpr int BURST = SCORE_BURST, BSTEPS = BURST / STEP;
   static_assert((BURST & (BURST - 1)) == 0, "bursts wrap round in LDS");
   struct Stream {
@@ -200,6 +202,7 @@ __global__ __launch_bounds__(256, SOLVE && M == 64 ? 1 : 2) void score_kernel(
   auto &hl = lds.s.hl;
   auto &sc_l = lds.s.sc_l;
   __shared__ double red[4][4];
+  static_assert(3 * (sizeof(wl) + sizeof(lds) + sizeof(red)) > 160 * 1024, "two workgroups a unit");
 
   PhiRegs<SOLVE ? M : 16> ph;
   if constexpr (SOLVE) ph.fetch(V.phi);
@@ -246,9 +249,8 @@ __global__ __launch_bounds__(256, SOLVE && M == 64 ? 1 : 2) void score_kernel(
     ss.fetch(shares);
     __builtin_amdgcn_sched_barrier(0);
   }
-  uint4 stg[FLIGHT][NLD];
-#pragma unroll
-  for (int u = 0; u < FLIGHT; ++u) load_step(u, stg[u]);
+  uint4 stg[NLD];
+  load_step(0, stg);
   // W^T follows the first step of keys through the load queue and waits in registers, so that the second step can be
   // requested as soon as the first has arrived and not only once W^T is in LDS
   constexpr int WN = (W_TERMS * WL::CHUNKS + 255) / 256;
@@ -354,8 +356,8 @@ __global__ __launch_bounds__(256, SOLVE && M == 64 ? 1 : 2) void score_kernel(
     }
   };
 
-  redistribute(stg[0]);
-  if (FLIGHT > 1 || nsteps > 1) load_step(FLIGHT, stg[0]);      // uniform
+  redistribute(stg);
+  if (nsteps > 1) load_step(1, stg);                            // uniform
 #pragma unroll
   for (int i = 0; i < (SOLVE ? 0 : WN); ++i) {
     const int cidx = tid + 256 * i;
@@ -373,28 +375,17 @@ __global__ __launch_bounds__(256, SOLVE && M == 64 ? 1 : 2) void score_kernel(
     __syncthreads();
     out.burst(sc_l, b0, cnt, av);
   };
-  // the operands of step `it` are in registers (kb) and the loads of the next FLIGHT steps in flight
-  auto next = [&](int it, uint4 (&from)[NLD]) {
+  // the operands of step `it` are in registers (kb) and the loads of the next one in flight
+  for (int it = 0; it + 1 < nsteps; ++it) {
     multiply(it);
     if ((it + 1) % BSTEPS == 0) {                   // uniform: a burst is complete
       leave((it / BSTEPS) * BURST);
       __syncthreads();                              // before the next burst's scores overwrite these
     }
-    redistribute(from);
-    if (FLIGHT > 1 || it + 2 < nsteps) load_step(it + 1 + FLIGHT, from);    // uniform
-  };
-  int it0 = 0;
-  for (; it0 + FLIGHT < nsteps; it0 += FLIGHT)
-#pragma unroll
-    for (int u = 0; u < FLIGHT; ++u) next(it0 + u, stg[(u + 1) % FLIGHT]);
-#pragma unroll
-  for (int u = 0; u < FLIGHT; ++u) {
-    if (u == FLIGHT - 1 || it0 + u + 1 == nsteps) {
-      multiply(it0 + u);
-      break;
-    }
-    next(it0 + u, stg[(u + 1) % FLIGHT]);
+    redistribute(stg);
+    if (it + 2 < nsteps) load_step(it + 2, stg);    // uniform
   }
+  multiply(nsteps - 1);
   leave((nsteps - 1) / BSTEPS * BURST);
   if (__any(bad)) {
     if (lane == 0) atomicOr(&status[s.ghead0 + w.head], COMPACTOR_STATUS_NONFINITE);
