@@ -88,7 +88,7 @@ int compute_units() {
 // of 1024 (16) 57.3 / 57.8 / 60.3, 2048 (32) 75.3 / 76.0 / 79.5, 4096 (64) 113 / 113 / 117, 8192 (128) 195 / 198 / 199.  Exact mode: 8 of
 // 65536 (32) 88.8 / 89.9 / 99.6, 131072 (64) 127 / 129 / 138; 32 of 18000 (35) 92 / 94 / 97, 57000 (111) 186 / 188 / 191; 256 of 4096 (64)
 // 126 / 126 / 128, 8192 (128) 206 / 211 / 210.
-struct GramPlan { int nwg, tiles_per_wg; bool fold; };
+struct GramPlan { int nwg, tiles_per_wg; GramKind kind; };
 GramPlan gram_plan(const compactor_params_t *p, const SegTable &T, int cus) {
   const long long total = total_tiles(T);
   const bool exact = p->sketch_dim == 0;
@@ -105,7 +105,7 @@ GramPlan gram_plan(const compactor_params_t *p, const SegTable &T, int cus) {
   // 4096 46.5 / 45.6.
   const int least = !exact && total <= 2ll * cus ? 4 : 8;
   if (g.tiles_per_wg < least && p->gram_wgs <= 0) g.tiles_per_wg = least;
-  g.fold = one && !plain && g.tiles_per_wg > 4;
+  g.kind = !one ? GRAM_TWO : plain || g.tiles_per_wg <= 4 ? GRAM_ONE : GRAM_FOLD;
   g.nwg = (int)((total + g.tiles_per_wg - 1) / g.tiles_per_wg);
   return g;
 }
@@ -336,7 +336,7 @@ int enqueue_score(const compactor_params_t *p, const SegTable &T, const GroupByt
   const int rpw = gp.tiles_per_wg;
   const Marks m{p->stage_events, st};
   MARK(m, 0);
-  HIP_TRY(launch_gram(T, gp.nwg, gp.tiles_per_wg, gp.fold, partials, st));
+  HIP_TRY(launch_gram(T, gp.nwg, gp.tiles_per_wg, gp.kind, partials, st));
   MARK(m, COMPACTOR_STAGE_GRAM + 1);
   MARK(m, COMPACTOR_STAGE_REDUCE + 1);       // the fp64 sum of the partials is part of the next kernel
   double *shares =

@@ -364,8 +364,10 @@ __device__ __forceinline__ long long partial_base(const SegTable &T, int lhead, 
 // All of them enqueue on `st` and return the hipGetLastError() of their launches.
 
 // Partial Gram matrices: the 10 upper 32x32 blocks (fp32) per (workgroup, head) intersection,
-// nwg + nheads slots.  fold: every tile is added up by itself (see gram_kernel).
-hipError_t launch_gram(const SegTable &T, int nwg, int tiles_per_wg, bool fold, float *partials, hipStream_t st);
+// nwg + nheads slots.  GRAM_ONE: a workgroup a compute unit; GRAM_FOLD: the same for longer runs, summed in parts (see
+// gram_kernel); GRAM_TWO: two a unit.
+enum GramKind { GRAM_ONE, GRAM_FOLD, GRAM_TWO };
+hipError_t launch_gram(const SegTable &T, int nwg, int tiles_per_wg, GramKind kind, float *partials, hipStream_t st);
 
 // Factorisation: partial Gram blocks -> W^T ([term][k_s][128] per head as W_TERMS bf16 planes; exact
 // mode: [term][128][128], rows up to the end of their group of 32 channels) and the status word.

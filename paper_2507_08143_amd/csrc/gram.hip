@@ -58,12 +58,17 @@ constexpr int GRAM_TG_UNROLL = 4;   // 16-token steps unrolled together (more op
 // is waited for does not depend on the way taken.  With conditions every second tile waited for all loads
 // (one workgroup of 8 waves a unit: 32 heads of 50001 tokens 73 us and 67 now, 8 of 131072 50 and 46; four a unit, 8 of
 // 40007 21 and 18).
+// GRAM_TWO: two workgroups a unit have one tile each under way.  With two each the memory loses more to disorder than it gains:
+// 256 heads of 32768 tokens 316 us, 306 with one, token by token 192 of 34660 285 and 260, 512 of 8192 175 and 158.  (Two that were
+// waited for together, as with loads under conditions, 321, 271 and 167.)
 // The body is compiled once per wave of a group: which blocks a wave owns is then known
 // at compile time, and the accumulators stay in fixed registers (a run-time switch inside the
 // loop makes the compiler copy them at every join).
-template <int wave, bool FOLD>
+template <int wave, GramKind KIND>
 __device__ __forceinline__ void gram_body(const SegTable &T, int tiles_per_wg, long long total,
                                           float *__restrict__ partials, unsigned char *smem) {
+  constexpr bool FOLD = KIND == GRAM_FOLD;
+  constexpr int AHEAD = KIND == GRAM_TWO ? 1 : 2;        // tiles under way
   const long long g0 = (long long)blockIdx.x * tiles_per_wg;
   const int count = (int)min((long long)tiles_per_wg, total - g0);
   if (count <= 0) return;
@@ -78,7 +83,7 @@ __device__ __forceinline__ void gram_body(const SegTable &T, int tiles_per_wg, l
     for (int v = 0; v < 16; ++v) acc[b][v] = sum[b][v] = 0.f;
   const int nblk = wave < 2 ? 3 : 2;
   const int first = wave == 0 ? 0 : (wave == 1 ? 3 : (wave == 2 ? 6 : 8));
-  TileCursor L, C;                 // load cursor runs two tiles ahead of the compute cursor
+  TileCursor L, C;                 // load cursor runs AHEAD tiles ahead of the compute cursor
   cursor_seek<GRAM_TILE>(T, g0, L);
   C = L;
 
@@ -199,26 +204,26 @@ __device__ __forceinline__ void gram_body(const SegTable &T, int tiles_per_wg, l
     cursor_next<GRAM_TILE>(T, C);
   };
 
-  // two tiles of global loads stay in flight while a third is being multiplied
-  uint4 stA[4], stB[4];
-  load_tile(0, stA);
-  load_tile(1, stB);
+  // AHEAD tiles of global loads stay in flight while another is being multiplied
+  uint4 st[AHEAD][4];
+#pragma unroll
+  for (int i = 0; i < AHEAD; ++i) load_tile(i, st[i]);
   // (one way out of the loop, for the same reason)
   int t = 0;
   for (; t + 2 <= count; t += 2) {
-    store_tile(smem, stA);
+    store_tile(smem, st[0]);
     __syncthreads();
-    load_tile(t + 2, stA);
+    load_tile(t + AHEAD, st[0]);
     compute_tile(smem, false);
     finish_tile(t + 1 == count, false);
-    store_tile(smem + TILE_BYTES, stB);
+    store_tile(smem + TILE_BYTES, st[1 % AHEAD]);
     __syncthreads();
-    load_tile(t + 3, stB);
+    load_tile(t + 1 + AHEAD, st[1 % AHEAD]);
     compute_tile(smem + TILE_BYTES, true);
     finish_tile(t + 2 == count, true);
   }
   if (t < count) {
-    store_tile(smem, stA);
+    store_tile(smem, st[0]);
     __syncthreads();
     compute_tile(smem, false);
     finish_tile(true, false);
@@ -243,25 +248,25 @@ __device__ __forceinline__ void gram_body(const SegTable &T, int tiles_per_wg, l
   }
 }
 
-template <bool FOLD>
+template <GramKind KIND>
 __global__ __launch_bounds__(256, GRAM_OCC) void gram_kernel(const SegTable T, int tiles_per_wg, long long total,
                                                              float *__restrict__ partials) {
   // two key tiles and room for one parked partial Gram matrix
   __shared__ __attribute__((aligned(16))) unsigned char smem[2 * TILE_BYTES + GRAM_PARTIAL_FLOATS * 4];
   // every wave passes the same workgroup barriers, each in its own copy of the loop
   switch (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) {
-    case 0: gram_body<0, FOLD>(T, tiles_per_wg, total, partials, smem); break;
-    case 1: gram_body<1, FOLD>(T, tiles_per_wg, total, partials, smem); break;
-    case 2: gram_body<2, FOLD>(T, tiles_per_wg, total, partials, smem); break;
-    default: gram_body<3, FOLD>(T, tiles_per_wg, total, partials, smem); break;
+    case 0: gram_body<0, KIND>(T, tiles_per_wg, total, partials, smem); break;
+    case 1: gram_body<1, KIND>(T, tiles_per_wg, total, partials, smem); break;
+    case 2: gram_body<2, KIND>(T, tiles_per_wg, total, partials, smem); break;
+    default: gram_body<3, KIND>(T, tiles_per_wg, total, partials, smem); break;
   }
 }
 
-hipError_t launch_gram(const SegTable &T, int nwg, int tiles_per_wg, bool fold, float *partials, hipStream_t st) {
+hipError_t launch_gram(const SegTable &T, int nwg, int tiles_per_wg, GramKind kind, float *partials, hipStream_t st) {
   const long long total = total_tiles(T);
   if (total <= 0 || nwg <= 0) return hipSuccess;
-  hipLaunchKernelGGL(fold ? gram_kernel<true> : gram_kernel<false>, dim3((unsigned)nwg), dim3(256), 0, st, T, tiles_per_wg,
-                     total, partials);
+  const auto kernel = kind == GRAM_FOLD ? gram_kernel<GRAM_FOLD> : kind == GRAM_TWO ? gram_kernel<GRAM_TWO> : gram_kernel<GRAM_ONE>;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)nwg), dim3(256), 0, st, T, tiles_per_wg, total, partials);
   return hipGetLastError();
 }
 
