@@ -77,7 +77,7 @@ int compute_units() {
 // Gram: a persistent launch, each workgroup taking an equal run of 64-row tiles.  Every (workgroup, head) partial costs
 // the factorisation 40 KB, so there is one workgroup a compute unit as long as its run stays short; long ones stream a little
 // faster with two.
-// Where that one workgroup sums its run as it goes on and where tile by tile (fold, see gram_kernel) goes by precision: as it
+// Where that one workgroup sums its run as it goes on and where tile by tile (GRAM_FOLD, see gram_kernel) goes by precision: as it
 // goes on up to 4 tiles, and up to 24 (17 to 32 heads: 16; exact mode: 32) with few heads and 8 tiles a unit or more; a call of other
 // sizes would else sum twice the rows in one accumulator that it used to.
 // compactor_score on MI355X, keys not in the last-level cache, us with one workgroup a unit / folding / two, tiles a unit in
@@ -88,6 +88,8 @@ int compute_units() {
 // of 1024 (16) 57.3 / 57.8 / 60.3, 2048 (32) 75.3 / 76.0 / 79.5, 4096 (64) 113 / 113 / 117, 8192 (128) 195 / 198 / 199.  Exact mode: 8 of
 // 65536 (32) 88.8 / 89.9 / 99.6, 131072 (64) 127 / 129 / 138; 32 of 18000 (35) 92 / 94 / 97, 57000 (111) 186 / 188 / 191; 256 of 4096 (64)
 // 126 / 126 / 128, 8192 (128) 206 / 211 / 210.
+// (Folding then meant two tiles at a time into one sum; a tile at a time into two takes up to 1 % longer: 8 of 131072 104 -> 105, exact
+// mode 128.5 -> 130; 32 of 40000 128.5 -> 131, 152.6 -> 154.4.  And two workgroups had two tiles each under way.)
 struct GramPlan { int nwg, tiles_per_wg; GramKind kind; };
 GramPlan gram_plan(const compactor_params_t *p, const SegTable &T, int cus) {
   const long long total = total_tiles(T);

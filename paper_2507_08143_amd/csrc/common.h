@@ -364,8 +364,8 @@ __device__ __forceinline__ long long partial_base(const SegTable &T, int lhead, 
 // All of them enqueue on `st` and return the hipGetLastError() of their launches.
 
 // Partial Gram matrices: the 10 upper 32x32 blocks (fp32) per (workgroup, head) intersection,
-// nwg + nheads slots.  GRAM_ONE: a workgroup a compute unit; GRAM_FOLD: the same for longer runs, summed in parts (see
-// gram_kernel); GRAM_TWO: two a unit.
+// nwg + nheads slots.  A workgroup a compute unit whose run is summed as it goes on (GRAM_ONE) or in pieces, for precision (GRAM_FOLD:
+// see gram_kernel), or two a unit (GRAM_TWO).
 enum GramKind { GRAM_ONE, GRAM_FOLD, GRAM_TWO };
 hipError_t launch_gram(const SegTable &T, int nwg, int tiles_per_wg, GramKind kind, float *partials, hipStream_t st);
 

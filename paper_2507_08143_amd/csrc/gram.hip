@@ -45,14 +45,17 @@ __device__ __forceinline__ bf16x4 lds_read_tr(const unsigned char *p) {
 constexpr int GRAM_OCC = 2;         // waves per SIMD the register budget is set for
 constexpr int GRAM_TG_UNROLL = 4;   // 16-token steps unrolled together (more operands in flight)
 //
-// FOLD: long runs in one workgroup a compute unit, which leaves half as many partials as two, and no less precise: the
-// products of every two tiles are added up by themselves and then to the sum of those before, so that a product passes
-// through eight roundings in the accumulator of the matrix core and one for every second tile behind it, where without FOLD
-// it passes through four for every tile behind it.  Relative error of the scores against 64 bits,
-// two workgroups a unit that do not / one that folds: exact mode, deficient keys, 64 heads of 8192 9.4e-6 / 7.6e-6, 128 of 4096
-// 9.5e-6 / 7.7e-6, 256 of 1024 7.8e-6 / 7.6e-6; k_s = 48, keys of low rank, 32 of 16384 4.6e-6 / 4.1e-6, 128 of 4096 4.8e-6 / 4.2e-6, 256
-// of 4096 4.6e-6 / 4.2e-6.  At every second tile and not at every fourth, say, because a fold under a condition makes
-// the compiler copy the accumulators where the paths join.
+// In how many pieces a run's products are added up (KIND), and so how much of them is rounded away.  A product of a run that is
+// summed as it goes on (GRAM_ONE) passes through several roundings in the accumulator of the matrix core for every tile behind
+// it, each of a sum that has grown to what the run has so far.  With every tile added up by itself it passes through those of one
+// tile and one for every tile behind it, and with the even and the odd tiles apart (GRAM_FOLD) through half as many, of half the
+// size, and one where they meet.  A workgroup that has a unit to itself does in one run what two, or two groups of
+// waves with sums of their own, did before; GRAM_TWO adds up every two tiles by themselves.
+// Relative error of the scores against 64 bits, keys whose channels are nearly alike (condition of G 1e6), two such groups or
+// workgroups / one sum of every two tiles / now: exact mode, 8 heads of 8192 (runs of 8 tiles) 6.8e-5 / 4.1e-5 / 3.8e-5, 64 of 2304 (9)
+// 7.5e-5 / 8.3e-5 / 7.5e-5, 64 of 8192 (32) 7.8e-5 / 9.0e-5 / 7.8e-5, 32 of 56000 (110) 8.2e-5 / 1.08e-4 / 8.2e-5; k_s = 48, 128 of
+// 8000 (63) 1.18e-4 / 1.43e-4 / 1.13e-4, 256 of 4096 (64) 4.7e-4 / 2.3e-4 / 1.8e-4; GRAM_TWO, 256 of 8192, summed as it goes on 6.3e-4,
+// now 1.6e-4.  (Time: gram_plan.)
 // Key loads stand under no condition (past a head's end its last row, cleared on the way to LDS; past the run's end one
 // piece for all lanes): two tiles are under way while a third is multiplied only if the number of loads behind the one that
 // is waited for does not depend on the way taken.  With conditions every second tile waited for all loads
@@ -67,7 +70,8 @@ constexpr int GRAM_TG_UNROLL = 4;   // 16-token steps unrolled together (more op
 template <int wave, GramKind KIND>
 __device__ __forceinline__ void gram_body(const SegTable &T, int tiles_per_wg, long long total,
                                           float *__restrict__ partials, unsigned char *smem) {
-  constexpr bool FOLD = KIND == GRAM_FOLD;
+  constexpr int FOLD = KIND == GRAM_ONE ? 0 : KIND == GRAM_TWO ? 2 : 1;      // tiles added up by themselves
+  constexpr bool APART = KIND == GRAM_FOLD;
   constexpr int AHEAD = KIND == GRAM_TWO ? 1 : 2;        // tiles under way
   const long long g0 = (long long)blockIdx.x * tiles_per_wg;
   const int count = (int)min((long long)tiles_per_wg, total - g0);
@@ -76,11 +80,11 @@ __device__ __forceinline__ void gram_body(const SegTable &T, int tiles_per_wg, l
   const int tid = threadIdx.x, lane = tid & 63;
   const int ld_row = tid >> 4, ld_chunk = tid & 15;   // loader: 16 lanes cover one 256-B row
 
-  f32x16 acc[3], sum[3];           // sum: with FOLD, the tiles before
+  f32x16 acc[3], sum[3], other[3];       // with FOLD the tiles before are in sum; other: APART, the odd ones
 #pragma unroll
   for (int b = 0; b < 3; ++b)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) acc[b][v] = sum[b][v] = 0.f;
+    for (int v = 0; v < 16; ++v) acc[b][v] = sum[b][v] = other[b][v] = 0.f;
   const int nblk = wave < 2 ? 3 : 2;
   const int first = wave == 0 ? 0 : (wave == 1 ? 3 : (wave == 2 ? 6 : 8));
   TileCursor L, C;                 // load cursor runs AHEAD tiles ahead of the compute cursor
@@ -114,7 +118,7 @@ __device__ __forceinline__ void gram_body(const SegTable &T, int tiles_per_wg, l
   const int tr_off = ((8 * g + (c16 >> 2)) * PITCH + 16 * half + 4 * (c16 & 3)) * 2;
 
 #define GRAM_MFMA(b, x, y) \
-  acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[x], op[y], FOLD && !odd && tg == 0 ? f32x16{} : acc[b], 0, 0, 0)
+  acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(op[x], op[y], tg == 0 && (FOLD == 1 || (FOLD == 2 && !odd)) ? f32x16{} : acc[b], 0, 0, 0)
   auto compute_tile = [&](const unsigned char *buf, bool odd) {
 #pragma unroll GRAM_TG_UNROLL
     for (int tg = 0; tg < GRAM_TILE / 16; ++tg) {        // 16 tokens per MFMA step
@@ -131,10 +135,10 @@ __device__ __forceinline__ void gram_body(const SegTable &T, int tiles_per_wg, l
       if constexpr (wave == 2) { GRAM_MFMA(0, 1, 3); GRAM_MFMA(1, 2, 2); }
       if constexpr (wave == 3) { GRAM_MFMA(0, 2, 3); GRAM_MFMA(1, 3, 3); }
     }
-    if (FOLD && odd) {
+    if (FOLD == 1 || (FOLD == 2 && odd)) {
 #pragma unroll
       for (int b = 0; b < 3; ++b)
-        if (b < nblk) sum[b] += acc[b];
+        if (b < nblk) (APART && odd ? other : sum)[b] += acc[b];
     }
   };
 #undef GRAM_MFMA
@@ -163,9 +167,12 @@ __device__ __forceinline__ void gram_body(const SegTable &T, int tiles_per_wg, l
   float *park = reinterpret_cast<float *>(smem + 2 * TILE_BYTES);
   int parked_lhead = -1;
   enum { TO_GLOBAL, TO_GLOBAL_STREAM, TO_LDS };
-  // odd: with FOLD, the products of the last tile are in the sums
+  // odd: the last tile was an odd one, whose products are in the sums with FOLD
   auto flush = [&](int lhead, int how, bool odd) {
-    auto left = [&](int b, int v) { return !FOLD ? acc[b][v] : odd ? sum[b][v] : sum[b][v] + acc[b][v]; };
+    auto left = [&](int b, int v) {
+      const float x = !FOLD ? acc[b][v] : FOLD == 1 || odd ? sum[b][v] : sum[b][v] + acc[b][v];
+      return APART ? other[b][v] + x : x;
+    };
     float *out = how == TO_LDS ? park
                                : partials + ((size_t)blockIdx.x + lhead) * GRAM_PARTIAL_FLOATS;
 #pragma unroll
@@ -181,7 +188,7 @@ __device__ __forceinline__ void gram_body(const SegTable &T, int tiles_per_wg, l
           else
             *reinterpret_cast<float4 *>(ob + (64 * q + lane) * 4) = v;
 #pragma unroll
-          for (int e = 4 * q; e < 4 * q + 4; ++e) acc[b][e] = sum[b][e] = 0.f;
+          for (int e = 4 * q; e < 4 * q + 4; ++e) acc[b][e] = sum[b][e] = other[b][e] = 0.f;
         }
       }
     }
@@ -265,7 +272,7 @@ __global__ __launch_bounds__(256, GRAM_OCC) void gram_kernel(const SegTable T, i
 hipError_t launch_gram(const SegTable &T, int nwg, int tiles_per_wg, GramKind kind, float *partials, hipStream_t st) {
   const long long total = total_tiles(T);
   if (total <= 0 || nwg <= 0) return hipSuccess;
-  const auto kernel = kind == GRAM_FOLD ? gram_kernel<GRAM_FOLD> : kind == GRAM_TWO ? gram_kernel<GRAM_TWO> : gram_kernel<GRAM_ONE>;
+  const auto kernel = kind == GRAM_ONE ? gram_kernel<GRAM_ONE> : kind == GRAM_FOLD ? gram_kernel<GRAM_FOLD> : gram_kernel<GRAM_TWO>;
   hipLaunchKernelGGL(kernel, dim3((unsigned)nwg), dim3(256), 0, st, T, tiles_per_wg, total, partials);
   return hipGetLastError();
 }
