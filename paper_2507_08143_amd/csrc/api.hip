@@ -190,9 +190,7 @@ GroupBytes group_bytes_needed(const compactor_params_t *p, const SegTable &T, bo
   const int cus = compute_units();
   const GramPlan gp = gram_plan(p, T, cus);
   GroupBytes g;
-  // heads for every unit: room for the two workgroups a unit that they get when they are long, whatever their length
-  const size_t gram_wgs = T.nheads < cus ? gp.nwg : gp.nwg < 2 * cus ? 2 * (size_t)cus : gp.nwg;
-  g.partials = align_up((gram_wgs + T.nheads) * GRAM_PARTIAL_FLOATS * sizeof(float));
+  g.partials = align_up(((size_t)gp.nwg + T.nheads) * GRAM_PARTIAL_FLOATS * sizeof(float));
   // Many workgroups per head form S = Phi^T G Phi (exact mode: G) only where the heads alone do not fill
   // the chip.  Factorisation stage on MI355X, us with / without shares, n = 2048:
   //   heads         8           64          128         256         512         1024       2048       4096

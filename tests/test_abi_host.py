@@ -136,6 +136,28 @@ def test_argument_errors_are_reported_on_the_host(B):
     assert B.compactor_version().count(".") == 1
 
 
+def _accepts(B, p, reqs, nbytes, fused=True):
+    """Whether a call (compress with its scores in the workspace, or score) takes a workspace of nbytes: the place is
+    misaligned, which is found out after the size and before anything is enqueued."""
+    args = (C.byref(p), reqs, len(reqs))
+    if fused:
+        rc = B._lib.compactor_compress(*args, 0, 0x3000, 0x4000, 0x5000, 0x6000, 0x7000, 0x10010, nbytes, None)
+    else:
+        rc = B._lib.compactor_score(*args, 0x3000, 0x4000, 0x10010, nbytes, None)
+    assert rc in (B.EALIGN, B.EWORKSPACE)
+    return rc == B.EALIGN
+
+
+@pytest.mark.parametrize("heads,n,ks", [(600, 64, 48), (600, 256, 48), (700, 64, 48), (800, 64, 16), (640, 128, 48),
+                                        (600, 100, 64)])
+def test_many_short_heads_fit_the_static_scratch(B, heads, n, ks):
+    """Room for the partial Gram matrices that the call's workgroups can leave, and no more: at least 8 tiles of 64 rows
+    a workgroup, and a partial for every head and workgroup."""
+    p = B._Params(heads // 8, 8, 128, ks, 0x2000, 0.0, 0.3, 0, 0, 0, 0, None)
+    reqs = (B._Request * 1)(_req(B, n=n))
+    assert _accepts(B, p, reqs, B.STATIC_SCRATCH_BYTES)
+
+
 def test_widened_entry_points_check_their_arguments_on_the_host(B):
     good = B._Params(2, 2, 128, 48, 0x2000, 0.0, 0.3, 0, 0, 0, 0, None)
     reqs = (B._Request * 1)(_req(B, n=100, ratio=0.5))

@@ -35,9 +35,9 @@ def _same(a, b, what):
         assert torch.equal(a[name].view(torch.int16), b[name].view(torch.int16)), "%s: %s differs" % (what, name)
 
 
-def _case(C, w, what, scope=0, with_scores=True):
+def _case(C, w, what, scope=0, with_scores=True, gram_wgs=0):
     params, reqs = U.make_call(C, w, DEV)
-    params.select_scope = scope
+    params.select_scope, params.gram_wgs = scope, gram_wgs
     ref = _buffers(C, params, reqs, w)
     got = _buffers(C, params, reqs, w)
     if not with_scores:
@@ -78,13 +78,14 @@ def test_static_scratch_compress_equals_compress():
 
 
 def test_static_scratch_needs_no_room_for_what_only_speeds_a_call_up():
+    """Up to 128 heads S is formed from shares where there is room for them (17 tiles, two to a Gram workgroup, bring nine or
+    ten partials a head), else by one workgroup per head: the same bits."""
     C = U.binding()
     _say("compress on the static scratch: a batch that fits it without the factorisation's shares")
-    w = W.config1(DEV, L=1, H=256, n=1000)
+    w = W.config1(DEV, L=1, H=128, n=1030)
     w.sketch_dim = 64
-    params, reqs = U.make_call(C, w, DEV)
+    params, reqs, _ = _case(C, w, "128 heads, k_s = 64", gram_wgs=1100)
     assert C.compactor_workspace_size(params, reqs) > C.STATIC_SCRATCH_BYTES
-    _case(C, w, "256 heads, k_s = 64")
 
 
 def test_static_scratch_refuses_what_does_not_fit():
