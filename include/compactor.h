@@ -166,10 +166,12 @@ int compactor_srht_phi(int32_t sketch_dim, const uint8_t *signs, const int32_t *
 
 /* Bytes of device workspace that score / select / compress need for this batch. host.
  * The workspace must be 256-byte aligned; its contents are scratch (no state is kept
- * between calls).  Part of it only speeds the factorisation of few heads up: a workspace that
- * lacks no more than that part is accepted too and gives the same results.  The size depends on the number of compute units of the current HIP device
- * (it sets the number of partial Gram matrices): ask with the device current that will run the
- * call.  Where no device can be queried the size for 256 compute units (MI355X) is returned. */
+ * between calls).  It also holds calls of the same requests at smaller lengths in the same
+ * proportions, some of which need more than this one.  Part of it only speeds small calls up: a
+ * workspace that lacks no more than that part is accepted too and gives the same results.  The
+ * size depends on the number of compute units of the current HIP device (it sets the number of
+ * partial Gram matrices): ask with the device current that will run the call.  Where no device can
+ * be queried the size for 256 compute units (MI355X) is returned. */
 int compactor_workspace_size(const compactor_params_t *p, const compactor_request_t *reqs,
                              int32_t nreq, size_t *bytes);
 
@@ -262,7 +264,7 @@ int compactor_compress(const compactor_params_t *p, const compactor_request_t *r
  * and outputs are the caller's, as in compactor_compress, and the results are the same bits.
  * A batch whose scratch exceeds COMPACTOR_STATIC_SCRATCH_BYTES is refused with COMPACTOR_EWORKSPACE
  * before anything is enqueued.  Only the scratch that the call cannot do without counts, which is what
- * compactor_workspace_size reports less the part that merely speeds the factorisation up (and less
+ * compactor_workspace_size reports less the part that merely speeds calls up (and less
  * the scores, if scores != NULL): a batch whose compactor_workspace_size fits is always accepted, one
  * somewhat larger may be.  params.group_bytes bounds the scratch of a large batch.  All calls on one GPU share
  * that GPU's buffer: calls that overlap in time on one GPU (two streams, two threads) race on it

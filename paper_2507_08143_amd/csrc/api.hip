@@ -3,6 +3,7 @@
 #include <math.h>
 #include <string.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "common.h"
@@ -90,7 +91,8 @@ int compute_units() {
 // 126 / 126 / 128, 8192 (128) 206 / 211 / 210.
 // (Folding then meant two tiles at a time into one sum; a tile at a time into two takes up to 1 % longer: 8 of 131072 104 -> 105, exact
 // mode 128.5 -> 130; 32 of 40000 128.5 -> 131, 152.6 -> 154.4.  And two workgroups had two tiles each under way.)
-struct GramPlan { int nwg, tiles_per_wg; GramKind kind; };
+// half_wgs: not 0 where two workgroups may share a run of 8 tiles, and how many there are then.
+struct GramPlan { int nwg, tiles_per_wg; GramKind kind; int half_wgs; };
 GramPlan gram_plan(const compactor_params_t *p, const SegTable &T, int cus) {
   const long long total = total_tiles(T);
   const bool exact = p->sketch_dim == 0;
@@ -102,13 +104,14 @@ GramPlan gram_plan(const compactor_params_t *p, const SegTable &T, int cus) {
   if (want < 1) want = 1;
   g.tiles_per_wg = (int)((total + want - 1) / want);
   // Not below 8 tiles (512 rows) a workgroup: every partial costs a 40 KB round trip; in small calls 4, where the run is what
-  // takes longest.  compactor_score, us with at least 4 / 8 tiles: one head of 2048 24.6 / 27.6, 4096 25.5 / 27.5, 8192 27.0 / 28.3,
-  // 8 of 1024 25.7 / 27.6, 2048 26.3 / 28.3, 4096 (512 tiles) 28.2 / 28.8, 8192 32.8 / 31.7; 64 of 1024 36.0 / 35.4; exact mode, 8 of
-  // 4096 46.5 / 45.6.
-  const int least = !exact && total <= 2ll * cus ? 4 : 8;
-  if (g.tiles_per_wg < least && p->gram_wgs <= 0) g.tiles_per_wg = least;
-  g.kind = !one ? GRAM_TWO : plain || g.tiles_per_wg <= 4 ? GRAM_ONE : GRAM_FOLD;
+  // takes longest, if the workspace has room for the partials.  compactor_score, us with 4 / 8 tiles: one head of 2048 24.6 / 27.6,
+  // 4096 25.5 / 27.5, 8192 27.0 / 28.3, 8 of 1024 25.7 / 27.6, 2048 26.3 / 28.3, 4096 (512 tiles) 28.2 / 28.8, 8192 32.8 / 31.7; 64 of
+  // 1024 36.0 / 35.4; 136 of 128 31.4 / 35.3, 256 of 64 33.9 / 39.6; exact mode, 8 of 4096 46.5 / 45.6.
+  if (g.tiles_per_wg < 2 * GRAM_HALF_RUN && p->gram_wgs <= 0) g.tiles_per_wg = 2 * GRAM_HALF_RUN;
+  const bool halves = !exact && p->gram_wgs <= 0 && total <= 2ll * cus;
+  g.kind = !one ? GRAM_TWO : plain || g.tiles_per_wg <= 4 ? GRAM_ONE : halves ? GRAM_HALVES : GRAM_FOLD;
   g.nwg = (int)((total + g.tiles_per_wg - 1) / g.tiles_per_wg);
+  g.half_wgs = halves ? (int)((total + GRAM_HALF_RUN - 1) / GRAM_HALF_RUN) : 0;
   return g;
 }
 
@@ -170,8 +173,8 @@ int score_tokens_for(const compactor_params_t *p, const SegTable &T, int cus) {
 
 struct GroupBytes {
   size_t partials, wt, hist1, sel, bstat, scores;   // in this order in the workspace
-  size_t shares;         // and, where the workspace has room for it, scratch that speeds up the
-                         // factorisation (the results do not depend on it)
+  size_t shares, halves; // and, where the workspace has room for one or both, scratch that speeds up the factorisation, and
+                         // partials of half runs (the results do not depend on them)
   size_t total() const { return partials + wt + hist1 + sel + bstat + scores; }
   size_t off_wt() const { return partials; }
   size_t off_hist1() const { return off_wt() + wt; }
@@ -179,8 +182,14 @@ struct GroupBytes {
   size_t off_bstat() const { return off_sel() + sel; }
   size_t off_scores() const { return off_bstat() + bstat; }
   size_t off_shares() const { return total(); }
-  size_t wanted() const { return total() + shares; }
+  size_t off_halves() const { return total() + shares; }
+  size_t with_shares() const { return total() + shares; }
+  size_t with_halves() const { return total() + shares + halves; }
 };
+
+size_t partial_bytes(const SegTable &T, long long wgs) {
+  return align_up((size_t)(wgs + T.nheads) * GRAM_PARTIAL_FLOATS * sizeof(float));
+}
 
 GroupBytes group_bytes_needed(const compactor_params_t *p, const SegTable &T, bool need_scores) {
   const int ks = p->sketch_dim;
@@ -190,7 +199,7 @@ GroupBytes group_bytes_needed(const compactor_params_t *p, const SegTable &T, bo
   const int cus = compute_units();
   const GramPlan gp = gram_plan(p, T, cus);
   GroupBytes g;
-  g.partials = align_up(((size_t)gp.nwg + T.nheads) * GRAM_PARTIAL_FLOATS * sizeof(float));
+  g.partials = partial_bytes(T, gp.nwg);
   // Many workgroups per head form S = Phi^T G Phi (exact mode: G) only where the heads alone do not fill
   // the chip.  Factorisation stage on MI355X, us with / without shares, n = 2048:
   //   heads         8           64          128         256         512         1024       2048       4096
@@ -204,7 +213,8 @@ GroupBytes group_bytes_needed(const compactor_params_t *p, const SegTable &T, bo
   // (Figures of sketched mode from before sketch_direct_kernel, which takes most calls of more than 128 heads now; their
   // room stays, since it is the lengths of a call that decide.)
   const int most_heads = ks > 0 ? cus : 3 * cus / 8;
-  g.shares = T.nheads <= most_heads ? align_up(solve_plan(T, ks, gp.tiles_per_wg).share_bytes) : 0;
+  const SolvePlan plan = solve_plan(T, ks, gp.tiles_per_wg, gp.half_wgs > 0);
+  g.shares = T.nheads <= most_heads ? align_up(plan.share_bytes) : 0;
   g.wt = align_up((size_t)T.nheads * W_TERMS * m * D * sizeof(uint16_t));
   g.hist1 = align_up((size_t)T.nheads * HIST1_BINS * sizeof(int));
   g.sel = select_needs_pools(T) ? align_up((size_t)select_scratch(T).ints() * sizeof(int)) : 0;
@@ -214,7 +224,35 @@ GroupBytes group_bytes_needed(const compactor_params_t *p, const SegTable &T, bo
     g.bstat = align_up((size_t)total_blocks(T, score_tokens_for(p, T, compute_units()), SCORE_STEP, false) *
                        4 * sizeof(double));
   g.scores = need_scores ? align_up((size_t)rows * sizeof(float)) : 0;
+  g.halves = gp.half_wgs > 0 && (g.shares > 0 || plan.direct) ? partial_bytes(T, gp.half_wgs) : 0;
   return g;
+}
+
+// What compactor_workspace_size counts.  A workspace is often asked for at the greatest lengths and used for shorter ones, which
+// may need more of something: runs are whole tiles (one head of 2048 tiles has 256 of them, of 2049 228), small calls have half runs,
+// and the workgroups of a score launch change with the lengths.  So this holds any call of the same heads at lengths of the same
+// proportions.
+size_t bytes_asked(const compactor_params_t *p, const SegTable &T, bool need_scores) {
+  const GroupBytes g = group_bytes_needed(p, T, need_scores);
+  const long long cus = compute_units(), total = total_tiles(T);
+  const long long most_wgs = p->gram_wgs > 0 ? p->gram_wgs : total < 112 * cus ? cus : 2 * cus;
+  const int least_run = p->gram_wgs > 0 ? 1 : 2 * GRAM_HALF_RUN;
+  auto runs = [&](int tiles, long long most) { return std::min((total + tiles - 1) / tiles, most); };
+  auto shares = [&](long long wgs, bool halves) {
+    return g.shares > 0 ? align_up(share_bytes_most(T, p->sketch_dim, least_run, wgs, halves)) : 0;
+  };
+  size_t rest = g.total() - g.partials;
+  if (g.bstat > 0) {
+    long long rows = 0;
+    for (int i = 0; i < T.nseg; ++i) rows += (long long)T.s[i].n * T.s[i].head_count;
+    // runs are of 1024 tokens or more, or one a unit
+    rest += std::max(g.bstat, align_up((size_t)(rows / 1024 + cus + T.nheads) * 4 * sizeof(double))) - g.bstat;
+  }
+  size_t asked = std::max(g.with_halves(), rest + shares(most_wgs, false) + partial_bytes(T, runs(least_run, most_wgs)));
+  if (p->sketch_dim > 0 && p->gram_wgs <= 0 && T.nheads <= 2 * cus)       // (more heads are more tiles)
+    asked = std::max(asked, rest + shares(cus / 4, true) + partial_bytes(T, runs(2 * GRAM_HALF_RUN, cus / 4)) +
+                                partial_bytes(T, runs(GRAM_HALF_RUN, cus / 2)));
+  return asked;
 }
 
 // Walks the batch in head order and cuts it into launch groups of about group_rows key rows
@@ -279,14 +317,14 @@ long long group_rows_of(const compactor_params_t *p) {
 }
 
 // Bytes of workspace a call needs: what its largest head group needs (groups run one after the
-// other on the stream and reuse the workspace).  wanted: with the optional parts.
+// other on the stream and reuse the workspace).  wanted: what compactor_workspace_size reports.
 int workspace_need(const compactor_params_t *p, const compactor_request_t *reqs, int32_t nreq,
                    bool local_scores, bool wanted, size_t *bytes) {
   size_t need = 0;
   const int rc = for_each_group(p, reqs, nreq, group_rows_of(p), local_scores,
                                 [&](const SegTable &T, long long) {
-                                  const GroupBytes gb = group_bytes_needed(p, T, local_scores);
-                                  const size_t t = wanted ? gb.wanted() : gb.total();
+                                  const size_t t = wanted ? bytes_asked(p, T, local_scores)
+                                                          : group_bytes_needed(p, T, local_scores).total();
                                   if (t > need) need = t;
                                   return COMPACTOR_OK;
                                 });
@@ -324,7 +362,6 @@ struct Marks {
 // of the final scores is left at gb.off_hist1() of the workspace (for the selection).
 int enqueue_score(const compactor_params_t *p, const SegTable &T, const GroupBytes &gb, float *scores,
                   int32_t *status, unsigned char *ws, size_t ws_bytes, hipStream_t st, bool want_hist1) {
-  float *partials = reinterpret_cast<float *>(ws);
   uint16_t *wt = reinterpret_cast<uint16_t *>(ws + gb.off_wt());
   int *hist1 = want_hist1 ? reinterpret_cast<int *>(ws + gb.off_hist1()) : nullptr;
   double *ostat = gb.bstat ? reinterpret_cast<double *>(ws + gb.off_bstat()) : nullptr;
@@ -336,16 +373,22 @@ int enqueue_score(const compactor_params_t *p, const SegTable &T, const GroupByt
   const int rpw = gp.tiles_per_wg;
   const Marks m{p->stage_events, st};
   MARK(m, 0);
-  HIP_TRY(launch_gram(T, gp.nwg, gp.tiles_per_wg, gp.kind, partials, st));
+  double *shares =
+      gb.shares > 0 && ws_bytes >= gb.with_shares() ? reinterpret_cast<double *>(ws + gb.off_shares()) : nullptr;
+  const bool halves = gb.halves > 0 && ws_bytes >= gb.with_halves();
+  float *partials = reinterpret_cast<float *>(halves ? ws + gb.off_halves() : ws);
+  if (halves) {
+    HIP_TRY(launch_gram(T, gp.half_wgs, GRAM_HALF_RUN, GRAM_HALF, partials, st));
+  } else {
+    HIP_TRY(launch_gram(T, gp.nwg, gp.tiles_per_wg, gp.kind, partials, st));
+  }
   MARK(m, COMPACTOR_STAGE_GRAM + 1);
   MARK(m, COMPACTOR_STAGE_REDUCE + 1);       // the fp64 sum of the partials is part of the next kernel
-  double *shares =
-      gb.shares > 0 && ws_bytes >= gb.wanted() ? reinterpret_cast<double *>(ws + gb.off_shares()) : nullptr;
   const int score_tokens = score_tokens_for(p, T, cus);
-  const SolvePlan plan = solve_plan(T, p->sketch_dim, rpw);
+  const SolvePlan plan = solve_plan(T, p->sketch_dim, rpw, gp.half_wgs > 0);
   const bool in_score = shares != nullptr && !plan.direct && score_solves(T, p->sketch_dim, score_tokens, cus);
   if (p->sketch_dim > 0) {
-    HIP_TRY(launch_sketch_solve(T, p->sketch_dim, rpw, plan, partials, shares, p->phi, p->ridge_rel,
+    HIP_TRY(launch_sketch_solve(T, p->sketch_dim, rpw, plan, partials, halves, shares, p->phi, p->ridge_rel,
                                 in_score ? nullptr : wt, status, zero, zero_ints, st));
   } else {
     HIP_TRY(launch_exact_solve(T, rpw, partials, shares, p->ridge_rel, wt, status, zero, zero_ints, st));

@@ -365,8 +365,10 @@ __device__ __forceinline__ long long partial_base(const SegTable &T, int lhead, 
 
 // Partial Gram matrices: the 10 upper 32x32 blocks (fp32) per (workgroup, head) intersection,
 // nwg + nheads slots.  A workgroup a compute unit whose run is summed as it goes on (GRAM_ONE) or in pieces, for precision (GRAM_FOLD:
-// see gram_kernel), or two a unit (GRAM_TWO).
-enum GramKind { GRAM_ONE, GRAM_FOLD, GRAM_TWO };
+// see gram_kernel), or two a unit (GRAM_TWO).  GRAM_HALVES: a run of 2 GRAM_HALF_RUN tiles, in two sums; GRAM_HALF: workgroups
+// of half such a run.
+enum GramKind { GRAM_ONE, GRAM_HALF, GRAM_HALVES, GRAM_FOLD, GRAM_TWO };
+constexpr int GRAM_HALF_RUN = 4;
 hipError_t launch_gram(const SegTable &T, int nwg, int tiles_per_wg, GramKind kind, float *partials, hipStream_t st);
 
 // Factorisation: partial Gram blocks -> W^T ([term][k_s][128] per head as W_TERMS bf16 planes; exact
@@ -375,13 +377,17 @@ hipError_t launch_gram(const SegTable &T, int nwg, int tiles_per_wg, GramKind ki
 // shares: plan.share_bytes of scratch, which lets many workgroups per head add the partials up (one
 // launch more), or null: one workgroup per head does it (the same bits).
 // wt null: the shares only, with the status words set to 0 (see launch_score).
+// halves: the partials are those of GRAM_HALF workgroups (tiles_per_wg: of two together); only with shares or where direct.
 struct SolvePlan {
   bool direct;           // sketched mode, many heads: without shares, whatever the room (wt is not null)
   int parts;             // the partials of a head are added in this many runs (sketched mode)
   int nshares;           // shares of a head (sketched mode)
   size_t share_bytes;
 };
-SolvePlan solve_plan(const SegTable &T, int ks, int tiles_per_wg);
+SolvePlan solve_plan(const SegTable &T, int ks, int tiles_per_wg, bool halves);       // halves: GramPlan::half_wgs > 0
+// The most share_bytes that T's heads may want at lengths of the same proportions and at most theirs, in runs of at least
+// least_run tiles and with at most most_wgs Gram workgroups.
+size_t share_bytes_most(const SegTable &T, int ks, int least_run, long long most_wgs, bool halves);
 
 // Exact mode: G + rho I -> Cholesky -> W^T = L^{-1}.
 hipError_t launch_exact_solve(const SegTable &T, int tiles_per_wg, const float *partials,
@@ -390,7 +396,7 @@ hipError_t launch_exact_solve(const SegTable &T, int tiles_per_wg, const float *
 
 // Sketched mode: S = Phi^T G Phi + rho I -> Cholesky -> W^T = L^{-1} Phi^T.
 hipError_t launch_sketch_solve(const SegTable &T, int ks, int tiles_per_wg, const SolvePlan &plan,
-                               const float *partials, double *shares, const float *phi,
+                               const float *partials, bool halves, double *shares, const float *phi,
                                float ridge_rel, uint16_t *wt, int32_t *status, int *zero,
                                long long zero_ints, hipStream_t st);
 

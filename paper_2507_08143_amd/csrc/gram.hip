@@ -51,6 +51,9 @@ constexpr int GRAM_TG_UNROLL = 4;   // 16-token steps unrolled together (more op
 // tile and one for every tile behind it, and with the even and the odd tiles apart (GRAM_FOLD) through half as many, of half the
 // size, and one where they meet.  A workgroup that has a unit to itself does in one run what two, or two groups of
 // waves with sums of their own, did before; GRAM_TWO adds up every two tiles by themselves.
+// In small calls a run of 8 has a sum for either half: with room for the partials two workgroups take one each
+// (GRAM_HALF) and the sum of their partials, rounded to fp32, is what one workgroup leaves without room (GRAM_HALVES), bit by bit (one
+// head of 4096, k_s = 48, 5.3e-5 where partials of 4 tiles summed as they went on and met in fp64 had 8.1e-5 and pairs 8.6e-5).
 // Relative error of the scores against 64 bits, keys whose channels are nearly alike (condition of G 1e6), two such groups or
 // workgroups / one sum of every two tiles / now: exact mode, 8 heads of 8192 (runs of 8 tiles) 6.8e-5 / 4.1e-5 / 3.8e-5, 64 of 2304 (9)
 // 7.5e-5 / 8.3e-5 / 7.5e-5, 64 of 8192 (32) 7.8e-5 / 9.0e-5 / 7.8e-5, 32 of 56000 (110) 8.2e-5 / 1.08e-4 / 8.2e-5; k_s = 48, 128 of
@@ -71,7 +74,7 @@ template <int wave, GramKind KIND>
 __device__ __forceinline__ void gram_body(const SegTable &T, int tiles_per_wg, long long total,
                                           float *__restrict__ partials, unsigned char *smem) {
   constexpr int FOLD = KIND == GRAM_ONE ? 0 : KIND == GRAM_TWO ? 2 : 1;      // tiles added up by themselves
-  constexpr bool APART = KIND == GRAM_FOLD;
+  constexpr bool APART = KIND == GRAM_FOLD, HALVES = KIND == GRAM_HALVES;
   constexpr int AHEAD = KIND == GRAM_TWO ? 1 : 2;        // tiles under way
   const long long g0 = (long long)blockIdx.x * tiles_per_wg;
   const int count = (int)min((long long)tiles_per_wg, total - g0);
@@ -80,7 +83,7 @@ __device__ __forceinline__ void gram_body(const SegTable &T, int tiles_per_wg, l
   const int tid = threadIdx.x, lane = tid & 63;
   const int ld_row = tid >> 4, ld_chunk = tid & 15;   // loader: 16 lanes cover one 256-B row
 
-  f32x16 acc[3], sum[3], other[3];       // with FOLD the tiles before are in sum; other: APART, the odd ones
+  f32x16 acc[3], sum[3], other[3];       // with FOLD the tiles before are in sum; other: the odd ones, or the first half
 #pragma unroll
   for (int b = 0; b < 3; ++b)
 #pragma unroll
@@ -171,7 +174,7 @@ __device__ __forceinline__ void gram_body(const SegTable &T, int tiles_per_wg, l
   auto flush = [&](int lhead, int how, bool odd) {
     auto left = [&](int b, int v) {
       const float x = !FOLD ? acc[b][v] : FOLD == 1 || odd ? sum[b][v] : sum[b][v] + acc[b][v];
-      return APART ? other[b][v] + x : x;
+      return APART || HALVES ? other[b][v] + x : x;
     };
     float *out = how == TO_LDS ? park
                                : partials + ((size_t)blockIdx.x + lhead) * GRAM_PARTIAL_FLOATS;
@@ -211,6 +214,14 @@ __device__ __forceinline__ void gram_body(const SegTable &T, int tiles_per_wg, l
     cursor_next<GRAM_TILE>(T, C);
   };
 
+  auto next_half = [&] {
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+      other[b] = sum[b];
+      sum[b] = f32x16{};
+    }
+  };
+
   // AHEAD tiles of global loads stay in flight while another is being multiplied
   uint4 st[AHEAD][4];
 #pragma unroll
@@ -218,6 +229,7 @@ __device__ __forceinline__ void gram_body(const SegTable &T, int tiles_per_wg, l
   // (one way out of the loop, for the same reason)
   int t = 0;
   for (; t + 2 <= count; t += 2) {
+    if (HALVES && t == GRAM_HALF_RUN) next_half();
     store_tile(smem, st[0]);
     __syncthreads();
     load_tile(t + AHEAD, st[0]);
@@ -230,6 +242,7 @@ __device__ __forceinline__ void gram_body(const SegTable &T, int tiles_per_wg, l
     finish_tile(t + 2 == count, true);
   }
   if (t < count) {
+    if (HALVES && t == GRAM_HALF_RUN) next_half();
     store_tile(smem, st[0]);
     __syncthreads();
     compute_tile(smem, false);
@@ -272,7 +285,11 @@ __global__ __launch_bounds__(256, GRAM_OCC) void gram_kernel(const SegTable T, i
 hipError_t launch_gram(const SegTable &T, int nwg, int tiles_per_wg, GramKind kind, float *partials, hipStream_t st) {
   const long long total = total_tiles(T);
   if (total <= 0 || nwg <= 0) return hipSuccess;
-  const auto kernel = kind == GRAM_ONE ? gram_kernel<GRAM_ONE> : kind == GRAM_FOLD ? gram_kernel<GRAM_FOLD> : gram_kernel<GRAM_TWO>;
+  const auto kernel = kind == GRAM_ONE      ? gram_kernel<GRAM_ONE>
+                      : kind == GRAM_HALF   ? gram_kernel<GRAM_HALF>
+                      : kind == GRAM_HALVES ? gram_kernel<GRAM_HALVES>
+                      : kind == GRAM_FOLD   ? gram_kernel<GRAM_FOLD>
+                                            : gram_kernel<GRAM_TWO>;
   hipLaunchKernelGGL(kernel, dim3((unsigned)nwg), dim3(256), 0, st, T, tiles_per_wg, total, partials);
   return hipGetLastError();
 }

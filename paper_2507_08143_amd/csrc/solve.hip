@@ -56,32 +56,49 @@ __device__ __forceinline__ void upper_block_pos(int b, int &I, int &J) {
 // 34660, k_s = 48, 393 us and not 390, and eight heads no less.  Whole
 // scores on MI355X, us, k_s = 48, 8 heads of 3000 / 10000, 64 of 7000: 28.3 -> 27.4, 35.6 -> 34.2, 66.9 -> 65.4; exact mode, where
 // one load waited for the other, 8 heads of 3000 / 10000: 46.0 -> 44.6, 54.5 -> 49.7.
-template <int Q, int FLIGHT = 8>
-__device__ __forceinline__ void sum_quads(const float *__restrict__ src, int count, double (&g)[4 * Q]) {
+// HALVES: partial i is the fp32 sum of those at 2i and 2i + 1, as far as they lie within least .. most.
+template <int Q, int FLIGHT = 8, bool HALVES = false>
+__device__ __forceinline__ void sum_quads(const float *__restrict__ src, int count, double (&g)[4 * Q], int least = 0,
+                                          int most = 0) {
   constexpr int FEW = FLIGHT >= 8 ? 2 : 1;
-  typedef float4 Batch[FLIGHT][Q];
-  auto load = [&](int s0, Batch &v, auto n) {
+  struct Batch {
+    float4 v[FLIGHT][Q], w[HALVES ? FLIGHT : 1][Q];
+    bool two[FLIGHT];
+  };
+  auto load = [&](int s0, Batch &b, auto n) {
 #pragma unroll
-    for (int u = 0; u < decltype(n)::value; ++u)
+    for (int u = 0; u < decltype(n)::value; ++u) {
+      const int i = min(s0 + u, count - 1), lo = HALVES ? max(2 * i, least) : i, hi = HALVES ? min(2 * i + 1, most) : i;
+      b.two[u] = lo < hi;
 #pragma unroll
-      for (int q = 0; q < Q; ++q)
-        v[u][q] = *reinterpret_cast<const float4 *>(src + (long long)min(s0 + u, count - 1) * GRAM_PARTIAL_FLOATS + 512 * q);
+      for (int q = 0; q < Q; ++q) {
+        b.v[u][q] = *reinterpret_cast<const float4 *>(src + (long long)lo * GRAM_PARTIAL_FLOATS + 512 * q);
+        if constexpr (HALVES)
+          b.w[u][q] = *reinterpret_cast<const float4 *>(src + (long long)hi * GRAM_PARTIAL_FLOATS + 512 * q);
+      }
+    }
     __builtin_amdgcn_sched_barrier(0);
   };
-  auto add = [&](int u, const Batch &v) {
+  auto add = [&](int u, const Batch &b) {
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
-      g[4 * q] += v[u][q].x; g[4 * q + 1] += v[u][q].y; g[4 * q + 2] += v[u][q].z; g[4 * q + 3] += v[u][q].w;
+      float4 x = b.v[u][q];
+      if constexpr (HALVES) {
+        const float4 y = b.w[u][q];
+        const bool two = b.two[u];         // (no branch: what waits in it would be waited for apart)
+        x = make_float4(x.x + (two ? y.x : 0.f), x.y + (two ? y.y : 0.f), x.z + (two ? y.z : 0.f), x.w + (two ? y.w : 0.f));
+      }
+      g[4 * q] += x.x; g[4 * q + 1] += x.y; g[4 * q + 2] += x.z; g[4 * q + 3] += x.w;
     }
   };
-  auto add_all = [&](const Batch &v) {
+  auto add_all = [&](const Batch &b) {
 #pragma unroll
-    for (int u = 0; u < FLIGHT; ++u) add(u, v);
+    for (int u = 0; u < FLIGHT; ++u) add(u, b);
   };
-  auto add_some = [&](int n, const Batch &v) {
+  auto add_some = [&](int n, const Batch &b) {
 #pragma unroll
     for (int u = 0; u < FLIGHT; ++u)
-      if (u < n) add(u, v);                // uniform
+      if (u < n) add(u, b);                // uniform
   };
   const std::integral_constant<int, FLIGHT> all;
 #pragma unroll
@@ -117,9 +134,9 @@ __device__ __forceinline__ void sum_quads(const float *__restrict__ src, int cou
 // loads per partial and holds them as A operands of T = G^T Phi_I as they are (step (h, s) of the
 // contraction takes row 16h + 4lq + s of lane group lq); T's accumulators are the B operands of
 // Phi_J^T T.  Nothing of G or T passes through LDS.
-template <int M>
+template <int M, bool HALVES = false>
 __device__ __forceinline__ void sketch_share(const float *__restrict__ src, int count, int w,
-                                             const float *__restrict__ phi, double *ba, double *bb) {
+                                             const float *__restrict__ phi, double *ba, double *bb, int least = 0, int most = 0) {
   constexpr int CT = M / 16, SP = M + 1;
   const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lq = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -140,7 +157,7 @@ __device__ __forceinline__ void sketch_share(const float *__restrict__ src, int 
     for (int ct = 0; ct < CT; ++ct)
       pj[v][ct] = phi[(32 * J + 16 * half + 4 * v + lq) * M + 16 * ct + l16];
   double g[8];
-  sum_quads<2, 4>(p, count, g);
+  sum_quads<2, HALVES ? 2 : 4, HALVES>(p, count, g, least, most);
   f64x4 tacc[CT];
 #pragma unroll
   for (int ct = 0; ct < CT; ++ct) tacc[ct] = f64x4{0.0, 0.0, 0.0, 0.0};
@@ -195,7 +212,23 @@ __device__ __forceinline__ void split_part(int nsplit, int parts, int r, int &fi
 // other, 60 MFMAs (k_s = 48) a wave, two barriers: 7 to 10 us for 8 heads with 8 to 64 partials
 // each, where one workgroup per head took 34 (8 partials, 4-byte loads) to 185 us (64) for this
 // step.  At 256 heads (24 us) the fp64 matrix cores count, 1200 MFMAs of 64 clocks a head: see sketch_direct_kernel.
-template <int M>
+// The slot where the halves of a head's partial `first` are (of which pb is the first's), or would be, and which of the slots from
+// there on are the head's.
+struct HalfRuns {
+  long long slot;
+  int least, most;
+  __device__ __forceinline__ HalfRuns(const SegTable &T, int lhead, long long pb, int first) {
+    int count;
+    const long long mine = partial_base(T, lhead, GRAM_HALF_RUN, count);
+    slot = 2 * (pb - lhead + first) + lhead;
+    least = (int)(mine - slot);
+    most = least + count - 1;
+  }
+};
+
+// HALVES: the partials are those of workgroups of half a run (GRAM_HALF), numbered as such; they are paired, and the pairs dealt out
+// and added in their order, as the partials of whole runs are.
+template <int M, bool HALVES>
 __global__ __launch_bounds__(256, 2) void sketch_share_kernel(
     const SegTable T, int tiles_per_wg, int parts, const float *__restrict__ partials,
     const float *__restrict__ phi, double *__restrict__ shares, int32_t *__restrict__ status,
@@ -209,9 +242,14 @@ __global__ __launch_bounds__(256, 2) void sketch_share_kernel(
     status[T.s[at.seg].ghead0 + at.head] = 0;
   }
   int nsplit, first, count;
-  const long long pb = partial_base(T, lhead, tiles_per_wg, nsplit);
+  const long long pb = partial_base(T, lhead, HALVES ? 2 * GRAM_HALF_RUN : tiles_per_wg, nsplit);
   split_part(nsplit, parts, r, first, count);
-  sketch_share<M>(partials + (pb + first) * GRAM_PARTIAL_FLOATS, count, w, phi, ba, bb);
+  if constexpr (HALVES) {
+    const HalfRuns hr(T, lhead, pb, first);
+    sketch_share<M, true>(partials + hr.slot * GRAM_PARTIAL_FLOATS, count, w, phi, ba, bb, hr.least, hr.most);
+  } else {
+    sketch_share<M>(partials + (pb + first) * GRAM_PARTIAL_FLOATS, count, w, phi, ba, bb);
+  }
   zero_slice(zero, zero_ints);   // histograms that the score and selection kernels add into
   __syncthreads();
   double *out = shares + (long long)blockIdx.x * Share<M>::DOUBLES;
@@ -325,11 +363,11 @@ __device__ __forceinline__ void sketch_columns(const double (&g)[5][8], const fl
 }
 
 // (At M = 64 the accumulators of S take 128 registers, so one workgroup on a unit.)
-template <int M>
+template <int M, bool HALVES>
 __global__ __launch_bounds__(256, M > 48 ? 1 : 2) void sketch_direct_kernel(
     const SegTable T, int tiles_per_wg, const float *__restrict__ partials, const float *__restrict__ phi, float ridge_rel,
     uint16_t *__restrict__ wt, int32_t *__restrict__ status, int *__restrict__ zero, long long zero_ints) {
-  constexpr int CT = M / 16, SP = M + 1, PP = SketchFactor<M>::PP, FLIGHT = 2;
+  constexpr int CT = M / 16, SP = M + 1, PP = SketchFactor<M>::PP, FLIGHT = 2;      // partials, or both halves of one, at a time
   struct Sketch {
     double halves[2][M * SP];
     float PH[D * PP];
@@ -346,18 +384,25 @@ __global__ __launch_bounds__(256, M > 48 ? 1 : 2) void sketch_direct_kernel(
   PhiRegs<M> ph;
   ph.fetch(phi);
   int nsplit;
-  const long long pb = partial_base(T, lhead, tiles_per_wg, nsplit);
+  long long pb = partial_base(T, lhead, HALVES ? 2 * GRAM_HALF_RUN : tiles_per_wg, nsplit);
+  int least = 0, most = nsplit - 1;
+  if constexpr (HALVES) {
+    const HalfRuns hr(T, lhead, pb, 0);
+    pb = hr.slot;
+    least = hr.least;
+    most = hr.most;
+  }
   const float *p = partials + pb * GRAM_PARTIAL_FLOATS + (32 * lq + 16 * half + l16) * 4;
   double g[5][8];
 #pragma unroll
   for (int b = 0; b < 5; ++b)
 #pragma unroll
     for (int q = 0; q < 8; ++q) g[b][q] = 0.0;
-  for (int sp = 0; sp < nsplit; sp += FLIGHT) {
+  for (int sp = 0; sp <= most; sp += FLIGHT) {
     float4 a[FLIGHT][5], c[FLIGHT][5];
 #pragma unroll
     for (int u = 0; u < FLIGHT; ++u) {
-      const float *pu = p + (long long)min(sp + u, nsplit - 1) * GRAM_PARTIAL_FLOATS;
+      const float *pu = p + (long long)min(max(sp + u, least), most) * GRAM_PARTIAL_FLOATS;
 #pragma unroll
       for (int b = 0; b < 5; ++b) {      // stored blocks (0,0) (0,3) (1,3) (2,3) (3,3), or (0,1) (1,1) (0,2) (1,2) (2,2)
         constexpr int outer_at[5] = {0, 3, 6, 8, 9}, inner_at[5] = {1, 4, 2, 5, 7};
@@ -366,9 +411,18 @@ __global__ __launch_bounds__(256, M > 48 ? 1 : 2) void sketch_direct_kernel(
         c[u][b] = *reinterpret_cast<const float4 *>(pb4 + 512);
       }
     }
+    if constexpr (HALVES) {
+      if (sp >= least && sp < most) {    // uniform: both are the head's, else they are the same
 #pragma unroll
-    for (int u = 0; u < FLIGHT; ++u)
-      if (sp + u < nsplit) {             // uniform
+        for (int b = 0; b < 5; ++b) {
+          a[0][b] = make_float4(a[0][b].x + a[1][b].x, a[0][b].y + a[1][b].y, a[0][b].z + a[1][b].z, a[0][b].w + a[1][b].w);
+          c[0][b] = make_float4(c[0][b].x + c[1][b].x, c[0][b].y + c[1][b].y, c[0][b].z + c[1][b].z, c[0][b].w + c[1][b].w);
+        }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < (HALVES ? 1 : FLIGHT); ++u)
+      if (sp + u <= most) {              // uniform
 #pragma unroll
         for (int b = 0; b < 5; ++b) {
           g[b][0] += a[u][b].x; g[b][1] += a[u][b].y; g[b][2] += a[u][b].z; g[b][3] += a[u][b].w;
@@ -531,6 +585,7 @@ __global__ __launch_bounds__(EXACT_THREADS) void exact_solve_kernel(
 
 // Longest run of partials a share of its own takes before the head's partials are cut into parts:
 // a batch of eight is in flight at a time, about 1 us each.
+// (Where partials may come in halves, half as many: the halves are what is loaded.)
 constexpr int SHARE_SPLITS = 64, SHARE_PARTS_MAX = 8;
 
 // Above DIRECT_HEADS heads, none of them with more than k_s - 4 partials, sketch_direct_kernel forms and factors S.  Scores
@@ -546,7 +601,8 @@ constexpr int SHARE_SPLITS = 64, SHARE_PARTS_MAX = 8;
 // k_s = 64 106/101 (47), 183/179 (59).  128 heads, 8 of them longer, k_s = 16 44.7/55.9 (17), k_s = 48 49.8/59.6 (17).
 constexpr int DIRECT_HEADS = 128;
 
-SolvePlan solve_plan(const SegTable &T, int ks, int tiles_per_wg) {
+// most: partials that a head may have; splits: of a part.
+static SolvePlan plan_of(const SegTable &T, int ks, long long most, int splits) {
   SolvePlan p;
   p.parts = 1;
   p.nshares = 0;
@@ -555,30 +611,42 @@ SolvePlan solve_plan(const SegTable &T, int ks, int tiles_per_wg) {
     p.share_bytes = (size_t)T.nheads * 10 * 1024 * sizeof(double);
     return p;
   }
-  int most = 1;
-  for (int i = 0; i < T.nseg; ++i) {
-    const int splits = (tiles_of(T.s[i].n) + tiles_per_wg - 1) / tiles_per_wg + 1;
-    if (splits > most) most = splits;
-  }
   p.direct = T.nheads > DIRECT_HEADS && most <= ks - 4;
-  p.parts = (most + SHARE_SPLITS - 1) / SHARE_SPLITS;
-  if (p.parts > SHARE_PARTS_MAX) p.parts = SHARE_PARTS_MAX;
+  const long long parts = (most + splits - 1) / splits;
+  p.parts = parts > SHARE_PARTS_MAX ? SHARE_PARTS_MAX : (int)parts;
   const int P = ks / 16;
   p.nshares = p.parts * SHARE_BLOCKS;
   p.share_bytes = (size_t)T.nheads * p.nshares * (P * (P + 1) / 2 * 256) * sizeof(double);
   return p;
 }
 
+static int longest_head(const SegTable &T) {
+  int tiles = 0;
+  for (int i = 0; i < T.nseg; ++i)
+    if (tiles_of(T.s[i].n) > tiles) tiles = tiles_of(T.s[i].n);
+  return tiles;
+}
+
+SolvePlan solve_plan(const SegTable &T, int ks, int tiles_per_wg, bool halves) {
+  return plan_of(T, ks, (longest_head(T) + tiles_per_wg - 1) / tiles_per_wg + 1, halves ? SHARE_SPLITS / 2 : SHARE_SPLITS);
+}
+
+size_t share_bytes_most(const SegTable &T, int ks, int least_run, long long most_wgs, bool halves) {
+  const long long longest = longest_head(T), total = total_tiles(T);
+  const long long by_run = (longest + least_run - 1) / least_run, by_wgs = (most_wgs * longest + total - 1) / total;
+  return plan_of(T, ks, (by_run < by_wgs ? by_run : by_wgs) + 1, halves ? SHARE_SPLITS / 2 : SHARE_SPLITS).share_bytes;
+}
+
 template <int M>
 static hipError_t launch_sketched(const SegTable &T, int tiles_per_wg, const SolvePlan &plan,
-                                  const float *partials, double *shares, const float *phi,
+                                  const float *partials, bool halves, double *shares, const float *phi,
                                   float ridge_rel, uint16_t *wt, int32_t *status, int *zero,
                                   long long zero_ints, hipStream_t st) {
   if (plan.direct) {
-    hipLaunchKernelGGL((sketch_direct_kernel<M>), dim3((unsigned)T.nheads), dim3(256), 0, st, T, tiles_per_wg, partials, phi,
+    hipLaunchKernelGGL((halves ? sketch_direct_kernel<M, true> : sketch_direct_kernel<M, false>), dim3((unsigned)T.nheads), dim3(256), 0, st, T, tiles_per_wg, partials, phi,
                        ridge_rel, wt, status, zero, zero_ints);
   } else if (shares != nullptr) {
-    hipLaunchKernelGGL((sketch_share_kernel<M>), dim3((unsigned)(T.nheads * plan.parts * SHARE_BLOCKS)),
+    hipLaunchKernelGGL((halves ? sketch_share_kernel<M, true> : sketch_share_kernel<M, false>), dim3((unsigned)(T.nheads * plan.parts * SHARE_BLOCKS)),
                        dim3(256), 0, st, T, tiles_per_wg, plan.parts, partials, phi, shares,
                        wt == nullptr ? status : nullptr, zero, zero_ints);
     if (wt == nullptr) return hipGetLastError();
@@ -594,16 +662,17 @@ static hipError_t launch_sketched(const SegTable &T, int tiles_per_wg, const Sol
 
 // Sketched mode: partial Gram blocks -> W^T (see above); wt null: the shares only.
 hipError_t launch_sketch_solve(const SegTable &T, int ks, int tiles_per_wg, const SolvePlan &plan,
-                               const float *partials, double *shares, const float *phi,
+                               const float *partials, bool halves, double *shares, const float *phi,
                                float ridge_rel, uint16_t *wt, int32_t *status, int *zero,
                                long long zero_ints, hipStream_t st) {
   if (T.nheads <= 0) return hipSuccess;
   if ((shares == nullptr || plan.direct) && wt == nullptr) return hipErrorInvalidValue;
+  if (halves && shares == nullptr && !plan.direct) return hipErrorInvalidValue;
   switch (ks) {
-    case 16: return launch_sketched<16>(T, tiles_per_wg, plan, partials, shares, phi, ridge_rel, wt, status, zero, zero_ints, st);
-    case 32: return launch_sketched<32>(T, tiles_per_wg, plan, partials, shares, phi, ridge_rel, wt, status, zero, zero_ints, st);
-    case 48: return launch_sketched<48>(T, tiles_per_wg, plan, partials, shares, phi, ridge_rel, wt, status, zero, zero_ints, st);
-    case 64: return launch_sketched<64>(T, tiles_per_wg, plan, partials, shares, phi, ridge_rel, wt, status, zero, zero_ints, st);
+    case 16: return launch_sketched<16>(T, tiles_per_wg, plan, partials, halves, shares, phi, ridge_rel, wt, status, zero, zero_ints, st);
+    case 32: return launch_sketched<32>(T, tiles_per_wg, plan, partials, halves, shares, phi, ridge_rel, wt, status, zero, zero_ints, st);
+    case 48: return launch_sketched<48>(T, tiles_per_wg, plan, partials, halves, shares, phi, ridge_rel, wt, status, zero, zero_ints, st);
+    case 64: return launch_sketched<64>(T, tiles_per_wg, plan, partials, halves, shares, phi, ridge_rel, wt, status, zero, zero_ints, st);
     default: return hipErrorInvalidValue;
   }
 }

@@ -158,6 +158,42 @@ def test_many_short_heads_fit_the_static_scratch(B, heads, n, ks):
     assert _accepts(B, p, reqs, B.STATIC_SCRATCH_BYTES)
 
 
+def _size(B, p, reqs):
+    nbytes = C.c_size_t(0)
+    assert B._lib.compactor_workspace_size(C.byref(p), reqs, len(reqs), C.byref(nbytes)) == 0
+    return nbytes.value
+
+
+@pytest.mark.parametrize("heads,ks", [(1, 48), (1, 0), (3, 16), (8, 48), (64, 64), (128, 16), (160, 48), (256, 48), (300, 32), (700, 0)])
+@pytest.mark.parametrize("scope", [0, 1])
+def test_a_workspace_for_the_longest_context_takes_shorter_ones(B, heads, ks, scope):
+    """Half runs, the number of Gram workgroups and of their runs, parts of shares and score workgroups change with the length,
+    some of them downwards: no length may need more than is asked for at a greater one."""
+    p = B._Params(heads, 1, 128, ks, 0x2000, 1e-4, 0.3, 0, 0, 0, scope, None)
+    tiles = sorted(set(list(range(1, 20)) + [int(20 * 1.07 ** i) for i in range(80)] + [255, 256, 257, 511, 512, 513, 2047, 2048, 2049]))
+    shortest = []
+    for t in reversed(tiles):
+        n = 64 * t - (t % 5)
+        req = _req(B, n=n)
+        req.attn = 0x8000
+        reqs = (B._Request * 1)(req)
+        size = _size(B, p, reqs)
+        shortest.append(min([size] + shortest[-1:]))
+        for fused in (True, False):
+            assert _accepts(B, p, reqs, shortest[-1], fused), n
+
+
+@pytest.mark.parametrize("heads,n,ks", [(1, 64, 16), (8, 4096, 48), (1, 32768, 48), (256, 500, 48), (128, 256, 64)])
+def test_room_for_half_runs_is_not_demanded(B, heads, n, ks):
+    """Runs of 8 tiles, a partial Gram matrix of 10 blocks of 32 x 32 floats for every run and head, two bf16 planes of W^T, a
+    histogram of 4096 ints and the scores are enough."""
+    p = B._Params(1, heads, 128, ks, 0x2000, 0.0, 0.3, 0, 0, 0, 0, None)
+    runs = -(-heads * -(-n // 64) // 8)
+    nbytes = 40960 * (runs + heads) + heads * (2 * 2 * 128 * ks + 4 * 4096 + 4 * n)
+    assert _accepts(B, p, (B._Request * 1)(_req(B, n=n)), nbytes + 256)
+    assert not _accepts(B, p, (B._Request * 1)(_req(B, n=n)), nbytes - 256)
+
+
 def test_widened_entry_points_check_their_arguments_on_the_host(B):
     good = B._Params(2, 2, 128, 48, 0x2000, 0.0, 0.3, 0, 0, 0, 0, None)
     reqs = (B._Request * 1)(_req(B, n=100, ratio=0.5))

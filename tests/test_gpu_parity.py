@@ -544,6 +544,35 @@ def test_factorisation_with_and_without_shares(C, ks, n, gram_wgs):
     _say("  workspace %d of %d bytes; max rel err %.3g" % (hi, full, stats["max_rel"]))
 
 
+# Small sketched calls: with room two Gram workgroups share a run of 8 tiles, 4 each, and what they leave is joined; without, one
+# takes both halves.  A head inside one half, at the edges of halves and runs, across several, three heads that begin and end inside
+# runs, three parts of pairs of partials, a workgroup for every head; 512 tiles is the most
+@pytest.mark.parametrize("ks,H,n", [(16, 1, 64), (48, 1, 256), (48, 1, 257), (32, 1, 512), (16, 1, 513), (32, 3, 700), (64, 5, 321),
+                                    (48, 7, 1100), (16, 1, 32768), (48, 128, 256), (16, 136, 192), (32, 200, 100),
+                                    (64, 256, 128)])
+def test_half_runs_with_and_without_room(C, ks, H, n):
+    w = W.config1(DEV, L=1, H=H, n=n)
+    w.sketch_dim = ks
+    stats, _ = U.run_and_check(C, w, DEV, heads=[(0, 0, 0), (0, 0, H - 1)])
+    params, reqs = U.make_call(C, w, DEV)
+    full = C.compactor_workspace_size(params, reqs)
+    ws = torch.full((full,), 0xff, dtype=torch.uint8, device=DEV)                            # NaN
+    want, st = C.compactor_score(params, reqs, workspace=ws)
+    want = want.clone()
+    taken = 0
+    for part in range(31, 0, -1):
+        room = full * part // 32 // 256 * 256
+        ws.fill_(0xff)
+        try:
+            got, _ = C.compactor_score(params, reqs, workspace=ws[:room])
+        except C.CompactorError:
+            break
+        taken += 1
+        assert torch.equal(got.view(torch.int32), want.view(torch.int32)), room
+    assert taken > 4                      # the half runs are more than an eighth of it
+    _say("  k_s = %d, %d heads of %d: max rel err %.3g, %d smaller workspaces" % (ks, H, n, stats["max_rel"], taken))
+
+
 # The partials of a head are added in batches of four (exact mode: eight; two where one workgroup of an exact head adds them
 # itself, above 96 heads), two batches in turn, one or two left over by themselves; one tile of 64 rows a partial here
 @pytest.mark.parametrize("ks,L,partials", [(16, 1, p) for p in (1, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 16, 17, 18, 19, 24, 33)] +
