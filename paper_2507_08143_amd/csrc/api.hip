@@ -191,6 +191,9 @@ size_t partial_bytes(const SegTable &T, long long wgs) {
   return align_up((size_t)(wgs + T.nheads) * GRAM_PARTIAL_FLOATS * sizeof(float));
 }
 
+// Heads up to which there are shares (see below).
+int share_heads(int ks, int cus) { return ks > 0 ? cus : 3 * cus / 8; }
+
 GroupBytes group_bytes_needed(const compactor_params_t *p, const SegTable &T, bool need_scores) {
   const int ks = p->sketch_dim;
   long long rows = 0;
@@ -210,11 +213,9 @@ GroupBytes group_bytes_needed(const compactor_params_t *p, const SegTable &T, bo
   // and in exact mode 41.8/45.8 at 64 heads of 4096, 42.5/43.4 at 96, 42.9/41.2 at 128; k_s = 48, one head
   // of n = 131072, which brings 64 partials: 27 against 210.  At 2048 heads and more k_s = 32 and 48 would
   // be 4 to 9 % of this stage faster with shares, for 60 KB of scratch a head: the stage is 2 % of such calls.
-  // (Figures of sketched mode from before sketch_direct_kernel, which takes most calls of more than 128 heads now; their
-  // room stays, since it is the lengths of a call that decide.)
-  const int most_heads = ks > 0 ? cus : 3 * cus / 8;
+  // (Figures of sketched mode from before sketch_direct_kernel, which takes most calls of more than 128 heads now, without shares.)
   const SolvePlan plan = solve_plan(T, ks, gp.tiles_per_wg, gp.half_wgs > 0);
-  g.shares = T.nheads <= most_heads ? align_up(plan.share_bytes) : 0;
+  g.shares = T.nheads <= share_heads(ks, cus) && !plan.direct ? align_up(plan.share_bytes) : 0;
   g.wt = align_up((size_t)T.nheads * W_TERMS * m * D * sizeof(uint16_t));
   g.hist1 = align_up((size_t)T.nheads * HIST1_BINS * sizeof(int));
   g.sel = select_needs_pools(T) ? align_up((size_t)select_scratch(T).ints() * sizeof(int)) : 0;
@@ -231,7 +232,7 @@ GroupBytes group_bytes_needed(const compactor_params_t *p, const SegTable &T, bo
 // What compactor_workspace_size counts.  A workspace is often asked for at the greatest lengths and used for shorter ones, which
 // may need more of something: runs are whole tiles (one head of 2048 tiles has 256 of them, of 2049 228), small calls have half runs,
 // and the workgroups of a score launch change with the lengths.  So this holds any call of the same heads at lengths of the same
-// proportions.
+// proportions (and shares, where only other proportions lead to them).
 size_t bytes_asked(const compactor_params_t *p, const SegTable &T, bool need_scores) {
   const GroupBytes g = group_bytes_needed(p, T, need_scores);
   const long long cus = compute_units(), total = total_tiles(T);
@@ -239,7 +240,7 @@ size_t bytes_asked(const compactor_params_t *p, const SegTable &T, bool need_sco
   const int least_run = p->gram_wgs > 0 ? 1 : 2 * GRAM_HALF_RUN;
   auto runs = [&](int tiles, long long most) { return std::min((total + tiles - 1) / tiles, most); };
   auto shares = [&](long long wgs, bool halves) {
-    return g.shares > 0 ? align_up(share_bytes_most(T, p->sketch_dim, least_run, wgs, halves)) : 0;
+    return T.nheads <= share_heads(p->sketch_dim, (int)cus) ? align_up(share_bytes_most(T, p->sketch_dim, least_run, wgs, halves)) : 0;
   };
   size_t rest = g.total() - g.partials;
   if (g.bstat > 0) {

@@ -386,7 +386,7 @@ struct SolvePlan {
 };
 SolvePlan solve_plan(const SegTable &T, int ks, int tiles_per_wg, bool halves);       // halves: GramPlan::half_wgs > 0
 // The most share_bytes that T's heads may want at lengths of the same proportions and at most theirs, in runs of at least
-// least_run tiles and with at most most_wgs Gram workgroups.
+// least_run tiles and with at most most_wgs Gram workgroups; none where no lengths up to theirs lead to shares.
 size_t share_bytes_most(const SegTable &T, int ks, int least_run, long long most_wgs, bool halves);
 
 // Exact mode: G + rho I -> Cholesky -> W^T = L^{-1}.

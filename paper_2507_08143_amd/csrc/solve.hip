@@ -634,6 +634,7 @@ SolvePlan solve_plan(const SegTable &T, int ks, int tiles_per_wg, bool halves) {
 size_t share_bytes_most(const SegTable &T, int ks, int least_run, long long most_wgs, bool halves) {
   const long long longest = longest_head(T), total = total_tiles(T);
   const long long by_run = (longest + least_run - 1) / least_run, by_wgs = (most_wgs * longest + total - 1) / total;
+  if (plan_of(T, ks, by_run + 1, SHARE_SPLITS).direct) return 0;       // whatever the proportions
   return plan_of(T, ks, (by_run < by_wgs ? by_run : by_wgs) + 1, halves ? SHARE_SPLITS / 2 : SHARE_SPLITS).share_bytes;
 }
 

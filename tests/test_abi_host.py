@@ -194,6 +194,16 @@ def test_room_for_half_runs_is_not_demanded(B, heads, n, ks):
     assert not _accepts(B, p, (B._Request * 1)(_req(B, n=n)), nbytes - 256)
 
 
+@pytest.mark.parametrize("heads,n,ks", [(256, 1000, 48), (129, 5000, 16), (200, 20000, 48)])
+def test_no_shares_are_asked_for_where_none_are_used(B, heads, n, ks):
+    """Above 128 heads whose partials are few at any length up to n: partials of one run or two a unit, or of shorter calls' runs
+    and half runs, W^T, histograms and scores."""
+    p = B._Params(1, heads, 128, ks, 0x2000, 0.0, 0.3, 0, 0, 0, 0, None)
+    tiles = heads * -(-n // 64)
+    partials = max(min(-(-tiles // 8), 256 if tiles < 112 * 256 else 512) + heads, 64 + 128 + 2 * heads)
+    assert _size(B, p, (B._Request * 1)(_req(B, n=n))) <= 40960 * partials + heads * (2 * 2 * 128 * ks + 4 * 4096 + 4 * n) + 1024
+
+
 def test_widened_entry_points_check_their_arguments_on_the_host(B):
     good = B._Params(2, 2, 128, 48, 0x2000, 0.0, 0.3, 0, 0, 0, 0, None)
     reqs = (B._Request * 1)(_req(B, n=100, ratio=0.5))
