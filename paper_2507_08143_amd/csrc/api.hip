@@ -89,15 +89,44 @@ int compute_units() {
 // of 1024 (16) 57.3 / 57.8 / 60.3, 2048 (32) 75.3 / 76.0 / 79.5, 4096 (64) 113 / 113 / 117, 8192 (128) 195 / 198 / 199.  Exact mode: 8 of
 // 65536 (32) 88.8 / 89.9 / 99.6, 131072 (64) 127 / 129 / 138; 32 of 18000 (35) 92 / 94 / 97, 57000 (111) 186 / 188 / 191; 256 of 4096 (64)
 // 126 / 126 / 128, 8192 (128) 206 / 211 / 210.
+// Heads for every unit that end inside runs: one workgroup waits for every partial but two of its run to leave, where two take turns, so
+// two it is unless they leave more.  us with one / two, k_s = 16: 304 of 500 (partials 487 / 304) 41.6 / 33.9, 768 of 200 (768 / 768)
+// 48.7 / 46.8, 1024 of 1000 (1024 / 1024) 129 / 120, 512 of 2048 (512 / 512) 108 / 102; 512 of 300 (512 / 768) 41.5 / 43.7, 256 of 1000
+// (256 / 512) 37.9 / 44.5, 384 of 4096 (638 / 512) 151 / 151, k_s = 48 182 / 183.  Up to 8 tiles a unit they are the same
+// workgroups, 400 of 300 38.4 / 40.0, 1024 of 64 36.1 / 36.5.
 // (Folding then meant two tiles at a time into one sum; a tile at a time into two takes up to 1 % longer: 8 of 131072 104 -> 105, exact
 // mode 128.5 -> 130; 32 of 40000 128.5 -> 131, 152.6 -> 154.4.  And two workgroups had two tiles each under way.)
 // half_wgs: not 0 where two workgroups may share a run of 8 tiles, and how many there are then.
 struct GramPlan { int nwg, tiles_per_wg; GramKind kind; int half_wgs; };
+// Tiles a workgroup: even shares, not below 8 (512 rows), since every partial costs a 40 KB round trip.
+int run_of(long long total, int wgs) { return (int)std::max((total + wgs - 1) / wgs, 2ll * GRAM_HALF_RUN); }
+
+// Partials that workgroups of `run` tiles leave: one for every head and every workgroup, less where both begin with the same tile.
+long long partials_left(const SegTable &T, int run) {
+  const long long total = total_tiles(T);
+  long long pieces = T.nheads + (total + run - 1) / run, first = 0;
+  for (int i = 0; i < T.nseg; ++i) {
+    const int tph = tiles_of(T.s[i].n), heads = T.s[i].head_count, step = tph % run;
+    int at = (int)(first % run), cycle = 0, rest = 0;      // the place in a run where a head begins comes again after `run` heads
+    for (int h = 0; h < std::min(heads, run); ++h) {
+      cycle += at == 0;
+      rest += at == 0 && h < heads % run;
+      at = at + step < run ? at + step : at + step - run;
+    }
+    pieces -= (long long)(heads / run) * cycle + rest;
+    first += (long long)tph * heads;
+  }
+  return pieces;
+}
+
 GramPlan gram_plan(const compactor_params_t *p, const SegTable &T, int cus) {
   const long long total = total_tiles(T);
   const bool exact = p->sketch_dim == 0;
   const int plain_most = T.nheads <= 16 ? (exact ? 32 : 24) : T.nheads <= 32 ? (exact ? 32 : 16) : 0;
-  const bool one = total < 112ll * cus, plain = total >= 8ll * cus && total < (long long)plain_most * cus;
+  const bool plain = total >= 8ll * cus && total < (long long)plain_most * cus;
+  bool one = total < 112ll * cus;
+  if (one && T.nheads >= cus && total > 8ll * cus && p->gram_wgs <= 0)
+    one = partials_left(T, run_of(total, 2 * cus)) > partials_left(T, run_of(total, cus));
   GramPlan g;
   long long want = p->gram_wgs > 0 ? p->gram_wgs : (one ? 1ll : 2ll) * cus;
   if (want > total) want = total;
@@ -236,7 +265,7 @@ GroupBytes group_bytes_needed(const compactor_params_t *p, const SegTable &T, bo
 size_t bytes_asked(const compactor_params_t *p, const SegTable &T, bool need_scores) {
   const GroupBytes g = group_bytes_needed(p, T, need_scores);
   const long long cus = compute_units(), total = total_tiles(T);
-  const long long most_wgs = p->gram_wgs > 0 ? p->gram_wgs : total < 112 * cus ? cus : 2 * cus;
+  const long long most_wgs = p->gram_wgs > 0 ? p->gram_wgs : total < 112 * cus && T.nheads < cus ? cus : 2 * cus;
   const int least_run = p->gram_wgs > 0 ? 1 : 2 * GRAM_HALF_RUN;
   auto runs = [&](int tiles, long long most) { return std::min((total + tiles - 1) / tiles, most); };
   auto shares = [&](long long wgs, bool halves) {

@@ -194,13 +194,37 @@ def test_room_for_half_runs_is_not_demanded(B, heads, n, ks):
     assert not _accepts(B, p, (B._Request * 1)(_req(B, n=n)), nbytes - 256)
 
 
+def _pieces(lengths, run):
+    """(workgroup, head) pairs that share a tile, runs of `run` tiles."""
+    at, pieces = 0, 0
+    for t in (-(-n // 64) for n in lengths):
+        pieces += (at + t - 1) // run - at // run + 1
+        at += t
+    return pieces
+
+
+@pytest.mark.parametrize("lengths,heads", [([500], 304), ([300], 512), ([1000], 256), ([1000], 1024), ([200], 768), ([4096], 384), ([5000], 300),
+                                           ([600, 130, 2000], 160), ([64, 900, 64, 1500, 320], 96), ([5000, 65], 256)])
+def test_two_gram_workgroups_a_unit_where_they_leave_no_more_partials(B, lengths, heads):
+    """From a head a unit on, more than 8 and less than 112 tiles a unit.  What a call demands tells how many workgroups it has."""
+    p = B._Params(1, heads, 128, 16, 0x2000, 0.0, 0.3, 0, 0, 0, 0, None)
+    reqs = (B._Request * len(lengths))(*[_req(B, n=n) for n in lengths])
+    per_head = [n for n in lengths for _ in range(heads)]
+    total = sum(-(-n // 64) for n in per_head)
+    assert len(per_head) >= 256 and 8 * 256 < total < 112 * 256
+    one, two = (max(8, -(-total // w)) for w in (256, 512))
+    run = two if _pieces(per_head, two) <= _pieces(per_head, one) else one
+    nbytes = 40960 * (-(-total // run) + len(per_head)) + len(per_head) * (2 * 2 * 128 * 16 + 4 * 4096) + 4 * sum(per_head)
+    assert _accepts(B, p, reqs, nbytes + 256 * len(lengths)) and not _accepts(B, p, reqs, nbytes - 256)
+
+
 @pytest.mark.parametrize("heads,n,ks", [(256, 1000, 48), (129, 5000, 16), (200, 20000, 48)])
 def test_no_shares_are_asked_for_where_none_are_used(B, heads, n, ks):
     """Above 128 heads whose partials are few at any length up to n: partials of one run or two a unit, or of shorter calls' runs
     and half runs, W^T, histograms and scores."""
     p = B._Params(1, heads, 128, ks, 0x2000, 0.0, 0.3, 0, 0, 0, 0, None)
     tiles = heads * -(-n // 64)
-    partials = max(min(-(-tiles // 8), 256 if tiles < 112 * 256 else 512) + heads, 64 + 128 + 2 * heads)
+    partials = max(min(-(-tiles // 8), 256 if tiles < 112 * 256 and heads < 256 else 512) + heads, 64 + 128 + 2 * heads)
     assert _size(B, p, (B._Request * 1)(_req(B, n=n))) <= 40960 * partials + heads * (2 * 2 * 128 * ks + 4 * 4096 + 4 * n) + 1024
 
 

@@ -438,10 +438,12 @@ def test_gram_partitions_that_cross_heads(C, gram_wgs):
     _say("  max rel err %.3g, swaps %d" % (st["max_rel"], st["swaps"]))
 
 
-@pytest.mark.parametrize("L,H,n,gram_wgs", [(32, 8, 100, 0), (17, 15, 100, 0), (24, 12, 129, 0), (32, 9, 60, 3)])
+@pytest.mark.parametrize("L,H,n,gram_wgs", [(32, 8, 100, 0), (17, 15, 100, 0), (24, 12, 129, 0), (32, 9, 60, 3), (38, 8, 449, 0),
+                                            (32, 8, 700, 0)])
 def test_gram_of_many_short_heads(C, L, H, n, gram_wgs):
-    """From 256 heads on plain workgroups, below pairs: 8 tiles hold four heads (the first one's partial waits in LDS, two
-    are written mid-run, the last at the end), or begin and end inside a head; 96 heads in a row."""
+    """4 or 8 tiles hold two or four heads (the first one's partial waits in LDS, two are written mid-run, the last at the
+    end), or begin and end inside a head; 96 heads in a row; with a head a unit or more two workgroups a unit of a head
+    each, and one of 11 tiles."""
     _say("%d heads of %d tokens" % (L * H, n))
     st, _ = U.run_and_check(C, W.config2(DEV, L=L, H=H, n=n), DEV, tune={"gram_wgs": gram_wgs})
     _say("  max rel err %.3g, swaps %d" % (st["max_rel"], st["swaps"]))
