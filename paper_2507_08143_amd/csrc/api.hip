@@ -200,7 +200,16 @@ int score_tokens_for(const compactor_params_t *p, const SegTable &T, int cus) {
   return best;
 }
 
+SolvePlan solve_plan_for(const compactor_params_t *p, const SegTable &T, const GramPlan &gp, int cus) {
+  const bool in_score = p->sketch_dim > 0 && T.nheads > DIRECT_HEADS && T.nheads <= cus &&
+                        score_solves(T, p->sketch_dim, score_tokens_for(p, T, cus), cus);
+  return solve_plan(T, p->sketch_dim, gp.tiles_per_wg, gp.half_wgs > 0, in_score, cus);
+}
+
+// What a group's launches are, and the bytes of workspace that they need.
 struct GroupBytes {
+  GramPlan gram;
+  SolvePlan solve;
   size_t partials, wt, hist1, sel, bstat, scores;   // in this order in the workspace
   size_t shares, halves; // and, where the workspace has room for one or both, scratch that speeds up the factorisation, and
                          // partials of half runs (the results do not depend on them)
@@ -229,9 +238,10 @@ GroupBytes group_bytes_needed(const compactor_params_t *p, const SegTable &T, bo
   for (int i = 0; i < T.nseg; ++i) rows += (long long)T.s[i].n * T.s[i].head_count;
   const int m = ks > 0 ? ks : D;
   const int cus = compute_units();
-  const GramPlan gp = gram_plan(p, T, cus);
   GroupBytes g;
-  g.partials = partial_bytes(T, gp.nwg);
+  g.gram = gram_plan(p, T, cus);
+  g.solve = solve_plan_for(p, T, g.gram, cus);
+  g.partials = partial_bytes(T, g.gram.nwg);
   // Many workgroups per head form S = Phi^T G Phi (exact mode: G) only where the heads alone do not fill
   // the chip.  Factorisation stage on MI355X, us with / without shares, n = 2048:
   //   heads         8           64          128         256         512         1024       2048       4096
@@ -243,8 +253,7 @@ GroupBytes group_bytes_needed(const compactor_params_t *p, const SegTable &T, bo
   // of n = 131072, which brings 64 partials: 27 against 210.  At 2048 heads and more k_s = 32 and 48 would
   // be 4 to 9 % of this stage faster with shares, for 60 KB of scratch a head: the stage is 2 % of such calls.
   // (Figures of sketched mode from before sketch_direct_kernel, which takes most calls of more than 128 heads now, without shares.)
-  const SolvePlan plan = solve_plan(T, ks, gp.tiles_per_wg, gp.half_wgs > 0);
-  g.shares = T.nheads <= share_heads(ks, cus) && !plan.direct ? align_up(plan.share_bytes) : 0;
+  g.shares = T.nheads <= share_heads(ks, cus) && !g.solve.direct ? align_up(g.solve.share_bytes) : 0;
   g.wt = align_up((size_t)T.nheads * W_TERMS * m * D * sizeof(uint16_t));
   g.hist1 = align_up((size_t)T.nheads * HIST1_BINS * sizeof(int));
   g.sel = select_needs_pools(T) ? align_up((size_t)select_scratch(T).ints() * sizeof(int)) : 0;
@@ -254,7 +263,7 @@ GroupBytes group_bytes_needed(const compactor_params_t *p, const SegTable &T, bo
     g.bstat = align_up((size_t)total_blocks(T, score_tokens_for(p, T, compute_units()), SCORE_STEP, false) *
                        4 * sizeof(double));
   g.scores = need_scores ? align_up((size_t)rows * sizeof(float)) : 0;
-  g.halves = gp.half_wgs > 0 && (g.shares > 0 || plan.direct) ? partial_bytes(T, gp.half_wgs) : 0;
+  g.halves = g.gram.half_wgs > 0 && (g.shares > 0 || g.solve.direct) ? partial_bytes(T, g.gram.half_wgs) : 0;
   return g;
 }
 
@@ -269,7 +278,8 @@ size_t bytes_asked(const compactor_params_t *p, const SegTable &T, bool need_sco
   const int least_run = p->gram_wgs > 0 ? 1 : 2 * GRAM_HALF_RUN;
   auto runs = [&](int tiles, long long most) { return std::min((total + tiles - 1) / tiles, most); };
   auto shares = [&](long long wgs, bool halves) {
-    return T.nheads <= share_heads(p->sketch_dim, (int)cus) ? align_up(share_bytes_most(T, p->sketch_dim, least_run, wgs, halves)) : 0;
+    if (T.nheads > share_heads(p->sketch_dim, (int)cus)) return (size_t)0;
+    return align_up(share_bytes_most(T, p->sketch_dim, least_run, wgs, halves, (int)cus));
   };
   size_t rest = g.total() - g.partials;
   if (g.bstat > 0) {
@@ -399,7 +409,8 @@ int enqueue_score(const compactor_params_t *p, const SegTable &T, const GroupByt
   int *zero = hist1;
   const long long zero_ints = hist1 ? (long long)T.nheads * HIST1_BINS : 0;
   const int cus = compute_units();
-  const GramPlan gp = gram_plan(p, T, cus);
+  const GramPlan &gp = gb.gram;
+  const SolvePlan &plan = gb.solve;
   const int rpw = gp.tiles_per_wg;
   const Marks m{p->stage_events, st};
   MARK(m, 0);
@@ -415,7 +426,6 @@ int enqueue_score(const compactor_params_t *p, const SegTable &T, const GroupByt
   MARK(m, COMPACTOR_STAGE_GRAM + 1);
   MARK(m, COMPACTOR_STAGE_REDUCE + 1);       // the fp64 sum of the partials is part of the next kernel
   const int score_tokens = score_tokens_for(p, T, cus);
-  const SolvePlan plan = solve_plan(T, p->sketch_dim, rpw, gp.half_wgs > 0);
   const bool in_score = shares != nullptr && !plan.direct && score_solves(T, p->sketch_dim, score_tokens, cus);
   if (p->sketch_dim > 0) {
     HIP_TRY(launch_sketch_solve(T, p->sketch_dim, rpw, plan, partials, halves, shares, p->phi, p->ridge_rel,

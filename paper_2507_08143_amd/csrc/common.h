@@ -340,24 +340,28 @@ inline long long total_tiles(const SegTable &T) {
   return t;
 }
 
-// First partial slot of launch-local head `lhead` and the number of consecutive slots (one per
-// workgroup that touched the head).
-__device__ __forceinline__ long long partial_base(const SegTable &T, int lhead, int tiles_per_wg,
-                                                  int &nsplit) {
+// First tile of launch-local head `lhead`, and how many it has.
+__device__ __forceinline__ long long head_tiles(const SegTable &T, int lhead, int &tph) {
   long long base = 0;
   for (int i = 0; i < T.nseg; ++i) {
-    const int tph = tiles_of(T.s[i].n);
+    tph = tiles_of(T.s[i].n);
     const int hh = lhead - T.s[i].lhead0;
-    if (hh < T.s[i].head_count || i == T.nseg - 1) {
-      const long long t0 = base + (long long)hh * tph;        // first tile of the head
-      const long long first = quotient(t0, tiles_per_wg), last = quotient(t0 + tph - 1, tiles_per_wg);
-      nsplit = (int)(last - first + 1);
-      return first + lhead;
-    }
+    if (hh < T.s[i].head_count || i == T.nseg - 1) return base + (long long)hh * tph;
     base += (long long)tph * T.s[i].head_count;
   }
-  nsplit = 0;
   return 0;
+}
+
+// First partial slot of a head and the number of consecutive slots (one per workgroup that touched the head).
+__device__ __forceinline__ long long partial_base(long long t0, int tph, int lhead, int tiles_per_wg, int &nsplit) {
+  const long long first = quotient(t0, tiles_per_wg), last = quotient(t0 + tph - 1, tiles_per_wg);
+  nsplit = (int)(last - first + 1);
+  return first + lhead;
+}
+__device__ __forceinline__ long long partial_base(const SegTable &T, int lhead, int tiles_per_wg, int &nsplit) {
+  int tph = 0;
+  const long long t0 = head_tiles(T, lhead, tph);
+  return partial_base(t0, tph, lhead, tiles_per_wg, nsplit);
 }
 
 // ---- host-side launchers (one per translation unit) -------------------------------------
@@ -384,10 +388,12 @@ struct SolvePlan {
   int nshares;           // shares of a head (sketched mode)
   size_t share_bytes;
 };
-SolvePlan solve_plan(const SegTable &T, int ks, int tiles_per_wg, bool halves);       // halves: GramPlan::half_wgs > 0
+// halves: GramPlan::half_wgs > 0; in_score: with shares score_solves() would hold (only asked for between DIRECT_HEADS and cus heads).
+constexpr int DIRECT_HEADS = 128;
+SolvePlan solve_plan(const SegTable &T, int ks, int tiles_per_wg, bool halves, bool in_score, int cus);
 // The most share_bytes that T's heads may want at lengths of the same proportions and at most theirs, in runs of at least
 // least_run tiles and with at most most_wgs Gram workgroups; none where no lengths up to theirs lead to shares.
-size_t share_bytes_most(const SegTable &T, int ks, int least_run, long long most_wgs, bool halves);
+size_t share_bytes_most(const SegTable &T, int ks, int least_run, long long most_wgs, bool halves, int cus);
 
 // Exact mode: G + rho I -> Cholesky -> W^T = L^{-1}.
 hipError_t launch_exact_solve(const SegTable &T, int tiles_per_wg, const float *partials,

@@ -7,6 +7,8 @@
 // so that the score of a token is o_i = || W^T k_i ||^2 = k^_i^T S^{-1} k^_i, which equals
 // diag(U~ U~^T) of Algorithm 1 lines 5-6 when rho = 0.  All arithmetic here is fp64; W^T leaves
 // as a sum of bf16 planes for the MFMA score pass.
+#include <algorithm>
+
 #include "factor.h"
 
 namespace cmp {
@@ -217,9 +219,9 @@ __device__ __forceinline__ void split_part(int nsplit, int parts, int r, int &fi
 struct HalfRuns {
   long long slot;
   int least, most;
-  __device__ __forceinline__ HalfRuns(const SegTable &T, int lhead, long long pb, int first) {
+  __device__ __forceinline__ HalfRuns(long long t0, int tph, int lhead, long long pb, int first) {
     int count;
-    const long long mine = partial_base(T, lhead, GRAM_HALF_RUN, count);
+    const long long mine = partial_base(t0, tph, lhead, GRAM_HALF_RUN, count);
     slot = 2 * (pb - lhead + first) + lhead;
     least = (int)(mine - slot);
     most = least + count - 1;
@@ -241,11 +243,12 @@ __global__ __launch_bounds__(256, 2) void sketch_share_kernel(
     const Where at = locate_head(T, lhead);
     status[T.s[at.seg].ghead0 + at.head] = 0;
   }
-  int nsplit, first, count;
-  const long long pb = partial_base(T, lhead, HALVES ? 2 * GRAM_HALF_RUN : tiles_per_wg, nsplit);
+  int tph = 0, nsplit, first, count;
+  const long long t0 = head_tiles(T, lhead, tph);
+  const long long pb = partial_base(t0, tph, lhead, HALVES ? 2 * GRAM_HALF_RUN : tiles_per_wg, nsplit);
   split_part(nsplit, parts, r, first, count);
   if constexpr (HALVES) {
-    const HalfRuns hr(T, lhead, pb, first);
+    const HalfRuns hr(t0, tph, lhead, pb, first);
     sketch_share<M, true>(partials + hr.slot * GRAM_PARTIAL_FLOATS, count, w, phi, ba, bb, hr.least, hr.most);
   } else {
     sketch_share<M>(partials + (pb + first) * GRAM_PARTIAL_FLOATS, count, w, phi, ba, bb);
@@ -383,11 +386,12 @@ __global__ __launch_bounds__(256, M > 48 ? 1 : 2) void sketch_direct_kernel(
 
   PhiRegs<M> ph;
   ph.fetch(phi);
-  int nsplit;
-  long long pb = partial_base(T, lhead, HALVES ? 2 * GRAM_HALF_RUN : tiles_per_wg, nsplit);
+  int tph = 0, nsplit;
+  const long long t0 = head_tiles(T, lhead, tph);
+  long long pb = partial_base(t0, tph, lhead, HALVES ? 2 * GRAM_HALF_RUN : tiles_per_wg, nsplit);
   int least = 0, most = nsplit - 1;
   if constexpr (HALVES) {
-    const HalfRuns hr(T, lhead, pb, 0);
+    const HalfRuns hr(t0, tph, lhead, pb, 0);
     pb = hr.slot;
     least = hr.least;
     most = hr.most;
@@ -402,7 +406,7 @@ __global__ __launch_bounds__(256, M > 48 ? 1 : 2) void sketch_direct_kernel(
     float4 a[FLIGHT][5], c[FLIGHT][5];
 #pragma unroll
     for (int u = 0; u < FLIGHT; ++u) {
-      const float *pu = p + (long long)min(max(sp + u, least), most) * GRAM_PARTIAL_FLOATS;
+      const float *pu = p + (long long)min(HALVES ? max(sp + u, least) : sp + u, most) * GRAM_PARTIAL_FLOATS;
 #pragma unroll
       for (int b = 0; b < 5; ++b) {      // stored blocks (0,0) (0,3) (1,3) (2,3) (3,3), or (0,1) (1,1) (0,2) (1,2) (2,2)
         constexpr int outer_at[5] = {0, 3, 6, 8, 9}, inner_at[5] = {1, 4, 2, 5, 7};
@@ -588,21 +592,30 @@ __global__ __launch_bounds__(EXACT_THREADS) void exact_solve_kernel(
 // (Where partials may come in halves, half as many: the halves are what is loaded.)
 constexpr int SHARE_SPLITS = 64, SHARE_PARTS_MAX = 8;
 
-// Above DIRECT_HEADS heads, none of them with more than k_s - 4 partials, sketch_direct_kernel forms and factors S.  Scores
-// alone on MI355X, us with shares (or, above a head a unit, with the shares of a head one after the other) / direct:
-//   heads x n  112x2048   128x2048   128x8192    160x2048   256x2048  304x2048   1024x1000  2048x500
-//   k_s = 16   39.4/42.6  40.2/41.6  96.4/98.5   53.0/52.4  60.4/56   81.0/79.3  132/130    164/158
-//   k_s = 32   45.0/47.7  45.5/47.5  103/104     58.9/57.1     -      93.5/86.7  153/141    210/188
-//   k_s = 48   52.7/53.5  53.9/54.0  112/111     68.9/63.0  78.9/69.8 112/97.3   197/165    293/231
-//   k_s = 64   66.9/63.1  68.1/63.9  132/126     82.2/72.8  101/83    134/120    246/217    376/322
-// up to 128 heads the score workgroups factor short heads themselves, and one head among many that is much longer waits for
-// its one workgroup: 192 heads, 8 of them longer, with (partials of a head) k_s = 16 59.2/58.8 (9), 109/106 (7), 114/112 (11),
-// 62.3/68.2 (17), 112/124 (17), 103/121 (47); k_s = 48 77.3/73.3 (17), 82.6/80.9 (33), 91.3/91.7 (47), 125/130 (17), 169/170 (59);
-// k_s = 64 106/101 (47), 183/179 (59).  128 heads, 8 of them longer, k_s = 16 44.7/55.9 (17), k_s = 48 49.8/59.6 (17).
-constexpr int DIRECT_HEADS = 128;
+// Above DIRECT_HEADS heads sketch_direct_kernel forms and factors S, unless some head may have more partials than direct_most: its one
+// workgroup adds them two by two, about 0.6 us each, where shares are added side by side but cost a launch, more products and, for
+// 48 and 64 rows, the matrix cores' time, which grows with the number of heads.  (Above a head a unit the shares of a head are formed
+// one after the other: 384 heads, 16 of them of 6000 tokens, k_s = 16, 13 partials, 67.5 / 71.5; k_s = 32, 17 partials, 224 / 225.)
+// Up to 128 heads the score workgroups factor short heads themselves (128 x 2048, k_s = 16, 40.2 with shares / 41.6 direct; 48 53.9 /
+// 54.0).  Scores alone on MI355X, us with shares / direct, 192 heads, 8 of them longer, partials of those in brackets:
+//   k_s = 16  (3) 87.1/83.5  (6) 71.9/71.4  (8) 92.3/93.4   (13) 61.2/64.0  (19) 60.9/72.3  (28) 64.4/84.4
+//   k_s = 32  (4) 93.3/89.9  (12) 81.9/81.6 (13) 63.1/62.9  (14) 68.8/69.6  (18) 72.4/74.6  (28) 70.0/76.1
+//   k_s = 48  (6) 86.2/80.6  (14) 87.9/85.2 (18) 92.0/90.7  (19) 73.0/72.7  (23) 86.9/87.8  (28) 78.5/81.3
+//   k_s = 64  (6) 101/91.0   (14) 103/95.1  (18) 107/99.9   (28) 92.4/89.8  (32) 102/101
+// 256 heads, k_s = 16 (6) 67.1/67.4, (7) 69.6/71.8, (13) 54.0/60.9; k_s = 48 (17) 116/107.
+// Where shares lead to score workgroups that factor their heads (score_solves) they save a launch more: 136 to 256 heads of 64 to
+// 4000 tokens (2 or 3) k_s = 16 -2 to +5 us, k_s = 32 0 to +4.5, 48 +1 to +9, 64 +5 to +18; 192 heads, 8 of them longer, k_s = 16
+// (5) 59.6/62.7, (8) 59.3/67.2; k_s = 32 (5) 59.9/66.3; k_s = 48 (5) 67.5/71.9, (7) 62.7/65.0; k_s = 64 (8) 85.3/84.2, (10) 85.6/84.3,
+// (12) 78.7/79.2.
+static long long direct_most(int ks, int heads, int cus, bool in_score) {
+  if (heads <= DIRECT_HEADS) return 0;
+  if (heads > cus) return ks - 4;
+  if (in_score) return ks == 16 ? 2 : ks <= 48 ? 3 : 11;
+  return ks == 16 ? 6 : ks == 32 ? 13 : ks == 48 ? 20 : 36;
+}
 
-// most: partials that a head may have; splits: of a part.
-static SolvePlan plan_of(const SegTable &T, int ks, long long most, int splits) {
+// most: partials that a head may have; splits: of a part; direct_up_to: see direct_most.
+static SolvePlan plan_of(const SegTable &T, int ks, long long most, int splits, long long direct_up_to) {
   SolvePlan p;
   p.parts = 1;
   p.nshares = 0;
@@ -611,7 +624,7 @@ static SolvePlan plan_of(const SegTable &T, int ks, long long most, int splits) 
     p.share_bytes = (size_t)T.nheads * 10 * 1024 * sizeof(double);
     return p;
   }
-  p.direct = T.nheads > DIRECT_HEADS && most <= ks - 4;
+  p.direct = most <= direct_up_to;
   const long long parts = (most + splits - 1) / splits;
   p.parts = parts > SHARE_PARTS_MAX ? SHARE_PARTS_MAX : (int)parts;
   const int P = ks / 16;
@@ -627,15 +640,17 @@ static int longest_head(const SegTable &T) {
   return tiles;
 }
 
-SolvePlan solve_plan(const SegTable &T, int ks, int tiles_per_wg, bool halves) {
-  return plan_of(T, ks, (longest_head(T) + tiles_per_wg - 1) / tiles_per_wg + 1, halves ? SHARE_SPLITS / 2 : SHARE_SPLITS);
+SolvePlan solve_plan(const SegTable &T, int ks, int tiles_per_wg, bool halves, bool in_score, int cus) {
+  return plan_of(T, ks, (longest_head(T) + tiles_per_wg - 1) / tiles_per_wg + 1, halves ? SHARE_SPLITS / 2 : SHARE_SPLITS,
+                 direct_most(ks, T.nheads, cus, in_score));
 }
 
-size_t share_bytes_most(const SegTable &T, int ks, int least_run, long long most_wgs, bool halves) {
+size_t share_bytes_most(const SegTable &T, int ks, int least_run, long long most_wgs, bool halves, int cus) {
   const long long longest = longest_head(T), total = total_tiles(T);
   const long long by_run = (longest + least_run - 1) / least_run, by_wgs = (most_wgs * longest + total - 1) / total;
-  if (plan_of(T, ks, by_run + 1, SHARE_SPLITS).direct) return 0;       // whatever the proportions
-  return plan_of(T, ks, (by_run < by_wgs ? by_run : by_wgs) + 1, halves ? SHARE_SPLITS / 2 : SHARE_SPLITS).share_bytes;
+  const long long always = std::min(direct_most(ks, T.nheads, cus, false), direct_most(ks, T.nheads, cus, true));
+  if (ks > 0 && by_run + 1 <= always) return 0;            // whatever the proportions
+  return plan_of(T, ks, std::min(by_run, by_wgs) + 1, halves ? SHARE_SPLITS / 2 : SHARE_SPLITS, 0).share_bytes;
 }
 
 template <int M>

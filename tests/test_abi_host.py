@@ -218,7 +218,7 @@ def test_two_gram_workgroups_a_unit_where_they_leave_no_more_partials(B, lengths
     assert _accepts(B, p, reqs, nbytes + 256 * len(lengths)) and not _accepts(B, p, reqs, nbytes - 256)
 
 
-@pytest.mark.parametrize("heads,n,ks", [(256, 1000, 48), (129, 5000, 16), (200, 20000, 48)])
+@pytest.mark.parametrize("heads,n,ks", [(256, 1000, 48), (129, 2000, 64), (240, 1000, 48)])
 def test_no_shares_are_asked_for_where_none_are_used(B, heads, n, ks):
     """Above 128 heads whose partials are few at any length up to n: partials of one run or two a unit, or of shorter calls' runs
     and half runs, W^T, histograms and scores."""

@@ -657,11 +657,17 @@ def test_sketched_scores_at_the_edges_of_steps(C, ks, n, L):
     _say("  k_s = %d, %d heads of %d: max rel err %.3g" % (ks, L, n, stats["max_rel"]))
 
 
-# Above 128 heads one workgroup forms and factors S of a head, unless one may have more than k_s - 4 partials (a tile of 64 rows
-# to each Gram workgroup and one more): one to three partials, a step to either side of 12, 25, 41 and 53
+# Above 128 heads one workgroup forms and factors S of a head, unless one may have too many partials: one to three partials; where the
+# score workgroups (two of 4200 tokens or more) leave the factorisation to a kernel of its own a step to either side of 6, 13, 20
+# and 36 (66 tiles in runs of 14 and 13, 6 and 5, 4 and 3, 2 and 1), where they would not of 2 and 3 (4 tiles in runs of 4, 2 and
+# 1) and 11; above 256 heads of k_s - 4 (28)
 @pytest.mark.parametrize("ks,L,n,gram_wgs", [(16, 128, 700, 0), (16, 129, 700, 0), (32, 130, 64, 0), (48, 131, 2047, 0), (64, 129, 513, 0),
                                              (48, 257, 65, 0), (16, 129, 760, 100000), (16, 129, 700, 100000), (32, 129, 1500, 100000),
-                                             (48, 129, 2500, 100000), (64, 129, 3300, 100000)])
+                                             (48, 129, 2500, 100000), (64, 129, 3300, 100000), (16, 129, 4200, 609), (16, 129, 4200, 655),
+                                             (32, 129, 4200, 1419), (32, 129, 4200, 1703), (48, 129, 4200, 2129), (48, 129, 4200, 2838),
+                                             (64, 129, 4200, 4257), (64, 129, 4200, 8514), (16, 129, 250, 129), (16, 129, 250, 258),
+                                             (48, 129, 250, 258), (48, 129, 250, 516), (64, 129, 640, 1290), (64, 129, 641, 1419),
+                                             (32, 257, 1700, 100000), (32, 257, 1800, 100000)])
 def test_sketches_of_many_heads(C, ks, L, n, gram_wgs):
     w = W.config1(DEV, L=L, H=1, n=n)
     w.sketch_dim = ks
