@@ -54,7 +54,7 @@ __device__ __forceinline__ void wave_fence() {
 
 // acc -= (a of lane K of the row) * b in one instruction.  The compiler does not see that the asm reads a across lanes: two
 // instructions have to lie between what writes a and the first of these (chol16_inverse: the update of the next column and
-// its reciprocal).
+// its reciprocal; tests/test_device_code.py looks at what is made of it).
 template <int K>
 __device__ __forceinline__ void sub_bcast16(double &acc, double a, double b) {
   asm volatile("v_fmac_f64_dpp %0, -%1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(a), "v"(b), "n"(K));
