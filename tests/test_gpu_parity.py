@@ -909,6 +909,54 @@ def test_non_finite_keys_poison_their_head_only(C, ks, what):
     assert np.array_equal(kept[:n // 2], np.arange(n // 2))        # all tie: lowest indices win
 
 
+@pytest.mark.parametrize("ks", [16, 32, 48, 64])
+@pytest.mark.parametrize("ridge", [0.0, 1e-3])
+@pytest.mark.parametrize("lengths", [(500, 300, 65), (190, 130, 65)])
+def test_bad_heads_among_many(C, ks, ridge, lengths):
+    """144 heads of three requests, where one workgroup forms and factors S of a head (from runs of 8 tiles, and from halves of
+    them): all-zero keys, equal rows, a NaN, an infinity and an overflow, on both sides of the requests' boundaries.  Each head is flagged
+    for itself, and the others score as they do without them and as the oracle has it."""
+    L, H = 6, 8
+    w = W.config4(DEV, L=L, H=H, n_req=3, n_lo=500, n_hi=500)
+    for r, n in zip(w.requests, lengths):
+        r.k, r.v, r.ratio = r.k[:, :, :n], r.v[:, :, :n], 0.5
+    w.sketch_dim, w.ridge_rel = ks, ridge
+    U.run_and_check(C, w, DEV, heads=[(0, 5, 6), (1, 0, 1), (1, 5, 6), (2, 0, 2), (2, 3, 3), (2, 5, 7)])
+    params, reqs = U.make_call(C, w, DEV)
+    want, status = C.compactor_score(params, reqs)
+    assert int(status.max()) == C.STATUS_OK
+    bad = {(0, 5, 7): "zero", (1, 0, 0): "nan", (1, 5, 7): "equal", (2, 0, 0): "inf", (2, 0, 1): "overflow"}
+    for (b, l, h), what in bad.items():
+        k = w.requests[b].k[l, h]
+        if what == "zero":
+            k.zero_()
+        elif what == "equal":
+            k[:] = k[:1].clone()
+        elif what == "overflow":
+            k *= 1e20
+        else:
+            k[17, 5] = float(what)
+    got, status = C.compactor_score(params, reqs)
+    torch.cuda.synchronize()
+    at = 0
+    for b, n in enumerate(lengths):
+        for l in range(L):
+            for h in range(H):
+                x, y = got[at:at + n], want[at:at + n]
+                st, what = int(status[b * L * H + l * H + h]), bad.get((b, l, h))
+                if what is None:
+                    assert st == C.STATUS_OK and torch.equal(x.view(torch.int32), y.view(torch.int32)), (b, l, h)
+                elif what == "zero":
+                    assert st == C.STATUS_PIVOT and not bool(x.any())
+                elif what == "equal":
+                    # one direction of weight n |k Phi|^2, its square sum spread over the k_s diagonal entries as the ridge
+                    one = 1.0 / (1.0 + ridge / ks)
+                    assert (st == C.STATUS_PIVOT) == (ridge == 0.0) and abs(float(x.double().sum()) - one) < 1e-3 * one
+                else:
+                    assert st == C.STATUS_PIVOT | C.STATUS_NONFINITE and bool(torch.isnan(x).all()), (b, l, h)
+                at += n
+
+
 def test_error_codes_reach_python(C):
     w = W.config1(device=DEV, L=1, H=1, n=64)
     params, reqs = U.make_call(C, w, DEV)
