@@ -82,20 +82,18 @@ int compute_units() {
 // goes on up to 4 tiles, and up to 24 (17 to 32 heads: 16; exact mode: 32) with few heads and 8 tiles a unit or more; a call of other
 // sizes would else sum twice the rows in one accumulator that it used to.
 // compactor_score on MI355X, keys not in the last-level cache, us with one workgroup a unit / folding / two, tiles a unit in
-// brackets.  k_s = 48: 8 heads of 8192 (4) 30.8 / 31.4 / 30.7, 16384 (8) 37.0 / 37.8 / 37.0, 32768 (16) 46.3 / 47.8 / 51.7, 48000 (23)
-// 55.9 / 56.6 / 62.1, 65536 (32) 64.6 / 65.1 / 70.4, 131072 (64) 102 / 102 / 107, 147000 (72) 118.6 / 119.1 / 121.3; 16 of 32768 (32)
-// 63.6 / 64.2 / 68.8; 32 of 8000 (16) 46.9 / 48.1 / 50.3, 32768 (64) 102 / 102 / 106, 47000 (92) 141 / 142 / 146; 64 of 2048 (8) 40.1 / 40.7 /
-// 40.1, 4096 (16) 49.5 / 50.0 / 52.4; 128 of 4096 (32) 70.1 / 70.8 / 74.9, 16384 (128) 188 / 192 / 193; 192 of 8192 (96) 167 / 164 / 167; 256
-// of 1024 (16) 57.3 / 57.8 / 60.3, 2048 (32) 75.3 / 76.0 / 79.5, 4096 (64) 113 / 113 / 117, 8192 (128) 195 / 198 / 199.  Exact mode: 8 of
-// 65536 (32) 88.8 / 89.9 / 99.6, 131072 (64) 127 / 129 / 138; 32 of 18000 (35) 92 / 94 / 97, 57000 (111) 186 / 188 / 191; 256 of 4096 (64)
-// 126 / 126 / 128, 8192 (128) 206 / 211 / 210.
+// brackets.  k_s = 48: 8 heads of 8192 (4) 30.4 / 31.3 / 32.4, 16384 (8) 36.7 / 38.1 / 39.5, 32768 (16) 45.9 / 47.0 / 51.3, 48000 (23)
+// 55.3 / 56.7 / 60.6, 65536 (32) 64.4 / 65.5 / 70.0, 131072 (64) 101 / 103 / 106, 147000 (72) 118 / 118 / 120; 16 of 32768 (32) 63.3 /
+// 64.7 / 68.5; 32 of 8000 (16) 45.9 / 47.7 / 49.7, 32768 (64) 102 / 103 / 105, 47000 (92) 141 / 143.5 / 144.5; 64 of 2048 (8) 39.8 / 40.6 /
+// 41.8, 4096 (16) 48.9 / 49.7 / 52.0; 128 of 4096 (32) 69.5 / 70.5 / 72.7, 16384 (128) 188 / 195 / 192; 192 of 8192 (96) 159 / 157 / 160;
+// 256 of 1024 (16) 48.3 / 49.1 / 55.7, 2048 (32) 66.7 / 67.8 / 74.2, 4096 (64) 104 / 105 / 111, 8192 (128) 187 / 194 / 191.  Exact mode: 8
+// of 65536 (32) 83.2 / 84.6 / 86.7, 131072 (64) 122 / 125 / 125; 32 of 18000 (35) 92.3 / 93.0 / 94.8, 57000 (111) 186 / 189 / 189; 256 of
+// 4096 (64) 125 / 128 / 128, 8192 (128) 209 / 214 / 210.
 // Heads for every unit that end inside runs: one workgroup waits for every partial but two of its run to leave, where two take turns, so
 // two it is unless they leave more.  us with one / two, k_s = 16: 304 of 500 (partials 487 / 304) 41.6 / 33.9, 768 of 200 (768 / 768)
 // 48.7 / 46.8, 1024 of 1000 (1024 / 1024) 129 / 120, 512 of 2048 (512 / 512) 108 / 102; 512 of 300 (512 / 768) 41.5 / 43.7, 256 of 1000
 // (256 / 512) 37.9 / 44.5, 384 of 4096 (638 / 512) 151 / 151, k_s = 48 182 / 183.  Up to 8 tiles a unit they are the same
 // workgroups, 400 of 300 38.4 / 40.0, 1024 of 64 36.1 / 36.5.
-// (Folding then meant two tiles at a time into one sum; a tile at a time into two takes up to 1 % longer: 8 of 131072 104 -> 105, exact
-// mode 128.5 -> 130; 32 of 40000 128.5 -> 131, 152.6 -> 154.4.  And two workgroups had two tiles each under way.)
 // half_wgs: not 0 where two workgroups may share a run of 8 tiles, and how many there are then.
 struct GramPlan { int nwg, tiles_per_wg; GramKind kind; int half_wgs; };
 // Tiles a workgroup: even shares, not below 8 (512 rows), since every partial costs a 40 KB round trip.
@@ -133,9 +131,10 @@ GramPlan gram_plan(const compactor_params_t *p, const SegTable &T, int cus) {
   if (want < 1) want = 1;
   g.tiles_per_wg = (int)((total + want - 1) / want);
   // Not below 8 tiles (512 rows) a workgroup: every partial costs a 40 KB round trip; in small calls 4, where the run is what
-  // takes longest, if the workspace has room for the partials.  compactor_score, us with 4 / 8 tiles: one head of 2048 24.6 / 27.6,
-  // 4096 25.5 / 27.5, 8192 27.0 / 28.3, 8 of 1024 25.7 / 27.6, 2048 26.3 / 28.3, 4096 (512 tiles) 28.2 / 28.8, 8192 32.8 / 31.7; 64 of
-  // 1024 36.0 / 35.4; 136 of 128 31.4 / 35.3, 256 of 64 33.9 / 39.6; exact mode, 8 of 4096 46.5 / 45.6.
+  // takes longest, if the workspace has room for the partials.  compactor_score, us with 4 / 8 tiles: one head of 2048 24.7 / 26.9,
+  // 4096 25.6 / 27.6, 8192 27.1 / 28.3, 8 of 1024 25.0 / 27.3, 2048 26.3 / 27.7, 4096 (512 tiles) 28.1 / 28.8, 64 of 512 30.7 / 31.9, 136 of
+  // 128 31.6 / 35.5, 256 of 64 34.0 / 39.8; beyond 512 tiles the partials cost more, 8 of 8192 32.8 / 31.7, 64 of 1024 36.0 / 35.4, as in
+  // exact mode, 8 of 4096 46.5 / 45.6.
   if (g.tiles_per_wg < 2 * GRAM_HALF_RUN && p->gram_wgs <= 0) g.tiles_per_wg = 2 * GRAM_HALF_RUN;
   const bool halves = !exact && p->gram_wgs <= 0 && total <= 2ll * cus;
   g.kind = !one ? GRAM_TWO : plain || g.tiles_per_wg <= 4 ? GRAM_ONE : halves ? GRAM_HALVES : GRAM_FOLD;

@@ -316,8 +316,8 @@ __device__ __forceinline__ void cursor_seek(const SegTable &T, long long g, Tile
   cursor_head<TILE>(T, c);
 }
 
-// Moves to the next tile.  Past the last tile of the launch the cursor wraps inside the last
-// segment; such positions are never loaded (the callers mask by tile count).
+// Moves to the next tile.  Past the last tile of the launch the cursor wraps inside the last segment: there too kp is a head's
+// first row, of which the Gram kernel loads a piece (used by nobody).
 template <int TILE>
 __device__ __forceinline__ void cursor_next(const SegTable &T, TileCursor &c) {
   if (++c.tile == c.tph) {

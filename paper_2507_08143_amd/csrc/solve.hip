@@ -588,7 +588,7 @@ __global__ __launch_bounds__(EXACT_THREADS) void exact_solve_kernel(
 }
 
 // Longest run of partials a share of its own takes before the head's partials are cut into parts:
-// a batch of eight is in flight at a time, about 1 us each.
+// two batches of four are in flight at a time, about 1 us each.
 // (Where partials may come in halves, half as many: the halves are what is loaded.)
 constexpr int SHARE_SPLITS = 64, SHARE_PARTS_MAX = 8;
 

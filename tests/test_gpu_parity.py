@@ -428,10 +428,9 @@ def test_ragged_token_counts(C, n):
 
 @pytest.mark.parametrize("gram_wgs", [1, 2, 5, 12])
 def test_gram_partitions_that_cross_heads(C, gram_wgs):
-    """The Gram kernel deals 64-row tiles out evenly, across head boundaries, here to pairs of wave groups that halve
-    a workgroup's run.  One workgroup for six heads of 11 tiles crosses five boundaries (the halves meet where a
-    head ends, the other partials are written mid-run); 5 workgroups of 14 tiles cross one or two, the halves of
-    7 tiles share a head or not; 12 cross none or one.  All must match the oracle."""
+    """The Gram kernel deals 64-row tiles out evenly, across head boundaries.  One workgroup for six heads of 11 tiles
+    crosses five boundaries (the first partial waits in LDS, the others but the last are written mid-run, after even
+    and after odd tiles); 5 workgroups of 14 tiles cross one or two; 12 cross none or one.  All must match the oracle."""
     _say("Gram partition with %d workgroup(s) over 6 heads of 700 tokens" % gram_wgs)
     w = W.config2(DEV, L=2, H=3, n=700)
     st, _ = U.run_and_check(C, w, DEV, tune={"gram_wgs": gram_wgs})
@@ -592,9 +591,9 @@ def test_exact_mode_around_the_limit_of_the_shares(C, L):
     U.run_and_check(C, w, DEV, heads=[(0, 0, 0), (0, L // 2, 0), (0, L - 1, 0)])
 
 
-# Score runs: one workgroup a compute unit as long as runs stay even and short.  Gram: a pair a unit up to 8 tiles each, one
-# plain workgroup up to 24 (17 to 32 heads: 16; exact mode: 32), pairs that fold up to 72 (exact mode: 112), two plain
-# ones beyond: a step to either side of the limits, a short head, blended scores
+# Score runs: one workgroup a compute unit as long as runs stay even and short.  Gram: one workgroup a unit, with runs of half the
+# length up to 2 tiles a unit, summed tile by tile up to 8, as they go on up to 24 (17 to 32 heads: 16; exact mode: 32), tile by
+# tile up to 112, two a unit beyond: a step to either side of the limits, a short head, blended scores
 @pytest.mark.parametrize("H,n,exact,blend", [(1, 130, False, False), (3, 257, False, True), (8, 8191, False, True),
                                              (2, 131071, False, False), (2, 131073, False, False),
                                              (8, 49089, False, False), (8, 49153, False, False),
