@@ -143,6 +143,36 @@ GramPlan gram_plan(const compactor_params_t *p, const SegTable &T, int cus) {
   return g;
 }
 
+long long key_rows(const SegTable &T) {
+  long long rows = 0;
+  for (int i = 0; i < T.nseg; ++i) rows += (long long)T.s[i].n * T.s[i].head_count;
+  return rows;
+}
+
+// Sketched mode, few heads: one workgroup per unit, which then factors its head itself (score_solves), as long as
+// no run is much longer than the even share of a unit; not below 256 tokens, where half the run changes nothing any
+// more.  compactor_score on MI355X, us with runs of 128 / 256 / 384 / 512 / 768 / 1024 tokens, k_s = 48: one head of 8192
+// 30.2 / 31.4 / 32.8 / 33.4 / 35.8 / 38.0, 8 heads of 4096 32.3 / 32.7 / 33.8 / 34.5 / 36.6 / 38.4, 8192 37.9 / 36.3 / 36.6 /
+// 37.5 / 39.5 / 41.1, 16384 48.1 / 45.0 / 47.3 / 42.3 / 44.7 / 46.4, 32768 63.4 / 60.2 / 62.5 / 55.7 / 57.7 / 53.4.  Against
+// the search of score_tokens_for, whose workgroups get W^T from a kernel of its own, with k_s = 16, 48 and 64: 8 heads of 40007
+// 50.3 / 54.7, 60.0 / 65.0, 69.6 / 74.5, 65536 65.3 / 67.5, 76.0 / 79.1, 87.9 / 87.5, 100000 89.6 / 92.4, 99.3 / 102.3, 112.3 / 112.3,
+// 32 heads of 30000 99.6 / 99.2, 111.0 / 110.7, 125.4 / 119.5.
+// The same runs where the workspace has no room for the shares (the sums of a blend are parted as the runs are, and its
+// scores are the same bits either way): the factorisation then costs 15 to 27 us more whatever the runs.  us without room with
+// these runs / the best of 512 to 4096 tokens, k_s = 48: 8 heads of 8192 55.7 / 57.2, 16384 68.8 / 68.8, 32768 79.6 / 79.5,
+// 40007 86.6 / 86.4, 65536 99.8 / 99.7, 100000 125.4 / 126.5, 32 of 8192 70.4 / 70.4, 30000 128.8 / 128.2, 128 of 4096 90.7 /
+// 90.4.
+// 0: no such runs.
+int unit_run(const compactor_params_t *p, const SegTable &T, int cus) {
+  if (p->sketch_dim == 0 || T.nheads > cus) return 0;
+  const int most = p->sketch_dim <= 48 ? SCORE_BURST : 1536;
+  const long long rows = key_rows(T), even = (rows + cus - 1) / cus;
+  int run = even > most ? most + 1 : (int)(even + SCORE_STEP - 1) / SCORE_STEP * SCORE_STEP;
+  if (run < 256) run = 256;
+  while (run <= most && total_blocks(T, run, SCORE_STEP, false) > cus) run += SCORE_STEP;
+  return run <= most && (run == 256 || (run - 256ll) * cus <= rows) ? run : 0;
+}
+
 // Score: workgroups of equal token runs inside a head, 2 (exact mode: 3) per compute unit at a time.  A launch
 // of W workgroups takes ceil(W / slots) rounds; the run length is chosen to keep the last
 // round full and the per-workgroup fixed cost (staging W^T, about 32 KB) small.
@@ -158,29 +188,8 @@ int score_tokens_for(const compactor_params_t *p, const SegTable &T, int cus) {
   // heads of 50001 196 / 194 / 202 / 200 / 233 and 189, 256 of 16384 415 / 405 / 397 / 414 / 408 and 397.
   const int cap = p->sketch_dim == 0 ? 16384 : SCORE_BURST;
   const int slots = (p->sketch_dim == 0 ? 3 : 2) * cus;
-  long long rows = 0;
-  for (int i = 0; i < T.nseg; ++i) rows += (long long)T.s[i].n * T.s[i].head_count;
-  // Sketched mode, few heads: one workgroup per unit, which then factors its head itself (score_solves), as long as
-  // no run is much longer than the even share of a unit; not below 256 tokens, where half the run changes nothing any
-  // more.  compactor_score on MI355X, us with runs of 128 / 256 / 384 / 512 / 768 / 1024 tokens, k_s = 48: one head of 8192
-  // 30.2 / 31.4 / 32.8 / 33.4 / 35.8 / 38.0, 8 heads of 4096 32.3 / 32.7 / 33.8 / 34.5 / 36.6 / 38.4, 8192 37.9 / 36.3 / 36.6 /
-  // 37.5 / 39.5 / 41.1, 16384 48.1 / 45.0 / 47.3 / 42.3 / 44.7 / 46.4, 32768 63.4 / 60.2 / 62.5 / 55.7 / 57.7 / 53.4.  Against
-  // the search below, whose workgroups get W^T from a kernel of its own, with k_s = 16, 48 and 64: 8 heads of 40007 50.3 / 54.7,
-  // 60.0 / 65.0, 69.6 / 74.5, 65536 65.3 / 67.5, 76.0 / 79.1, 87.9 / 87.5, 100000 89.6 / 92.4, 99.3 / 102.3, 112.3 / 112.3,
-  // 32 heads of 30000 99.6 / 99.2, 111.0 / 110.7, 125.4 / 119.5.
-  // The same runs where the workspace has no room for the shares (the sums of a blend are parted as the runs are, and its
-  // scores are the same bits either way): the factorisation then costs 15 to 27 us more whatever the runs.  us without room with
-  // these runs / the best of 512 to 4096 tokens, k_s = 48: 8 heads of 8192 55.7 / 57.2, 16384 68.8 / 68.8, 32768 79.6 / 79.5,
-  // 40007 86.6 / 86.4, 65536 99.8 / 99.7, 100000 125.4 / 126.5, 32 of 8192 70.4 / 70.4, 30000 128.8 / 128.2, 128 of 4096 90.7 /
-  // 90.4.
-  if (p->sketch_dim > 0 && T.nheads <= cus) {
-    const int most = p->sketch_dim <= 48 ? SCORE_BURST : 1536;
-    const long long even = (rows + cus - 1) / cus;
-    int run = even > most ? most + 1 : (int)(even + SCORE_STEP - 1) / SCORE_STEP * SCORE_STEP;
-    if (run < 256) run = 256;
-    while (run <= most && total_blocks(T, run, SCORE_STEP, false) > cus) run += SCORE_STEP;
-    if (run <= most && (run == 256 || (run - 256ll) * cus <= rows)) return run;
-  }
+  const long long rows = key_rows(T);
+  if (const int run = unit_run(p, T, cus)) return run;
   // A call of few heads that gives a compute unit less than 1024 tokens is all latency: one workgroup per
   // unit.  Whole call on MI355X, exact mode, us with runs of 128 / 256 / 512 / 768 / 1024 tokens, 8 heads of 8192
   // 80.0 / 79.8 / 82.1 / 86.5 / 90.3.
@@ -200,8 +209,9 @@ int score_tokens_for(const compactor_params_t *p, const SegTable &T, int cus) {
 }
 
 SolvePlan solve_plan_for(const compactor_params_t *p, const SegTable &T, const GramPlan &gp, int cus) {
-  const bool in_score = p->sketch_dim > 0 && T.nheads > DIRECT_HEADS && T.nheads <= cus &&
-                        score_solves(T, p->sketch_dim, score_tokens_for(p, T, cus), cus);
+  bool in_score = false;
+  if (p->sketch_dim > 0 && T.nheads > DIRECT_HEADS && T.nheads <= cus)
+    in_score = p->score_tokens > 0 ? score_solves(T, p->sketch_dim, score_tokens_for(p, T, cus), cus) : unit_run(p, T, cus) > 0;
   return solve_plan(T, p->sketch_dim, gp.tiles_per_wg, gp.half_wgs > 0, in_score, cus);
 }
 
@@ -231,15 +241,14 @@ size_t partial_bytes(const SegTable &T, long long wgs) {
 // Heads up to which there are shares (see below).
 int share_heads(int ks, int cus) { return ks > 0 ? cus : 3 * cus / 8; }
 
-GroupBytes group_bytes_needed(const compactor_params_t *p, const SegTable &T, bool need_scores) {
+// demand: only what total() counts is wanted, no plan of the factorisation.
+GroupBytes group_bytes_needed(const compactor_params_t *p, const SegTable &T, bool need_scores, bool demand = false) {
   const int ks = p->sketch_dim;
-  long long rows = 0;
-  for (int i = 0; i < T.nseg; ++i) rows += (long long)T.s[i].n * T.s[i].head_count;
   const int m = ks > 0 ? ks : D;
   const int cus = compute_units();
   GroupBytes g;
   g.gram = gram_plan(p, T, cus);
-  g.solve = solve_plan_for(p, T, g.gram, cus);
+  g.solve = demand ? SolvePlan{} : solve_plan_for(p, T, g.gram, cus);
   g.partials = partial_bytes(T, g.gram.nwg);
   // Many workgroups per head form S = Phi^T G Phi (exact mode: G) only where the heads alone do not fill
   // the chip.  Factorisation stage on MI355X, us with / without shares, n = 2048:
@@ -252,7 +261,7 @@ GroupBytes group_bytes_needed(const compactor_params_t *p, const SegTable &T, bo
   // of n = 131072, which brings 64 partials: 27 against 210.  At 2048 heads and more k_s = 32 and 48 would
   // be 4 to 9 % of this stage faster with shares, for 60 KB of scratch a head: the stage is 2 % of such calls.
   // (Figures of sketched mode from before sketch_direct_kernel, which takes most calls of more than 128 heads now, without shares.)
-  g.shares = T.nheads <= share_heads(ks, cus) && !g.solve.direct ? align_up(g.solve.share_bytes) : 0;
+  g.shares = !demand && T.nheads <= share_heads(ks, cus) && !g.solve.direct ? align_up(g.solve.share_bytes) : 0;
   g.wt = align_up((size_t)T.nheads * W_TERMS * m * D * sizeof(uint16_t));
   g.hist1 = align_up((size_t)T.nheads * HIST1_BINS * sizeof(int));
   g.sel = select_needs_pools(T) ? align_up((size_t)select_scratch(T).ints() * sizeof(int)) : 0;
@@ -261,7 +270,7 @@ GroupBytes group_bytes_needed(const compactor_params_t *p, const SegTable &T, bo
   if (blend_wanted(T))
     g.bstat = align_up((size_t)total_blocks(T, score_tokens_for(p, T, compute_units()), SCORE_STEP, false) *
                        4 * sizeof(double));
-  g.scores = need_scores ? align_up((size_t)rows * sizeof(float)) : 0;
+  g.scores = need_scores ? align_up((size_t)key_rows(T) * sizeof(float)) : 0;
   g.halves = g.gram.half_wgs > 0 && (g.shares > 0 || g.solve.direct) ? partial_bytes(T, g.gram.half_wgs) : 0;
   return g;
 }
@@ -282,10 +291,8 @@ size_t bytes_asked(const compactor_params_t *p, const SegTable &T, bool need_sco
   };
   size_t rest = g.total() - g.partials;
   if (g.bstat > 0) {
-    long long rows = 0;
-    for (int i = 0; i < T.nseg; ++i) rows += (long long)T.s[i].n * T.s[i].head_count;
     // runs are of 1024 tokens or more, or one a unit
-    rest += std::max(g.bstat, align_up((size_t)(rows / 1024 + cus + T.nheads) * 4 * sizeof(double))) - g.bstat;
+    rest += std::max(g.bstat, align_up((size_t)(key_rows(T) / 1024 + cus + T.nheads) * 4 * sizeof(double))) - g.bstat;
   }
   size_t asked = std::max(g.with_halves(), rest + shares(most_wgs, false) + partial_bytes(T, runs(least_run, most_wgs)));
   if (p->sketch_dim > 0 && p->gram_wgs <= 0 && T.nheads <= 2 * cus)       // (more heads are more tiles)
@@ -363,7 +370,7 @@ int workspace_need(const compactor_params_t *p, const compactor_request_t *reqs,
   const int rc = for_each_group(p, reqs, nreq, group_rows_of(p), local_scores,
                                 [&](const SegTable &T, long long) {
                                   const size_t t = wanted ? bytes_asked(p, T, local_scores)
-                                                          : group_bytes_needed(p, T, local_scores).total();
+                                                          : group_bytes_needed(p, T, local_scores, true).total();
                                   if (t > need) need = t;
                                   return COMPACTOR_OK;
                                 });
